@@ -469,7 +469,7 @@ int spmm_split_colblocks(const int32_t* d_rowptr, const int32_t* d_colidx, const
  * order (stable), so the result is unique: bit-exact.  Returns SAGNN_EFORMAT if a column index
  * is outside [0,n) (outputs are then unspecified, nothing faults).  One-time set-up step;
  * synchronises the stream once.  d_ws: scratch of spmm_transpose_workspace_bytes() bytes
- * (about 16 bytes per stored entry).
+ * (about 17 bytes per stored entry).
  */
 int spmm_transpose_workspace_bytes(int64_t nnz, size_t* bytes);
 int spmm_csr_transpose(const int32_t* d_rowptr, const int32_t* d_colidx, const float* d_val,

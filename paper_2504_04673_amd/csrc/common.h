@@ -259,22 +259,27 @@ int tile_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float* 
 int tile_launch(const TilePlan& p, uint64_t generation, char* base, const TileWsLayout& L, const float* B,
                 int64_t ldb, uint32_t kmax, int32_t f, int64_t m, float* C, int64_t ldc, hipStream_t s);
 
-// Stable least-significant-digit radix sort of (key, payload) pairs on the device (stages.hip),
-// 8 bits per pass over key bits [0, bits).  With pay_in == NULL the payload is the index of the
+// Stable least-significant-digit radix sort of (key, payload) pairs on the device (radix.hip),
+// over key bits [0, bits).  With pay_in == NULL the payload is the index of the
 // pair.  The sorted pairs end up in w.keys[*result], w.pay[*result].  A workspace carved for n
-// pairs serves any smaller count.
+// pairs serves any smaller count.  With limit > 0, err[0] (device, cleared by the caller) is set to 1 if
+// some key is >= limit.
 struct RadixWs {
   uint32_t *keys[2], *pay[2];
-  int32_t* counts;     // [256][ntiles + 1]
-  int32_t* tilesum;    // [256][nscan + 1]
-  int64_t* digit_off;  // [257]
-  int64_t ntiles, nscan;
+  int32_t* counts;     // [digits][tiles]
+  int32_t* totals;     // [digits]
   int64_t cap;         // pairs the workspace was carved for
   size_t bytes;
 };
 RadixWs carve_radix(void* base, int64_t n);   // base == NULL: sizes only
 int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* pay_in, int64_t n, int bits, const RadixWs& w,
-                     hipStream_t s, int* result);
+                     hipStream_t s, int* result, int64_t limit = 0, int32_t* err = nullptr);
+// rowptr[c] = number of the cnt sorted keys below c, c in [0, n]
+int launch_sorted_rowptr(const uint32_t* keys, int64_t cnt, int64_t n, int32_t* rowptr, hipStream_t s);
+// the transpose without its argument checks and error read-back; ws: transpose_ws_bytes(nnz)
+size_t transpose_ws_bytes(int64_t nnz);
+int launch_transpose(const int32_t* rowptr, const int32_t* colidx, const float* val, int64_t m, int64_t n, int64_t nnz,
+                     int32_t* rowptr_t, int32_t* colidx_t, float* val_t, void* ws, int32_t* d_err, hipStream_t s);
 
 int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_t transW,
                 int64_t m, int32_t kdim, int32_t nout, int32_t prec, int32_t act,

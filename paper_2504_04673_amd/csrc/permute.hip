@@ -26,11 +26,6 @@ inline dim3 grid_for(int64_t items) {
   return dim3((unsigned)b);
 }
 
-__global__ __launch_bounds__(kThreads) void iota_kernel(int32_t* __restrict__ a, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) a[i] = (int32_t)i;
-}
-
 // out[i] = map[in[i]]; an id outside [0, n) sets err[0] and maps to 0
 __global__ __launch_bounds__(kThreads) void relabel_kernel(const int32_t* __restrict__ in, int64_t cnt,
                                                            const int32_t* __restrict__ map, int64_t n,
@@ -48,13 +43,14 @@ __global__ __launch_bounds__(kThreads) void relabel_kernel(const int32_t* __rest
   }
 }
 
-// inv[perm[i]] = i
-__global__ __launch_bounds__(kThreads) void invert_kernel(const int32_t* __restrict__ perm, int64_t n,
-                                                          int32_t* __restrict__ inv) {
+// perm[i] = order[i], inv[order[i]] = i
+__global__ __launch_bounds__(kThreads) void order_kernel(const uint32_t* __restrict__ order, int64_t n,
+                                                         int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
-    const int32_t p = perm[i];
-    if (p >= 0 && p < n) inv[p] = (int32_t)i;
+    const int32_t p = (int32_t)order[i];   // a payload of the sort: always in [0, n)
+    perm[i] = p;
+    inv[p] = (int32_t)i;
   }
 }
 
@@ -83,9 +79,8 @@ struct PermuteWs {
 };
 
 int carve_permute(void* base, int64_t n, int64_t nnz, PermuteWs* w) {
-  size_t tb = 0;
-  int rc = spmm_transpose_workspace_bytes(nnz, &tb);
-  if (rc != SAGNN_OK) return rc;
+  if (nnz < 0 || nnz > 0x7FFFFFFFll) return SAGNN_EINVAL;
+  const size_t tb = transpose_ws_bytes(nnz);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = base ? static_cast<char*>(base) + off : nullptr;
@@ -94,7 +89,7 @@ int carve_permute(void* base, int64_t n, int64_t nnz, PermuteWs* w) {
   };
   const size_t e = (size_t)(nnz > 0 ? nnz : 1);
   w->ci_a = reinterpret_cast<int32_t*>(take(4 * e));
-  w->rp_b = reinterpret_cast<int32_t*>(take(4 * (size_t)(n + 1)));
+  w->rp_b = reinterpret_cast<int32_t*>(take(4 * (size_t)(n + 2)));
   w->ci_b = reinterpret_cast<int32_t*>(take(4 * e));
   w->va_b = reinterpret_cast<float*>(take(4 * e));
   w->seen = reinterpret_cast<int32_t*>(take(4 * (size_t)(n > 0 ? n : 1)));
@@ -134,21 +129,26 @@ SAGNN_EXPORT int spmm_perm_from_labels(const int32_t* d_labels, int64_t n, int32
   if (n_parts > 1024 || (int64_t)n_parts > (n > 0 ? n : 1)) return SAGNN_EINVAL;
   for (int32_t q = 0; q <= n_parts; ++q) h_part_off[q] = 0;
   if (n == 0) return SAGNN_OK;
-  // pattern with one entry per row: rowptr = 0..n, column id = label, value unused
-  hipLaunchKernelGGL(iota_kernel, grid_for(n + 1), dim3(kThreads), 0, s, w.ci_a, n + 1);
+  // stable sort of the vertices by label; the part offsets come from the sorted labels.  The error flag lies
+  // behind the offsets so that one copy brings both to the host.
+  int32_t* d_off = w.rp_b;
+  int32_t* d_err = w.rp_b + n_parts + 1;
+  SAGNN_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
+  const RadixWs rw = carve_radix(w.tws, n);
+  int bits = 1;
+  while ((1 << bits) < n_parts) ++bits;
+  int res = 0;
+  rc = radix_sort_pairs(reinterpret_cast<const uint32_t*>(d_labels), nullptr, n, bits, rw, s, &res, n_parts, d_err);
+  if (rc != SAGNN_OK) return rc;
+  rc = launch_sorted_rowptr(rw.keys[res], n, n_parts, d_off, s);
+  if (rc != SAGNN_OK) return rc;
+  hipLaunchKernelGGL(order_kernel, grid_for(n), dim3(kThreads), 0, s, rw.pay[res], n, d_perm, d_inv);
   SAGNN_LAUNCH_CHECK();
-  // transpose: row q of the result lists the vertices with label q, ascending = the new order
-  rc = spmm_csr_transpose(w.ci_a, d_labels, reinterpret_cast<const float*>(d_labels), n, n_parts, n,
-                          w.rp_b, d_perm, w.va_b, w.tws, w.tws_bytes, stream);
-  if (rc != SAGNN_OK) return rc;   // SAGNN_EFORMAT: a label outside [0, n_parts)
-  hipLaunchKernelGGL(invert_kernel, grid_for(n), dim3(kThreads), 0, s, d_perm, n, d_inv);
-  SAGNN_LAUNCH_CHECK();
-  // part offsets -> host (32-bit on the device, widened here)
-  int32_t stack_off[1025];
-  SAGNN_HIP(hipMemcpyAsync(stack_off, w.rp_b, sizeof(int32_t) * (size_t)(n_parts + 1),
-                           hipMemcpyDeviceToHost, s));
+  int32_t h[1026];
+  SAGNN_HIP(hipMemcpyAsync(h, d_off, sizeof(int32_t) * (size_t)(n_parts + 2), hipMemcpyDeviceToHost, s));
   SAGNN_HIP(hipStreamSynchronize(s));
-  for (int32_t q = 0; q <= n_parts; ++q) h_part_off[q] = stack_off[q];
+  if (h[n_parts + 1]) return SAGNN_EFORMAT;   // a label outside [0, n_parts)
+  for (int32_t q = 0; q <= n_parts; ++q) h_part_off[q] = h[q];
   return SAGNN_OK;
 }
 
@@ -175,17 +175,12 @@ SAGNN_EXPORT int spmm_csr_permute_symmetric(const int32_t* d_rowptr, const int32
     hipLaunchKernelGGL(check_perm_kernel, grid_for(n), dim3(kThreads), 0, s, d_inv, n, w.seen, w.err);
     SAGNN_LAUNCH_CHECK();
   }
-  int32_t h_err[4] = {0, 0, 0, 0};
-  SAGNN_HIP(hipMemcpyAsync(h_err, w.err, sizeof(h_err), hipMemcpyDeviceToHost, s));
-  SAGNN_HIP(hipStreamSynchronize(s));
-  if (h_err[1]) return SAGNN_EFORMAT;          // d_inv is not a permutation of [0, n)
   if (nnz > 0) {
     hipLaunchKernelGGL(relabel_kernel, grid_for(nnz), dim3(kThreads), 0, s, d_colidx, nnz, d_inv, n,
                        w.ci_a, w.err);
     SAGNN_LAUNCH_CHECK();
   }
-  rc = spmm_csr_transpose(d_rowptr, w.ci_a, d_val, n, n, nnz, w.rp_b, w.ci_b, w.va_b, w.tws,
-                          w.tws_bytes, stream);
+  rc = launch_transpose(d_rowptr, w.ci_a, d_val, n, n, nnz, w.rp_b, w.ci_b, w.va_b, w.tws, w.err + 2, s);
   if (rc != SAGNN_OK) return rc;
   if (nnz > 0) {
     // ci_b holds old row ids (always in range); relabel them in place into ci_a
@@ -193,11 +188,13 @@ SAGNN_EXPORT int spmm_csr_permute_symmetric(const int32_t* d_rowptr, const int32
                        w.ci_a, w.err);
     SAGNN_LAUNCH_CHECK();
   }
-  rc = spmm_csr_transpose(w.rp_b, w.ci_a, w.va_b, n, n, nnz, d_rowptr_p, d_colidx_p, d_val_p, w.tws,
-                          w.tws_bytes, stream);
+  rc = launch_transpose(w.rp_b, w.ci_a, w.va_b, n, n, nnz, d_rowptr_p, d_colidx_p, d_val_p, w.tws, w.err + 3, s);
   if (rc != SAGNN_OK) return rc;
+  // err: a column index outside [0, n), d_inv not a permutation of [0, n) (then also the last two perhaps: ids it
+  // maps outside [0, n) are caught where they are sorted)
+  int32_t h_err[4] = {0, 0, 0, 0};
   SAGNN_HIP(hipMemcpyAsync(h_err, w.err, sizeof(h_err), hipMemcpyDeviceToHost, s));
   SAGNN_HIP(hipStreamSynchronize(s));
-  if (h_err[0]) return SAGNN_EFORMAT;          // a column index outside [0, n)
+  if (h_err[0] || h_err[1] || h_err[2] || h_err[3]) return SAGNN_EFORMAT;
   return SAGNN_OK;
 }

@@ -1,0 +1,458 @@
+// Stable radix sort on the device and the CSR transpose built on it (Sec. 2.1 / Sec. 4.1: the forward
+// pass multiplies by A^T, the backward pass by A; a directed graph needs both orientations).
+//
+// Least-significant digit first, at most 8 bits per pass (the key bits are spread evenly over the
+// passes), three launches per pass over tiles of consecutive pairs:
+//   count    digit histogram of a tile in LDS -> counts[digit][tile]
+//   scan     one workgroup per digit: exclusive scan along the tiles, digit total
+//   scatter  ranks inside the tile by ballots (stable), the tile is sorted by digit in LDS and then
+//            written out in that order, so that neighbouring lanes store to neighbouring places
+// What bounds it: HBM.  A pass reads and writes every key and payload word once and reads the keys once
+// more for the counts.  The earlier form (one wavefront per tile, a serial loop over the distinct digits
+// of 64 keys, stores in entry order) took 14.4 ms for seven passes over 21 M pairs, almost all of it in
+// that loop and in scattered stores.
+//
+// The transpose sorts the entries by column with their row and value as payload, so no entry index is
+// looked up afterwards: the first pass reads the caller's arrays (a tile's rows come from the slice of
+// rowptr that covers it), the last pass writes the caller's outputs.  Stability makes the entries of a
+// transposed row come out in the order of the rows they came from, and keeps duplicates in stored order.
+#include <algorithm>
+
+#include "common.h"
+
+namespace sagnn {
+namespace {
+
+constexpr int kMaxBins = 256;
+// Tiles of at least 8192 pairs keep the runs of one digit long enough for whole-line stores; fewer pairs
+// are cut into smaller tiles while that leaves CUs without work.
+constexpr int64_t kTileSmallMax = 1 << 18;   // up to here: tiles of 1024 pairs
+constexpr int64_t kTileMidMax = 1 << 22;     // up to here: tiles of 2048 pairs
+
+inline int radix_tile(int64_t n) { return n <= kTileSmallMax ? 1024 : (n <= kTileMidMax ? 2048 : 8192); }
+
+struct PassArgs {
+  const uint32_t* keys_in;
+  const uint32_t* p0_in;      // first payload word (SRC_ARRAYS)
+  const uint32_t* p1_in;      // second payload word (NP == 2)
+  uint32_t *keys_out, *p0_out, *p1_out;
+  int64_t n, ntiles;
+  int32_t shift, bits;
+  int32_t* counts;            // [bins][ntiles]
+  int32_t* totals;            // [bins]
+  const int32_t* rowptr;      // SRC_ROWS: the first payload word is the row of the entry
+  int64_t m;
+};
+
+enum Src { SRC_ARRAYS = 0, SRC_INDEX = 1, SRC_ROWS = 2 };
+
+// limit > 0: err[0] = 1 if some key is >= limit
+template <int THREADS, int KPT>
+__global__ __launch_bounds__(THREADS) void radix_count_kernel(const uint32_t* __restrict__ keys, int64_t n,
+                                                              int64_t ntiles, int32_t shift, int32_t bits,
+                                                              int32_t* __restrict__ counts, uint32_t limit,
+                                                              int32_t* __restrict__ err) {
+  __shared__ int32_t hist[kMaxBins];
+  const int bins = 1 << bits;
+  for (int i = threadIdx.x; i < bins; i += THREADS) hist[i] = 0;
+  const int64_t e0 = (int64_t)blockIdx.x * (THREADS * KPT) + threadIdx.x;
+  uint32_t key[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) key[j] = e0 + j * THREADS < n ? keys[e0 + j * THREADS] : 0u;
+  __syncthreads();
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < KPT; ++j)
+    if (e0 + j * THREADS < n) {
+      bad |= limit != 0u && key[j] >= limit;
+      atomicAdd(&hist[(key[j] >> shift) & (uint32_t)(bins - 1)], 1);
+    }
+  if (bad) err[0] = 1;
+  __syncthreads();
+  for (int i = threadIdx.x; i < bins; i += THREADS) counts[(int64_t)i * ntiles + blockIdx.x] = hist[i];
+}
+
+// exclusive scan of one value per thread over the workgroup; *total = sum
+template <int THREADS>
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t* wsum, int32_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t t = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  int32_t before = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) {
+    if (w < wave) before += wsum[w];
+    tot += wsum[w];
+  }
+  __syncthreads();
+  *total = tot;
+  return before + inc - v;
+}
+
+__global__ __launch_bounds__(1024) void radix_scan_kernel(int32_t* __restrict__ counts, int64_t ntiles,
+                                                          int32_t* __restrict__ totals) {
+  __shared__ int32_t wsum[16];
+  int32_t* __restrict__ c = counts + (int64_t)blockIdx.x * ntiles;
+  int32_t carry = 0;
+  for (int64_t base = 0; base < ntiles; base += 4096) {
+    const int64_t i = base + (int64_t)threadIdx.x * 4;
+    int32_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = i + q < ntiles ? c[i + q] : 0;
+    int32_t tot;
+    int32_t ex = carry + block_scan<1024>(v[0] + v[1] + v[2] + v[3], wsum, &tot);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (i + q < ntiles) c[i + q] = ex;
+      ex += v[q];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// Largest r in [0, m) with rowptr[r] <= e, found by one wavefront (64 probes per step).
+__device__ __forceinline__ int64_t wave_find_row(const int32_t* __restrict__ rowptr, int64_t m, int64_t e) {
+  const int lane = threadIdx.x & 63;
+  int64_t lo = 0, hi = m;            // the answer lies in [lo, hi)
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t p = lo + (int64_t)(lane + 1) * step;      // probes ascend with the lane
+    const bool below = p < hi && (int64_t)rowptr[p] <= e;
+    const int cnt = __popcll(__ballot(below));              // a prefix of the lanes (rowptr is monotone)
+    const int64_t nlo = lo + (int64_t)cnt * step;
+    hi = nlo + step < hi ? nlo + step : hi;
+    lo = nlo;
+  }
+  return lo;
+}
+
+template <int THREADS, int KPT, int NP, int SRC>
+__global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a) {
+  constexpr int TILE = THREADS * KPT, WAVES = THREADS / 64;
+  __shared__ uint32_t stage[TILE];
+  __shared__ int32_t hist[WAVES][kMaxBins];
+  __shared__ int32_t gbase[kMaxBins];      // output position of a digit's first pair, minus its staged position
+  __shared__ int32_t wsum[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int bins = 1 << a.bits;
+  const int64_t tile0 = (int64_t)blockIdx.x * TILE;
+  const int cnt = (int)(a.n - tile0 < TILE ? a.n - tile0 : TILE);
+  for (int i = tid; i < WAVES * kMaxBins; i += THREADS) (&hist[0][0])[i] = 0;
+  // a wavefront owns 64 * KPT consecutive pairs
+  const int seg = wave * 64 * KPT + lane;
+  uint32_t key[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) key[j] = seg + j * 64 < cnt ? a.keys_in[tile0 + seg + j * 64] : 0u;
+  __syncthreads();
+
+  // rank of every pair among the wavefront's earlier pairs of its digit
+  int32_t pos[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const bool act = seg + j * 64 < cnt;
+    const uint32_t d = (key[j] >> a.shift) & (uint32_t)(bins - 1);
+    uint64_t peers = __ballot(act);
+    for (int b = 0; b < a.bits; ++b) {
+      const bool one = (d >> b) & 1u;
+      const uint64_t ones = __ballot(one);
+      peers &= one ? ones : ~ones;
+    }
+    const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0));
+    // (the LDS operations of one wavefront are carried out in order: read, then the first peer's update)
+    const int32_t have = __hip_atomic_load(&hist[wave][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    pos[j] = have + below;
+    if (act && below == 0)
+      __hip_atomic_store(&hist[wave][d], have + __popcll(peers), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  // digits -> first staged position; hist becomes the staged position of a wavefront's first pair of a digit
+  {
+    const int d = tid;
+    int32_t mine = 0;
+    if (d < bins) {
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) mine += hist[w][d];
+    }
+    int32_t tot, dtot;
+    const int32_t start = block_scan<THREADS>(mine, wsum, &tot);
+    const int32_t before = block_scan<THREADS>(d < bins ? a.totals[d] : 0, wsum, &dtot);
+    if (d < bins) {
+      gbase[d] = before + a.counts[(int64_t)d * a.ntiles + blockIdx.x] - start;
+      int32_t run = start;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {
+        const int32_t t = hist[w][d];
+        hist[w][d] = run;
+        run += t;
+      }
+    }
+  }
+  static_assert(THREADS >= kMaxBins, "one thread per digit");
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) pos[j] += hist[wave][(key[j] >> a.shift) & (uint32_t)(bins - 1)];
+
+  uint32_t row[SRC == SRC_ROWS ? KPT : 1];
+  if constexpr (SRC == SRC_ROWS) {
+    // rows of the tile's entries: the slice of rowptr that covers the tile in LDS, a binary search per entry
+    __shared__ int64_t ends[2];
+    if (wave < 2) {
+      const int64_t r = wave_find_row(a.rowptr, a.m, wave == 0 ? tile0 : tile0 + cnt - 1);
+      if (lane == 0) ends[wave] = r;
+    }
+    __syncthreads();
+    const int64_t r_lo = ends[0], r_hi = ends[1];
+    const int64_t nstart = r_hi - r_lo;                       // rows that begin inside the tile (the first one aside)
+    if (nstart <= TILE) {
+      for (int i = tid; i < nstart; i += THREADS) stage[i] = (uint32_t)a.rowptr[r_lo + 1 + i];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      const int64_t e = tile0 + seg + j * 64;
+      int64_t lo = 0, hi = nstart;                            // number of those rows that begin at or before e
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        const int64_t s = nstart <= TILE ? (int64_t)(int32_t)stage[mid] : (int64_t)a.rowptr[r_lo + 1 + mid];
+        if (s <= e) lo = mid + 1; else hi = mid;
+      }
+      row[j] = (uint32_t)(r_lo + lo);
+    }
+    __syncthreads();
+  }
+
+#pragma unroll
+  for (int j = 0; j < KPT; ++j)
+    if (seg + j * 64 < cnt) stage[pos[j]] = key[j];
+  __syncthreads();
+  int32_t dst[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const int i = j * THREADS + tid;
+    dst[j] = -1;
+    if (i < cnt) {
+      const uint32_t k = stage[i];
+      dst[j] = gbase[(k >> a.shift) & (uint32_t)(bins - 1)] + i;
+      a.keys_out[dst[j]] = k;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const uint32_t* __restrict__ in = q == 0 ? a.p0_in : a.p1_in;
+    uint32_t* __restrict__ out = q == 0 ? a.p0_out : a.p1_out;
+    uint32_t v[KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      const int i = seg + j * 64;
+      if (q == 0 && SRC == SRC_INDEX) v[j] = (uint32_t)(tile0 + i);
+      else if (q == 0 && SRC == SRC_ROWS) v[j] = row[SRC == SRC_ROWS ? j : 0];
+      else v[j] = i < cnt ? in[tile0 + i] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < KPT; ++j)
+      if (seg + j * 64 < cnt) stage[pos[j]] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < KPT; ++j)
+      if (dst[j] >= 0) out[dst[j]] = stage[j * THREADS + tid];
+  }
+}
+
+template <int THREADS, int KPT>
+int run_pass(const PassArgs& a, int np, int src, uint32_t limit, int32_t* err, hipStream_t s) {
+  const dim3 grid((unsigned)a.ntiles);
+  hipLaunchKernelGGL((radix_count_kernel<THREADS, KPT>), grid, dim3(THREADS), 0, s, a.keys_in, a.n, a.ntiles, a.shift,
+                     a.bits, a.counts, limit, err);
+  SAGNN_LAUNCH_CHECK();
+  hipLaunchKernelGGL(radix_scan_kernel, dim3(1u << a.bits), dim3(1024), 0, s, a.counts, a.ntiles, a.totals);
+  SAGNN_LAUNCH_CHECK();
+  if (src == SRC_ROWS) hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 2, SRC_ROWS>), grid, dim3(THREADS), 0, s, a);
+  else if (src == SRC_INDEX) hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 1, SRC_INDEX>), grid, dim3(THREADS), 0, s, a);
+  else if (np == 2) hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 2, SRC_ARRAYS>), grid, dim3(THREADS), 0, s, a);
+  else hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 1, SRC_ARRAYS>), grid, dim3(THREADS), 0, s, a);
+  SAGNN_LAUNCH_CHECK();
+  return SAGNN_OK;
+}
+
+int run_pass(PassArgs a, int np, int src, uint32_t limit, int32_t* err, hipStream_t s) {
+  const int tile = radix_tile(a.n);
+  a.ntiles = ceil_div(a.n, tile);
+  if (tile == 1024) return run_pass<256, 4>(a, np, src, limit, err, s);
+  if (tile == 2048) return run_pass<256, 8>(a, np, src, limit, err, s);
+  return run_pass<512, 16>(a, np, src, limit, err, s);
+}
+
+inline int passes_of(int bits) { return (bits + 7) / 8; }
+
+}  // namespace
+
+RadixWs carve_radix(void* base, int64_t n) {
+  RadixWs w{};
+  const int64_t cap = n > 0 ? n : 1;
+  // sized for the count that needs the most tiles among all counts <= cap
+  const int64_t max_tiles = std::max(ceil_div(cap, radix_tile(cap)),
+                                     std::max(std::min(ceil_div(cap, 1024), ceil_div(kTileSmallMax, 1024)),
+                                              std::min(ceil_div(cap, 2048), ceil_div(kTileMidMax, 2048))));
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? static_cast<char*>(base) + off : nullptr;
+    off += round_up(bytes, 256);
+    return p;
+  };
+  for (int i = 0; i < 2; ++i) {
+    w.keys[i] = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)cap));
+    w.pay[i] = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)cap));
+  }
+  w.counts = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * kMaxBins * (size_t)max_tiles));
+  w.totals = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * kMaxBins));
+  w.cap = cap;
+  w.bytes = off;
+  return w;
+}
+
+int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* pay_in, int64_t n, int bits, const RadixWs& w,
+                     hipStream_t s, int* result, int64_t limit, int32_t* err) {
+  if (n < 0 || n > w.cap || bits < 1 || bits > 32 || (limit > 0 && !err)) return SAGNN_EINVAL;
+  const int passes = passes_of(bits);
+  *result = (passes - 1) & 1;
+  if (n == 0) return SAGNN_OK;
+  const int per = (bits + passes - 1) / passes;
+  for (int p = 0; p < passes; ++p) {
+    PassArgs a{};
+    a.n = n;
+    a.keys_in = p == 0 ? keys_in : w.keys[(p - 1) & 1];
+    a.p0_in = p == 0 ? pay_in : w.pay[(p - 1) & 1];
+    a.keys_out = w.keys[p & 1];
+    a.p0_out = w.pay[p & 1];
+    a.shift = p * per;
+    a.bits = std::min(per, bits - p * per);
+    a.counts = w.counts;
+    a.totals = w.totals;
+    const int rc = run_pass(a, 1, p == 0 && !pay_in ? SRC_INDEX : SRC_ARRAYS, p == 0 ? (uint32_t)limit : 0u, err, s);
+    if (rc != SAGNN_OK) return rc;
+  }
+  return SAGNN_OK;
+}
+
+namespace {
+
+constexpr int kThreads = 256;
+
+// rowptr[c] = number of sorted keys below c, c in [0, n], from the places where the sorted keys change: the
+// pair at i fills rowptr(previous key .. its key] = i.  Long gaps (runs of empty rows) are filled by the
+// whole wavefront.
+__global__ __launch_bounds__(kThreads) void sorted_rowptr_kernel(const uint32_t* __restrict__ keys, int64_t cnt,
+                                                                 int64_t n, int32_t* __restrict__ rowptr) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  // (the thread behind the last pair closes the array; keys are clamped, an out-of-range key is an error elsewhere)
+  int64_t from = 0, to = -1;
+  if (i <= cnt) {
+    const int64_t prev = i > 0 ? (int64_t)keys[i - 1] : -1;
+    const int64_t cur = i < cnt ? (int64_t)keys[i] : n;
+    from = (prev < n ? prev : n) + 1;
+    to = cur < n ? cur : n;
+  }
+  const bool wide = to - from >= 8;
+  if (!wide)
+    for (int64_t c = from; c <= to; ++c) rowptr[c] = (int32_t)i;
+  for (uint64_t left = __ballot(wide); left; left &= left - 1) {
+    const int src = __builtin_ctzll(left);
+    const int64_t f = __shfl(from, src, 64), t = __shfl(to, src, 64), v = __shfl(i, src, 64);
+    for (int64_t c = f + lane; c <= t; c += 64) rowptr[c] = (int32_t)v;
+  }
+}
+
+int bits_for(int64_t n) {
+  int bits = 1;
+  while (bits < 31 && (1ll << bits) < n) ++bits;
+  return bits;
+}
+
+}  // namespace
+
+int launch_sorted_rowptr(const uint32_t* keys, int64_t cnt, int64_t n, int32_t* rowptr, hipStream_t s) {
+  hipLaunchKernelGGL(sorted_rowptr_kernel, dim3((unsigned)ceil_div(cnt + 1, kThreads)), dim3(kThreads), 0, s, keys, cnt,
+                     n, rowptr);
+  SAGNN_LAUNCH_CHECK();
+  return SAGNN_OK;
+}
+
+size_t transpose_ws_bytes(int64_t nnz) { return carve_radix(nullptr, nnz).bytes + 256; }   // sort, error flag
+
+// d_err[0] is set to 1 if a column is outside [0, n); the caller has cleared it
+int launch_transpose(const int32_t* rowptr, const int32_t* colidx, const float* val, int64_t m, int64_t n, int64_t nnz,
+                     int32_t* rowptr_t, int32_t* colidx_t, float* val_t, void* ws, int32_t* d_err, hipStream_t s) {
+  const RadixWs w = carve_radix(ws, nnz);
+  uint32_t* val_ws = w.pay[1];   // (w.pay[0] takes the rows)
+  const int bits = bits_for(n), passes = passes_of(bits), per = (bits + passes - 1) / passes;
+  int last = 0;
+  for (int p = 0; p < passes && nnz > 0; ++p) {
+    // the passes alternate between the workspace and the output arrays so that the last one ends in the outputs
+    const bool to_out = ((passes - 1 - p) & 1) == 0;
+    uint32_t* rows_out = to_out ? reinterpret_cast<uint32_t*>(colidx_t) : w.pay[0];
+    uint32_t* vals_out = to_out ? reinterpret_cast<uint32_t*>(val_t) : val_ws;
+    PassArgs a{};
+    a.n = nnz;
+    a.keys_in = p == 0 ? reinterpret_cast<const uint32_t*>(colidx) : w.keys[(p - 1) & 1];
+    a.p0_in = p == 0 ? nullptr : (to_out ? w.pay[0] : reinterpret_cast<const uint32_t*>(colidx_t));
+    a.p1_in = p == 0 ? reinterpret_cast<const uint32_t*>(val)
+                     : (to_out ? val_ws : reinterpret_cast<const uint32_t*>(val_t));
+    a.keys_out = w.keys[p & 1];
+    a.p0_out = rows_out;
+    a.p1_out = vals_out;
+    a.shift = p * per;
+    a.bits = std::min(per, bits - p * per);
+    a.counts = w.counts;
+    a.totals = w.totals;
+    a.rowptr = rowptr;
+    a.m = m;
+    const int rc = run_pass(a, 2, p == 0 ? SRC_ROWS : SRC_ARRAYS, p == 0 ? (uint32_t)n : 0u, d_err, s);
+    if (rc != SAGNN_OK) return rc;
+    last = p & 1;
+  }
+  return launch_sorted_rowptr(w.keys[last], nnz, n, rowptr_t, s);
+}
+
+}  // namespace sagnn
+
+SAGNN_EXPORT int spmm_transpose_workspace_bytes(int64_t nnz, size_t* bytes) {
+  using namespace sagnn;
+  if (!bytes || nnz < 0 || nnz > 0x7FFFFFFFll) return SAGNN_EINVAL;
+  *bytes = transpose_ws_bytes(nnz);
+  return SAGNN_OK;
+}
+
+SAGNN_EXPORT int spmm_csr_transpose(const int32_t* d_rowptr, const int32_t* d_colidx,
+                                    const float* d_val, int64_t m, int64_t n, int64_t nnz,
+                                    int32_t* d_rowptr_t, int32_t* d_colidx_t, float* d_val_t,
+                                    void* d_ws, size_t ws_bytes, void* stream) {
+  using namespace sagnn;
+  if (m < 0 || n < 0 || nnz < 0 || m > 0x7FFFFFFFll || n > 0x7FFFFFFFll || nnz > 0x7FFFFFFFll)
+    return SAGNN_EINVAL;
+  if (!d_rowptr || !d_rowptr_t || !d_ws) return SAGNN_EINVAL;
+  if (nnz > 0 && (!d_colidx || !d_val || !d_colidx_t || !d_val_t)) return SAGNN_EINVAL;
+  if (reinterpret_cast<uintptr_t>(d_ws) & 255u) return SAGNN_EINVAL;
+  const size_t need = transpose_ws_bytes(nnz);
+  if (ws_bytes < need) return SAGNN_ECAPACITY;
+  if (n == 0 && nnz > 0) return SAGNN_EFORMAT;   // no column index can be valid
+  hipStream_t s = (hipStream_t)stream;
+  int32_t* d_err = reinterpret_cast<int32_t*>(static_cast<char*>(d_ws) + need - 256);
+  SAGNN_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
+  const int rc = launch_transpose(d_rowptr, d_colidx, d_val, m, n, nnz, d_rowptr_t, d_colidx_t, d_val_t, d_ws, d_err, s);
+  if (rc != SAGNN_OK) return rc;
+  int32_t h_err = 0;
+  SAGNN_HIP(hipMemcpyAsync(&h_err, d_err, sizeof(h_err), hipMemcpyDeviceToHost, s));
+  SAGNN_HIP(hipStreamSynchronize(s));
+  if (h_err) return SAGNN_EFORMAT;
+  return SAGNN_OK;
+}

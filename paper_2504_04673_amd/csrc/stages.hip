@@ -198,27 +198,6 @@ __global__ __launch_bounds__(kThreads) void split_scan_tiles_kernel(int32_t* __r
   if (threadIdx.x == 0) ts[ntiles] = carry;
 }
 
-// The three scan steps in one launch for rows that fit one scan tile (m + 1 <= kScanTile): one
-// workgroup per block q scans its counts in place, total into element m and into ts[1] (ts laid
-// out with one tile per block, as split_offsets_kernel reads it).
-__global__ __launch_bounds__(kThreads) void split_scan_small_kernel(int32_t* __restrict__ rowptr_blk, int64_t m,
-                                                                    int32_t* __restrict__ tilesum) {
-  int32_t* __restrict__ a = rowptr_blk + (int64_t)blockIdx.x * (m + 1);
-  const int64_t i0 = (int64_t)threadIdx.x * 8;
-  int x[8], ex[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) x[i] = (i0 + i < m) ? a[i0 + i] : 0;
-  const int total = tile_scan(x, ex);
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-    if (i0 + i < m) a[i0 + i] = ex[i];
-  if (threadIdx.x == 0) {
-    a[m] = total;
-    tilesum[(int64_t)blockIdx.x * 2] = 0;
-    tilesum[(int64_t)blockIdx.x * 2 + 1] = total;
-  }
-}
-
 // nnz_off[q] = sum of the totals of blocks < q (nb <= 256; one workgroup of 256 threads: the
 // totals are fetched in parallel, the running sum is taken over LDS)
 __global__ __launch_bounds__(kThreads) void split_offsets_kernel(const int32_t* __restrict__ tilesum, int64_t ntiles,
@@ -237,109 +216,6 @@ __global__ __launch_bounds__(kThreads) void split_offsets_kernel(const int32_t* 
   nnz_off[nb] = run;
 }
 
-// ------------------------------------------------------------------------------------------
-// Transpose by a stable least-significant-digit radix sort of (column, entry index) pairs.
-// One pass = the same three steps as the column-block split, with tiles of kSortTile entries
-// in place of rows and the 256 values of an 8-bit digit in place of the column blocks: count
-// per (digit, tile), scan along the tiles of each digit, scatter with the tile-local stable
-// rank.  Stability makes the entries of a transposed row come out in the order of the rows
-// they came from (ascending), and keeps duplicates in their stored order.
-constexpr int kSortTile = 2048;       // keys per wavefront and pass
-constexpr int kSortTileSmall = 256;   // for counts small enough that 2048-key tiles would leave the chip idle
-
-template <bool SCATTER>
-__global__ __launch_bounds__(kThreads) void radix_tile_kernel(
-    const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ pay_in, int64_t nnz, int shift,
-    int64_t ntiles, int32_t* __restrict__ counts, const int64_t* __restrict__ digit_off,
-    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ pay_out, int tile) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * kThreads) >> 6;
-  for (int64_t t = wave0; t < ntiles; t += nwaves) {
-    const int64_t b = t * tile;
-    const int64_t e = b + tile < nnz ? b + tile : nnz;
-    int32_t cnt[4] = {0, 0, 0, 0};
-    for (int64_t base = b; base < e; base += 64) {
-      const int64_t i = base + lane;
-      const bool active = i < e;
-      const uint32_t key = active ? keys_in[i] : 0u;
-      const int q = active ? (int)((key >> shift) & 255u) : -1;
-      uint64_t remaining = __ballot(q >= 0);
-      while (remaining) {
-        const int leader = __builtin_ctzll(remaining);
-        const int q0 = __shfl(q, leader, 64);
-        const uint64_t mask = __ballot(q == q0);
-        int32_t have = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int32_t v = __shfl(cnt[j], q0 & 63, 64);
-          if (j == (q0 >> 6)) have = v;
-        }
-        if (SCATTER && q == q0) {
-          const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-          const int64_t o = digit_off[q0] + counts[(int64_t)q0 * (ntiles + 1) + t] + have + rank;
-          if (o >= 0 && o < nnz) {
-            keys_out[o] = key;
-            pay_out[o] = pay_in ? pay_in[i] : (uint32_t)i;
-          }
-        }
-        if (lane == (q0 & 63)) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (j == (q0 >> 6)) cnt[j] += __popcll(mask);
-        }
-        remaining &= ~mask;
-      }
-    }
-    if (!SCATTER) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) counts[(int64_t)(j * 64 + lane) * (ntiles + 1) + t] = cnt[j];
-    }
-  }
-}
-
-// err[0] = 1 if some column index is outside [0, n)
-__global__ __launch_bounds__(kThreads) void transpose_check_kernel(const int32_t* __restrict__ colidx,
-                                                                   int64_t nnz, int64_t n,
-                                                                   int32_t* __restrict__ err) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nnz; i += stride)
-    if (colidx[i] < 0 || colidx[i] >= n) err[0] = 1;
-}
-
-// rowptr_t[c] = number of sorted keys below c (lower bound), c in [0, n]
-__global__ __launch_bounds__(kThreads) void transpose_rowptr_kernel(const uint32_t* __restrict__ keys,
-                                                                    int64_t nnz, int64_t n,
-                                                                    int32_t* __restrict__ rowptr_t) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x; c <= n; c += stride) {
-    int64_t lo = 0, hi = nnz;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)keys[mid] < c) lo = mid + 1; else hi = mid;
-    }
-    rowptr_t[c] = (int32_t)lo;
-  }
-}
-
-// entry i of the transpose is entry perm[i] of A: its column there is A's row of that entry
-__global__ __launch_bounds__(kThreads) void transpose_gather_kernel(
-    const int32_t* __restrict__ rowptr, const float* __restrict__ val, int64_t m, int64_t nnz,
-    const uint32_t* __restrict__ perm, int32_t* __restrict__ colidx_t, float* __restrict__ val_t) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nnz; i += stride) {
-    const int64_t e = perm[i];
-    int64_t lo = 0, hi = m;            // largest r with rowptr[r] <= e
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)rowptr[mid] <= e) lo = mid; else hi = mid;
-    }
-    colidx_t[i] = (int32_t)lo;
-    val_t[i] = e < nnz ? val[e] : 0.f;
-  }
-}
-
 unsigned wave_grid(int64_t rows) {
   int64_t b = ceil_div(rows, kThreads / 64);
   if (b > 256 * 64) b = 256 * 64;
@@ -349,93 +225,6 @@ unsigned wave_grid(int64_t rows) {
 
 }  // namespace
 
-namespace {
-// keys per wavefront: small tiles while they still fit the one-launch scan (at most kScanTile - 1 tiles)
-inline int radix_tile(int64_t n) {
-  return n <= (int64_t)kSortTileSmall * (kScanTile - 1) ? kSortTileSmall : kSortTile;
-}
-}  // namespace
-
-RadixWs carve_radix(void* base, int64_t n) {
-  RadixWs w{};
-  const int64_t cap = n > 0 ? n : 1;
-  w.ntiles = ceil_div(cap, radix_tile(cap));
-  w.nscan = ceil_div(w.ntiles + 1, kScanTile);
-  // sized for the count that needs the most tiles among all counts <= cap
-  const int64_t max_tiles = std::max(w.ntiles, std::min<int64_t>(ceil_div(cap, kSortTileSmall), kScanTile - 1));
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    char* p = base ? static_cast<char*>(base) + off : nullptr;
-    off += round_up(bytes, 256);
-    return p;
-  };
-  for (int i = 0; i < 2; ++i) {
-    w.keys[i] = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)cap));
-    w.pay[i] = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)cap));
-  }
-  w.counts = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 256 * (size_t)(max_tiles + 1)));
-  w.tilesum = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 256 * (size_t)(w.nscan + 1)));
-  w.digit_off = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * 257));
-  w.cap = cap;
-  w.bytes = off;
-  return w;
-}
-
-int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* pay_in, int64_t n, int bits, const RadixWs& w0,
-                     hipStream_t s, int* result) {
-  RadixWs w = w0;
-  if (n < 0 || n > w0.cap || bits < 1 || bits > 32) return SAGNN_EINVAL;
-  const int tile = radix_tile(n > 0 ? n : 1);
-  w.ntiles = ceil_div(n > 0 ? n : 1, tile);          // the workspace may have been carved for more
-  w.nscan = ceil_div(w.ntiles + 1, kScanTile);
-  const int passes = (bits + 7) / 8;
-  const dim3 sgrid((unsigned)w.nscan, 256u);
-  for (int pass = 0; pass < passes; ++pass) {
-    const uint32_t* kin = pass == 0 ? keys_in : w.keys[(pass - 1) & 1];
-    const uint32_t* pin = pass == 0 ? pay_in : w.pay[(pass - 1) & 1];
-    hipLaunchKernelGGL(radix_tile_kernel<false>, dim3(wave_grid(w.ntiles)), dim3(kThreads), 0, s, kin, pin, n,
-                       pass * 8, w.ntiles, w.counts, (const int64_t*)nullptr, (uint32_t*)nullptr,
-                       (uint32_t*)nullptr, tile);
-    SAGNN_LAUNCH_CHECK();
-    if (w.ntiles + 1 <= kScanTile) {   // nscan == 1: the three scan steps as one launch
-      hipLaunchKernelGGL(split_scan_small_kernel, dim3(256), dim3(kThreads), 0, s, w.counts, w.ntiles, w.tilesum);
-      SAGNN_LAUNCH_CHECK();
-    } else {
-      hipLaunchKernelGGL(split_scan_kernel<0>, sgrid, dim3(kThreads), 0, s, w.counts, w.ntiles, w.nscan, w.tilesum);
-      SAGNN_LAUNCH_CHECK();
-      hipLaunchKernelGGL(split_scan_tiles_kernel, dim3(256), dim3(kThreads), 0, s, w.tilesum, w.nscan);
-      SAGNN_LAUNCH_CHECK();
-      hipLaunchKernelGGL(split_scan_kernel<1>, sgrid, dim3(kThreads), 0, s, w.counts, w.ntiles, w.nscan, w.tilesum);
-      SAGNN_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(split_offsets_kernel, dim3(1), dim3(kThreads), 0, s, w.tilesum, w.nscan, 256, w.digit_off);
-    SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(radix_tile_kernel<true>, dim3(wave_grid(w.ntiles)), dim3(kThreads), 0, s, kin, pin, n,
-                       pass * 8, w.ntiles, w.counts, (const int64_t*)w.digit_off, w.keys[pass & 1],
-                       w.pay[pass & 1], tile);
-    SAGNN_LAUNCH_CHECK();
-  }
-  *result = (passes - 1) & 1;
-  return SAGNN_OK;
-}
-
-namespace {
-
-struct TransposeWs {
-  RadixWs r;
-  int32_t* err;
-  size_t bytes;
-};
-
-TransposeWs carve_transpose(void* base, int64_t nnz) {
-  TransposeWs w{};
-  w.r = carve_radix(base, nnz);
-  w.err = reinterpret_cast<int32_t*>(base ? static_cast<char*>(base) + w.r.bytes : nullptr);
-  w.bytes = w.r.bytes + 256;
-  return w;
-}
-
-}  // namespace
 }  // namespace sagnn
 
 SAGNN_EXPORT int spmm_split_workspace_bytes(int64_t m, int32_t nb, size_t* bytes) {
@@ -493,61 +282,6 @@ SAGNN_EXPORT int spmm_split_colblocks(const int32_t* d_rowptr, const int32_t* d_
                            hipMemcpyDeviceToHost, s));
   SAGNN_HIP(hipStreamSynchronize(s));
   if (h_nnz_off[nb] > nnz) return SAGNN_EFORMAT;   // rows overlap: rowptr is not a CSR row pointer
-  return SAGNN_OK;
-}
-
-SAGNN_EXPORT int spmm_transpose_workspace_bytes(int64_t nnz, size_t* bytes) {
-  using namespace sagnn;
-  if (!bytes || nnz < 0 || nnz > 0x7FFFFFFFll) return SAGNN_EINVAL;
-  *bytes = carve_transpose(nullptr, nnz).bytes;
-  return SAGNN_OK;
-}
-
-SAGNN_EXPORT int spmm_csr_transpose(const int32_t* d_rowptr, const int32_t* d_colidx,
-                                    const float* d_val, int64_t m, int64_t n, int64_t nnz,
-                                    int32_t* d_rowptr_t, int32_t* d_colidx_t, float* d_val_t,
-                                    void* d_ws, size_t ws_bytes, void* stream) {
-  using namespace sagnn;
-  if (m < 0 || n < 0 || nnz < 0 || m > 0x7FFFFFFFll || n > 0x7FFFFFFFll || nnz > 0x7FFFFFFFll)
-    return SAGNN_EINVAL;
-  if (!d_rowptr || !d_rowptr_t || !d_ws) return SAGNN_EINVAL;
-  if (nnz > 0 && (!d_colidx || !d_val || !d_colidx_t || !d_val_t)) return SAGNN_EINVAL;
-  if (reinterpret_cast<uintptr_t>(d_ws) & 255u) return SAGNN_EINVAL;
-  const TransposeWs w = carve_transpose(d_ws, nnz);
-  if (ws_bytes < w.bytes) return SAGNN_ECAPACITY;
-  hipStream_t s = (hipStream_t)stream;
-  auto grid = [](int64_t items) {
-    int64_t b = ceil_div(items, kThreads);
-    if (b > 256 * 32) b = 256 * 32;
-    if (b < 1) b = 1;
-    return dim3((unsigned)b);
-  };
-  SAGNN_HIP(hipMemsetAsync(w.err, 0, sizeof(int32_t) * 4, s));
-  const uint32_t* sorted_keys = reinterpret_cast<const uint32_t*>(d_colidx);
-  const uint32_t* perm = nullptr;
-  if (nnz > 0) {
-    hipLaunchKernelGGL(transpose_check_kernel, grid(nnz), dim3(kThreads), 0, s, d_colidx, nnz, n, w.err);
-    SAGNN_LAUNCH_CHECK();
-    int bits = 1;
-    while (bits < 31 && (1ll << bits) < n) ++bits;
-    int res = 0;
-    const int rc = radix_sort_pairs(reinterpret_cast<const uint32_t*>(d_colidx), nullptr, nnz, bits, w.r, s, &res);
-    if (rc != SAGNN_OK) return rc;
-    sorted_keys = w.r.keys[res];
-    perm = w.r.pay[res];
-  }
-  hipLaunchKernelGGL(transpose_rowptr_kernel, grid(n + 1), dim3(kThreads), 0, s, sorted_keys, nnz, n,
-                     d_rowptr_t);
-  SAGNN_LAUNCH_CHECK();
-  if (nnz > 0) {
-    hipLaunchKernelGGL(transpose_gather_kernel, grid(nnz), dim3(kThreads), 0, s, d_rowptr, d_val, m, nnz,
-                       perm, d_colidx_t, d_val_t);
-    SAGNN_LAUNCH_CHECK();
-  }
-  int32_t h_err[4] = {0, 0, 0, 0};
-  SAGNN_HIP(hipMemcpyAsync(h_err, w.err, sizeof(h_err), hipMemcpyDeviceToHost, s));
-  SAGNN_HIP(hipStreamSynchronize(s));
-  if (h_err[0]) return SAGNN_EFORMAT;
   return SAGNN_OK;
 }
 

@@ -234,6 +234,17 @@ def test_csr_transpose(case, cfg1):
         assert e.value.code == -3
 
 
+@pytest.mark.parametrize("nnz,m,n", [(1, 1, 1), (1024, 5, 256), (1025, 3000, 257), (262_144, 1000, 1 << 16),
+                                     (262_145, 700_000, 1000), (4_194_305, 40_000, 70_001)])
+def test_csr_transpose_at_the_edges_of_the_sort_tiles(nnz, m, n):
+    """Full and one-over tiles of every tile size, one to three digit passes, and a matrix whose tiles are covered
+    by more rows than a tile has entries."""
+    rng = np.random.default_rng(nnz)
+    rowptr = np.array([0, *np.sort(rng.integers(0, nnz + 1, size=m - 1)), nnz], dtype=np.int32)
+    colidx = rng.integers(0, n, size=nnz).astype(np.int32)
+    check_transpose(rowptr, colidx, rng.standard_normal(nnz).astype(np.float32), n)
+
+
 def test_directed_graph_layer_uses_both_orientations():
     """Directed graph: the forward product runs on A^T (Sec. 2.1 forward equation), the backward
     product on A.  A^T comes from the device transpose; both layer calls against the oracle."""
