@@ -272,6 +272,23 @@ def test_directed_graph_layer_uses_both_orientations():
 
 # ------------------------------------------------------------------------------------ reordering
 
+@pytest.mark.parametrize("degrees", [[0, 1, 63, 64], [65, 128, 129, 3], [256, 257, 512, 0], [513, 2, 40, 0], [700, 700, 1, 0]])
+def test_permute_symmetric_at_the_row_lengths_where_the_method_changes(degrees):
+    """Rows around one, two, four and eight columns a lane, and past the longest row that is permuted by itself;
+    unsorted columns with repeats."""
+    rng = np.random.default_rng(sum(degrees))
+    n = 1001
+    deg = np.array(degrees)[rng.integers(0, len(degrees), size=n)]
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    colidx = rng.integers(0, n, size=rowptr[-1]).astype(np.int32)
+    val = rng.standard_normal(colidx.size).astype(np.float32)
+    inv = rng.permutation(n).astype(np.int32)
+    rpp, cip, vap = sagnn.spmm_csr_permute_symmetric(dev(rowptr), dev(colidx), dev(val), dev(inv))
+    orp, oci, ova = oracle.permute_symmetric(rowptr, colidx, val, inv)
+    assert np.array_equal(rpp.cpu().numpy(), orp) and np.array_equal(cip.cpu().numpy(), oci)
+    assert vap.cpu().numpy().tobytes() == ova.tobytes()
+
+
 @pytest.mark.parametrize("case", ["cfg1_random_labels", "sbm_communities", "unsorted_dup", "one_part", "tiny"])
 def test_reorder_by_labels_and_permute_symmetric(case, cfg1):
     """Renumbering by partition labels and the symmetric permutation of A (Sec. 5 / 6.1), bit for
