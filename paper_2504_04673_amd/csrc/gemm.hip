@@ -24,6 +24,7 @@
 // contiguous per column, so an operand is one LDS read), accumulates a full f_in x f_out
 // partial in registers (8 wavefronts x 2x4 tiles) and writes it to scratch; a second kernel
 // sums the partials in a fixed order (reproducible, no atomics).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -342,22 +343,17 @@ struct TnArgs {
   float* partial;  // [gridDim.x][fi][fo]
 };
 
-// PREC as in gemm_nn_kernel; PREC = 2 keeps three bfloat16 planes (one per term) of both staged operands
-template <int PREC>
+// operands rounded to bfloat16
 __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
-  constexpr bool BF16 = PREC == SAGNN_GEMM_BF16;
-  constexpr bool X3 = PREC == SAGNN_GEMM_FP32_BF16X3;
-  using lds_t = typename std::conditional<PREC != SAGNN_GEMM_FP32, __bf16, float>::type;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  lds_t* Xs = reinterpret_cast<lds_t*>(smem);                    // [fi][KP]
-  lds_t* Ss = Xs + (size_t)((g.fi + 31) / 32) * 32 * KP;         // [fo][KP], after the padded X part
-  const int plane = ((g.fi + 31) / 32 + (g.fo + 31) / 32) * 32 * KP;   // elements per term plane (X3)
+  __bf16* Xs = reinterpret_cast<__bf16*>(smem);                    // [fi][KP]
+  __bf16* Ss = Xs + (size_t)((g.fi + 31) / 32) * 32 * KP;         // [fo][KP], after the padded X part
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i = lane & 31, h = lane >> 5;
   const int wa = wave >> 1, wb = wave & 1;  // wave tile: a-tiles {2wa,2wa+1}, b-tiles {4wb..4wb+3}
   const int TA = (g.fi + 31) / 32, TB = (g.fo + 31) / 32;
   // columns of the last tile that lie beyond fi / fo are never staged: keep them zero
-  for (int idx = tid; idx < (TA + TB) * 32 * KP * (X3 ? 3 : 1); idx += kTnThreads) Xs[idx] = (lds_t)0.f;
+  for (int idx = tid; idx < (TA + TB) * 32 * KP; idx += kTnThreads) Xs[idx] = (__bf16)0.f;
   __syncthreads();
 
   const int64_t r_begin = (int64_t)blockIdx.x * g.rows_per_wg;
@@ -389,17 +385,12 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
                                          : make_float4(0.f, 0.f, 0.f, 0.f);
       }
   };
-  // Transposing stores: column col = 4 cg + c of the stage goes to LDS row col, k contiguous, so a
-  // lane's two rows (k, k + 1) of one column are one 4-byte (bfloat16) or 8-byte (fp32) store.  Row
-  // starts are 20 (40) words apart: lanes that store the same c fall on two banks only.  Lane cg
-  // therefore takes its four columns in the order c = (j + cg / 2) mod 4, which spreads a store over
-  // eight banks.
-  auto pick = [](const float (&a)[4], int c) { return c == 0 ? a[0] : (c == 1 ? a[1] : (c == 2 ? a[2] : a[3])); };
+  // Transposing stores: column col = 4 cg + c of the stage goes to LDS row col, k contiguous, so a lane's two
+  // rows (k, k + 1) of one column are one 4-byte store.  (Lanes that store the same c fall on two banks; taking
+  // the columns in a rotated order spreads them over eight but lengthens the path from a load to its store, which
+  // is what bounds a stage: 1.0 -> 1.2 ms at 2 M x 256 x 256.)
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   auto store_stage = [&]() {
-    // (rounded-bfloat16 mode: the stage is short and bound by the latency of its loads; the selects of
-    // the rotation would only lengthen the path from a load to its store)
-    const int rot = BF16 ? 0 : (cg >> 1) & 3;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       const int kk = (kp + 8 * p) * 2;
@@ -408,52 +399,16 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
       const float sa[4] = {sr[p][0].x, sr[p][0].y, sr[p][0].z, sr[p][0].w};
       const float sb[4] = {sr[p][1].x, sr[p][1].y, sr[p][1].z, sr[p][1].w};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = BF16 ? j : (j + rot) & 3;
+      for (int c = 0; c < 4; ++c) {
         const int col = cg * 4 + c;
-        const float x0 = BF16 ? xa[j] : pick(xa, c), x1 = BF16 ? xb[j] : pick(xb, c);
-        const float s0 = BF16 ? sa[j] : pick(sa, c), s1 = BF16 ? sb[j] : pick(sb, c);
-        if constexpr (X3) {
-          __bf16* Xb = reinterpret_cast<__bf16*>(Xs);
-          __bf16* Sb = reinterpret_cast<__bf16*>(Ss);
-          __bf16 lo[3], hi[3];
-          if (col < g.fi) {
-            split3(x0, lo[0], lo[1], lo[2]);
-            split3(x1, hi[0], hi[1], hi[2]);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              bf16x2 t;
-              t[0] = lo[q]; t[1] = hi[q];
-              *reinterpret_cast<bf16x2*>(Xb + q * plane + col * KP + kk) = t;
-            }
-          }
-          if (col < g.fo) {
-            split3(s0, lo[0], lo[1], lo[2]);
-            split3(s1, hi[0], hi[1], hi[2]);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              bf16x2 t;
-              t[0] = lo[q]; t[1] = hi[q];
-              *reinterpret_cast<bf16x2*>(Sb + q * plane + col * KP + kk) = t;
-            }
-          }
-        } else if constexpr (BF16) {
-          __bf16* Xb = reinterpret_cast<__bf16*>(Xs);
-          __bf16* Sb = reinterpret_cast<__bf16*>(Ss);
-          bf16x2 t;
-          if (col < g.fi) {
-            t[0] = (__bf16)x0; t[1] = (__bf16)x1;
-            *reinterpret_cast<bf16x2*>(Xb + col * KP + kk) = t;
-          }
-          if (col < g.fo) {
-            t[0] = (__bf16)s0; t[1] = (__bf16)s1;
-            *reinterpret_cast<bf16x2*>(Sb + col * KP + kk) = t;
-          }
-        } else {
-          float* Xf = reinterpret_cast<float*>(Xs);
-          float* Sf = reinterpret_cast<float*>(Ss);
-          if (col < g.fi) *reinterpret_cast<float2*>(Xf + col * KP + kk) = make_float2(x0, x1);
-          if (col < g.fo) *reinterpret_cast<float2*>(Sf + col * KP + kk) = make_float2(s0, s1);
+        bf16x2 t;
+        if (col < g.fi) {
+          t[0] = (__bf16)xa[c]; t[1] = (__bf16)xb[c];
+          *reinterpret_cast<bf16x2*>(Xs + col * KP + kk) = t;
+        }
+        if (col < g.fo) {
+          t[0] = (__bf16)sa[c]; t[1] = (__bf16)sb[c];
+          *reinterpret_cast<bf16x2*>(Ss + col * KP + kk) = t;
         }
       }
     }
@@ -465,39 +420,6 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
     store_stage();
     __syncthreads();
     if (r0 + KB < r_end) load_stage(r0 + KB);  // prefetch the next stage into registers
-    if constexpr (X3) {
-      const __bf16* Xb = reinterpret_cast<const __bf16*>(Xs);
-      const __bf16* Sb = reinterpret_cast<const __bf16*>(Ss);
-#pragma unroll 1
-      for (int ks = 0; ks < KB / 16; ++ks) {
-        // (the terms of one operand pair at a time: 128 accumulator registers leave room for little else)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int tb = 4 * wb + b;
-          bf16x8 bv[3];
-#pragma unroll
-          for (int t = 0; t < 3; ++t)
-            bv[t] = *reinterpret_cast<const bf16x8*>(Sb + t * plane + ((tb < TB ? tb : 0) * 32 + i) * KP + ks * 16 + 8 * h);
-#pragma unroll
-          for (int a = 0; a < 2; ++a) {
-            const int ta = 2 * wa + a;
-            bf16x8 av[3];
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-              av[t] = *reinterpret_cast<const bf16x8*>(Xb + t * plane + ((ta < TA ? ta : 0) * 32 + i) * KP + ks * 16 + 8 * h);
-            if (ta < TA && tb < TB) {
-              // the six products down to 2^-16 of the leading one, smallest first
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[2], bv[0], acc[a][b], 0, 0, 0);
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0], bv[2], acc[a][b], 0, 0, 0);
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[1], bv[1], acc[a][b], 0, 0, 0);
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[1], bv[0], acc[a][b], 0, 0, 0);
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0], bv[1], acc[a][b], 0, 0, 0);
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0], bv[0], acc[a][b], 0, 0, 0);
-            }
-          }
-        }
-      }
-    } else if (BF16) {
 #pragma unroll
       for (int ks = 0; ks < KB / 16; ++ks) {
         bf16x8 av[2], bv[4];
@@ -505,13 +427,13 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
         for (int a = 0; a < 2; ++a) {
           const int ta = 2 * wa + a;
           av[a] = *reinterpret_cast<const bf16x8*>(
-              reinterpret_cast<const __bf16*>(Xs) + ((ta < TA ? ta : 0) * 32 + i) * KP + ks * 16 + 8 * h);
+              Xs + ((ta < TA ? ta : 0) * 32 + i) * KP + ks * 16 + 8 * h);
         }
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int tb = 4 * wb + b;
           bv[b] = *reinterpret_cast<const bf16x8*>(
-              reinterpret_cast<const __bf16*>(Ss) + ((tb < TB ? tb : 0) * 32 + i) * KP + ks * 16 + 8 * h);
+              Ss + ((tb < TB ? tb : 0) * 32 + i) * KP + ks * 16 + 8 * h);
         }
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -520,28 +442,6 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
             if (2 * wa + a < TA && 4 * wb + b < TB)
               acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a], bv[b], acc[a][b], 0, 0, 0);
       }
-    } else {
-#pragma unroll 4
-      for (int ks = 0; ks < KB / 2; ++ks) {
-        float av[2], bv[4];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const int ta = 2 * wa + a;
-          av[a] = reinterpret_cast<const float*>(Xs)[((ta < TA ? ta : 0) * 32 + i) * KP + ks * 2 + h];
-        }
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int tb = 4 * wb + b;
-          bv[b] = reinterpret_cast<const float*>(Ss)[((tb < TB ? tb : 0) * 32 + i) * KP + ks * 2 + h];
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b)
-            if (2 * wa + a < TA && 4 * wb + b < TB)
-              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[a], bv[b], acc[a][b], 0, 0, 0);
-      }
-    }
   }
 
   float* __restrict__ P = g.partial + (int64_t)blockIdx.x * g.fi * g.fo;
@@ -559,34 +459,272 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
     }
 }
 
-__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ partial,
-                                                        int32_t nparts, int64_t elems,
-                                                        float* __restrict__ Y) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= elems) return;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  int p = 0;
-  for (; p + 4 <= nparts; p += 4) {
-    s0 += partial[(int64_t)(p + 0) * elems + idx];
-    s1 += partial[(int64_t)(p + 1) * elems + idx];
-    s2 += partial[(int64_t)(p + 2) * elems + idx];
-    s3 += partial[(int64_t)(p + 3) * elems + idx];
-  }
-  for (; p < nparts; ++p) s0 += partial[(int64_t)p * elems + idx];
-  Y[idx] = (s0 + s1) + (s2 + s3);
+// Y = X^T S straight from registers.  In X^T S the reduction index is the row, so the lanes of an operand that
+// hold one k hold one row of X: a lane loads V consecutive columns of a row (V = 1, 2 or 4) and register c of
+// those loads is the operand of the tile with columns V*i + c, i = 0..15.  No transpose, no LDS in the loop.
+//   fp32                    16x16x4: a load brings 4 rows, one per 16 lanes
+//   bfloat16, three terms   16x16x32: 8 loads bring 32 rows, lane group q the rows 8q..8q+7, packed in registers
+// A wavefront owns a block of up to 64 x 64 of Y and a share of the rows of its workgroup's slice; the shares
+// are summed through LDS, the slices by tn_reduce_kernel, both in a fixed order.
+// It replaces a form that staged every slab transposed in LDS for all shapes (16 x 16 over 1 M rows took 1 ms:
+// the staging work did not shrink with the width); that one is kept where it is faster (see launch_gemm_tn).
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+constexpr int kTdWaves = 8;
+
+template <int V> struct ColVec;
+template <> struct ColVec<1> { typedef float T; };
+template <> struct ColVec<2> { typedef float T __attribute__((ext_vector_type(2))); };
+template <> struct ColVec<4> { typedef float T __attribute__((ext_vector_type(4))); };
+template <int V>
+__device__ __forceinline__ float comp(const typename ColVec<V>::T& v, int c) {
+  if constexpr (V == 1) return v;
+  else return v[c];
 }
 
-inline int32_t tn_parts(int64_t m) {
-  int64_t p = ceil_div(m, 4 * KB);  // at least 4 stages of work per workgroup
-  if (p > 256) p = 256;
-  if (p < 1) p = 1;
-  return (int32_t)p;
+template <int PREC, int VA, int VB>
+__global__ __launch_bounds__(kTdWaves * 64) void gemm_tn_direct_kernel(const TnArgs g, int nbx, int nbs, int per,
+                                                                             int kshare) {
+  constexpr int KROWS = PREC == SAGNN_GEMM_FP32 ? 4 : 32;      // rows of one matrix instruction
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  using xvec = typename ColVec<VA>::T;
+  using svec = typename ColVec<VB>::T;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int i = lane & 15, q = lane >> 4;
+  const int nb = nbx * nbs;
+  const int first = (int)blockIdx.x * per;
+  const int here = nb - first < per ? nb - first : per;             // blocks of Y in this workgroup
+  const int blk = first + wave % here, share = wave / here;
+  const bool busy = share < kshare;
+  const int xb = blk / nbs * 64, sb = blk % nbs * 64;
+  // a lane whose columns lie past the end reads column 0: its results are not stored
+  const int xc = xb + VA * i < g.fi ? xb + VA * i : 0, sc = sb + VB * i < g.fo ? sb + VB * i : 0;
+  const int64_t r0 = (int64_t)blockIdx.y * g.rows_per_wg;
+  int64_t r_end = r0 + g.rows_per_wg;
+  if (r_end > g.m) r_end = g.m;
+
+  floatx4 acc[VA][VB];
+#pragma unroll
+  for (int a = 0; a < VA; ++a)
+#pragma unroll
+    for (int b = 0; b < VB; ++b) acc[a][b] = floatx4(0.f);
+
+  if constexpr (PREC == SAGNN_GEMM_FP32) {
+    constexpr int U = VA * VB >= 8 ? 4 : 8;                    // instructions' worth of rows in flight
+    const int64_t step = (int64_t)kshare * (U * KROWS);
+    int64_t r = r0 + (int64_t)share * (U * KROWS);
+    const float* xp = g.X + (r + q) * g.ldx + xc;
+    const float* sp = g.S + (r + q) * g.lds_ + sc;
+    xvec x[U];
+    svec s[U];
+    auto full = [&](int64_t at) { return busy && at + U * KROWS <= r_end; };
+    if (full(r)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x[u] = *reinterpret_cast<const xvec*>(xp + (int64_t)(u * KROWS) * g.ldx);
+        s[u] = *reinterpret_cast<const svec*>(sp + (int64_t)(u * KROWS) * g.lds_);
+      }
+    }
+    while (full(r)) {
+      r += step;
+      xp += step * g.ldx;
+      sp += step * g.lds_;
+      const bool more = full(r);
+      xvec xn[U];
+      svec sn[U];
+      if (more) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          xn[u] = *reinterpret_cast<const xvec*>(xp + (int64_t)(u * KROWS) * g.ldx);
+          sn[u] = *reinterpret_cast<const svec*>(sp + (int64_t)(u * KROWS) * g.lds_);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int a = 0; a < VA; ++a)
+#pragma unroll
+          for (int b = 0; b < VB; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp<VA>(x[u], a), comp<VB>(s[u], b), acc[a][b], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x[u] = xn[u];
+        s[u] = sn[u];
+      }
+    }
+    if (busy)
+      for (int u = 0; u < U; ++u) {                            // the rows of the last, partial step
+        const int64_t row = r + u * KROWS + q;
+        if (r + u * KROWS >= r_end) break;
+        xvec xt = xvec(0.f);
+        svec st = svec(0.f);
+        if (row < r_end) {
+          xt = *reinterpret_cast<const xvec*>(g.X + row * g.ldx + xc);
+          st = *reinterpret_cast<const svec*>(g.S + row * g.lds_ + sc);
+        }
+#pragma unroll
+        for (int a = 0; a < VA; ++a)
+#pragma unroll
+          for (int b = 0; b < VB; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp<VA>(xt, a), comp<VB>(st, b), acc[a][b], 0, 0, 0);
+      }
+  } else {
+    constexpr int T = PREC == SAGNN_GEMM_BF16 ? 1 : 3;         // bfloat16 terms per element
+    xvec x[8];
+    svec s[8];
+    auto load_x = [&](int64_t at) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int64_t row = at + 8 * q + t;
+        x[t] = xvec(0.f);
+        if (row < r_end) x[t] = *reinterpret_cast<const xvec*>(g.X + row * g.ldx + xc);
+      }
+    };
+    auto load_s = [&](int64_t at) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int64_t row = at + 8 * q + t;
+        s[t] = svec(0.f);
+        if (row < r_end) s[t] = *reinterpret_cast<const svec*>(g.S + row * g.lds_ + sc);
+      }
+    };
+    const int64_t step = (int64_t)kshare * KROWS;
+    int64_t r = r0 + (int64_t)share * KROWS;
+    if (busy && r < r_end) {
+      load_x(r);
+      load_s(r);
+    }
+    while (busy && r < r_end) {
+      // the operands of S are packed first and their registers refilled under the matrix instructions, those of X
+      // one column at a time (all at once, with three terms each, do not fit the registers beside the sums)
+      bf16x8 sa[VB][T];
+#pragma unroll
+      for (int b = 0; b < VB; ++b)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          if constexpr (T == 1) {
+            sa[b][0][t] = (__bf16)comp<VB>(s[t], b);
+          } else {
+            __bf16 t1, t2, t3;
+            split3(comp<VB>(s[t], b), t1, t2, t3);
+            sa[b][0][t] = t1; sa[b][1][t] = t2; sa[b][2][t] = t3;
+          }
+        }
+      r += step;
+      // (64 x 64 with three terms: only once half of X has been packed)
+      constexpr int refill = T == 3 && VA * VB == 16 ? 2 : 0;
+#pragma unroll
+      for (int a = 0; a < VA; ++a) {
+        if (a == refill && r < r_end) load_s(r);
+        bf16x8 xa[T];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          if constexpr (T == 1) {
+            xa[0][t] = (__bf16)comp<VA>(x[t], a);
+          } else {
+            __bf16 t1, t2, t3;
+            split3(comp<VA>(x[t], a), t1, t2, t3);
+            xa[0][t] = t1; xa[1][t] = t2; xa[2][t] = t3;
+          }
+        }
+        if (a == VA - 1 && r < r_end) load_x(r);
+#pragma unroll
+        for (int b = 0; b < VB; ++b) {
+          floatx4 z = acc[a][b];
+          if constexpr (T == 3) {                              // smallest products first
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[2], sa[b][0], z, 0, 0, 0);
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[0], sa[b][2], z, 0, 0, 0);
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[1], sa[b][1], z, 0, 0, 0);
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[1], sa[b][0], z, 0, 0, 0);
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[0], sa[b][1], z, 0, 0, 0);
+          }
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[0], sa[b][0], z, 0, 0, 0);
+        }
+        if constexpr (T == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+
+  // sum of the shares of a block: the upper half hands its sums to the lower half until one is left
+  for (int n = kshare; n > 1;) {
+    const int keep = (n + 1) / 2;
+    floatx4* slot = reinterpret_cast<floatx4*>(smem) + ((size_t)(share - keep) * here + wave % here) * (VA * VB * 64) + lane;
+    if (busy && share >= keep && share < n) {
+#pragma unroll
+      for (int a = 0; a < VA; ++a)
+#pragma unroll
+        for (int b = 0; b < VB; ++b) slot[(a * VB + b) * 64] = acc[a][b];
+    }
+    __syncthreads();
+    if (busy && share + keep < n) {
+      const floatx4* from = reinterpret_cast<const floatx4*>(smem) + ((size_t)share * here + wave % here) * (VA * VB * 64) + lane;
+#pragma unroll
+      for (int a = 0; a < VA; ++a)
+#pragma unroll
+        for (int b = 0; b < VB; ++b) acc[a][b] += from[(a * VB + b) * 64];
+    }
+    __syncthreads();
+    n = keep;
+  }
+  if (share != 0) return;
+  float* __restrict__ P = g.partial + (int64_t)blockIdx.y * g.fi * g.fo;
+#pragma unroll
+  for (int a = 0; a < VA; ++a)
+#pragma unroll
+    for (int b = 0; b < VB; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int ro = xb + VA * (4 * q + v) + a, co = sb + VB * i + b;
+        if (ro < g.fi && co < g.fo) P[(int64_t)ro * g.fo + co] = acc[a][b][v];
+      }
+}
+
+// Y[e] = sum of the slices' partials in a fixed order.  32 elements x 8 groups of slices per workgroup: enough
+// loads in flight also for a small Y (one thread per element over 256 slices took 20 us whatever the size).
+__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ partial, int32_t nparts, int64_t elems,
+                                                        float* __restrict__ Y) {
+  __shared__ float red[8][33];
+  const int e = threadIdx.x & 31, grp = threadIdx.x >> 5;
+  const int64_t idx = (int64_t)blockIdx.x * 32 + e;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  if (idx < elems) {
+    int p = grp;
+    for (; p + 56 < nparts; p += 64) {
+      float t[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = partial[(int64_t)(p + 8 * j) * elems + idx];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s[j & 3] += t[j];
+    }
+    for (; p < nparts; p += 8) s[0] += partial[(int64_t)p * elems + idx];
+  }
+  red[grp][e] = (s[0] + s[1]) + (s[2] + s[3]);
+  __syncthreads();
+  if (grp == 0 && idx < elems) {
+    float t = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t += red[j][e];
+    Y[idx] = t;
+  }
+}
+
+// Slices of rows, at least 128 rows each: two workgroups per CU, one where a partial result is large.
+inline int32_t tn_parts(int64_t m, int32_t fi, int32_t fo) {
+  const int64_t most = (int64_t)fi * fo <= 16384 ? 512 : 256;
+  return (int32_t)std::max<int64_t>(1, std::min(most, ceil_div(m, 128)));
+}
+
+// The LDS-staged form reads every row once per workgroup, the direct form once per 64 columns of the other
+// operand (through L1 / L2).  With rounded operands, where the matrix instructions are too short to hide that,
+// the staged form wins as soon as one workgroup does not cover Y (1 M rows: 462 against 773 us at 256 x 256, 320
+// against 534 at 160 x 160, but 296 against 265 at 192 x 96).
+inline bool tn_staged(int32_t fi, int32_t fo, int32_t prec) {
+  return prec == SAGNN_GEMM_BF16 && ((fi + 63) / 64) * ((fo + 63) / 64) > kTdWaves;
 }
 
 }  // namespace
 
 size_t gemm_tn_ws_bytes(int64_t m, int32_t fi, int32_t fo) {
-  return round_up(sizeof(float) * (size_t)tn_parts(m) * (size_t)fi * (size_t)fo, 256);
+  return round_up(sizeof(float) * (size_t)tn_parts(m, fi, fo) * (size_t)fi * (size_t)fo, 256);
 }
 
 int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, int64_t m,
@@ -599,27 +737,52 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
   if (!Y || !yws || !aligned16(yws)) return SAGNN_EINVAL;
   if (m > 0 && (!X || !S || !aligned16(X) || !aligned16(S))) return SAGNN_EINVAL;
   if (yws_bytes < gemm_tn_ws_bytes(m, fi, fo)) return SAGNN_ECAPACITY;
-  const int32_t parts = tn_parts(m);
+  const int32_t parts = tn_parts(m, fi, fo);
   TnArgs g{};
   g.X = X; g.ldx = ldx; g.S = S; g.lds_ = lds_; g.m = m; g.fi = fi; g.fo = fo;
   g.rows_per_wg = ceil_div(ceil_div(m > 0 ? m : 1, parts), KB) * KB;
   g.partial = reinterpret_cast<float*>(yws);
-  const size_t lds = (size_t)(((fi + 31) / 32 + (fo + 31) / 32) * 32) * KP *
-                     (prec == SAGNN_GEMM_BF16 ? 2 : (prec == SAGNN_GEMM_FP32_BF16X3 ? 6 : 4));
-  auto go = [&](auto kern) -> int {
-    SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+  if (tn_staged(fi, fo, prec)) {
+    const size_t lds = (size_t)(((fi + 31) / 32 + (fo + 31) / 32) * 32) * KP * 2;
+    SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds));
-    hipLaunchKernelGGL(kern, dim3(parts), dim3(kTnThreads), lds, s, g);
-    return SAGNN_OK;
-  };
-  int rc;
-  if (prec == SAGNN_GEMM_BF16) rc = go(gemm_tn_kernel<SAGNN_GEMM_BF16>);
-  else if (prec == SAGNN_GEMM_FP32_BF16X3) rc = go(gemm_tn_kernel<SAGNN_GEMM_FP32_BF16X3>);
-  else rc = go(gemm_tn_kernel<SAGNN_GEMM_FP32>);
-  if (rc != SAGNN_OK) return rc;
-  SAGNN_LAUNCH_CHECK();
+    hipLaunchKernelGGL(gemm_tn_kernel, dim3(parts), dim3(kTnThreads), lds, s, g);
+    SAGNN_LAUNCH_CHECK();
+  } else {
+    const int va = fi <= 16 ? 1 : (fi <= 32 ? 2 : 4), vb = fo <= 16 ? 1 : (fo <= 32 ? 2 : 4);
+    const int nbx = (fi + 63) / 64, nbs = (fo + 63) / 64, nb = nbx * nbs;
+    const int nwg = (nb + kTdWaves - 1) / kTdWaves, per = (nb + nwg - 1) / nwg, kshare = kTdWaves / per;
+    const size_t lds = (size_t)(kshare / 2) * per * va * vb * 64 * 16;   // at most 64 KB
+    const dim3 grid((unsigned)nwg, (unsigned)parts);   // (workgroups that read the same rows run side by side)
+    auto go = [&](auto kern) -> int {
+      if (lds > 48 * 1024)
+        SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      hipLaunchKernelGGL(kern, grid, dim3((unsigned)(per * kshare * 64)), lds, s, g, nbx, nbs, per, kshare);
+      SAGNN_LAUNCH_CHECK();
+      return SAGNN_OK;
+    };
+    auto width = [&](auto p) -> int {
+      constexpr int PREC = decltype(p)::value;
+      switch (va * 8 + vb) {
+        case 9: return go(gemm_tn_direct_kernel<PREC, 1, 1>);
+        case 10: return go(gemm_tn_direct_kernel<PREC, 1, 2>);
+        case 12: return go(gemm_tn_direct_kernel<PREC, 1, 4>);
+        case 17: return go(gemm_tn_direct_kernel<PREC, 2, 1>);
+        case 18: return go(gemm_tn_direct_kernel<PREC, 2, 2>);
+        case 20: return go(gemm_tn_direct_kernel<PREC, 2, 4>);
+        case 33: return go(gemm_tn_direct_kernel<PREC, 4, 1>);
+        case 34: return go(gemm_tn_direct_kernel<PREC, 4, 2>);
+        default: return go(gemm_tn_direct_kernel<PREC, 4, 4>);
+      }
+    };
+    int rc;
+    if (prec == SAGNN_GEMM_BF16) rc = width(std::integral_constant<int, SAGNN_GEMM_BF16>{});
+    else if (prec == SAGNN_GEMM_FP32_BF16X3) rc = width(std::integral_constant<int, SAGNN_GEMM_FP32_BF16X3>{});
+    else rc = width(std::integral_constant<int, SAGNN_GEMM_FP32>{});
+    if (rc != SAGNN_OK) return rc;
+  }
   const int64_t elems = (int64_t)fi * fo;
-  hipLaunchKernelGGL(tn_reduce_kernel, dim3((unsigned)ceil_div(elems, 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(tn_reduce_kernel, dim3((unsigned)ceil_div(elems, 32)), dim3(256), 0, s,
                      g.partial, parts, elems, Y);
   SAGNN_LAUNCH_CHECK();
   return SAGNN_OK;

@@ -886,6 +886,23 @@ def test_bf16_gemm_is_tight_against_bf16_rounded_oracle():
     assert_close(Z, ref, zabs, 2e-5, "bf16 gemm vs bf16-rounded oracle")
 
 
+@pytest.mark.parametrize("fin,fout", [(4, 4), (16, 20), (20, 16), (32, 36), (36, 32), (64, 68), (132, 64), (160, 160), (256, 132), (256, 256)])
+@pytest.mark.parametrize("m", [1, 31, 129, 4100])
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_weight_gradient_at_the_edges_of_its_blocks(prec, m, fin, fout):
+    """Y = H^T S with S = G (identity matrix): one, two and four columns a lane, several blocks of 64 columns with
+    ragged ends, fewer rows than one matrix instruction takes, a slice's partial last step."""
+    rp = dev(np.arange(m + 1, dtype=np.int32))
+    ci, v = dev(np.arange(m, dtype=np.int32)), dev(np.ones(m, np.float32))
+    H = synth.normal((m, fin), 1, synth.STREAM_H)
+    G = synth.normal((m, fout), 1, synth.STREAM_G)
+    W = synth.normal((fin, fout), 1, synth.STREAM_W)
+    _, _, Y = sagnn.gcn_layer_bwd(rp, ci, v, dev(G), dev(W), None, dev(H), prec=prec, want_gprev=False)
+    torch.cuda.synchronize()
+    ref, yabs = oracle.gemm(H, G, bf16=(prec == 1), transX=True, want_abs=True)
+    assert_close(Y, ref, yabs, RTOL_GEMM_FP32, "weight gradient")
+
+
 @pytest.mark.parametrize("prec,fin,fout", [(0, 128, 128), (1, 256, 256), (0, 64, 32), (0, 16, 16), (1, 48, 20),
                                            (2, 128, 128), (2, 256, 256), (2, 48, 20)])
 def test_gcn_layer_fwd_bwd_small(prec, fin, fout):
