@@ -181,8 +181,8 @@ int spmm_pack_rows(const float* d_H, int64_t n, int64_t ldh, int32_t f, const in
  *
  * Scheduling: the pattern (and here also the values) of A is fixed during training, so a
  * one-time spmm_csr_prepare() builds a schedule in the workspace:
- *   - always: the entries are cut into equal chunks (nonzero splitting) and the row in which
- *     each chunk starts is recorded, so hub rows and runs of short rows are balanced;
+ *   - always: the entries are cut into chunks of about equal length (nonzero splitting) and the row in
+ *     which each chunk starts is recorded, so hub rows and runs of short rows are balanced;
  *   - for large power-law matrices with f a multiple of 64 (or exactly 32 or 16): the entries
  *     of long rows are copied
  *     into the workspace re-ordered by column slab ("slab sweep"), so that all wavefronts of an

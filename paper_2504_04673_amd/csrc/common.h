@@ -36,8 +36,15 @@ inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // --- SpMM workspace geometry (host and device agree through these) -----------------------
-// Entries per chunk of the nonzero-splitting schedule.  One wavefront owns one chunk.
-constexpr int kSpmmChunk = 256;
+// Chunks of the nonzero-splitting schedule: about T entries each, T a multiple of 16.  Long enough that what a
+// chunk costs besides its entries does not count, short enough that small matrices fill the chip: 8192 wavefronts
+// (32 per CU) of 64 / lanes-per-entry chunks.  Serial sums stay below 1.5 T = 192 terms.
+constexpr int kSpmmChunkMax = 128;
+inline int64_t spmm_chunk_entries(int64_t nnz, int32_t f) {
+  const int64_t groups = f <= 16 ? 16 : (f <= 32 ? 8 : (f <= 64 ? 4 : (f <= 128 ? 2 : 1)));
+  const int64_t t = (nnz / (8192 * groups) + 15) / 16 * 16;
+  return t < 16 ? 16 : (t > kSpmmChunkMax ? kSpmmChunkMax : t);
+}
 constexpr uint32_t kSpmmMagic = 0x53A66E02u;
 
 // Slab-sweep schedule (long rows): a wavefront owns kSweepSlots row pieces.
@@ -81,16 +88,26 @@ static_assert(sizeof(SpmmWsHeader) <= 256, "header must fit its slot");
 
 // Fixed layout (a function of m, k, nnz, f only; every array has its worst-case size):
 struct SpmmWsLayout {
-  size_t header, chunk_row, flags, rowptr_s, rowmap_s, code, vals, piece_info, piece_target,
+  size_t header, chunks, fix_list, flags, rowptr_s, rowmap_s, code, vals, piece_info, piece_target,
       wave_base, wave_steps, sync_off, barrier, sched, multi_row, multi_first, partial, carry, plan, wpack, total;
   int64_t max_chunks, max_pieces, max_waves, max_multi_rows, max_multi_pieces, stream_cap;
 };
 
-inline int64_t spmm_nchunks(int64_t nnz) { return ceil_div(nnz, kSpmmChunk); }
+inline int64_t spmm_nchunks(int64_t nnz, int64_t T) { return ceil_div(nnz, T); }
 
 inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
   SpmmWsLayout L{};
-  L.max_chunks = spmm_nchunks(nnz) + 1;
+  {
+    // T grows with the count, so a part of the entries (the short rows of a sweep) may be cut finer than all of them
+    const int64_t T = spmm_chunk_entries(nnz, f);
+    L.max_chunks = spmm_nchunks(nnz, T) + 1;
+    for (int64_t t = 16; t < T; t += 16) {   // the most entries that get chunks of t
+      const int64_t groups = f <= 16 ? 16 : (f <= 32 ? 8 : (f <= 64 ? 4 : (f <= 128 ? 2 : 1)));
+      const int64_t most = (t + 1) * 8192 * groups;
+      const int64_t chunks = (most < nnz ? most : nnz) / t + 2;
+      if (chunks > L.max_chunks) L.max_chunks = chunks;
+    }
+  }
   // every long row has >= kSweepMinLong entries; splitting adds at most nnz/1024 pieces; every
   // short row may become a piece of its own (whole-row wavefronts behind those of the long rows)
   const int64_t long_pieces = nnz / kSweepMinLong + nnz / 1024 + kSweepSlots;
@@ -105,12 +122,13 @@ inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
   // wavefront) also to the longest of its group streams inside every interval.  If a pattern
   // needs more than this, the planner lays the streams out as one interval.  A whole-row
   // wavefront has one interval: at most 8 steps of padding for each of its up to 4 group streams.
-  L.stream_cap = nnz + nnz / 4 + 256 * long_waves + 32 * short_waves + 4 * kSpmmChunk;
+  L.stream_cap = nnz + nnz / 4 + 256 * long_waves + 32 * short_waves + 1024;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };
   L.header = take(256);
-  L.chunk_row = take(sizeof(int32_t) * (size_t)(L.max_chunks + 1));
-  L.flags = take((size_t)L.max_chunks * (kSpmmChunk / 8));
+  L.chunks = take(4 * sizeof(int32_t) * (size_t)L.max_chunks);
+  L.fix_list = take(2 * sizeof(int32_t) * (size_t)L.max_chunks);
+  L.flags = take(sizeof(uint32_t) * (size_t)(nnz / 32 + 4));
   L.rowptr_s = take(sizeof(int32_t) * (size_t)(m + 1));
   L.rowmap_s = take(sizeof(int32_t) * (size_t)(m + 1));
   L.code = take(sizeof(uint32_t) * (size_t)L.stream_cap);
@@ -143,6 +161,7 @@ struct SpmmHostDesc {
   int64_t m, nnz;
   int32_t f, mode;
   int64_t c_rows, c_nnz, c_nchunks;
+  int64_t n_fix, n_fix_big; // rows whose shares the carry fix-up adds: with few, with many chunks
   int64_t n_waves, n_multi_rows, sweep_stream_len;
   int32_t has_empty_rows;
   int32_t groups;
@@ -178,6 +197,21 @@ void spmm_desc_erase(const void* ws);
 int launch_spmm(const int32_t* rowptr, const int32_t* colidx, const float* val, int64_t m,
                 int64_t k, int64_t nnz, const float* B, int64_t ldb, int32_t f, float* C,
                 int64_t ldc, int32_t accumulate, void* ws, size_t ws_bytes, hipStream_t s);
+
+// nonzero-splitting part (spmm_flat.hip)
+struct FlatArgs {
+  int64_t rows, nnz, nchunks;          // of the CSR being walked
+  const int32_t* colidx; const float* val; const float* B; int64_t ldb; uint32_t kmax;
+  float* C; int64_t ldc; int32_t accumulate;
+  const SpmmWsHeader* hdr; uint64_t generation;
+  const int4* chunks; const uint32_t* flags; float* carry; int64_t carry_ld; const int32_t* rowmap;
+};
+// d_stat (4 ints of device memory): [0] 1 if some row is empty, [1] / [2] rows on the front / back fix-up list
+int flat_build_tables(const int32_t* d_rowptr, int64_t rows, int64_t nnz, int64_t T, char* ws, const SpmmWsLayout& L,
+                      int32_t* d_stat, hipStream_t s);
+int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s);   // columns [col0, col0 + fw), fw <= 256
+int flat_fixup(const FlatArgs& a, const int2* list, int64_t list_cap, int64_t n_small, int64_t n_big, int32_t f_total,
+               hipStream_t s);
 
 // slab-sweep part (spmm_sweep.hip)
 struct SweepPlanResult {

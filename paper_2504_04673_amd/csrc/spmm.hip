@@ -1,25 +1,10 @@
 // Local CSR x tall-skinny dense product  C (+)= A * B  (Alg. 1 / Alg. 2, the statement
 // "Z <- Z + SpMM(A_iq, H^)"; Sec. 4.1 block-sum equation).  fp32 FMA on the vector ALUs.
 //
-// Schedule: nonzero splitting.  The nnz stored entries are cut into chunks of kSpmmChunk
-// consecutive entries; one wavefront owns one chunk, whatever rows it covers, so a hub row of
-// a power-law graph is spread over many wavefronts and a run of short rows shares one.
-// Because the sparsity pattern is fixed for the whole training run, spmm_csr_prepare() records
-// once (a) the row in which each chunk starts and (b) one bit per entry telling whether the
-// entry is the last of its row.  The product kernel then walks its chunk as a flat stream:
-// the column indices and values of a batch are wavefront-uniform (scalar loads), the 64
-// lanes split the f columns of the dense row (coalesced 64*FPL*4-byte reads along f), all
-// loads of a batch are issued before the first FMA, and a set "row end" bit flushes the
-// accumulator to C.  A row that started in an earlier chunk is flushed to a per-chunk carry
-// slot instead; a second small kernel adds the carries to C in chunk order, so the result is
-// reproducible (no floating-point atomics).
-//
-// Narrow matrices (f < 64) use sub-wavefront groups: G = f/4 lanes (rounded up to a power of
-// two) read one dense row as float4 pieces, and 64/G entries are processed per step; a row
-// end inside a step triggers a cross-group butterfly reduction.
-//
-// Widths other than 64/128/256 are processed as column slabs of those widths plus a narrow
-// remainder.
+// This file holds the entry points, the preparation, the dispatch between the schedules (nonzero splitting:
+// spmm_flat.hip; slab sweep: spmm_sweep.hip; dense tiles: tiles.hip), the kernel of accumulating calls over
+// chunks, the kernel without a workspace and the layer's rows that the sweep leaves over.
+// Operands wider than 256 are processed as column slabs.
 #include <stdlib.h>
 
 
@@ -29,7 +14,6 @@
 namespace sagnn {
 namespace {
 
-constexpr int kT = kSpmmChunk;
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlock = kWavesPerBlock * 64;
 
@@ -51,28 +35,20 @@ __device__ __forceinline__ bool ws_matches(const SpmmWsHeader* __restrict__ hdr,
          hdr->c_nnz == d.nnz && hdr->c_nchunks == d.nchunks;
 }
 
-__device__ __forceinline__ int next_row(int r, bool has_empty, const int32_t* __restrict__ rowptr,
-                                        int64_t m) {
-  ++r;
-  if (has_empty)
-    while (r < m - 1 && rowptr[r + 1] == rowptr[r]) ++r;
-  return r;
-}
-
 #define SPMM_PTR_PARAMS                                                                     \
   const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,                   \
       const float *__restrict__ val, const float *__restrict__ B, float *__restrict__ C,    \
-      const SpmmWsHeader *__restrict__ hdr, const int32_t *__restrict__ chunk_row,          \
+      const SpmmWsHeader *__restrict__ hdr, const int4 *__restrict__ chunks,                \
       const uint32_t *__restrict__ flags, float *__restrict__ carry_base,                   \
       const int32_t *__restrict__ rowmap
 
 // ------------------------------------------------------------------------------------------
-// wide kernel: f == 64 * FPL, one entry per wavefront load.
-// Per batch of U entries: U dense-row loads are issued back to back (their column indices and
-// values are already in scalar registers), then the scalar loads of the NEXT batch, then the
-// FMAs with a uniform branch at every row end.
-template <int FPL, int U, bool BUF, bool AHEAD>
-__global__ __launch_bounds__(kBlock) void spmm_wide_kernel(SPMM_PTR_PARAMS, const SpmmDims d) {
+// Accumulating calls (the per-stage sums of Alg. 2) at f == 64 * FPL: one chunk per wavefront, one entry per load.
+// They read the old row of C at every row end; with short rows that read would sit on the critical path once per row,
+// so the rows that end inside a batch of U entries are fetched together with the batch's rows of B.  (Column ids and
+// values of a batch are wavefront-uniform: scalar loads.)
+template <int FPL, int U, bool BUF>
+__global__ __launch_bounds__(kBlock) void spmm_wide_accumulate_kernel(SPMM_PTR_PARAMS, const SpmmDims d) {
   using vec = typename Vec<FPL>::T;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t loff = lane * (FPL * 4);  // byte offset of this lane's columns inside a row
@@ -80,41 +56,31 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_kernel(SPMM_PTR_PARAMS, cons
   const int64_t k = (int64_t)blockIdx.x * kWavesPerBlock + wave;
   if (k >= d.nchunks) return;
   if (!ws_matches(hdr, d)) return;
-  const bool has_empty = hdr->has_empty_rows != 0 && rowmap == nullptr;
-  const int32_t e0 = (int32_t)(k * kT);
-  const int32_t e1 = (int32_t)((d.nnz - e0 < kT) ? d.nnz : e0 + kT);
-  int r = chunk_row[k];
-  r = r < 0 ? 0 : (r > d.m - 1 ? (int)(d.m - 1) : r);
-  bool head = rowptr[r] < e0;  // first row began in an earlier chunk -> carry slot
-  const uint32_t* __restrict__ fl = flags + (e0 >> 5);
+  const int4 ch = chunks[k];
+  const int32_t e0 = ch.x < 0 ? 0 : ch.x;
+  const int32_t e1 = ch.y > d.nnz ? (int32_t)d.nnz : ch.y;
+  if (e0 >= e1) return;
+  int r = ch.z;
+  bool head = ch.w & 1;  // first row began in an earlier chunk -> carry slot
   char* __restrict__ carry = reinterpret_cast<char*>(carry_base + k * d.carry_ld) + loff;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
+  auto c_row = [&](int rr) -> vec* {
+    const int rc = rr < 0 ? 0 : (rr < d.m ? rr : (int)(d.m - 1));
+    const int64_t ro = rowmap ? rowmap[rc] : rc;
+    return reinterpret_cast<vec*>(reinterpret_cast<char*>(C + ro * d.ldc) + loff);
+  };
 
   vec acc = 0.f;
-  // `old` = the current contents of the row of C when they were fetched ahead (accumulating
-  // calls), otherwise they are read here
-  auto flush = [&](const vec old, const bool have_old) {
-    if (r >= d.m) return;  // cannot happen with a consistent rowptr; keeps stores in bounds
-    if (head) {
-      *reinterpret_cast<vec*>(carry) = acc;
-      head = false;
-    } else {
-      const int64_t ro = rowmap ? rowmap[r] : r;
-      vec* p = reinterpret_cast<vec*>(reinterpret_cast<char*>(C + ro * d.ldc) + loff);
-      if (d.accumulate) acc += have_old ? old : *p;
-      *p = acc;
+  auto flush = [&](const vec old) {
+    if (r < d.m) {
+      if (head) *reinterpret_cast<vec*>(carry) = acc;
+      else *c_row(r) = acc + old;
     }
+    head = false;
     acc = 0.f;
-    r = next_row(r, has_empty, rowptr, d.m);
+    ++r;
   };
-  // Accumulating calls (the per-stage sums of Alg. 2) read the old row of C at every row end.
-  // With short rows that read would sit on the critical path once per row, so the rows that
-  // end inside a batch are fetched together with the batch's rows of B.  (Rows are consecutive
-  // in the row list unless empty rows are being stepped over.)
-  // (AHEAD is chosen by the launcher for accumulating calls that walk a row list without empty rows.)
-  const bool ahead = AHEAD && d.accumulate != 0 && !has_empty;
-
-  // entry e of the chunk, clamped so that the (only) partial chunk never reads past nnz
+  // entry e of the chunk, clamped so that the last batch never reads past the chunk
   auto fetch = [&](int32_t e, int32_t (&c)[U], float (&v)[U]) {
     if (e + U <= e1) {
 #pragma unroll
@@ -135,10 +101,10 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_kernel(SPMM_PTR_PARAMS, cons
   int32_t c[U];
   float v[U];
   fetch(e0, c, v);
-  for (int b = 0; b < kT / U; ++b) {
-    const int32_t e = e0 + b * U;
-    if (e >= e1) break;
-    const uint32_t fbits = (fl[(b * U) >> 5] >> ((b * U) & 31)) & (uint32_t)((1ull << U) - 1ull);
+  for (int32_t e = e0; e < e1; e += U) {
+    const uint64_t two = (uint64_t)flags[e >> 5] | ((uint64_t)flags[(e >> 5) + 1] << 32);
+    uint32_t fbits = (uint32_t)(two >> (e & 31)) & ((1u << U) - 1u);
+    if (e + U > e1) fbits &= (1u << (e1 - e)) - 1u;
     vec h[U];
     float vc[U];
 #pragma unroll
@@ -147,21 +113,14 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_kernel(SPMM_PTR_PARAMS, cons
       h[u] = load_row<FPL, BUF>(rs, B, cc, loff, d.row_bytes, d.ldb);
       vc[u] = v[u];
     }
-    vec cold[AHEAD ? U : 1];
+    vec cold[U];
 #pragma unroll
-    for (int u = 0; u < (AHEAD ? U : 1); ++u) cold[u] = 0.f;
-    if (AHEAD && ahead && fbits) {
+    for (int u = 0; u < U; ++u) cold[u] = 0.f;
+    if (fbits) {
       int rr = r;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if ((fbits >> u) & 1u) {
-          const int rc = rr < d.m ? rr : (int)(d.m - 1);
-          const int64_t ro = rowmap ? rowmap[rc] : rc;
-          cold[AHEAD ? u : 0] =
-              *reinterpret_cast<const vec*>(reinterpret_cast<const char*>(C + ro * d.ldc) + loff);
-          ++rr;
-        }
-      }
+      for (int u = 0; u < U; ++u)
+        if ((fbits >> u) & 1u) cold[u] = *c_row(rr++);
     }
     if (e + U < e1) fetch(e + U, c, v);
     // keep the U loads above together (the compiler would otherwise sink each one next to its use)
@@ -170,167 +129,12 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_kernel(SPMM_PTR_PARAMS, cons
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       acc += vc[u] * h[u];
-      if ((fbits >> u) & 1u) flush(cold[AHEAD ? u : 0], ahead);
+      if ((fbits >> u) & 1u) flush(cold[u]);
     }
   }
   const int32_t last = e1 - 1;
   const bool closed = (flags[last >> 5] >> (last & 31)) & 1u;
-  if (!closed) flush(vec(0.f), false);  // the row continues in the next chunk: store the partial sum
-}
-
-// ------------------------------------------------------------------------------------------
-// narrow kernel: f <= 64 (G lanes x float4 per entry, P = 64/G entries per step)
-typedef float vec4 __attribute__((ext_vector_type(4)));
-
-template <int G>
-__device__ __forceinline__ vec4 group_sum(vec4 t) {
-#pragma unroll
-  for (int dlt = G; dlt < 64; dlt <<= 1) {
-    t.x += __shfl_xor(t.x, dlt, 64);
-    t.y += __shfl_xor(t.y, dlt, 64);
-    t.z += __shfl_xor(t.z, dlt, 64);
-    t.w += __shfl_xor(t.w, dlt, 64);
-  }
-  return t;
-}
-
-template <int G, int U>
-__global__ __launch_bounds__(kBlock) void spmm_narrow_kernel(SPMM_PTR_PARAMS, const SpmmDims d) {
-  constexpr int P = 64 / G;
-  static_assert(P <= 32 && P >= 1, "group size");
-  const int lane = threadIdx.x & 63;
-  const int g = lane / G, li = lane % G;
-  const bool active = li * 4 < d.f;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t k = (int64_t)blockIdx.x * kWavesPerBlock + wave;
-  if (k >= d.nchunks) return;
-  if (!ws_matches(hdr, d)) return;
-  const bool has_empty = hdr->has_empty_rows != 0 && rowmap == nullptr;
-  const int32_t e0 = (int32_t)(k * kT);
-  const int32_t e1 = (int32_t)((d.nnz - e0 < kT) ? d.nnz : e0 + kT);
-  int r = chunk_row[k];
-  r = r < 0 ? 0 : (r > d.m - 1 ? (int)(d.m - 1) : r);
-  bool head = rowptr[r] < e0;
-  const float* __restrict__ Bl = B + li * 4;
-  float* __restrict__ Cl = C + li * 4;
-  float* __restrict__ carry = carry_base + k * d.carry_ld + li * 4;
-  vec4 acc = 0.f;
-
-  auto emit = [&](vec4 t) {  // t: this lane's contribution to the row that ends / is cut here
-    t = group_sum<G>(t);
-    if (r >= d.m) return;  // cannot happen with a consistent rowptr; keeps stores in bounds
-    if (head) {
-      if (g == 0 && active) *reinterpret_cast<vec4*>(carry) = t;
-      head = false;
-    } else if (g == 0 && active) {
-      const int64_t ro = rowmap ? rowmap[r] : r;
-      vec4* p = reinterpret_cast<vec4*>(Cl + ro * d.ldc);
-      if (d.accumulate) t += *p;
-      *p = t;
-    }
-    r = next_row(r, has_empty, rowptr, d.m);
-  };
-
-  constexpr int kSteps = kT / P;
-  for (int s0 = 0; s0 < kSteps; s0 += U) {
-    if (e0 + s0 * P >= e1) break;
-    // the batch's U*P (<= 64) column ids and values arrive with one coalesced load each (lane l
-    // takes the l-th entry of the batch); a step's group then picks its entry with a lane
-    // permute, which keeps the vector-memory pipeline for the gathers of B
-    static_assert(U * P <= 64, "a batch must fit one wavefront-wide load");
-    const int32_t mine = e0 + s0 * P + lane;
-    const bool have = lane < U * P && mine < e1;
-    const int32_t cb = have ? colidx[mine] : 0;
-    const float vb = have ? val[mine] : 0.f;
-    int32_t c[U];
-    float v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      c[u] = __shfl(cb, u * P + g, 64);
-      v[u] = __shfl(vb, u * P + g, 64);
-    }
-    vec4 h[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t cc = (uint32_t)c[u] > d.kmax ? d.kmax : (uint32_t)c[u];
-      h[u] = 0.f;
-      if (active) h[u] = *reinterpret_cast<const vec4*>(Bl + (int64_t)cc * d.ldb);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int32_t es = e0 + (s0 + u) * P;  // uniform
-      if (es < e1) {
-        uint32_t fm = (flags[es >> 5] >> (es & 31)) & (uint32_t)((1ull << P) - 1ull);
-        const vec4 prod = v[u] * h[u];
-        if (fm == 0) {
-          acc += prod;
-        } else {
-          int lo = 0;
-          while (fm) {
-            const int j = __builtin_ctz(fm);
-            fm &= fm - 1;
-            vec4 t = acc;
-            if (g >= lo && g <= j) t += prod;
-            emit(t);
-            acc = 0.f;
-            lo = j + 1;
-          }
-          if (g >= lo) acc = prod;
-        }
-      }
-    }
-  }
-  const int32_t last = e1 - 1;
-  const bool closed = (flags[last >> 5] >> (last & 31)) & 1u;
-  if (!closed) emit(acc);
-}
-
-// ------------------------------------------------------------------------------------------
-// carries: chunk k holds a carry iff its first row began before the chunk.  The first such
-// chunk of a row ("leader") sums the carries of all following chunks of the same row in a
-// fixed order and adds them to C.
-__global__ __launch_bounds__(kBlock) void spmm_fixup_kernel(SPMM_PTR_PARAMS, const SpmmDims d,
-                                                            int32_t f_total) {
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t k = (int64_t)blockIdx.x * kWavesPerBlock + wave;
-  if (k >= d.nchunks || k == 0) return;
-  if (!ws_matches(hdr, d)) return;
-  int R = chunk_row[k];
-  if (R < 0 || R >= d.m) return;
-  const int64_t begin = rowptr[R];
-  if (begin >= k * kT) return;               // no carry in this chunk
-  if (begin < (k - 1) * kT) return;          // an earlier chunk leads this row
-  int64_t kend = k + 1;
-  while (kend < d.nchunks && chunk_row[kend] == R) ++kend;
-  for (int c4 = lane; c4 * 4 < f_total; c4 += 64) {
-    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f), s1 = s0, s2 = s0, s3 = s0;
-    int64_t j = k;
-    for (; j + 4 <= kend; j += 4) {
-      const float4 t0 = *reinterpret_cast<const float4*>(carry_base + (j + 0) * d.carry_ld + c4 * 4);
-      const float4 t1 = *reinterpret_cast<const float4*>(carry_base + (j + 1) * d.carry_ld + c4 * 4);
-      const float4 t2 = *reinterpret_cast<const float4*>(carry_base + (j + 2) * d.carry_ld + c4 * 4);
-      const float4 t3 = *reinterpret_cast<const float4*>(carry_base + (j + 3) * d.carry_ld + c4 * 4);
-      s0.x += t0.x; s0.y += t0.y; s0.z += t0.z; s0.w += t0.w;
-      s1.x += t1.x; s1.y += t1.y; s1.z += t1.z; s1.w += t1.w;
-      s2.x += t2.x; s2.y += t2.y; s2.z += t2.z; s2.w += t2.w;
-      s3.x += t3.x; s3.y += t3.y; s3.z += t3.z; s3.w += t3.w;
-    }
-    for (; j < kend; ++j) {
-      const float4 t0 = *reinterpret_cast<const float4*>(carry_base + j * d.carry_ld + c4 * 4);
-      s0.x += t0.x; s0.y += t0.y; s0.z += t0.z; s0.w += t0.w;
-    }
-    const int64_t ro = rowmap ? rowmap[R] : R;
-    float4* p = reinterpret_cast<float4*>(C + ro * d.ldc + c4 * 4);
-    float4 o = *p;
-    o.x += (s0.x + s1.x) + (s2.x + s3.x);
-    o.y += (s0.y + s1.y) + (s2.y + s3.y);
-    o.z += (s0.z + s1.z) + (s2.z + s3.z);
-    o.w += (s0.w + s1.w) + (s2.w + s3.w);
-    *p = o;
-  }
+  if (!closed) flush(head ? vec(0.f) : *c_row(r));  // the row continues in the next chunk: store the partial sum
 }
 
 // rows without entries: C[r,:] = 0 when overwriting (no chunk ever visits them)
@@ -384,47 +188,6 @@ __global__ __launch_bounds__(kBlock) void spmm_row_kernel(SPMM_PTR_PARAMS, const
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// preparation
-__global__ __launch_bounds__(kBlock) void prep_clear_flags_kernel(uint32_t* flags, int64_t words) {
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += stride) flags[i] = 0;
-}
-
-// chunk_row[k] = last row r with rowptr[r] <= k*kT (the non-empty row that holds entry k*kT)
-__global__ __launch_bounds__(kBlock) void prep_chunks_kernel(const int32_t* __restrict__ rowptr,
-                                                             int64_t m, int64_t nchunks,
-                                                             int32_t* __restrict__ chunk_row) {
-  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (k > nchunks) return;
-  if (k == nchunks) {
-    chunk_row[k] = (int32_t)m;
-    return;
-  }
-  const int64_t target = k * kT;
-  int64_t lo = 0, hi = m;  // invariant: rowptr[lo] <= target; answer in [lo, hi)
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if ((int64_t)rowptr[mid] <= target) lo = mid; else hi = mid;
-  }
-  chunk_row[k] = (int32_t)lo;
-}
-
-__global__ __launch_bounds__(kBlock) void prep_rowend_kernel(const int32_t* __restrict__ rowptr,
-                                                             int64_t m, int64_t nnz,
-                                                             uint32_t* __restrict__ flags,
-                                                             int32_t* __restrict__ has_empty) {
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < m; r += stride) {
-    const int64_t b = rowptr[r], e = rowptr[r + 1];
-    if (e > b && e <= nnz && e >= 1) {
-      atomicOr(&flags[(e - 1) >> 5], 1u << ((e - 1) & 31));
-    } else if (e == b) {
-      *has_empty = 1;
-    }
-  }
-}
-
 inline unsigned capped_grid(int64_t blocks) {
   const int64_t cap = 256 * 64;
   if (blocks > cap) blocks = cap;
@@ -434,7 +197,7 @@ inline unsigned capped_grid(int64_t blocks) {
 
 struct SpmmPtrs {
   const int32_t* rowptr; const int32_t* colidx; const float* val; const float* B; float* C;
-  const SpmmWsHeader* hdr; const int32_t* chunk_row; const uint32_t* flags; float* carry;
+  const SpmmWsHeader* hdr; const int4* chunks; const uint32_t* flags; float* carry;
   const int32_t* rowmap;
 };
 
@@ -442,28 +205,7 @@ template <typename Kern, typename... Extra>
 inline void launch_waves(Kern kern, int64_t blocks, const SpmmPtrs& p, const SpmmDims& d,
                          hipStream_t s, Extra... extra) {
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kBlock), 0, s, p.rowptr, p.colidx, p.val,
-                     p.B, p.C, p.hdr, p.chunk_row, p.flags, p.carry, p.rowmap, d, extra...);
-}
-
-// chunk-table construction for a CSR (rowptr of `rows` rows, `nnz` entries)
-int build_chunk_tables(const int32_t* d_rowptr, int64_t rows, int64_t nnz, int32_t* chunk_row,
-                       uint32_t* flags, int32_t* d_has_empty, hipStream_t s) {
-  const int64_t nchunks = spmm_nchunks(nnz);
-  const int64_t words = nchunks * (kSpmmChunk / 32);
-  if (words > 0) {
-    hipLaunchKernelGGL(prep_clear_flags_kernel, dim3(capped_grid(ceil_div(words, kBlock))), dim3(kBlock),
-                       0, s, flags, words);
-    SAGNN_LAUNCH_CHECK();
-  }
-  if (rows > 0) {
-    hipLaunchKernelGGL(prep_chunks_kernel, dim3((unsigned)ceil_div(nchunks + 1, kBlock)), dim3(kBlock), 0,
-                       s, d_rowptr, rows, nchunks, chunk_row);
-    SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(prep_rowend_kernel, dim3(capped_grid(ceil_div(rows, kBlock))), dim3(kBlock), 0, s,
-                       d_rowptr, rows, nnz, flags, d_has_empty);
-    SAGNN_LAUNCH_CHECK();
-  }
-  return SAGNN_OK;
+                     p.B, p.C, p.hdr, p.chunks, p.flags, p.carry, p.rowmap, d, extra...);
 }
 
 }  // namespace
@@ -502,7 +244,6 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   d.m = m; d.nnz = nnz; d.ldb = ldb; d.ldc = ldc;
   d.kmax = k > 0 ? (uint32_t)(k - 1) : 0u;
   d.f = f; d.accumulate = accumulate;
-  d.nchunks = spmm_nchunks(nnz);
   d.carry_ld = f;
 
   if (!ws) {
@@ -539,10 +280,11 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   if (ws_bytes < L.total) return SAGNN_ECAPACITY;
   char* base = reinterpret_cast<char*>(ws);
   p.hdr = reinterpret_cast<const SpmmWsHeader*>(base + L.header);
-  p.chunk_row = reinterpret_cast<const int32_t*>(base + L.chunk_row);
+  p.chunks = reinterpret_cast<const int4*>(base + L.chunks);
   p.flags = reinterpret_cast<const uint32_t*>(base + L.flags);
   p.carry = reinterpret_cast<float*>(base + L.carry);
   d.generation = desc.generation;
+  d.nchunks = desc.c_nchunks;
 
   if (!accumulate && desc.has_empty_rows) {
     launch_waves(spmm_zero_empty_kernel, capped_grid(ceil_div(m, kWavesPerBlock)), p, d, s, f);
@@ -558,7 +300,7 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
     p.rowmap = reinterpret_cast<const int32_t*>(base + L.rowmap_s);
     p.colidx = reinterpret_cast<const int32_t*>(base + L.code) + short_base;
     p.val = reinterpret_cast<const float*>(base + L.vals) + short_base;
-    d.m = desc.c_rows; d.nnz = desc.c_nnz; d.nchunks = desc.c_nchunks;
+    d.m = desc.c_rows; d.nnz = desc.c_nnz;
   } else if (desc.c_rows != m) {
     // empty rows were taken out of the row list when the workspace was prepared
     p.rowptr = reinterpret_cast<const int32_t*>(base + L.rowptr_s);
@@ -566,46 +308,48 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
     d.m = desc.c_rows;
   }
 
-  const int64_t blocks = ceil_div(d.nchunks, kWavesPerBlock);
+  FlatArgs fl{};
+  fl.rows = d.m; fl.nnz = d.nnz; fl.nchunks = d.nchunks; fl.colidx = p.colidx; fl.val = p.val; fl.B = B; fl.ldb = ldb;
+  fl.kmax = d.kmax; fl.C = C; fl.ldc = ldc; fl.accumulate = accumulate; fl.hdr = p.hdr; fl.generation = d.generation;
+  fl.chunks = p.chunks; fl.flags = p.flags; fl.carry = p.carry; fl.carry_ld = f; fl.rowmap = p.rowmap;
   const int32_t max_slab = desc.mode == 1 && desc.max_slab == 128 ? 128 : 256;
-  // column slabs: 256 / 128 / 64 wide through the wide kernels, the rest through the narrow one
+  // column slabs: the sweep's kernels are 256, 128 or 64 wide (32 and 16 exactly), those of the chunks up to 256
   int32_t col0 = 0;
   while (col0 < f) {
     const int32_t rest = f - col0;
-    SpmmPtrs sp = p;
-    SpmmDims sd = d;
-    sp.B = B + col0; sp.C = C + col0; sp.carry = p.carry + col0;
-    sd.f = rest >= 256 && max_slab >= 256 ? 256 : (rest >= 128 ? 128 : (rest >= 64 ? 64 : rest));
-    const bool buf = buffer_addressable(d.kmax, ldb, sd.f, &sd.b_bytes);
-    sd.row_bytes = (uint32_t)(ldb * 4);
+    int32_t fw = rest >= 256 ? 256 : rest;
     if (desc.mode == 1) {
-      int rc = sweep_launch(desc, L, base, B, ldb, col0, sd.f, d.kmax, C, ldc, accumulate, f, s);
+      fw = rest >= 256 && max_slab >= 256 ? 256 : (rest >= 128 ? 128 : (rest >= 64 ? 64 : rest));
+      int rc = sweep_launch(desc, L, base, B, ldb, col0, fw, d.kmax, C, ldc, accumulate, f, s);
       if (rc != SAGNN_OK) return rc;
     }
     if (d.nchunks > 0) {
-      // accumulating calls over a row list without empty rows fetch the old rows of C ahead
-      const bool ahead = accumulate != 0 && !(desc.has_empty_rows && sp.rowmap == nullptr);
-#define SAGNN_WIDE(FPL_, BUF_)                                                              \
-  (ahead ? launch_waves(spmm_wide_kernel<FPL_, 8, BUF_, true>, blocks, sp, sd, s)           \
-         : launch_waves(spmm_wide_kernel<FPL_, 8, BUF_, false>, blocks, sp, sd, s))
-      if (sd.f == 256 && buf) SAGNN_WIDE(4, true);
-      else if (sd.f == 256) SAGNN_WIDE(4, false);
-      else if (sd.f == 128 && buf) SAGNN_WIDE(2, true);
-      else if (sd.f == 128) SAGNN_WIDE(2, false);
-      else if (sd.f == 64 && buf) SAGNN_WIDE(1, true);
-      else if (sd.f == 64) SAGNN_WIDE(1, false);
+      if (accumulate && (fw == 64 || fw == 128 || fw == 256)) {
+        SpmmPtrs sp = p;
+        SpmmDims sd = d;
+        sp.B = B + col0; sp.C = C + col0; sp.carry = p.carry + col0;
+        sd.f = fw;
+        sd.row_bytes = (uint32_t)(ldb * 4);
+        const bool buf = buffer_addressable(d.kmax, ldb, fw, &sd.b_bytes);
+        const int64_t blocks = ceil_div(d.nchunks, kWavesPerBlock);
+#define SAGNN_WIDE(FPL_)                                                                        \
+  (buf ? launch_waves(spmm_wide_accumulate_kernel<FPL_, 8, true>, blocks, sp, sd, s)            \
+       : launch_waves(spmm_wide_accumulate_kernel<FPL_, 8, false>, blocks, sp, sd, s))
+        if (fw == 256) SAGNN_WIDE(4);
+        else if (fw == 128) SAGNN_WIDE(2);
+        else SAGNN_WIDE(1);
 #undef SAGNN_WIDE
-      else if (rest > 32) launch_waves(spmm_narrow_kernel<16, 4>, blocks, sp, sd, s);
-      else if (rest > 16) launch_waves(spmm_narrow_kernel<8, 4>, blocks, sp, sd, s);
-      else if (rest > 8) launch_waves(spmm_narrow_kernel<4, 4>, blocks, sp, sd, s);
-      else launch_waves(spmm_narrow_kernel<2, 2>, blocks, sp, sd, s);
-      SAGNN_LAUNCH_CHECK();
+        SAGNN_LAUNCH_CHECK();
+      } else {
+        int rc = flat_launch(fl, col0, fw, s);
+        if (rc != SAGNN_OK) return rc;
+      }
     }
-    col0 += sd.f;
+    col0 += fw;
   }
-  if (d.nchunks > 1) {
-    launch_waves(spmm_fixup_kernel, blocks, p, d, s, f);
-    SAGNN_LAUNCH_CHECK();
+  {
+    int rc = flat_fixup(fl, reinterpret_cast<const int2*>(base + L.fix_list), L.max_chunks, desc.n_fix, desc.n_fix_big, f, s);
+    if (rc != SAGNN_OK) return rc;
   }
   if (desc.mode == 1) {
     int rc = sweep_combine(desc, L, base, C, ldc, f, accumulate, s);
@@ -838,7 +582,13 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
     }
     // no tile is dense enough: the plain preparation below
   }
-  int32_t* d_has_empty = reinterpret_cast<int32_t*>(base + L.carry);  // scratch until the first product
+  int32_t* d_stat = reinterpret_cast<int32_t*>(base + L.carry);  // scratch until the first product
+  int32_t stat[4] = {0, 0, 0, 0};    // of flat_build_tables
+  auto read_stat = [&]() -> int {
+    SAGNN_HIP(hipMemcpyAsync(stat, d_stat, sizeof(stat), hipMemcpyDeviceToHost, s));
+    SAGNN_HIP(hipStreamSynchronize(s));
+    return SAGNN_OK;
+  };
 
   SweepPlanResult plan{};
   if ((f & 63) == 0 || f == 32 || f == 16) {
@@ -846,48 +596,48 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
     if (rc != SAGNN_OK) return rc;
   }
   SpmmWsHeader h{};
-  SAGNN_HIP(hipMemsetAsync(d_has_empty, 0, 4, s));   // set-up call: never recorded into a graph
   if (plan.use_sweep) {
     h = plan.hdr;
-    int rc = build_chunk_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), h.c_rows, h.c_nnz,
-                                reinterpret_cast<int32_t*>(base + L.chunk_row),
-                                reinterpret_cast<uint32_t*>(base + L.flags), d_has_empty, s);
-    if (rc != SAGNN_OK) return rc;
+    if (h.c_nchunks > 0) {
+      int rc = flat_build_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), h.c_rows, h.c_nnz,
+                                 spmm_chunk_entries(h.c_nnz, f), base, L, d_stat, s);
+      if (rc == SAGNN_OK) rc = read_stat();
+      if (rc != SAGNN_OK) return rc;
+    }
   } else {
     h.magic = kSpmmMagic;
     h.m = m; h.nnz = nnz; h.f = f; h.mode = 0;
     h.generation = spmm_next_generation();
-    h.c_rows = m; h.c_nnz = nnz; h.c_nchunks = spmm_nchunks(nnz);
-    int rc = build_chunk_tables(d_rowptr, m, nnz, reinterpret_cast<int32_t*>(base + L.chunk_row),
-                                reinterpret_cast<uint32_t*>(base + L.flags), d_has_empty, s);
+    const int64_t T = spmm_chunk_entries(nnz, f);
+    h.c_rows = m; h.c_nnz = nnz; h.c_nchunks = spmm_nchunks(nnz, T);
+    int rc = flat_build_tables(d_rowptr, m, nnz, T, base, L, d_stat, s);
+    if (rc == SAGNN_OK) rc = read_stat();
     if (rc != SAGNN_OK) return rc;
-    int32_t he = 0;
-    SAGNN_HIP(hipMemcpyAsync(&he, d_has_empty, 4, hipMemcpyDeviceToHost, s));
-    SAGNN_HIP(hipStreamSynchronize(s));
-    h.has_empty_rows = he;
-    if (he && nnz > 0) {
-      // Rows without entries (e.g. one column block of a row block, Alg. 2) would make a chunk's
-      // wavefront step over them one dependent load at a time.  Walk a row list without them
-      // instead: the same compacted-CSR form the short rows of the sweep schedule use.
+    h.has_empty_rows = stat[0];
+    if (stat[0] && nnz > 0) {
+      // Rows without entries (e.g. one column block of a row block, Alg. 2) would have to be stepped over one
+      // dependent load at a time.  Walk a row list without them instead: the same compacted-CSR form the short rows
+      // of the sweep schedule use.
       // The row pass of the sweep planner with a threshold no row reaches makes exactly that list
       // (every row with entries is "short").
       SweepRowTotals t{};
       rc = sweep_plan_rows(d_rowptr, m, nnz, 0x7FFFFFFF, 1024, base, L, s, &t);
       if (rc != SAGNN_OK) return rc;
       if (!t.bad && t.short_entries == nnz) {   // (a malformed row pointer keeps the plain walk, which clamps everything)
-        rc = build_chunk_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), t.short_rows, nnz,
-                                reinterpret_cast<int32_t*>(base + L.chunk_row),
-                                reinterpret_cast<uint32_t*>(base + L.flags), d_has_empty, s);
+        rc = flat_build_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), t.short_rows, nnz, T, base, L, d_stat, s);
+        if (rc == SAGNN_OK) rc = read_stat();
         if (rc != SAGNN_OK) return rc;
         h.c_rows = t.short_rows;
       }
     }
   }
+  if (stat[1] < 0 || stat[2] < 0 || (int64_t)stat[1] + stat[2] > L.max_chunks) return SAGNN_EFORMAT;   // (overlapping rows)
   SAGNN_HIP(hipMemcpyAsync(base + L.header, &h, sizeof(h), hipMemcpyHostToDevice, s));
   SAGNN_HIP(hipStreamSynchronize(s));
   SpmmHostDesc desc{};
   desc.generation = h.generation; desc.m = m; desc.nnz = nnz; desc.f = f; desc.mode = h.mode;
   desc.c_rows = h.c_rows; desc.c_nnz = h.c_nnz; desc.c_nchunks = h.c_nchunks;
+  desc.n_fix = stat[1]; desc.n_fix_big = stat[2];
   desc.n_waves = h.n_waves; desc.n_multi_rows = h.n_multi_rows; desc.has_empty_rows = h.has_empty_rows;
   desc.sweep_stream_len = h.n_long_entries;
   desc.groups = h.groups > 0 ? h.groups : 1;

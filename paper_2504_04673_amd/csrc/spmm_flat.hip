@@ -1,0 +1,457 @@
+// Nonzero-splitting schedule of the local SpMM, C (+)= A * B (Alg. 1 / Alg. 2, "Z <- Z + SpMM(A_iq, H^)"):
+// chunk tables (built once per matrix), product kernel, carry fix-up.
+//
+// The entries are cut into chunks of about T consecutive entries, T = 16 .. 128 chosen so that the chip is full
+// (spmm_chunk_entries).  A chunk ends at the row end nearest behind the multiple of T where there is one within 16 entries, so that
+// only rows that are long against T are shared by several chunks; the shares of such a row go to carry slots that a
+// second kernel adds in chunk order (reproducible, no floating-point atomics), and a matrix without such rows needs
+// no second kernel.
+//
+// Product kernel.  A group of LPE lanes (4, 8, .. 64: as many as hold a row of up to 4 LPE floats, 16 bytes a lane)
+// walks one chunk, so one load instruction serves 64 / LPE entries.  Column ids and values of 16 or 32 entries arrive
+// with one load each, spread over the lanes of a DPP unit (a quad below 16 lanes per entry, a row of 16 above), and are
+// handed to the whole group by DPP broadcasts that ride on the instructions that use them: per entry and
+// group one add for the address, one load, four multiply-adds.
+// Bound by: the latency of its dependent loads on small matrices (chunk, columns, rows of B: hence the short
+// chunks), by what the L2s do not hold of B on large ones (7.5 TB/s behind the L2s whatever the row length).
+// The kernels it replaces took 256 entries per wavefront, eight at a time: 30 k rows x 12 entries, f = 100: 64 -> 28 us;
+// 4 k x 8, f = 256: 29 -> 15 us.
+#include "common.h"
+#include "rowload.h"
+
+namespace sagnn {
+namespace {
+
+constexpr int kBlock = 256;
+constexpr int kWaves = kBlock / 64;
+typedef float vec4 __attribute__((ext_vector_type(4)));
+
+struct FlatDims {
+  int64_t m, nnz, nchunks, ldb, ldc, carry_ld;   // m, nnz: of the CSR being walked
+  uint64_t generation;
+  uint32_t b_bytes, row_bytes, kmax;
+  int32_t f, accumulate;
+};
+
+__device__ __forceinline__ bool ws_matches(const SpmmWsHeader* __restrict__ hdr, const FlatDims& d) {
+  return hdr->magic == kSpmmMagic && hdr->generation == d.generation && hdr->c_rows == d.m &&
+         hdr->c_nnz == d.nnz && hdr->c_nchunks == d.nchunks;
+}
+
+// value of lane S of the DPP unit (quad or row of 16) in all its lanes
+template <bool QUAD, int S>
+__device__ __forceinline__ uint32_t unit_bcast(uint32_t x) {
+  constexpr int ctrl = QUAD ? S * 0x55 : 0x150 + S;   // quad_perm:[S,S,S,S] / row_newbcast:S
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xF, 0xF, true);
+}
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+#define FLAT_PTR_PARAMS                                                                                          \
+  const int32_t *__restrict__ colidx, const float *__restrict__ val, const float *__restrict__ B,                \
+      float *__restrict__ C, const SpmmWsHeader *__restrict__ hdr, const int4 *__restrict__ chunks,              \
+      const uint32_t *__restrict__ flags, float *__restrict__ carry, const int32_t *__restrict__ rowmap
+
+// NC: entries a lane holds of a span (2 above quads; 8 in quads, so that whole lines of the entry arrays are used up
+// at once -- with 4 the lines are out of the L1 again before their second half is needed, 670 against 587 us on
+// 50 M entries at f = 16 -- or 4 where the chunks are shorter than such a span)
+template <int LPE, int NC, bool BUF>
+__global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, const FlatDims d) {
+  constexpr bool QUAD = LPE < 16;
+  constexpr int R = 64 / LPE;                // groups (chunks) per wavefront
+  constexpr int UNIT = QUAD ? 4 : 16;        // lanes of a DPP unit
+  constexpr int SPAN = UNIT * NC;            // entries per fetch of column ids and values
+  constexpr int U = 8;                       // rows of B in flight
+  const int lane = threadIdx.x & 63;
+  const int lig = lane % LPE, sub = lane % UNIT;
+  const bool active = lig * 4 < d.f;
+  const uint32_t loff = active ? lig * 16 : 0;     // (idle lanes read the row's first piece again)
+  if (!ws_matches(hdr, d)) return;
+  const int64_t wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6));
+  if (wave * R >= d.nchunks) return;
+  const int64_t k = wave * R + lane / LPE;
+  int4 ch = make_int4(0, 0, 0, 0);
+  if (k < d.nchunks) ch = chunks[k];
+  int32_t e0 = ch.x, e1 = ch.y, r = ch.z;
+  bool head = ch.w & 1;
+  // (nothing below trusts the tables: entries stay inside [0, nnz), rows inside [0, m))
+  e0 = e0 < 0 ? 0 : e0;
+  e1 = e1 > d.nnz ? (int32_t)d.nnz : e1;
+  const int32_t len = e1 > e0 ? e1 - e0 : 0;
+  int longest = len;
+#pragma unroll
+  for (int o = LPE; o < 64; o <<= 1) {
+    const int t = __shfl_xor(longest, o, 64);
+    longest = t > longest ? t : longest;
+  }
+  longest = __builtin_amdgcn_readfirstlane(longest);
+  const int32_t elast = len > 0 ? e1 - 1 : 0;
+  const int32_t rmax = (int32_t)(d.m - 1);
+  auto row_at = [&](int32_t i) {
+    const int32_t ii = i < 0 ? 0 : (i > rmax ? rmax : i);
+    return rowmap ? rowmap[ii] : ii;
+  };
+  int32_t rid = row_at(r);
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
+  const float* __restrict__ Bl = B + (active ? lig * 4 : 0);
+  float* __restrict__ Cl = C + lig * 4;
+  float* __restrict__ slot = carry + k * d.carry_ld + lig * 4;
+
+  vec4 acc = 0.f;
+  auto emit = [&]() {   // the row that ends (or is cut) here
+    if (active && r <= rmax) {
+      if (head) {
+        *reinterpret_cast<vec4*>(slot) = acc;
+      } else {
+        vec4* p = reinterpret_cast<vec4*>(Cl + (int64_t)rid * d.ldc);
+        if (d.accumulate) acc += *p;
+        *p = acc;
+      }
+    }
+    head = false;
+    acc = 0.f;
+    ++r;
+    rid = row_at(r);
+  };
+
+  // column ids, values and row ends of a span; those of the next one are requested before this one is worked on
+  uint32_t c[NC], cn[NC];
+  float v[NC], vn[NC];
+  uint64_t f2 = 0, f2n = 0;
+  auto fetch = [&](int base, uint32_t (&ci)[NC], float (&vi)[NC], uint64_t& fw) {
+    const int32_t mine = e0 + base + sub * NC;
+    // all groups have a whole span left: vector loads
+    if (__ballot(base + SPAN <= len) == ~0ull) {
+      constexpr int W = NC < 4 ? NC : 4;
+      struct __attribute__((packed, aligned(4))) iv { int32_t x[W]; };
+      struct __attribute__((packed, aligned(4))) fv { float x[W]; };
+#pragma unroll
+      for (int q = 0; q < NC / W; ++q) {
+        const iv ii = *reinterpret_cast<const iv*>(colidx + mine + q * W);
+        const fv ff = *reinterpret_cast<const fv*>(val + mine + q * W);
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+          ci[q * W + i] = (uint32_t)ii.x[i];
+          vi[q * W + i] = ff.x[i];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const bool in = mine + i < e1 && len > 0;
+        const int32_t ee = in ? mine + i : elast;
+        ci[i] = (uint32_t)colidx[ee];
+        vi[i] = in ? val[ee] : 0.f;
+      }
+    }
+    const int32_t fb = e0 + base < elast ? e0 + base : elast;   // (the flags array has two words of slack behind it)
+    fw = (uint64_t)flags[fb >> 5] | ((uint64_t)flags[(fb >> 5) + 1] << 32);
+  };
+  if (longest > 0) fetch(0, c, v, f2);
+
+  for (int base = 0; base < longest; base += SPAN) {
+    if (base + SPAN < longest) fetch(base + SPAN, cn, vn, f2n);
+    // row ends among the span's entries of this group
+    const int32_t fb = e0 + base < elast ? e0 + base : elast;
+    uint32_t fl = (uint32_t)(f2 >> (fb & 31));
+    const int left = len - base;
+    fl = left >= 32 ? fl : (left > 0 ? fl & ((1u << left) - 1u) : 0u);
+    uint32_t off[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      c[i] = c[i] > d.kmax ? d.kmax : c[i];
+      off[i] = BUF ? c[i] * d.row_bytes : 0u;
+    }
+    // bit s of `any`: some group's row ends at step s (lane j of a unit stands for its entries NC j .. NC j + NC - 1)
+    uint32_t any = 0;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      uint64_t b = __ballot((fl >> (sub * NC + i)) & 1u);
+      b |= b >> 32;
+      b |= b >> 16;
+      if constexpr (QUAD) {
+        b |= b >> 8;
+        b |= b >> 4;
+        // four bits, one per lane of the quad: spread to steps 0, NC, 2 NC, 3 NC
+        const uint32_t q = (uint32_t)b & 0xFu;
+        any |= ((q & 1u) | ((q & 2u) << (NC - 1)) | ((q & 4u) << (2 * NC - 2)) | ((q & 8u) << (3 * NC - 3))) << i;
+      } else {
+        uint32_t q = (uint32_t)b & 0xFFFFu;               // sixteen bits, spread to every other step
+        q = (q | (q << 8)) & 0x00FF00FFu;
+        q = (q | (q << 4)) & 0x0F0F0F0Fu;
+        q = (q | (q << 2)) & 0x33333333u;
+        q = (q | (q << 1)) & 0x55555555u;
+        any |= q << i;
+      }
+    }
+    any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
+    const int steps = longest - base;
+    static_for<0, SPAN / U>([&](auto ib) {
+      constexpr int s0 = decltype(ib)::value * U;
+      if (s0 >= steps) return;
+      vec4 h[U];
+      static_for<0, U>([&](auto iu) {
+        constexpr int s = s0 + decltype(iu)::value;
+        if constexpr (BUF) {
+          const uint32_t o = unit_bcast<QUAD, s / NC>(off[s % NC]) + loff;
+          h[s - s0] = __builtin_bit_cast(vec4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
+        } else {
+          const uint32_t col = unit_bcast<QUAD, s / NC>(c[s % NC]);
+          h[s - s0] = *reinterpret_cast<const vec4*>(Bl + (int64_t)col * d.ldb);
+        }
+      });
+#pragma unroll
+      for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
+      static_for<0, U>([&](auto iu) {
+        constexpr int s = s0 + decltype(iu)::value;
+        const float vs = __builtin_bit_cast(float, unit_bcast<QUAD, s / NC>(__builtin_bit_cast(uint32_t, v[s % NC])));
+        acc += vs * h[s - s0];
+        if ((any >> s) & 1u) {
+          asm volatile("");   // (a scalar branch first: the two tests are not to be merged)
+          if ((fl >> s) & 1u) emit();
+        }
+      });
+    });
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      c[i] = cn[i];
+      v[i] = vn[i];
+    }
+    f2 = f2n;
+  }
+  // a row that continues in the next chunk: its share so far
+  if (len > 0) {
+    const bool closed = (flags[elast >> 5] >> (elast & 31)) & 1u;
+    if (!closed) emit();
+  }
+}
+
+// Carries: a chunk that starts inside a row leaves its share of that row in its carry slot.  The chunks of a row
+// that do so follow each other; the list holds the first one of every such row.  Up to kFixWave chunks are added by
+// one wavefront, more (hub rows) by a workgroup; fixed order either way.
+constexpr int kFixWave = 32;
+
+struct FixDims {
+  int64_t nchunks, m, ldc, carry_ld;
+  uint64_t generation;
+  int32_t f_total;
+};
+
+template <bool WG>
+__global__ __launch_bounds__(kBlock) void flat_fixup_kernel(const SpmmWsHeader* __restrict__ hdr, const int4* __restrict__ chunks,
+                                                            const int2* __restrict__ list, int64_t n_list,
+                                                            const float* __restrict__ carry, const int32_t* __restrict__ rowmap,
+                                                            float* __restrict__ C, const FixDims d) {
+  __shared__ float4 part[WG ? kWaves : 1][64];
+  if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->c_nchunks != d.nchunks) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t q = WG ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kWaves + wave;
+  if (q >= n_list) return;                                   // (WG: the whole workgroup)
+  const int2 it = list[q];                                   // first chunk, number of chunks
+  const int64_t k = it.x;
+  int64_t cnt = it.y;
+  if (k < 0 || cnt <= 0 || k + cnt > d.nchunks) return;
+  const int32_t R = chunks[k].z;
+  if (R < 0 || R >= d.m) return;
+  const int64_t ro = rowmap ? rowmap[R] : R;
+  // share of this wavefront
+  const int64_t per = WG ? (cnt + kWaves - 1) / kWaves : cnt;
+  const int64_t a = WG ? wave * per : 0, b = a + per < cnt ? a + per : cnt;
+  for (int c0 = 0; c0 < d.f_total; c0 += 256) {
+    const int c4 = c0 + lane * 4;
+    const bool on = c4 < d.f_total;
+    float4 s[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (on) {
+      const float* p = carry + (k + a) * d.carry_ld + c4;
+      int64_t j = a;
+      for (; j + 8 <= b; j += 8, p += 8 * d.carry_ld) {
+        float4 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const float4*>(p + u * d.carry_ld);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          s[u & 3].x += t[u].x; s[u & 3].y += t[u].y; s[u & 3].z += t[u].z; s[u & 3].w += t[u].w;
+        }
+      }
+      for (; j < b; ++j, p += d.carry_ld) {
+        const float4 t = *reinterpret_cast<const float4*>(p);
+        s[0].x += t.x; s[0].y += t.y; s[0].z += t.z; s[0].w += t.w;
+      }
+    }
+    float4 t;
+    t.x = (s[0].x + s[1].x) + (s[2].x + s[3].x);
+    t.y = (s[0].y + s[1].y) + (s[2].y + s[3].y);
+    t.z = (s[0].z + s[1].z) + (s[2].z + s[3].z);
+    t.w = (s[0].w + s[1].w) + (s[2].w + s[3].w);
+    if constexpr (WG) {
+      __syncthreads();
+      part[wave][lane] = t;
+      __syncthreads();
+      if (wave != 0) continue;
+      for (int w = 1; w < kWaves; ++w) {
+        const float4 o = part[w][lane];
+        t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+      }
+    }
+    if (on) {
+      float4* p = reinterpret_cast<float4*>(C + ro * d.ldc + c4);
+      float4 o = *p;
+      o.x += t.x; o.y += t.y; o.z += t.z; o.w += t.w;
+      *p = o;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// tables
+__global__ __launch_bounds__(kBlock) void flat_clear_kernel(uint32_t* __restrict__ flags, int64_t words,
+                                                            int32_t* __restrict__ stat) {
+  const int64_t stride = (int64_t)gridDim.x * kBlock;
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += stride) flags[i] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 4) stat[threadIdx.x] = 0;
+}
+
+// flags: one bit per entry that ends a row; stat[0] = 1 if some row has no entries
+__global__ __launch_bounds__(kBlock) void flat_rowend_kernel(const int32_t* __restrict__ rowptr, int64_t m, int64_t nnz,
+                                                             uint32_t* __restrict__ flags, int32_t* __restrict__ stat) {
+  const int64_t stride = (int64_t)gridDim.x * kBlock;
+  for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < m; r += stride) {
+    const int64_t b = rowptr[r], e = rowptr[r + 1];
+    if (e > b && e <= nnz && e >= 1) atomicOr(&flags[(e - 1) >> 5], 1u << ((e - 1) & 31));
+    else if (e == b) stat[0] = 1;
+  }
+}
+
+// How far a boundary may move: the longest chunk of a wavefront's groups decides when it is done, so long chunks are
+// not allowed to differ by much (T / 2 at T = 128 cost 20 % at f = 16).
+__device__ __forceinline__ int64_t cut_slack(int64_t T) { return T / 2 < 16 ? T / 2 : 16; }
+
+struct Cut { int64_t at, row; bool head; };   // a chunk boundary: entry, row it lies in, whether it cuts that row
+
+__device__ __forceinline__ Cut chunk_cut(const int32_t* __restrict__ rowptr, int64_t m, int64_t nnz, int64_t T, int64_t k) {
+  Cut c{};
+  const int64_t target = k * T;
+  if (target >= nnz) return Cut{nnz, m, false};
+  int64_t lo = 0, hi = m;                     // last row r with rowptr[r] <= target (the row that holds it)
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)rowptr[mid] <= target) lo = mid; else hi = mid;
+  }
+  const int64_t b = rowptr[lo], e = rowptr[lo + 1];
+  if (b == target) return Cut{target, lo, false};
+  if (e > target && e <= nnz && e - target <= cut_slack(T)) {   // the row ends soon: the boundary moves behind it
+    // (the next row with entries starts there; rows without entries in between are stepped over)
+    int64_t r = lo + 1;
+    while (r < m - 1 && rowptr[r + 1] == rowptr[r]) ++r;
+    return Cut{e, r, false};
+  }
+  return Cut{target, lo, b < target};
+}
+
+// chunks[k] = {first entry, end, first row, 1 if the chunk starts inside a row}; rows whose later shares are carries
+// are appended to the lists (list order does not matter: every row has one writer)
+__global__ __launch_bounds__(kBlock) void flat_chunks_kernel(const int32_t* __restrict__ rowptr, int64_t m, int64_t nnz,
+                                                             int64_t T, int64_t nchunks, int4* __restrict__ chunks,
+                                                             int2* __restrict__ list, int64_t list_cap,
+                                                             int32_t* __restrict__ stat) {
+  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (k >= nchunks) return;
+  const Cut a = chunk_cut(rowptr, m, nnz, T, k), b = chunk_cut(rowptr, m, nnz, T, k + 1);
+  chunks[k] = make_int4((int32_t)a.at, (int32_t)b.at, (int32_t)a.row, a.head ? 1 : 0);
+  if (!a.head) return;
+  // the first carry of its row?
+  if (k > 0) {
+    const Cut p = chunk_cut(rowptr, m, nnz, T, k - 1);
+    if (p.head && p.row == a.row) return;
+  }
+  int64_t cnt = 1;                            // chunks that start inside the row: multiples of T below its end
+  const int64_t e = rowptr[a.row + 1];
+  // the last cut inside the row is the largest multiple of T more than the slack before its end
+  const int64_t last = (e - cut_slack(T) - 1) / T;
+  if (last > k) cnt = last - k + 1;
+  if (k + cnt > nchunks) cnt = nchunks - k;
+  const bool big = cnt > kFixWave;
+  const int32_t at = atomicAdd(&stat[big ? 2 : 1], 1);
+  // small ones from the front, big ones from the back
+  const int64_t pos = big ? list_cap - 1 - at : at;
+  if (pos >= 0 && pos < list_cap) list[pos] = make_int2((int32_t)k, (int32_t)cnt);
+}
+
+inline unsigned capped_grid(int64_t blocks) {
+  const int64_t cap = 256 * 64;
+  return (unsigned)(blocks > cap ? cap : (blocks < 1 ? 1 : blocks));
+}
+
+}  // namespace
+
+int flat_build_tables(const int32_t* d_rowptr, int64_t rows, int64_t nnz, int64_t T, char* ws, const SpmmWsLayout& L,
+                      int32_t* d_stat, hipStream_t s) {
+  const int64_t nchunks = spmm_nchunks(nnz, T);
+  uint32_t* flags = reinterpret_cast<uint32_t*>(ws + L.flags);
+  const int64_t words = nnz / 32 + 3;
+  hipLaunchKernelGGL(flat_clear_kernel, dim3(capped_grid(ceil_div(words, kBlock))), dim3(kBlock), 0, s, flags, words, d_stat);
+  SAGNN_LAUNCH_CHECK();
+  if (rows > 0) {
+    hipLaunchKernelGGL(flat_rowend_kernel, dim3(capped_grid(ceil_div(rows, kBlock))), dim3(kBlock), 0, s, d_rowptr, rows,
+                       nnz, flags, d_stat);
+    SAGNN_LAUNCH_CHECK();
+  }
+  if (rows > 0 && nchunks > 0) {
+    hipLaunchKernelGGL(flat_chunks_kernel, dim3((unsigned)ceil_div(nchunks, kBlock)), dim3(kBlock), 0, s, d_rowptr, rows,
+                       nnz, T, nchunks, reinterpret_cast<int4*>(ws + L.chunks), reinterpret_cast<int2*>(ws + L.fix_list),
+                       L.max_chunks, d_stat);
+    SAGNN_LAUNCH_CHECK();
+  }
+  return SAGNN_OK;
+}
+
+int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
+  FlatDims d{};
+  d.m = a.rows; d.nnz = a.nnz; d.nchunks = a.nchunks; d.ldb = a.ldb; d.ldc = a.ldc; d.carry_ld = a.carry_ld;
+  d.generation = a.generation; d.kmax = a.kmax; d.f = fw; d.accumulate = a.accumulate;
+  d.row_bytes = (uint32_t)(a.ldb * 4);
+  const bool buf = buffer_addressable(a.kmax, a.ldb, fw, &d.b_bytes);
+  auto go = [&](auto kern, int lpe) -> int {
+    const int64_t waves = ceil_div(a.nchunks, 64 / lpe);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(waves, kWaves)), dim3(kBlock), 0, s, a.colidx, a.val, a.B + col0,
+                       a.C + col0, a.hdr, a.chunks, a.flags, a.carry + col0, a.rowmap, d);
+    SAGNN_LAUNCH_CHECK();
+    return SAGNN_OK;
+  };
+#define SAGNN_FLAT(LPE_, NC_) (buf ? go(spmm_flat_kernel<LPE_, NC_, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, false>, LPE_))
+  const bool brief = a.nnz < 64 * a.nchunks;
+  if (fw <= 16) return brief ? SAGNN_FLAT(4, 4) : SAGNN_FLAT(4, 8);
+  if (fw <= 32) return brief ? SAGNN_FLAT(8, 4) : SAGNN_FLAT(8, 8);
+  if (fw <= 64) return SAGNN_FLAT(16, 2);
+  if (fw <= 128) return SAGNN_FLAT(32, 2);
+  return SAGNN_FLAT(64, 2);
+#undef SAGNN_FLAT
+}
+
+int flat_fixup(const FlatArgs& a, const int2* list, int64_t list_cap, int64_t n_small, int64_t n_big, int32_t f_total,
+               hipStream_t s) {
+  FixDims d{};
+  d.nchunks = a.nchunks; d.m = a.rows; d.ldc = a.ldc; d.carry_ld = a.carry_ld; d.generation = a.generation;
+  d.f_total = f_total;
+  if (n_small > 0) {
+    hipLaunchKernelGGL(flat_fixup_kernel<false>, dim3((unsigned)ceil_div(n_small, kWaves)), dim3(kBlock), 0, s, a.hdr,
+                       a.chunks, list, n_small, a.carry, a.rowmap, a.C, d);
+    SAGNN_LAUNCH_CHECK();
+  }
+  if (n_big > 0) {
+    hipLaunchKernelGGL(flat_fixup_kernel<true>, dim3((unsigned)n_big), dim3(kBlock), 0, s, a.hdr, a.chunks,
+                       list + (list_cap - n_big), n_big, a.carry, a.rowmap, a.C, d);
+    SAGNN_LAUNCH_CHECK();
+  }
+  return SAGNN_OK;
+}
+
+}  // namespace sagnn

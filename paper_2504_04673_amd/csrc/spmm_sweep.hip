@@ -1274,7 +1274,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
     if (h_flags[0] || h_flags[2]) return SAGNN_OK;   // unsorted long row, column out of range, pieces left over: plain schedule
     stream_len = h_total;
     short_base = (int64_t)round_up((size_t)stream_len + 64, 256);
-    const bool fits = !h_flags[1] && short_base + short_entries_csr + kSpmmChunk <= L.stream_cap;
+    const bool fits = !h_flags[1] && short_base + short_entries_csr + 256 <= L.stream_cap;
     if (fits) break;
     if (attempt == 1 || NI == 1) return SAGNN_OK;
     NI = 1;                                // the interval padding did not fit: lay out without it
@@ -1311,7 +1311,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.has_empty_rows = has_empty ? 1 : 0;
   h.m = m; h.nnz = nnz; h.f = f; h.mode = 1;
   h.generation = g_generation.fetch_add(1);
-  h.c_rows = whole_rows ? 0 : short_rows; h.c_nnz = short_entries_csr; h.c_nchunks = spmm_nchunks(short_entries_csr);
+  h.c_rows = whole_rows ? 0 : short_rows; h.c_nnz = short_entries_csr; h.c_nchunks = spmm_nchunks(short_entries_csr, spmm_chunk_entries(short_entries_csr, f));
   h.n_waves = NWT4; h.n_long_entries = stream_len;   // padded length of the sweep streams
   h.n_multi_rows = tot.multi_rows; h.n_multi_pieces = tot.multi_pieces;
   h.n_slabs = (int32_t)S; h.slab_width = (int32_t)width;

@@ -311,6 +311,30 @@ def force_sweep(request, monkeypatch):
     monkeypatch.setenv("SAGNN_SWEEP_GROUPS", "2")      # lane-group kernels at f = 128 / 64 even with little reuse
 
 
+@pytest.mark.parametrize("f,target", [(4, 3_000), (16, 8_500_000), (20, 400_000), (32, 4_300_000), (36, 40_000), (64, 600_000),
+                                      (100, 300_000), (132, 140_000), (256, 270_000), (260, 1_100_000)])
+def test_spmm_chunks_at_their_edges(f, target, monkeypatch):
+    """Nonzero splitting with chunks of every length (16 entries up to 128): rows that end on, just before and just
+    behind a chunk boundary, rows shared by two, some and many chunks (both carry fix-ups), empty rows, every lane-group
+    width with a full and a ragged operand."""
+    monkeypatch.setenv("SAGNN_SWEEP", "0")
+    rng = np.random.default_rng(f)
+    kinds = np.array([0, 1, 7, 8, 9, 15, 16, 17, 31, 33, 100, 129, 300])
+    deg = kinds[rng.integers(0, kinds.size, size=max(8, target // 55))]
+    deg[deg.size // 2] = min(20_000, target)
+    deg[-1] = 3000
+    n = 5000
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    colidx = rng.integers(0, n, size=rowptr[-1]).astype(np.int32)
+    val = rng.standard_normal(colidx.size).astype(np.float32)
+    B = synth.normal((n, f), f, synth.STREAM_H)
+    ref, zabs = oracle.spmm(rowptr, colidx, val, B, want_abs=True)
+    assert_close(run_spmm(rowptr, colidx, val, B, True, expect_mode=0), ref, zabs, RTOL_SPMM, f"chunks f={f}")
+    C0 = synth.normal((deg.size, f), f + 1, synth.STREAM_G)
+    ref2, zabs2 = oracle.spmm(rowptr, colidx, val, B, C=C0, want_abs=True)
+    assert_close(run_spmm(rowptr, colidx, val, B, True, C0=C0), ref2, zabs2, RTOL_SPMM, f"chunks accumulate f={f}")
+
+
 @pytest.mark.parametrize("f", [16, 32, 64, 128, 192, 256, 320])
 def test_spmm_slab_sweep_schedule(f, force_sweep):
     rng = np.random.default_rng(100 + f)
