@@ -218,7 +218,8 @@ typedef struct sagnn_spmm_options {
   int32_t schedule;        /* 0 heuristic, 1 nonzero splitting only, 2 slab sweep whenever possible */
   int32_t min_long;        /* rows with at least this many entries are swept (0 = decide; >= 16;
                               negative: -min_long replaces 64 where the rule would pick 64)         */
-  int32_t piece;           /* longest piece a swept row is cut into (0 = 4096; 1024..32768)         */
+  int32_t piece;           /* longest piece a swept row is cut into (0 = decide: 256..4096 by the
+                              number of entries, 4096 with schedule 2; 1024..32768)                  */
   int32_t slab_kb;         /* KiB of B per slab (0 = 4096); -1 = as many slabs as the format allows  */
   int32_t min_waves;       /* fewer than 16 pieces per wavefront below this many wavefronts (0 = 8192) */
   int32_t window_pct;      /* dealing window in % of the resident pieces (0 = 400); -1 = one window  */

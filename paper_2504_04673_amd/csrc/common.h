@@ -61,6 +61,20 @@ constexpr int kSweepMaxIntervals = 64;
 constexpr int kSweepBarrierSlots = 65536;   // arrival counters (cohort x XCD x interval)
 constexpr int kSweepMaxWindows = 2048;      // dealing windows of a matrix (11 bits of a sort key)
 
+// Longest piece of a swept row where the caller does not say: about what a stream holds on average when 8192
+// wavefronts share the entries (a longer piece makes one stream the whole product waits for: 2.4 M entries at f = 128
+// took 433 us with pieces of 4096 and 167 with 1024), a power of two up to 4096.
+inline int32_t sweep_piece_default(int64_t nnz, int32_t f) {
+  const int64_t streams = 8192 * (f == 128 ? 2 : (f < 128 ? 4 : 1));
+  int32_t p = 256;
+  while (p < 4096 && 2 * (int64_t)p * streams <= nnz) p *= 2;
+  return p;
+}
+inline int32_t sweep_piece_floor(int64_t nnz, int32_t f) {   // what the workspace is sized for
+  const int32_t p = sweep_piece_default(nnz, f);
+  return p < 1024 ? p : 1024;
+}
+
 struct SpmmWsHeader {       // first 256 bytes of the SpMM workspace (device copy)
   uint32_t magic;
   int32_t has_empty_rows;   // some row of the matrix has no entries
@@ -108,15 +122,16 @@ inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
       if (chunks > L.max_chunks) L.max_chunks = chunks;
     }
   }
-  // every long row has >= kSweepMinLong entries; splitting adds at most nnz/1024 pieces; every
+  // every long row has >= kSweepMinLong entries; splitting adds at most nnz/floor pieces; every
   // short row may become a piece of its own (whole-row wavefronts behind those of the long rows)
-  const int64_t long_pieces = nnz / kSweepMinLong + nnz / 1024 + kSweepSlots;
+  const int64_t floor = sweep_piece_floor(nnz, f);
+  const int64_t long_pieces = nnz / kSweepMinLong + nnz / floor + kSweepSlots;
   const int64_t long_waves = ceil_div(long_pieces, kSweepSlots) + 1;
   const int64_t short_waves = ceil_div(m, kSweepSlots) + 4;
   L.max_pieces = long_pieces + m;
   L.max_waves = long_waves + short_waves;
-  L.max_multi_rows = nnz / 1024 + 1;
-  L.max_multi_pieces = 2 * (nnz / 1024) + 2;
+  L.max_multi_rows = nnz / floor + 1;
+  L.max_multi_pieces = 2 * (nnz / floor) + 2;
   // sweep streams + gap + short CSR entries + padding.  A wavefront's stream is padded to the
   // batch of 8 steps at every interval boundary; with lane groups (up to 4 zipped streams per
   // wavefront) also to the longest of its group streams inside every interval.  If a pattern

@@ -1072,12 +1072,14 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const int force = opt.schedule == 1 ? 0 : (opt.schedule == 2 ? 1 : -1);
   if (force == 0 || nnz < 4096 || k <= 0 || k >= (1ll << kSweepColBits) || m <= 0) return SAGNN_OK;
   const int64_t b_bytes = k * (int64_t)f * 4;
-  // worth it only if B is much larger than an L2 (the long-row share is checked below)
-  if (force != 1 && (nnz < (1 << 20) || b_bytes <= (8ll << 20))) return SAGNN_OK;
+  // worth it only if B is much larger than an L2 (the long-row share is checked below) and there are enough entries
+  // for balanced streams on every CU (2.4 M entries: 129 against 139 us at f = 128, 49 against 67 at f = 16; 4 M: 154
+  // against 146 the other way)
+  if (force != 1 && (nnz < (3 << 20) || b_bytes <= (8ll << 20))) return SAGNN_OK;
 
   if (!sweep_plan_fits(L)) return SAGNN_OK;
-  int piece_max = opt.piece > 0 ? opt.piece : 4096;
-  if (piece_max < 1024) piece_max = 1024;
+  int piece_max = opt.piece > 0 ? opt.piece : (force == 1 ? 4096 : sweep_piece_default(nnz, f));
+  if (piece_max < sweep_piece_floor(nnz, f)) piece_max = sweep_piece_floor(nnz, f);
   if (piece_max > 32768) piece_max = 32768;
   const int64_t slab_bytes = opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : 4096) << 10;
   int64_t S = slab_bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * slab_bytes) : kSweepMaxSlabs;
