@@ -162,18 +162,25 @@ def _check(rc: int, where: str):
         raise SagnnError(rc, where)
 
 
+# Marshalling is on the path of every call and a launch is only a few microseconds: pointers travel as plain
+# integers (the argument types convert them), the stream comes from the runtime without a Stream object.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _host(a: np.ndarray) -> int:
+    """Address of a host array."""
+    return a.__array_interface__["data"][0]
 
 
 def _dev(t: torch.Tensor, dtype, name: str):
     if not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA/HIP tensor (there is no CPU path)")
-    if t.dtype != dtype or not t.is_contiguous():
+    if t.dtype is not dtype or not t.is_contiguous():
         raise ValueError(f"{name}: expected contiguous {dtype}")
     return t
 
@@ -183,15 +190,17 @@ def _mat(t: torch.Tensor, name: str):
     the row stride is passed to the library as the leading dimension."""
     if not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA/HIP tensor (there is no CPU path)")
-    if t.dtype != torch.float32 or t.dim() != 2:
+    if t.dtype is not torch.float32 or t.dim() != 2:
         raise ValueError(f"{name}: expected a 2-D float32 tensor")
-    if t.shape[0] > 1 and t.shape[1] > 0 and (t.stride(1) != 1 or t.stride(0) < t.shape[1]):
+    if not t.is_contiguous() and t.shape[0] > 1 and t.shape[1] > 0 and (t.stride(1) != 1 or t.stride(0) < t.shape[1]):
         raise ValueError(f"{name}: rows must be contiguous (unit stride inside a row)")
     return t
 
 
 def _ld(t: torch.Tensor) -> int:
-    return int(t.stride(0)) if t.shape[0] > 1 else max(int(t.stride(0)), int(t.shape[1]))
+    n, f = t.shape
+    ld = t.stride(0)
+    return ld if n > 1 or ld > f else f
 
 
 def _ws(nbytes: int, device) -> torch.Tensor:
@@ -236,12 +245,14 @@ def spmm_plan_needed_rows(rowptr, colidx, n: int, colblk, want_compact=True, val
     ws, needed, compact = bufs
     blk_off = np.zeros(nb + 1, dtype=np.int64)
     rc = L.spmm_plan_needed_rows(_ptr(rowptr), _ptr(colidx), m, n, nnz,
-                                 colblk.ctypes.data_as(ctypes.c_void_p), nb, _ptr(needed), cap,
-                                 blk_off.ctypes.data_as(ctypes.c_void_p), _ptr(compact), _ptr(ws),
+                                 _host(colblk), nb, _ptr(needed), cap,
+                                 _host(blk_off), _ptr(compact), _ptr(ws),
                                  ws.numel(), _plan_flags(validate, oblivious, multipass), _stream())
     _check(rc, "spmm_plan_needed_rows")
     N = int(blk_off[-1])
-    return Plan(needed[:N], blk_off, compact[:nnz] if compact is not None else None)
+    if compact is not None and compact.numel() != nnz:
+        compact = compact[:nnz]
+    return Plan(needed if N == needed.numel() else needed[:N], blk_off, compact)
 
 
 def spmm_plan_needed_rows_noalloc(rowptr, colidx, n: int, colblk, needed, compact=None, validate=False,
@@ -259,8 +270,8 @@ def spmm_plan_needed_rows_noalloc(rowptr, colidx, n: int, colblk, needed, compac
     nb = colblk.size - 1
     blk_off = np.zeros(nb + 1, dtype=np.int64)
     rc = lib().spmm_plan_needed_rows_noalloc(
-        _ptr(rowptr), _ptr(colidx), m, n, nnz, colblk.ctypes.data_as(ctypes.c_void_p), nb, _ptr(needed),
-        needed.numel(), blk_off.ctypes.data_as(ctypes.c_void_p), _ptr(compact),
+        _ptr(rowptr), _ptr(colidx), m, n, nnz, _host(colblk), nb, _ptr(needed),
+        needed.numel(), _host(blk_off), _ptr(compact),
         _plan_flags(validate, oblivious, multipass), _stream())
     _check(rc, "spmm_plan_needed_rows_noalloc")
     N = int(blk_off[-1])
@@ -316,7 +327,7 @@ class SpmmWorkspace:
     def info(self) -> dict:
         """Schedule chosen by spmm_csr_prepare (see spmm_csr_schedule_info)."""
         a = np.zeros(16, dtype=np.int64)
-        _check(lib().spmm_csr_schedule_info(_ptr(self.buf), a.ctypes.data_as(ctypes.c_void_p)),
+        _check(lib().spmm_csr_schedule_info(_ptr(self.buf), _host(a)),
                "spmm_csr_schedule_info")
         keys = ("mode", "sweep_waves", "sweep_entries", "chunk_rows", "chunk_entries", "chunks",
                 "split_rows", "has_empty_rows", "intervals", "sync_slabs", "gave_up_offset", "groups",
@@ -326,7 +337,7 @@ class SpmmWorkspace:
     def tile_info(self) -> dict:
         """What a preparation with dense tiles decided (see spmm_csr_tile_info)."""
         a = np.zeros(6, dtype=np.int64)
-        _check(lib().spmm_csr_tile_info(_ptr(self.buf), a.ctypes.data_as(ctypes.c_void_p)), "spmm_csr_tile_info")
+        _check(lib().spmm_csr_tile_info(_ptr(self.buf), _host(a)), "spmm_csr_tile_info")
         keys = ("tiles", "tile_entries", "kept_tiles", "items", "ranked_rows", "rest_entries")
         return dict(zip(keys, (int(x) for x in a)))
 
@@ -375,7 +386,7 @@ def spmm_csr_prepare_tuned(rowptr, colidx, val, B, C=None, options: SpmmOptions 
     choice = np.zeros(4, dtype=np.int32)
     _check(L.spmm_csr_prepare_tuned(_ptr(rowptr), _ptr(colidx), _ptr(val), m, k, nnz, f, _ptr(buf),
                                     buf.numel(), _ptr(B), B.stride(0), _ptr(C), C.stride(0),
-                                    choice.ctypes.data_as(ctypes.c_void_p), ctypes.byref(opt), _stream()),
+                                    _host(choice), ctypes.byref(opt), _stream()),
            "spmm_csr_prepare_tuned")
     return SpmmWorkspace(buf, m, nnz, f, {"piece": int(choice[0]), "min_long": int(choice[1]),
                                          "best_us": int(choice[2]), "variant": int(choice[3])}, int(k))
@@ -520,8 +531,8 @@ def spmm_split_colblocks(rowptr, colidx, val, bounds) -> ColBlocks:
     va = torch.empty(max(nnz, 1), dtype=torch.float32, device=dev)
     off = np.zeros(nb + 1, dtype=np.int64)
     rc = L.spmm_split_colblocks(_ptr(rowptr), _ptr(colidx), _ptr(val), m, nnz,
-                                bounds.ctypes.data_as(ctypes.c_void_p), nb, _ptr(rp), _ptr(ci), _ptr(va),
-                                off.ctypes.data_as(ctypes.c_void_p), _ptr(ws), ws.numel(), _stream())
+                                _host(bounds), nb, _ptr(rp), _ptr(ci), _ptr(va),
+                                _host(off), _ptr(ws), ws.numel(), _stream())
     _check(rc, "spmm_split_colblocks")
     return ColBlocks(rp, ci[:nnz], va[:nnz], off)
 
@@ -551,7 +562,7 @@ def spmm_stage_loop(stages, m: int, H, T0, T1, Z, accumulate_first=False, pack_s
     cap = min(T0.shape[0], T1.shape[0])
     if T0.shape[1] != f or T1.shape[1] != f:
         raise ValueError("packed buffers must have H's width")
-    ps = _stream() if pack_stream is None else ctypes.c_void_p(pack_stream.cuda_stream)
+    ps = _stream() if pack_stream is None else pack_stream.cuda_stream
     rc = lib().spmm_stage_loop(ctypes.cast(arr, ctypes.c_void_p), len(stages), m, _ptr(H), n,
                                H.stride(0), f, _ptr(T0), _ptr(T1), cap, _ptr(Z), Z.stride(0),
                                int(accumulate_first), _stream(), ps)
@@ -565,8 +576,8 @@ def spmm_volume_stats(counts, f: int, elem_bytes: int = 4) -> dict:
     if c.ndim != 2 or c.shape[0] != c.shape[1]:
         raise ValueError("counts must be P x P")
     out = np.zeros(8, dtype=np.float64)
-    _check(lib().spmm_volume_stats(c.ctypes.data_as(ctypes.c_void_p), c.shape[0], f, elem_bytes,
-                                   out.ctypes.data_as(ctypes.c_void_p)), "spmm_volume_stats")
+    _check(lib().spmm_volume_stats(_host(c), c.shape[0], f, elem_bytes,
+                                   _host(out)), "spmm_volume_stats")
     keys = ("total_bytes", "avg_bytes", "max_recv_bytes", "recv_imbalance_pct", "max_send_bytes",
             "send_imbalance_pct", "cut_rows", "cut_bytes")
     return dict(zip(keys, (float(x) for x in out)))
@@ -608,7 +619,7 @@ def spmm_perm_from_labels(labels, n_parts: int):
     inv = torch.empty(max(n, 1), dtype=torch.int32, device=dev)
     off = np.zeros(n_parts + 1, dtype=np.int64)
     _check(lib().spmm_perm_from_labels(_ptr(labels), n, n_parts, _ptr(perm), _ptr(inv),
-                                       off.ctypes.data_as(ctypes.c_void_p), _ptr(ws), ws.numel(), _stream()),
+                                       _host(off), _ptr(ws), ws.numel(), _stream()),
            "spmm_perm_from_labels")
     return perm[:n], inv[:n], off
 
