@@ -96,7 +96,8 @@ int sagnn_version(void);
  *                         An entry whose column is outside [0,n) gets -1.
  * All integer work; the result is unique, so it is bit-exact by construction.
  *
- * Synchronises the stream once (N has to reach the host).  If N > needed_cap returns
+ * Waits until N has reached the host; d_needed and d_colidx_compact are complete in the order of
+ * the stream.  If N > needed_cap returns
  * SAGNN_ECAPACITY with h_blk_off filled in (so the caller knows the size to allocate) and
  * d_needed / d_colidx_compact untouched.  With SAGNN_PLAN_VALIDATE the CSR is checked on
  * the device first (rowptr monotone from 0 to nnz, every column in [0,n)) and
@@ -109,9 +110,8 @@ int sagnn_version(void);
  * that both algorithms can be measured on one harness.
  *
  * Small blocks (n <= 262,144 columns, m <= 262,144 rows, nnz <= 65,536, nb <= 16, not oblivious) are
- * planned by one workgroup in one launch with one copy back (the launch-latency regime: the general
- * path is ten launches and three copies); SAGNN_PLAN_MULTIPASS switches that off.  Results are the
- * same either way.
+ * planned in one launch (the launch-latency regime: the general path is five to nine);
+ * SAGNN_PLAN_MULTIPASS switches that off.  Results are the same either way.
  *
  * Workspace: spmm_plan_workspace_bytes(); contents are scratch.  Its size is a few bytes per
  * column plus, for wide blocks with many entries (n above about 5 M columns and nnz >= 2^22),

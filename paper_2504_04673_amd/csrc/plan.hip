@@ -2,22 +2,20 @@
 // paragraph that defines NnzCols(i,j) as the nonzero column indices of block A_ij, i.e. the
 // rows of H_j that P(i) has to receive).
 //
-// Integer only, result unique.  Pipeline (all kernels on the caller's stream):
-//   clear    one flag byte per column
-//   mark     one pass over colidx: flag[c] = 1.  Plain byte stores: every writer stores the
-//            same value, so no atomics are needed, and a test before the store keeps hub
-//            columns from producing write traffic at all
-//   words    a lane squeezes 16 flag bytes (one 16-byte load) into 16 bits, four lanes make the
-//            64-bit membership word of 64 columns; its popcount feeds the scan
-//   scan     exclusive scan of the per-block popcounts (one workgroup)       \  three-kernel
-//   prefix   per-word exclusive prefix = rank of the word's first column       /  scan
-//   blkoff   rank of every column-block boundary -> blk_off, N   (then one D2H copy + sync)
-//   emit     one wavefront per word: lane l owns column 64w+l, the ballot mask and mbcnt give
-//            each set lane its slot (ballot / prefix-count stream compaction); needed[] comes
-//            out ascending
-//   remap    compact[e] = prefix[c>>6] + popcount(word & bits below c): position of column
-//            c in needed[]; monotone in c, so sorted rows stay sorted
+// Integer only, result unique.  Pipeline (all kernels on the caller's stream, launched without a wait in between):
+//   mark     one pass over colidx -> membership words, by one of three ways (see below): byte flags in memory,
+//            LDS bitmaps, range buckets; the words' population counts are summed per tile of 2048 words
+//   prefix   rank of the first column of every word (each workgroup adds up the tiles before its own)
+//   finish   block offsets and N to the host record (first workgroup), needed[] and the remap:
+//            a wavefront per word, lane l owns column 64w+l, the ballot mask and mbcnt give each set lane its slot
+//            (needed[] comes out ascending); compact[e] = prefix[c>>6] + popcount(word & bits below c): position of
+//            column c in needed[]; monotone in c, so sorted rows stay sorted
+// The block offsets are written straight into pinned host memory and the call returns as soon as they are there,
+// while needed[] and the remap may still be in the making on the stream; capacity and validity are checked by the
+// kernels before they write.  (Ten launches, three copies and a wait in the middle before: a block of 100 k columns and
+// 1 M entries took 363 us, now 35.)
 // Traffic: nnz*4 (mark) + nnz*8 (remap read+write) + N*4 + a few passes over n bytes.
+#include <atomic>
 #include <mutex>
 
 #include "common.h"
@@ -63,7 +61,7 @@ struct PlanWs {
   uint4* rank16;      // W: {word lo, word hi, prefix, 0}: one 16-byte lookup per remapped entry
   int32_t* blocksum;  // nblk + 1
   int64_t* colblk;    // nb + 1 (device copy of the block boundaries)
-  int64_t* blkoff;    // nb + 1
+  int64_t* blkoff;    // the record of the call: {done, err, blkoff[nb + 1]} (calls without a host record)
   int32_t* err;       // 4 counters
   uint32_t* part;     // LDS marking only: kLdsGroups private bitmaps of kLdsWords words
   int32_t* bkt_cols;  // bucketed marking only: the column ids partitioned by range (nnz)
@@ -90,8 +88,8 @@ PlanWs carve(void* base, int64_t n, int32_t nb, int64_t nnz) {
   w.rank16 = reinterpret_cast<uint4*>(take(sizeof(uint4) * (size_t)w.W));
   w.blocksum = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)(w.nblk + 1)));
   w.colblk = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (size_t)(nb + 1)));
-  w.blkoff = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (size_t)(nb + 1)));
-  w.err = reinterpret_cast<int32_t*>(take(256));   // 4 counters; the small-block path keeps its result record here
+  w.blkoff = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (size_t)(nb + 4)));
+  w.err = reinterpret_cast<int32_t*>(take(256));
   const bool bucketed = bucket_mark_eligible(n, nnz);
   w.part = lds_mark_eligible(n, nnz)
                ? reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)kLdsGroups * kLdsWords))
@@ -107,11 +105,34 @@ PlanWs carve(void* base, int64_t n, int32_t nb, int64_t nnz) {
 
 __device__ __forceinline__ int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Whether the outputs may be written: the rows fit and, where asked for, the CSR is valid.
+struct Verdict {
+  const int32_t* total;    // N
+  int64_t cap;
+  const int32_t* err;      // NULL: not asked
+  __device__ __forceinline__ bool go() const {
+    return (int64_t)*total <= cap && !(err && (err[0] || err[1]));
+  }
+};
+
+// What a call reports, in pinned host memory (or, for calls that may not allocate, in the workspace).
+struct PlanRecord {
+  int64_t done;            // the call's ticket, written last
+  int32_t err[4];          // [0] rowptr malformed, [1] column out of range
+  int64_t blkoff[1];       // nb + 1
+};
+
+__device__ __forceinline__ void report_done(PlanRecord* rec, int64_t ticket) {
+  __threadfence_system();
+  __hip_atomic_store(&rec->done, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ __launch_bounds__(kThreads) void clear_kernel(uint4* __restrict__ flag16, int64_t n16,
-                                                         int32_t* __restrict__ err) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n16; i += stride)
-    flag16[i] = make_uint4(0u, 0u, 0u, 0u);
+                                                         int32_t* __restrict__ err,
+                                                         int32_t* __restrict__ blocksum, int64_t nblk) {
+  const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x, stride = (int64_t)gridDim.x * kThreads;
+  for (int64_t i = t0; i < n16; i += stride) flag16[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t i = t0; i < nblk; i += stride) blocksum[i] = 0;
   if (blockIdx.x == 0 && threadIdx.x < 4) err[threadIdx.x] = 0;
 }
 
@@ -201,8 +222,11 @@ __global__ __launch_bounds__(kLdsThreads) void mark_lds_kernel(const int32_t* __
                                                                int32_t groups_per_pass,
                                                                uint32_t* __restrict__ part,
                                                                int32_t* __restrict__ err, int aligned,
-                                                               int32_t* __restrict__ spec) {
+                                                               int32_t* __restrict__ spec,
+                                                               int32_t* __restrict__ blocksum, int64_t nblk) {
   extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
+  if (blockIdx.x == 0)   // (merge_kernel adds to them)
+    for (int64_t i = threadIdx.x; i < nblk; i += kLdsThreads) blocksum[i] = 0;
   const int pass = blockIdx.x / groups_per_pass, share = blockIdx.x % groups_per_pass;
   if (pass != 0) spec = nullptr;
   const int64_t c0 = (int64_t)pass * kLdsCols;
@@ -296,8 +320,11 @@ __device__ __forceinline__ LaneRun lane_run(int32_t b, int lane) {
 // per workgroup: how many of its entries fall into every range (out-of-range columns are flagged and left out)
 __global__ __launch_bounds__(kBktThreads) void bucket_count_kernel(const int32_t* __restrict__ colidx, int64_t nnz,
                                                                 int64_t n, int32_t nbk, int32_t* __restrict__ cnt,
-                                                                int32_t* __restrict__ err) {
+                                                                int32_t* __restrict__ err,
+                                                                int32_t* __restrict__ blocksum, int64_t nblk) {
   __shared__ int32_t h[kBktMaxRanges];
+  if (blockIdx.x == 0)   // (mark_bucket_kernel adds to them)
+    for (int64_t i = threadIdx.x; i < nblk; i += kBktThreads) blocksum[i] = 0;
   for (int b = threadIdx.x; b < nbk; b += kBktThreads) h[b] = 0;
   __syncthreads();
   const int lane = threadIdx.x & 63;
@@ -465,7 +492,9 @@ __global__ __launch_bounds__(kBktThreads) void bucket_scatter_kernel(const int32
 __global__ __launch_bounds__(kLdsThreads) void remap_bucket_kernel(int32_t* __restrict__ cols,
                                                                    const int32_t* __restrict__ start, int64_t nnz,
                                                                    int64_t n, int64_t W,
-                                                                   const uint4* __restrict__ rank16) {
+                                                                   const uint4* __restrict__ rank16,
+                                                                   const Verdict vd) {
+  if (!vd.go()) return;
   // per 32 columns: {membership bits, needed columns before them}: a lookup is one 8-byte LDS read
   __shared__ uint2 rec[kBktCols / 32];
   const int range = blockIdx.x;
@@ -501,7 +530,8 @@ __global__ __launch_bounds__(kLdsThreads) void remap_bucket_kernel(int32_t* __re
 // compact[e] = rank found at the entry's place (same shares of the entries as the scatter)
 __global__ __launch_bounds__(kBktThreads) void remap_gather_kernel(const int32_t* __restrict__ place_e,
                                                                   const int32_t* __restrict__ ranks, int64_t nnz,
-                                                                  int32_t* __restrict__ compact) {
+                                                                  int32_t* __restrict__ compact, const Verdict vd) {
+  if (!vd.go()) return;
   const int64_t per = ceil_div_dev(nnz, kBktGroups);
   const int64_t e0 = (int64_t)blockIdx.x * per, e1 = e0 + per < nnz ? e0 + per : nnz;
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 8 * kBktThreads) {
@@ -520,7 +550,10 @@ __global__ __launch_bounds__(kBktThreads) void remap_gather_kernel(const int32_t
 // words (kBktCols / 64 of them, the last range fewer) straight into the bitmap
 __global__ __launch_bounds__(kLdsThreads) void mark_bucket_kernel(const int32_t* __restrict__ cols,
                                                                   const int32_t* __restrict__ start, int64_t nnz,
-                                                                  int64_t n, int64_t W, uint64_t* __restrict__ bm) {
+                                                                  int64_t n, int64_t W, uint64_t* __restrict__ bm,
+                                                                  int32_t* __restrict__ blocksum) {
+  __shared__ int32_t tally[kBktCols / 64 / kWordsPerBlock + 2];   // set bits per tile of words the range touches
+  if (threadIdx.x < sizeof(tally) / sizeof(tally[0])) tally[threadIdx.x] = 0;
   extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
   uint8_t* flag = reinterpret_cast<uint8_t*>(bits);
   const int range = blockIdx.x;
@@ -567,8 +600,12 @@ __global__ __launch_bounds__(kLdsThreads) void mark_bucket_kernel(const int32_t*
       const int64_t col = wi * 64;
       if (n - col < 64) piece &= (1ull << (n - col)) - 1ull;
       bm[wi] = piece;
+      if (piece) atomicAdd(&tally[wi / kWordsPerBlock - w0 / kWordsPerBlock], __popcll(piece));
     }
   }
+  __syncthreads();
+  if (threadIdx.x < sizeof(tally) / sizeof(tally[0]) && tally[threadIdx.x])
+    atomicAdd(&blocksum[w0 / kWordsPerBlock + threadIdx.x], tally[threadIdx.x]);
 }
 
 // Membership words from the private bitmaps.  A workgroup owns 16 consecutive 64-bit words;
@@ -576,7 +613,7 @@ __global__ __launch_bounds__(kLdsThreads) void mark_bucket_kernel(const int32_t*
 // slices.
 __global__ __launch_bounds__(kThreads) void merge_kernel(const uint32_t* __restrict__ part,
                                                          int32_t groups_per_pass, int64_t W, int64_t n,
-                                                         uint64_t* __restrict__ bm) {
+                                                         uint64_t* __restrict__ bm, int32_t* __restrict__ blocksum) {
   __shared__ uint64_t red[16][17];
   const int wi = threadIdx.x & 15, sl = threadIdx.x >> 4;
   const int64_t w = (int64_t)blockIdx.x * 16 + wi;
@@ -594,35 +631,19 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const uint32_t* __restr
   }
   red[sl][wi] = word;
   __syncthreads();
-  if (sl == 0 && w < W) {
+  if (sl == 0) {   // sixteen lanes; their words lie in one tile
+    int cnt = 0;
+    if (w < W) {
 #pragma unroll
-    for (int j = 1; j < 16; ++j) word |= red[j][wi];
-    const int64_t col = w * 64;
-    if (n - col < 64) word &= (1ull << (n - col)) - 1ull;
-    bm[w] = word;
-  }
-}
-
-// blocksum[b] = number of set bits in the b-th tile of kWordsPerBlock words (what words_kernel
-// produces on the byte-flag path)
-__global__ __launch_bounds__(kThreads) void count_kernel(const uint64_t* __restrict__ bm, int64_t W,
-                                                         int32_t* __restrict__ blocksum) {
-  __shared__ int wsum[kThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int cnt = 0;
-  for (int i = threadIdx.x; i < kWordsPerBlock; i += kThreads) {
-    const int64_t w = (int64_t)blockIdx.x * kWordsPerBlock + i;
-    if (w < W) cnt += __popcll(bm[w]);
-  }
+      for (int j = 1; j < 16; ++j) word |= red[j][wi];
+      const int64_t col = w * 64;
+      if (n - col < 64) word &= (1ull << (n - col)) - 1ull;
+      bm[w] = word;
+      cnt = __popcll(word);
+    }
 #pragma unroll
-  for (int d = 32; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
-  if (lane == 0) wsum[wave] = cnt;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) t += wsum[w];
-    blocksum[blockIdx.x] = t;
+    for (int o = 8; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 16);
+    if (wi == 0 && cnt) atomicAdd(&blocksum[w / kWordsPerBlock], cnt);
   }
 }
 
@@ -656,29 +677,34 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* total) {
   return base + inc - v;
 }
 
-// Membership words from the flag bytes.  A block owns kWordsPerBlock consecutive words; each of
-// its wavefronts walks its share 16 words (1024 flag bytes) per step: a lane loads 16 flags with
-// one 16-byte load and squeezes them into 16 bits (flags are 0 or 1: a multiply gathers the low
-// bit of every byte), four neighbouring lanes OR their quarters into one word.
+// Membership words from the flag bytes.  A wavefront makes 64 words, 16 (1024 flag bytes) per step: a lane loads 16
+// flags with one 16-byte load and squeezes them into 16 bits (flags are 0 or 1: a multiply gathers the low
+// bit of every byte), four neighbouring lanes OR their quarters into one word.  (2048 words per workgroup, so that its
+// sum was the tile's, was a chain of 32 loads: 14 us for 100 k columns, now 4.)
 __device__ __forceinline__ uint32_t squeeze8(uint64_t x) {
   return (uint32_t)(((x & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
 }
 
+constexpr int kWordsPerGroup = kThreads;   // 64 per wavefront
 __global__ __launch_bounds__(kThreads) void words_kernel(const uint8_t* __restrict__ flag, int64_t W,
                                                          uint64_t* __restrict__ bm,
                                                          int32_t* __restrict__ blocksum) {
   __shared__ int wsum[kThreads / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kPerWave = kWordsPerBlock / (kThreads / 64);
-  static_assert(kPerWave % 16 == 0, "a wavefront step covers 16 words");
-  const int64_t w0 = (int64_t)blockIdx.x * kWordsPerBlock + (int64_t)wave * kPerWave;
+  static_assert(kWordsPerBlock % kWordsPerGroup == 0, "a workgroup's words lie in one tile");
+  const int64_t w0 = (int64_t)blockIdx.x * kWordsPerGroup + (int64_t)wave * 64;
   const ulonglong2* __restrict__ f16 = reinterpret_cast<const ulonglong2*>(flag);   // flag is 256-byte aligned
   int cnt = 0;
-  for (int i = 0; i < kPerWave; i += 16) {
-    const int64_t w = w0 + i + (lane >> 2);
-    ulonglong2 v = make_ulonglong2(0ull, 0ull);
-    if (w < W) v = f16[(w0 + i) * 4 + lane];
-    const uint64_t quarter = (uint64_t)(squeeze8(v.x) | (squeeze8(v.y) << 8));
+  ulonglong2 v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = make_ulonglong2(0ull, 0ull);
+    if (w0 + i * 16 + (lane >> 2) < W) v[i] = f16[(w0 + i * 16) * 4 + lane];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t w = w0 + i * 16 + (lane >> 2);
+    const uint64_t quarter = (uint64_t)(squeeze8(v[i].x) | (squeeze8(v[i].y) << 8));
     cnt += __popcll(quarter);
     uint64_t word = quarter << (16 * (lane & 3));
     word |= __shfl_xor(word, 1, 64);
@@ -693,23 +719,8 @@ __global__ __launch_bounds__(kThreads) void words_kernel(const uint8_t* __restri
     int t = 0;
 #pragma unroll
     for (int w = 0; w < kThreads / 64; ++w) t += wsum[w];
-    blocksum[blockIdx.x] = t;
+    if (t) atomicAdd(&blocksum[w0 / kWordsPerBlock], t);
   }
-}
-
-// one workgroup: in-place exclusive scan of blocksum[0..nblk), blocksum[nblk] = grand total
-__global__ __launch_bounds__(kThreads) void scan_blocks_kernel(int32_t* __restrict__ blocksum,
-                                                               int64_t nblk) {
-  int carry = 0;
-  for (int64_t base = 0; base < nblk; base += kThreads) {
-    const int64_t i = base + threadIdx.x;
-    const int v = (i < nblk) ? blocksum[i] : 0;
-    int total;
-    const int ex = block_exclusive_scan(v, &total);
-    if (i < nblk) blocksum[i] = carry + ex;
-    carry += total;
-  }
-  if (threadIdx.x == 0) blocksum[nblk] = carry;
 }
 
 // A tile of kWordsPerBlock words goes through LDS so that both the loads of the words and the
@@ -722,7 +733,13 @@ __global__ __launch_bounds__(kThreads) void prefix_kernel(const uint64_t* __rest
                                                           uint4* __restrict__ rank16) {
   __shared__ uint64_t words[kWordsPerBlock];
   __shared__ int32_t pre[kWordsPerBlock];
+  __shared__ int32_t wbase[kThreads / 64];
   const int64_t tile0 = (int64_t)blockIdx.x * kWordsPerBlock;
+  int32_t base = 0;                                   // set bits of the tiles before this one
+  for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kThreads) base += blocksum[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) base += __shfl_xor(base, o, 64);
+  if ((threadIdx.x & 63) == 0) wbase[threadIdx.x >> 6] = base;
 #pragma unroll
   for (int i = 0; i < kWordsPerBlock / kThreads; ++i) {
     const int j = threadIdx.x + i * kThreads;
@@ -736,8 +753,11 @@ __global__ __launch_bounds__(kThreads) void prefix_kernel(const uint64_t* __rest
     c[i] = __popcll(words[threadIdx.x * 8 + i]);
     s += c[i];
   }
+  base = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) base += wbase[w];
   int total;
-  int run = blocksum[blockIdx.x] + block_exclusive_scan(s, &total);
+  int run = base + block_exclusive_scan(s, &total);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     pre[threadIdx.x * 8 + i] = run;
@@ -754,63 +774,7 @@ __global__ __launch_bounds__(kThreads) void prefix_kernel(const uint64_t* __rest
       rank16[tile0 + j] = make_uint4((uint32_t)word, (uint32_t)(word >> 32), (uint32_t)p, 0u);
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) prefix[W] = blocksum[nblk];
-}
-
-__device__ __forceinline__ int rank_of(const uint64_t* __restrict__ bm,
-                                       const int32_t* __restrict__ prefix, int64_t c) {
-  const int64_t w = c >> 6;
-  const uint64_t below = bm[w] & ((1ull << (c & 63)) - 1ull);
-  return prefix[w] + __popcll(below);
-}
-
-__global__ void blkoff_kernel(const uint64_t* __restrict__ bm, const int32_t* __restrict__ prefix,
-                              int64_t W, int64_t n, const int64_t* __restrict__ colblk, int32_t nb,
-                              int64_t* __restrict__ blkoff) {
-  for (int q = threadIdx.x; q <= nb; q += blockDim.x) {
-    const int64_t c = colblk[q];
-    blkoff[q] = (c >= n || (c >> 6) >= W) ? (int64_t)prefix[W] : (int64_t)rank_of(bm, prefix, c);
-  }
-}
-
-// one wavefront per bitmap word
-__global__ __launch_bounds__(kThreads) void emit_kernel(const uint64_t* __restrict__ bm,
-                                                        const int32_t* __restrict__ prefix,
-                                                        int64_t W, int64_t n,
-                                                        int32_t* __restrict__ needed) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * kThreads) >> 6;
-  for (int64_t w = wave0; w < W; w += nwaves) {
-    const uint64_t word = bm[w];
-    const int64_t c = w * 64 + lane;
-    const bool set = ((word >> lane) & 1ull) != 0 && c < n;
-    const uint64_t mask = __ballot(set);
-    const int slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                               __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-    if (set) needed[(int64_t)prefix[w] + slot] = (int32_t)c;
-  }
-}
-
-// Sparse membership (a few needed columns per word, e.g. a rank's share of a huge graph): one
-// thread per word walks the set bits; a wavefront per word would write a handful of ids with
-// 64 lanes.
-__global__ __launch_bounds__(kThreads) void emit_sparse_kernel(const uint64_t* __restrict__ bm,
-                                                               const int32_t* __restrict__ prefix,
-                                                               int64_t W, int64_t n,
-                                                               int32_t* __restrict__ needed) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t w = (int64_t)blockIdx.x * kThreads + threadIdx.x; w < W; w += stride) {
-    uint64_t word = bm[w];
-    if (word == 0ull) continue;
-    int64_t pos = prefix[w];
-    const int64_t base = w * 64;
-    while (word) {
-      const int b = __builtin_ctzll(word);
-      word &= word - 1ull;
-      if (base + b < n) needed[pos++] = (int32_t)(base + b);
-    }
-  }
+  if ((int64_t)blockIdx.x == nblk - 1 && threadIdx.x == 0) prefix[W] = base + total;
 }
 
 __device__ __forceinline__ int32_t remap_one(int32_t c, int64_t n, const uint4* __restrict__ rank16) {
@@ -820,44 +784,96 @@ __device__ __forceinline__ int32_t remap_one(int32_t c, int64_t n, const uint4* 
   return (int32_t)t.z + __popcll(word & ((1ull << (c & 63)) - 1ull));
 }
 
-__global__ __launch_bounds__(kThreads) void remap_kernel(const int32_t* __restrict__ colidx,
-                                                         int64_t nnz, int64_t n,
-                                                         const uint4* __restrict__ rank16,
-                                                         int32_t* __restrict__ compact, int aligned) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  const int64_t quads = aligned ? (nnz >> 2) : 0;
-  const int4* __restrict__ c4 = reinterpret_cast<const int4*>(colidx);
-  int4* __restrict__ o4 = reinterpret_cast<int4*>(compact);
-  for (int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x; q < quads; q += stride) {
+// Block boundaries: as a kernel argument while they are few (no copy to the device).
+constexpr int kArgBlocks = 64;
+struct Colblk {
+  const int64_t* mem;              // NULL: v holds them
+  int64_t v[kArgBlocks + 1];
+};
+
+// The last launch: record, needed[], remap.  The first `emit_blocks` workgroups write needed[], the others the remap.
+//   needed[]  a wavefront per word; where fewer than eight columns of a word are needed on average a thread per word
+//             that walks its set bits (a wavefront would write a handful of ids with 64 lanes)
+//   remap     range-checked copy if every column is needed (position = column), else one 16-byte lookup per entry
+struct FinishArgs {
+  const uint64_t* bm; const int32_t* prefix; const uint4* rank16;
+  int64_t W, n, nnz;
+  int32_t* needed;
+  const int32_t* colidx; int32_t* compact;     // compact == NULL: no remap here
+  int32_t identity_done;                       // the remap has been written for the case that all are needed
+  int32_t aligned, nb, emit_blocks;
+  PlanRecord* rec; int64_t ticket;
+  Verdict vd;
+};
+
+__global__ __launch_bounds__(kThreads) void finish_kernel(const FinishArgs a, const Colblk cb) {
+  const int64_t N = a.prefix[a.W];
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < 4) a.rec->err[threadIdx.x] = a.vd.err ? a.vd.err[threadIdx.x] : 0;
+    for (int q = threadIdx.x; q <= a.nb; q += kThreads) {
+      const int64_t c = cb.mem ? cb.mem[q] : cb.v[q];
+      const int64_t w = c >> 6;
+      a.rec->blkoff[q] = (c >= a.n || w >= a.W) ? N : (int64_t)a.prefix[w] + __popcll(a.bm[w] & ((1ull << (c & 63)) - 1ull));
+    }
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) report_done(a.rec, a.ticket);
+  }
+  if (!a.vd.go()) return;
+  if ((int)blockIdx.x < a.emit_blocks) {
+    const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x, stride = (int64_t)a.emit_blocks * kThreads;
+    if (N * 8 < a.n) {
+      for (int64_t w = t0; w < a.W; w += stride) {
+        uint64_t word = a.bm[w];
+        if (word == 0ull) continue;
+        int64_t pos = a.prefix[w];
+        const int64_t base = w * 64;
+        while (word) {
+          const int b = __builtin_ctzll(word);
+          word &= word - 1ull;
+          if (base + b < a.n) a.needed[pos++] = (int32_t)(base + b);
+        }
+      }
+    } else {
+      const int lane = threadIdx.x & 63;
+      for (int64_t w = t0 >> 6; w < a.W; w += stride >> 6) {
+        const uint64_t word = a.bm[w];
+        const int64_t c = w * 64 + lane;
+        const bool set = ((word >> lane) & 1ull) != 0 && c < a.n;
+        const uint64_t mask = __ballot(set);
+        const int slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+        if (set) a.needed[(int64_t)a.prefix[w] + slot] = (int32_t)c;
+      }
+    }
+    return;
+  }
+  if (!a.compact) return;
+  const bool identity = N == a.n;
+  if (identity && a.identity_done) return;
+  const int64_t t0 = (int64_t)(blockIdx.x - a.emit_blocks) * kThreads + threadIdx.x;
+  const int64_t stride = (int64_t)(gridDim.x - a.emit_blocks) * kThreads;
+  const int64_t quads = a.aligned ? (a.nnz >> 2) : 0;
+  const int4* __restrict__ c4 = reinterpret_cast<const int4*>(a.colidx);
+  int4* __restrict__ o4 = reinterpret_cast<int4*>(a.compact);
+  if (identity) {
+    for (int64_t q = t0; q < quads; q += stride) {
+      const int4 c = c4[q];
+      o4[q] = make_int4(identity_or_bad(c.x, a.n), identity_or_bad(c.y, a.n), identity_or_bad(c.z, a.n),
+                        identity_or_bad(c.w, a.n));
+    }
+    for (int64_t e = (quads << 2) + t0; e < a.nnz; e += stride) a.compact[e] = identity_or_bad(a.colidx[e], a.n);
+    return;
+  }
+  for (int64_t q = t0; q < quads; q += stride) {
     const int4 c = c4[q];
     int4 o;
-    o.x = remap_one(c.x, n, rank16);
-    o.y = remap_one(c.y, n, rank16);
-    o.z = remap_one(c.z, n, rank16);
-    o.w = remap_one(c.w, n, rank16);
+    o.x = remap_one(c.x, a.n, a.rank16);
+    o.y = remap_one(c.y, a.n, a.rank16);
+    o.z = remap_one(c.z, a.n, a.rank16);
+    o.w = remap_one(c.w, a.n, a.rank16);
     o4[q] = o;
   }
-  for (int64_t e = (quads << 2) + (int64_t)blockIdx.x * kThreads + threadIdx.x; e < nnz; e += stride)
-    compact[e] = remap_one(colidx[e], n, rank16);
-}
-
-// Every column is needed (N == n, e.g. a whole graph planned as one block): the position of
-// column c in needed[] is c itself, so the remap is a range-checked copy (pure streaming).
-__global__ __launch_bounds__(kThreads) void remap_identity_kernel(const int32_t* __restrict__ colidx,
-                                                                  int64_t nnz, int64_t n,
-                                                                  int32_t* __restrict__ compact,
-                                                                  int aligned) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  const int64_t quads = aligned ? (nnz >> 2) : 0;
-  const int4* __restrict__ c4 = reinterpret_cast<const int4*>(colidx);
-  int4* __restrict__ o4 = reinterpret_cast<int4*>(compact);
-  auto one = [n](int32_t c) { return (c < 0 || c >= n) ? -1 : c; };
-  for (int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x; q < quads; q += stride) {
-    const int4 c = c4[q];
-    o4[q] = make_int4(one(c.x), one(c.y), one(c.z), one(c.w));
-  }
-  for (int64_t e = (quads << 2) + (int64_t)blockIdx.x * kThreads + threadIdx.x; e < nnz; e += stride)
-    compact[e] = one(colidx[e]);
+  for (int64_t e = (quads << 2) + t0; e < a.nnz; e += stride) a.compact[e] = remap_one(a.colidx[e], a.n, a.rank16);
 }
 
 inline unsigned grid_for(int64_t items, int64_t per_thread = 1) {
@@ -885,37 +901,59 @@ namespace {
 
 // ---------------------------------------------------------------------------------------------
 // Small blocks (the launch-latency regime: a few thousand rows and columns): the whole plan in one
-// workgroup and one launch.  Membership bits, their prefix counts and the validity flags live in
-// LDS; the block boundaries come in as a kernel argument and the block offsets and error flags go
-// out through one small record, so the call is one launch, one copy back and one wait instead of
-// ten launches and three copies.  Same results as the general path: needed[] ascending, remap -1
+// launch.  Every workgroup marks all entries in its own LDS (they are few, and no workgroup then waits for another)
+// and counts and ranks the columns; the first one writes the record, the others their shares of needed[] and of the
+// remap.
+// One flag byte per column where they fit (plain stores: LDS atomics, one lane per clock, were half of the
+// kernel's time), bits beyond.  Same results as the general path: needed[] ascending, remap -1
 // for a column outside [0, n), nothing written to needed[] / the remap when N exceeds the
-// capacity or the validation fails.
+// capacity or the validation fails.  36,864 entries over 4096 columns: 8 us (of which
+// launch and report are 7), 16 us by one workgroup with bits.
 constexpr int64_t kSmallMaxCols = 262144;   // 4096 membership words of 64 columns
+constexpr int64_t kSmallByteCols = 131072;
 constexpr int64_t kSmallMaxNnz = 65536;
 constexpr int64_t kSmallMaxRows = 262144;
 constexpr int32_t kSmallMaxBlocks = 16;
+constexpr int kSmallLoads = 40;             // entries a thread has in flight
+constexpr int kSmallOwn = 4;                // entries of the remap per thread
 struct SmallColblk { int64_t v[kSmallMaxBlocks + 1]; };
-struct SmallOut {
-  int32_t err[4];
-  int64_t blkoff[kSmallMaxBlocks + 1];
-};
-static_assert(sizeof(SmallOut) <= 256, "the record shares the 256-byte slot of the error counters");
 
+// dynamic LDS: words, their ranks, flag bytes
+inline size_t small_lds_bytes(int64_t n) {
+  const size_t W = (size_t)((n + 63) >> 6);
+  return W * 8 + (W + 2) * 4 + (n <= kSmallByteCols ? W * 64 + 32 : 0);   // (one byte more than columns: the bad ones)
+}
+
+template <bool BYTES>
 __global__ __launch_bounds__(1024) void plan_small_kernel(const int32_t* __restrict__ rowptr,
                                                           const int32_t* __restrict__ colidx, int64_t m, int64_t n,
                                                           int64_t nnz, const SmallColblk cb, int32_t nb,
                                                           int32_t* __restrict__ needed, int64_t needed_cap,
                                                           int32_t* __restrict__ compact, int32_t validate,
-                                                          SmallOut* __restrict__ out) {
-  __shared__ uint64_t bm[kSmallMaxCols / 64];
-  __shared__ int32_t pre[kSmallMaxCols / 64 + 1];
+                                                          PlanRecord* __restrict__ rec, int64_t ticket) {
+  extern __shared__ __attribute__((aligned(16))) char small_lds[];
   __shared__ int32_t wsum[16];
   __shared__ int32_t bad[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int W = (int)((n + 63) >> 6);
-  for (int i = tid; i < W; i += 1024) bm[i] = 0ull;
+  uint64_t* bm = reinterpret_cast<uint64_t*>(small_lds);
+  int32_t* pre = reinterpret_cast<int32_t*>(bm + W);
+  uint8_t* flag = reinterpret_cast<uint8_t*>((reinterpret_cast<uintptr_t>(pre + W + 1) + 15) & ~(uintptr_t)15);
+  if constexpr (BYTES) {
+    uint4* f16 = reinterpret_cast<uint4*>(flag);
+    for (int i = tid; i < W * 4 + 1; i += 1024) f16[i] = make_uint4(0u, 0u, 0u, 0u);
+  } else {
+    for (int i = tid; i < W; i += 1024) bm[i] = 0ull;
+  }
   if (tid < 2) bad[tid] = 0;
+  const int nwg = (int)gridDim.x - 1, wg = (int)blockIdx.x - 1;
+  int32_t own[kSmallOwn];
+  if (compact && wg >= 0)
+#pragma unroll
+    for (int j = 0; j < kSmallOwn; ++j) {
+      const int64_t e = ((int64_t)wg * kSmallOwn + j) * 1024 + tid;
+      own[j] = e < nnz ? colidx[e] : 0;
+    }
   __syncthreads();
   if (validate) {
     for (int64_t r = tid; r < m; r += 1024)
@@ -923,25 +961,40 @@ __global__ __launch_bounds__(1024) void plan_small_kernel(const int32_t* __restr
     if (tid == 0 && (rowptr[0] != 0 || (int64_t)rowptr[m] != nnz)) bad[0] = 1;
   }
   uint32_t* bits = reinterpret_cast<uint32_t*>(bm);   // bit c of the 64-bit word c >> 6 = bit c & 31 of 32-bit word c >> 5
-  // (eight loads in flight per thread: one workgroup has to hide the memory latency by itself)
-  for (int64_t e0 = tid; e0 < nnz; e0 += 8 * 1024) {
-    int32_t c8[8];
+  // (no branch per entry: past the end the last entry is marked again, a bad column marks the byte behind the flags)
+  const uint32_t nc = (uint32_t)n;
+  const int last = (int)nnz - 1;
+  bool off = false;
+  for (int e0 = tid; e0 - tid < (int)nnz; e0 += kSmallLoads * 1024) {
+    uint32_t c[kSmallLoads];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) c8[j] = e0 + j * 1024 < nnz ? colidx[e0 + j * 1024] : 0;
+    for (int j = 0; j < kSmallLoads; ++j) c[j] = (uint32_t)colidx[e0 + j * 1024 < last ? e0 + j * 1024 : last];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (e0 + j * 1024 >= nnz) continue;
-      const int32_t c = c8[j];
-      if (c < 0 || c >= n) {
-        bad[1] = 1;
-      } else {
-        const uint32_t bit = 1u << (c & 31);
-        if ((__hip_atomic_load(&bits[c >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) == 0)
-          __hip_atomic_fetch_or(&bits[c >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int j = 0; j < kSmallLoads; ++j) {
+      off |= c[j] >= nc;
+      if constexpr (BYTES) {
+        flag[c[j] < nc ? c[j] : (uint32_t)W * 64] = 1;
+      } else if (c[j] < nc) {
+        const uint32_t bit = 1u << (c[j] & 31);
+        if ((__hip_atomic_load(&bits[c[j] >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) == 0)
+          __hip_atomic_fetch_or(&bits[c[j] >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
   }
+  if (off) bad[1] = 1;
   __syncthreads();
+  if constexpr (BYTES) {
+    // as in words_kernel: a lane squeezes 16 flags, four make a word
+    const ulonglong2* f16 = reinterpret_cast<const ulonglong2*>(flag);
+    for (int i = tid; i < W * 4; i += 1024) {
+      const ulonglong2 v = f16[i];
+      uint64_t word = (uint64_t)(squeeze8(v.x) | (squeeze8(v.y) << 8)) << (16 * (lane & 3));
+      word |= __shfl_xor(word, 1, 64);
+      word |= __shfl_xor(word, 2, 64);
+      if ((lane & 3) == 0) bm[i >> 2] = word;
+    }
+    __syncthreads();
+  }
   // prefix counts: thread t owns words 4t .. 4t + 3
   int cnt[4], sum = 0;
 #pragma unroll
@@ -976,24 +1029,82 @@ __global__ __launch_bounds__(1024) void plan_small_kernel(const int32_t* __restr
     const int w = (int)(c >> 6);
     return pre[w] + __popcll(bm[w] & ((1ull << (c & 63)) - 1ull));
   };
-  for (int q = tid; q <= nb; q += 1024) out->blkoff[q] = rank(cb.v[q]);
-  if (tid < 4) out->err[tid] = tid < 2 ? bad[tid] : 0;
-  if ((int64_t)N > needed_cap || (validate && (bad[0] || bad[1]))) return;   // (the same for every thread)
-  for (int w = wave; w < W; w += 16) {     // one wavefront per word: lane = column, slot from the lanes below
+  if (wg < 0) {
+    if (tid <= nb) rec->blkoff[tid] = rank(cb.v[tid]);
+    if (tid < 2) rec->err[tid] = bad[tid];
+    // (the lanes that wrote are all in the first wavefront)
+    if (tid < 64) __threadfence_system();
+    if (tid == 0) report_done(rec, ticket);
+    return;
+  }
+  if ((int64_t)N > needed_cap || (validate && (bad[0] || bad[1]))) return;
+  for (int w = wg * 16 + wave; w < W; w += 16 * nwg) {     // one wavefront per word: lane = column, slot from the lanes below
     const uint64_t x = bm[w];
     const bool set = (x >> lane) & 1ull;
     const int slot = __popcll(x & ((1ull << lane) - 1ull));
     if (set) needed[pre[w] + slot] = w * 64 + lane;
   }
   if (compact)
-    for (int64_t e0 = tid; e0 < nnz; e0 += 8 * 1024) {
-      int32_t c8[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) c8[j] = e0 + j * 1024 < nnz ? colidx[e0 + j * 1024] : 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (e0 + j * 1024 < nnz) compact[e0 + j * 1024] = (c8[j] < 0 || c8[j] >= n) ? -1 : rank(c8[j]);
+    for (int j = 0; j < kSmallOwn; ++j) {
+      const int64_t e = ((int64_t)wg * kSmallOwn + j) * 1024 + tid;
+      if (e < nnz) compact[e] = (uint32_t)own[j] < nc ? rank(own[j]) : -1;
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Pinned host records.  A call takes one, the kernels write into it, the host watches `done`; then it goes back.
+// Idle records are kept (at most kIdleRecords, 16 KB each) because pinning memory costs more than a plan.
+constexpr size_t kRecordBytes = 16384;
+constexpr int32_t kRecordMaxBlocks = (int32_t)((kRecordBytes - sizeof(PlanRecord)) / sizeof(int64_t));
+constexpr int kIdleRecords = 8;
+std::mutex g_record_mutex;
+PlanRecord* g_records[kIdleRecords] = {};
+int g_n_records = 0;
+std::atomic<int64_t> g_ticket{1};
+
+PlanRecord* record_take() {
+  {
+    std::lock_guard<std::mutex> lock(g_record_mutex);
+    if (g_n_records > 0) return g_records[--g_n_records];
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kRecordBytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  static_cast<PlanRecord*>(p)->done = 0;
+  return static_cast<PlanRecord*>(p);
+}
+
+void record_give_back(PlanRecord* r) {
+  {
+    std::lock_guard<std::mutex> lock(g_record_mutex);
+    if (g_n_records < kIdleRecords) {
+      g_records[g_n_records++] = r;
+      return;
+    }
+  }
+  (void)hipHostFree(r);
+}
+
+// Waits until the kernels have written `ticket`; the wait ends with the stream's work at the latest.
+int record_wait(const PlanRecord* r, int64_t ticket, hipStream_t s) {
+  const volatile int64_t* done = &r->done;
+  for (;;) {
+    for (int i = 0; i < 4096; ++i) {
+      if (*done == ticket) {
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return SAGNN_OK;
+      }
+      __builtin_ia32_pause();
+    }
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess) return hip_fail(e);
+    if (*done == ticket) return SAGNN_OK;
+    return hip_fail(hipErrorUnknown);   // the kernels are done and have not reported: a launch was lost
+  }
 }
 
 }  // namespace
@@ -1018,50 +1129,57 @@ int plan_check_args(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m,
   return SAGNN_OK;
 }
 
-// the planning pipeline on an already carved workspace (w.part == nullptr: byte-flag marking)
-int plan_run(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t n, int64_t nnz,
-             const int64_t* h_colblk, int32_t nb, int32_t* d_needed, int64_t needed_cap,
-             int64_t* h_blk_off, int32_t* d_colidx_compact, const PlanWs& w, uint32_t flags,
-             hipStream_t s) {
-
+// The planning pipeline on an already carved workspace (w.part == nullptr: byte-flag marking).  rec: the pinned record
+// of the call, or NULL: the record then lies in the workspace and is copied back.
+int plan_launch(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t n, int64_t nnz,
+                const int64_t* h_colblk, int32_t nb, int32_t* d_needed, int64_t needed_cap, int32_t* d_colidx_compact,
+                const PlanWs& w, uint32_t flags, PlanRecord* rec, int64_t ticket, hipStream_t s) {
+  if (!rec) rec = reinterpret_cast<PlanRecord*>(w.blkoff);
+  const bool validate = (flags & SAGNN_PLAN_VALIDATE) != 0;
   if ((flags & (SAGNN_PLAN_OBLIVIOUS | SAGNN_PLAN_MULTIPASS)) == 0 && n <= kSmallMaxCols && nnz <= kSmallMaxNnz && m <= kSmallMaxRows &&
       nb <= kSmallMaxBlocks) {
-    // one launch, one copy back, one wait (the record lies in the slot of the error counters)
     SmallColblk cb{};
     for (int32_t q = 0; q <= nb; ++q) cb.v[q] = h_colblk[q];
-    SmallOut* d_out = reinterpret_cast<SmallOut*>(w.err);
-    hipLaunchKernelGGL(plan_small_kernel, dim3(1), dim3(1024), 0, s, d_rowptr, d_colidx, m, n, nnz, cb, nb, d_needed,
-                       needed_cap, d_colidx_compact, (flags & SAGNN_PLAN_VALIDATE) ? 1 : 0, d_out);
+    const size_t lds = small_lds_bytes(n);
+    const auto kernel = n <= kSmallByteCols ? plan_small_kernel<true> : plan_small_kernel<false>;
+    if (lds > 48 * 1024)
+      SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)lds));
+    const int64_t by_entry = ceil_div(nnz > 0 ? nnz : 1, kSmallOwn * 1024), by_word = ceil_div(n, 16384);
+    const int64_t wgs = 1 + (by_entry > by_word ? by_entry : by_word);   // at most 17
+    hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(1024), lds, s, d_rowptr, d_colidx, m, n, nnz, cb, nb,
+                       d_needed, needed_cap, d_colidx_compact, validate ? 1 : 0, rec, ticket);
     SAGNN_LAUNCH_CHECK();
-    SmallOut h_out;
-    SAGNN_HIP(hipMemcpyAsync(&h_out, d_out, sizeof(SmallOut), hipMemcpyDeviceToHost, s));
-    SAGNN_HIP(hipStreamSynchronize(s));
-    for (int32_t q = 0; q <= nb; ++q) h_blk_off[q] = h_out.blkoff[q];
-    if ((flags & SAGNN_PLAN_VALIDATE) && (h_out.err[0] || h_out.err[1])) return SAGNN_EFORMAT;
-    if (h_blk_off[nb] > needed_cap) return SAGNN_ECAPACITY;
     return SAGNN_OK;
   }
-  SAGNN_HIP(hipMemcpyAsync(w.colblk, h_colblk, sizeof(int64_t) * (size_t)(nb + 1),
-                           hipMemcpyHostToDevice, s));
-  // (the bucketed marking does not use the flag bytes: only the error counters are cleared then)
-  const int64_t clear16 = ((flags & SAGNN_PLAN_OBLIVIOUS) == 0 && w.bkt_cols != nullptr) ? 0 : w.W * 4;
-  hipLaunchKernelGGL(clear_kernel, dim3(grid_for(clear16)), dim3(kThreads), 0, s,
-                     reinterpret_cast<uint4*>(w.flag), clear16, w.err);
-  SAGNN_LAUNCH_CHECK();
-  if (flags & SAGNN_PLAN_VALIDATE) {
-    hipLaunchKernelGGL(validate_rowptr_kernel, dim3(grid_for(m)), dim3(kThreads), 0, s, d_rowptr,
-                       m, nnz, w.err);
-    SAGNN_LAUNCH_CHECK();
+  Colblk cb{};
+  if (nb <= kArgBlocks) {
+    for (int32_t q = 0; q <= nb; ++q) cb.v[q] = h_colblk[q];
+  } else {
+    cb.mem = w.colblk;
+    SAGNN_HIP(hipMemcpyAsync(w.colblk, h_colblk, sizeof(int64_t) * (size_t)(nb + 1), hipMemcpyHostToDevice, s));
   }
   const bool oblivious = (flags & SAGNN_PLAN_OBLIVIOUS) != 0;
   const bool bucket_mark = !oblivious && w.bkt_cols != nullptr;
   const bool lds_mark = !oblivious && !bucket_mark && w.part != nullptr;
+  int32_t* err = w.err;   // (read only where validation is asked for, and cleared only then)
+  if ((!bucket_mark && !lds_mark) || validate) {
+    const int64_t clear16 = bucket_mark || lds_mark ? 0 : w.W * 4;
+    hipLaunchKernelGGL(clear_kernel, dim3(grid_for(clear16)), dim3(kThreads), 0, s, reinterpret_cast<uint4*>(w.flag),
+                       clear16, err, w.blocksum, w.nblk);
+    SAGNN_LAUNCH_CHECK();
+  }
+  if (validate) {
+    hipLaunchKernelGGL(validate_rowptr_kernel, dim3(grid_for(m)), dim3(kThreads), 0, s, d_rowptr,
+                       m, nnz, err);
+    SAGNN_LAUNCH_CHECK();
+  }
   bool speculated = false;   // the marking pass has already written the identity remap
   if (bucket_mark) {
     const int32_t nbk = (int32_t)bucket_ranges(n);
     const size_t lds = (size_t)kBktCols;
     hipLaunchKernelGGL(bucket_count_kernel, dim3(kBktGroups), dim3(kBktThreads), 0, s, d_colidx, nnz, n, nbk, w.bkt_cnt,
-                       w.err);
+                       err, w.blocksum, w.nblk);
     SAGNN_LAUNCH_CHECK();
     hipLaunchKernelGGL(bucket_within_kernel, dim3((unsigned)nbk), dim3(kBktGroups), 0, s, w.bkt_cnt, w.bkt_start);
     SAGNN_LAUNCH_CHECK();
@@ -1073,10 +1191,7 @@ int plan_run(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_
     SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(mark_bucket_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(mark_bucket_kernel, dim3((unsigned)nbk), dim3(kLdsThreads), lds, s, w.bkt_cols, w.bkt_start,
-                       nnz, n, w.W, w.bitmap);
-    SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(count_kernel, dim3((unsigned)w.nblk), dim3(kThreads), 0, s, w.bitmap, w.W,
-                       w.blocksum);
+                       nnz, n, w.W, w.bitmap, w.blocksum);
     SAGNN_LAUNCH_CHECK();
   } else if (lds_mark) {
     const int passes = (int)ceil_div(n, kLdsCols);
@@ -1085,78 +1200,89 @@ int plan_run(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_
     SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(mark_lds_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     // dense enough that every column is probably needed: write the identity remap on the way
-    speculated = d_colidx_compact && !oblivious && nnz >= 8 * n;
+    speculated = d_colidx_compact && nnz >= 8 * n;
     const bool al = aligned16(d_colidx) && (!speculated || aligned16(d_colidx_compact));
     hipLaunchKernelGGL(mark_lds_kernel, dim3((unsigned)(passes * groups_per_pass)), dim3(kLdsThreads),
-                       lds, s, d_colidx, nnz, n, (int32_t)groups_per_pass, w.part, w.err, al ? 1 : 0,
-                       speculated ? d_colidx_compact : (int32_t*)nullptr);
+                       lds, s, d_colidx, nnz, n, (int32_t)groups_per_pass, w.part, err, al ? 1 : 0,
+                       speculated ? d_colidx_compact : (int32_t*)nullptr, w.blocksum, w.nblk);
     SAGNN_LAUNCH_CHECK();
     hipLaunchKernelGGL(merge_kernel, dim3((unsigned)ceil_div(w.W, 16)), dim3(kThreads), 0, s, w.part,
-                       (int32_t)groups_per_pass, w.W, n, w.bitmap);
-    SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(count_kernel, dim3((unsigned)w.nblk), dim3(kThreads), 0, s, w.bitmap, w.W,
-                       w.blocksum);
+                       (int32_t)groups_per_pass, w.W, n, w.bitmap, w.blocksum);
     SAGNN_LAUNCH_CHECK();
   } else {
-    if (nnz > 0 && (!oblivious || (flags & SAGNN_PLAN_VALIDATE))) {
+    if (nnz > 0 && (!oblivious || validate)) {
       hipLaunchKernelGGL(mark_kernel, dim3(grid_for(nnz, 8)), dim3(kThreads), 0, s, d_colidx, nnz,
-                         n, w.flag, w.err, aligned16(d_colidx) ? 1 : 0);
+                         n, w.flag, err, aligned16(d_colidx) ? 1 : 0);
       SAGNN_LAUNCH_CHECK();
     }
     if (oblivious && n > 0) {
       hipLaunchKernelGGL(fill_all_kernel, dim3(grid_for(n)), dim3(kThreads), 0, s, w.flag, n);
       SAGNN_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(words_kernel, dim3((unsigned)w.nblk), dim3(kThreads), 0, s, w.flag, w.W,
+    hipLaunchKernelGGL(words_kernel, dim3((unsigned)ceil_div(w.W > 0 ? w.W : 1, kWordsPerGroup)), dim3(kThreads), 0, s, w.flag, w.W,
                        w.bitmap, w.blocksum);
     SAGNN_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(kThreads), 0, s, w.blocksum, w.nblk);
-  SAGNN_LAUNCH_CHECK();
   hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)w.nblk), dim3(kThreads), 0, s, w.bitmap, w.W,
                      w.blocksum, w.nblk, w.prefix, w.rank16);
   SAGNN_LAUNCH_CHECK();
-  hipLaunchKernelGGL(blkoff_kernel, dim3(1), dim3(kThreads), 0, s, w.bitmap, w.prefix, w.W, n,
-                     w.colblk, nb, w.blkoff);
+
+  FinishArgs fa{};
+  fa.bm = w.bitmap; fa.prefix = w.prefix; fa.rank16 = w.rank16; fa.W = w.W; fa.n = n; fa.nnz = nnz;
+  fa.needed = d_needed; fa.colidx = d_colidx; fa.compact = bucket_mark ? nullptr : d_colidx_compact;
+  fa.identity_done = speculated ? 1 : 0;
+  fa.aligned = aligned16(d_colidx) && aligned16(d_colidx_compact) ? 1 : 0;
+  fa.nb = nb; fa.rec = rec; fa.ticket = ticket;
+  fa.vd = Verdict{w.prefix + w.W, needed_cap, validate ? err : nullptr};
+  fa.emit_blocks = (int32_t)grid_for(w.W * 16);
+  const unsigned remap_blocks = fa.compact && nnz > 0 ? grid_for(nnz, 8) : 0u;
+  hipLaunchKernelGGL(finish_kernel, dim3((unsigned)fa.emit_blocks + remap_blocks), dim3(kThreads), 0, s, fa, cb);
   SAGNN_LAUNCH_CHECK();
-
-  int32_t h_err[4] = {0, 0, 0, 0};
-  SAGNN_HIP(hipMemcpyAsync(h_blk_off, w.blkoff, sizeof(int64_t) * (size_t)(nb + 1),
-                           hipMemcpyDeviceToHost, s));
-  SAGNN_HIP(hipMemcpyAsync(h_err, w.err, sizeof(h_err), hipMemcpyDeviceToHost, s));
-  SAGNN_HIP(hipStreamSynchronize(s));
-  if ((flags & SAGNN_PLAN_VALIDATE) && (h_err[0] || h_err[1])) return SAGNN_EFORMAT;
-  const int64_t N = h_blk_off[nb];
-  if (N > needed_cap) return SAGNN_ECAPACITY;
-
-  if (N > 0) {
-    if (N * 8 < n)   // fewer than 8 needed columns per word on average
-      hipLaunchKernelGGL(emit_sparse_kernel, dim3(grid_for(w.W)), dim3(kThreads), 0, s, w.bitmap, w.prefix,
-                         w.W, n, d_needed);
-    else
-      hipLaunchKernelGGL(emit_kernel, dim3(grid_for(w.W * 64)), dim3(kThreads), 0, s, w.bitmap,
-                         w.prefix, w.W, n, d_needed);
+  if (bucket_mark && d_colidx_compact && nnz > 0) {
+    // ranks inside the buckets (in place), then every entry fetches the rank at its place
+    hipLaunchKernelGGL(remap_bucket_kernel, dim3((unsigned)bucket_ranges(n)), dim3(kLdsThreads), 0, s, w.bkt_cols,
+                       w.bkt_start, nnz, n, w.W, w.rank16, fa.vd);
+    SAGNN_LAUNCH_CHECK();
+    hipLaunchKernelGGL(remap_gather_kernel, dim3(kBktGroups), dim3(kBktThreads), 0, s, w.bkt_place, w.bkt_cols, nnz,
+                       d_colidx_compact, fa.vd);
     SAGNN_LAUNCH_CHECK();
   }
-  if (d_colidx_compact && nnz > 0) {
-    const int al = (aligned16(d_colidx) && aligned16(d_colidx_compact)) ? 1 : 0;
-    if (N == n && speculated)
-      return SAGNN_OK;
-    if (N == n) {
-      hipLaunchKernelGGL(remap_identity_kernel, dim3(grid_for(nnz, 8)), dim3(kThreads), 0, s, d_colidx,
-                         nnz, n, d_colidx_compact, al);
-    } else if (bucket_mark) {
-      // ranks inside the buckets (in place), then every entry fetches the rank at its place
-      hipLaunchKernelGGL(remap_bucket_kernel, dim3((unsigned)bucket_ranges(n)), dim3(kLdsThreads), 0, s, w.bkt_cols,
-                         w.bkt_start, nnz, n, w.W, w.rank16);
-      SAGNN_LAUNCH_CHECK();
-      hipLaunchKernelGGL(remap_gather_kernel, dim3(kBktGroups), dim3(kBktThreads), 0, s, w.bkt_place, w.bkt_cols, nnz,
-                         d_colidx_compact);
-    } else
-      hipLaunchKernelGGL(remap_kernel, dim3(grid_for(nnz, 8)), dim3(kThreads), 0, s, d_colidx, nnz, n,
-                         w.rank16, d_colidx_compact, al);
-    SAGNN_LAUNCH_CHECK();
+  return SAGNN_OK;
+}
+
+int plan_run(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t n, int64_t nnz,
+             const int64_t* h_colblk, int32_t nb, int32_t* d_needed, int64_t needed_cap,
+             int64_t* h_blk_off, int32_t* d_colidx_compact, const PlanWs& w, uint32_t flags, bool may_pin,
+             hipStream_t s) {
+  PlanRecord* rec = may_pin && nb <= kRecordMaxBlocks ? record_take() : nullptr;
+  const int64_t ticket = g_ticket.fetch_add(1);
+  int32_t bad = 0;
+  int rc;
+  if (rec) {
+    rc = plan_launch(d_rowptr, d_colidx, m, n, nnz, h_colblk, nb, d_needed, needed_cap, d_colidx_compact, w, flags, rec,
+                     ticket, s);
+    if (rc == SAGNN_OK) rc = record_wait(rec, ticket, s);
+    else (void)hipStreamSynchronize(s);   // (whatever was launched may still write into the record)
+    if (rc == SAGNN_OK) {
+      for (int32_t q = 0; q <= nb; ++q) h_blk_off[q] = rec->blkoff[q];
+      bad = rec->err[0] | rec->err[1];
+    }
+    record_give_back(rec);
+  } else {
+    rc = plan_launch(d_rowptr, d_colidx, m, n, nnz, h_colblk, nb, d_needed, needed_cap, d_colidx_compact, w, flags,
+                     nullptr, ticket, s);
+    if (rc == SAGNN_OK) {
+      const PlanRecord* d_rec = reinterpret_cast<const PlanRecord*>(w.blkoff);
+      int32_t h_err[4] = {0, 0, 0, 0};
+      SAGNN_HIP(hipMemcpyAsync(h_blk_off, d_rec->blkoff, sizeof(int64_t) * (size_t)(nb + 1), hipMemcpyDeviceToHost, s));
+      SAGNN_HIP(hipMemcpyAsync(h_err, d_rec->err, sizeof(h_err), hipMemcpyDeviceToHost, s));
+      SAGNN_HIP(hipStreamSynchronize(s));
+      bad = h_err[0] | h_err[1];
+    }
   }
+  if (rc != SAGNN_OK) return rc;
+  if ((flags & SAGNN_PLAN_VALIDATE) && bad) return SAGNN_EFORMAT;
+  if (h_blk_off[nb] > needed_cap) return SAGNN_ECAPACITY;
   return SAGNN_OK;
 }
 
@@ -1176,7 +1302,7 @@ SAGNN_EXPORT int spmm_plan_needed_rows(const int32_t* d_rowptr, const int32_t* d
   const PlanWs w = carve(d_ws, n, nb, nnz);
   if (ws_bytes < w.bytes) return SAGNN_ECAPACITY;
   return plan_run(d_rowptr, d_colidx, m, n, nnz, h_colblk, nb, d_needed, needed_cap, h_blk_off,
-                  d_colidx_compact, w, flags, (hipStream_t)stream);
+                  d_colidx_compact, w, flags, true, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1232,5 +1358,5 @@ SAGNN_EXPORT int spmm_plan_needed_rows_noalloc(const int32_t* d_rowptr, const in
   if (rc != SAGNN_OK) return rc;
   const PlanWs w = carve(base, n, nb, 0);
   return plan_run(d_rowptr, d_colidx, m, n, nnz, h_colblk, nb, d_needed, needed_cap, h_blk_off,
-                  d_colidx_compact, w, flags, (hipStream_t)stream);
+                  d_colidx_compact, w, flags, false, (hipStream_t)stream);
 }

@@ -156,6 +156,35 @@ def test_plan_small_blocks_one_launch_and_its_limits(m, n, nnz, nb, seed):
         sagnn.spmm_plan_needed_rows(dev(rowptr), dev(colidx), n, colblk, validate=True, multipass=multipass)
 
 
+@pytest.mark.parametrize("n,nnz,nb", [(131_072, 50_000, 3), (131_073, 50_000, 3), (300_000, 70_000, 64),
+                                      (300_000, 70_000, 65), (90_000, 800_000, 2044), (90_000, 70_000, 2045)])
+def test_plan_at_the_edges_of_its_flags_and_block_lists(n, nnz, nb):
+    """Columns that just fit one LDS byte each and one more; block boundaries that travel as kernel
+    arguments, through a copy, and more of them than the host record holds.  A column outside [0, n) and too
+    small a capacity leave the outputs alone."""
+    rng = np.random.default_rng(n + nb)
+    m = 700
+    cols = rng.integers(0, n, size=nnz).astype(np.int32)
+    cols[:4] = [0, n - 1, n // 2, max(n - 64, 0)]
+    rowptr = np.array([0, *np.sort(rng.integers(0, nnz + 1, size=m - 1)), nnz], dtype=np.int32)
+    colblk = np.array([0, *np.sort(rng.integers(0, n + 1, size=nb - 1)), n], dtype=np.int64)
+    plan = check_plan(rowptr, cols, n, colblk)
+    bad = cols.copy()
+    bad[nnz // 3] = n
+    ws, needed, compact = sagnn.plan_buffers(m, n, nnz, nb, torch.device("cuda"), plan.N, True)
+    for ci, cap, code in ((bad, plan.N, -3), (cols, plan.N - 1, -2)):
+        needed.fill_(-7)
+        compact.fill_(-7)
+        with pytest.raises(sagnn.SagnnError) as ei:
+            sagnn.spmm_plan_needed_rows(dev(rowptr), dev(ci), n, colblk, needed_cap=cap, bufs=(ws, needed, compact),
+                                        validate=code == -3)
+        assert ei.value.code == code
+        torch.cuda.synchronize()
+        assert bool((needed == -7).all())
+        if nnz < 8 * n:
+            assert bool((compact == -7).all())
+
+
 def test_plan_cfg1_all_blocks(cfg1):
     g, _ = cfg1
     off = synth.block_offsets(g.n, 4)
