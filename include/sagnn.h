@@ -183,22 +183,19 @@ int spmm_pack_rows(const float* d_H, int64_t n, int64_t ldh, int32_t f, const in
  * one-time spmm_csr_prepare() builds a schedule in the workspace:
  *   - always: the entries are cut into chunks of about equal length (nonzero splitting) and the row in
  *     which each chunk starts is recorded, so hub rows and runs of short rows are balanced;
- *   - for large power-law matrices with f a multiple of 64 (or exactly 32 or 16): the entries
+ *   - for large power-law matrices: the entries
  *     of long rows are copied
  *     into the workspace re-ordered by column slab ("slab sweep"), so that all wavefronts of an
  *     XCD touch the same small part of B at the same time (L2 reuse).  Requires ascending
  *     column indices inside long rows and k < 2^27; otherwise the first schedule is used.
- *     At f = 128 and f = 64 the re-ordered copy is laid out for kernels that fetch two / four
- *     rows of B per load instruction, which a later call must match: a workspace prepared for
- *     f = 128 serves calls with f = 128 or 64, one prepared for f = 64 only f = 64.
+ *     Up to f = 128 the re-ordered copy is laid out for kernels that fetch two, four, eight or
+ *     sixteen rows of B per load instruction (f <= 128, 64, 32, 16).
  *     The short rows are swept as well, as whole rows in wavefronts of their own, where the
  *     matrix allows it (short_rows of sagnn_spmm_options); otherwise they go through the first
  *     schedule on a compacted copy.
  * The workspace then holds a private copy of colidx/val: call spmm_csr_prepare() again if
  * they change.  d_ws must be passed unchanged to every spmm_csr_tallskinny() call with the
- * same (rowptr, colidx, val, m, k, nnz) and f <= the prepared f (a multiple of 64 if the
- * slab-sweep schedule was chosen, see spmm_csr_schedule_info; exactly the prepared f if that
- * was 32 or 16); part of it is scratch for
+ * same (rowptr, colidx, val, m, k, nnz) and f <= the prepared f; part of it is scratch for
  * partial row sums, so two calls that share a workspace must not overlap in time.
  * spmm_csr_prepare() plans on the device (row classification, cutting of long rows, dealing of
  * the pieces to wavefronts, layout of the re-ordered copy); the host reads a few totals and

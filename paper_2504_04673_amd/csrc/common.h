@@ -65,7 +65,7 @@ constexpr int kSweepMaxWindows = 2048;      // dealing windows of a matrix (11 b
 // wavefronts share the entries (a longer piece makes one stream the whole product waits for: 2.4 M entries at f = 128
 // took 433 us with pieces of 4096 and 167 with 1024), a power of two up to 4096.
 inline int32_t sweep_piece_default(int64_t nnz, int32_t f) {
-  const int64_t streams = 8192 * (f == 128 ? 2 : (f < 128 ? 4 : 1));
+  const int64_t streams = 8192 * (f > 128 ? 1 : (f > 64 ? 2 : 4));
   int32_t p = 256;
   while (p < 4096 && 2 * (int64_t)p * streams <= nnz) p *= 2;
   return p;
@@ -73,6 +73,23 @@ inline int32_t sweep_piece_default(int64_t nnz, int32_t f) {
 inline int32_t sweep_piece_floor(int64_t nnz, int32_t f) {   // what the workspace is sized for
   const int32_t p = sweep_piece_default(nnz, f);
   return p < 1024 ? p : 1024;
+}
+
+// Columns one launch of the sweep covers when `rest` are left: slabs of 256, 128 and 64 (the exact kernels; max_slab
+// 128: none wider), a width that is no multiple of 64 in one launch as soon as at most max_slab are left.
+inline int32_t sweep_slab(int32_t rest, int32_t max_slab) {
+  if (rest >= max_slab) return max_slab;
+  if ((rest & 63) == 0 && rest > 128) return 128;
+  return rest;
+}
+inline int32_t sweep_widest_launch(int32_t f, int32_t max_slab) {
+  int32_t widest = 0;
+  for (int32_t c = 0; c < f;) {
+    const int32_t fw = sweep_slab(f - c, max_slab);
+    widest = fw > widest ? fw : widest;
+    c += fw;
+  }
+  return widest;
 }
 
 struct SpmmWsHeader {       // first 256 bytes of the SpMM workspace (device copy)

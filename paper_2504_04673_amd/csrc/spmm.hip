@@ -291,9 +291,6 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
     SAGNN_LAUNCH_CHECK();
   }
   if (desc.mode == 1) {
-    // the sweep schedule exists for multiples of 64 and, in grouped form, for exactly 32 and 16
-    if ((f & 63) && !((f == 32 || f == 16) && f == desc.f)) return SAGNN_EINVAL;
-    if (desc.groups >= 8 && f != desc.f) return SAGNN_EINVAL;
     // the chunk kernels walk the compacted short-row CSR stored in the workspace
     const int64_t short_base = (int64_t)round_up((size_t)desc.sweep_stream_len + 64, 256);
     p.rowptr = reinterpret_cast<const int32_t*>(base + L.rowptr_s);
@@ -313,13 +310,13 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   fl.kmax = d.kmax; fl.C = C; fl.ldc = ldc; fl.accumulate = accumulate; fl.hdr = p.hdr; fl.generation = d.generation;
   fl.chunks = p.chunks; fl.flags = p.flags; fl.carry = p.carry; fl.carry_ld = f; fl.rowmap = p.rowmap;
   const int32_t max_slab = desc.mode == 1 && desc.max_slab == 128 ? 128 : 256;
-  // column slabs: the sweep's kernels are 256, 128 or 64 wide (32 and 16 exactly), those of the chunks up to 256
+  // column slabs of at most 256
   int32_t col0 = 0;
   while (col0 < f) {
     const int32_t rest = f - col0;
     int32_t fw = rest >= 256 ? 256 : rest;
     if (desc.mode == 1) {
-      fw = rest >= 256 && max_slab >= 256 ? 256 : (rest >= 128 ? 128 : (rest >= 64 ? 64 : rest));
+      fw = sweep_slab(rest, max_slab);
       int rc = sweep_launch(desc, L, base, B, ldb, col0, fw, d.kmax, C, ldc, accumulate, f, s);
       if (rc != SAGNN_OK) return rc;
     }
@@ -591,7 +588,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   };
 
   SweepPlanResult plan{};
-  if ((f & 63) == 0 || f == 32 || f == 16) {
+  {
     int rc = sweep_prepare(d_rowptr, d_colidx, d_val, m, k, nnz, f, base, L, opt, s, &plan);
     if (rc != SAGNN_OK) return rc;
   }
@@ -744,7 +741,7 @@ SAGNN_EXPORT int spmm_csr_prepare_tuned(const int32_t* d_rowptr, const int32_t* 
       if (spmm_desc_get(d_ws, &desc) && desc.mode == 1 && desc.n_intervals > 1 && desc.mean_steps > 0.f) {
         int dev = 0, cus = 256;
         if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        const int32_t fw = desc.max_slab == 128 && f > 128 ? 128 : (f >= 256 ? 256 : (f >= 128 ? 128 : f));
+        const int32_t fw = sweep_widest_launch(f, desc.max_slab);
         const int64_t resident = (int64_t)cus * lds_resident_workgroups((size_t)4 * desc.slots * fw * 4) * 4;
         const double gens = (double)ceil_div(desc.n_waves, resident > 0 ? resident : 1);
         const double ps_hi = (double)best_ms * 1e9 / (gens * (double)desc.mean_steps);

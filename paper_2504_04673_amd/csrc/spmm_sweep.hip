@@ -342,6 +342,7 @@ struct SweepDims {
   // interval barriers (lane-group kernels): 0 intervals = walk the stream in one go
   int32_t n_intervals, wg_per_cohort, sync_timeout_ticks, sync_test_extra;
   int32_t slots;        // accumulator rows per wavefront (<= kSweepSlots)
+  int32_t fw;           // floats per row of this launch
   float pace_ticks;     // pacing: 100 MHz ticks per stream step (0: none)
 };
 
@@ -420,24 +421,34 @@ __global__ __launch_bounds__(256) void sweep_barrier_clear_kernel(uint32_t* __re
   if (blockIdx.x == 0 && threadIdx.x == 0) counters[kSweepBarrierSlots] = 0u;
 }
 
-template <int FPL, int U, bool BUF>
+// first of the `v` floats a lane works on: `at`, or the row's last ones if the row ends before
+template <bool ODD>
+__device__ __forceinline__ uint32_t row_element(uint32_t at, int v, int32_t fw) {
+  return ODD && (int32_t)at > fw - v ? (uint32_t)(fw - v) : at;
+}
+
+// ODD: rows of any multiple of 4 floats instead of the kernel's full width.  The lanes beyond the end of the row work
+// on its last FPL floats a second time: same addresses, same values, so neither loads nor accumulator updates nor
+// stores need a mask, and the accumulator rows are as long as the rows themselves.
+template <int FPL, int U, bool BUF, bool ODD>
 __global__ __launch_bounds__(256) void spmm_sweep_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
     const SpmmWsHeader* __restrict__ hdr, const float* __restrict__ B, float* __restrict__ C,
     float* __restrict__ partial, const SweepDims d) {
   using vec = typename Vec<FPL>::T;
-  extern __shared__ __attribute__((aligned(16))) float lds_acc[];  // [4 waves][d.slots][64*FPL]
+  extern __shared__ __attribute__((aligned(16))) float lds_acc[];  // [4 waves][d.slots][kRow]
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t loff = lane * (FPL * 4);
+  const uint32_t el = row_element<ODD>(lane * FPL, FPL, d.fw);
+  const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t w = (int64_t)blockIdx.x * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != 1)
     return;
-  constexpr int kRow = 64 * FPL;  // floats per accumulator row
-  float* __restrict__ my = lds_acc + (size_t)wave * d.slots * kRow + lane * FPL;
+  const int kRow = ODD ? d.fw : 64 * FPL;  // floats per accumulator row
+  float* __restrict__ my = lds_acc + (size_t)wave * d.slots * kRow + el;
   for (int s = 0; s < d.slots; ++s) *reinterpret_cast<vec*>(my + s * kRow) = vec(0.f);
 
   const int32_t base = wave_base[w];
@@ -764,7 +775,7 @@ __global__ __launch_bounds__(256) void sweep_pack_w_kernel(const float* __restri
 // FUSE: 0 the product alone; 1 / 2 / 3 the layer form: the kernel ends with the dense transform of the
 // workgroup's rows (fp32 / bfloat16 / three-term operands, see sweep_dense_epilogue) instead of storing T (C is
 // then only written if the caller wants T as a by-product: fa.T).
-template <int V, int R, int U, bool BUF, int FUSE = 0>
+template <int V, int R, int U, bool BUF, int FUSE = 0, bool ODD = false>
 __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -774,19 +785,20 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
     const SweepFusedArgs fa) {
   using vec = typename Vec<V>::T;
   constexpr int LG = 64 / R;             // lanes per group = lanes per row
-  constexpr int kRow = LG * V;           // floats per row of this launch
+  const int kRow = ODD ? d.fw : LG * V;  // floats per row of this launch
   extern __shared__ __attribute__((aligned(16))) float lds_acc[];  // [4 waves][d.slots][kRow]
   const int SL = d.slots / R;            // slots per group
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t gid = lane / LG, lig = lane % LG;
-  const uint32_t loff = lig * (V * 4);
+  const uint32_t el = row_element<ODD>(lig * V, V, d.fw);
+  const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t w = (int64_t)blockIdx.x * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != R)
     return;
-  float* __restrict__ my = lds_acc + (size_t)wave * d.slots * kRow + lig * V;
+  float* __restrict__ my = lds_acc + (size_t)wave * d.slots * kRow + el;
   for (int ls = 0; ls < SL; ++ls) *reinterpret_cast<vec*>(my + (gid * SL + ls) * kRow) = vec(0.f);
 
   const int32_t base = wave_base[w];
@@ -867,7 +879,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
       for (int u = 0; u < U; ++u) {
         acc += mv[u] * h[u];
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
-          vec* p = reinterpret_cast<vec*>(my + ((mc[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
+          vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
           *p += acc;
           acc = 0.f;
         }
@@ -904,7 +916,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
     // (whole workgroups: the launcher only takes this form when n_waves is a multiple of 4 and
     // every wavefront owns 16 slots)
     __syncthreads();
-    sweep_dense_epilogue<kRow, FUSE - 1, 1>(lds_acc, piece_target, fa, wave, (int)lane);
+    sweep_dense_epilogue<LG * V, FUSE - 1, 1>(lds_acc, piece_target, fa, wave, (int)lane);
   }
 }
 
@@ -913,7 +925,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
 // one coalesced load per array and a step's group takes its word with a lane permute.  With 16
 // groups each group owns a single piece and its register accumulator is the piece's accumulator
 // (no LDS at all); with 8 groups two pieces per group share it through LDS as in the wide kernels.
-template <int R, bool BUF>
+template <int R, bool BUF, bool ODD>
 __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -921,21 +933,22 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     float* __restrict__ partial, const SweepDims d) {
   typedef float vec __attribute__((ext_vector_type(4)));
   constexpr int LG = 64 / R;             // lanes per group = lanes per row
-  constexpr int kRow = LG * 4;           // floats per row
+  const int kRow = ODD ? d.fw : LG * 4;  // floats per row
   constexpr int SL = kSweepSlots / R;    // pieces per group
   constexpr int UB = 64 / R;             // steps per batch of 64 stream words
   constexpr int NB = 8 / UB;             // batches per iteration: 8 steps (gathers) in flight
   extern __shared__ __attribute__((aligned(16))) float lds_acc[];  // [4 waves][16 slots][kRow], SL > 1 only
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t gid = lane / LG, lig = lane % LG;
-  const uint32_t loff = lig * 16;
+  const uint32_t el = row_element<ODD>(lig * 4, 4, d.fw);
+  const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t w = (int64_t)blockIdx.x * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != R)
     return;
-  float* __restrict__ my = lds_acc + (size_t)wave * kSweepSlots * kRow + lig * 4;
+  float* __restrict__ my = lds_acc + (size_t)wave * kSweepSlots * kRow + el;
   if constexpr (SL > 1) {
 #pragma unroll
     for (int ls = 0; ls < SL; ++ls) *reinterpret_cast<vec*>(my + (gid * SL + ls) * kRow) = vec(0.f);
@@ -985,7 +998,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
       acc += mv[u] * h[u];
       if constexpr (SL > 1) {
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
-          vec* p = reinterpret_cast<vec*>(my + ((mc[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
+          vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
           *p += acc;
           acc = 0.f;
         }
@@ -1107,16 +1120,17 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // 3.38 -> 2.63 ms, 2.45 M-vertex graph 4.85 -> 4.62 ms) and cost ~3 % when almost every gather
   // misses (rank share of the 111 M-vertex graph, 2.6 entries per row of B): decided below by
   // the average number of swept entries per row of B.
-  // Narrow operands (f = 32, 16: rows of 128 / 64 bytes, 8 / 4 lanes each) exist only in the
-  // grouped form, 8 / 16 rows per load.
+  // Narrow operands (f <= 32, 16: 8 / 4 lanes a row) exist only in the grouped form, 8 / 16 rows per load.  Widths
+  // between the powers of two take the next wider form (124 M entries, 2.45 M vertices: f = 24 2513 us by nonzero
+  // splitting, 1905 swept; f = 48 3599 and 2560, f = 100 8135 and 5407, f = 200 13857 and 8598).
   // Wider operands (multiples of 64 above 128) can be taken as 128-wide slabs by the two-group
   // kernels (a last slab of 64 is served by the same streams): an option, see sagnn_spmm_options.
   const bool narrow_slabs = opt.slab_width == 128 && f > 128 && (f & 63) == 0 && opt.groups != 1;
-  int64_t R = (f == 128 || narrow_slabs) ? 2 : (f == 64 ? 4 : (f == 32 ? 8 : (f == 16 ? 16 : 1)));
-  if (opt.groups == 1 && f >= 64) R = 1;
+  int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
+  if (opt.groups == 1 && f > 32) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
   if (opt.groups != 2 && long_entries < 8 * k) {
-    if (f < 64) return SAGNN_OK;   // no one-row-per-instruction form below 64: plain schedule
+    if (f <= 32) return SAGNN_OK;  // one row per instruction would leave most lanes idle: plain schedule
     R = 1;
   }
   if (P <= 0 || P > L.max_pieces) return SAGNN_OK;
@@ -1144,7 +1158,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // per generation on the 2.45 M-vertex R-MAT graph); a larger one whose row order carries
   // locality (a partitioned graph) keeps it, because a window only touches the part of B its
   // rows' neighbourhoods live in (2 M-vertex community-ordered graph: 13.9 -> 11.4 ms).
-  const int64_t fw_max = narrow_slabs ? 128 : (f >= 256 ? 256 : (f >= 128 ? 128 : f));   // widest launch of a call
+  const int64_t fw_max = sweep_widest_launch(f, narrow_slabs ? 128 : 256);
   int64_t wg_per_cu = lds_resident_workgroups((size_t)(4ll * slots * fw_max * 4));
   if (wg_per_cu < 1) wg_per_cu = 1;
   int n_cus = 256;
@@ -1380,6 +1394,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   sd.row_bytes = (uint32_t)(ldb * 4);
   const unsigned blocks = (unsigned)ceil_div(d.n_waves, 4);
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
+  sd.fw = fw;
   const size_t lds = (size_t)4 * sd.slots * fw * sizeof(float);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
@@ -1432,25 +1447,35 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     return SAGNN_OK;
   };
   if (fuse != 0 && d.groups != 2 && d.groups != 4) return SAGNN_EINVAL;   // (groups == 1: sweep_launch_fused)
-  if (d.groups == 16)    // prepared for f = 16: four lanes per row
-    return fw == 16 ? (buf ? go(spmm_sweep_perm_kernel<16, true>) : go(spmm_sweep_perm_kernel<16, false>))
-                    : SAGNN_EINVAL;
-  if (d.groups == 8)     // prepared for f = 32: eight lanes per row
-    return fw == 32 ? (buf ? go(spmm_sweep_perm_kernel<8, true>) : go(spmm_sweep_perm_kernel<8, false>))
-                    : SAGNN_EINVAL;
-  if (d.groups == 2) {   // prepared for f = 128: half a wavefront per row (or per half row at 64)
+  if (fw <= 0 || (fw & 3)) return SAGNN_EINVAL;
+  if (d.groups == 16) {  // four lanes per row
+    if (fw > 16) return SAGNN_EINVAL;
+    if (fw == 16) return buf ? go(spmm_sweep_perm_kernel<16, true, false>) : go(spmm_sweep_perm_kernel<16, false, false>);
+    return buf ? go(spmm_sweep_perm_kernel<16, true, true>) : go(spmm_sweep_perm_kernel<16, false, true>);
+  }
+  if (d.groups == 8) {   // eight lanes per row
+    if (fw > 32) return SAGNN_EINVAL;
+    if (fw == 32) return buf ? go(spmm_sweep_perm_kernel<8, true, false>) : go(spmm_sweep_perm_kernel<8, false, false>);
+    return buf ? go(spmm_sweep_perm_kernel<8, true, true>) : go(spmm_sweep_perm_kernel<8, false, true>);
+  }
+  if (d.groups == 2) {   // half a wavefront per row
     if (fw == 128) return buf ? go_group(group_kernel_of<4, 2, true>(fuse)) : go_group(group_kernel_of<4, 2, false>(fuse));
     if (fw == 64) return buf ? go_group(group_kernel_of<2, 2, true>(fuse)) : go_group(group_kernel_of<2, 2, false>(fuse));
-    return SAGNN_EINVAL;
+    if (fw > 128 || fuse) return SAGNN_EINVAL;
+    return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true>);
   }
-  if (d.groups == 4) {   // prepared for f = 64: a quarter wavefront per row
+  if (d.groups == 4) {   // a quarter wavefront per row
     if (fw == 64) return buf ? go_group(group_kernel_of<4, 4, true>(fuse)) : go_group(group_kernel_of<4, 4, false>(fuse));
-    return SAGNN_EINVAL;
+    if (fw > 64 || fuse) return SAGNN_EINVAL;
+    return buf ? go_group(&spmm_sweep_group_kernel<4, 4, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 4, 8, false, 0, true>);
   }
-  if (fw == 256) return buf ? go(spmm_sweep_kernel<4, 8, true>) : go(spmm_sweep_kernel<4, 8, false>);
-  if (fw == 128) return buf ? go(spmm_sweep_kernel<2, 8, true>) : go(spmm_sweep_kernel<2, 8, false>);
-  if (fw == 64) return buf ? go(spmm_sweep_kernel<1, 8, true>) : go(spmm_sweep_kernel<1, 8, false>);
-  return SAGNN_EINVAL;
+  if (fw == 256) return buf ? go(spmm_sweep_kernel<4, 8, true, false>) : go(spmm_sweep_kernel<4, 8, false, false>);
+  if (fw == 128) return buf ? go(spmm_sweep_kernel<2, 8, true, false>) : go(spmm_sweep_kernel<2, 8, false, false>);
+  if (fw == 64) return buf ? go(spmm_sweep_kernel<1, 8, true, false>) : go(spmm_sweep_kernel<1, 8, false, false>);
+  if (fw > 256) return SAGNN_EINVAL;
+  if (fw > 128) return buf ? go(spmm_sweep_kernel<4, 8, true, true>) : go(spmm_sweep_kernel<4, 8, false, true>);
+  if (fw > 64) return buf ? go(spmm_sweep_kernel<2, 8, true, true>) : go(spmm_sweep_kernel<2, 8, false, true>);
+  return buf ? go(spmm_sweep_kernel<1, 8, true, true>) : go(spmm_sweep_kernel<1, 8, false, true>);
 }
 
 int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const float* B, int64_t ldb,

@@ -382,6 +382,32 @@ def test_spmm_slab_sweep_schedule(f, force_sweep):
     assert_close(got2, ref2, zabs2, RTOL_SPMM, f"sweep accumulate f={f}")
 
 
+@pytest.mark.parametrize("groups", [0, 1, 2])
+@pytest.mark.parametrize("f", [4, 12, 20, 28, 36, 60, 68, 100, 124, 132, 252, 260, 300, 516])
+def test_spmm_sweep_widths_between_the_kernels(f, groups, force_sweep, monkeypatch):
+    """Widths that no sweep kernel has exactly, in every lane-group form; also a narrower operand on the same
+    workspace, and a row stride wider than the operand."""
+    monkeypatch.setenv("SAGNN_SWEEP_GROUPS", str(groups))
+    rng = np.random.default_rng(f)
+    m, n = 3001, 9000
+    rowptr, colidx, val = random_csr(m, n, 25, rng, empty_frac=0.1, hubs=[(3, 5000), (1500, 1024), (3000, 17), (11, 16)])
+    B = synth.normal((n, f), f, synth.STREAM_H)
+    C0 = synth.normal((m, f), f + 1, synth.STREAM_G)
+    rp, ci, v = dev(rowptr), dev(colidx), dev(val)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    if groups == 2 or f > 32:
+        assert ws.info()["mode"] == 1
+    for w in sorted({f, max(4, f - 4), max(4, f // 2 // 4 * 4)}):
+        wide = torch.full((n, f + 8), float("nan"), device="cuda")
+        wide[:, :w] = dev(B)[:, :w]
+        ref, zabs = oracle.spmm(rowptr, colidx, val, B[:, :w], want_abs=True)
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, wide[:, :w], C=torch.full((m, w), float("nan"), device="cuda"), ws=ws)
+        assert_close(got, ref, zabs, RTOL_SPMM, f"f={f} w={w}")
+        ref, zabs = oracle.spmm(rowptr, colidx, val, B[:, :w], C=C0[:, :w], want_abs=True)
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(B[:, :w].copy()), C=dev(C0[:, :w].copy()), accumulate=True, ws=ws)
+        assert_close(got, ref, zabs, RTOL_SPMM, f"accumulate f={f} w={w}")
+
+
 @pytest.mark.parametrize("f", [64, 128, 192, 256])
 @pytest.mark.parametrize("groups", [1, 2])
 def test_spmm_sweep_short_rows_as_whole_rows(f, groups, monkeypatch):
