@@ -92,6 +92,25 @@ inline int32_t sweep_widest_launch(int32_t f, int32_t max_slab) {
   return widest;
 }
 
+// Cache lines of 128 bytes a row of f floats touches on average when rows lie ldb floats apart (the first row aligned)
+inline double spmm_row_lines(int32_t f, int64_t ldb) {
+  int lines = 0;
+  for (int i = 0; i < 32; ++i) lines += (int)(((ldb * 4 * i) % 128 + (int64_t)f * 4 + 127) / 128);
+  return lines / 32.0;
+}
+inline int32_t spmm_padded_width(int32_t f) { return f <= 16 ? 16 : (f + 31) / 32 * 32; }
+// Whether k rows of B are copied to rows that begin on a cache line (on half of one where f <= 16) before nnz of them
+// are gathered.  Time of the saved lines and of the copy at the rates both run at (7.5 TB/s of lines that miss the L2,
+// copies 4.8 TB/s); hits save a quarter of that, hence the margin: 400 k vertices, 8 M entries lose 10 us of 143 at f = 24
+// (3.6 times the copy), 1 M vertices, 50 M entries gain 95 of 680 (9 times), 300 of 1323 at f = 60 (6 times) and 310 of
+// 2212 at f = 124 (3 times).  Small operands stay in the L2s and are not copied.
+inline bool spmm_pad_pays(int64_t k, int64_t nnz, int32_t f, int64_t ldb) {
+  const int32_t fp = spmm_padded_width(f);
+  if (f > 128 || k * (int64_t)f * 4 < (8 << 20)) return false;
+  const double saved = spmm_row_lines(f, ldb) - spmm_row_lines(f, fp);
+  return (double)nnz * saved * 128 / 7.5 > (f <= 64 ? 4 : 2) * ((double)k * (f + fp) * 4 / 4.8);
+}
+
 struct SpmmWsHeader {       // first 256 bytes of the SpMM workspace (device copy)
   uint32_t magic;
   int32_t has_empty_rows;   // some row of the matrix has no entries
@@ -120,8 +139,9 @@ static_assert(sizeof(SpmmWsHeader) <= 256, "header must fit its slot");
 // Fixed layout (a function of m, k, nnz, f only; every array has its worst-case size):
 struct SpmmWsLayout {
   size_t header, chunks, fix_list, flags, rowptr_s, rowmap_s, code, vals, piece_info, piece_target,
-      wave_base, wave_steps, sync_off, barrier, sched, multi_row, multi_first, partial, carry, plan, wpack, total;
+      wave_base, wave_steps, sync_off, barrier, sched, multi_row, multi_first, partial, carry, plan, wpack, padded, total;
   int64_t max_chunks, max_pieces, max_waves, max_multi_rows, max_multi_pieces, stream_cap;
+  int64_t padded_rows;   // rows of B the padded copy has room for
 };
 
 inline int64_t spmm_nchunks(int64_t nnz, int64_t T) { return ceil_div(nnz, T); }
@@ -182,6 +202,9 @@ inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
   // W of a fused layer call packed for the bfloat16 matrix instructions (at most 256 x 256, up to
   // three terms per element)
   L.wpack = take(3 * 256 * 256 * 2);
+  // the layout does not know how many rows B has: as many as A where a copy pays then
+  L.padded_rows = spmm_pad_pays(m, nnz, f, f) ? m : 0;
+  L.padded = take(sizeof(float) * (size_t)L.padded_rows * (size_t)spmm_padded_width(f));
   L.total = off;
   return L;
 }

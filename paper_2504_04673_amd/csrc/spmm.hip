@@ -151,6 +151,27 @@ __global__ __launch_bounds__(kBlock) void spmm_zero_empty_kernel(SPMM_PTR_PARAMS
   }
 }
 
+// Rows of B moved to rows that begin on a cache line (see spmm_pad_pays): a row of 96 bytes touches one line instead of
+// one and a half.  1 M rows, 50 M entries, f = 24: 677 -> 585 us with the copy, f = 60: 1323 -> 1023.
+__global__ __launch_bounds__(kBlock) void spmm_pad_kernel(const float* __restrict__ B, int64_t ldb, int32_t f4,
+                                                          int64_t quads, float* __restrict__ out, int32_t ld_out) {
+  const int64_t q0 = (int64_t)blockIdx.x * (4 * kBlock) + threadIdx.x;
+  float4 v[4];
+  int64_t r[4];
+  int32_t c[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int64_t q = q0 + j * kBlock;
+    if (q >= quads) break;
+    r[j] = (uint64_t)q < 0x80000000ull ? (uint32_t)q / (uint32_t)f4 : q / f4;
+    c[j] = (int32_t)(q - r[j] * f4) * 4;
+    v[j] = *reinterpret_cast<const float4*>(B + r[j] * ldb + c[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (q0 + j * kBlock < quads) *reinterpret_cast<float4*>(out + r[j] * ld_out + c[j]) = v[j];
+}
+
 // ------------------------------------------------------------------------------------------
 // fallback without a prepared workspace: one wavefront per row, float4 pieces along f
 __global__ __launch_bounds__(kBlock) void spmm_row_kernel(SPMM_PTR_PARAMS, const SpmmDims d,
@@ -286,6 +307,16 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   d.generation = desc.generation;
   d.nchunks = desc.c_nchunks;
 
+  if (k <= L.padded_rows && f <= desc.f && spmm_padded_width(f) <= spmm_padded_width(desc.f) && spmm_pad_pays(k, nnz, f, ldb)) {
+    float* padded = reinterpret_cast<float*>(base + L.padded);
+    const int32_t fp = spmm_padded_width(f);
+    const int64_t quads = k * (f / 4);
+    hipLaunchKernelGGL(spmm_pad_kernel, dim3((unsigned)ceil_div(quads, 4 * kBlock)), dim3(kBlock), 0, s, B, ldb, f / 4,
+                       quads, padded, fp);
+    SAGNN_LAUNCH_CHECK();
+    B = p.B = padded;
+    ldb = d.ldb = fp;
+  }
   if (!accumulate && desc.has_empty_rows) {
     launch_waves(spmm_zero_empty_kernel, capped_grid(ceil_div(m, kWavesPerBlock)), p, d, s, f);
     SAGNN_LAUNCH_CHECK();

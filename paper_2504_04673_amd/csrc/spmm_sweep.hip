@@ -1070,6 +1070,12 @@ __global__ __launch_bounds__(256) void sweep_combine_kernel(
 
 std::atomic<uint64_t> g_generation{1};
 
+// Floats per accumulator row for which LDS is asked.  Rows of 97 to 127 floats would let a fifth workgroup onto a CU;
+// four are faster because their wavefronts drift apart less (1 M vertices, 50 M entries, f = 100: 1592 against
+// 1943 us; f = 80 with six workgroups 1326 against 1337; above 128 every further wavefront counts: f = 140 2088 against
+// 3052 us with the two that rows of 256 allow).
+int32_t sweep_lds_width(int32_t fw) { return fw > 96 && fw < 128 ? 128 : fw; }
+
 }  // namespace
 
 // ---------------------------------------------------------------------------------------
@@ -1159,7 +1165,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // locality (a partitioned graph) keeps it, because a window only touches the part of B its
   // rows' neighbourhoods live in (2 M-vertex community-ordered graph: 13.9 -> 11.4 ms).
   const int64_t fw_max = sweep_widest_launch(f, narrow_slabs ? 128 : 256);
-  int64_t wg_per_cu = lds_resident_workgroups((size_t)(4ll * slots * fw_max * 4));
+  int64_t wg_per_cu = lds_resident_workgroups((size_t)(4ll * slots * sweep_lds_width(fw_max) * 4));
   if (wg_per_cu < 1) wg_per_cu = 1;
   int n_cus = 256;
   {
@@ -1395,7 +1401,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   const unsigned blocks = (unsigned)ceil_div(d.n_waves, 4);
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
   sd.fw = fw;
-  const size_t lds = (size_t)4 * sd.slots * fw * sizeof(float);
+  const size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),

@@ -408,6 +408,33 @@ def test_spmm_sweep_widths_between_the_kernels(f, groups, force_sweep, monkeypat
         assert_close(got, ref, zabs, RTOL_SPMM, f"accumulate f={f} w={w}")
 
 
+@pytest.mark.parametrize("f,n", [(12, 200_000), (24, 90_000), (28, 90_001), (60, 40_000), (124, 20_000)])
+@pytest.mark.parametrize("sweep", [False, True])
+def test_spmm_rows_moved_to_cache_lines(f, n, sweep, monkeypatch):
+    """Widths and entry counts at which B is copied to aligned rows first, by both schedules: rows of B with gaps between
+    them, fewer rows of B than the workspace has room for, more of them (no copy then)."""
+    monkeypatch.setenv("SAGNN_SWEEP", "1" if sweep else "0")
+    rng = np.random.default_rng(f)
+    deg = 30 if f < 60 else 60
+    for m, k in ((n, n), (n, n - 777), (n // 2, n)):
+        nnz = deg * n
+        rowptr = np.concatenate([[0], np.cumsum(rng.multinomial(nnz, np.full(m, 1.0 / m)))]).astype(np.int32)
+        rows = np.repeat(np.arange(m), np.diff(rowptr))
+        colidx = rng.integers(0, k, size=nnz)
+        colidx = colidx[np.lexsort((colidx, rows))].astype(np.int32)
+        val = rng.standard_normal(nnz).astype(np.float32)
+        B = synth.normal((k, f), f, synth.STREAM_H)
+        rp, ci, v = dev(rowptr), dev(colidx), dev(val)
+        ws = sagnn.spmm_csr_prepare(rp, ci, v, k, f)
+        wide = torch.full((k, f + 4), float("nan"), device="cuda")
+        wide[:, :f] = dev(B)
+        ref = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double(), (m, k)) @ dev(B).double()
+        zabs = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double().abs(), (m, k)) @ dev(B).double().abs()
+        for operand in (dev(B), wide[:, :f]):
+            got = sagnn.spmm_csr_tallskinny(rp, ci, v, operand, C=torch.full((m, f), float("nan"), device="cuda"), ws=ws)
+            assert_close(got, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} m={m} k={k}")
+
+
 @pytest.mark.parametrize("f", [64, 128, 192, 256])
 @pytest.mark.parametrize("groups", [1, 2])
 def test_spmm_sweep_short_rows_as_whole_rows(f, groups, monkeypatch):
