@@ -28,7 +28,6 @@ namespace {
 
 constexpr int kT = 256;
 constexpr int kRowTile = kT * 8;          // rows per workgroup in the row passes
-constexpr uint32_t kFullUnit = 0xFFFFFFFFu;
 
 enum Stat : int {
   ST_MID = 0,       // entries in rows of kSweepMinLong..63 entries
@@ -59,6 +58,7 @@ __global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restr
     else if (d >= kSweepMinLong && d < 64) mid += d;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && (rowptr[0] != 0 || (int64_t)rowptr[m] != nnz)) bad = 1;
+  __shared__ long long part[kT / 64][3];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     mid += __shfl_down(mid, o, 64);
@@ -66,9 +66,16 @@ __global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restr
     bad += __shfl_down(bad, o, 64);
   }
   if ((threadIdx.x & 63) == 0) {
-    if (mid) atomicAdd(&stat[ST_MID], (unsigned long long)mid);
-    if (empty) atomicAdd(&stat[ST_EMPTY], (unsigned long long)empty);
-    if (bad) atomicAdd(&stat[ST_BAD], (unsigned long long)bad);
+    part[threadIdx.x >> 6][0] = mid;
+    part[threadIdx.x >> 6][1] = empty;
+    part[threadIdx.x >> 6][2] = bad;
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    static_assert(ST_MID == 0 && ST_EMPTY == 1 && ST_BAD == 2, "order of part[]");
+    long long t = 0;
+    for (int w = 0; w < kT / 64; ++w) t += part[w][threadIdx.x];
+    if (t) atomicAdd(&stat[threadIdx.x], (unsigned long long)t);
   }
 }
 
@@ -306,23 +313,20 @@ __global__ __launch_bounds__(kT) void plan_fill_tables_kernel(int32_t* __restric
 }
 
 __global__ __launch_bounds__(kT) void plan_zero_units_kernel(int32_t* __restrict__ load, int32_t* __restrict__ used,
-                                                             int64_t U, int32_t* __restrict__ done,
-                                                             int32_t* __restrict__ assigned, int32_t nwin) {
+                                                             int64_t U, int32_t* __restrict__ done, int32_t nwin) {
   const int64_t stride = (int64_t)gridDim.x * kT;
   for (int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x; u < U; u += stride) {
     load[u] = 0;
     used[u] = 0;
   }
   if (blockIdx.x == 0)
-    for (int w = threadIdx.x; w < nwin; w += kT) {
-      done[w] = 0;
-      assigned[w] = 0;
-    }
+    for (int w = threadIdx.x; w < nwin; w += kT) done[w] = 0;
 }
 
 struct DealDims {
   int64_t P, window, U;    // pieces, pieces per window, streams (units) in all
   int32_t nwin, R, SL;     // windows, lane groups per wavefront, slots per unit
+  int32_t load_bits, win_bits;   // of a stream's sort key: an open stream's length, its window; one more bit: not open
 };
 
 __device__ __forceinline__ int32_t window_of_unit(const int32_t* __restrict__ win_unit0, int32_t nwin, int64_t u) {
@@ -347,17 +351,20 @@ __device__ __forceinline__ void put_piece(int32_t* __restrict__ info, int32_t* _
   target[g] = mf < 0 ? row : -mf - 1;
 }
 
-// sort key of a stream: (window, length) while it has a free slot and its window has pieces left
+// sort key of a stream: (window, length) while it has a free slot and its window has pieces left.
+// done_next starts as a copy of done (the windows in which nothing is dealt keep theirs).
 __global__ __launch_bounds__(kT) void deal_keys_kernel(DealDims d, const int32_t* __restrict__ win_unit0,
                                                        const int32_t* __restrict__ load,
                                                        const int32_t* __restrict__ used,
                                                        const int32_t* __restrict__ done,
-                                                       uint32_t* __restrict__ keys) {
+                                                       int32_t* __restrict__ done_next, uint32_t* __restrict__ keys) {
+  if (blockIdx.x == 0)
+    for (int w = threadIdx.x; w < d.nwin; w += kT) done_next[w] = done[w];
   const int64_t stride = (int64_t)gridDim.x * kT;
   for (int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x; u < d.U; u += stride) {
     const int32_t w = window_of_unit(win_unit0, d.nwin, u);
     const bool open = used[u] < d.SL && (int64_t)done[w] < window_pieces(d, w);
-    keys[u] = open ? (((uint32_t)w << 20) | (uint32_t)load[u]) : kFullUnit;
+    keys[u] = open ? (((uint32_t)w << d.load_bits) | (uint32_t)load[u]) : 1u << (d.load_bits + d.win_bits);
   }
 }
 
@@ -366,7 +373,7 @@ __global__ __launch_bounds__(kT) void deal_first_kernel(DealDims d, const uint32
                                                         int32_t* __restrict__ first) {
   const int w = blockIdx.x * kT + threadIdx.x;
   if (w >= d.nwin) return;
-  const uint32_t wkey = (uint32_t)w << 20;
+  const uint32_t wkey = (uint32_t)w << d.load_bits;
   int64_t lo = 0, hi = d.U;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
@@ -376,7 +383,9 @@ __global__ __launch_bounds__(kT) void deal_first_kernel(DealDims d, const uint32
 }
 
 // position i of the sorted streams: the rank-th shortest open stream of its window takes the
-// rank-th largest piece the window has left, for rank < B = half the window's streams
+// rank-th largest piece the window has left, for rank < B = half the window's streams.  The last of them in a window
+// says how many have been dealt (one atomic per stream instead was a queue of U additions to one word:
+// 148 us a batch of 33 k streams, now 4).
 __global__ __launch_bounds__(kT) void deal_assign_kernel(DealDims d, const int32_t* __restrict__ win_unit0,
                                                          const uint32_t* __restrict__ skeys,
                                                          const uint32_t* __restrict__ sunit,
@@ -384,35 +393,25 @@ __global__ __launch_bounds__(kT) void deal_assign_kernel(DealDims d, const int32
                                                          const uint32_t* __restrict__ piece_order, PieceArrays pa,
                                                          int32_t* __restrict__ load, int32_t* __restrict__ used,
                                                          const int32_t* __restrict__ done,
-                                                         int32_t* __restrict__ assigned, int32_t* __restrict__ info,
+                                                         int32_t* __restrict__ done_next, int32_t* __restrict__ info,
                                                          int32_t* __restrict__ target) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (i >= d.U) return;
-  const uint32_t key = skeys[i];
-  if (key == kFullUnit) return;
-  const int32_t w = (int32_t)(key >> 20);
-  if (w >= d.nwin) return;
+  const int32_t w = (int32_t)(skeys[i] >> d.load_bits);
+  if (w >= d.nwin) return;      // (not open)
   const int64_t rank = i - (d.nwin > 1 ? (int64_t)first[w] : 0);
   const int64_t units_w = (int64_t)win_unit0[w + 1] - win_unit0[w];
   const int64_t B = units_w / 2 > 0 ? units_w / 2 : 1;
   const int64_t left = window_pieces(d, w) - done[w];
-  if (rank >= B || rank >= left) return;
+  const int64_t most = B < left ? B : left;
+  if (rank >= most) return;
+  if (rank == most - 1 || i + 1 == d.U || (int32_t)(skeys[i + 1] >> d.load_bits) != w) done_next[w] = done[w] + (int32_t)rank + 1;
   const int64_t id = piece_order[(int64_t)w * d.window + done[w] + rank];
   const int64_t u = sunit[i];
   const int32_t slot = used[u];
   used[u] = slot + 1;
   load[u] += pa.size[id];
   put_piece(info, target, (u / d.R) * kSweepSlots + (u % d.R) * d.SL + slot, pa, id);
-  atomicAdd(&assigned[w], 1);
-}
-
-__global__ __launch_bounds__(kT) void deal_advance_kernel(int32_t* __restrict__ done, int32_t* __restrict__ assigned,
-                                                          int32_t nwin) {
-  const int w = blockIdx.x * kT + threadIdx.x;
-  if (w < nwin) {
-    done[w] += assigned[w];
-    assigned[w] = 0;
-  }
 }
 
 // flag[0] = 1 if a window still has pieces, else 0 (one workgroup)
@@ -500,7 +499,7 @@ PlanScratch carve_plan(char* base, int64_t max_pieces, int64_t max_units) {
 struct PlanSmall {               // the L.plan region
   unsigned long long* stat;      // [ST_COUNT]
   unsigned long long* win_entries;  // [kSweepMaxWindows]
-  int32_t *win_unit0, *done, *assigned;   // [kSweepMaxWindows + 1] each
+  int32_t *win_unit0, *done, *done_next;   // [kSweepMaxWindows + 1] each
   int32_t* tilesum;              // [5][ntiles + 1]
 };
 
@@ -511,7 +510,7 @@ PlanSmall carve_small(char* ws, const SpmmWsLayout& L) {
   p.win_entries = reinterpret_cast<unsigned long long*>(b); b += 8 * (size_t)kSweepMaxWindows;
   p.win_unit0 = reinterpret_cast<int32_t*>(b); b += 4 * (size_t)(kSweepMaxWindows + 64);
   p.done = reinterpret_cast<int32_t*>(b); b += 4 * (size_t)(kSweepMaxWindows + 64);
-  p.assigned = reinterpret_cast<int32_t*>(b); b += 4 * (size_t)(kSweepMaxWindows + 64);
+  p.done_next = reinterpret_cast<int32_t*>(b); b += 4 * (size_t)(kSweepMaxWindows + 64);
   p.tilesum = reinterpret_cast<int32_t*>(b);
   return p;
 }
@@ -537,7 +536,9 @@ int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int64_t nnz, int32_t opt
   const int64_t ntiles = ceil_div(m, kRowTile);
   hipLaunchKernelGGL(plan_zero_kernel, dim3(1), dim3(kT), 0, s, sm.stat, d_flag);
   SAGNN_LAUNCH_CHECK();
-  hipLaunchKernelGGL(plan_rowstat_kernel, grid_for(m), dim3(kT), 0, s, d_rowptr, m, nnz, sm.stat);
+  // (few workgroups: all of them add to one cache line)
+  hipLaunchKernelGGL(plan_rowstat_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(m, kT), 512)), dim3(kT), 0, s, d_rowptr, m,
+                     nnz, sm.stat);
   SAGNN_LAUNCH_CHECK();
   hipLaunchKernelGGL(plan_rule_kernel, dim3(1), dim3(64), 0, s, sm.stat, nnz, opt_min_long);
   SAGNN_LAUNCH_CHECK();
@@ -608,7 +609,7 @@ int sweep_plan_deal_short(char* ws, const SpmmWsLayout& L, int64_t P_long, int64
 }
 
 int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, const int32_t* h_win_unit0,
-                    int32_t nwin, int64_t n_waves4, int32_t R, int32_t SL, bool snake, hipStream_t s) {
+                    int32_t nwin, int64_t n_waves4, int32_t R, int32_t SL, int32_t piece_max, bool snake, hipStream_t s) {
   const PlanSmall sm = carve_small(ws, L);
   const PlanScratch sc = carve_plan(ws + L.code, L.max_pieces, L.max_waves * kSweepSlots);
   int32_t* d_flag = reinterpret_cast<int32_t*>(ws + L.carry);
@@ -635,14 +636,17 @@ int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, 
   uint32_t* piece_order = sc.piece_keys;
   SAGNN_HIP(hipMemcpyAsync(piece_order, sc.radix.pay[res], sizeof(uint32_t) * (size_t)P, hipMemcpyDeviceToDevice, s));
 
-  DealDims d{P, window, U, nwin, R, SL};
+  // (an open stream holds at most SL - 1 pieces; a window of the key that is not open sorts behind all of them)
+  int load_bits = 0;
+  while (((int64_t)(SL - 1) * piece_max) >> load_bits) ++load_bits;
+  DealDims d{P, window, U, nwin, R, SL, load_bits, wbits};
   if (snake) {
     hipLaunchKernelGGL(deal_snake_kernel, grid_for(P), dim3(kT), 0, s, d, sm.win_unit0, piece_order, sc.pa, info,
                        target, d_flag + 2);
     SAGNN_LAUNCH_CHECK();
     return SAGNN_OK;
   }
-  hipLaunchKernelGGL(plan_zero_units_kernel, grid_for(U), dim3(kT), 0, s, sc.load, sc.used, U, sm.done, sm.assigned,
+  hipLaunchKernelGGL(plan_zero_units_kernel, grid_for(U), dim3(kT), 0, s, sc.load, sc.used, U, sm.done,
                      nwin);
   SAGNN_LAUNCH_CHECK();
   // A stream has a free slot in at most SL batches after the batches of B pieces have ended, and
@@ -656,11 +660,12 @@ int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, 
     per_unit = std::max(per_unit, ceil_div(n_w, std::max<int64_t>(units_w / 2, 1)));
   }
   int next_check = (int)std::min<int64_t>(per_unit + 1, max_batches);
+  int32_t *done = sm.done, *done_next = sm.done_next;
   for (int b = 0; b < max_batches; ++b) {
-    hipLaunchKernelGGL(deal_keys_kernel, grid_for(U), dim3(kT), 0, s, d, sm.win_unit0, sc.load, sc.used, sm.done,
-                       sc.unit_keys);
+    hipLaunchKernelGGL(deal_keys_kernel, grid_for(U), dim3(kT), 0, s, d, sm.win_unit0, sc.load, sc.used, done,
+                       done_next, sc.unit_keys);
     SAGNN_LAUNCH_CHECK();
-    rc = radix_sort_pairs(sc.unit_keys, nullptr, U, nwin > 1 ? 20 + wbits : 24, sc.radix, s, &res);
+    rc = radix_sort_pairs(sc.unit_keys, nullptr, U, load_bits + wbits + 1, sc.radix, s, &res);
     if (rc != SAGNN_OK) return rc;
     int32_t* first = reinterpret_cast<int32_t*>(sm.win_entries);   // the window sums have been read back
     if (nwin > 1) {
@@ -669,14 +674,12 @@ int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, 
       SAGNN_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(deal_assign_kernel, dim3((unsigned)ceil_div(U, kT)), dim3(kT), 0, s, d, sm.win_unit0,
-                       sc.radix.keys[res], sc.radix.pay[res], first, piece_order, sc.pa, sc.load, sc.used, sm.done,
-                       sm.assigned, info, target);
+                       sc.radix.keys[res], sc.radix.pay[res], first, piece_order, sc.pa, sc.load, sc.used, done,
+                       done_next, info, target);
     SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(deal_advance_kernel, dim3((unsigned)ceil_div(nwin, kT)), dim3(kT), 0, s, sm.done, sm.assigned,
-                       nwin);
-    SAGNN_LAUNCH_CHECK();
+    std::swap(done, done_next);
     if (b + 1 == next_check || b + 1 == max_batches) {
-      hipLaunchKernelGGL(deal_check_kernel, dim3(1), dim3(kT), 0, s, d, sm.done, d_flag + 2);
+      hipLaunchKernelGGL(deal_check_kernel, dim3(1), dim3(kT), 0, s, d, done, d_flag + 2);
       SAGNN_LAUNCH_CHECK();
       int32_t left = 0;
       SAGNN_HIP(hipMemcpyAsync(&left, d_flag + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s));
