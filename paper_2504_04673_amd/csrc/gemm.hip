@@ -7,7 +7,7 @@
 // Tall-skinny shapes: m is 10^5..10^7 rows, the feature widths are <= 256, so W fits in LDS
 // and every kernel streams the tall operand from HBM exactly once.
 //
-// gemm_nn_kernel (Z = X op(W)): a workgroup stages its slab of W in LDS once and then walks
+// gemm_nn_kernel (gemm_nn.h, one source file per operand mode; Z = X op(W)): a workgroup stages its slab of W in LDS once and then walks
 // row tiles persistently; each wavefront owns a 32-row tile and keeps NT 32x32 accumulator
 // tiles in registers.  The A operand of the MFMA is read straight from global memory in
 // operand layout: the k order inside an MFMA does not matter as long as both operands agree,
@@ -27,307 +27,10 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "gemm.h"
 
 namespace sagnn {
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-struct GemmArgs {
-  const float* X; int64_t ldx;
-  const float* W; int64_t ldw; int32_t transW;
-  int64_t m; int32_t kdim, nout;
-  int32_t act;
-  const float* mask; int64_t ldmask;
-  float* Z; int64_t ldz;
-  float* A; int64_t lda;
-  int32_t n0;  // first output column of this launch's slab
-};
-
-// Split mode: a finite fp32 number x is the exact sum of three bfloat16 numbers: t1 = x rounded to
-// nearest, t2 = (x - t1) rounded, t3 = x - t1 - t2, which needs no rounding (8 + 8 + 8 significant
-// bits); both subtractions are exact, |t2| <= 2^-8 |x| and |t3| <= 2^-16 |x|.
-__device__ __forceinline__ void split3(float x, __bf16& t1, __bf16& t2, __bf16& t3) {
-  t1 = (__bf16)x;
-  const float r = x - (float)t1;
-  t2 = (__bf16)r;
-  t3 = (__bf16)(r - (float)t2);
-}
-
-// ------------------------------------------------------------------------------------------
-// KPAD: kdim is not a multiple of 32, loads of X are guarded against the real k extent.
-// NG > 0: the k loop has exactly NG groups of 32 and is fully unrolled.  In straight-line code the
-// compiler counts outstanding loads exactly; around a loop back-edge it waits for ALL of them,
-// which would make the prefetch of the next group useless.
-template <int NT, int PREC, int WAVES, bool KPAD, int NG>
-__global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int NB = NT * 32;
-  constexpr bool BF16 = PREC == SAGNN_GEMM_BF16;
-  constexpr bool SPLIT = PREC == SAGNN_GEMM_FP32_BF16X3;
-  const int tid = threadIdx.x;
-  const int kreal = g.kdim;                  // any multiple of 4
-  const int kdim = (kreal + 31) & ~31;       // the k loop runs over the zero-padded extent
-
-  // stage the W slab: fp32 as Ws[k][n]; bf16 packed as Ws[k/8][n][k%8] (split mode: three such
-  // planes, one per term); zero outside W
-  for (int idx = tid; idx < kdim * NB; idx += WAVES * 64) {
-    const int k = idx / NB, n = idx - k * NB;
-    const int col = g.n0 + n;
-    float w = 0.f;
-    if (col < g.nout && k < kreal)
-      w = g.transW ? g.W[(int64_t)col * g.ldw + k] : g.W[(int64_t)k * g.ldw + col];
-    if (SPLIT) {
-      __bf16* Wp = reinterpret_cast<__bf16*>(smem);
-      const int at = ((k >> 3) * NB + n) * 8 + (k & 7);
-      split3(w, Wp[at], Wp[kdim * NB + at], Wp[2 * kdim * NB + at]);
-    } else if (BF16) {
-      reinterpret_cast<__bf16*>(smem)[((k >> 3) * NB + n) * 8 + (k & 7)] = (__bf16)w;
-    } else {
-      reinterpret_cast<float*>(smem)[k * NB + n] = w;
-    }
-  }
-  __syncthreads();
-
-  const int lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 31, h = lane >> 5;
-  const int64_t ntiles = (g.m + 31) >> 5;
-  for (int64_t t = (int64_t)blockIdx.x * WAVES + wave; t < ntiles; t += (int64_t)gridDim.x * WAVES) {
-    int64_t row = t * 32 + r;
-    if (row >= g.m) row = g.m - 1;  // clamped read, result discarded at the store
-    const float* __restrict__ xrow = g.X + row * g.ldx;
-    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    auto ldx4 = [&](int col) {   // X[row][col..col+3], zero beyond the real k extent
-      if constexpr (KPAD) return col < kreal ? *reinterpret_cast<const float4*>(xrow + col) : zero4;
-      else return *reinterpret_cast<const float4*>(xrow + col);
-    };
-    floatx16 acc[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[nt][v] = 0.f;
-
-    // The k loop runs in groups of JB steps; the A-operand loads of the next group are issued
-    // before the MFMAs of the current one, so HBM latency hides behind matrix-core work.
-    if (SPLIT) {
-      const bf16x8* __restrict__ Ws = reinterpret_cast<const bf16x8*>(smem);
-      const int plane = (kdim >> 3) * NB;      // bf16x8 elements per term plane
-      constexpr int JB = 2;
-      const int ngroups = NG > 0 ? NG : kdim / (16 * JB);
-      float4 cur[JB][2], nxt[JB][2];
-#pragma unroll
-      for (int q = 0; q < JB; ++q) {
-        cur[q][0] = ldx4(16 * q + 8 * h);
-        cur[q][1] = ldx4(16 * q + 8 * h + 4);
-      }
-#pragma unroll
-      for (int gi = 0; gi < (NG > 0 ? NG : ngroups); ++gi) {
-        if (gi + 1 < ngroups) {
-#pragma unroll
-          for (int q = 0; q < JB; ++q) {
-            nxt[q][0] = ldx4(16 * ((gi + 1) * JB + q) + 8 * h);
-            nxt[q][1] = ldx4(16 * ((gi + 1) * JB + q) + 8 * h + 4);
-          }
-        }
-        if constexpr (NG > 0) __builtin_amdgcn_sched_barrier(0);   // keep the prefetch ahead of this group's MFMAs
-#pragma unroll
-        for (int q = 0; q < JB; ++q) {
-          const int j = gi * JB + q;
-          const float xs[8] = {cur[q][0].x, cur[q][0].y, cur[q][0].z, cur[q][0].w,
-                               cur[q][1].x, cur[q][1].y, cur[q][1].z, cur[q][1].w};
-          bf16x8 a1, a2, a3;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            __bf16 t1, t2, t3;
-            split3(xs[i], t1, t2, t3);
-            a1[i] = t1; a2[i] = t2; a3[i] = t3;
-          }
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const int at = (2 * j + h) * NB + nt * 32 + r;
-            const bf16x8 b1 = Ws[at], b2 = Ws[plane + at], b3 = Ws[2 * plane + at];
-            // the six products down to 2^-16 of the leading one, smallest first
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b1, acc[nt], 0, 0, 0);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b3, acc[nt], 0, 0, 0);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2, acc[nt], 0, 0, 0);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b1, acc[nt], 0, 0, 0);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b2, acc[nt], 0, 0, 0);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[nt], 0, 0, 0);
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < JB; ++q) {
-          cur[q][0] = nxt[q][0];
-          cur[q][1] = nxt[q][1];
-        }
-      }
-    } else if (BF16) {
-      const bf16x8* __restrict__ Ws = reinterpret_cast<const bf16x8*>(smem);
-      constexpr int JB = 2;
-      const int ngroups = NG > 0 ? NG : kdim / (16 * JB);
-      float4 cur[JB][2], nxt[JB][2];
-#pragma unroll
-      for (int q = 0; q < JB; ++q) {
-        cur[q][0] = ldx4(16 * q + 8 * h);
-        cur[q][1] = ldx4(16 * q + 8 * h + 4);
-      }
-#pragma unroll
-      for (int gi = 0; gi < (NG > 0 ? NG : ngroups); ++gi) {
-        if (gi + 1 < ngroups) {
-#pragma unroll
-          for (int q = 0; q < JB; ++q) {
-            nxt[q][0] = ldx4(16 * ((gi + 1) * JB + q) + 8 * h);
-            nxt[q][1] = ldx4(16 * ((gi + 1) * JB + q) + 8 * h + 4);
-          }
-        }
-        if constexpr (NG > 0) __builtin_amdgcn_sched_barrier(0);   // keep the prefetch ahead of this group's MFMAs
-#pragma unroll
-        for (int q = 0; q < JB; ++q) {
-          const int j = gi * JB + q;
-          const float4 x0 = cur[q][0], x1 = cur[q][1];
-          bf16x8 a;
-          a[0] = (__bf16)x0.x; a[1] = (__bf16)x0.y; a[2] = (__bf16)x0.z; a[3] = (__bf16)x0.w;
-          a[4] = (__bf16)x1.x; a[5] = (__bf16)x1.y; a[6] = (__bf16)x1.z; a[7] = (__bf16)x1.w;
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const bf16x8 b = Ws[(2 * j + h) * NB + nt * 32 + r];
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[nt], 0, 0, 0);
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < JB; ++q) {
-          cur[q][0] = nxt[q][0];
-          cur[q][1] = nxt[q][1];
-        }
-      }
-    } else {
-      const float* __restrict__ Ws = reinterpret_cast<const float*>(smem);
-      constexpr int JB = 4;
-      const int ngroups = NG > 0 ? NG : kdim / (8 * JB);
-      float4 cur[JB], nxt[JB];
-#pragma unroll
-      for (int q = 0; q < JB; ++q) cur[q] = ldx4(8 * q + 4 * h);
-#pragma unroll
-      for (int gi = 0; gi < (NG > 0 ? NG : ngroups); ++gi) {
-        if (gi + 1 < ngroups) {
-#pragma unroll
-          for (int q = 0; q < JB; ++q)
-            nxt[q] = ldx4(8 * ((gi + 1) * JB + q) + 4 * h);
-        }
-        if constexpr (NG > 0) __builtin_amdgcn_sched_barrier(0);   // keep the prefetch ahead of this group's MFMAs
-#pragma unroll
-        for (int q = 0; q < JB; ++q) {
-          const int j = gi * JB + q;
-          const float xs[4] = {cur[q].x, cur[q].y, cur[q].z, cur[q].w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float* wrow = Ws + (8 * j + 4 * h + i) * NB + r;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-              acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[i], wrow[nt * 32], acc[nt], 0, 0, 0);
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < JB; ++q) cur[q] = nxt[q];
-      }
-    }
-
-    if (t * 32 + 32 <= g.m && g.n0 + NB <= g.nout) {
-      // full tile: no bounds checks; one base pointer per output array, rows reached by adding
-      // the leading dimension (the 16 values of a lane are rows 8*(v/4) + 4*h + v%4)
-      const int64_t row0 = t * 32 + h * 4;
-      const int col0 = g.n0 + r;
-      const float* mk = g.mask ? g.mask + row0 * g.ldmask + col0 : nullptr;
-      float* zp = g.Z ? g.Z + row0 * g.ldz + col0 : nullptr;
-      float* ap = g.A ? g.A + row0 * g.lda + col0 : nullptr;
-      const bool relu = g.act == SAGNN_ACT_RELU;
-      if (mk) {
-        // the mask is applied in a pass of its own: between the stores below its loads would each
-        // have to wait for the store before them (the arrays may alias as far as the compiler
-        // knows), one memory round trip per element
-        // and its loads are issued a batch at a time (16 to 32 in flight) ahead of their uses
-        constexpr int VB = NT >= 8 ? 2 : 4;
-#pragma unroll
-        for (int v0 = 0; v0 < 16; v0 += VB) {
-          float mv[VB][NT];
-#pragma unroll
-          for (int dv = 0; dv < VB; ++dv) {
-            const int64_t dr = ((v0 + dv) >> 2) * 8 + ((v0 + dv) & 3);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) mv[dv][nt] = mk[dr * g.ldmask + nt * 32];
-          }
-          __builtin_amdgcn_sched_barrier(0);   // keep the batch of loads together, ahead of the selects
-#pragma unroll
-          for (int dv = 0; dv < VB; ++dv)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-              if (!(mv[dv][nt] > 0.f)) acc[nt][v0 + dv] = 0.f;
-        }
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t dr = (v >> 2) * 8 + (v & 3);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const float z = acc[nt][v];
-          if (zp) zp[dr * g.ldz + nt * 32] = z;
-          if (ap) ap[dr * g.lda + nt * 32] = relu ? (z > 0.f ? z : 0.f) : z;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int col = g.n0 + nt * 32 + r;
-        if (col >= g.nout) continue;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t ro = t * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
-          if (ro >= g.m) continue;
-          float z = acc[nt][v];
-          if (g.mask && !(g.mask[ro * g.ldmask + col] > 0.f)) z = 0.f;
-          if (g.Z) g.Z[ro * g.ldz + col] = z;
-          if (g.A) g.A[ro * g.lda + col] = (g.act == SAGNN_ACT_RELU) ? (z > 0.f ? z : 0.f) : z;
-        }
-      }
-    }
-  }
-}
-
-template <int NT, int PREC, int WAVES>
-int launch_nn_waves(const GemmArgs& g, size_t lds, hipStream_t s) {
-  void (*kern)(const GemmArgs) = gemm_nn_kernel<NT, PREC, WAVES, false, 0>;
-  if (g.kdim & 31) kern = gemm_nn_kernel<NT, PREC, WAVES, true, 0>;
-  else if (g.kdim == 128) kern = gemm_nn_kernel<NT, PREC, WAVES, false, 4>;
-  else if (g.kdim == 256) kern = gemm_nn_kernel<NT, PREC, WAVES, false, 8>;
-  SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  const int64_t ntiles = (g.m + 31) / 32;
-  int64_t blocks = ceil_div(ntiles, WAVES);
-  const int64_t per_cu = lds > 80 * 1024 ? 1 : (lds > 40 * 1024 ? 2 : 4);
-  if (blocks > 256 * per_cu) blocks = 256 * per_cu;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(WAVES * 64), lds, s, g);
-  SAGNN_LAUNCH_CHECK();
-  return SAGNN_OK;
-}
-
-// bytes of LDS the W slab of NT*32 columns takes (split mode: three bfloat16 planes)
-inline size_t nn_slab_bytes(int32_t kdim, int nt, int prec) {
-  const size_t elems = (size_t)((kdim + 31) & ~31) * nt * 32;
-  return prec == SAGNN_GEMM_FP32 ? elems * 4 : (prec == SAGNN_GEMM_BF16 ? elems * 2 : elems * 6);
-}
-
-template <int NT, int PREC>
-int launch_nn(const GemmArgs& g, hipStream_t s) {
-  const size_t lds = nn_slab_bytes(g.kdim, NT, PREC);
-  if (lds > 160 * 1024) return SAGNN_EINVAL;
-  // fp32: 4 wavefronts per workgroup, two workgroups per CU while the W slab allows it; when the
-  // slab is so large that only one workgroup fits a CU, 8 wavefronts keep two per SIMD
-  if (PREC != SAGNN_GEMM_FP32 || lds > 80 * 1024) return launch_nn_waves<NT, PREC, 8>(g, lds, s);
-  return launch_nn_waves<NT, PREC, 4>(g, lds, s);
-}
 
 // ------------------------------------------------------------------------------------------
 // Y = X^T S.  KB rows per stage; LDS rows padded to KP elements (16-byte multiple).
@@ -811,10 +514,10 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
   if (prec == SAGNN_GEMM_BF16) {
     g.n0 = 0;
     const int tiles = (nout + 31) / 32;
-    if (tiles <= 1) return launch_nn<1, SAGNN_GEMM_BF16>(g, s);
-    if (tiles <= 2) return launch_nn<2, SAGNN_GEMM_BF16>(g, s);
-    if (tiles <= 4) return launch_nn<4, SAGNN_GEMM_BF16>(g, s);
-    return launch_nn<8, SAGNN_GEMM_BF16>(g, s);
+    if (tiles <= 1) return gemm_nn_bf16(1, g, s);
+    if (tiles <= 2) return gemm_nn_bf16(2, g, s);
+    if (tiles <= 4) return gemm_nn_bf16(4, g, s);
+    return gemm_nn_bf16(8, g, s);
   }
   if (prec == SAGNN_GEMM_FP32_BF16X3) {
     // the widest column slab whose three planes fit the LDS: 128 columns up to k = 128, 64 beyond
@@ -823,9 +526,9 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
       g.n0 = n0;
       const int tiles = ((nout - n0 < slab ? nout - n0 : slab) + 31) / 32;
       int rc;
-      if (tiles <= 1) rc = launch_nn<1, SAGNN_GEMM_FP32_BF16X3>(g, s);
-      else if (tiles <= 2) rc = launch_nn<2, SAGNN_GEMM_FP32_BF16X3>(g, s);
-      else rc = launch_nn<4, SAGNN_GEMM_FP32_BF16X3>(g, s);
+      if (tiles <= 1) rc = gemm_nn_bf16x3(1, g, s);
+      else if (tiles <= 2) rc = gemm_nn_bf16x3(2, g, s);
+      else rc = gemm_nn_bf16x3(4, g, s);
       if (rc != SAGNN_OK) return rc;
     }
     return SAGNN_OK;
@@ -834,9 +537,9 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
     g.n0 = n0;
     const int tiles = ((nout - n0 < 128 ? nout - n0 : 128) + 31) / 32;
     int rc;
-    if (tiles <= 1) rc = launch_nn<1, SAGNN_GEMM_FP32>(g, s);
-    else if (tiles <= 2) rc = launch_nn<2, SAGNN_GEMM_FP32>(g, s);
-    else rc = launch_nn<4, SAGNN_GEMM_FP32>(g, s);
+    if (tiles <= 1) rc = gemm_nn_fp32(1, g, s);
+    else if (tiles <= 2) rc = gemm_nn_fp32(2, g, s);
+    else rc = gemm_nn_fp32(4, g, s);
     if (rc != SAGNN_OK) return rc;
   }
   return SAGNN_OK;

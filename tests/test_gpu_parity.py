@@ -950,6 +950,38 @@ def test_dense_gemm(m, k, n, prec, transW):
     assert torch.equal(Zm == 0, (dev(mask) <= 0) | (Z == 0))
 
 
+@pytest.mark.parametrize("prec", [sagnn.GEMM_FP32, sagnn.GEMM_BF16, sagnn.GEMM_FP32_BF16X3])
+@pytest.mark.parametrize("m,k,n", [(31, 4, 4), (32, 32, 32), (33, 36, 36), (95, 64, 100), (64, 68, 132), (97, 96, 128), (70, 100, 20),
+                                   (65, 124, 256), (64, 128, 200), (40, 132, 64), (96, 160, 256), (33, 252, 12), (64, 256, 252)])
+def test_dense_gemm_at_the_edges_of_its_groups_and_slabs(m, k, n, prec):
+    """Every number of 32-wide k groups, full and ragged; full and ragged column slabs; rows that fill their last tile
+    and rows that do not.  What lies beyond X's and W's columns is NaN, W begins anywhere and has an odd leading
+    dimension; with and without mask, both outputs."""
+    gen = torch.Generator().manual_seed(1000 * k + n)
+    X = torch.randn(m, k, generator=gen)
+    W = torch.randn(k, n, generator=gen)
+    mask = torch.randint(-1, 2, (m, n), generator=gen).float()
+    ref = X.double() @ W.double()
+    # any order of k fp32 additions: k 2^-24 of the sum of the terms' sizes; both operands rounded to bfloat16: 2 2^-9
+    tol = (2 * 2.0**-9 if prec == sagnn.GEMM_BF16 else 2 * 2.0**-23) + (k + 2) * 2.0**-24
+    bound = tol * (X.abs().double() @ W.abs().double())
+
+    def inside(t, wide, off):
+        out = torch.full((t.shape[0], wide), float("nan"), device="cuda")
+        out[:, off:off + t.shape[1]] = t.cuda()
+        return out[:, off:off + t.shape[1]]
+
+    for trans in (False, True):
+        Wt = W.t().contiguous() if trans else W
+        for Wd in (Wt.cuda(), inside(Wt, Wt.shape[1] + 5, 1), inside(Wt, Wt.shape[1] + 8, 4)):
+            for mk in (None, mask.cuda()):
+                Z, A = sagnn.dense_gemm_act(inside(X, k + 8, 0), Wd, transW=trans, prec=prec, act=sagnn.ACT_RELU, mask=mk,
+                                            want_z=True, want_act=True)
+                want = ref if mk is None else torch.where(mask > 0, ref, torch.zeros(()).double())
+                assert bool(((Z.cpu().double() - want).abs() <= bound).all())
+                assert torch.equal(A, Z.clamp(min=0))
+
+
 @pytest.mark.parametrize("k,n", [(128, 128), (256, 256), (100, 44)])
 def test_bf16x3_gemm_has_the_accuracy_of_the_fp32_gemm(k, n):
     """fp32 operands as three bfloat16 terms, six products: every operand bit takes part, so the
