@@ -219,7 +219,8 @@ typedef struct sagnn_spmm_options {
                               number of entries, 4096 with schedule 2; 1024..32768)                  */
   int32_t slab_kb;         /* KiB of B per slab (0 = 4096); -1 = as many slabs as the format allows  */
   int32_t min_waves;       /* fewer than 16 pieces per wavefront below this many wavefronts (0 = 8192) */
-  int32_t window_pct;      /* dealing window in % of the resident pieces (0 = 400); -1 = one window  */
+  int32_t window_pct;      /* dealing window in % of the resident pieces (0 = 25 where the row
+                              order carries locality, else 400); -1 = one window                    */
   int32_t snake;           /* 1: deal pieces in snake order instead of longest-first (one stream per wavefront) */
   int32_t groups;          /* lane groups: 0 decide, 1 never, 2 whenever the width has them         */
   int32_t sync_slabs;      /* slabs per interval of the sweep (0 = decide, -1 = one interval).  At

@@ -283,14 +283,17 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
 struct SweepRowTotals {
   int64_t pieces, short_rows, short_entries, multi_rows, multi_pieces;
   int32_t min_long;
+  int32_t locality;   // permille: how far the columns of neighbouring rows differ from those of all rows
   bool has_empty, bad;
 };
 bool sweep_plan_fits(const SpmmWsLayout& L);
 // classify rows, build the short-row CSR, the list of split rows and the piece records; one
 // stream synchronisation (a 128-byte copy)
 // (short_pieces: the short rows also get piece records, one whole row each, behind those of the long rows)
-int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int64_t nnz, int32_t opt_min_long, int32_t piece_max,
-                    char* ws, const SpmmWsLayout& L, hipStream_t s, SweepRowTotals* out, bool short_pieces = false);
+// (d_colidx may be null: no locality then)
+int sweep_plan_rows(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz,
+                    int32_t opt_min_long, int32_t piece_max, char* ws, const SpmmWsLayout& L, hipStream_t s,
+                    SweepRowTotals* out, bool short_pieces = false);
 // entries of the pieces of every window (only needed with several windows; synchronises)
 int sweep_plan_window_entries(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, int32_t nwin,
                               hipStream_t s, std::vector<int64_t>* entries);

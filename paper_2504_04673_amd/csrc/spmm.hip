@@ -666,7 +666,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
       // The row pass of the sweep planner with a threshold no row reaches makes exactly that list
       // (every row with entries is "short").
       SweepRowTotals t{};
-      rc = sweep_plan_rows(d_rowptr, m, nnz, 0x7FFFFFFF, 1024, base, L, s, &t);
+      rc = sweep_plan_rows(d_rowptr, nullptr, m, k, nnz, 0x7FFFFFFF, 1024, base, L, s, &t);
       if (rc != SAGNN_OK) return rc;
       if (!t.bad && t.short_entries == nnz) {   // (a malformed row pointer keeps the plain walk, which clamps everything)
         rc = flat_build_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), t.short_rows, nnz, T, base, L, d_stat, s);

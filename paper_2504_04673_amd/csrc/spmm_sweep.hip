@@ -1210,7 +1210,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // the host gets the totals.
   SweepRowTotals tot{};
   {
-    const int rc = sweep_plan_rows(d_rowptr, m, nnz, opt.min_long, piece_max, ws, L, s, &tot, opt.short_rows >= 0);
+    const int rc = sweep_plan_rows(d_rowptr, d_colidx, m, k, nnz, opt.min_long, piece_max, ws, L, s, &tot, opt.short_rows >= 0);
     if (rc != SAGNN_OK) return rc;
   }
   if (tot.bad) return SAGNN_OK;   // not a CSR row pointer for this nnz: keep the plain schedule
@@ -1260,9 +1260,13 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // the pieces are sorted by size and dealt longest-first, so its wavefronts have nearly equal
   // stream lengths (they pass the slabs in step).  A matrix of up to ~4 generations is one
   // window (measured best on randomly labelled graphs: 4.95 ms against 5.4 ms with one window
-  // per generation on the 2.45 M-vertex R-MAT graph); a larger one whose row order carries
-  // locality (a partitioned graph) keeps it, because a window only touches the part of B its
-  // rows' neighbourhoods live in (2 M-vertex community-ordered graph: 13.9 -> 11.4 ms).
+  // per generation on the 2.45 M-vertex R-MAT graph).  Where the row order carries locality (plan_locality_kernel) a
+  // window of a quarter of a generation keeps its wavefronts in the part of B that its rows' neighbourhoods share.
+  // One generation in four against four generations, 50 entries a row in 16 communities: 1 M vertices f = 16 783 ->
+  // 418 us, f = 64 1733 -> 1420, f = 256 6383 -> 5960; 300 k vertices f = 16 208 -> 94, f = 256 1834 -> 1468; 2 M of
+  // 42 f = 256 11213 -> 10942.  Random labels lose (1 M R-MAT vertices of 100 entries: f = 32 930 -> 1192 us).
+  // The line lies between what the two kinds measure, 50 to 100 permille and 700 to 900.
+  constexpr int kLocalPermille = 400;
   const int64_t fw_max = sweep_widest_launch(f, narrow_slabs ? 128 : 256);
   int64_t wg_per_cu = lds_resident_workgroups((size_t)(4ll * slots * sweep_lds_width(fw_max) * 4));
   if (wg_per_cu < 1) wg_per_cu = 1;
@@ -1276,7 +1280,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const int64_t resident_waves = (int64_t)n_cus * wg_per_cu * 4;
   int64_t window = resident_waves * slots_used;              // pieces per window
   {
-    const int pct = opt.window_pct < 0 ? 0 : (opt.window_pct > 0 ? opt.window_pct : 400);
+    const int pct = opt.window_pct < 0 ? 0 : (opt.window_pct > 0 ? opt.window_pct : (tot.locality >= kLocalPermille ? 25 : 400));
     window = pct <= 0 ? P : std::max<int64_t>(slots_used, window * pct / 100);
   }
   if (window > P) window = P;

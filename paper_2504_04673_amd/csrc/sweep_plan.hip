@@ -39,6 +39,7 @@ enum Stat : int {
   ST_SHORT_ENTRIES,
   ST_MULTI_ROWS,
   ST_MULTI_PIECES,
+  ST_LOCALITY,      // permille, see plan_locality_kernel
   ST_COUNT = 16
 };
 
@@ -91,6 +92,60 @@ __global__ void plan_rule_kernel(unsigned long long* __restrict__ stat, int64_t 
     min_long = ((long long)stat[ST_MID] * 4 >= nnz) ? kSweepMinLong : (min_long < 0 ? -min_long : 64);
   if (min_long < kSweepMinLong) min_long = kSweepMinLong;
   stat[ST_MINLONG] = (unsigned long long)min_long;
+}
+
+// Does the row order carry locality?  32 runs of 64 neighbouring rows, evenly spread, up to 32 evenly spaced entries
+// of every row, counted by column range (64 of them): the mean over the runs of half the sum of |share in the run -
+// share in all runs|.  0.05 to 0.1 where neighbouring rows share nothing but what all rows share (random labels,
+// power law or not), 0.89 for sixteen communities in order with one partner in twenty elsewhere.
+// One workgroup, all samples of a row in flight: two chains of three dependent loads.
+constexpr int kLocRuns = 32, kLocBins = 64, kLocSamples = 32;
+__global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+                                                             int64_t m, int64_t nnz, int64_t k,
+                                                             unsigned long long* __restrict__ stat) {
+  __shared__ int hist[kLocRuns][kLocBins];
+  __shared__ float diff[kLocRuns];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < kLocRuns * kLocBins; i += 1024) hist[i / kLocBins][i % kLocBins] = 0;
+  __syncthreads();
+  for (int j = wave; j < kLocRuns; j += 16) {
+    const int64_t r = m * j / kLocRuns + lane;
+    int64_t lo = 0, d = 0;
+    if (r < m) {
+      lo = rowptr[r];
+      d = rowptr[r + 1] - lo;
+      if (lo < 0 || d < 0 || lo + d > nnz) d = 0;      // (not a CSR row pointer: the row pass reports it)
+    }
+    if (d > 0) {
+      const int n = d < kLocSamples ? (int)d : kLocSamples;
+      uint32_t c[kLocSamples];
+#pragma unroll
+      for (int i = 0; i < kLocSamples; ++i) c[i] = (uint32_t)colidx[lo + (i < n ? i * d / n : 0)];
+#pragma unroll
+      for (int i = 0; i < kLocSamples; ++i)
+        if (i < n) atomicAdd(&hist[j][c[i] < (uint64_t)k ? (int)((uint64_t)c[i] * kLocBins / (uint64_t)k) : kLocBins - 1], 1);
+    }
+  }
+  __syncthreads();
+  int all = 0;
+  for (int j = 0; j < kLocRuns; ++j) all += hist[j][lane];
+  auto sum = [](auto v) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+    return v;
+  };
+  const float share = (float)all / (float)max(1, sum(all));
+  for (int j = wave; j < kLocRuns; j += 16) {
+    const int mine = hist[j][lane], n = sum(mine);
+    const float t = sum(n > 0 ? fabsf((float)mine / (float)n - share) : 0.f);
+    if (lane == 0) diff[j] = 0.5f * t;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+    for (int j = 0; j < kLocRuns; ++j) t += diff[j];
+    stat[ST_LOCALITY] = (unsigned long long)(t * (1000.f / kLocRuns));
+  }
 }
 
 struct RowQ {
@@ -528,8 +583,9 @@ bool sweep_plan_fits(const SpmmWsLayout& L) {
   return carve_plan(nullptr, L.max_pieces, L.max_waves * kSweepSlots).bytes <= have;
 }
 
-int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int64_t nnz, int32_t opt_min_long, int32_t piece_max,
-                    char* ws, const SpmmWsLayout& L, hipStream_t s, SweepRowTotals* out, bool short_pieces) {
+int sweep_plan_rows(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz,
+                    int32_t opt_min_long, int32_t piece_max, char* ws, const SpmmWsLayout& L, hipStream_t s,
+                    SweepRowTotals* out, bool short_pieces) {
   const PlanSmall sm = carve_small(ws, L);
   const PlanScratch sc = carve_plan(ws + L.code, L.max_pieces, L.max_waves * kSweepSlots);
   int32_t* d_flag = reinterpret_cast<int32_t*>(ws + L.carry);
@@ -540,6 +596,10 @@ int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int64_t nnz, int32_t opt
   hipLaunchKernelGGL(plan_rowstat_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(m, kT), 512)), dim3(kT), 0, s, d_rowptr, m,
                      nnz, sm.stat);
   SAGNN_LAUNCH_CHECK();
+  if (d_colidx && k > 0) {
+    hipLaunchKernelGGL(plan_locality_kernel, dim3(1), dim3(1024), 0, s, d_rowptr, d_colidx, m, nnz, k, sm.stat);
+    SAGNN_LAUNCH_CHECK();
+  }
   hipLaunchKernelGGL(plan_rule_kernel, dim3(1), dim3(64), 0, s, sm.stat, nnz, opt_min_long);
   SAGNN_LAUNCH_CHECK();
   int32_t* rowptr_s = reinterpret_cast<int32_t*>(ws + L.rowptr_s);
@@ -563,6 +623,7 @@ int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int64_t nnz, int32_t opt
   out->bad = h[ST_BAD] != 0;
   out->has_empty = h[ST_EMPTY] != 0;
   out->min_long = (int32_t)h[ST_MINLONG];
+  out->locality = (int32_t)h[ST_LOCALITY];
   out->pieces = (int64_t)h[ST_PIECES];
   out->short_rows = (int64_t)h[ST_SHORT_ROWS];
   out->short_entries = (int64_t)h[ST_SHORT_ENTRIES];

@@ -435,6 +435,35 @@ def test_spmm_rows_moved_to_cache_lines(f, n, sweep, monkeypatch):
             assert_close(got, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} m={m} k={k}")
 
 
+@pytest.mark.parametrize("f,labels", [(16, "order"), (100, "order"), (256, "order"), (64, "random"), (256, "random"), (64, "hubs")])
+def test_spmm_sweep_with_and_without_locality_of_the_rows(f, labels):
+    """The sweep of a matrix whose row order carries locality is dealt in many small windows, of others in few: communities
+    in row order, the same degrees with columns that lie anywhere, or at the same few places for all rows.  Each with a
+    hub row, empty rows and rows at the long-row threshold."""
+    rng = np.random.default_rng(f)
+    n, size = 150_000, 10_000
+    deg = 16 + rng.exponential(14.0, size=n).astype(np.int64)
+    deg[::1000] = 0
+    deg[7] = 20_000
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    rows = np.repeat(np.arange(n), deg)
+    if labels == "order":
+        colidx = rows // size * size + rng.integers(0, size, size=rows.size)
+    else:
+        colidx = rng.integers(0, n if labels == "random" else n // 16, size=rows.size)
+    colidx = colidx[np.lexsort((colidx, rows))].astype(np.int32)
+    val = rng.standard_normal(colidx.size).astype(np.float32)
+    B = synth.normal((n, f), f, synth.STREAM_H)
+    rp, ci, v = dev(rowptr), dev(colidx), dev(val)
+
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 1
+    got = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(B), ws=ws)
+    ref = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double(), (n, n)) @ dev(B).double()
+    zabs = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double().abs(), (n, n)) @ dev(B).double().abs()
+    assert_close(got, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} {labels}")
+
+
 @pytest.mark.parametrize("f", [64, 128, 192, 256])
 @pytest.mark.parametrize("groups", [1, 2])
 def test_spmm_sweep_short_rows_as_whole_rows(f, groups, monkeypatch):
