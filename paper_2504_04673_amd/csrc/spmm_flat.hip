@@ -244,14 +244,10 @@ struct FixDims {
 };
 
 template <bool WG>
-__global__ __launch_bounds__(kBlock) void flat_fixup_kernel(const SpmmWsHeader* __restrict__ hdr, const int4* __restrict__ chunks,
-                                                            const int2* __restrict__ list, int64_t n_list,
-                                                            const float* __restrict__ carry, const int32_t* __restrict__ rowmap,
-                                                            float* __restrict__ C, const FixDims d) {
-  __shared__ float4 part[WG ? kWaves : 1][64];
-  if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->c_nchunks != d.nchunks) return;
+__device__ __forceinline__ void fix_row(const int4* __restrict__ chunks, const int2* __restrict__ list, int64_t q, int64_t n_list,
+                                        const float* __restrict__ carry, const int32_t* __restrict__ rowmap, float* __restrict__ C,
+                                        const FixDims& d, float4 (*part)[64]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t q = WG ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kWaves + wave;
   if (q >= n_list) return;                                   // (WG: the whole workgroup)
   const int2 it = list[q];                                   // first chunk, number of chunks
   const int64_t k = it.x;
@@ -308,6 +304,20 @@ __global__ __launch_bounds__(kBlock) void flat_fixup_kernel(const SpmmWsHeader* 
       *p = o;
     }
   }
+}
+
+// one launch: the hub rows' workgroups come first, their chain is the longest (two launches before: 2.4 M entries,
+// 170 k rows, f = 256: 9.2 + 5.6 us, now 9.2)
+__global__ __launch_bounds__(kBlock) void flat_fixup_kernel(const SpmmWsHeader* __restrict__ hdr, const int4* __restrict__ chunks,
+                                                            const int2* __restrict__ list, int64_t n_list,
+                                                            const int2* __restrict__ big, int64_t n_big,
+                                                            const float* __restrict__ carry, const int32_t* __restrict__ rowmap,
+                                                            float* __restrict__ C, const FixDims d) {
+  __shared__ float4 part[kWaves][64];
+  if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->c_nchunks != d.nchunks) return;
+  const int64_t b = blockIdx.x;
+  if (b < n_big) fix_row<true>(chunks, big, b, n_big, carry, rowmap, C, d, part);
+  else fix_row<false>(chunks, list, (b - n_big) * kWaves + (threadIdx.x >> 6), n_list, carry, rowmap, C, d, part);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -441,16 +451,10 @@ int flat_fixup(const FlatArgs& a, const int2* list, int64_t list_cap, int64_t n_
   FixDims d{};
   d.nchunks = a.nchunks; d.m = a.rows; d.ldc = a.ldc; d.carry_ld = a.carry_ld; d.generation = a.generation;
   d.f_total = f_total;
-  if (n_small > 0) {
-    hipLaunchKernelGGL(flat_fixup_kernel<false>, dim3((unsigned)ceil_div(n_small, kWaves)), dim3(kBlock), 0, s, a.hdr,
-                       a.chunks, list, n_small, a.carry, a.rowmap, a.C, d);
-    SAGNN_LAUNCH_CHECK();
-  }
-  if (n_big > 0) {
-    hipLaunchKernelGGL(flat_fixup_kernel<true>, dim3((unsigned)n_big), dim3(kBlock), 0, s, a.hdr, a.chunks,
-                       list + (list_cap - n_big), n_big, a.carry, a.rowmap, a.C, d);
-    SAGNN_LAUNCH_CHECK();
-  }
+  if (n_small + n_big <= 0) return SAGNN_OK;
+  hipLaunchKernelGGL(flat_fixup_kernel, dim3((unsigned)(n_big + ceil_div(n_small, kWaves))), dim3(kBlock), 0, s, a.hdr, a.chunks,
+                     list, n_small, list + (list_cap - n_big), n_big, a.carry, a.rowmap, a.C, d);
+  SAGNN_LAUNCH_CHECK();
   return SAGNN_OK;
 }
 
