@@ -213,17 +213,11 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_count_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const int32_t* __restrict__ piece_info, int32_t n_slabs, int32_t slab_width, uint32_t kmax,
     int32_t groups, int32_t slots_per_group, int32_t n_intervals, int32_t sync_slabs,
-    int32_t* __restrict__ sync_off, int32_t* __restrict__ wave_steps, int64_t first_whole_row_wave,
-    int32_t* __restrict__ unsorted) {
+    int32_t* __restrict__ sync_off, int32_t* __restrict__ wave_steps, int32_t* __restrict__ unsorted) {
   extern __shared__ __attribute__((aligned(16))) int32_t build_lds[];
   __shared__ BuildPieces pc;
   __shared__ int32_t ivl_len[kSweepMaxIntervals];
   const int64_t w = blockIdx.x;
-  // wavefronts of whole short rows keep every row as one segment: one slab that covers all of B
-  if (w >= first_whole_row_wave) {
-    n_slabs = 1;
-    slab_width = 0x7FFFFFFF;
-  }
   const int S = n_slabs, R = groups;
   const BuildTables T = carve_tables(build_lds, S);
   build_tables<true>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, slots_per_group, pc, T, unsorted);
@@ -330,15 +324,11 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
     const float* __restrict__ val, const int32_t* __restrict__ piece_info,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ sync_off, int32_t n_slabs,
     int32_t slab_width, uint32_t kmax, int32_t groups, int32_t slots_per_group, int32_t n_intervals,
-    int32_t sync_slabs, uint32_t* __restrict__ code, float* __restrict__ vals, int64_t first_whole_row_wave) {
+    int32_t sync_slabs, uint32_t* __restrict__ code, float* __restrict__ vals) {
   extern __shared__ __attribute__((aligned(16))) int32_t build_lds[];
   __shared__ BuildPieces pc;
   const int64_t w = blockIdx.x;
   const int tid = threadIdx.x;
-  if (w >= first_whole_row_wave) {   // whole short rows: one segment per row (see sweep_count_kernel)
-    n_slabs = 1;
-    slab_width = 0x7FFFFFFF;
-  }
   const int S = n_slabs, R = groups, SL = slots_per_group;
   const BuildTables T = carve_tables(build_lds, S);
   int32_t* slab_base_ = T.slab_tot + S * kSweepSlots;          // [S][16]: first step of slab s, group g
@@ -407,6 +397,82 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
       vals[pos] = v[q];
     }
   }
+}
+
+// The wavefronts of whole short rows: every row is one segment of its group's stream, so there are no slabs and no
+// tables.  A stream holds a few hundred entries and its chain piece - row pointer - entries is its time: sixteen
+// streams are counted, four laid out by a workgroup, where a workgroup each went through the tables with a slab that
+// covers all of B.  40 M entries, 580 k short rows: counting 217 -> 160 us, layout 535 -> 510 (8 and 70 of it here).
+__global__ __launch_bounds__(kBuildThreads) void sweep_short_count_kernel(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ piece_info, int64_t w0, int64_t w1, int32_t slots_per_group,
+    int32_t* __restrict__ sync_off, int32_t* __restrict__ wave_steps) {
+  const int64_t w = w0 + ((int64_t)blockIdx.x * kBuildThreads + threadIdx.x) / kSweepSlots;   // sixteen lanes a wavefront
+  const int slot = threadIdx.x & (kSweepSlots - 1);
+  const int32_t row = w < w1 ? piece_info[2 * (w * kSweepSlots + slot)] : -1;
+  int32_t t = row >= 0 ? rowptr[row + 1] - rowptr[row] : 0;
+  for (int o = 1; o < kSweepSlots; o <<= 1) {                  // sum over a group, largest of the groups
+    const int32_t u = __shfl_xor(t, o, kSweepSlots);
+    t = o < slots_per_group ? t + u : (u > t ? u : t);
+  }
+  t = (t + 7) & ~7;
+  if (w < w1 && slot == 0) {
+    wave_steps[w] = t;
+    sync_off[w * (kSweepMaxIntervals + 1)] = 0;
+    sync_off[w * (kSweepMaxIntervals + 1) + 1] = t;
+  }
+}
+
+__global__ __launch_bounds__(kBuildThreads) void sweep_short_build_kernel(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx, const float* __restrict__ val,
+    const int32_t* __restrict__ piece_info, const int32_t* __restrict__ wave_base, int64_t w0, int64_t w1, uint32_t kmax,
+    int32_t groups, int32_t slots_per_group, uint32_t* __restrict__ code, float* __restrict__ vals) {
+  __shared__ BuildPieces pieces[kBuildThreads / 64];
+  const int lane = threadIdx.x & 63;
+  BuildPieces& pc = pieces[threadIdx.x >> 6];
+  const int64_t w = w0 + (int64_t)blockIdx.x * (kBuildThreads / 64) + (threadIdx.x >> 6);
+  const int R = groups, SL = slots_per_group;
+  if (lane < kSweepSlots) {
+    const int32_t row = w < w1 ? piece_info[2 * (w * kSweepSlots + lane)] : -1;
+    const int32_t beg = row >= 0 ? rowptr[row] : 0, deg = row >= 0 ? rowptr[row + 1] - beg : 0;
+    pc.beg[lane] = beg;
+    pc.deg[lane] = deg;
+    lay_slots(pc, lane, deg);
+  }
+  __syncthreads();
+  if (w >= w1) return;
+  const int64_t base = wave_base[w];
+  const int32_t steps = (int32_t)((wave_base[w + 1] - base) / R);
+  const int32_t total = pc.pre[kSweepSlots];
+  for (int32_t e0 = lane; e0 < total; e0 += 4 * 64) {
+    int slot[4];
+    uint32_t c[4];
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t e = e0 + q * 64 < total ? e0 + q * 64 : total - 1;
+      slot[q] = slot_at(pc, e);
+      const int32_t at = pc.beg[slot[q]] + e - pc.pre[slot[q]];
+      c[q] = (uint32_t)colidx[at];
+      v[q] = val[at];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t e = e0 + q * 64;
+      if (e >= total) break;
+      const int sl = slot[q], gi = sl / SL;
+      const int32_t rank = e - pc.pre[sl];
+      // (a segment also ends every kSweepRunMax entries, see sweep_build_kernel)
+      const bool last = rank + 1 >= pc.deg[sl] || (rank & (kSweepRunMax - 1)) == kSweepRunMax - 1;
+      const int64_t pos = base + (int64_t)(e - pc.pre[gi * SL]) * R + gi;
+      code[pos] = (c[q] > kmax ? kmax : c[q]) | ((uint32_t)sl << kSweepColBits) | (last ? 0x80000000u : 0u);
+      vals[pos] = v[q];
+    }
+  }
+  for (int gi = 0; gi < R; ++gi)                               // steps no entry lands on
+    for (int32_t t = pc.pre[(gi + 1) * SL] - pc.pre[gi * SL] + lane; t < steps; t += 64) {
+      code[base + (int64_t)t * R + gi] = 0u;
+      vals[base + (int64_t)t * R + gi] = 0.f;
+    }
 }
 
 inline size_t sweep_count_lds_bytes(int64_t S) {
@@ -1340,7 +1406,6 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
       NWT4 = NW4;
     }
   }
-  const int64_t first_whole_row_wave = whole_rows ? NW4 : INT64_MAX;
   const int64_t short_entries_csr = whole_rows ? 0 : short_entries;   // entries of the compacted short-row CSR
   // Inside a window: largest piece first, each to the stream that is shortest so far and still
   // has a free slot.  Streams come out equal to within a piece of the smallest size class, which
@@ -1382,10 +1447,15 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)build_lds));
   int64_t stream_len = 0, short_base = 0;
   for (int attempt = 0; attempt < 2; ++attempt) {
-    hipLaunchKernelGGL(sweep_count_kernel, dim3((unsigned)NWT4), dim3(kBuildThreads), count_lds, s, d_rowptr,
+    hipLaunchKernelGGL(sweep_count_kernel, dim3((unsigned)NW4), dim3(kBuildThreads), count_lds, s, d_rowptr,
                        d_colidx, d_info, (int32_t)S, (int32_t)width, kmax, (int32_t)R, (int32_t)SL, (int32_t)NI,
-                       (int32_t)sync_slabs, d_sync_off, d_wave_steps, first_whole_row_wave, d_flag);
+                       (int32_t)sync_slabs, d_sync_off, d_wave_steps, d_flag);
     SAGNN_LAUNCH_CHECK();
+    if (NWT4 > NW4) {
+      hipLaunchKernelGGL(sweep_short_count_kernel, dim3((unsigned)ceil_div(NWT4 - NW4, kBuildThreads / kSweepSlots)),
+                         dim3(kBuildThreads), 0, s, d_rowptr, d_info, NW4, NWT4, (int32_t)SL, d_sync_off, d_wave_steps);
+      SAGNN_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL(sweep_scan_kernel, dim3(1), dim3(1024), 0, s, d_wave_steps, NWT4, (int32_t)R,
                        d_wave_base, reinterpret_cast<SweepScanRecord*>(d_flag + 1));
     SAGNN_LAUNCH_CHECK();
@@ -1406,11 +1476,17 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
                        reinterpret_cast<float*>(ws + L.sched));
     SAGNN_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(sweep_build_kernel, dim3((unsigned)NWT4), dim3(kBuildThreads), build_lds, s, d_rowptr,
+  hipLaunchKernelGGL(sweep_build_kernel, dim3((unsigned)NW4), dim3(kBuildThreads), build_lds, s, d_rowptr,
                      d_colidx, d_val, d_info, d_wave_base, d_sync_off, (int32_t)S, (int32_t)width, kmax,
                      (int32_t)R, (int32_t)SL, (int32_t)NI, (int32_t)sync_slabs, reinterpret_cast<uint32_t*>(ws + L.code),
-                     reinterpret_cast<float*>(ws + L.vals), first_whole_row_wave);
+                     reinterpret_cast<float*>(ws + L.vals));
   SAGNN_LAUNCH_CHECK();
+  if (NWT4 > NW4) {
+    hipLaunchKernelGGL(sweep_short_build_kernel, dim3((unsigned)ceil_div(NWT4 - NW4, kBuildThreads / 64)), dim3(kBuildThreads), 0,
+                       s, d_rowptr, d_colidx, d_val, d_info, d_wave_base, NW4, NWT4, kmax, (int32_t)R, (int32_t)SL,
+                       reinterpret_cast<uint32_t*>(ws + L.code), reinterpret_cast<float*>(ws + L.vals));
+    SAGNN_LAUNCH_CHECK();
+  }
   // zero the gap between the long stream and the short entries (tail batches read into it)
   hipLaunchKernelGGL(sweep_zero_gap_kernel, dim3(1), dim3(256), 0, s,
                      reinterpret_cast<uint32_t*>(ws + L.code) + stream_len,
