@@ -137,6 +137,13 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_accumulate_kernel(SPMM_PTR_P
   if (!closed) flush(head ? vec(0.f) : *c_row(r));  // the row continues in the next chunk: store the partial sum
 }
 
+// header of a prepared workspace; empty: its has_empty_rows where the host does not know it yet
+__global__ void spmm_header_kernel(SpmmWsHeader h, const int32_t* __restrict__ empty, SpmmWsHeader* __restrict__ out) {
+  if (threadIdx.x != 0) return;
+  if (empty) h.has_empty_rows = *empty;
+  *out = h;
+}
+
 // rows without entries: C[r,:] = 0 when overwriting (no chunk ever visits them).  A lane looks at a row, the wavefront
 // zeroes the empty ones together (a wavefront per row for the look as well: 72 us for 1 M rows, now 26).
 __global__ __launch_bounds__(kBlock) void spmm_zero_empty_kernel(SPMM_PTR_PARAMS, const SpmmDims d,
@@ -634,6 +641,13 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
     SAGNN_HIP(hipStreamSynchronize(s));
     return SAGNN_OK;
   };
+  // (the header travels as a kernel argument: a copy from the host's stack cost a wait of its own)
+  bool header_there = false;
+  auto put_header = [&](const SpmmWsHeader& hd, const int32_t* d_empty) -> int {
+    hipLaunchKernelGGL(spmm_header_kernel, dim3(1), dim3(64), 0, s, hd, d_empty, reinterpret_cast<SpmmWsHeader*>(base + L.header));
+    SAGNN_LAUNCH_CHECK();
+    return SAGNN_OK;
+  };
 
   SweepPlanResult plan{};
   {
@@ -656,9 +670,11 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
     const int64_t T = spmm_chunk_entries(nnz, f);
     h.c_rows = m; h.c_nnz = nnz; h.c_nchunks = spmm_nchunks(nnz, T);
     int rc = flat_build_tables(d_rowptr, m, nnz, T, base, L, d_stat, s);
+    if (rc == SAGNN_OK) rc = put_header(h, d_stat);
     if (rc == SAGNN_OK) rc = read_stat();
     if (rc != SAGNN_OK) return rc;
     h.has_empty_rows = stat[0];
+    header_there = true;
     if (stat[0] && nnz > 0) {
       // Rows without entries (e.g. one column block of a row block, Alg. 2) would have to be stepped over one
       // dependent load at a time.  Walk a row list without them instead: the same compacted-CSR form the short rows
@@ -673,12 +689,16 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
         if (rc == SAGNN_OK) rc = read_stat();
         if (rc != SAGNN_OK) return rc;
         h.c_rows = t.short_rows;
+        header_there = false;
       }
     }
   }
   if (stat[1] < 0 || stat[2] < 0 || (int64_t)stat[1] + stat[2] > L.max_chunks) return SAGNN_EFORMAT;   // (overlapping rows)
-  SAGNN_HIP(hipMemcpyAsync(base + L.header, &h, sizeof(h), hipMemcpyHostToDevice, s));
-  SAGNN_HIP(hipStreamSynchronize(s));
+  if (!header_there) {
+    const int rc = put_header(h, nullptr);
+    if (rc != SAGNN_OK) return rc;
+    SAGNN_HIP(hipStreamSynchronize(s));
+  }
   SpmmHostDesc desc{};
   desc.generation = h.generation; desc.m = m; desc.nnz = nnz; desc.f = f; desc.mode = h.mode;
   desc.c_rows = h.c_rows; desc.c_nnz = h.c_nnz; desc.c_nchunks = h.c_nchunks;
