@@ -38,7 +38,7 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // --- SpMM workspace geometry (host and device agree through these) -----------------------
 // Chunks of the nonzero-splitting schedule: about T entries each, T a multiple of 16.  Long enough that what a
 // chunk costs besides its entries does not count, short enough that small matrices fill the chip: 8192 wavefronts
-// (32 per CU) of 64 / lanes-per-entry chunks.  Serial sums stay below 1.5 T = 192 terms.
+// (32 per CU) of 64 / lanes-per-entry chunks.  Serial sums stay below T + 32 <= 160 terms.
 constexpr int kSpmmChunkMax = 128;
 inline int64_t spmm_chunk_entries(int64_t nnz, int32_t f) {
   const int64_t groups = f <= 16 ? 16 : (f <= 32 ? 8 : (f <= 64 ? 4 : (f <= 128 ? 2 : 1)));
