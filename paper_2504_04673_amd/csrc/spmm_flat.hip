@@ -2,11 +2,10 @@
 // chunk tables (built once per matrix), product kernel, carry fix-up.
 //
 // The entries are cut into chunks of about T consecutive entries, T = 16 .. 128 chosen so that the chip is full
-// (spmm_chunk_entries).  A chunk ends at the row end nearest behind the multiple of T where there is one within 16 entries (32 where T is
-// 16), so that
-// only rows that are long against T are shared by several chunks; the shares of such a row go to carry slots that a
-// second kernel adds in chunk order (reproducible, no floating-point atomics), and a matrix without such rows needs
-// no second kernel.
+// (spmm_chunk_entries).  A chunk ends at the row end nearest behind the multiple of T where there is one within 16
+// entries (32 where T is 16), so that only rows that are long against T are shared by several chunks; the shares of such
+// a row go to carry slots that a second kernel adds in chunk order (reproducible, no floating-point atomics), and a
+// matrix without such rows needs no second kernel.
 //
 // Product kernel.  A group of LPE lanes (4, 8, .. 64: as many as hold a row of up to 4 LPE floats, 16 bytes a lane)
 // walks one chunk, so one load instruction serves 64 / LPE entries.  Column ids and values of 16 or 32 entries arrive
