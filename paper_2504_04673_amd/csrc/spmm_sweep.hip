@@ -42,6 +42,8 @@ namespace {
 
 constexpr int kBuildThreads = 256;
 constexpr uint32_t kColMask = (1u << kSweepColBits) - 1u;
+constexpr int kSweepOwnSteps = 2;   // (behind the two boundaries of a single interval)
+static_assert(kSweepOwnSteps + kSweepSlots <= kSweepMaxIntervals + 1, "lengths of sixteen streams in sync_off");
 
 // ---------------------------------------------------------------------------------------
 // preparation kernels
@@ -238,7 +240,8 @@ __device__ __forceinline__ BuildTables carve_tables(int32_t* lds, int S) {
 // Pass 1: length of every interval of a wavefront's stream.  An interval's R group streams are
 // padded to the longest of them and to a whole batch (8 steps), so that every wavefront reaches
 // an interval boundary at a batch boundary.  sync_off[w][i] = first step of interval i,
-// wave_steps[w] = total steps.
+// wave_steps[w] = total steps.  Sixteen streams have one interval: sync_off[w][kSweepOwnSteps + g] = steps of
+// stream g without its padding.
 __global__ __launch_bounds__(kBuildThreads) void sweep_count_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const int32_t* __restrict__ piece_info, int32_t n_slabs, int32_t slab_width, uint32_t kmax,
@@ -253,6 +256,7 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_count_kernel(
   build_tables<true>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, slots_per_group, pc, T, unsorted);
   const int per = sync_slabs > 0 ? sync_slabs : S;
   const int lane = threadIdx.x & 63;
+  int32_t* so = sync_off + w * (kSweepMaxIntervals + 1);
   for (int i = threadIdx.x >> 6; i < n_intervals; i += kBuildThreads / 64) {   // a wavefront per interval
     const int s0 = i * per, s1 = (i + 1) * per < S ? (i + 1) * per : S;
     int32_t longest = 0;
@@ -261,6 +265,7 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_count_kernel(
       for (int s = s0 + lane; s < s1; s += 64) t += T.TOT(s, gi);
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+      if (R == kSweepSlots && lane == 0) so[kSweepOwnSteps + gi] = t;
       longest = t > longest ? t : longest;
     }
     if (lane == 0) ivl_len[i] = (longest + 7) & ~7;
@@ -268,7 +273,6 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_count_kernel(
   __syncthreads();
   if (threadIdx.x == 0) {
     int32_t run = 0;
-    int32_t* so = sync_off + w * (kSweepMaxIntervals + 1);
     for (int i = 0; i < n_intervals; ++i) {
       so[i] = run;
       run += ivl_len[i];
@@ -1120,12 +1124,16 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
 // one coalesced load per array and a step's group takes its word with a lane permute.  With 16
 // groups each group owns a single piece and its register accumulator is the piece's accumulator
 // (no LDS at all); with 8 groups two pieces per group share it through LDS as in the wide kernels.
+// Padding multiplies row 0 of B by 0, which is no 0 where that row holds an infinity or NaN.  In the LDS forms it
+// lands behind the last flush; here it would land in the result, so the steps behind the end of the wavefront's shortest
+// stream are masked per lane (no check in the steps before: 1 M vertices, 50 M entries, training at f = 16
+// 2281 us without and 2283 with the masks).
 template <int R, bool BUF, bool ODD>
 __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
     const SpmmWsHeader* __restrict__ hdr, const float* __restrict__ B, float* __restrict__ C,
-    float* __restrict__ partial, const SweepDims d) {
+    float* __restrict__ partial, const int32_t* __restrict__ sync_off, const SweepDims d) {
   typedef float vec __attribute__((ext_vector_type(4)));
   constexpr int LG = 64 / R;             // lanes per group = lanes per row
   const int kRow = ODD ? d.fw : LG * 4;  // floats per row
@@ -1153,6 +1161,18 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
   const uint32_t* __restrict__ cw = code + base;
   const float* __restrict__ vw = vals + base;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
+
+  int32_t own = 0, all_own = 0;          // SL == 1: steps of this group's stream, of the shortest stream
+  if constexpr (SL == 1) {
+    own = sync_off[w * (kSweepMaxIntervals + 1) + kSweepOwnSteps + gid];
+    all_own = own > 0 ? own : steps;     // (a group without a piece: nothing of it is stored)
+#pragma unroll
+    for (int o = LG; o < 64; o <<= 1) {
+      const int32_t t = __shfl_xor(all_own, o, 64);
+      all_own = t < all_own ? t : all_own;
+    }
+    all_own = __builtin_amdgcn_readfirstlane(all_own);
+  }
 
   vec acc = 0.f, tot = 0.f;
   uint32_t cb[NB];
@@ -1188,18 +1208,25 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(h[u]));
+    if constexpr (SL > 1) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      acc += mv[u] * h[u];
-      if constexpr (SL > 1) {
+      for (int u = 0; u < 8; ++u) {
+        acc += mv[u] * h[u];
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
           vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
           *p += acc;
           acc = 0.f;
         }
       }
-    }
-    if constexpr (SL == 1) {
+    } else {
+      if (e + 8 <= all_own) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += mv[u] * h[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (e + u < own) acc += mv[u] * h[u];
+      }
       // no slots to flush into: fold the running sum every 64 entries instead (two-level sum)
       if ((e & 63) == 56) {
         tot += acc;
@@ -1619,6 +1646,18 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     SAGNN_LAUNCH_CHECK();
     return SAGNN_OK;
   };
+  auto go_perm = [&](auto kern) -> int {   // (at most 32 KB of LDS)
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s,
+                       reinterpret_cast<const uint32_t*>(ws + L.code),
+                       reinterpret_cast<const float*>(ws + L.vals),
+                       reinterpret_cast<const int32_t*>(ws + L.wave_base),
+                       reinterpret_cast<const int32_t*>(ws + L.piece_target),
+                       reinterpret_cast<const SpmmWsHeader*>(ws + L.header), B + col0, C + col0,
+                       reinterpret_cast<float*>(ws + L.partial),
+                       reinterpret_cast<const int32_t*>(ws + L.sync_off), sd);
+    SAGNN_LAUNCH_CHECK();
+    return SAGNN_OK;
+  };
   // lane-group kernels: walk the stream interval by interval, with a barrier of the XCD's
   // resident workgroups in between when the schedule was laid out for it
   auto go_group = [&](auto kern) -> int {
@@ -1659,13 +1698,13 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   if (fw <= 0 || (fw & 3)) return SAGNN_EINVAL;
   if (d.groups == 16) {  // four lanes per row
     if (fw > 16) return SAGNN_EINVAL;
-    if (fw == 16) return buf ? go(spmm_sweep_perm_kernel<16, true, false>) : go(spmm_sweep_perm_kernel<16, false, false>);
-    return buf ? go(spmm_sweep_perm_kernel<16, true, true>) : go(spmm_sweep_perm_kernel<16, false, true>);
+    if (fw == 16) return buf ? go_perm(spmm_sweep_perm_kernel<16, true, false>) : go_perm(spmm_sweep_perm_kernel<16, false, false>);
+    return buf ? go_perm(spmm_sweep_perm_kernel<16, true, true>) : go_perm(spmm_sweep_perm_kernel<16, false, true>);
   }
   if (d.groups == 8) {   // eight lanes per row
     if (fw > 32) return SAGNN_EINVAL;
-    if (fw == 32) return buf ? go(spmm_sweep_perm_kernel<8, true, false>) : go(spmm_sweep_perm_kernel<8, false, false>);
-    return buf ? go(spmm_sweep_perm_kernel<8, true, true>) : go(spmm_sweep_perm_kernel<8, false, true>);
+    if (fw == 32) return buf ? go_perm(spmm_sweep_perm_kernel<8, true, false>) : go_perm(spmm_sweep_perm_kernel<8, false, false>);
+    return buf ? go_perm(spmm_sweep_perm_kernel<8, true, true>) : go_perm(spmm_sweep_perm_kernel<8, false, true>);
   }
   if (d.groups == 2) {   // half a wavefront per row
     if (fw == 128) return buf ? go_group(group_kernel_of<4, 2, true>(fuse)) : go_group(group_kernel_of<4, 2, false>(fuse));

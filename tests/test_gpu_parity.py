@@ -408,6 +408,36 @@ def test_spmm_sweep_widths_between_the_kernels(f, groups, force_sweep, monkeypat
         assert_close(got, ref, zabs, RTOL_SPMM, f"accumulate f={f} w={w}")
 
 
+@pytest.mark.parametrize("f,sync", [(4, 0), (8, 0), (12, 0), (16, 0), (20, 0), (32, 0), (64, 0), (100, 0), (128, 0), (256, 0)])
+def test_spmm_sweep_keeps_a_non_finite_row_of_b_to_the_rows_that_use_it(f, sync, monkeypatch):
+    """The steps that pad a stream multiply row 0 of B by 0: where that row holds NaN and infinities, a row of C has them
+    if and only if one of its entries lies in column 0."""
+    for name, value in (("", 1), ("_MINDEG", 16), ("_PIECE", 1024), ("_SLAB_MB", 0), ("_GROUPS", 2), ("_SYNC", sync)):
+        monkeypatch.setenv("SAGNN_SWEEP" + name, str(value))
+    rng = np.random.default_rng(f)
+    m, n = 3001, 9000
+    rowptr, colidx, val = random_csr(m, n, 25, rng, empty_frac=0.1, hubs=[(3, 5000), (40, 20), (1500, 1024), (3000, 17)])
+    colidx = np.maximum(colidx, 1)
+    users = np.array([3, 40, 1500])
+    colidx[rowptr[users]] = 0
+    B = synth.normal((n, f), f, synth.STREAM_H)
+    B[0, 0::2], B[0, 1::2] = np.nan, np.inf
+    finite = B.copy()
+    finite[0] = 0.0
+    rp, ci, v = dev(rowptr), dev(colidx), dev(val)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 1 and (ws.info()["intervals"] > 1) == (sync > 0)
+    others = np.setdiff1d(np.arange(m), users)
+    infinity = np.broadcast_to(np.copysign(np.inf, val[rowptr[users]])[:, None], (users.size, f // 2))
+    for C0 in (None, synth.normal((m, f), f + 1, synth.STREAM_G)):
+        ref, zabs = oracle.spmm(rowptr, colidx, val, finite, C=C0, want_abs=True)
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(B), C=None if C0 is None else dev(C0), accumulate=C0 is not None,
+                                        ws=ws).cpu().numpy()
+        assert np.isfinite(got[others]).all(), f"{(~np.isfinite(got[others])).any(axis=1).sum()} rows that do not use row 0"
+        assert_close(got[others], ref[others], zabs[others], RTOL_SPMM, f"f={f}")
+        assert np.isnan(got[users, 0::2]).all() and np.array_equal(got[users, 1::2], infinity)
+
+
 @pytest.mark.parametrize("f,n", [(12, 200_000), (24, 90_000), (28, 90_001), (60, 40_000), (124, 20_000)])
 @pytest.mark.parametrize("sweep", [False, True])
 def test_spmm_rows_moved_to_cache_lines(f, n, sweep, monkeypatch):
