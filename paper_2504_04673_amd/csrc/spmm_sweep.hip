@@ -1026,9 +1026,9 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   const bool paced = d.pace_ticks > 0.f && n_iv > 1;
   const uint64_t t_start = paced ? wall_clock64() : 0ull;
 
-  vec acc = 0.f;
   int32_t e = 0;
   for (int iv = 0; iv < n_iv; ++iv) {
+    vec acc = 0.f;   // (what the padding of the interval before left in it is not summed: see spmm_sweep_perm_kernel)
     const int32_t e_end = iv + 1 < n_iv ? so[iv + 1] : steps;
     for (; e < e_end; e += U) {
       uint32_t c[U][R];

@@ -408,10 +408,11 @@ def test_spmm_sweep_widths_between_the_kernels(f, groups, force_sweep, monkeypat
         assert_close(got, ref, zabs, RTOL_SPMM, f"accumulate f={f} w={w}")
 
 
-@pytest.mark.parametrize("f,sync", [(4, 0), (8, 0), (12, 0), (16, 0), (20, 0), (32, 0), (64, 0), (100, 0), (128, 0), (256, 0)])
+@pytest.mark.parametrize("f,sync", [(4, 0), (8, 0), (12, 0), (16, 0), (20, 0), (32, 0), (64, 0), (100, 0), (128, 0), (256, 0),
+                                    (48, 96), (64, 96), (128, 96)])
 def test_spmm_sweep_keeps_a_non_finite_row_of_b_to_the_rows_that_use_it(f, sync, monkeypatch):
-    """The steps that pad a stream multiply row 0 of B by 0: where that row holds NaN and infinities, a row of C has them
-    if and only if one of its entries lies in column 0."""
+    """The steps that pad a stream, or an interval of `sync` slabs, multiply row 0 of B by 0: where that row holds NaN and
+    infinities, a row of C has them if and only if one of its entries lies in column 0."""
     for name, value in (("", 1), ("_MINDEG", 16), ("_PIECE", 1024), ("_SLAB_MB", 0), ("_GROUPS", 2), ("_SYNC", sync)):
         monkeypatch.setenv("SAGNN_SWEEP" + name, str(value))
     rng = np.random.default_rng(f)
