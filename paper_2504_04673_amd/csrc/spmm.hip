@@ -104,7 +104,9 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_accumulate_kernel(SPMM_PTR_P
   for (int32_t e = e0; e < e1; e += U) {
     const uint64_t two = (uint64_t)flags[e >> 5] | ((uint64_t)flags[(e >> 5) + 1] << 32);
     uint32_t fbits = (uint32_t)(two >> (e & 31)) & ((1u << U) - 1u);
-    if (e + U > e1) fbits &= (1u << (e1 - e)) - 1u;
+    // (the chunk's last entry hands over the sum in any case: a row that continues in the next chunk before the steps
+    // that fill up the batch, which multiply the last column's row by 0 whatever it holds)
+    if (e + U >= e1) fbits = (fbits & ((1u << (e1 - e)) - 1u)) | (1u << (e1 - e - 1));
     vec h[U];
     float vc[U];
 #pragma unroll
@@ -132,9 +134,6 @@ __global__ __launch_bounds__(kBlock) void spmm_wide_accumulate_kernel(SPMM_PTR_P
       if ((fbits >> u) & 1u) flush(cold[u]);
     }
   }
-  const int32_t last = e1 - 1;
-  const bool closed = (flags[last >> 5] >> (last & 31)) & 1u;
-  if (!closed) flush(head ? vec(0.f) : *c_row(r));  // the row continues in the next chunk: store the partial sum
 }
 
 // header of a prepared workspace; empty: its has_empty_rows where the host does not know it yet

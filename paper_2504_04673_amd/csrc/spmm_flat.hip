@@ -157,11 +157,13 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
 
   for (int base = 0; base < longest; base += SPAN) {
     if (base + SPAN < longest) fetch(base + SPAN, cn, vn, f2n);
-    // row ends among the span's entries of this group
+    // row ends among the span's entries of this group.  The chunk's last entry counts as one: a row that continues in
+    // the next chunk hands over its share there, before the steps that only longer groups need (they multiply the last
+    // column's row by 0, which is no 0 where that row holds an infinity or NaN)
     const int32_t fb = e0 + base < elast ? e0 + base : elast;
     uint32_t fl = (uint32_t)(f2 >> (fb & 31));
     const int left = len - base;
-    fl = left >= 32 ? fl : (left > 0 ? fl & ((1u << left) - 1u) : 0u);
+    if (left <= 32) fl = left > 0 ? (fl & ((2u << (left - 1)) - 1u)) | (1u << (left - 1)) : 0u;
     uint32_t off[NC];
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -224,11 +226,6 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
       v[i] = vn[i];
     }
     f2 = f2n;
-  }
-  // a row that continues in the next chunk: its share so far
-  if (len > 0) {
-    const bool closed = (flags[elast >> 5] >> (elast & 31)) & 1u;
-    if (!closed) emit();
   }
 }
 

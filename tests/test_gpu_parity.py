@@ -364,6 +364,33 @@ def test_spmm_chunks_at_their_edges(f, target, monkeypatch):
     assert_close(run_spmm(rowptr, colidx, val, B, True, C0=C0), ref2, zabs2, RTOL_SPMM, f"chunks accumulate f={f}")
 
 
+@pytest.mark.parametrize("f,target", [(4, 3_000), (16, 8_500_000), (32, 400_000), (64, 600_000), (100, 300_000), (128, 300_000),
+                                      (256, 270_000), (320, 60_000)])
+def test_spmm_infinities_in_rows_that_chunks_cut(f, target, monkeypatch):
+    """Nonzero splitting: entries and operand are positive, some rows of B infinite, so every row of C that uses one of them
+    is +inf and no other is.  A chunk that is done before its neighbours goes on with weight 0 on its last column; a row
+    that the chunk's end cuts is open until then."""
+    monkeypatch.setenv("SAGNN_SWEEP", "0")
+    rng = np.random.default_rng(f)
+    kinds = np.array([0, 1, 7, 9, 17, 33, 40, 50, 70, 100, 129, 300])
+    deg = kinds[rng.integers(0, kinds.size, size=max(8, target // 63))]
+    deg[deg.size // 2] = min(20_000, target)
+    n = 5000
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    colidx = rng.integers(0, n, size=rowptr[-1]).astype(np.int32)
+    val = rng.uniform(0.5, 1.5, size=colidx.size).astype(np.float32)
+    B = np.abs(synth.normal((n, f), f, synth.STREAM_H)) + np.float32(0.1)
+    infinite = rng.random(n) < 0.02
+    rows = np.repeat(np.arange(deg.size), deg)
+    hit = np.bincount(rows[infinite[colidx]], minlength=deg.size) > 0
+    ref, zabs = oracle.spmm(rowptr, colidx, val, B, want_abs=True)
+    B[infinite] = np.inf
+    for C0 in (None, np.ones((deg.size, f), np.float32)):
+        got = run_spmm(rowptr, colidx, val, B, True, C0=C0, expect_mode=0).cpu().numpy()
+        assert np.isposinf(got[hit]).all(), f"{np.isnan(got[hit]).any(axis=1).sum()} of {hit.sum()} rows hold NaN"
+        assert_close(got[~hit], ref[~hit] + (0 if C0 is None else 1), zabs[~hit] + 1, RTOL_SPMM, f"f={f}")
+
+
 @pytest.mark.parametrize("f", [16, 32, 64, 128, 192, 256, 320])
 def test_spmm_slab_sweep_schedule(f, force_sweep):
     rng = np.random.default_rng(100 + f)
