@@ -269,6 +269,10 @@ typedef struct sagnn_spmm_options {
   int32_t tile_reuse_x10;  /* a tile is kept when it holds at least this many entries per column, in
                               tenths (0 = 25, i.e. every staged row is used 2.5 times on average)     */
 } sagnn_spmm_options;
+/* A buffer of the size reported for a matrix is accepted for every matrix with no more rows, no more
+ * entries and no wider operand.  The size includes room for a copy of B whose rows begin on cache lines
+ * where such a copy pays (f <= 128 and no multiple of 32, many entries per row of B); where a buffer that
+ * was sized for another matrix has no room for it, the product runs without the copy. */
 int spmm_csr_workspace_bytes(int64_t m, int64_t nnz, int32_t f, size_t* bytes);
 /* Workspace size for a preparation with the given options: spmm_csr_workspace_bytes() plus, with
  * dense_tiles = 1, the tile region.  h_opt may be NULL.

@@ -40,9 +40,9 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // chunk costs besides its entries does not count, short enough that small matrices fill the chip: 8192 wavefronts
 // (32 per CU) of 64 / lanes-per-entry chunks.  Serial sums stay below T + 32 <= 160 terms.
 constexpr int kSpmmChunkMax = 128;
+inline int64_t spmm_chunk_groups(int32_t f) { return f <= 16 ? 16 : (f <= 32 ? 8 : (f <= 64 ? 4 : (f <= 128 ? 2 : 1))); }
 inline int64_t spmm_chunk_entries(int64_t nnz, int32_t f) {
-  const int64_t groups = f <= 16 ? 16 : (f <= 32 ? 8 : (f <= 64 ? 4 : (f <= 128 ? 2 : 1)));
-  const int64_t t = (nnz / (8192 * groups) + 15) / 16 * 16;
+  const int64_t t = (nnz / (8192 * spmm_chunk_groups(f)) + 15) / 16 * 16;
   return t < 16 ? 16 : (t > kSpmmChunkMax ? kSpmmChunkMax : t);
 }
 constexpr uint32_t kSpmmMagic = 0x53A66E02u;
@@ -64,13 +64,14 @@ constexpr int kSweepMaxWindows = 2048;      // dealing windows of a matrix (11 b
 // Longest piece of a swept row where the caller does not say: about what a stream holds on average when 8192
 // wavefronts share the entries (a longer piece makes one stream the whole product waits for: 2.4 M entries at f = 128
 // took 433 us with pieces of 4096 and 167 with 1024), a power of two up to 4096.
+inline int64_t sweep_piece_streams(int32_t f) { return 8192 * (f > 128 ? 1 : (f > 64 ? 2 : 4)); }
 inline int32_t sweep_piece_default(int64_t nnz, int32_t f) {
-  const int64_t streams = 8192 * (f > 128 ? 1 : (f > 64 ? 2 : 4));
+  const int64_t streams = sweep_piece_streams(f);
   int32_t p = 256;
   while (p < 4096 && 2 * (int64_t)p * streams <= nnz) p *= 2;
   return p;
 }
-inline int32_t sweep_piece_floor(int64_t nnz, int32_t f) {   // what the workspace is sized for
+inline int32_t sweep_piece_floor(int64_t nnz, int32_t f) {   // no piece is cut shorter
   const int32_t p = sweep_piece_default(nnz, f);
   return p < 1024 ? p : 1024;
 }
@@ -140,35 +141,58 @@ static_assert(sizeof(SpmmWsHeader) <= 256, "header must fit its slot");
 struct SpmmWsLayout {
   size_t header, chunks, fix_list, flags, rowptr_s, rowmap_s, code, vals, piece_info, piece_target,
       wave_base, wave_steps, sync_off, barrier, sched, multi_row, multi_first, partial, carry, plan, wpack, padded, total;
+  size_t need;           // enough for every call; with `total` there is room for the padded copy
   int64_t max_chunks, max_pieces, max_waves, max_multi_rows, max_multi_pieces, stream_cap;
   int64_t padded_rows;   // rows of B the padded copy has room for
 };
 
 inline int64_t spmm_nchunks(int64_t nnz, int64_t T) { return ceil_div(nnz, T); }
 
+// A workspace that is enough for a matrix is enough for every smaller one: fewer rows, entries or columns of B.  Chunks
+// and pieces get longer with the number of entries and with the width, so what they need is the most that any smaller
+// count, and any narrower operand, comes to.
+// Chunks of any count up to nnz at width f (the short rows of a sweep are such a part of the entries)
+inline int64_t spmm_most_chunks(int64_t nnz, int32_t f) {
+  const int64_t T = spmm_chunk_entries(nnz, f);
+  int64_t most = spmm_nchunks(nnz, T) + 1;
+  for (int64_t t = 16; t < T; t += 16) {
+    const int64_t upto = (t + 1) * 8192 * spmm_chunk_groups(f);   // the most entries that get chunks of t
+    const int64_t chunks = (upto < nnz ? upto : nnz) / t + 2;
+    most = chunks > most ? chunks : most;
+  }
+  return most;
+}
+// Times that rows of any count up to nnz are cut at width f (a piece has at least sweep_piece_floor entries)
+inline int64_t sweep_most_cuts(int64_t nnz, int32_t f) {
+  int64_t most = nnz / sweep_piece_floor(nnz, f);
+  for (int64_t p = 256; p < sweep_piece_floor(nnz, f); p *= 2) {
+    const int64_t cuts = (2 * p * sweep_piece_streams(f) - 1) / p;   // at the most entries that get pieces of p
+    most = cuts > most ? cuts : most;
+  }
+  return most;
+}
+
 inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
   SpmmWsLayout L{};
-  {
-    // T grows with the count, so a part of the entries (the short rows of a sweep) may be cut finer than all of them
-    const int64_t T = spmm_chunk_entries(nnz, f);
-    L.max_chunks = spmm_nchunks(nnz, T) + 1;
-    for (int64_t t = 16; t < T; t += 16) {   // the most entries that get chunks of t
-      const int64_t groups = f <= 16 ? 16 : (f <= 32 ? 8 : (f <= 64 ? 4 : (f <= 128 ? 2 : 1)));
-      const int64_t most = (t + 1) * 8192 * groups;
-      const int64_t chunks = (most < nnz ? most : nnz) / t + 2;
-      if (chunks > L.max_chunks) L.max_chunks = chunks;
-    }
+  int64_t cuts = 0, carry_floats = 0, partial_floats = 0;
+  for (int32_t top = 16;; top *= 2) {   // widths up to 16, 32, 64, 128 and beyond differ
+    const int32_t w = top > 128 || f < top ? f : top;
+    const int64_t chunks = spmm_most_chunks(nnz, w), c = sweep_most_cuts(nnz, w);
+    L.max_chunks = chunks > L.max_chunks ? chunks : L.max_chunks;
+    cuts = c > cuts ? c : cuts;
+    carry_floats = chunks * w > carry_floats ? chunks * w : carry_floats;
+    partial_floats = (2 * c + 2) * w > partial_floats ? (2 * c + 2) * w : partial_floats;
+    if (w == f) break;
   }
-  // every long row has >= kSweepMinLong entries; splitting adds at most nnz/floor pieces; every
+  // every long row has >= kSweepMinLong entries; splitting adds at most `cuts` pieces; every
   // short row may become a piece of its own (whole-row wavefronts behind those of the long rows)
-  const int64_t floor = sweep_piece_floor(nnz, f);
-  const int64_t long_pieces = nnz / kSweepMinLong + nnz / floor + kSweepSlots;
+  const int64_t long_pieces = nnz / kSweepMinLong + cuts + kSweepSlots;
   const int64_t long_waves = ceil_div(long_pieces, kSweepSlots) + 1;
   const int64_t short_waves = ceil_div(m, kSweepSlots) + 4;
   L.max_pieces = long_pieces + m;
   L.max_waves = long_waves + short_waves;
-  L.max_multi_rows = nnz / floor + 1;
-  L.max_multi_pieces = 2 * (nnz / floor) + 2;
+  L.max_multi_rows = cuts + 1;
+  L.max_multi_pieces = partial_floats / f;   // (at least twice the cuts at width f, and 2)
   // sweep streams + gap + short CSR entries + padding.  A wavefront's stream is padded to the
   // batch of 8 steps at every interval boundary; with lane groups (up to 4 zipped streams per
   // wavefront) also to the longest of its group streams inside every interval.  If a pattern
@@ -194,14 +218,15 @@ inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
   L.sched = take(sizeof(float) * (size_t)(kSweepMaxIntervals + 2));
   L.multi_row = take(sizeof(int32_t) * (size_t)L.max_multi_rows);
   L.multi_first = take(sizeof(int32_t) * (size_t)(L.max_multi_rows + 1));
-  L.partial = take(sizeof(float) * (size_t)L.max_multi_pieces * (size_t)f);
-  L.carry = take(sizeof(float) * (size_t)L.max_chunks * (size_t)f);
+  L.partial = take(sizeof(float) * (size_t)partial_floats);
+  L.carry = take(sizeof(float) * (size_t)carry_floats);
   // planner: totals, per-window arrays, tile sums of the five row scans (2048 rows per tile)
   L.plan = take(256 + (size_t)kSweepMaxWindows * 8 + 3 * 4 * (size_t)(kSweepMaxWindows + 64) +
                 5 * sizeof(int32_t) * (size_t)(ceil_div(m, 2048) + 2));
   // W of a fused layer call packed for the bfloat16 matrix instructions (at most 256 x 256, up to
   // three terms per element)
   L.wpack = take(3 * 256 * 256 * 2);
+  L.need = off;
   // the layout does not know how many rows B has: as many as A where a copy pays then
   L.padded_rows = spmm_pad_pays(m, nnz, f, f) ? m : 0;
   L.padded = take(sizeof(float) * (size_t)L.padded_rows * (size_t)spmm_padded_width(f));

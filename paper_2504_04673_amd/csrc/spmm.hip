@@ -302,7 +302,7 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
     // dense tiles: the rest CSR (stored behind the plain workspace) through the schedule prepared
     // for it, then C += tiles * B out of LDS
     if (desc.m != m || desc.full_nnz != nnz || desc.f != f || k < desc.k) return SAGNN_EINVAL;
-    const size_t plain = round_up(spmm_ws_bytes(m, desc.full_nnz, desc.f), 256);
+    const size_t plain = spmm_ws_layout(m, desc.full_nnz, desc.f).need;
     const TileWsLayout TL = tile_ws_layout(m, desc.k, desc.full_nnz, desc.f);
     if (ws_bytes < plain + TL.total) return SAGNN_ECAPACITY;
     char* tb = reinterpret_cast<char*>(ws) + plain;
@@ -321,7 +321,7 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   // operand with fewer rows would be read out of range
   if (nnz > 0 && k < desc.k) return SAGNN_EINVAL;
   const SpmmWsLayout L = spmm_ws_layout(m, nnz, desc.f);
-  if (ws_bytes < L.total) return SAGNN_ECAPACITY;
+  if (ws_bytes < L.need) return SAGNN_ECAPACITY;
   char* base = reinterpret_cast<char*>(ws);
   p.hdr = reinterpret_cast<const SpmmWsHeader*>(base + L.header);
   p.chunks = reinterpret_cast<const int4*>(base + L.chunks);
@@ -330,7 +330,7 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   d.generation = desc.generation;
   d.nchunks = desc.c_nchunks;
 
-  if (k <= L.padded_rows && f <= desc.f && spmm_padded_width(f) <= spmm_padded_width(desc.f) && spmm_pad_pays(k, nnz, f, ldb)) {
+  if (k <= L.padded_rows && ws_bytes >= L.total && f <= desc.f && spmm_padded_width(f) <= spmm_padded_width(desc.f) && spmm_pad_pays(k, nnz, f, ldb)) {
     float* padded = reinterpret_cast<float*>(base + L.padded);
     const int32_t fp = spmm_padded_width(f);
     const int64_t quads = k * (f / 4);
@@ -497,7 +497,7 @@ int launch_fused_sweep_layer(const int32_t* rowptr, const int32_t* colidx, const
   if (nnz > 0 && k < desc.k) return SAGNN_EINVAL;
   if (!rowptr || !H || !W || (!Z && !Hout) || ldh < f_in || (ldh & 3) || !aligned16(H)) return SAGNN_EINVAL;
   const SpmmWsLayout L = spmm_ws_layout(m, nnz, desc.f);
-  if (ws_bytes < L.total) return SAGNN_ECAPACITY;
+  if (ws_bytes < L.need) return SAGNN_ECAPACITY;
   char* base = reinterpret_cast<char*>(ws);
   const SpmmWsHeader* hdr = reinterpret_cast<const SpmmWsHeader*>(base + L.header);
   const uint32_t kmax = k > 0 ? (uint32_t)(k - 1) : 0u;
@@ -563,7 +563,7 @@ SAGNN_EXPORT int spmm_csr_workspace_bytes_opt(int64_t m, int64_t k, int64_t nnz,
     return SAGNN_EINVAL;
   size_t b = spmm_ws_bytes(m, nnz, f);
   TileGeom g{};
-  if (h_opt && h_opt->dense_tiles == 1 && tile_geom(f, &g)) b = round_up(b, 256) + tile_ws_layout(m, k, nnz, f).total;
+  if (h_opt && h_opt->dense_tiles == 1 && tile_geom(f, &g)) b += tile_ws_layout(m, k, nnz, f).total;
   *bytes = b;
   return SAGNN_OK;
 }
@@ -598,7 +598,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   if (!d_rowptr || !d_ws || (reinterpret_cast<uintptr_t>(d_ws) & 255u)) return SAGNN_EINVAL;
   if (nnz > 0 && (!d_colidx || !d_val)) return SAGNN_EINVAL;
   const SpmmWsLayout L = spmm_ws_layout(m, nnz, f);
-  if (ws_bytes < L.total) return SAGNN_ECAPACITY;
+  if (ws_bytes < L.need) return SAGNN_ECAPACITY;
   hipStream_t s = (hipStream_t)stream;
   char* base = reinterpret_cast<char*>(d_ws);
   if (opt.dense_tiles < -1 || opt.dense_tiles > 1 || opt.tile_reuse_x10 < 0) return SAGNN_EINVAL;
@@ -606,7 +606,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   if (opt.dense_tiles == 1 && tile_geom(f, &tg) && m > 0 && k > 0 && nnz > 0) {
     // dense tiles: split A into the kept tiles and a rest CSR (both in the tile region behind the
     // plain workspace), then prepare the rest like any other matrix
-    const size_t plain = round_up(L.total, 256);
+    const size_t plain = L.need;
     const TileWsLayout TL = tile_ws_layout(m, k, nnz, f);
     if (ws_bytes < plain + TL.total) return SAGNN_ECAPACITY;
     TilePlan tp{};

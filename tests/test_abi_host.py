@@ -2,6 +2,7 @@
 header declares, and argument validation rejects bad calls before any HIP call is made."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -71,6 +72,35 @@ def test_workspace_queries():
     assert L.gcn_bwd_workspace_bytes(1000, 256, 256, ctypes.byref(b)) == 0 and b.value >= 256 * 256 * 4
     assert L.gcn_bwd_workspace_bytes(1000, 102, 256, ctypes.byref(b)) == -1
     assert L.gcn_bwd_workspace_bytes(1000, 16, 260, ctypes.byref(b)) == -1
+
+
+@pytest.mark.parametrize("f", [4, 16, 32, 64, 100, 128, 132, 256, 512])
+def test_product_workspace_grows_with_the_entries(f):
+    """On both sides of every count at which chunks or pieces get longer, a matrix of more entries needs no less room."""
+    def size(nnz):
+        b = ctypes.c_size_t(0)
+        assert sagnn.lib().spmm_csr_workspace_bytes(1_000_000, nnz, f, ctypes.byref(b)) == 0
+        return b.value
+
+    steps = {8192 << e for e in range(18)} | {8192 * g * t for g in (1, 2, 4, 8, 16) for t in range(15, 130)}
+    counts = sorted({c for s in steps for c in (s - 1, s, s + 1, s + s // 16)} | {0, 1, 4095, 2_147_483_647})
+    sizes = [size(c) for c in counts]
+    for a, b, x, y in zip(counts, counts[1:], sizes, sizes[1:]):
+        assert x <= y, f"{x} bytes for {a} entries, {y} for {b}"
+
+
+def test_product_workspace_grows_with_rows_entries_and_width():
+    """Room for a matrix is room for every smaller one (widths that are never copied to aligned rows: there the room for
+    the copy comes on top and is not asked for)."""
+    rng = random.Random(5)
+    for _ in range(20_000):
+        small = rng.randint(0, 1 << rng.randint(0, 24)), rng.randint(0, (1 << rng.randint(0, 31)) - 1), 32 * rng.randint(1, 16)
+        large = small[0] + rng.randint(0, 1 << rng.randint(0, 24)), min(small[1] + rng.randint(0, 1 << rng.randint(0, 31)),
+                                                                        2_147_483_647), small[2] + 32 * rng.randint(0, 8)
+        b = [ctypes.c_size_t(0), ctypes.c_size_t(0)]
+        for x, (m, nnz, f) in zip(b, (small, large)):
+            assert sagnn.lib().spmm_csr_workspace_bytes(m, nnz, f, ctypes.byref(x)) == 0
+        assert b[0].value <= b[1].value, (small, large)
 
 
 def test_argument_validation_before_launch():

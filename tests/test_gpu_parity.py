@@ -1,6 +1,7 @@
 """GPU parity: every step of the hot path, called through the C ABI, element by element against
 the CPU oracle on the same seeded inputs.  Integer results bit-exact; fp32 SpMM within
 1e-5 * sum|terms|; bf16 GEMM within 1e-2 * sum|terms|."""
+import ctypes
 import math
 
 import numpy as np
@@ -491,6 +492,42 @@ def test_spmm_rows_moved_to_cache_lines(f, n, sweep, monkeypatch):
         for operand in (dev(B), wide[:, :f]):
             got = sagnn.spmm_csr_tallskinny(rp, ci, v, operand, C=torch.full((m, f), float("nan"), device="cuda"), ws=ws)
             assert_close(got, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} m={m} k={k}")
+
+
+@pytest.mark.parametrize("f,n,more", [(24, 270_000, 280_000), (60, 180_000, 190_000)])
+def test_spmm_workspace_of_a_matrix_with_more_rows_serves_one_with_fewer(f, n, more):
+    """With more rows the copy of B to aligned rows does not pay and the workspace has no room for it; the matrix with
+    fewer rows, which would be given a copy, goes without one in that room."""
+    nnz = 6_000_000
+    L = sagnn.lib()
+
+    def size(m):
+        b = ctypes.c_size_t(0)
+        assert L.spmm_csr_workspace_bytes(m, nnz, f, ctypes.byref(b)) == 0
+        return b.value
+
+    assert size(more) < size(n)
+    rng = np.random.default_rng(f)
+    rowptr = np.concatenate([[0], np.cumsum(rng.multinomial(nnz, np.full(n, 1.0 / n)))]).astype(np.int32)
+    rows = np.repeat(np.arange(n), np.diff(rowptr))
+    colidx = rng.integers(0, n, size=nnz)
+    colidx = colidx[np.lexsort((colidx, rows))].astype(np.int32)
+    rp, ci, v, B = dev(rowptr), dev(colidx), dev(rng.standard_normal(nnz).astype(np.float32)), dev(synth.normal((n, f), f, synth.STREAM_H))
+    ref = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double(), (n, n)) @ B.double()
+    zabs = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double().abs(), (n, n)) @ B.double().abs()
+    C, guard = torch.empty((n, f), device="cuda"), 4096
+    stream = torch.cuda.current_stream().cuda_stream
+    for schedule in (1, 2):
+        opt = sagnn.SpmmOptions()
+        opt.schedule = schedule
+        buf = torch.full((size(more) + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+        args = (rp.data_ptr(), ci.data_ptr(), v.data_ptr(), n, n, nnz)
+        assert L.spmm_csr_prepare_opt(*args, f, buf.data_ptr(), size(more), ctypes.byref(opt), stream) == 0
+        C.fill_(float("nan"))
+        assert L.spmm_csr_tallskinny(*args, B.data_ptr(), f, f, C.data_ptr(), f, 0, buf.data_ptr(), size(more), stream) == 0
+        assert_close(C, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} schedule {schedule}")
+        assert bool((buf[size(more):] == 0xA5).all())
+        assert L.spmm_csr_release(buf.data_ptr()) == 0
 
 
 @pytest.mark.parametrize("f,labels", [(16, "order"), (100, "order"), (256, "order"), (64, "random"), (256, "random"), (64, "hubs")])
