@@ -411,9 +411,12 @@ __global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict_
 }
 
 // Slices of rows, at least 128 rows each: two workgroups per CU, one where a partial result is large.
-inline int32_t tn_parts(int64_t m, int32_t fi, int32_t fo) {
-  const int64_t most = (int64_t)fi * fo <= 16384 ? 512 : 256;
-  return (int32_t)std::max<int64_t>(1, std::min(most, ceil_div(m, 128)));
+constexpr int64_t kTnSmall = 16384;   // elements of a result that is not large
+inline int64_t tn_parts(int64_t m, int64_t elems) {
+  return std::max<int64_t>(1, std::min<int64_t>(elems <= kTnSmall ? 512 : 256, ceil_div(m, 128)));
+}
+inline size_t tn_partial_bytes(int64_t m, int64_t elems) {
+  return round_up(sizeof(float) * (size_t)(tn_parts(m, elems) * elems), 256);
 }
 
 // The LDS-staged form reads every row once per workgroup, the direct form once per 64 columns of the other
@@ -426,8 +429,10 @@ inline bool tn_staged(int32_t fi, int32_t fo, int32_t prec) {
 
 }  // namespace
 
+// enough for narrower operands too: their result may be cut into more slices
 size_t gemm_tn_ws_bytes(int64_t m, int32_t fi, int32_t fo) {
-  return round_up(sizeof(float) * (size_t)tn_parts(m, fi, fo) * (size_t)fi * (size_t)fo, 256);
+  const int64_t elems = (int64_t)fi * fo;
+  return std::max(tn_partial_bytes(m, elems), tn_partial_bytes(m, std::min(elems, kTnSmall)));
 }
 
 int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, int64_t m,
@@ -439,8 +444,8 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
   if (prec != SAGNN_GEMM_FP32 && prec != SAGNN_GEMM_BF16 && prec != SAGNN_GEMM_FP32_BF16X3) return SAGNN_EINVAL;
   if (!Y || !yws || !aligned16(yws)) return SAGNN_EINVAL;
   if (m > 0 && (!X || !S || !aligned16(X) || !aligned16(S))) return SAGNN_EINVAL;
-  if (yws_bytes < gemm_tn_ws_bytes(m, fi, fo)) return SAGNN_ECAPACITY;
-  const int32_t parts = tn_parts(m, fi, fo);
+  if (yws_bytes < tn_partial_bytes(m, (int64_t)fi * fo)) return SAGNN_ECAPACITY;
+  const int32_t parts = (int32_t)tn_parts(m, (int64_t)fi * fo);
   TnArgs g{};
   g.X = X; g.ldx = ldx; g.S = S; g.lds_ = lds_; g.m = m; g.fi = fi; g.fo = fo;
   g.rows_per_wg = ceil_div(ceil_div(m > 0 ? m : 1, parts), KB) * KB;

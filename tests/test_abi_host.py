@@ -103,6 +103,34 @@ def test_product_workspace_grows_with_rows_entries_and_width():
         assert b[0].value <= b[1].value, (small, large)
 
 
+def test_scratch_of_the_other_calls_grows_with_their_sizes():
+    """Room for a call is room for every smaller one: weight gradient (rows and both widths), column split, transpose,
+    permutation."""
+    rng = random.Random(6)
+    L = sagnn.lib()
+
+    def size(query, *args):
+        b = ctypes.c_size_t(0)
+        assert query(*args, ctypes.byref(b)) == 0
+        return b.value
+
+    def pair(high):
+        return sorted(rng.randint(0, (1 << rng.randint(0, high)) - 1) for _ in range(2))
+
+    widths = [4, 60, 64, 100, 124, 128, 132, 160, 192, 252, 256]
+    for m in (0, 1, 128, 129, 32_768, 32_769, 65_536, 65_537, 10_000_000):
+        sizes = [[size(L.gcn_bwd_workspace_bytes, m, fi, fo) for fo in widths] for fi in widths]
+        for i in range(len(widths)):
+            assert sizes[i] == sorted(sizes[i]) and [r[i] for r in sizes] == sorted(r[i] for r in sizes), (m, widths[i])
+    for _ in range(20_000):
+        (m0, m1), (e0, e1) = pair(24), pair(31)
+        b0, b1 = sorted(rng.randint(1, 64) for _ in range(2))
+        assert size(L.gcn_bwd_workspace_bytes, m0, 64, 100) <= size(L.gcn_bwd_workspace_bytes, m1, 64, 100)
+        assert size(L.spmm_transpose_workspace_bytes, e0) <= size(L.spmm_transpose_workspace_bytes, e1)
+        assert size(L.spmm_permute_workspace_bytes, m0, e0) <= size(L.spmm_permute_workspace_bytes, m1, e1)
+        assert size(L.spmm_split_workspace_bytes, m0, b0) <= size(L.spmm_split_workspace_bytes, m1, b1)
+
+
 def test_argument_validation_before_launch():
     L = sagnn.lib()
     # pack: bad f, null pointers, bad leading dimension
