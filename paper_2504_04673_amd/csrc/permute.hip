@@ -351,6 +351,7 @@ SAGNN_EXPORT int spmm_csr_permute_symmetric(const int32_t* d_rowptr, const int32
   int rc = carve_permute(d_ws, n, nnz, &w);
   if (rc != SAGNN_OK) return rc;
   if (ws_bytes < w.bytes) return SAGNN_ECAPACITY;
+  if (n == 0 && nnz > 0) return SAGNN_EFORMAT;   // no column is in range
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(zero_i32_kernel, grid_for(n + 4), dim3(kThreads), 0, s, w.seen, n);
   SAGNN_LAUNCH_CHECK();

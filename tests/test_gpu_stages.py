@@ -355,3 +355,16 @@ def test_reorder_rejects_bad_labels_and_maps():
         sagnn.spmm_csr_permute_symmetric(dev(rowptr), dev(badcol), dev(val), ok)
     assert ei.value.code == -3
     sagnn.spmm_csr_permute_symmetric(dev(rowptr), dev(colidx), dev(val), ok)
+
+
+@pytest.mark.parametrize("nnz", [1, 300])
+def test_permute_symmetric_refuses_entries_without_rows(nnz):
+    """A matrix of no rows and columns holds no entries: every column id is out of range."""
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    for last in (0, nnz):
+        with pytest.raises(sagnn.SagnnError) as ei:
+            sagnn.spmm_csr_permute_symmetric(dev(np.array([last], np.int32)), dev(np.zeros(nnz, np.int32)),
+                                             dev(np.ones(nnz, np.float32)), none)
+        assert ei.value.code == -3
+    rpp, cip, _ = sagnn.spmm_csr_permute_symmetric(dev(np.zeros(1, np.int32)), none, none.float(), none)
+    assert rpp.cpu().tolist() == [0] and cip.numel() == 0
