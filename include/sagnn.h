@@ -216,7 +216,8 @@ typedef struct sagnn_spmm_options {
   int32_t min_long;        /* rows with at least this many entries are swept (0 = decide; >= 16;
                               negative: -min_long replaces 64 where the rule would pick 64)         */
   int32_t piece;           /* longest piece a swept row is cut into (0 = decide: 256..4096 by the
-                              number of entries, 4096 with schedule 2; 1024..32768)                  */
+                              number of entries, 4096 with schedule 2); 1024..32768, shorter ones
+                              down to 256 where the number of entries makes that the shortest        */
   int32_t slab_kb;         /* KiB of B per slab (0 = 4096); -1 = as many slabs as the format allows  */
   int32_t min_waves;       /* fewer than 16 pieces per wavefront below this many wavefronts (0 = 8192) */
   int32_t window_pct;      /* dealing window in % of the resident pieces (0 = 25 where the row
@@ -272,7 +273,11 @@ typedef struct sagnn_spmm_options {
 /* A buffer of the size reported for a matrix is accepted for every matrix with no more rows, no more
  * entries and no wider operand.  The size includes room for a copy of B whose rows begin on cache lines
  * where such a copy pays (f <= 128 and no multiple of 32, many entries per row of B); where a buffer that
- * was sized for another matrix has no room for it, the product runs without the copy. */
+ * was sized for another matrix has no room for it, the product runs without the copy.
+ * About 20 bytes per entry and 55 per row; 4 f bytes more for every chunk of nonzero splitting, which
+ * may begin inside a row and then leaves its share of that row there: chunks have 128 entries (4 f / 128
+ * bytes per entry) and fewer, down to 16, on matrices too small to fill the chip with them (4 f / 16); 8 f
+ * bytes for every 256 to 1024 entries, for the pieces of rows that the sweep cuts; the aligned copy. */
 int spmm_csr_workspace_bytes(int64_t m, int64_t nnz, int32_t f, size_t* bytes);
 /* Workspace size for a preparation with the given options: spmm_csr_workspace_bytes() plus, with
  * dense_tiles = 1, the tile region.  h_opt may be NULL.
