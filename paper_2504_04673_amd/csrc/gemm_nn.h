@@ -324,7 +324,23 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
               if (!(mv[dv][nt] > 0.f)) acc[nt][v0 + dv] = 0.f;
         }
       }
-      if constexpr (!RAG) {
+      if constexpr (!RAG && PREC == SAGNN_GEMM_FP32 && NT == 2) {
+        // 64 columns in fp32: a pointer per lane.  With scalar row addresses one output of 64 columns takes longer than
+        // two (2.45 M x 128 x 64: 502 us with one, 504 with both; 600 k: 142); this way 430 and 515 (600 k: 115).  The
+        // other slabs are as fast or faster with scalars (128 columns, masked, 600 k: 223 against 235).
+        float* zl = g.Z ? g.Z + (t * 32 + h * 4) * g.ldz + col0 : nullptr;
+        float* al = g.A ? g.A + (t * 32 + h * 4) * g.lda + col0 : nullptr;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int64_t dr = (v >> 2) * 8 + (v & 3);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            const float z = acc[nt][v];
+            if (zl) zl[dr * g.ldz + nt * 32] = z;
+            if (al) al[dr * g.lda + nt * 32] = relu ? (z > 0.f ? z : 0.f) : z;
+          }
+        }
+      } else if constexpr (!RAG) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int64_t dr = (v >> 2) * 8 + (v & 3);
@@ -369,11 +385,19 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
 
 template <int NT, int PREC, int WAVES>
 int launch_nn_waves(const GemmArgs& g, size_t lds, hipStream_t s) {
-  // a k extent of up to 128, or 256, has its loop unrolled (see NG); the padded form also serves whole groups where
-  // the unpadded one would gain nothing (few groups: the loads are clamped, not skipped)
+  // A k extent of up to 128, or 256, has its loop unrolled (see NG).  Whole groups take the form without guards in fp32
+  // and three-term mode: on many rows the guards cost a quarter (2.45 M rows, fp32, activation only: 64 x 64 345 us with
+  // and 309 without, 96 x 64 512 and 377).  A single group has nothing to prefetch and is not unrolled (32 x 64: 245 with
+  // guards, 219 unrolled, 190 as a loop, the last two with the stores of 64 columns below).  With operands rounded to
+  // bfloat16 the guarded forms are as fast or faster (96 x 64: 283 and 301).
   auto pick = [&](auto rag) -> void (*)(const GemmArgs) {
     constexpr bool RAG = decltype(rag)::value;
     const int ng = (g.kdim + 31) / 32;
+    if constexpr (PREC != SAGNN_GEMM_BF16) {
+      if (g.kdim == 32) return gemm_nn_kernel<NT, PREC, WAVES, false, 0, RAG>;
+      if (g.kdim == 64) return gemm_nn_kernel<NT, PREC, WAVES, false, 2, RAG>;
+      if (g.kdim == 96) return gemm_nn_kernel<NT, PREC, WAVES, false, 3, RAG>;
+    }
     if (ng == 1) return gemm_nn_kernel<NT, PREC, WAVES, true, 1, RAG>;
     if (g.kdim == 128) return gemm_nn_kernel<NT, PREC, WAVES, false, 4, RAG>;
     if constexpr (NT < 8) {   // (256 columns leave no registers for the guards of an unrolled loop)

@@ -1106,6 +1106,27 @@ def test_dense_gemm_at_the_edges_of_its_groups_and_slabs(m, k, n, prec):
                 assert torch.equal(A, Z.clamp(min=0))
 
 
+@pytest.mark.parametrize("prec", [sagnn.GEMM_FP32, sagnn.GEMM_FP32_BF16X3])
+@pytest.mark.parametrize("m,k,n", [(31, 32, 64), (64, 32, 32), (97, 64, 64), (128, 64, 192), (65, 96, 64), (4100, 96, 32), (160, 128, 64)])
+def test_dense_gemm_of_whole_k_groups_and_64_columns(m, k, n, prec):
+    """One to four whole groups of k by slabs of 32 and 64 columns, each output alone and both, masked and not."""
+    gen = torch.Generator().manual_seed(100 * k + n)
+    X, W = torch.randn(m, k, generator=gen), torch.randn(k, n, generator=gen)
+    mask = torch.randint(-1, 2, (m, n), generator=gen).float()
+    ref = X.double() @ W.double()
+    # any order of k fp32 additions: k 2^-24 of the sum of the terms' sizes
+    bound = (2 * 2.0**-23 + (k + 2) * 2.0**-24) * (X.abs().double() @ W.abs().double())
+    for mk in (None, mask.cuda()):
+        want = ref if mk is None else torch.where(mask > 0, ref, torch.zeros(()).double())
+        for z, a in ((True, False), (False, True), (True, True)):
+            Z, A = sagnn.dense_gemm_act(X.cuda(), W.cuda(), prec=prec, act=sagnn.ACT_RELU, mask=mk, want_z=z, want_act=a)
+            assert (Z is not None) == z and (A is not None) == a
+            if z:
+                assert bool(((Z.cpu().double() - want).abs() <= bound).all())
+            if a:
+                assert bool(((A.cpu().double() - want.clamp(min=0)).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("k,n", [(128, 128), (256, 256), (100, 44)])
 def test_bf16x3_gemm_has_the_accuracy_of_the_fp32_gemm(k, n):
     """fp32 operands as three bfloat16 terms, six products: every operand bit takes part, so the
