@@ -11,7 +11,7 @@
 // walks one chunk, so one load instruction serves 64 / LPE entries.  Column ids and values of 16 or 32 entries arrive
 // with one load each, spread over the lanes of a DPP unit (a quad below 16 lanes per entry, a row of 16 above), and are
 // handed to the whole group by DPP broadcasts that ride on the instructions that use them: per entry and
-// group one add for the address, one load, four multiply-adds.
+// group one add for the address, one load, four multiply-adds (and at narrow widths four adds per batch: see FOLD).
 // Bound by: the latency of its dependent loads on small matrices (chunk, columns, rows of B: hence the short
 // chunks), by what the L2s do not hold of B on large ones (7.5 TB/s behind the L2s whatever the row length).
 // The kernels it replaces took 256 entries per wavefront, eight at a time: 30 k rows x 12 entries, f = 100: 64 -> 28 us;
@@ -61,7 +61,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 // NC: entries a lane holds of a span (2 above quads; 8 in quads, so that whole lines of the entry arrays are used up
 // at once -- with 4 the lines are out of the L1 again before their second half is needed, 670 against 587 us on
 // 50 M entries at f = 16 -- or 4 where the chunks are shorter than such a span)
-template <int LPE, int NC, bool BUF>
+// FOLD > 0: two-level sums, the entries of a batch of eight in FOLD sums of their own, then the batches.  For the widths
+// at which a row's entries used to be spread over several lane groups and added as a tree: one sum in stored order was
+// further from exact there, by 50 % at f = 16 and rows of 60 entries (1.09e-7 against 7.2e-8 in the 2-norm, now 7.3e-8), by
+// 11 % at f = 48 and rows of 12 (6.4e-8, 5.8e-8, 5.7e-8).  Costs registers and four additions per batch; the widths of whole
+// lane groups were always one sum and stay one (folded at f = 128: stage loop of a rank 431 -> 440 us, six wavefronts
+// per SIMD instead of seven).  30 k rows x 12, training 140.0 -> 140.3 us; 1 M x 50, f = 16, training 2278 -> 2286.
+template <int LPE, int NC, int FOLD, bool BUF>
 __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, const FlatDims d) {
   constexpr bool QUAD = LPE < 16;
   constexpr int R = 64 / LPE;                // groups (chunks) per wavefront
@@ -75,7 +81,7 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
   if (!ws_matches(hdr, d)) return;
   const int64_t wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6));
   if (wave * R >= d.nchunks) return;
-  const int64_t k = wave * R + lane / LPE;
+  const int32_t k = (int32_t)(wave * R) + lane / LPE;
   int4 ch = make_int4(0, 0, 0, 0);
   if (k < d.nchunks) ch = chunks[k];
   int32_t e0 = ch.x, e1 = ch.y, r = ch.z;
@@ -100,16 +106,20 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
   int32_t rid = row_at(r);
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
   const float* __restrict__ Bl = B + (active ? lig * 4 : 0);
-  float* __restrict__ Cl = C + lig * 4;
-  float* __restrict__ slot = carry + k * d.carry_ld + lig * 4;
 
-  vec4 acc = 0.f;
+  vec4 acc = 0.f, part[2] = {0.f, 0.f};   // the row's sum up to this batch, and in this batch
+  auto fold = [&]() {
+    if constexpr (FOLD == 1) acc += part[0];
+    if constexpr (FOLD == 2) acc += part[0] + part[1];
+    part[0] = part[1] = 0.f;
+  };
   auto emit = [&]() {   // the row that ends (or is cut) here
+    fold();
     if (active && r <= rmax) {
       if (head) {
-        *reinterpret_cast<vec4*>(slot) = acc;
+        *reinterpret_cast<vec4*>(carry + (k * d.carry_ld + lig * 4)) = acc;
       } else {
-        vec4* p = reinterpret_cast<vec4*>(Cl + (int64_t)rid * d.ldc);
+        vec4* p = reinterpret_cast<vec4*>(C + (rid * d.ldc + lig * 4));
         if (d.accumulate) acc += *p;
         *p = acc;
       }
@@ -213,12 +223,14 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
       static_for<0, U>([&](auto iu) {
         constexpr int s = s0 + decltype(iu)::value;
         const float vs = __builtin_bit_cast(float, unit_bcast<QUAD, s / NC>(__builtin_bit_cast(uint32_t, v[s % NC])));
-        acc += vs * h[s - s0];
+        if constexpr (FOLD == 0) acc += vs * h[s - s0];
+        else part[s % FOLD] += vs * h[s - s0];
         if ((any >> s) & 1u) {
           asm volatile("");   // (a scalar branch first: the two tests are not to be merged)
           if ((fl >> s) & 1u) emit();
         }
       });
+      fold();
     });
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -435,13 +447,16 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
     SAGNN_LAUNCH_CHECK();
     return SAGNN_OK;
   };
-#define SAGNN_FLAT(LPE_, NC_) (buf ? go(spmm_flat_kernel<LPE_, NC_, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, false>, LPE_))
+#define SAGNN_FLAT(LPE_, NC_, FOLD_) \
+  (buf ? go(spmm_flat_kernel<LPE_, NC_, FOLD_, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, FOLD_, false>, LPE_))
   const bool brief = a.nnz < 64 * a.nchunks;
-  if (fw <= 16) return brief ? SAGNN_FLAT(4, 4) : SAGNN_FLAT(4, 8);
-  if (fw <= 32) return brief ? SAGNN_FLAT(8, 4) : SAGNN_FLAT(8, 8);
-  if (fw <= 64) return SAGNN_FLAT(16, 2);
-  if (fw <= 128) return SAGNN_FLAT(32, 2);
-  return SAGNN_FLAT(64, 2);
+  if (fw <= 16) return brief ? SAGNN_FLAT(4, 4, 2) : SAGNN_FLAT(4, 8, 2);
+  if (fw <= 32) return brief ? SAGNN_FLAT(8, 4, 1) : SAGNN_FLAT(8, 8, 1);
+  if (fw < 64) return SAGNN_FLAT(16, 2, 1);
+  if (fw == 64) return SAGNN_FLAT(16, 2, 0);
+  if (fw < 128) return SAGNN_FLAT(32, 2, 1);
+  if (fw == 128) return SAGNN_FLAT(32, 2, 0);
+  return SAGNN_FLAT(64, 2, 0);
 #undef SAGNN_FLAT
 }
 
