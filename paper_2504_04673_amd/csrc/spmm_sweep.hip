@@ -626,6 +626,35 @@ __device__ __forceinline__ uint32_t row_element(uint32_t at, int v, int32_t fw) 
   return ODD && (int32_t)at > fw - v ? (uint32_t)(fw - v) : at;
 }
 
+// Sum of a segment.  TWO: the entries of a batch of eight in two sums, then the batches, where a plain sum goes on through
+// the segment.  For the widths between the kernels' own (ODD) below 64, and below 128 with one row per load: nonzero
+// splitting, which had these widths before, added their entries as a tree.  Error against 64 bits (2-norm) by the tree,
+// by a plain sum, by two: 300 k vertices of 42 in 16 communities f = 8 6.9e-8, 1.18e-7, 6.9e-8, f = 48 7.8e-8, 1.17e-7,
+// 7.4e-8; a rank's rows f = 48 3.0e-8, 3.6e-8, 3.2e-8.  (What is left is the order of the slabs: random columns, 40 a row,
+// f = 48 7.7e-8, 8.3e-8, 8.5e-8, as the full widths always had.)  1 M vertices, 50 M
+// entries: f = 36 870 -> 893 us, f = 48 838 -> 852, the other widths and graphs within 1 %.  At f = 100 to 252 with lane
+// groups or four floats a lane the plain sum was no worse than the tree, and two would cost 2 %.
+template <typename vec, bool TWO>
+struct SegmentSum {
+  vec acc = 0.f, part[2] = {0.f, 0.f};
+  __device__ __forceinline__ void add(int u, float v, const vec& h) {
+    if constexpr (TWO) part[u & 1] += v * h;
+    else acc += v * h;
+  }
+  __device__ __forceinline__ void batch_ends() {
+    if constexpr (TWO) {
+      acc += part[0] + part[1];
+      part[0] = part[1] = 0.f;
+    }
+  }
+  __device__ __forceinline__ vec take() {
+    batch_ends();
+    const vec t = acc;
+    acc = 0.f;
+    return t;
+  }
+};
+
 // ODD: rows of any multiple of 4 floats instead of the kernel's full width.  The lanes beyond the end of the row work
 // on its last FPL floats a second time: same addresses, same values, so neither loads nor accumulator updates nor
 // stores need a mask, and the accumulator rows are as long as the rows themselves.
@@ -656,7 +685,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
   const float* __restrict__ vw = vals + base;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
-  vec acc = 0.f;
+  SegmentSum<vec, ODD && FPL <= 2> sum;
   for (int32_t e = 0; e < len; e += U) {
     uint32_t c[U];
     float v[U];
@@ -672,13 +701,13 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
     for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      acc += v[u] * h[u];
+      sum.add(u, v[u], h[u]);
       if (c[u] >> 31) {   // last entry of a (piece, slab) segment: fold into the piece's LDS row
         vec* p = reinterpret_cast<vec*>(my + ((c[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
-        *p += acc;
-        acc = 0.f;
+        *p += sum.take();
       }
     }
+    sum.batch_ends();
   }
 
 #pragma unroll 1
@@ -1028,7 +1057,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
 
   int32_t e = 0;
   for (int iv = 0; iv < n_iv; ++iv) {
-    vec acc = 0.f;   // (what the padding of the interval before left in it is not summed: see spmm_sweep_perm_kernel)
+    SegmentSum<vec, ODD && R == 4> sum;   // (what the padding of the interval before left is not summed: see spmm_sweep_perm_kernel)
     const int32_t e_end = iv + 1 < n_iv ? so[iv + 1] : steps;
     for (; e < e_end; e += U) {
       uint32_t c[U][R];
@@ -1076,13 +1105,13 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
       for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        acc += mv[u] * h[u];
+        sum.add(u, mv[u], h[u]);
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
           vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
-          *p += acc;
-          acc = 0.f;
+          *p += sum.take();
         }
       }
+      sum.batch_ends();
     }
     // between two intervals: wait for the cohort (barrier mode) or hold the wavefront to the
     // schedule (pacing); a wavefront with nothing in an interval still takes part
@@ -1174,7 +1203,8 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     all_own = __builtin_amdgcn_readfirstlane(all_own);
   }
 
-  vec acc = 0.f, tot = 0.f;
+  SegmentSum<vec, ODD> sum;
+  vec tot = 0.f;
   uint32_t cb[NB];
   float vb[NB];
 #pragma unroll
@@ -1211,27 +1241,25 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     if constexpr (SL > 1) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        acc += mv[u] * h[u];
+        sum.add(u, mv[u], h[u]);
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
           vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
-          *p += acc;
-          acc = 0.f;
+          *p += sum.take();
         }
       }
+      sum.batch_ends();
     } else {
       if (e + 8 <= all_own) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += mv[u] * h[u];
+        for (int u = 0; u < 8; ++u) sum.add(u, mv[u], h[u]);
       } else {
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (e + u < own) acc += mv[u] * h[u];
+          if (e + u < own) sum.add(u, mv[u], h[u]);
       }
-      // no slots to flush into: fold the running sum every 64 entries instead (two-level sum)
-      if ((e & 63) == 56) {
-        tot += acc;
-        acc = 0.f;
-      }
+      sum.batch_ends();
+      // no slots to flush into: fold the running sum every 64 entries instead
+      if ((e & 63) == 56) tot += sum.take();
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
@@ -1239,14 +1267,14 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
       vb[q] = nvb[q];
     }
   }
-  if constexpr (SL == 1) acc += tot;
+  if constexpr (SL == 1) tot += sum.take();
 
 #pragma unroll 1
   for (int ls = 0; ls < SL; ++ls) {
     const int slot = (int)gid * SL + ls;
     const int32_t tgt = piece_target[w * kSweepSlots + slot];
     if (tgt == INT32_MIN) continue;
-    vec r = acc;
+    vec r = tot;
     if constexpr (SL > 1) r = *reinterpret_cast<const vec*>(my + slot * kRow);
     if (tgt >= 0) {
       vec* p = reinterpret_cast<vec*>(reinterpret_cast<char*>(C + (int64_t)tgt * d.ldc) + loff);
