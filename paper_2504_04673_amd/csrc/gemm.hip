@@ -19,11 +19,11 @@
 // The epilogue applies the optional mask and activation and stores from the accumulator
 // layout (row = 8*(v/4) + 4*(lane/32) + v%4, col = lane%32 of each 32x32 tile).
 //
-// gemm_tn_kernel (Y = X^T S): the reduction runs over the m rows.  Each workgroup takes a
-// contiguous slab of rows, stages 32 rows of X and S at a time in LDS transposed (k
-// contiguous per column, so an operand is one LDS read), accumulates a full f_in x f_out
-// partial in registers (8 wavefronts x 2x4 tiles) and writes it to scratch; a second kernel
-// sums the partials in a fixed order (reproducible, no atomics).
+// Y = X^T S: the reduction runs over the m rows, cut into slices whose partial results tn_reduce_kernel adds in a
+// fixed order (reproducible, no atomics).  gemm_tn_direct_kernel takes its operands straight from memory, for every
+// mode; gemm_tn_kernel stages 32 rows of X and S at a time in LDS transposed (k contiguous per column, so an operand is
+// one LDS read) and holds a full f_in x f_out partial in registers (8 wavefronts x 2x4 tiles), for rounded operands
+// whose result one workgroup of the other does not cover (see tn_staged).
 #include <algorithm>
 #include <type_traits>
 

@@ -19,7 +19,7 @@
 // LDS row whenever a (piece, slab) segment ends), so nothing is spilled to HBM between slabs.
 // Pieces of a split row are summed in a fixed order by a small second kernel.  Short rows are
 // swept as whole rows -- 16 per wavefront, each one segment, in wavefronts of their own -- where
-// the matrix allows it, else they go through the nonzero-splitting kernels of spmm.hip on a
+// the matrix allows it, else they go through the nonzero-splitting kernel of spmm_flat.hip on a
 // compacted CSR.
 //
 // The entry stream of a wavefront is stored in the workspace as (code, value) pairs sorted by
