@@ -66,7 +66,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // further from exact there, by 50 % at f = 16 and rows of 60 entries (1.09e-7 against 7.2e-8 in the 2-norm, now 7.3e-8), by
 // 11 % at f = 48 and rows of 12 (6.4e-8, 5.8e-8, 5.7e-8).  Costs registers and four additions per batch; the widths of whole
 // lane groups were always one sum and stay one (folded at f = 128: stage loop of a rank 431 -> 440 us, six wavefronts
-// per SIMD instead of seven).  30 k rows x 12, training 140.0 -> 140.3 us; 1 M x 50, f = 16, training 2278 -> 2286.
+// per SIMD instead of seven).  30 k rows x 12, training 140.0 -> 140.3 us; 1 M x 50, f = 16, training 2278 -> 2286;
+// 4 k rows x 8, f = 16, this kernel 10.5 -> 11.2.  One sum per batch at f <= 16: 10.8 us, but 7.6e-8 on the rows of 60; four
+// sums through the whole row: 11.4 us and 7.5e-8.
 template <int LPE, int NC, int FOLD, bool BUF>
 __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, const FlatDims d) {
   constexpr bool QUAD = LPE < 16;
