@@ -655,6 +655,34 @@ struct SegmentSum {
   }
 };
 
+// Who of a SIMD's wavefronts may issue next.  Left alone the hardware serves the oldest first: at the middle of a
+// generation the six wavefronts of a SIMD stood 0.10 to 0.29 of a stream apart in order of their age, so the L2 held the
+// rows of B that the first of them wanted and the last fetched them again.  A wavefront goes down through the four
+// priorities as it walks, one per `stride` steps, and begins again at the top: of those less than four strides apart the
+// one behind goes first.  64 steps a stride (power-law streams of 1600 to 4600 steps: 32 to 128 within 1 %, 8 and none
+// 4 to 6 % slower), a sixteenth of a shorter stream.  2.45 M vertices, 125 M entries: f = 128 4363 -> 4132 us, f = 64
+// 2705 -> 2322; 233 k, 114 M, f = 128 2455 -> 2328; partitioned 2 M, 84 M, f = 128 5588 -> 5376.  No gain and not used
+// with sixteen groups, whose wavefronts wait for the address units.  Progress counted in memory, so that the order holds
+// beyond four strides, costs more than it gives: an atomic per level and wavefront, 4.7 ms and more for the first figure.
+struct TurnTaking {
+  int32_t next, stride;
+  uint32_t level;
+  __device__ __forceinline__ explicit TurnTaking(int32_t steps) : next(0), level(0) {
+    stride = (steps >> 4) & ~7;
+    stride = stride > 64 ? 64 : (stride < 8 ? 8 : stride);
+  }
+  __device__ __forceinline__ void at(int32_t e) {   // before the batch that begins with step e, e a multiple of 8
+    if (e != next) return;
+    next += stride;
+    switch (level++ & 3u) {
+      case 0: __builtin_amdgcn_s_setprio(3); break;
+      case 1: __builtin_amdgcn_s_setprio(2); break;
+      case 2: __builtin_amdgcn_s_setprio(1); break;
+      default: __builtin_amdgcn_s_setprio(0); break;
+    }
+  }
+};
+
 // ODD: rows of any multiple of 4 floats instead of the kernel's full width.  The lanes beyond the end of the row work
 // on its last FPL floats a second time: same addresses, same values, so neither loads nor accumulator updates nor
 // stores need a mask, and the accumulator rows are as long as the rows themselves.
@@ -686,7 +714,9 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
   SegmentSum<vec, ODD && FPL <= 2> sum;
+  TurnTaking turn(len);
   for (int32_t e = 0; e < len; e += U) {
+    turn.at(e);
     uint32_t c[U];
     float v[U];
 #pragma unroll
@@ -931,7 +961,9 @@ __global__ __launch_bounds__(256) void spmm_sweep_fused_kernel(
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
   vec acc = 0.f;
+  TurnTaking turn(len);
   for (int32_t e = 0; e < len; e += U) {
+    turn.at(e);
     uint32_t c[U];
     float v[U];
 #pragma unroll
@@ -1055,11 +1087,13 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   const bool paced = d.pace_ticks > 0.f && n_iv > 1;
   const uint64_t t_start = paced ? wall_clock64() : 0ull;
 
+  TurnTaking turn(steps);
   int32_t e = 0;
   for (int iv = 0; iv < n_iv; ++iv) {
     SegmentSum<vec, ODD && R == 4> sum;   // (what the padding of the interval before left is not summed: see spmm_sweep_perm_kernel)
     const int32_t e_end = iv + 1 < n_iv ? so[iv + 1] : steps;
     for (; e < e_end; e += U) {
+      turn.at(e);
       uint32_t c[U][R];
       float v[U][R];
 #pragma unroll
@@ -1212,7 +1246,9 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     cb[q] = steps > 0 ? cw[q * 64 + lane] : 0u;
     vb[q] = steps > 0 ? vw[q * 64 + lane] : 0.f;
   }
+  TurnTaking turn(steps);
   for (int32_t e = 0; e < steps; e += 8) {
+    if constexpr (SL > 1) turn.at(e);
     // the next iteration's stream words are requested before this one's gathers are waited for
     const bool more = e + 8 < steps;
     uint32_t ncb[NB];
