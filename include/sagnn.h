@@ -246,7 +246,9 @@ typedef struct sagnn_spmm_options {
                               (16 rows need 32768 bytes of LDS per workgroup and 5 x 32768 do not
                               fit).  Measured slower on the free-running sweep (more wavefronts
                               thrash the L2 more) and equal under pacing; off unless asked for     */
-  int32_t slab_width;      /* widest column slab of B one launch covers: 0 = 256; 128 = operands wider
+  int32_t slab_width;      /* widest column slab of B one launch covers: 0 = 256, or 64 on matrices without
+                              hubs whose neighbouring rows share rows of B (widths that are multiples of
+                              64, groups = 0); 128 = operands wider
                               than 128 are processed as 128-wide slabs by the kernels that fetch two
                               rows of B per load (faster on the 2.45 M-vertex power-law graph at
                               f = 256, slower on the community-ordered one; the measured choice of

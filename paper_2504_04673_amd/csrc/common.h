@@ -134,6 +134,8 @@ struct SpmmWsHeader {       // first 256 bytes of the SpMM workspace (device cop
   int32_t barriers;         // 1: barriers at interval boundaries
   int32_t pace_ps_per_step; // pacing asked for at prepare time (0: none)
   int32_t max_slab;         // widest column slab of B per launch (256 or 128)
+  int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
+  int32_t launch_waves;     // wavefronts per launch (0: all in one)
 };
 static_assert(sizeof(SpmmWsHeader) <= 256, "header must fit its slot");
 
@@ -250,6 +252,8 @@ struct SpmmHostDesc {
   int32_t slots;
   int32_t barriers, pace_ps_per_step;
   int32_t max_slab;         // widest column slab of B per launch (256, or 128 for the lane-group kernels at wider f)
+  int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
+  int32_t launch_waves;     // wavefronts per launch (0: all in one)
   float mean_steps;         // average stream steps per wavefront (the end of the pacing schedule)
   float max_steps;          // steps of the longest stream
   // dense-tile schedule (tiles.hip): when tiles != 0 everything above describes the rest CSR
@@ -309,6 +313,7 @@ struct SweepRowTotals {
   int64_t pieces, short_rows, short_entries, multi_rows, multi_pieces;
   int32_t min_long;
   int32_t locality;   // permille: how far the columns of neighbouring rows differ from those of all rows
+  int32_t span;       // permille of the columns that neighbouring rows choose from
   bool has_empty, bad;
 };
 bool sweep_plan_fits(const SpmmWsLayout& L);

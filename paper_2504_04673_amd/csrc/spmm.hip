@@ -363,18 +363,19 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   fl.rows = d.m; fl.nnz = d.nnz; fl.nchunks = d.nchunks; fl.colidx = p.colidx; fl.val = p.val; fl.B = B; fl.ldb = ldb;
   fl.kmax = d.kmax; fl.C = C; fl.ldc = ldc; fl.accumulate = accumulate; fl.hdr = p.hdr; fl.generation = d.generation;
   fl.chunks = p.chunks; fl.flags = p.flags; fl.carry = p.carry; fl.carry_ld = f; fl.rowmap = p.rowmap;
-  const int32_t max_slab = desc.mode == 1 && desc.max_slab == 128 ? 128 : 256;
-  // column slabs of at most 256
-  int32_t col0 = 0;
-  while (col0 < f) {
-    const int32_t rest = f - col0;
-    int32_t fw = rest >= 256 ? 256 : rest;
-    if (desc.mode == 1) {
-      fw = sweep_slab(rest, max_slab);
+  if (desc.mode == 1) {
+    const int32_t max_slab = desc.max_slab == 128 ? 128 : 256;
+    const bool narrow = desc.col_slab > 0 && f % desc.col_slab == 0;
+    for (int32_t col0 = 0, fw = 0; col0 < f; col0 += fw) {
+      fw = narrow ? desc.col_slab : sweep_slab(f - col0, max_slab);
       int rc = sweep_launch(desc, L, base, B, ldb, col0, fw, d.kmax, C, ldc, accumulate, f, s);
       if (rc != SAGNN_OK) return rc;
     }
-    if (d.nchunks > 0) {
+  }
+  // column slabs of at most 256
+  if (d.nchunks > 0) {
+    for (int32_t col0 = 0, fw = 0; col0 < f; col0 += fw) {
+      fw = f - col0 >= 256 ? 256 : f - col0;
       if (accumulate && (fw == 64 || fw == 128 || fw == 256)) {
         SpmmPtrs sp = p;
         SpmmDims sd = d;
@@ -396,7 +397,6 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
         if (rc != SAGNN_OK) return rc;
       }
     }
-    col0 += fw;
   }
   {
     int rc = flat_fixup(fl, reinterpret_cast<const int2*>(base + L.fix_list), L.max_chunks, desc.n_fix, desc.n_fix_big, f, s);
@@ -710,6 +710,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   desc.sync_timeout_ticks = h.sync_timeout_ticks; desc.sync_test_extra = h.sync_test_extra;
   desc.slots = h.slots;
   desc.max_slab = h.max_slab > 0 ? h.max_slab : 256;
+  desc.col_slab = h.col_slab; desc.launch_waves = h.launch_waves;
   desc.barriers = h.barriers; desc.pace_ps_per_step = h.pace_ps_per_step > 0 ? h.pace_ps_per_step : 0;
   desc.mean_steps = plan.mean_steps;
   desc.max_steps = plan.max_steps;

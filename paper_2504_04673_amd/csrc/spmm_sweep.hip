@@ -553,6 +553,7 @@ struct SweepDims {
   int32_t slots;        // accumulator rows per wavefront (<= kSweepSlots)
   int32_t fw;           // floats per row of this launch
   float pace_ticks;     // pacing: 100 MHz ticks per stream step (0: none)
+  int32_t block0;       // first workgroup of this launch (one row per load)
 };
 
 // Barrier between two intervals of the sweep for the workgroups that run at the same time on
@@ -671,8 +672,8 @@ struct TurnTaking {
     stride = (steps >> 4) & ~7;
     stride = stride > 64 ? 64 : (stride < 8 ? 8 : stride);
   }
-  __device__ __forceinline__ void at(int32_t e) {   // before the batch that begins with step e, e a multiple of 8
-    if (e != next) return;
+  __device__ __forceinline__ void at(int32_t e) {   // before the batch that begins with step e
+    if (e < next) return;
     next += stride;
     switch (level++ & 3u) {
       case 0: __builtin_amdgcn_s_setprio(3); break;
@@ -698,7 +699,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
   const uint32_t el = row_element<ODD>(lane * FPL, FPL, d.fw);
   const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t w = ((int64_t)d.block0 + blockIdx.x) * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != 1)
@@ -715,29 +716,37 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
 
   SegmentSum<vec, ODD && FPL <= 2> sum;
   TurnTaking turn(len);
-  for (int32_t e = 0; e < len; e += U) {
-    turn.at(e);
-    uint32_t c[U];
-    float v[U];
+  auto batch = [&](int32_t e, auto n) {
+    constexpr int N = decltype(n)::value;
+    uint32_t c[N];
+    float v[N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < N; ++u) {
       c[u] = cw[e + u];
       v[u] = vw[e + u];
     }
-    vec h[U];
+    vec h[N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
+    for (int u = 0; u < N; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
 #pragma unroll
-    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
+    for (int u = 0; u < N; ++u) asm volatile("" : "+v"(h[u]));
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < N; ++u) {
       sum.add(u, v[u], h[u]);
       if (c[u] >> 31) {   // last entry of a (piece, slab) segment: fold into the piece's LDS row
         vec* p = reinterpret_cast<vec*>(my + ((c[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
         *p += sum.take();
       }
+      if ((u & 7) == 7) sum.batch_ends();
     }
-    sum.batch_ends();
+  };
+  int32_t e = 0;
+  for (; e + U <= len; e += U) {
+    turn.at(e);
+    batch(e, std::integral_constant<int, U>{});
+  }
+  if constexpr (U > 8) {
+    if (e < len) batch(e, std::integral_constant<int, 8>{});
   }
 
 #pragma unroll 1
@@ -784,18 +793,11 @@ __device__ __forceinline__ void sweep_split3(float x, __bf16& t1, __bf16& t2, __
 template <int KROW, int MODE, int QT>
 __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ lds_acc,
                                                      const int32_t* __restrict__ piece_target,
-                                                     const SweepFusedArgs& fa, int wave, int lane) {
+                                                     const SweepFusedArgs& fa, int64_t block, int wave, int lane) {
   constexpr int kRow = KROW;
   const int r = lane & 31, h = lane >> 5;
   const int rt = wave & 1;
   const int nct = (fa.f_out + 31) >> 5;
-  // rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4
-  int32_t tg[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int tr = rt * 32 + (v >> 2) * 8 + h * 4 + (v & 3);
-    tg[v] = piece_target[((int64_t)blockIdx.x * 4 + (tr >> 4)) * kSweepSlots + (tr & 15)];
-  }
   const float* __restrict__ trow = lds_acc + (size_t)(rt * 32 + r) * kRow;
   // this wavefront's column tiles: ct_first, ct_first + 2, ..  (at most 4 of the at most 8).  k runs
   // in the outer loop so that a row piece of T is read from LDS once for the tiles of a pass, and the
@@ -818,24 +820,22 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
       const int NB = nct * 32;
       const int64_t plane = (int64_t)(kRow / 8) * NB;
       constexpr int J = kRow / 16;
+      constexpr bool kAhead = KROW > 64;   // (few steps at 64: not worth the registers that keep workgroups out)
       sweep_bf16x8 cur[QT][3], nxt[QT][3];
+      auto wload = [&](int j, sweep_bf16x8 (&dst)[QT][3]) {
 #pragma unroll
-      for (int q = 0; q < QT; ++q)
-        if (q < nmy) {
+        for (int q = 0; q < QT; ++q)
+          if (q < nmy) {
 #pragma unroll
-          for (int t = 0; t < 3; ++t) cur[q][t] = Wp[t * plane + (int64_t)h * NB + (ct0 + 2 * q) * 32 + r];
-        }
+            for (int t = 0; t < 3; ++t)
+              dst[q][t] = Wp[t * plane + (int64_t)(2 * j + h) * NB + (ct0 + 2 * q) * 32 + r];
+          }
+      };
+      if constexpr (kAhead) wload(0, cur);
 #pragma unroll 1
       for (int j = 0; j < J; ++j) {
-        if (j + 1 < J) {
-#pragma unroll
-          for (int q = 0; q < QT; ++q)
-            if (q < nmy) {
-#pragma unroll
-              for (int t = 0; t < 3; ++t)
-                nxt[q][t] = Wp[t * plane + (int64_t)(2 * (j + 1) + h) * NB + (ct0 + 2 * q) * 32 + r];
-            }
-        }
+        if constexpr (!kAhead) wload(j, cur);
+        else if (j + 1 < J) wload(j + 1, nxt);
         const float4 x0 = *reinterpret_cast<const float4*>(trow + 16 * j + 8 * h);
         const float4 x1 = *reinterpret_cast<const float4*>(trow + 16 * j + 8 * h + 4);
         const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
@@ -856,10 +856,12 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
             z[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, cur[q][1], z[q], 0, 0, 0);
             z[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, cur[q][0], z[q], 0, 0, 0);
           }
+        if constexpr (kAhead) {
 #pragma unroll
-        for (int q = 0; q < QT; ++q)
+          for (int q = 0; q < QT; ++q)
 #pragma unroll
-          for (int t = 0; t < 3; ++t) cur[q][t] = nxt[q][t];
+            for (int t = 0; t < 3; ++t) cur[q][t] = nxt[q][t];
+        }
       }
     } else if constexpr (MODE == 1) {
       // W as packed by sweep_pack_w_kernel: [k / 8][NB] vectors of 8 bfloat16 (zero beyond f_out)
@@ -919,23 +921,33 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
           for (int i = 0; i < 4; ++i) cur[q][i] = nxt[q][i];
       }
     }
+    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4.  (Looked up here and
+    // not before the loop over k, whose registers decide how many workgroups walk at the same time; hence the opaque index.)
+    uint32_t t0 = (uint32_t)block * (4 * kSweepSlots) + rt * 32 + h * 4;
+    asm volatile("" : "+v"(t0));
 #pragma unroll
-    for (int q = 0; q < QT; ++q) {
-      const int col = (ct0 + 2 * q) * 32 + r;
-      if (q >= nmy || col >= fa.f_out) continue;
+    for (int vq = 0; vq < 4; ++vq) {
+      int32_t tg[4];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (tg[v] < 0) continue;               // unused slot, or a piece of a split row
-        const float zz = z[q][v];
-        if (fa.Z) fa.Z[(int64_t)tg[v] * fa.f_out + col] = zz;
-        if (fa.Hout) fa.Hout[(int64_t)tg[v] * fa.f_out + col] = fa.act == SAGNN_ACT_RELU ? (zz > 0.f ? zz : 0.f) : zz;
+      for (int i = 0; i < 4; ++i) tg[i] = piece_target[t0 + vq * 8 + i];
+#pragma unroll
+      for (int q = 0; q < QT; ++q) {
+        const int col = (ct0 + 2 * q) * 32 + r;
+        if (q >= nmy || col >= fa.f_out) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (tg[i] < 0) continue;             // unused slot, or a piece of a split row
+          const float zz = z[q][4 * vq + i];
+          if (fa.Z) fa.Z[(int64_t)tg[i] * fa.f_out + col] = zz;
+          if (fa.Hout) fa.Hout[(int64_t)tg[i] * fa.f_out + col] = fa.act == SAGNN_ACT_RELU ? (zz > 0.f ? zz : 0.f) : zz;
+        }
       }
     }
   }
 }
 
 template <int FPL, int U, bool BUF, int MODE>
-__global__ __launch_bounds__(256) void spmm_sweep_fused_kernel(
+__global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
     const SpmmWsHeader* __restrict__ hdr, const float* __restrict__ B, float* __restrict__ partial,
@@ -945,7 +957,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_fused_kernel(
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t loff = lane * (FPL * 4);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t w = ((int64_t)d.block0 + blockIdx.x) * 4 + wave;
   // (the launch has whole workgroups: n_waves is a multiple of 4, checked by the launcher)
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != 1)
@@ -962,22 +974,22 @@ __global__ __launch_bounds__(256) void spmm_sweep_fused_kernel(
 
   vec acc = 0.f;
   TurnTaking turn(len);
-  for (int32_t e = 0; e < len; e += U) {
-    turn.at(e);
-    uint32_t c[U];
-    float v[U];
+  auto batch = [&](int32_t e, auto n) {
+    constexpr int N = decltype(n)::value;
+    uint32_t c[N];
+    float v[N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < N; ++u) {
       c[u] = cw[e + u];
       v[u] = vw[e + u];
     }
-    vec h[U];
+    vec h[N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
+    for (int u = 0; u < N; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
 #pragma unroll
-    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
+    for (int u = 0; u < N; ++u) asm volatile("" : "+v"(h[u]));
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < N; ++u) {
       acc += v[u] * h[u];
       if (c[u] >> 31) {
         vec* p = reinterpret_cast<vec*>(my + ((c[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
@@ -985,6 +997,14 @@ __global__ __launch_bounds__(256) void spmm_sweep_fused_kernel(
         acc = 0.f;
       }
     }
+  };
+  int32_t e = 0;
+  for (; e + U <= len; e += U) {
+    if constexpr (FPL < 4) turn.at(e);   // (at 256 columns two wavefronts share a SIMD)
+    batch(e, std::integral_constant<int, U>{});
+  }
+  if constexpr (U > 8) {
+    if (e < len) batch(e, std::integral_constant<int, 8>{});
   }
 
   // pieces of split rows to `partial`; T rows to memory if wanted
@@ -1004,7 +1024,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_fused_kernel(
 
   // tiles per pass: 4 at f = 256 (the LDS already limits a CU to two workgroups; 2 with three operand
   // terms per tile in registers), 1 below
-  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(lds_acc, piece_target, fa, wave, (int)lane);
+  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(lds_acc, piece_target, fa, (int64_t)d.block0 + blockIdx.x, wave, (int)lane);
 }
 
 // W (f_in x f_out, row-major fp32) -> [f_in / 8][NB] vectors of 8 bfloat16 (k fastest), NB = f_out
@@ -1178,7 +1198,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
     // (whole workgroups: the launcher only takes this form when n_waves is a multiple of 4 and
     // every wavefront owns 16 slots)
     __syncthreads();
-    sweep_dense_epilogue<LG * V, FUSE - 1, 1>(lds_acc, piece_target, fa, wave, (int)lane);
+    sweep_dense_epilogue<LG * V, FUSE - 1, 1>(lds_acc, piece_target, fa, blockIdx.x, wave, (int)lane);
   }
 }
 
@@ -1386,12 +1406,6 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   int piece_max = opt.piece > 0 ? opt.piece : (force == 1 ? 4096 : sweep_piece_default(nnz, f));
   if (piece_max < sweep_piece_floor(nnz, f)) piece_max = sweep_piece_floor(nnz, f);
   if (piece_max > 32768) piece_max = 32768;
-  const int64_t slab_bytes = opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : 4096) << 10;
-  int64_t S = slab_bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * slab_bytes) : kSweepMaxSlabs;
-  if (S < 8) S = 8;
-  if (S > kSweepMaxSlabs) S = kSweepMaxSlabs;
-  const int64_t width = ceil_div(k, S);
-
   // Row classification, the short-row CSR, the list of split rows and one record per piece are
   // made on the device (the long-row threshold is chosen there from the degree distribution);
   // the host gets the totals.
@@ -1417,9 +1431,27 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // splitting, 1905 swept; f = 48 3599 and 2560, f = 100 8135 and 5407, f = 200 13857 and 8598).
   // Wider operands (multiples of 64 above 128) can be taken as 128-wide slabs by the two-group
   // kernels (a last slab of 64 is served by the same streams): an option, see sagnn_spmm_options.
+  constexpr int kLocalPermille = 400;   // (between what the two kinds of order measure, see the windows below)
   const bool narrow_slabs = opt.slab_width == 128 && f > 128 && (f & 63) == 0 && opt.groups != 1;
+  // Columns 64 at a time, one row per load and one stream per wavefront, where the product costs what its L2 misses cost
+  // and the rows that are resident together want the same rows of B: an XCD holds 16384 rows of A then (256 workgroups of
+  // 16 KB), four times as many as at 256 columns, so a row of B is wanted that many times more often while they pass over
+  // it; sixteen rows in one stream stand at the same column to within 2 % of the stream where four streams of four rows
+  // are 4 % apart; and a load of one float per lane costs the address units 5 clocks (two floats 16, four 16).
+  // us as before (256 columns at once; two streams of 128; four of 64) and so, f = 256, 128, 64: 16 communities of 125 k
+  // vertices, 84 M entries 10999, 5557, 2866 -> 7131, 3524, 1837; of 62 k, 30 M 3719, 1834, 893 -> 2818, 1479, 852; one of
+  // the former as a row block 590, 279, 134 -> 424, 200, 105; random columns, 250 k vertices of 60 1864, 973, 501 -> 1265,
+  // 642, 329; 1 M of 40 5825, 2829, 1461 -> 5200, 2598, 1298.
+  // Not where the columns that neighbouring rows choose from fit the L2s anyway (communities of 19 k, f = 256: 1242 as
+  // before, 1412 so; of 5 k: 480, 536), where there are too many for a second use (a rank's rows), and not with hubs, whose
+  // rows hit in any case (233 k vertices of 489: 5627, 7060).
+  const bool local = tot.locality >= kLocalPermille;
+  const double span = (double)k * tot.span / 1000.0;
+  const bool col_groups = f >= 64 && (f & 63) == 0 && opt.groups == 0 && opt.slab_width == 0 && opt.sync_slabs <= 0 &&
+                          opt.barriers != 1 && opt.pace_ps_per_step <= 0 && span >= 40000.0 &&
+                          16384.0 * (double)nnz >= 0.5 * span * (double)m && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz;
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
-  if (opt.groups == 1 && f > 32) R = 1;
+  if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
   if (opt.groups != 2 && long_entries < 8 * k) {
     if (f <= 32) return SAGNN_OK;  // one row per instruction would leave most lanes idle: plain schedule
@@ -1453,8 +1485,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // 418 us, f = 64 1733 -> 1420, f = 256 6383 -> 5960; 300 k vertices f = 16 208 -> 94, f = 256 1834 -> 1468; 2 M of
   // 42 f = 256 11213 -> 10942.  Random labels lose (1 M R-MAT vertices of 100 entries: f = 32 930 -> 1192 us).
   // The line lies between what the two kinds measure, 50 to 100 permille and 700 to 900.
-  constexpr int kLocalPermille = 400;
-  const int64_t fw_max = sweep_widest_launch(f, narrow_slabs ? 128 : 256);
+  const int64_t fw_max = col_groups ? 64 : sweep_widest_launch(f, narrow_slabs ? 128 : 256);
   int64_t wg_per_cu = lds_resident_workgroups((size_t)(4ll * slots * sweep_lds_width(fw_max) * 4));
   if (wg_per_cu < 1) wg_per_cu = 1;
   int n_cus = 256;
@@ -1467,7 +1498,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const int64_t resident_waves = (int64_t)n_cus * wg_per_cu * 4;
   int64_t window = resident_waves * slots_used;              // pieces per window
   {
-    const int pct = opt.window_pct < 0 ? 0 : (opt.window_pct > 0 ? opt.window_pct : (tot.locality >= kLocalPermille ? 25 : 400));
+    const int pct = opt.window_pct < 0 ? 0 : (opt.window_pct > 0 ? opt.window_pct : (local ? (col_groups ? 12 : 25) : 400));
     window = pct <= 0 ? P : std::max<int64_t>(slots_used, window * pct / 100);
   }
   if (window > P) window = P;
@@ -1481,6 +1512,15 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
     const int64_t up = round_up((size_t)n_target_waves, (size_t)resident_waves);
     if (up + 64 <= L.max_waves - 8) n_target_waves = up;
   }
+  // (column groups without locality: not under 8192 rows a slab, which wide operands would get; 250 k vertices of 60, f = 256
+  // 1286 -> 1254 us, a row block of a partitioned graph 445 -> 424.  Finer slabs than 4 MB of the whole width for narrow
+  // operands would be up to 5 % faster, but a row's sum has a term per slab it has entries in, and more terms are further
+  // from exact: f = 64 8.7e-8 with 4 MB, 1.04e-7 with 2.)
+  const int64_t slab_bytes = opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : (col_groups && !local && f > 128 ? 32 * f : 4096)) << 10;
+  int64_t S = slab_bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * slab_bytes) : kSweepMaxSlabs;
+  if (S < 8) S = 8;
+  if (S > kSweepMaxSlabs) S = kSweepMaxSlabs;
+  const int64_t width = ceil_div(k, S);
   std::vector<int64_t> win_entries(1, long_entries);
   if (nwin > 1) {
     const int rc = sweep_plan_window_entries(ws, L, P, window, (int32_t)nwin, s, &win_entries);
@@ -1640,6 +1680,8 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.barriers = opt.barriers == 1 && sync_slabs > 0 ? 1 : 0;
   h.pace_ps_per_step = sync_slabs > 0 && !h.barriers ? opt.pace_ps_per_step : 0;
   h.max_slab = narrow_slabs && R == 2 ? 128 : 256;
+  h.col_slab = col_groups ? 64 : 0;
+  h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
   out->mean_steps = rec.scan.mean_steps;
   out->max_steps = rec.scan.max_steps;
   out->use_sweep = true;
@@ -1700,14 +1742,20 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s,
-                       reinterpret_cast<const uint32_t*>(ws + L.code),
-                       reinterpret_cast<const float*>(ws + L.vals),
-                       reinterpret_cast<const int32_t*>(ws + L.wave_base),
-                       reinterpret_cast<const int32_t*>(ws + L.piece_target),
-                       reinterpret_cast<const SpmmWsHeader*>(ws + L.header), B + col0, C + col0,
-                       reinterpret_cast<float*>(ws + L.partial), sd);
-    SAGNN_LAUNCH_CHECK();
+    // Column groups: two generations of wavefronts a launch, so that those that pass over B together begin together
+    // (2 M vertices in communities, f = 256: 8.45 ms in one launch per group, 7.1 so; as good as one generation each).
+    const unsigned per = d.col_slab > 0 && fw == d.col_slab && d.launch_waves >= 4 ? (unsigned)(d.launch_waves / 4) : blocks;
+    for (unsigned b0 = 0; b0 < blocks; b0 += per) {
+      sd.block0 = (int32_t)b0;
+      hipLaunchKernelGGL(kern, dim3(blocks - b0 < per ? blocks - b0 : per), dim3(256), lds, s,
+                         reinterpret_cast<const uint32_t*>(ws + L.code),
+                         reinterpret_cast<const float*>(ws + L.vals),
+                         reinterpret_cast<const int32_t*>(ws + L.wave_base),
+                         reinterpret_cast<const int32_t*>(ws + L.piece_target),
+                         reinterpret_cast<const SpmmWsHeader*>(ws + L.header), B + col0, C + col0,
+                         reinterpret_cast<float*>(ws + L.partial), sd);
+      SAGNN_LAUNCH_CHECK();
+    }
     return SAGNN_OK;
   };
   auto go_perm = [&](auto kern) -> int {   // (at most 32 KB of LDS)
@@ -1832,14 +1880,21 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s,
-                       reinterpret_cast<const uint32_t*>(ws + L.code),
-                       reinterpret_cast<const float*>(ws + L.vals),
-                       reinterpret_cast<const int32_t*>(ws + L.wave_base),
-                       reinterpret_cast<const int32_t*>(ws + L.piece_target),
-                       reinterpret_cast<const SpmmWsHeader*>(ws + L.header), B,
-                       reinterpret_cast<float*>(ws + L.partial), sd, fb);
-    SAGNN_LAUNCH_CHECK();
+    // (two generations a launch for column groups, as sweep_launch, but at 128 columns only, 1 M vertices in communities,
+    // 30 M entries: 1713 -> 1592 us.  At 64 and 256 the dense parts of workgroups that end together are left without
+    // gathers beside them: 803 -> 822, 3862 -> 4120.)
+    const unsigned per = f_in == 128 && d.col_slab > 0 && d.launch_waves >= 8 ? (unsigned)(d.launch_waves / 8) : blocks;
+    for (unsigned b0 = 0; b0 < blocks; b0 += per) {
+      sd.block0 = (int32_t)b0;
+      hipLaunchKernelGGL(kern, dim3(blocks - b0 < per ? blocks - b0 : per), dim3(256), lds, s,
+                         reinterpret_cast<const uint32_t*>(ws + L.code),
+                         reinterpret_cast<const float*>(ws + L.vals),
+                         reinterpret_cast<const int32_t*>(ws + L.wave_base),
+                         reinterpret_cast<const int32_t*>(ws + L.piece_target),
+                         reinterpret_cast<const SpmmWsHeader*>(ws + L.header), B,
+                         reinterpret_cast<float*>(ws + L.partial), sd, fb);
+      SAGNN_LAUNCH_CHECK();
+    }
     return SAGNN_OK;
   };
 #define SAGNN_SWF(FPL_)                                                                                      \

@@ -40,6 +40,7 @@ enum Stat : int {
   ST_MULTI_ROWS,
   ST_MULTI_PIECES,
   ST_LOCALITY,      // permille, see plan_locality_kernel
+  ST_SPAN,          // permille of the columns, see there
   ST_COUNT = 16
 };
 
@@ -98,13 +99,15 @@ __global__ void plan_rule_kernel(unsigned long long* __restrict__ stat, int64_t 
 // of every row, counted by column range (64 of them): the mean over the runs of half the sum of |share in the run -
 // share in all runs|.  0.05 to 0.1 where neighbouring rows share nothing but what all rows share (random labels,
 // power law or not), 0.89 for sixteen communities in order with one partner in twenty elsewhere.
+// And how many columns do neighbouring rows choose from?  1 / sum of share^2 ranges, the mean over the runs: 64 of 64
+// where they choose from all, 4.5 with sixteen communities.
 // One workgroup, all samples of a row in flight: two chains of three dependent loads.
 constexpr int kLocRuns = 32, kLocBins = 64, kLocSamples = 32;
 __global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                                              int64_t m, int64_t nnz, int64_t k,
                                                              unsigned long long* __restrict__ stat) {
   __shared__ int hist[kLocRuns][kLocBins];
-  __shared__ float diff[kLocRuns];
+  __shared__ float diff[kLocRuns], span[kLocRuns];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = threadIdx.x; i < kLocRuns * kLocBins; i += 1024) hist[i / kLocBins][i % kLocBins] = 0;
   __syncthreads();
@@ -138,13 +141,21 @@ __global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __re
   for (int j = wave; j < kLocRuns; j += 16) {
     const int mine = hist[j][lane], n = sum(mine);
     const float t = sum(n > 0 ? fabsf((float)mine / (float)n - share) : 0.f);
-    if (lane == 0) diff[j] = 0.5f * t;
+    const float q = sum((float)mine * (float)mine);
+    if (lane == 0) {
+      diff[j] = 0.5f * t;
+      span[j] = n > 0 ? (float)n * (float)n / (q * kLocBins) : 0.f;
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int j = 0; j < kLocRuns; ++j) t += diff[j];
+    float t = 0.f, w = 0.f;
+    for (int j = 0; j < kLocRuns; ++j) {
+      t += diff[j];
+      w += span[j];
+    }
     stat[ST_LOCALITY] = (unsigned long long)(t * (1000.f / kLocRuns));
+    stat[ST_SPAN] = (unsigned long long)(w * (1000.f / kLocRuns));
   }
 }
 
@@ -624,6 +635,7 @@ int sweep_plan_rows(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m,
   out->has_empty = h[ST_EMPTY] != 0;
   out->min_long = (int32_t)h[ST_MINLONG];
   out->locality = (int32_t)h[ST_LOCALITY];
+  out->span = (int32_t)h[ST_SPAN];
   out->pieces = (int64_t)h[ST_PIECES];
   out->short_rows = (int64_t)h[ST_SHORT_ROWS];
   out->short_entries = (int64_t)h[ST_SHORT_ENTRIES];

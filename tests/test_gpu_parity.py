@@ -518,6 +518,51 @@ def test_spmm_rows_moved_to_cache_lines(f, n, sweep, monkeypatch):
             assert_close(got, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} m={m} k={k}")
 
 
+@pytest.mark.parametrize("f,n,deg,parts", [(64, 300_000, 20, 1), (128, 150_000, 24, 1), (192, 60_000, 60, 1), (256, 60_000, 60, 1),
+                                           (64, 200_000, 20, 4), (256, 180_000, 20, 4)])
+def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
+    """Matrices without hubs whose rows of B are wanted several times by rows that are resident together: 64 columns a
+    launch, several launches for many rows.  Rows of B with gaps, an operand narrower than the workspace was prepared for
+    (one that is a multiple of 64 and one that is not), accumulation, and the layer that needs whole rows of A H."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(f + n)
+    count = torch.randint(deg - 6, deg + 7, (n,), device="cuda", generator=gen)
+    count[::977] = 0
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(count, 0)
+    nnz, part = int(rp[-1]), n // parts
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), count)
+    col = row // part * part + torch.randint(part, (nnz,), device="cuda", generator=gen)
+    col = torch.where(torch.rand(nnz, device="cuda", generator=gen) < 0.05, torch.randint(n, (nnz,), device="cuda", generator=gen), col)
+    ci = (torch.sort(row * n + col.clamp(max=n - 1))[0] - row * n).to(torch.int32)
+    v = torch.randn(nnz, device="cuda", generator=gen)
+    wide = torch.randn(n, f + 12, device="cuda", generator=gen)
+    B = wide[:, :f]
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 1 and ws.info()["groups"] == 1
+    A, Aabs = (torch.sparse_csr_tensor(rp.long(), ci.long(), x.double(), (n, n)) for x in (v, v.abs()))
+    C0 = torch.randn(n, f, device="cuda", generator=gen)
+    for w in {f, 64, 52}:
+        ref, zabs = A @ B[:, :w].double(), Aabs @ B[:, :w].double().abs()
+        for C in (None, C0[:, :w].contiguous()):
+            want, scale = (ref, zabs) if C is None else (ref + C.double(), zabs + C.double().abs())
+            got = sagnn.spmm_csr_tallskinny(rp, ci, v, B[:, :w], C=C, accumulate=C is not None, ws=ws)
+            err = (got.double() - want).abs() - RTOL_SPMM * scale
+            assert float(err.max()) <= 1e-30, f"f={f} w={w} accumulate={C is not None}"
+    if f == 192:
+        return
+    W = torch.randn(f, 40, device="cuda", generator=gen) / f ** 0.5
+    T, Z, H = sagnn.gcn_layer_fwd(rp, ci, v, B, W, ws=ws)
+    assert sagnn.gcn_layer_fwd_form(ws, f, 40) == 2
+    _, Z2, H2 = sagnn.gcn_layer_fwd(rp, ci, v, B, W, ws=ws, want_t=False)
+    scale = (Aabs @ B.double().abs()) @ W.double().abs()
+    want = (A @ B.double()) @ W.double()
+    for z, h in ((Z, H), (Z2, H2)):
+        # the rows of A H, then f products and sums in 32 bits: both within the forward error of their sums
+        assert float(((z.double() - want).abs() - (RTOL_SPMM + f * 2.0 ** -24) * scale).max()) <= 1e-30
+        assert torch.equal(h, torch.relu(z))
+
+
 @pytest.mark.parametrize("f,n,more", [(24, 270_000, 280_000), (60, 180_000, 190_000)])
 def test_spmm_workspace_of_a_matrix_with_more_rows_serves_one_with_fewer(f, n, more):
     """With more rows the copy of B to aligned rows does not pay and the workspace has no room for it; the matrix with
