@@ -554,6 +554,7 @@ struct SweepDims {
   int32_t fw;           // floats per row of this launch
   float pace_ticks;     // pacing: 100 MHz ticks per stream step (0: none)
   int32_t block0;       // first workgroup of this launch (one row per load)
+  int32_t turn;         // steps between two priorities, at most (TurnTaking)
 };
 
 // Barrier between two intervals of the sweep for the workgroups that run at the same time on
@@ -660,20 +661,20 @@ struct SegmentSum {
 // generation the six wavefronts of a SIMD stood 0.10 to 0.29 of a stream apart in order of their age, so the L2 held the
 // rows of B that the first of them wanted and the last fetched them again.  A wavefront goes down through the four
 // priorities as it walks, one per `stride` steps, and begins again at the top: of those less than four strides apart the
-// one behind goes first.  64 steps a stride (power-law streams of 1600 to 4600 steps: 32 to 128 within 1 %, 8 and none
-// 4 to 6 % slower), a sixteenth of a shorter stream.  2.45 M vertices, 125 M entries: f = 128 4363 -> 4132 us, f = 64
-// 2705 -> 2322; 233 k, 114 M, f = 128 2455 -> 2328; partitioned 2 M, 84 M, f = 128 5588 -> 5376.  No gain and not used
-// with sixteen groups, whose wavefronts wait for the address units.  Progress counted in memory, so that the order holds
-// beyond four strides, costs more than it gives: an atomic per level and wavefront, 4.7 ms and more for the first figure.
+// one behind goes first.  A sixteenth of the stream a stride, at most 32 steps where B fits the memory-side cache and 128
+// where it does not (turn_steps).  2.45 M vertices, 125 M entries: f = 128 4363 -> 4132 us, f = 64 2705 -> 2322; 233 k,
+// 114 M, f = 128 2455 -> 2328; partitioned 2 M, 84 M, f = 128 5588 -> 5376.  No gain and not used with sixteen groups, whose
+// wavefronts wait for the address units.  Progress counted in memory, so that the order holds beyond four strides, costs
+// more than it gives: an atomic per level and wavefront, 4.7 ms and more for the first figure.
 struct TurnTaking {
   int32_t next, stride;
   uint32_t level;
-  __device__ __forceinline__ explicit TurnTaking(int32_t steps) : next(0), level(0) {
+  __device__ __forceinline__ TurnTaking(int32_t steps, int32_t longest) : next(0), level(0) {
     stride = (steps >> 4) & ~7;
-    stride = stride > 64 ? 64 : (stride < 8 ? 8 : stride);
+    stride = stride > longest ? longest : (stride < 8 ? 8 : stride);
   }
-  __device__ __forceinline__ void at(int32_t e) {   // before the batch that begins with step e
-    if (e < next) return;
+  __device__ __forceinline__ void at(int32_t e) {   // before the batch that begins with step e, e a multiple of 8
+    if (e != next) return;
     next += stride;
     switch (level++ & 3u) {
       case 0: __builtin_amdgcn_s_setprio(3); break;
@@ -683,6 +684,64 @@ struct TurnTaking {
     }
   }
 };
+
+// One row per load: a wavefront's stream, `len` steps (a multiple of U), into its accumulator rows `my`.
+// FPL == 4: the words of the next batch are requested before this one's rows are waited for, two sets of scalar registers
+// in turn.  They come from HBM, and with the eight wavefronts that 256 columns leave a CU nobody else hides it: 2.45 M
+// vertices, 125 M entries, f = 256 9544 -> 8759 us, 233 k, 114 M 5669 -> 4650.  Not at fewer columns, where four times as
+// many wavefronts do and those that run ahead cost more misses (250 k vertices of 60, f = 64: 332 -> 409; f = 128 the same).
+template <int FPL, int U, bool BUF, bool TWO, bool TURN>
+__device__ __forceinline__ void walk_stream(const uint32_t* __restrict__ cw, const float* __restrict__ vw, int32_t len,
+                                            __amdgpu_buffer_rsrc_t rs, const float* __restrict__ B, const SweepDims& d, uint32_t loff,
+                                            float* __restrict__ my, int kRow) {
+  using vec = typename Vec<FPL>::T;
+  constexpr bool kAhead = FPL == 4;
+  SegmentSum<vec, TWO> sum;
+  TurnTaking turn(len, d.turn);
+  auto words = [&](int32_t at, uint32_t (&c)[U], float (&v)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      c[u] = cw[at + u];
+      v[u] = vw[at + u];
+    }
+  };
+  auto batch = [&](int32_t e, uint32_t (&c)[U], float (&v)[U], uint32_t (&cn)[U], float (&vn)[U]) {
+    if constexpr (TURN) turn.at(e);
+    if constexpr (!kAhead) words(e, c, v);
+    vec h[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
+    if constexpr (kAhead) {
+      __builtin_amdgcn_sched_barrier(0);
+      words(e + U < len ? e + U : e, cn, vn);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sum.add(u, v[u], h[u]);
+      if (c[u] >> 31) {   // last entry of a (piece, slab) segment: fold into the piece's LDS row
+        vec* p = reinterpret_cast<vec*>(my + ((c[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
+        *p += sum.take();
+      }
+    }
+    sum.batch_ends();
+  };
+  uint32_t c0[U], c1[U];
+  float v0[U], v1[U];
+  if constexpr (kAhead) {
+    if (len > 0) words(0, c0, v0);
+    for (int32_t e = 0; e < len; e += U) {
+      batch(e, c0, v0, c1, v1);
+      e += U;
+      if (e >= len) break;
+      batch(e, c1, v1, c0, v0);
+    }
+  } else {
+    for (int32_t e = 0; e < len; e += U) batch(e, c0, v0, c0, v0);
+  }
+}
 
 // ODD: rows of any multiple of 4 floats instead of the kernel's full width.  The lanes beyond the end of the row work
 // on its last FPL floats a second time: same addresses, same values, so neither loads nor accumulator updates nor
@@ -714,40 +773,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
   const float* __restrict__ vw = vals + base;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
-  SegmentSum<vec, ODD && FPL <= 2> sum;
-  TurnTaking turn(len);
-  auto batch = [&](int32_t e, auto n) {
-    constexpr int N = decltype(n)::value;
-    uint32_t c[N];
-    float v[N];
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      c[u] = cw[e + u];
-      v[u] = vw[e + u];
-    }
-    vec h[N];
-#pragma unroll
-    for (int u = 0; u < N; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
-#pragma unroll
-    for (int u = 0; u < N; ++u) asm volatile("" : "+v"(h[u]));
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      sum.add(u, v[u], h[u]);
-      if (c[u] >> 31) {   // last entry of a (piece, slab) segment: fold into the piece's LDS row
-        vec* p = reinterpret_cast<vec*>(my + ((c[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
-        *p += sum.take();
-      }
-      if ((u & 7) == 7) sum.batch_ends();
-    }
-  };
-  int32_t e = 0;
-  for (; e + U <= len; e += U) {
-    turn.at(e);
-    batch(e, std::integral_constant<int, U>{});
-  }
-  if constexpr (U > 8) {
-    if (e < len) batch(e, std::integral_constant<int, 8>{});
-  }
+  walk_stream<FPL, U, BUF, ODD && FPL <= 2, true>(cw, vw, len, rs, B, d, loff, my, kRow);
 
 #pragma unroll 1
   for (int s = 0; s < d.slots; ++s) {
@@ -972,40 +998,8 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
   const float* __restrict__ vw = vals + base;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
-  vec acc = 0.f;
-  TurnTaking turn(len);
-  auto batch = [&](int32_t e, auto n) {
-    constexpr int N = decltype(n)::value;
-    uint32_t c[N];
-    float v[N];
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      c[u] = cw[e + u];
-      v[u] = vw[e + u];
-    }
-    vec h[N];
-#pragma unroll
-    for (int u = 0; u < N; ++u) h[u] = load_row<FPL, BUF>(rs, B, c[u] & kColMask, loff, d.row_bytes, d.ldb);
-#pragma unroll
-    for (int u = 0; u < N; ++u) asm volatile("" : "+v"(h[u]));
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      acc += v[u] * h[u];
-      if (c[u] >> 31) {
-        vec* p = reinterpret_cast<vec*>(my + ((c[u] >> kSweepColBits) & (kSweepSlots - 1)) * kRow);
-        *p += acc;
-        acc = 0.f;
-      }
-    }
-  };
-  int32_t e = 0;
-  for (; e + U <= len; e += U) {
-    if constexpr (FPL < 4) turn.at(e);   // (at 256 columns two wavefronts share a SIMD)
-    batch(e, std::integral_constant<int, U>{});
-  }
-  if constexpr (U > 8) {
-    if (e < len) batch(e, std::integral_constant<int, 8>{});
-  }
+  // (turns: at 256 columns only two wavefronts share a SIMD)
+  walk_stream<FPL, U, BUF, false, FPL < 4>(cw, vw, len, rs, B, d, loff, my, kRow);
 
   // pieces of split rows to `partial`; T rows to memory if wanted
 #pragma unroll 1
@@ -1055,7 +1049,7 @@ __global__ __launch_bounds__(256) void sweep_pack_w_kernel(const float* __restri
 // FUSE: 0 the product alone; 1 / 2 / 3 the layer form: the kernel ends with the dense transform of the
 // workgroup's rows (fp32 / bfloat16 / three-term operands, see sweep_dense_epilogue) instead of storing T (C is
 // then only written if the caller wants T as a by-product: fa.T).
-template <int V, int R, int U, bool BUF, int FUSE = 0, bool ODD = false>
+template <int V, int R, int U, bool BUF, int FUSE = 0, bool ODD = false, bool AHEAD = true>
 __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1107,53 +1101,75 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   const bool paced = d.pace_ticks > 0.f && n_iv > 1;
   const uint64_t t_start = paced ? wall_clock64() : 0ull;
 
-  TurnTaking turn(steps);
+  TurnTaking turn(steps, d.turn);
+  // Words of H steps in scalar registers, requested while the rows of the steps before are on their way: they come from
+  // HBM, and waiting for them at the head of a batch left the address units idle.  With four groups half a batch, a whole
+  // one does not fit the scalar registers (1547 and 1947 us for 1723 before: 233 k vertices, 114 M entries, f = 64).
+  // f = 128 2313 -> 2102; 2.45 M, 125 M entries 4200 -> 4022.  (Before the wavefronts took turns this cost more misses
+  // than it gave.  One vector load per batch with DPP broadcasts instead, half the vector instructions: 2671, 4196;
+  // vector loads return in order, so every row waits for the words before it.)
+  // AHEAD false: at 128 columns of more than 1 GB, where HBM gives all it has and running ahead only costs misses (the
+  // step of the 2.45 M-vertex graph 5593 us without, 5702 and 5741 with; 1.2 M vertices, 614 MB 1856 without, 1739 with).
+  constexpr int kParts = R == 4 ? 2 : 1, H = U / kParts;
+  uint32_t c[H][R];
+  float v[H][R];
+  auto words = [&](int32_t at) {
+#pragma unroll
+    for (int i = 0; i < H; ++i)
+#pragma unroll
+      for (int g = 0; g < R; ++g) {
+        c[i][g] = cw[(at + i) * R + g];
+        v[i][g] = vw[(at + i) * R + g];
+      }
+  };
+  if (AHEAD && steps > 0) words(0);
   int32_t e = 0;
   for (int iv = 0; iv < n_iv; ++iv) {
     SegmentSum<vec, ODD && R == 4> sum;   // (what the padding of the interval before left is not summed: see spmm_sweep_perm_kernel)
     const int32_t e_end = iv + 1 < n_iv ? so[iv + 1] : steps;
     for (; e < e_end; e += U) {
       turn.at(e);
-      uint32_t c[U][R];
-      float v[U][R];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int g = 0; g < R; ++g) {
-          c[u][g] = cw[(e + u) * R + g];
-          v[u][g] = vw[(e + u) * R + g];
-        }
       uint32_t mc[U];
       float mv[U];
       vec h[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        mc[u] = c[u][0];
-        mv[u] = v[u][0];
-        if constexpr (BUF) {
-          uint32_t off = (c[u][0] & kColMask) * d.row_bytes;
+      for (int p = 0; p < kParts; ++p) {
+        if constexpr (!AHEAD) words(e + p * H);
 #pragma unroll
-          for (int g = 1; g < R; ++g)
-            if (gid == (uint32_t)g) {
-              mc[u] = c[u][g];
-              mv[u] = v[u][g];
-              off = (c[u][g] & kColMask) * d.row_bytes;
-            }
-          off += loff;
-          if constexpr (V == 1) h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-          else if constexpr (V == 2) h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
-          else h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-        } else {
-          const char* rowp = reinterpret_cast<const char*>(B + (int64_t)(c[u][0] & kColMask) * d.ldb);
+        for (int i = 0; i < H; ++i) {
+          const int u = p * H + i;
+          mc[u] = c[i][0];
+          mv[u] = v[i][0];
+          if constexpr (BUF) {
+            uint32_t off = (c[i][0] & kColMask) * d.row_bytes;
 #pragma unroll
-          for (int g = 1; g < R; ++g)
-            if (gid == (uint32_t)g) {
-              mc[u] = c[u][g];
-              mv[u] = v[u][g];
-              rowp = reinterpret_cast<const char*>(B + (int64_t)(c[u][g] & kColMask) * d.ldb);
-            }
-          h[u] = *reinterpret_cast<const vec*>(rowp + loff);
+            for (int g = 1; g < R; ++g)
+              if (gid == (uint32_t)g) {
+                mc[u] = c[i][g];
+                mv[u] = v[i][g];
+                off = (c[i][g] & kColMask) * d.row_bytes;
+              }
+            off += loff;
+            if constexpr (V == 1) h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+            else if constexpr (V == 2) h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+            else h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+          } else {
+            const char* rowp = reinterpret_cast<const char*>(B + (int64_t)(c[i][0] & kColMask) * d.ldb);
+#pragma unroll
+            for (int g = 1; g < R; ++g)
+              if (gid == (uint32_t)g) {
+                mc[u] = c[i][g];
+                mv[u] = v[i][g];
+                rowp = reinterpret_cast<const char*>(B + (int64_t)(c[i][g] & kColMask) * d.ldb);
+              }
+            h[u] = *reinterpret_cast<const vec*>(rowp + loff);
+          }
         }
+        // the words after these, while the rows are on their way (the last ones again at the end of the stream)
+        __builtin_amdgcn_sched_barrier(0);
+        const int32_t en = e + (p + 1) * H;
+        if constexpr (AHEAD) words(en < steps ? en : e);
+        __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) asm volatile("" : "+v"(h[u]));
@@ -1266,7 +1282,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     cb[q] = steps > 0 ? cw[q * 64 + lane] : 0u;
     vb[q] = steps > 0 ? vw[q * 64 + lane] : 0.f;
   }
-  TurnTaking turn(steps);
+  TurnTaking turn(steps, d.turn);
   for (int32_t e = 0; e < steps; e += 8) {
     if constexpr (SL > 1) turn.at(e);
     // the next iteration's stream words are requested before this one's gathers are waited for
@@ -1710,6 +1726,13 @@ int resident_workgroups(const void* kern, size_t lds) {
 }  // namespace
 
 namespace {
+// Strides of 32, 64 and 128 steps on three matrices in turn: 233 k vertices f = 128 (119 MB) 1992, 2057, 2101 us; 1 M f = 64
+// (256 MB) 710, 716, 711, f = 128 1320, 1329, 1299; 1.2 M f = 128 1740, 1751, 1765; 2.45 M f = 64 (627 MB) 2230, 2249, 2156,
+// f = 128 4155, 4240, 4127.
+int32_t turn_steps(uint32_t kmax, int32_t fw) { return ((int64_t)kmax + 1) * fw * 4 > (256ll << 20) ? 128 : 32; }
+}  // namespace
+
+namespace {
 // lane-group kernels: fuse = 0 product, 1 / 2 / 3 layer form with fp32 / bfloat16 / three-term operands
 template <int V, int R, bool BUF>
 auto group_kernel_of(int fuse) {
@@ -1737,6 +1760,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   const unsigned blocks = (unsigned)ceil_div(d.n_waves, 4);
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
   sd.fw = fw;
+  sd.turn = turn_steps(kmax, fw);
   const size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
@@ -1819,6 +1843,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     return buf ? go_perm(spmm_sweep_perm_kernel<8, true, true>) : go_perm(spmm_sweep_perm_kernel<8, false, true>);
   }
   if (d.groups == 2) {   // half a wavefront per row
+    if (fw == 128 && !fuse && buf && ((int64_t)kmax + 1) * fw * 4 > (1ll << 30)) return go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, false, false>);
     if (fw == 128) return buf ? go_group(group_kernel_of<4, 2, true>(fuse)) : go_group(group_kernel_of<4, 2, false>(fuse));
     if (fw == 64) return buf ? go_group(group_kernel_of<2, 2, true>(fuse)) : go_group(group_kernel_of<2, 2, false>(fuse));
     if (fw > 128 || fuse) return SAGNN_EINVAL;
@@ -1861,6 +1886,7 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   SweepDims sd{};
   sd.n_waves = d.n_waves; sd.ldb = ldb; sd.ldc = f_in; sd.f_total = f_in;
   sd.generation = d.generation; sd.col0 = 0; sd.accumulate = 0; sd.slots = kSweepSlots;
+  sd.turn = turn_steps(kmax, f_in);
   sd.b_bytes = 0;
   const bool buf = buffer_addressable(kmax, ldb, f_in, &sd.b_bytes);
   sd.row_bytes = (uint32_t)(ldb * 4);
