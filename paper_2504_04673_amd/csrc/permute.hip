@@ -57,8 +57,8 @@ __global__ __launch_bounds__(kThreads) void order_kernel(const uint32_t* __restr
   }
 }
 
-// Checks of the two maps, and the row lengths of B.  err[1] = 1 unless map is a permutation of [0, n) (every value
-// in range and seen exactly once); err[2] = 1 if the rows of A cannot be permuted one by one (a row longer than
+// Checks of the two maps, the row lengths of B, and the inverse map: seen[p] = 1 + the row of A that becomes row p.
+// err[1] = 1 unless map is a permutation of [0, n) (every value in range and seen exactly once); err[2] = 1 if the rows of A cannot be permuted one by one (a row longer than
 // kRowSortMax, or rowptr is no CSR row pointer).
 constexpr int kRowSortMax = 512;
 __global__ __launch_bounds__(kThreads) void check_perm_kernel(const int32_t* __restrict__ map,
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void check_perm_kernel(const int32_t* __r
     if (p < 0 || p >= n) {
       err[1] = 1;
     } else {
-      if (atomicAdd(&seen[p], 1) != 0) err[1] = 1;
+      if (atomicExch(&seen[p], (int32_t)i + 1) != 0) err[1] = 1;
       len[p] = (int32_t)(e - b);
     }
   }
@@ -140,12 +140,58 @@ __global__ __launch_bounds__(kThreads) void scan_add_kernel(const int32_t* __res
   else if (i == n) rowptr[n] = (int32_t)nnz;
 }
 
-// Rows of B from rows of A.  A wavefront ranks the relabelled columns of a row by counting the smaller ones
-// (equal ones: the earlier ones), every column handed to all lanes once by a lane read, and stores the row in
-// that order.  Bound by the latency of its dependent loads (row pointer, columns, new ids), so a wavefront has
-// four rows in flight while they fit 64 lanes each.  There the key carries the lane in its low bits (n <= 2^26), which
-// makes equal columns different and a comparison one instruction.  21 M entries in 500 k rows: 0.30 ms, 0.40 ms
-// with the lane compared apart; relabelling and sorting them twice through memory took 1.4 ms.
+// Ascending bitonic sort over the 64 lanes.  Partners at 1, 2, 4 and 8 lanes come by DPP (two steps for 4), at 16 and 32
+// by the row swaps, so no step goes through the LDS: about 75 instructions, where counting the smaller keys takes three
+// for every entry of the row.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+template <int J>
+__device__ __forceinline__ void sort_step(uint32_t& x, bool keep_smaller) {
+  uint32_t lo, hi;
+  if constexpr (J <= 8) {
+    uint32_t y;
+    if constexpr (J == 1) y = dpp_move<0xB1>(x);                          // quad_perm:[1,0,3,2]
+    else if constexpr (J == 2) y = dpp_move<0x4E>(x);                     // quad_perm:[2,3,0,1]
+    else if constexpr (J == 4) y = dpp_move<0x1B>(dpp_move<0x141>(x));    // lane 7 - i of eight, then 3 - i of four
+    else y = dpp_move<0x128>(x);                                          // row_ror:8
+    lo = x < y ? x : y;
+    hi = x < y ? y : x;
+  } else {
+    // both rows (halves) of a pair get the keys of the lower one in `a`, of the upper one in `b`
+    const auto ab = J == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false) : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const uint32_t a = ab[0], b = ab[1];
+    lo = a < b ? a : b;
+    hi = a < b ? b : a;
+  }
+  x = keep_smaller ? lo : hi;
+}
+template <int K, int J>
+__device__ __forceinline__ void sort_merge(uint32_t& x, int lane) {
+  if constexpr (J > 0) {
+    sort_step<J>(x, ((lane & J) == 0) == ((lane & K) == 0));
+    sort_merge<K, J / 2>(x, lane);
+  }
+}
+__device__ __forceinline__ void sort_lanes(uint32_t& x, int lane) {
+  sort_merge<2, 1>(x, lane);
+  sort_merge<4, 2>(x, lane);
+  sort_merge<8, 4>(x, lane);
+  sort_merge<16, 8>(x, lane);
+  sort_merge<32, 16>(x, lane);
+  sort_merge<64, 32>(x, lane);
+}
+
+// Rows of B from rows of A, in the order of B: rows that lie together are written together (rows of A are read where
+// they are; the other way round every row's ends were partly written lines).  A wavefront relabels a row's columns and
+// sorts them (a row of up to 64) or ranks them by counting the smaller ones, equal ones the earlier ones first.  Bound by
+// the latency of its dependent loads (old row, row pointer, columns, new ids), so a wavefront has four rows in flight
+// while they fit 64 lanes each.  There the key carries the lane in its low bits (n <= 2^26), which makes equal columns
+// different and finds the value.  21 M entries in 500 k rows: 300 us by ranks and in the order of A, 265 so, 236 with eight
+// wavefronts per SIMD (the registers that rows of 257 to 512 entries would like are spilled there: no slower); in the
+// order of A 245.  27 M requests to the L2s, most of them the new ids of random columns, at 85 % of the rate gathers reach.
+// Relabelling and sorting the entries twice through memory took 1.4 ms.
 // Nothing is done where check_perm_kernel found a reason against it (the host looks afterwards).
 template <int K>
 __device__ __forceinline__ void permute_row(const int32_t* __restrict__ colidx, const float* __restrict__ val,
@@ -189,10 +235,11 @@ __device__ __forceinline__ void permute_row(const int32_t* __restrict__ colidx, 
     }
 }
 
-__global__ __launch_bounds__(kThreads) void permute_rows_kernel(const int32_t* __restrict__ rowptr,
+__global__ __launch_bounds__(kThreads, 8) void permute_rows_kernel(const int32_t* __restrict__ rowptr,
                                                                 const int32_t* __restrict__ colidx,
                                                                 const float* __restrict__ val, int64_t n,
                                                                 const int32_t* __restrict__ inv,
+                                                                const int32_t* __restrict__ seen,
                                                                 const int32_t* __restrict__ rowptr_p,
                                                                 int32_t* __restrict__ colidx_p,
                                                                 float* __restrict__ val_p, int32_t* __restrict__ err) {
@@ -200,26 +247,25 @@ __global__ __launch_bounds__(kThreads) void permute_rows_kernel(const int32_t* _
   if (err[1] | err[2]) return;
   const int lane = threadIdx.x & 63;
   const int64_t wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6));
-  const int64_t r0 = wave * R;
+  const int64_t p0 = wave * R;
   int64_t b[R], out[R];
   int d[R], longest = 0;
 #pragma unroll
   for (int t = 0; t < R; ++t) {
-    const int64_t r = r0 + t < n ? r0 + t : n - 1;
+    const int64_t p = p0 + t < n ? p0 + t : n - 1;
+    const int64_t r = (int64_t)seen[p] - 1;      // (in [0, n): check_perm_kernel found a permutation)
     b[t] = rowptr[r];
-    d[t] = r0 + t < n ? (int)(rowptr[r + 1] - b[t]) : 0;
+    d[t] = p0 + t < n ? (int)(rowptr[r + 1] - b[t]) : 0;
     longest = d[t] > longest ? d[t] : longest;
-    out[t] = rowptr_p[inv[r]];
+    out[t] = rowptr_p[p];
   }
   if (longest <= 64 && n <= (1 << 26)) {
     uint32_t key[R];
     float v[R];
-    int rank[R];
 #pragma unroll
     for (int t = 0; t < R; ++t) {
-      key[t] = 0xFFFFFFFFu;
+      key[t] = 0xFFFFFFC0u | (uint32_t)lane;     // (lanes past the end of a row: behind all keys)
       v[t] = 0.f;
-      rank[t] = 0;
       if (lane < d[t]) {
         const int32_t c = colidx[b[t] + lane];
         v[t] = val[b[t] + lane];
@@ -227,19 +273,16 @@ __global__ __launch_bounds__(kThreads) void permute_rows_kernel(const int32_t* _
         else err[0] = 1;
       }
     }
-    for (int l = 0; l < longest; ++l) {   // (lanes past the end of a row hold the largest key: they count for nobody)
 #pragma unroll
-      for (int t = 0; t < R; ++t) {
-        const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key[t], l);
-        rank[t] += kj < key[t];
+    for (int t = 0; t < R; ++t) sort_lanes(key[t], lane);
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+      const float moved = __shfl(v[t], (int)(key[t] & 63u), 64);
+      if (lane < d[t]) {
+        colidx_p[out[t] + lane] = (int32_t)(key[t] >> 6);
+        val_p[out[t] + lane] = moved;
       }
     }
-#pragma unroll
-    for (int t = 0; t < R; ++t)
-      if (lane < d[t]) {
-        colidx_p[out[t] + rank[t]] = (int32_t)(key[t] >> 6);
-        val_p[out[t] + rank[t]] = v[t];
-      }
     return;
   }
 #pragma unroll 1
@@ -251,13 +294,14 @@ __global__ __launch_bounds__(kThreads) void permute_rows_kernel(const int32_t* _
   }
 }
 
-__global__ __launch_bounds__(kThreads) void zero_i32_kernel(int32_t* __restrict__ a, int64_t n) {
+__global__ __launch_bounds__(kThreads) void zero_i32_kernel(int32_t* __restrict__ a, int64_t n, int32_t* __restrict__ b, int m) {
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) a[i] = 0;
+  if (blockIdx.x == 0 && (int)threadIdx.x < m) b[threadIdx.x] = 0;
 }
 
 struct PermuteWs {
-  int32_t *ci_a, *rp_b, *ci_b, *seen, *err;
+  int32_t *ci_a, *rp_b, *ci_b, *seen, *tilesum, *err;
   float* va_b;
   char* tws;
   size_t tws_bytes, bytes;
@@ -278,6 +322,7 @@ int carve_permute(void* base, int64_t n, int64_t nnz, PermuteWs* w) {
   w->ci_b = reinterpret_cast<int32_t*>(take(4 * e));
   w->va_b = reinterpret_cast<float*>(take(4 * e));
   w->seen = reinterpret_cast<int32_t*>(take(4 * (size_t)(n > 0 ? n : 1)));
+  w->tilesum = reinterpret_cast<int32_t*>(take(4 * (size_t)(ceil_div(n > 0 ? n : 1, kScanTile) + 1)));
   w->err = reinterpret_cast<int32_t*>(take(16));
   w->tws = take(tb);
   w->tws_bytes = tb;
@@ -353,9 +398,7 @@ SAGNN_EXPORT int spmm_csr_permute_symmetric(const int32_t* d_rowptr, const int32
   if (ws_bytes < w.bytes) return SAGNN_ECAPACITY;
   if (n == 0 && nnz > 0) return SAGNN_EFORMAT;   // no column is in range
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(zero_i32_kernel, grid_for(n + 4), dim3(kThreads), 0, s, w.seen, n);
-  SAGNN_LAUNCH_CHECK();
-  hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(kThreads), 0, s, w.err, 4);
+  hipLaunchKernelGGL(zero_i32_kernel, grid_for(n), dim3(kThreads), 0, s, w.seen, n, w.err, 4);
   SAGNN_LAUNCH_CHECK();
   if (n > 0) {
     hipLaunchKernelGGL(check_perm_kernel, grid_for(n), dim3(kThreads), 0, s, d_inv, d_rowptr, n, nnz, w.seen, w.rp_b, w.err);
@@ -364,16 +407,16 @@ SAGNN_EXPORT int spmm_csr_permute_symmetric(const int32_t* d_rowptr, const int32
   int32_t h_err[4] = {0, 0, 0, 0};
   {
     const int64_t ntiles = ceil_div(n > 0 ? n : 1, kScanTile);
-    hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, s, w.rp_b, n, d_rowptr_p, w.seen);
+    hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, s, w.rp_b, n, d_rowptr_p, w.tilesum);
     SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kThreads), 0, s, w.seen, ntiles);
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kThreads), 0, s, w.tilesum, ntiles);
     SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)ceil_div(n + 1, kThreads)), dim3(kThreads), 0, s, w.seen, n, nnz,
+    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)ceil_div(n + 1, kThreads)), dim3(kThreads), 0, s, w.tilesum, n, nnz,
                        d_rowptr_p);
     SAGNN_LAUNCH_CHECK();
     if (nnz > 0 && n > 0) {
       hipLaunchKernelGGL(permute_rows_kernel, dim3((unsigned)ceil_div(n, 4 * (kThreads / 64))), dim3(kThreads), 0, s,
-                         d_rowptr, d_colidx, d_val, n, d_inv, d_rowptr_p, d_colidx_p, d_val_p, w.err);
+                         d_rowptr, d_colidx, d_val, n, d_inv, w.seen, d_rowptr_p, d_colidx_p, d_val_p, w.err);
       SAGNN_LAUNCH_CHECK();
     }
     SAGNN_HIP(hipMemcpyAsync(h_err, w.err, sizeof(h_err), hipMemcpyDeviceToHost, s));
