@@ -33,9 +33,12 @@ struct FlatDims {
   int32_t f, accumulate;
 };
 
+// (no short cuts: all fields are read at once instead of one after the other)
 __device__ __forceinline__ bool ws_matches(const SpmmWsHeader* __restrict__ hdr, const FlatDims& d) {
-  return hdr->magic == kSpmmMagic && hdr->generation == d.generation && hdr->c_rows == d.m &&
-         hdr->c_nnz == d.nnz && hdr->c_nchunks == d.nchunks;
+  const uint32_t magic = hdr->magic;
+  const uint64_t generation = hdr->generation;
+  const int64_t rows = hdr->c_rows, nnz = hdr->c_nnz, nchunks = hdr->c_nchunks;
+  return (magic == kSpmmMagic) & (generation == d.generation) & (rows == d.m) & (nnz == d.nnz) & (nchunks == d.nchunks);
 }
 
 // value of lane S of the DPP unit (quad or row of 16) in all its lanes
@@ -80,13 +83,13 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
   const int lig = lane % LPE, sub = lane % UNIT;
   const bool active = lig * 4 < d.f;
   const uint32_t loff = active ? lig * 16 : 0;     // (idle lanes read the row's first piece again)
-  if (!ws_matches(hdr, d)) return;
   const int64_t wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6));
   if (wave * R >= d.nchunks) return;
   const int32_t k = (int32_t)(wave * R) + lane / LPE;
-  int4 ch = make_int4(0, 0, 0, 0);
-  if (k < d.nchunks) ch = chunks[k];
-  int32_t e0 = ch.x, e1 = ch.y, r = ch.z;
+  // (the header is looked at beside the chunk, not before it: a trip to memory less in a chain of four)
+  const int4 ch = chunks[k < d.nchunks ? k : d.nchunks - 1];
+  const bool ours = ws_matches(hdr, d) & (k < d.nchunks);
+  int32_t e0 = ch.x, e1 = ours ? ch.y : ch.x, r = ch.z;
   bool head = ch.w & 1;
   // (nothing below trusts the tables: entries stay inside [0, nnz), rows inside [0, m))
   e0 = e0 < 0 ? 0 : e0;
@@ -255,7 +258,7 @@ struct FixDims {
 };
 
 template <bool WG>
-__device__ __forceinline__ void fix_row(const int4* __restrict__ chunks, const int2* __restrict__ list, int64_t q, int64_t n_list,
+__device__ __forceinline__ void fix_row(bool ours, const int4* __restrict__ chunks, const int2* __restrict__ list, int64_t q, int64_t n_list,
                                         const float* __restrict__ carry, const int32_t* __restrict__ rowmap, float* __restrict__ C,
                                         const FixDims& d, float4 (*part)[64]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -263,7 +266,7 @@ __device__ __forceinline__ void fix_row(const int4* __restrict__ chunks, const i
   const int2 it = list[q];                                   // first chunk, number of chunks
   const int64_t k = it.x;
   int64_t cnt = it.y;
-  if (k < 0 || cnt <= 0 || k + cnt > d.nchunks) return;
+  if (!ours || k < 0 || cnt <= 0 || k + cnt > d.nchunks) return;
   const int32_t R = chunks[k].z;
   if (R < 0 || R >= d.m) return;
   const int64_t ro = rowmap ? rowmap[R] : R;
@@ -325,10 +328,13 @@ __global__ __launch_bounds__(kBlock) void flat_fixup_kernel(const SpmmWsHeader* 
                                                             const float* __restrict__ carry, const int32_t* __restrict__ rowmap,
                                                             float* __restrict__ C, const FixDims d) {
   __shared__ float4 part[kWaves][64];
-  if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->c_nchunks != d.nchunks) return;
+  const uint32_t magic = hdr->magic;
+  const uint64_t generation = hdr->generation;
+  const int64_t nchunks = hdr->c_nchunks;
+  const bool ours = (magic == kSpmmMagic) & (generation == d.generation) & (nchunks == d.nchunks);
   const int64_t b = blockIdx.x;
-  if (b < n_big) fix_row<true>(chunks, big, b, n_big, carry, rowmap, C, d, part);
-  else fix_row<false>(chunks, list, (b - n_big) * kWaves + (threadIdx.x >> 6), n_list, carry, rowmap, C, d, part);
+  if (b < n_big) fix_row<true>(ours, chunks, big, b, n_big, carry, rowmap, C, d, part);
+  else fix_row<false>(ours, chunks, list, (b - n_big) * kWaves + (threadIdx.x >> 6), n_list, carry, rowmap, C, d, part);
 }
 
 // ------------------------------------------------------------------------------------------
