@@ -27,7 +27,8 @@ struct GemmArgs {
   const float* mask; int64_t ldmask;
   float* Z; int64_t ldz;
   float* A; int64_t lda;
-  int32_t n0;  // first output column of this launch's slab
+  int32_t n0;     // first output column of this launch
+  int32_t slabs;  // column slabs of this launch
 };
 
 // bytes of LDS the W slab of NT*32 columns takes (split mode: three bfloat16 planes)

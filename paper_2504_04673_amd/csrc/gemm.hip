@@ -516,35 +516,40 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
   g.X = X; g.ldx = ldx; g.W = W; g.ldw = ldw; g.transW = transW; g.m = m; g.kdim = kdim;
   g.nout = nout; g.act = act; g.mask = mask; g.ldmask = ldmask; g.Z = Z; g.ldz = ldz; g.A = A;
   g.lda = lda;
-  if (prec == SAGNN_GEMM_BF16) {
-    g.n0 = 0;
-    const int tiles = (nout + 31) / 32;
-    if (tiles <= 1) return gemm_nn_bf16(1, g, s);
-    if (tiles <= 2) return gemm_nn_bf16(2, g, s);
-    if (tiles <= 4) return gemm_nn_bf16(4, g, s);
-    return gemm_nn_bf16(8, g, s);
+  const int tiles = (nout + 31) / 32;
+  auto run = [&](int nt) {
+    if (prec == SAGNN_GEMM_FP32) return gemm_nn_fp32(nt, g, s);
+    return prec == SAGNN_GEMM_BF16 ? gemm_nn_bf16(nt, g, s) : gemm_nn_bf16x3(nt, g, s);
+  };
+  // 32-column tiles of the widest slab: all of W in one launch with rounded operands; 128 columns in fp32 and in three
+  // terms, 64 where the three planes of 128 do not fit the LDS (beyond k = 128)
+  const int widest = prec == SAGNN_GEMM_BF16 ? 8 : (prec == SAGNN_GEMM_FP32 || nn_slab_bytes(kdim, 4, prec) <= 160 * 1024 ? 4 : 2);
+  int nt = 1;
+  while (nt < widest && nt < tiles) nt *= 2;
+  // Few rows: narrower slabs, side by side in one launch, until this many wavefronts have a tile.  A wide slab is a chain
+  // on a few CUs there: staging W, then the matrix instructions of all its columns, and the slabs one after the other.
+  // us before and so, fp32 4096 x 256 x 256 86, 13; 128 x 128 18, 10; 30 k 256 x 256 94, 53; 128 x 128 23, 21; 45 k
+  // 256 x 256 98, 77; 200 x 100 48, 44; rounded 10 k 256 x 256 26, 17; three terms 10 k 256 x 256 65, 25.  The lines lie
+  // where the wide form is as fast: fp32 70 k x 100 x 64 (2188 row tiles) 30 and 34, 100 k x 200 x 100 (3125) 97 and 104;
+  // rounded operands, whose matrix instructions cost little and whose workgroups have eight wavefronts, 20 k x 128 x 128
+  // 15, with 1024 wavefronts 13, with 2048 17; three terms 45 k x 256 x 40 20 and 24, but where the wide form is several
+  // launches 30 k x 256 x 256 73 and 53.  An output that overlaps X is written tile by tile behind the reads as before.
+  const int64_t row_tiles = (m + 31) / 32;
+  const int64_t enough = prec == SAGNN_GEMM_BF16 ? 1024 : (prec == SAGNN_GEMM_FP32 ? (tiles >= 4 ? 3072 : 2048) : (tiles > widest ? 4096 : 1024));
+  auto apart = [&](const float* out, int64_t ld) {
+    return !out || out + (m - 1) * ld + nout <= X || X + (m - 1) * ldx + kdim <= out;
+  };
+  if (row_tiles * ((tiles + nt - 1) / nt) < enough && apart(Z, ldz) && apart(A, lda)) {
+    while (nt > 1 && row_tiles * ((tiles + nt - 1) / nt) < enough) nt /= 2;
+    g.slabs = (tiles + nt - 1) / nt;
+    return run(nt);
   }
-  if (prec == SAGNN_GEMM_FP32_BF16X3) {
-    // the widest column slab whose three planes fit the LDS: 128 columns up to k = 128, 64 beyond
-    const int32_t slab = nn_slab_bytes(kdim, 4, prec) <= 160 * 1024 ? 128 : 64;
-    for (int32_t n0 = 0; n0 < nout; n0 += slab) {
-      g.n0 = n0;
-      const int tiles = ((nout - n0 < slab ? nout - n0 : slab) + 31) / 32;
-      int rc;
-      if (tiles <= 1) rc = gemm_nn_bf16x3(1, g, s);
-      else if (tiles <= 2) rc = gemm_nn_bf16x3(2, g, s);
-      else rc = gemm_nn_bf16x3(4, g, s);
-      if (rc != SAGNN_OK) return rc;
-    }
-    return SAGNN_OK;
-  }
-  for (int32_t n0 = 0; n0 < nout; n0 += 128) {
+  g.slabs = 1;
+  for (int32_t n0 = 0; n0 < nout; n0 += widest * 32) {
     g.n0 = n0;
-    const int tiles = ((nout - n0 < 128 ? nout - n0 : 128) + 31) / 32;
-    int rc;
-    if (tiles <= 1) rc = gemm_nn_fp32(1, g, s);
-    else if (tiles <= 2) rc = gemm_nn_fp32(2, g, s);
-    else rc = gemm_nn_fp32(4, g, s);
+    const int left = (nout - n0 + 31) / 32;
+    for (nt = 1; nt < widest && nt < left;) nt *= 2;
+    const int rc = run(nt);
     if (rc != SAGNN_OK) return rc;
   }
   return SAGNN_OK;

@@ -17,7 +17,7 @@ namespace {
 // One element per thread and round trip before: 4096 x 256 x 256 bf16 40 -> 22 us as it lies, 44 -> 19 transposed;
 // 125 k rows 131 -> 93 and 119 -> 89.
 template <int NB, int PREC, int THREADS>
-__device__ __forceinline__ void stage_w(const GemmArgs& g, char* smem, int kdim, int tid) {
+__device__ __forceinline__ void stage_w(const GemmArgs& g, int n0, char* smem, int kdim, int tid) {
   constexpr bool SPLIT = PREC == SAGNN_GEMM_FP32_BF16X3;
   const int kreal = g.kdim;
   float* __restrict__ Wf = reinterpret_cast<float*>(smem);
@@ -30,7 +30,7 @@ __device__ __forceinline__ void stage_w(const GemmArgs& g, char* smem, int kdim,
       for (int b = 0; b < 2; ++b) {
         const int u = u0 + b * THREADS;
         const int k0 = (u / NB) * 8;
-        const int col = g.n0 + u % NB;
+        const int col = n0 + u % NB;
         const float* __restrict__ src = g.W + (col < g.nout ? col : g.nout - 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) w[b][i] = src[(int64_t)(k0 + i < kreal ? k0 + i : kreal - 1) * g.ldw];
@@ -41,7 +41,7 @@ __device__ __forceinline__ void stage_w(const GemmArgs& g, char* smem, int kdim,
         const int u = u0 + b * THREADS;
         if (u >= units) break;
         const int n = u % NB, k0 = (u / NB) * 8;
-        const bool in = g.n0 + n < g.nout;
+        const bool in = n0 + n < g.nout;
 #pragma unroll
         for (int i = 0; i < 8; ++i) w[b][i] = in && k0 + i < kreal ? w[b][i] : 0.f;
         if constexpr (PREC == SAGNN_GEMM_FP32) {
@@ -74,7 +74,7 @@ __device__ __forceinline__ void stage_w(const GemmArgs& g, char* smem, int kdim,
       for (int b = 0; b < 4; ++b) {
         const int u = u0 + b * THREADS;
         const int k0 = ((u / (8 * NB)) * 8 + (u & 7)) * 4;
-        const int col = g.n0 + (u >> 3) % NB;
+        const int col = n0 + (u >> 3) % NB;
         // (kreal is a multiple of 4: a quad lies inside or outside as a whole)
         const float* __restrict__ src = g.W + (int64_t)(col < g.nout ? col : g.nout - 1) * g.ldw + (k0 < kreal ? k0 : kreal - 4);
         if (quads) w[b] = *reinterpret_cast<const float4*>(src);
@@ -86,7 +86,7 @@ __device__ __forceinline__ void stage_w(const GemmArgs& g, char* smem, int kdim,
         const int u = u0 + b * THREADS;
         if (u >= units) break;
         const int n = (u >> 3) % NB, k0 = ((u / (8 * NB)) * 8 + (u & 7)) * 4;
-        const bool in = g.n0 + n < g.nout && k0 < kreal;
+        const bool in = n0 + n < g.nout && k0 < kreal;
         const float x[4] = {in ? w[b].x : 0.f, in ? w[b].y : 0.f, in ? w[b].z : 0.f, in ? w[b].w : 0.f};
         if constexpr (PREC == SAGNN_GEMM_FP32) {
 #pragma unroll
@@ -127,7 +127,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
   const int kreal = g.kdim;                  // any multiple of 4
   const int kdim = (kreal + 31) & ~31;       // the k loop runs over the zero-padded extent
 
-  stage_w<NB, PREC, WAVES * 64>(g, smem, kdim, tid);
+  const int n0 = g.n0 + (int)blockIdx.y * NB;   // first column of this workgroup's slab
+  stage_w<NB, PREC, WAVES * 64>(g, n0, smem, kdim, tid);
   __syncthreads();
 
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -291,10 +292,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
     asm volatile("" : "+v"(moff), "+v"(zoff), "+v"(aoff));
     if (t * 32 + 32 <= g.m && near) {
       // full tile of rows (the 16 values of a lane are rows 8*(v/4) + 4*h + v%4)
-      const int col0 = g.n0 + r;
-      const char* mt = reinterpret_cast<const char*>(g.mask + (t * 32 * ldmask + g.n0));
-      char* zt = reinterpret_cast<char*>(g.Z + (t * 32 * ldz + g.n0));
-      char* at = reinterpret_cast<char*>(g.A + (t * 32 * lda + g.n0));
+      const int col0 = n0 + r;
+      const char* mt = reinterpret_cast<const char*>(g.mask + (t * 32 * ldmask + n0));
+      char* zt = reinterpret_cast<char*>(g.Z + (t * 32 * ldz + n0));
+      char* at = reinterpret_cast<char*>(g.A + (t * 32 * lda + n0));
       const bool relu = g.act == SAGNN_ACT_RELU;
       if (g.mask) {
         // the mask is applied in a pass of its own: between the stores below its loads would each
@@ -367,7 +368,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
     } else {
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const int col = g.n0 + nt * 32 + r;
+        const int col = n0 + nt * 32 + r;
         if (col >= g.nout) continue;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -408,7 +409,7 @@ int launch_nn_waves(const GemmArgs& g, size_t lds, hipStream_t s) {
     if (g.kdim == 256) return gemm_nn_kernel<NT, PREC, WAVES, false, 8, RAG>;
     return g.kdim & 31 ? gemm_nn_kernel<NT, PREC, WAVES, true, 0, RAG> : gemm_nn_kernel<NT, PREC, WAVES, false, 0, RAG>;
   };
-  void (*kern)(const GemmArgs) = g.n0 + NT * 32 <= g.nout ? pick(std::false_type{}) : pick(std::true_type{});
+  void (*kern)(const GemmArgs) = g.n0 + g.slabs * NT * 32 <= g.nout ? pick(std::false_type{}) : pick(std::true_type{});
   SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   const int64_t ntiles = (g.m + 31) / 32;
@@ -417,7 +418,7 @@ int launch_nn_waves(const GemmArgs& g, size_t lds, hipStream_t s) {
   const int64_t per_cu = lds > 80 * 1024 ? 1 : (lds > 40 * 1024 ? 2 : (lds > 18 * 1024 || NT > 1 ? 4 : (WAVES == 4 ? 5 : 3)));
   if (blocks > 256 * per_cu) blocks = 256 * per_cu;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(WAVES * 64), lds, s, g);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)g.slabs), dim3(WAVES * 64), lds, s, g);
   SAGNN_LAUNCH_CHECK();
   return SAGNN_OK;
 }

@@ -1201,6 +1201,34 @@ def test_dense_gemm_at_the_edges_of_its_groups_and_slabs(m, k, n, prec):
                 assert torch.equal(A, Z.clamp(min=0))
 
 
+@pytest.mark.parametrize("prec", [sagnn.GEMM_FP32, sagnn.GEMM_BF16, sagnn.GEMM_FP32_BF16X3])
+@pytest.mark.parametrize("m,k,n", [(65_537, 36, 64), (98_305, 64, 132), (98_306, 100, 256), (49_130, 128, 256), (131_073, 132, 96),
+                                   (131_041, 256, 256), (16_380, 160, 200), (32_770, 40, 40), (200_001, 28, 20),
+                                   (40_000, 64, 64)])
+def test_dense_gemm_with_wide_and_narrow_slabs(m, k, n, prec):
+    """Row counts on both sides of the lines between one launch of narrow slabs side by side and slabs as wide as W; with
+    mask, W as it lies and transposed, and the product written over X."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + k)
+    X = torch.randn(m, k, device="cuda", generator=gen)
+    W = torch.randn(k, n, device="cuda", generator=gen)
+    mask = torch.randn(m, n, device="cuda", generator=gen)
+    ref, size = X.double() @ W.double(), X.abs().double() @ W.abs().double()
+    # any order of k fp32 additions: k 2^-24 of the sum of the terms' sizes; an operand rounded to the 8 bits of bfloat16
+    # is off by half of its last, 2^-8 of its size at most: (1 + 2^-8)^2 - 1 for the product of two
+    tol = (2 * 2.0**-8 + 2.0**-16 if prec == sagnn.GEMM_BF16 else 2 * 2.0**-23) + (k + 2) * 2.0**-24
+    for trans in (False, True):
+        Wd = W.t().contiguous() if trans else W
+        Z, A = sagnn.dense_gemm_act(X, Wd, transW=trans, prec=prec, act=sagnn.ACT_RELU, want_z=True, want_act=True)
+        assert bool(((Z.double() - ref).abs() <= tol * size).all()) and torch.equal(A, Z.clamp(min=0))
+        Zm, _ = sagnn.dense_gemm_act(X, Wd, transW=trans, prec=prec, mask=mask)
+        assert torch.equal(Zm, torch.where(mask > 0, Z, torch.zeros_like(Z)))
+    if n == k and n <= 64:   # one slab
+        over = X.clone()
+        sagnn.dense_gemm_act(over, W, prec=prec, want_z=True, out=(over, None))
+        assert torch.equal(over, Z)
+
+
 @pytest.mark.parametrize("prec", [sagnn.GEMM_FP32, sagnn.GEMM_FP32_BF16X3])
 @pytest.mark.parametrize("m,k,n", [(31, 32, 64), (64, 32, 32), (97, 64, 64), (128, 64, 192), (65, 96, 64), (4100, 96, 32), (160, 128, 64)])
 def test_dense_gemm_of_whole_k_groups_and_64_columns(m, k, n, prec):
