@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
 }
 
 // Y = X^T S straight from registers.  In X^T S the reduction index is the row, so the lanes of an operand that
-// hold one k hold one row of X: a lane loads V consecutive columns of a row (V = 1, 2 or 4) and register c of
+// hold one k hold one row of X: a lane loads V consecutive columns of a row (V = 1 to 4) and register c of
 // those loads is the operand of the tile with columns V*i + c, i = 0..15.  No transpose, no LDS in the loop.
 //   fp32                    16x16x4: a load brings 4 rows, one per 16 lanes
 //   bfloat16, three terms   16x16x32: 8 loads bring 32 rows, lane group q the rows 8q..8q+7, packed in registers
@@ -172,12 +172,26 @@ __global__ __launch_bounds__(kTnThreads) void gemm_tn_kernel(const TnArgs g) {
 // It replaces a form that staged every slab transposed in LDS for all shapes (16 x 16 over 1 M rows took 1 ms:
 // the staging work did not shrink with the width); that one is kept where it is faster (see launch_gemm_tn).
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-constexpr int kTdWaves = 8;
+// Wavefronts of a workgroup: sixteen where the sums and the rows on their way fit 128 registers, which takes loading the
+// next rows into the registers that the matrix instructions have just read: with a second set of them two wavefronts per
+// SIMD were resident (160 registers, workgroups of eight), the slices ran in two rounds, and the loads' latency showed.
+// fp32, 170 k rows: 128 x 128 69 -> 59 us, 128 x 256 121 -> 113; 60 k x 128 x 128 36 -> 30; 1 M x 128 x 128 322 -> 282.
+// (matrix instructions alone 213, reading the operands 213; their rates together are what is left)
+constexpr int td_waves(int prec) { return prec == SAGNN_GEMM_FP32 ? 16 : 8; }
 
 template <int V> struct ColVec;
 template <> struct ColVec<1> { typedef float T; };
 template <> struct ColVec<2> { typedef float T __attribute__((ext_vector_type(2))); };
 template <> struct ColVec<4> { typedef float T __attribute__((ext_vector_type(4))); };
+// three columns: 12 bytes at any multiple of 4 (a vector of three would be read as four)
+template <> struct ColVec<3> {
+  struct T {
+    float v[3];
+    __device__ T() {}
+    __device__ explicit T(float a) : v{a, a, a} {}
+    __device__ float operator[](int c) const { return v[c]; }
+  };
+};
 template <int V>
 __device__ __forceinline__ float comp(const typename ColVec<V>::T& v, int c) {
   if constexpr (V == 1) return v;
@@ -185,7 +199,7 @@ __device__ __forceinline__ float comp(const typename ColVec<V>::T& v, int c) {
 }
 
 template <int PREC, int VA, int VB>
-__global__ __launch_bounds__(kTdWaves * 64) void gemm_tn_direct_kernel(const TnArgs g, int nbx, int nbs, int per,
+__global__ __launch_bounds__(td_waves(PREC) * 64) void gemm_tn_direct_kernel(const TnArgs g, int nbx, int nbs, int per,
                                                                              int kshare) {
   constexpr int KROWS = PREC == SAGNN_GEMM_FP32 ? 4 : 32;      // rows of one matrix instruction
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -198,7 +212,7 @@ __global__ __launch_bounds__(kTdWaves * 64) void gemm_tn_direct_kernel(const TnA
   const int here = nb - first < per ? nb - first : per;             // blocks of Y in this workgroup
   const int blk = first + wave % here, share = wave / here;
   const bool busy = share < kshare;
-  const int xb = blk / nbs * 64, sb = blk % nbs * 64;
+  const int xb = blk / nbs * (16 * VA), sb = blk % nbs * (16 * VB);
   // a lane whose columns lie past the end reads column 0: its results are not stored
   const int xc = xb + VA * i < g.fi ? xb + VA * i : 0, sc = sb + VB * i < g.fo ? sb + VB * i : 0;
   const int64_t r0 = (int64_t)blockIdx.y * g.rows_per_wg;
@@ -219,40 +233,35 @@ __global__ __launch_bounds__(kTdWaves * 64) void gemm_tn_direct_kernel(const TnA
     const float* sp = g.S + (r + q) * g.lds_ + sc;
     xvec x[U];
     svec s[U];
-    auto full = [&](int64_t at) { return busy && at + U * KROWS <= r_end; };
+    // (three columns a lane may reach past a row's end, into the next row: the last row of all is read one by one)
+    const int64_t whole = VA == 3 || VB == 3 ? (r_end < g.m ? r_end : g.m - 1) : r_end;
+    auto full = [&](int64_t at) { return busy && at + U * KROWS <= whole; };
+    auto load = [&](int u) {
+      x[u] = *reinterpret_cast<const xvec*>(xp + (int64_t)(u * KROWS) * g.ldx);
+      s[u] = *reinterpret_cast<const svec*>(sp + (int64_t)(u * KROWS) * g.lds_);
+    };
+    auto multiply = [&](int u) {
+#pragma unroll
+      for (int a = 0; a < VA; ++a)
+#pragma unroll
+        for (int b = 0; b < VB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp<VA>(x[u], a), comp<VB>(s[u], b), acc[a][b], 0, 0, 0);
+    };
     if (full(r)) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        x[u] = *reinterpret_cast<const xvec*>(xp + (int64_t)(u * KROWS) * g.ldx);
-        s[u] = *reinterpret_cast<const svec*>(sp + (int64_t)(u * KROWS) * g.lds_);
-      }
-    }
-    while (full(r)) {
-      r += step;
-      xp += step * g.ldx;
-      sp += step * g.lds_;
-      const bool more = full(r);
-      xvec xn[U];
-      svec sn[U];
-      if (more) {
+      for (int u = 0; u < U; ++u) load(u);
+      for (r += step; full(r); r += step) {
+        xp += step * g.ldx;
+        sp += step * g.lds_;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          xn[u] = *reinterpret_cast<const xvec*>(xp + (int64_t)(u * KROWS) * g.ldx);
-          sn[u] = *reinterpret_cast<const svec*>(sp + (int64_t)(u * KROWS) * g.lds_);
+          multiply(u);
+          load(u);                                             // (the next step's rows, into the registers just read)
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int a = 0; a < VA; ++a)
-#pragma unroll
-          for (int b = 0; b < VB; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp<VA>(x[u], a), comp<VB>(s[u], b), acc[a][b], 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        x[u] = xn[u];
-        s[u] = sn[u];
-      }
+      for (int u = 0; u < U; ++u) multiply(u);
     }
     if (busy)
       for (int u = 0; u < U; ++u) {                            // the rows of the last, partial step
@@ -261,8 +270,20 @@ __global__ __launch_bounds__(kTdWaves * 64) void gemm_tn_direct_kernel(const TnA
         xvec xt = xvec(0.f);
         svec st = svec(0.f);
         if (row < r_end) {
-          xt = *reinterpret_cast<const xvec*>(g.X + row * g.ldx + xc);
-          st = *reinterpret_cast<const svec*>(g.S + row * g.lds_ + sc);
+          const float* xr = g.X + row * g.ldx + xc;
+          const float* sr = g.S + row * g.lds_ + sc;
+          if constexpr (VA == 3) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) xt.v[c] = xr[xc + c < g.fi ? c : 0];
+          } else {
+            xt = *reinterpret_cast<const xvec*>(xr);
+          }
+          if constexpr (VB == 3) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) st.v[c] = sr[sc + c < g.fo ? c : 0];
+          } else {
+            st = *reinterpret_cast<const svec*>(sr);
+          }
         }
 #pragma unroll
         for (int a = 0; a < VA; ++a)
@@ -424,7 +445,7 @@ inline size_t tn_partial_bytes(int64_t m, int64_t elems) {
 // the staged form wins as soon as one workgroup does not cover Y (1 M rows: 462 against 773 us at 256 x 256, 320
 // against 534 at 160 x 160, but 296 against 265 at 192 x 96).
 inline bool tn_staged(int32_t fi, int32_t fo, int32_t prec) {
-  return prec == SAGNN_GEMM_BF16 && ((fi + 63) / 64) * ((fo + 63) / 64) > kTdWaves;
+  return prec == SAGNN_GEMM_BF16 && ((fi + 63) / 64) * ((fo + 63) / 64) > td_waves(SAGNN_GEMM_BF16);
 }
 
 }  // namespace
@@ -445,7 +466,8 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
   if (!Y || !yws || !aligned16(yws)) return SAGNN_EINVAL;
   if (m > 0 && (!X || !S || !aligned16(X) || !aligned16(S))) return SAGNN_EINVAL;
   if (yws_bytes < tn_partial_bytes(m, (int64_t)fi * fo)) return SAGNN_ECAPACITY;
-  const int32_t parts = (int32_t)tn_parts(m, (int64_t)fi * fo);
+  int32_t parts = (int32_t)tn_parts(m, (int64_t)fi * fo);
+  if (td_waves(prec) == 16) parts = std::min(parts, 256);      // (one workgroup fills a CU)
   TnArgs g{};
   g.X = X; g.ldx = ldx; g.S = S; g.lds_ = lds_; g.m = m; g.fi = fi; g.fo = fo;
   g.rows_per_wg = ceil_div(ceil_div(m > 0 ? m : 1, parts), KB) * KB;
@@ -457,10 +479,21 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
     hipLaunchKernelGGL(gemm_tn_kernel, dim3(parts), dim3(kTnThreads), lds, s, g);
     SAGNN_LAUNCH_CHECK();
   } else {
-    const int va = fi <= 16 ? 1 : (fi <= 32 ? 2 : 4), vb = fo <= 16 ? 1 : (fo <= 32 ? 2 : 4);
-    const int nbx = (fi + 63) / 64, nbs = (fo + 63) / 64, nb = nbx * nbs;
-    const int nwg = (nb + kTdWaves - 1) / kTdWaves, per = (nb + nwg - 1) / nwg, kshare = kTdWaves / per;
-    const size_t lds = (size_t)(kshare / 2) * per * va * vb * 64 * 16;   // at most 64 KB
+    // Columns of a lane: four, but three where blocks of 48 waste less on columns that are not there (33 to 48, 65 to 96,
+    // 129 to 144) and the matrix instructions bound it: fp32, 170 k x 96 x 96 57 -> 37 us, 256 x 40 63 -> 50, 48 x 48 23 -> 15.
+    auto columns = [&](int32_t w) {
+      if (w <= 16) return 1;
+      if (w <= 32) return 2;
+      return prec == SAGNN_GEMM_FP32 && (w + 47) / 48 * 3 < (w + 63) / 64 * 4 && (w + 47) / 48 == (w + 63) / 64 ? 3 : 4;
+    };
+    const int va = columns(fi), vb = columns(fo);
+    const int nbx = (fi + 16 * va - 1) / (16 * va), nbs = (fo + 16 * vb - 1) / (16 * vb), nb = nbx * nbs;
+    const int waves = td_waves(prec), nwg = (nb + waves - 1) / waves, per = (nb + nwg - 1) / nwg;
+    // Shares of a slice's rows: as many as there are wavefronts for, in fp32 of 64 rows at least (30 k x 100 x 64: 13.9 us
+    // in eight shares of 16 rows, 10.0 in two; 10 k x 128 x 128 20.0 and 16.4).
+    int kshare = waves / per;
+    if (prec == SAGNN_GEMM_FP32) kshare = (int)std::max<int64_t>(1, std::min<int64_t>(kshare, g.rows_per_wg / 64));
+    const size_t lds = (size_t)(kshare / 2) * per * va * vb * 64 * 16;   // at most 8 KB a wavefront
     const dim3 grid((unsigned)nwg, (unsigned)parts);   // (workgroups that read the same rows run side by side)
     auto go = [&](auto kern) -> int {
       if (lds > 48 * 1024)
@@ -471,17 +504,19 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
     };
     auto width = [&](auto p) -> int {
       constexpr int PREC = decltype(p)::value;
-      switch (va * 8 + vb) {
-        case 9: return go(gemm_tn_direct_kernel<PREC, 1, 1>);
-        case 10: return go(gemm_tn_direct_kernel<PREC, 1, 2>);
-        case 12: return go(gemm_tn_direct_kernel<PREC, 1, 4>);
-        case 17: return go(gemm_tn_direct_kernel<PREC, 2, 1>);
-        case 18: return go(gemm_tn_direct_kernel<PREC, 2, 2>);
-        case 20: return go(gemm_tn_direct_kernel<PREC, 2, 4>);
-        case 33: return go(gemm_tn_direct_kernel<PREC, 4, 1>);
-        case 34: return go(gemm_tn_direct_kernel<PREC, 4, 2>);
-        default: return go(gemm_tn_direct_kernel<PREC, 4, 4>);
-      }
+      auto with = [&](auto a) -> int {
+        constexpr int VA = decltype(a)::value;
+        if (vb == 1) return go(gemm_tn_direct_kernel<PREC, VA, 1>);
+        if (vb == 2) return go(gemm_tn_direct_kernel<PREC, VA, 2>);
+        if constexpr (PREC == SAGNN_GEMM_FP32)
+          if (vb == 3) return go(gemm_tn_direct_kernel<PREC, VA, 3>);
+        return go(gemm_tn_direct_kernel<PREC, VA, 4>);
+      };
+      if (va == 1) return with(std::integral_constant<int, 1>{});
+      if (va == 2) return with(std::integral_constant<int, 2>{});
+      if constexpr (PREC == SAGNN_GEMM_FP32)
+        if (va == 3) return with(std::integral_constant<int, 3>{});
+      return with(std::integral_constant<int, 4>{});
     };
     int rc;
     if (prec == SAGNN_GEMM_BF16) rc = width(std::integral_constant<int, SAGNN_GEMM_BF16>{});

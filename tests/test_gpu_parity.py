@@ -1309,6 +1309,23 @@ def test_weight_gradient_at_the_edges_of_its_blocks(prec, m, fin, fout):
     assert_close(Y, ref, yabs, RTOL_GEMM_FP32, "weight gradient")
 
 
+@pytest.mark.parametrize("fin,fout", [(36, 16), (48, 48), (16, 40), (68, 64), (96, 92), (36, 100), (132, 44), (140, 144), (256, 72)])
+@pytest.mark.parametrize("m", [1, 17, 64, 131, 5003, 40_003])
+def test_weight_gradient_with_three_columns_a_lane(m, fin, fout):
+    """Widths that blocks of 48 columns cover, whole and ragged; with NaN in the first two columns of H, which is what a
+    lane of three columns reads past a row's end and must not use."""
+    gen = torch.Generator().manual_seed(m + fin)
+    rp = torch.arange(m + 1, dtype=torch.int32, device="cuda")
+    ci, v = torch.arange(m, dtype=torch.int32, device="cuda"), torch.ones(m, device="cuda")
+    H, G, W = torch.randn(m, fin, generator=gen), torch.randn(m, fout, generator=gen), torch.zeros(fin, fout, device="cuda")
+    ref, size = H.double().T @ G.double(), H.abs().double().T @ G.abs().double()
+    for first in (0, 2):
+        H[:, :first] = float("nan")
+        _, _, Y = sagnn.gcn_layer_bwd(rp, ci, v, G.cuda(), W, None, H.cuda(), prec=sagnn.GEMM_FP32, want_gprev=False)
+        # any order of m additions: at most m 2^-24 of the sum of the terms' sizes
+        assert bool(((Y.cpu().double() - ref).abs() <= (m + 2) * 2.0**-24 * size)[first:].all())
+
+
 @pytest.mark.parametrize("prec,fin,fout", [(0, 128, 128), (1, 256, 256), (0, 64, 32), (0, 16, 16), (1, 48, 20),
                                            (2, 128, 128), (2, 256, 256), (2, 48, 20)])
 def test_gcn_layer_fwd_bwd_small(prec, fin, fout):
