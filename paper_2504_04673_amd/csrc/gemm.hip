@@ -489,10 +489,10 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
     const int va = columns(fi), vb = columns(fo);
     const int nbx = (fi + 16 * va - 1) / (16 * va), nbs = (fo + 16 * vb - 1) / (16 * vb), nb = nbx * nbs;
     const int waves = td_waves(prec), nwg = (nb + waves - 1) / waves, per = (nb + nwg - 1) / nwg;
-    // Shares of a slice's rows: as many as there are wavefronts for, in fp32 of 64 rows at least (30 k x 100 x 64: 13.9 us
-    // in eight shares of 16 rows, 10.0 in two; 10 k x 128 x 128 20.0 and 16.4).
-    int kshare = waves / per;
-    if (prec == SAGNN_GEMM_FP32) kshare = (int)std::max<int64_t>(1, std::min<int64_t>(kshare, g.rows_per_wg / 64));
+    // Shares of a slice's rows: one for each wavefront, but of eight where a slice has 128 rows, the fewest (30 k x 128 x
+    // 128: 21 us with sixteen, 18 with eight).  Still fewer would take up to 2 us off such calls, but sums of 64 rows in a
+    // chain are up to 1.4 times as far from exact as sums of 16.
+    const int kshare = std::max(1, (g.rows_per_wg > 128 ? waves : std::min(waves, 8)) / per);
     const size_t lds = (size_t)(kshare / 2) * per * va * vb * 64 * 16;   // at most 8 KB a wavefront
     const dim3 grid((unsigned)nwg, (unsigned)parts);   // (workgroups that read the same rows run side by side)
     auto go = [&](auto kern) -> int {
