@@ -136,6 +136,9 @@ struct SpmmWsHeader {       // first 256 bytes of the SpMM workspace (device cop
   int32_t max_slab;         // widest column slab of B per launch (256 or 128)
   int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
   int32_t launch_waves;     // wavefronts per launch (0: all in one)
+  int32_t apart;            // a small matrix without hubs: the layer's dense transform is not the sweep's epilogue.  Its wavefronts
+                            // may hold fewer than 16 rows, which the epilogue multiplies all the same: 60 k vertices of 20 in
+                            // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
 };
 static_assert(sizeof(SpmmWsHeader) <= 256, "header must fit its slot");
 
@@ -254,6 +257,9 @@ struct SpmmHostDesc {
   int32_t max_slab;         // widest column slab of B per launch (256, or 128 for the lane-group kernels at wider f)
   int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
   int32_t launch_waves;     // wavefronts per launch (0: all in one)
+  int32_t apart;            // a small matrix without hubs: the layer's dense transform is not the sweep's epilogue.  Its wavefronts
+                            // may hold fewer than 16 rows, which the epilogue multiplies all the same: 60 k vertices of 20 in
+                            // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
   float mean_steps;         // average stream steps per wavefront (the end of the pacing schedule)
   float max_steps;          // steps of the longest stream
   // dense-tile schedule (tiles.hip): when tiles != 0 everything above describes the rest CSR
@@ -304,9 +310,12 @@ struct SweepPlanResult {
   float max_steps;   // steps of the longest stream
   SpmmWsHeader hdr;  // filled in for mode 1 (sweep part + short CSR sizes)
 };
+// Sizes at which every matrix is looked at for the sweep (see sweep_prepare); below them those without hubs are
+inline bool sweep_size(int64_t k, int64_t nnz, int32_t f) { return nnz >= (3 << 20) && k * (int64_t)f * 4 > (8ll << 20); }
+// no_hubs: no row is known to hold many times the others' entries
 int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float* d_val, int64_t m,
                   int64_t k, int64_t nnz, int32_t f, char* ws, const SpmmWsLayout& L,
-                  const sagnn_spmm_options& opt, hipStream_t s, SweepPlanResult* out);
+                  const sagnn_spmm_options& opt, bool no_hubs, hipStream_t s, SweepPlanResult* out);
 // device side of the planner (sweep_plan.hip); the scratch arrays live in the stream arrays of the
 // workspace, which are written last
 struct SweepRowTotals {

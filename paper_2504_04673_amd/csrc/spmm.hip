@@ -475,6 +475,7 @@ __global__ __launch_bounds__(256) void layer_leftover_kernel(
 bool fused_sweep_layer_applicable(const void* ws, int32_t f_in, int32_t f_out) {
   SpmmHostDesc desc{};
   if (!ws || !spmm_desc_get(ws, &desc)) return false;
+  if (desc.apart) return false;
   if (desc.tiles) return false;   // rows with entries in dense tiles are not finished by the sweep
   if (desc.mode != 1 || desc.slots != kSweepSlots || desc.n_waves <= 0 || (desc.n_waves & 3)) return false;
   if (!(f_in == 64 || f_in == 128 || f_in == 256) || f_in > desc.f || f_in > desc.max_slab) return false;
@@ -650,12 +651,30 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
 
   SweepPlanResult plan{};
   {
-    int rc = sweep_prepare(d_rowptr, d_colidx, d_val, m, k, nnz, f, base, L, opt, s, &plan);
+    int rc = sweep_prepare(d_rowptr, d_colidx, d_val, m, k, nnz, f, base, L, opt, false, s, &plan);
     if (rc != SAGNN_OK) return rc;
   }
   SpmmWsHeader h{};
+  const int64_t T = spmm_chunk_entries(nnz, f);
+  if (!plan.use_sweep) {
+    h.magic = kSpmmMagic;
+    h.m = m; h.nnz = nnz; h.f = f; h.mode = 0;
+    h.generation = spmm_next_generation();
+    h.c_rows = m; h.c_nnz = nnz; h.c_nchunks = spmm_nchunks(nnz, T);
+    int rc = flat_build_tables(d_rowptr, m, nnz, T, base, L, d_stat, s);
+    if (rc == SAGNN_OK) rc = put_header(h, d_stat);
+    if (rc == SAGNN_OK) rc = read_stat();
+    if (rc != SAGNN_OK) return rc;
+    // The tables tell, at no cost to a matrix with hubs, that there is none: then the sweep is looked at again (its own
+    // row pass and wait take about 0.1 ms, the whole plan about 1).
+    if (opt.schedule == 0 && stat[2] == 0 && !sweep_size(k, nnz, f)) {
+      rc = sweep_prepare(d_rowptr, d_colidx, d_val, m, k, nnz, f, base, L, opt, true, s, &plan);
+      if (rc != SAGNN_OK) return rc;
+    }
+  }
   if (plan.use_sweep) {
     h = plan.hdr;
+    stat[1] = stat[2] = 0;
     if (h.c_nchunks > 0) {
       int rc = flat_build_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), h.c_rows, h.c_nnz,
                                  spmm_chunk_entries(h.c_nnz, f), base, L, d_stat, s);
@@ -663,15 +682,6 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
       if (rc != SAGNN_OK) return rc;
     }
   } else {
-    h.magic = kSpmmMagic;
-    h.m = m; h.nnz = nnz; h.f = f; h.mode = 0;
-    h.generation = spmm_next_generation();
-    const int64_t T = spmm_chunk_entries(nnz, f);
-    h.c_rows = m; h.c_nnz = nnz; h.c_nchunks = spmm_nchunks(nnz, T);
-    int rc = flat_build_tables(d_rowptr, m, nnz, T, base, L, d_stat, s);
-    if (rc == SAGNN_OK) rc = put_header(h, d_stat);
-    if (rc == SAGNN_OK) rc = read_stat();
-    if (rc != SAGNN_OK) return rc;
     h.has_empty_rows = stat[0];
     header_there = true;
     if (stat[0] && nnz > 0) {
@@ -681,7 +691,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
       // The row pass of the sweep planner with a threshold no row reaches makes exactly that list
       // (every row with entries is "short").
       SweepRowTotals t{};
-      rc = sweep_plan_rows(d_rowptr, nullptr, m, k, nnz, 0x7FFFFFFF, 1024, base, L, s, &t);
+      int rc = sweep_plan_rows(d_rowptr, nullptr, m, k, nnz, 0x7FFFFFFF, 1024, base, L, s, &t);
       if (rc != SAGNN_OK) return rc;
       if (!t.bad && t.short_entries == nnz) {   // (a malformed row pointer keeps the plain walk, which clamps everything)
         rc = flat_build_tables(reinterpret_cast<const int32_t*>(base + L.rowptr_s), t.short_rows, nnz, T, base, L, d_stat, s);
@@ -711,6 +721,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   desc.slots = h.slots;
   desc.max_slab = h.max_slab > 0 ? h.max_slab : 256;
   desc.col_slab = h.col_slab; desc.launch_waves = h.launch_waves;
+  desc.apart = plan.use_sweep && !sweep_size(k, nnz, f) && opt.schedule != 2;
   desc.barriers = h.barriers; desc.pace_ps_per_step = h.pace_ps_per_step > 0 ? h.pace_ps_per_step : 0;
   desc.mean_steps = plan.mean_steps;
   desc.max_steps = plan.max_steps;

@@ -629,8 +629,9 @@ __device__ __forceinline__ uint32_t row_element(uint32_t at, int v, int32_t fw) 
 }
 
 // Sum of a segment.  TWO: the entries of a batch of eight in two sums, then the batches, where a plain sum goes on through
-// the segment.  For the widths between the kernels' own (ODD) below 64, and below 128 with one row per load: nonzero
-// splitting, which had these widths before, added their entries as a tree.  Error against 64 bits (2-norm) by the tree,
+// the segment.  For the widths between the kernels' own (ODD) below 64, and below 128 with one row per load, for 16 and 32
+// (1 M vertices, 50 M entries, training at f = 16 2267 us with a plain sum, 2249 so), and below 128 in small matrices:
+// nonzero splitting, which had these widths before, added their entries as a tree.  Error against 64 bits (2-norm) by the tree,
 // by a plain sum, by two: 300 k vertices of 42 in 16 communities f = 8 6.9e-8, 1.18e-7, 6.9e-8, f = 48 7.8e-8, 1.17e-7,
 // 7.4e-8; a rank's rows f = 48 3.0e-8, 3.6e-8, 3.2e-8.  (What is left is the order of the slabs: random columns, 40 a row,
 // f = 48 7.7e-8, 8.3e-8, 8.5e-8, as the full widths always had.)  1 M vertices, 50 M
@@ -1049,7 +1050,7 @@ __global__ __launch_bounds__(256) void sweep_pack_w_kernel(const float* __restri
 // FUSE: 0 the product alone; 1 / 2 / 3 the layer form: the kernel ends with the dense transform of the
 // workgroup's rows (fp32 / bfloat16 / three-term operands, see sweep_dense_epilogue) instead of storing T (C is
 // then only written if the caller wants T as a by-product: fa.T).
-template <int V, int R, int U, bool BUF, int FUSE = 0, bool ODD = false, bool AHEAD = true>
+template <int V, int R, int U, bool BUF, int FUSE = 0, bool ODD = false, bool AHEAD = true, bool TWO = ODD && R == 4>
 __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1125,7 +1126,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   if (AHEAD && steps > 0) words(0);
   int32_t e = 0;
   for (int iv = 0; iv < n_iv; ++iv) {
-    SegmentSum<vec, ODD && R == 4> sum;   // (what the padding of the interval before left is not summed: see spmm_sweep_perm_kernel)
+    SegmentSum<vec, TWO> sum;   // (what the padding of the interval before left is not summed: see spmm_sweep_perm_kernel)
     const int32_t e_end = iv + 1 < n_iv ? so[iv + 1] : steps;
     for (; e < e_end; e += U) {
       turn.at(e);
@@ -1273,7 +1274,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     all_own = __builtin_amdgcn_readfirstlane(all_own);
   }
 
-  SegmentSum<vec, ODD> sum;
+  SegmentSum<vec, true> sum;
   vec tot = 0.f;
   uint32_t cb[NB];
   float vb[NB];
@@ -1330,8 +1331,8 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
           if (e + u < own) sum.add(u, mv[u], h[u]);
       }
       sum.batch_ends();
-      // no slots to flush into: fold the running sum every 64 entries instead
-      if ((e & 63) == 56) tot += sum.take();
+      // no slots to flush into: fold the running sum every 32 entries instead
+      if ((e & 31) == 24) tot += sum.take();
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
@@ -1408,15 +1409,19 @@ int32_t sweep_lds_width(int32_t fw) { return fw > 96 && fw < 128 ? 128 : fw; }
 // CSR are device work (sweep_plan.hip), as is the layout of the streams (the passes above).
 int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float* d_val, int64_t m,
                   int64_t k, int64_t nnz, int32_t f, char* ws, const SpmmWsLayout& L,
-                  const sagnn_spmm_options& opt, hipStream_t s, SweepPlanResult* out) {
+                  const sagnn_spmm_options& opt, bool no_hubs, hipStream_t s, SweepPlanResult* out) {
   out->use_sweep = false;
   const int force = opt.schedule == 1 ? 0 : (opt.schedule == 2 ? 1 : -1);
   if (force == 0 || nnz < 4096 || k <= 0 || k >= (1ll << kSweepColBits) || m <= 0) return SAGNN_OK;
   const int64_t b_bytes = k * (int64_t)f * 4;
   // worth it only if B is much larger than an L2 (the long-row share is checked below) and there are enough entries
   // for balanced streams on every CU (2.4 M entries: 129 against 139 us at f = 128, 49 against 67 at f = 16; 4 M: 154
-  // against 146 the other way)
-  if (force != 1 && (nnz < (3 << 20) || b_bytes <= (8ll << 20))) return SAGNN_OK;
+  // against 146 the other way), or if no row is so long that it would have to be cut: then 1 M entries are enough, whatever
+  // the size of B.  us by nonzero splitting and swept, random columns: 30 k vertices of 48, f = 16, 64, 256 34, 45, 190 and
+  // 15, 33, 123; 100 k of 24 47, 91, 352 and 33, 64, 250; 100 k of 64, f = 16 109 and 50; 10 k of 120 28, 29, 115 and 17,
+  // 30, 72; in communities: 30 k of 64 42, 44, 162 and 22, 38, 136; a row block of 85 k rows of 30, f = 64, 256 97, 375 and
+  // 56, 217.  Under 1 M entries some lose: 30 k of 24 in communities, f = 100, 256 36, 89 and 46, 101.
+  if (force != 1 && (no_hubs ? nnz < (1 << 20) : !sweep_size(k, nnz, f))) return SAGNN_OK;
 
   if (!sweep_plan_fits(L)) return SAGNN_OK;
   int piece_max = opt.piece > 0 ? opt.piece : (force == 1 ? 4096 : sweep_piece_default(nnz, f));
@@ -1469,6 +1474,16 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
+  // Without hubs, small: short rows are swept beside the others above 32 columns only (100 k rows of 16, 55 % of the entries
+  // in rows of 16 or more, f = 16 29 us by nonzero splitting, 31 swept); hardly any re-use (a rank's 125 k rows of 15 by
+  // 8 M columns, f = 64, 256 85, 298 and 124, 321).  Nonzero splitting adds as a tree at the widths under 128 but 64, and a
+  // row's sum here has a term per slab: not swept at these where the slabs that locality needs are more than a row's
+  // entries fill (a row block of 85 k rows of 30 in communities, f = 100 6.7e-8 from 64 bits, 7.5e-8 in the slabs of the
+  // other widths, 6.8e-8 in so few that nothing is gained).
+  const bool tree = f > 16 && f < 128 && f != 64;
+  if (no_hubs && (10 * tot.multi_pieces * (int64_t)piece_max > nnz || (f <= 32 && long_entries * 10 < nnz * 9) ||
+                  (double)nnz < 8.0 * span || (tree && !local && 2.0 * span < (double)k)))
+    return SAGNN_OK;
   if (opt.groups != 2 && long_entries < 8 * k) {
     if (f <= 32) return SAGNN_OK;  // one row per instruction would leave most lanes idle: plain schedule
     R = 1;
@@ -1489,7 +1504,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   int64_t slots_used = ceil_div(P, (int64_t)(opt.min_waves > 0 ? opt.min_waves : 8192));
   if (slots_used < R) slots_used = R;          // every lane group of a wavefront gets a piece
   if (slots_used > slots) slots_used = slots;
-  if (ceil_div(P, slots_used) + 64 > L.max_waves - 8) slots_used = slots;
+  while (slots_used < slots && ceil_div(P, slots_used) + 64 > L.max_waves - 8) ++slots_used;
   // Pieces are dealt window by window.  A window is a run of consecutive long rows holding a
   // few times as many pieces as the chip keeps resident at once (LDS-limited); inside a window
   // the pieces are sorted by size and dealt longest-first, so its wavefronts have nearly equal
@@ -1535,6 +1550,16 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const int64_t slab_bytes = opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : (col_groups && !local && f > 128 ? 32 * f : 4096)) << 10;
   int64_t S = slab_bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * slab_bytes) : kSweepMaxSlabs;
   if (S < 8) S = 8;
+  // Small matrices: the columns that neighbouring rows choose from in four slabs where the order of the rows carries
+  // locality, in eight where all choose from the same, but four where nonzero splitting would add as a tree, and one per 64
+  // entries of a row at 17 to 32 columns, where a stream has two rows.  Error against 64 bits by nonzero splitting and so:
+  // random columns, 30 k vertices of 60, f = 16, 32, 64, 100, 256 7.3e-8, 7.4e-8, 12.2e-8, 7.7e-8, 13.1e-8 and 7.0e-8,
+  // 7.5e-8, 7.8e-8, 7.0e-8, 7.8e-8; communities 7.3e-8, 7.4e-8, 12.3e-8, 7.7e-8, 13.1e-8 and 7.0e-8, 7.5e-8, 8.7e-8,
+  // 7.7e-8, 8.7e-8 (in eight slabs for all 13.8e-8 from f = 64, and 131 us for 110 at f = 256).
+  if (no_hubs && opt.slab_kb == 0) {
+    const double per_span = f > 16 && f <= 32 ? (double)ceil_div(nnz, 64 * m) : (local || tree ? 4.0 : 8.0);
+    S = per_span <= 1.0 ? 1 : (int64_t)(per_span * (double)k / std::max(span, 1.0) + 0.5);
+  }
   if (S > kSweepMaxSlabs) S = kSweepMaxSlabs;
   const int64_t width = ceil_div(k, S);
   std::vector<int64_t> win_entries(1, long_entries);
@@ -1847,6 +1872,11 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     if (fw == 128) return buf ? go_group(group_kernel_of<4, 2, true>(fuse)) : go_group(group_kernel_of<4, 2, false>(fuse));
     if (fw == 64) return buf ? go_group(group_kernel_of<2, 2, true>(fuse)) : go_group(group_kernel_of<2, 2, false>(fuse));
     if (fw > 128 || fuse) return SAGNN_EINVAL;
+    // (two sums where nonzero splitting would be the alternative, with its tree: communities, 30 k vertices of 60, f = 100
+    // 7.7e-8 from 64 bits by the tree, 13.8e-8 by one sum; elsewhere they cost up to 2 %)
+    if (d.apart)
+      return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true, true, true>)
+                 : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true, true, true>);
     return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true>);
   }
   if (d.groups == 4) {   // a quarter wavefront per row

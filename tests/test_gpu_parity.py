@@ -563,6 +563,61 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
         assert torch.equal(h, torch.relu(z))
 
 
+@pytest.mark.parametrize("f", [4, 16, 20, 32, 36, 64, 72, 100, 128, 192, 256])
+@pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "hub", "few"])
+def test_spmm_small_matrices_without_hubs(kind, f):
+    """From 1 M entries on a matrix whose rows are all of a size is swept; one row of many entries, or fewer entries, and it
+    is not.  Rows of 20 to 52 entries, some empty, some of exactly a piece's 256; products, sums and the layer."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(f)
+    m, k = (28_000 if kind == "few" else 31_003), 30_011
+    deg = torch.randint(20, 53, (m,), device="cuda", generator=gen)
+    if kind == "empty rows":
+        deg[::7] = 0
+        deg[1::7] += 24
+    if kind == "long":
+        deg[::500] = 256
+    if kind == "hub":
+        deg[17] = 12_000
+    rp = torch.zeros(m + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(deg, 0)
+    nnz = int(rp[-1])
+    assert (nnz < 1 << 20) == (kind == "few")
+    row = torch.repeat_interleave(torch.arange(m, device="cuda"), deg)
+    ci = torch.randint(k, (nnz,), device="cuda", generator=gen)
+    if kind == "local":
+        ci = (row * k // m // 2000 * 2000 + ci % 2000).clamp(max=k - 1)
+    ci = torch.sort(row * k + ci)[0] % k
+    v = torch.randn(nnz, device="cuda", generator=gen)
+    B = torch.randn(k, f, device="cuda", generator=gen)
+    ci32 = ci.to(torch.int32)
+    ws = sagnn.spmm_csr_prepare(rp, ci32, v, k, f)
+    assert ws.info()["mode"] == (0 if kind in ("hub", "few") else 1)
+    ref = torch.zeros(m, f, dtype=torch.float64, device="cuda")
+    size = torch.zeros_like(ref)
+    for at in range(0, nnz, 1 << 18):
+        s = slice(at, min(nnz, at + (1 << 18)))
+        t = v[s, None].double() * B[ci[s]].double()
+        ref.index_add_(0, row[s], t)
+        size.index_add_(0, row[s], t.abs())
+    # any order of a row's additions: at most its number of entries 2^-24 of the sum of the terms' sizes
+    bound = (deg.double() + 2)[:, None] * 2.0**-24 * size
+    C = sagnn.spmm_csr_tallskinny(rp, ci32, v, B, ws=ws)
+    assert bool(((C.double() - ref).abs() <= bound).all())
+    C0 = torch.randn(m, f, device="cuda", generator=gen)
+    C2 = sagnn.spmm_csr_tallskinny(rp, ci32, v, B, C=C0.clone(), accumulate=True, ws=ws)
+    assert bool(((C2.double() - ref - C0.double()).abs() <= bound + 2.0**-22 * (size + C0.abs().double())).all())
+    W = torch.randn(f, 32, device="cuda", generator=gen)
+    T, Z, _ = sagnn.gcn_layer_fwd(rp, ci32, v, B, W, act=sagnn.ACT_IDENTITY, ws=ws, want_h=False)
+    assert torch.equal(T, C)
+    Zn = Z
+    if sagnn.gcn_layer_fwd_form(ws, f, 32, sagnn.GEMM_FP32) != 0:
+        _, Zn, _ = sagnn.gcn_layer_fwd(rp, ci32, v, B, W, act=sagnn.ACT_IDENTITY, ws=ws, want_h=False, want_t=False)
+    want, wsize = ref @ W.double(), size @ W.abs().double()
+    for z in (Z, Zn):
+        assert bool(((z.double() - want).abs() <= (deg.double()[:, None] + f + 4) * 2.0**-24 * wsize).all())
+
+
 @pytest.mark.parametrize("f,n,more", [(24, 270_000, 280_000), (60, 180_000, 190_000)])
 def test_spmm_workspace_of_a_matrix_with_more_rows_serves_one_with_fewer(f, n, more):
     """With more rows the copy of B to aligned rows does not pay and the workspace has no room for it; the matrix with
