@@ -747,7 +747,7 @@ __device__ __forceinline__ void walk_stream(const uint32_t* __restrict__ cw, con
 // ODD: rows of any multiple of 4 floats instead of the kernel's full width.  The lanes beyond the end of the row work
 // on its last FPL floats a second time: same addresses, same values, so neither loads nor accumulator updates nor
 // stores need a mask, and the accumulator rows are as long as the rows themselves.
-template <int FPL, int U, bool BUF, bool ODD>
+template <int FPL, int U, bool BUF, bool ODD, bool TURN>
 __global__ __launch_bounds__(256) void spmm_sweep_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
   const float* __restrict__ vw = vals + base;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
-  walk_stream<FPL, U, BUF, ODD && FPL <= 2, true>(cw, vw, len, rs, B, d, loff, my, kRow);
+  walk_stream<FPL, U, BUF, ODD && FPL <= 2, TURN>(cw, vw, len, rs, B, d, loff, my, kRow);
 
 #pragma unroll 1
   for (int s = 0; s < d.slots; ++s) {
@@ -1464,13 +1464,16 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // the former as a row block 590, 279, 134 -> 424, 200, 105; random columns, 250 k vertices of 60 1864, 973, 501 -> 1265,
   // 642, 329; 1 M of 40 5825, 2829, 1461 -> 5200, 2598, 1298.
   // Not where the columns that neighbouring rows choose from fit the L2s anyway (communities of 19 k, f = 256: 1242 as
-  // before, 1412 so; of 5 k: 480, 536), where there are too many for a second use (a rank's rows), and not with hubs, whose
+  // before, 1412 so; of 5 k: 480, 536) or nearly and rows are short (communities of 44 k, 16 a row, f = 64, 256 398, 1538
+  // and 421, 1649; 36 a row 695, 2828 and 786, 2539; of 125 k, 16 a row 1129, 4835 and 1180, 4696; 24 a row 1557, 6355 and
+  // 1338, 5005), where there are too many for a second use (a rank's rows), and not with hubs, whose
   // rows hit in any case (233 k vertices of 489: 5627, 7060).
   const bool local = tot.locality >= kLocalPermille;
   const double span = (double)k * tot.span / 1000.0;
   const bool col_groups = f >= 64 && (f & 63) == 0 && opt.groups == 0 && opt.slab_width == 0 && opt.sync_slabs <= 0 &&
                           opt.barriers != 1 && opt.pace_ps_per_step <= 0 && span >= 40000.0 &&
-                          16384.0 * (double)nnz >= 0.5 * span * (double)m && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz;
+                          16384.0 * (double)nnz >= 0.5 * span * (double)m && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz &&
+                          (!local || (nnz >= 18 * m && (f > 64 || span >= 60000.0)));
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
@@ -1884,13 +1887,20 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     if (fw > 64 || fuse) return SAGNN_EINVAL;
     return buf ? go_group(&spmm_sweep_group_kernel<4, 4, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 4, 8, false, 0, true>);
   }
-  if (fw == 256) return buf ? go(spmm_sweep_kernel<4, 8, true, false>) : go(spmm_sweep_kernel<4, 8, false, false>);
-  if (fw == 128) return buf ? go(spmm_sweep_kernel<2, 8, true, false>) : go(spmm_sweep_kernel<2, 8, false, false>);
-  if (fw == 64) return buf ? go(spmm_sweep_kernel<1, 8, true, false>) : go(spmm_sweep_kernel<1, 8, false, false>);
   if (fw > 256) return SAGNN_EINVAL;
-  if (fw > 128) return buf ? go(spmm_sweep_kernel<4, 8, true, true>) : go(spmm_sweep_kernel<4, 8, false, true>);
-  if (fw > 64) return buf ? go(spmm_sweep_kernel<2, 8, true, true>) : go(spmm_sweep_kernel<2, 8, false, true>);
-  return buf ? go(spmm_sweep_kernel<1, 8, true, true>) : go(spmm_sweep_kernel<1, 8, false, true>);
+  // Up to 128 columns a matrix whose rows of B are hardly used twice gains nothing by an order among the wavefronts, and
+  // looking for one's turn before every batch costs it up to 3 % (676 k vertices of 11, f = 64, 96 229, 362 us, without 224,
+  // 354; at 256 columns it gains, 835 and 808).
+  const bool turns = d.col_slab > 0 || d.f > 128;   // (otherwise one row per load is for such matrices, see sweep_prepare)
+#define SAGNN_ONE(FPL_, ODD_, TURN_) \
+  (buf ? go(spmm_sweep_kernel<FPL_, 8, true, ODD_, TURN_>) : go(spmm_sweep_kernel<FPL_, 8, false, ODD_, TURN_>))
+  if (fw == 256) return SAGNN_ONE(4, false, true);
+  if (fw == 128) return turns ? SAGNN_ONE(2, false, true) : SAGNN_ONE(2, false, false);
+  if (fw == 64) return turns ? SAGNN_ONE(1, false, true) : SAGNN_ONE(1, false, false);
+  if (fw > 128) return SAGNN_ONE(4, true, true);
+  if (fw > 64) return turns ? SAGNN_ONE(2, true, true) : SAGNN_ONE(2, true, false);
+  return turns ? SAGNN_ONE(1, true, true) : SAGNN_ONE(1, true, false);
+#undef SAGNN_ONE
 }
 
 int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const float* B, int64_t ldb,
