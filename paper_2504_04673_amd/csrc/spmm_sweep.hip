@@ -1888,14 +1888,14 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     return buf ? go_group(&spmm_sweep_group_kernel<4, 4, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 4, 8, false, 0, true>);
   }
   if (fw > 256) return SAGNN_EINVAL;
-  // Up to 128 columns a matrix whose rows of B are hardly used twice gains nothing by an order among the wavefronts, and
+  // Under 128 columns a matrix whose rows of B are hardly used twice gains nothing by an order among the wavefronts, and
   // looking for one's turn before every batch costs it up to 3 % (676 k vertices of 11, f = 64, 96 229, 362 us, without 224,
-  // 354; at 256 columns it gains, 835 and 808).
+  // 354; a rank's 440 k rows of 20 f = 96 513, 499).  At 128 it gains (a rank's step, 867 k rows of 15, 2207 us without, 2168).
   const bool turns = d.col_slab > 0 || d.f > 128;   // (otherwise one row per load is for such matrices, see sweep_prepare)
 #define SAGNN_ONE(FPL_, ODD_, TURN_) \
   (buf ? go(spmm_sweep_kernel<FPL_, 8, true, ODD_, TURN_>) : go(spmm_sweep_kernel<FPL_, 8, false, ODD_, TURN_>))
   if (fw == 256) return SAGNN_ONE(4, false, true);
-  if (fw == 128) return turns ? SAGNN_ONE(2, false, true) : SAGNN_ONE(2, false, false);
+  if (fw == 128) return SAGNN_ONE(2, false, true);
   if (fw == 64) return turns ? SAGNN_ONE(1, false, true) : SAGNN_ONE(1, false, false);
   if (fw > 128) return SAGNN_ONE(4, true, true);
   if (fw > 64) return turns ? SAGNN_ONE(2, true, true) : SAGNN_ONE(2, true, false);
