@@ -1553,6 +1553,14 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const int64_t slab_bytes = opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : (col_groups && !local && f > 128 ? 32 * f : 4096)) << 10;
   int64_t S = slab_bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * slab_bytes) : kSweepMaxSlabs;
   if (S < 8) S = 8;
+  // Where the order of the rows carries locality at least four slabs (eight with 64 entries a row) in the columns that
+  // neighbouring rows choose from: slabs of 4 MB may hold all of them, and then nothing keeps the wavefronts of a window in
+  // step, and a row's entries are one long sum.  Sixteen communities, us and error against 64 bits before and so: 100 k
+  // vertices of 40, f = 100, 256 204, 448, 11.4e-8, 8.9e-8 and 179, 378, 7.6e-8, 7.6e-8; 250 k of 100, f = 128, 256 1414,
+  // 2441, 13.2e-8, 10.5e-8 and 1273, 2098, 9.5e-8, 9.5e-8; 250 k of 40, f = 64 284, 11.4e-8 and 276, 7.6e-8 (100 k, f = 64
+  // 106 and 109, f = 32 48 and 52: not there).
+  if (local && opt.slab_kb == 0 && (f > 64 || (f > 32 && b_bytes >= (48ll << 20))))
+    S = std::max(S, (int64_t)((nnz >= 64 * m ? 8.0 : 4.0) * (double)k / std::max(span, 1.0) + 0.5));
   // Small matrices: the columns that neighbouring rows choose from in four slabs where the order of the rows carries
   // locality, in eight where all choose from the same, but four where nonzero splitting would add as a tree, and one per 64
   // entries of a row at 17 to 32 columns, where a stream has two rows.  Error against 64 bits by nonzero splitting and so:
