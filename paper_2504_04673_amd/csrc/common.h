@@ -136,9 +136,7 @@ struct SpmmWsHeader {       // first 256 bytes of the SpMM workspace (device cop
   int32_t max_slab;         // widest column slab of B per launch (256 or 128)
   int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
   int32_t launch_waves;     // wavefronts per launch (0: all in one)
-  int32_t apart;            // a small matrix without hubs: the layer's dense transform is not the sweep's epilogue.  Its wavefronts
-                            // may hold fewer than 16 rows, which the epilogue multiplies all the same: 60 k vertices of 20 in
-                            // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
+  int32_t fused_waves;      // the same with the layer's dense transform behind the sweep
 };
 static_assert(sizeof(SpmmWsHeader) <= 256, "header must fit its slot");
 
@@ -257,6 +255,7 @@ struct SpmmHostDesc {
   int32_t max_slab;         // widest column slab of B per launch (256, or 128 for the lane-group kernels at wider f)
   int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
   int32_t launch_waves;     // wavefronts per launch (0: all in one)
+  int32_t fused_waves;      // the same with the layer's dense transform behind the sweep
   int32_t apart;            // a small matrix without hubs: the layer's dense transform is not the sweep's epilogue.  Its wavefronts
                             // may hold fewer than 16 rows, which the epilogue multiplies all the same: 60 k vertices of 20 in
                             // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253

@@ -720,7 +720,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   desc.sync_timeout_ticks = h.sync_timeout_ticks; desc.sync_test_extra = h.sync_test_extra;
   desc.slots = h.slots;
   desc.max_slab = h.max_slab > 0 ? h.max_slab : 256;
-  desc.col_slab = h.col_slab; desc.launch_waves = h.launch_waves;
+  desc.col_slab = h.col_slab; desc.launch_waves = h.launch_waves; desc.fused_waves = h.fused_waves;
   desc.apart = plan.use_sweep && !sweep_size(k, nnz, f) && opt.schedule != 2;
   desc.barriers = h.barriers; desc.pace_ps_per_step = h.pace_ps_per_step > 0 ? h.pace_ps_per_step : 0;
   desc.mean_steps = plan.mean_steps;

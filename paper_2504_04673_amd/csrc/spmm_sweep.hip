@@ -1464,16 +1464,17 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // the former as a row block 590, 279, 134 -> 424, 200, 105; random columns, 250 k vertices of 60 1864, 973, 501 -> 1265,
   // 642, 329; 1 M of 40 5825, 2829, 1461 -> 5200, 2598, 1298.
   // Not where the columns that neighbouring rows choose from fit the L2s anyway (communities of 19 k, f = 256: 1242 as
-  // before, 1412 so; of 5 k: 480, 536) or nearly and rows are short (communities of 44 k, 16 a row, f = 64, 256 398, 1538
-  // and 421, 1649; 36 a row 695, 2828 and 786, 2539; of 125 k, 16 a row 1129, 4835 and 1180, 4696; 24 a row 1557, 6355 and
-  // 1338, 5005), where there are too many for a second use (a rank's rows), and not with hubs, whose
-  // rows hit in any case (233 k vertices of 489: 5627, 7060).
+  // before, 1412 so; of 5 k: 480, 536) or nearly (of 44 k, 36 a row, f = 64, 128, 256 695, 1428, 2828 and 786, 1400, 2539, and
+  // inference, whose dense part needs the whole width in one launch, at f = 128 1628 and 1831) or rows are short (of 125 k,
+  // 16 a row, f = 64, 256 1129, 4835 and 1180, 4696; 24 a row 1557, 6355 and 1338, 5005), where there are too many for a
+  // second use (a rank's rows; random columns, 500 k of 18, f = 128 661 and 653, 1 M of 30 in inference 2278 and 2392), and
+  // not with hubs, whose rows hit in any case (233 k vertices of 489: 5627, 7060).
   const bool local = tot.locality >= kLocalPermille;
   const double span = (double)k * tot.span / 1000.0;
   const bool col_groups = f >= 64 && (f & 63) == 0 && opt.groups == 0 && opt.slab_width == 0 && opt.sync_slabs <= 0 &&
                           opt.barriers != 1 && opt.pace_ps_per_step <= 0 && span >= 40000.0 &&
-                          16384.0 * (double)nnz >= 0.5 * span * (double)m && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz &&
-                          (!local || (nnz >= 18 * m && (f > 64 || span >= 60000.0)));
+                          16384.0 * (double)nnz >= 0.6 * span * (double)m && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz &&
+                          (!local || (nnz >= 18 * m && span >= 60000.0));
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
@@ -1734,6 +1735,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.max_slab = narrow_slabs && R == 2 ? 128 : 256;
   h.col_slab = col_groups ? 64 : 0;
   h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
+  h.fused_waves = local ? h.launch_waves / 2 : 0;
   out->mean_steps = rec.scan.mean_steps;
   out->max_steps = rec.scan.max_steps;
   out->use_sweep = true;
@@ -1954,10 +1956,12 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    // (two generations a launch for column groups, as sweep_launch, but at 128 columns only, 1 M vertices in communities,
-    // 30 M entries: 1713 -> 1592 us.  At 64 and 256 the dense parts of workgroups that end together are left without
-    // gathers beside them: 803 -> 822, 3862 -> 4120.)
-    const unsigned per = f_in == 128 && d.col_slab > 0 && d.launch_waves >= 8 ? (unsigned)(d.launch_waves / 8) : blocks;
+    // (two generations a launch for column groups, as sweep_launch, but at 128 columns only, where the order of the rows
+    // carries locality and the dense part is not long: 1.6 M vertices of 40 in communities to 40 columns in fp32 3950 -> 3718
+    // us, to 128 in bfloat16 4042 -> 3795, in fp32 4086 -> 4132; random columns, 500 k of 24, 976 -> 1096.  At 64 and 256 the
+    // dense parts of workgroups that end together are left without gathers beside them: 803 -> 822, 3862 -> 4120.)
+    const bool brief = mode != 0 || fb.f_out <= 64;
+    const unsigned per = f_in == 128 && brief && d.fused_waves >= 4 ? (unsigned)(d.fused_waves / 4) : blocks;
     for (unsigned b0 = 0; b0 < blocks; b0 += per) {
       sd.block0 = (int32_t)b0;
       hipLaunchKernelGGL(kern, dim3(blocks - b0 < per ? blocks - b0 : per), dim3(256), lds, s,

@@ -519,7 +519,7 @@ def test_spmm_rows_moved_to_cache_lines(f, n, sweep, monkeypatch):
 
 
 @pytest.mark.parametrize("f,n,deg,parts", [(64, 300_000, 20, 1), (128, 150_000, 24, 1), (192, 60_000, 60, 1), (256, 60_000, 60, 1),
-                                           (64, 300_000, 20, 4), (256, 180_000, 20, 4)])
+                                           (64, 300_000, 20, 4), (256, 260_000, 20, 4)])
 def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
     """Matrices without hubs whose rows of B are wanted several times by rows that are resident together: 64 columns a
     launch, several launches for many rows.  Rows of B with gaps, an operand narrower than the workspace was prepared for
