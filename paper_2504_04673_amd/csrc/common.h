@@ -287,6 +287,10 @@ int launch_spmm(const int32_t* rowptr, const int32_t* colidx, const float* val, 
                 int64_t k, int64_t nnz, const float* B, int64_t ldb, int32_t f, float* C,
                 int64_t ldc, int32_t accumulate, void* ws, size_t ws_bytes, hipStream_t s);
 
+// rows of H into `out`, and of a second list into `out2` in the same launch (N2 = 0: none)
+int launch_pack(const float* H, int64_t n, int64_t ldh, int32_t f, const int32_t* rows, int64_t N, float* out,
+                const int32_t* rows2, int64_t N2, float* out2, int64_t ldo, hipStream_t s);
+
 // nonzero-splitting part (spmm_flat.hip)
 struct FlatArgs {
   int64_t rows, nnz, nchunks;          // of the CSR being walked

@@ -16,12 +16,22 @@ typedef float vec4 __attribute__((ext_vector_type(4)));  // one 16-byte piece
 
 // f4 = f/4 16-byte pieces per row.  blockDim = (px, py) with px a power of two <= 64 and
 // px*py = kPackThreads, so a wavefront covers 64/px rows and px adjacent pieces of each; no
-// integer division is needed.  A block owns kUnroll*py consecutive output rows.
+// integer division is needed.  A block owns kUnroll*py consecutive output rows of one of two lists (the second may be
+// empty): the first `split` blocks those of the first.
+struct PackList {
+  const int32_t* rows;
+  int64_t N;
+  vec4* out;
+};
 __global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(
-    const vec4* __restrict__ H, int64_t n, int64_t ldh4, int32_t f4,
-    const int32_t* __restrict__ rows, int64_t N, vec4* __restrict__ out, int64_t ldo4) {
+    const vec4* __restrict__ H, int64_t n, int64_t ldh4, int32_t f4, const PackList one, const PackList two,
+    uint32_t split, int64_t ldo4) {
   const int px = blockDim.x, py = blockDim.y;
-  const int64_t r0 = (int64_t)blockIdx.x * (kUnroll * py) + threadIdx.y;
+  const bool first = blockIdx.x < split;
+  const int32_t* __restrict__ rows = first ? one.rows : two.rows;
+  vec4* __restrict__ out = first ? one.out : two.out;
+  const int64_t N = first ? one.N : two.N;
+  const int64_t r0 = (int64_t)(first ? blockIdx.x : blockIdx.x - split) * (kUnroll * py) + threadIdx.y;
   int64_t src[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
@@ -48,25 +58,29 @@ __global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(
 }
 
 }  // namespace
+
+int launch_pack(const float* H, int64_t n, int64_t ldh, int32_t f, const int32_t* rows, int64_t N, float* out,
+                const int32_t* rows2, int64_t N2, float* out2, int64_t ldo, hipStream_t s) {
+  if (n < 0 || N < 0 || N2 < 0 || f <= 0 || (f & 3) || ldh < f || ldo < f || (ldh & 3) || (ldo & 3)) return SAGNN_EINVAL;
+  if (N == 0 && N2 == 0) return SAGNN_OK;
+  if (!H || !aligned16(H) || (N > 0 && (!rows || !out || !aligned16(out))) || (N2 > 0 && (!rows2 || !out2 || !aligned16(out2))))
+    return SAGNN_EINVAL;
+  const int32_t f4 = f / 4;
+  int px = 1;
+  while (px < f4 && px < 64) px <<= 1;
+  const int py = kPackThreads / px;
+  const int64_t split = ceil_div(N, (int64_t)kUnroll * py), blocks = split + ceil_div(N2, (int64_t)kUnroll * py);
+  if (blocks > 0x7FFFFFFFll) return SAGNN_EINVAL;
+  hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)blocks), dim3(px, py), 0, s, reinterpret_cast<const vec4*>(H), n,
+                     ldh / 4, f4, PackList{rows, N, reinterpret_cast<vec4*>(out)},
+                     PackList{rows2, N2, reinterpret_cast<vec4*>(out2)}, (uint32_t)split, ldo / 4);
+  SAGNN_LAUNCH_CHECK();
+  return SAGNN_OK;
+}
 }  // namespace sagnn
 
 SAGNN_EXPORT int spmm_pack_rows(const float* d_H, int64_t n, int64_t ldh, int32_t f,
                                 const int32_t* d_rows, int64_t N, float* d_out, int64_t ldo,
                                 void* stream) {
-  using namespace sagnn;
-  if (n < 0 || N < 0 || f <= 0 || (f & 3) || ldh < f || ldo < f || (ldh & 3) || (ldo & 3))
-    return SAGNN_EINVAL;
-  if (N == 0) return SAGNN_OK;
-  if (!d_H || !d_rows || !d_out || !aligned16(d_H) || !aligned16(d_out)) return SAGNN_EINVAL;
-  const int32_t f4 = f / 4;
-  int px = 1;
-  while (px < f4 && px < 64) px <<= 1;
-  const int py = kPackThreads / px;
-  const int64_t blocks = ceil_div(N, (int64_t)kUnroll * py);
-  if (blocks > 0x7FFFFFFFll) return SAGNN_EINVAL;
-  hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)blocks), dim3(px, py), 0,
-                     (hipStream_t)stream, reinterpret_cast<const vec4*>(d_H), n, ldh / 4, f4,
-                     d_rows, N, reinterpret_cast<vec4*>(d_out), ldo / 4);
-  SAGNN_LAUNCH_CHECK();
-  return SAGNN_OK;
+  return sagnn::launch_pack(d_H, n, ldh, f, d_rows, N, d_out, nullptr, 0, nullptr, ldo, (hipStream_t)stream);
 }
