@@ -161,6 +161,42 @@ def test_stage_loop_with_empty_block_and_capacity_error():
     assert e.value.code == -2
 
 
+@pytest.mark.parametrize("f", [4, 100, 128, 256])
+@pytest.mark.parametrize("sizes", [[33], [32, 31], [1, 0], [0, 1], [0, 0, 65], [64, 7, 32], [5, 1000, 0, 40, 9]])
+def test_stage_loop_packs_two_stages_at_a_time(sizes, f):
+    """On one stream the rows of an even stage and of the next are packed in one launch: odd numbers of stages, empty lists
+    on either side, lists that end inside a workgroup's rows.  Same bits as on two streams, where each has its own, and the
+    two buffers hold the last two stages' rows."""
+    gen = torch.Generator().manual_seed(f + len(sizes))
+    m, n, cap = 300, 1200, max(max(sizes), 1)
+    H = torch.randn(n, f, generator=gen).cuda()
+    stages = []
+    for N in sizes:
+        deg = torch.randint(0, 6, (m,), generator=gen) * (N > 0)
+        rp = torch.zeros(m + 1, dtype=torch.int32)
+        rp[1:] = torch.cumsum(deg, 0)
+        nnz = int(rp[-1])
+        stages.append({"rowptr": rp.cuda(), "colidx": torch.randint(max(N, 1), (nnz,), generator=gen).to(torch.int32).cuda(),
+                       "val": torch.randn(nnz, generator=gen).cuda(),
+                       "rows": torch.randperm(n, generator=gen)[:N].sort()[0].to(torch.int32).cuda()})
+    out = []
+    for side in (None, torch.cuda.Stream()):
+        T = [torch.full((cap, f), 3.0, device="cuda") for _ in range(2)]
+        Z = torch.full((m, f), 7.0, device="cuda")
+        sagnn.spmm_stage_loop(stages, m, H, T[0], T[1], Z, pack_stream=side)
+        torch.cuda.synchronize()
+        out.append(Z)
+        for k in range(max(len(sizes) - 2, 0), len(sizes)):
+            assert torch.equal(T[k & 1][:sizes[k]], H[stages[k]["rows"].long()])
+    assert torch.equal(out[0], out[1])
+    want = torch.zeros(m, f, dtype=torch.float64, device="cuda")
+    for st, N in zip(stages, sizes):
+        row = torch.repeat_interleave(torch.arange(m, device="cuda"), torch.diff(st["rowptr"]).long())
+        want.index_add_(0, row, st["val"][:, None].double() * H[st["rows"].long()][st["colidx"].long()].double())
+    # at most 25 terms a row: 32 2^-24 of sums of at most 25 products of two normal numbers
+    assert float((out[0].double() - want).abs().max()) <= 32 * 2.0**-24 * 25 * 36
+
+
 def test_volume_stats_cfg1_all_row_blocks(cfg1):
     """Counts |NnzCols(i,q)| of all P = 4 row blocks from the GPU plan; statistics from the
     library against the oracle's, sparsity-aware and sparsity-oblivious."""
