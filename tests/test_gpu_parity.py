@@ -564,10 +564,10 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
 
 
 @pytest.mark.parametrize("f", [4, 16, 20, 32, 36, 64, 72, 100, 128, 192, 256])
-@pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "hub", "few"])
+@pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "around 64", "hub", "few"])
 def test_spmm_small_matrices_without_hubs(kind, f):
     """From 1 M entries on a matrix whose rows are all of a size is swept; one row of many entries, or fewer entries, and it
-    is not.  Rows of 20 to 52 entries, some empty, some of exactly a piece's 256; products, sums and the layer."""
+    is not.  Rows of 20 to 52 entries, some empty, some of exactly a piece's 256, or of 60 to 92; products, sums and the layer."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(f)
     m, k = (28_000 if kind == "few" else 31_003), 30_011
@@ -577,6 +577,8 @@ def test_spmm_small_matrices_without_hubs(kind, f):
         deg[1::7] += 24
     if kind == "long":
         deg[::500] = 256
+    if kind == "around 64":
+        deg += 40
     if kind == "hub":
         deg[17] = 12_000
     rp = torch.zeros(m + 1, dtype=torch.int32, device="cuda")
