@@ -772,7 +772,11 @@ SAGNN_EXPORT int spmm_csr_prepare_tuned(const int32_t* d_rowptr, const int32_t* 
     if (rc != SAGNN_OK) { cleanup(); return rc; }
     last = c;
     SpmmHostDesc desc{};
-    if (!spmm_desc_get(d_ws, &desc) || desc.mode != 1) { best = c; break; }   // nothing to tune
+    if (!spmm_desc_get(d_ws, &desc) || desc.mode != 1) {
+      if (c > 0) continue;   // (a higher threshold may leave too few long rows; the plans timed so far stay)
+      best = c;              // nothing to tune
+      break;
+    }
     if (!e0) {
       hipError_t e = hipEventCreate(&e0);
       if (e == hipSuccess) e = hipEventCreate(&e1);

@@ -1433,7 +1433,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
     // (without hubs every row that may be is long: sixteen short rows of up to 63 entries are several times the stream of a
     // small matrix' other wavefronts.  15 k rows of 80, f = 64, 256 32, 139 us by nonzero splitting, 46, 126 with rows from
     // 64 entries on long, 27, 78 from 16 on)
-    const int32_t min_long = no_hubs && opt.min_long == 0 ? kSweepMinLong : opt.min_long;
+    const int32_t min_long = no_hubs && opt.min_long <= 0 ? kSweepMinLong : opt.min_long;   // (negative: "where 64 is picked")
     const int rc = sweep_plan_rows(d_rowptr, d_colidx, m, k, nnz, min_long, piece_max, ws, L, s, &tot, opt.short_rows >= 0);
     if (rc != SAGNN_OK) return rc;
   }

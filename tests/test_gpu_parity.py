@@ -1099,6 +1099,27 @@ def test_spmm_prepare_tuned_keeps_a_correct_plan(monkeypatch):
     assert_close(got0, ref, zabs, RTOL_SPMM, "plain schedule through the tuned entry point")
 
 
+@pytest.mark.parametrize("f,n", [(16, 20_000), (32, 20_000), (64, 20_000), (64, 60_000)])
+def test_spmm_prepare_tuned_goes_on_behind_a_variant_that_cannot_be_swept(f, n):
+    """Rows of 60 to 92 entries: the default plan is swept, the variants whose threshold is 96 entries would leave no
+    row to the sweep.  The tuned preparation keeps a plan that it has timed, on a small matrix and on one of 4.5 M entries."""
+    gen = torch.Generator(device="cuda").manual_seed(f)
+    deg = torch.randint(60, 93, (n,), device="cuda", generator=gen)
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(deg, 0)
+    nnz = int(rp[-1])
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), deg)
+    ci = (torch.sort(row * n + torch.randint(n, (nnz,), device="cuda", generator=gen))[0] % n).to(torch.int32)
+    v, B = torch.randn(nnz, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    assert nnz >= 1 << 20 and sagnn.spmm_csr_prepare(rp, ci, v, n, f).info()["mode"] == 1
+    ws = sagnn.spmm_csr_prepare_tuned(rp, ci, v, B)
+    assert ws.info()["mode"] == 1 and ws.choice["best_us"] > 0
+    C = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+    ref = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double(), (n, n)) @ B.double()
+    size = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double().abs(), (n, n)) @ B.double().abs()
+    assert bool(((C.double() - ref).abs() <= (deg.double() + 2)[:, None] * 2.0**-24 * size).all())
+
+
 def test_spmm_rmat_with_and_without_sweep(monkeypatch):
     g = synth.rmat_graph(60_000, 4_000_000, 9)
     H = synth.normal((g.n, 128), 9, synth.STREAM_H)
