@@ -247,9 +247,11 @@ typedef struct sagnn_spmm_options {
                               fit).  Measured slower on the free-running sweep (more wavefronts
                               thrash the L2 more) and equal under pacing; off unless asked for     */
   int32_t slab_width;      /* widest column slab of B one launch covers: 0 = 256, or 64 on matrices without
-                              hubs whose neighbouring rows share rows of B (widths that are multiples of
-                              64, groups = 0); 128 = operands wider
-                              than 128 are processed as 128-wide slabs by the kernels that fetch two
+                              hubs where rows that are resident together use rows of B several times,
+                              neighbours in communities or any rows of a matrix of few columns (widths
+                              that are multiples of 64; groups = 0 and neither interval barriers nor
+                              pacing nor sync_slabs asked for; spmm_csr_launch_info tells); 128 =
+                              operands wider than 128 are processed as 128-wide slabs by the kernels that fetch two
                               rows of B per load (faster on the 2.45 M-vertex power-law graph at
                               f = 256, slower on the community-ordered one; the measured choice of
                               spmm_csr_prepare_tuned tries it)                                       */
@@ -344,6 +346,11 @@ int spmm_csr_prepare_tuned(const int32_t* d_rowptr, const int32_t* d_colidx, con
  * average is [2] / ([1] * [11]).
  * SAGNN_EINVAL if the workspace is unknown. */
 int spmm_csr_schedule_info(const void* d_ws, int64_t* h_info);
+/* How the product of a prepared workspace is launched (host query, no GPU work).  h_info[4], all 0 without a sweep:
+ * [0] columns of B per launch where the width is a multiple of them (0 = all that one kernel takes),
+ * [1] wavefronts per launch then, [2] the same of the layer without A H at 128 columns and a short dense part
+ * (0 = all in one), [3] slabs of B that a stream passes over.  SAGNN_EINVAL if the workspace is unknown. */
+int spmm_csr_launch_info(const void* d_ws, int64_t* h_info);
 /* Forget the host descriptor of a prepared workspace.  Call it before the workspace memory is
  * freed or reused for something else: afterwards the address is unknown to the library again
  * (spmm_csr_tallskinny with it returns SAGNN_EINVAL until it is prepared anew), and nothing of

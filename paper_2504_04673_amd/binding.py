@@ -17,7 +17,7 @@ PLAN_VALIDATE, PLAN_OBLIVIOUS, PLAN_MULTIPASS = 1, 2, 4
 EXPORTS = [
     "sagnn_strerror", "sagnn_last_hip_error", "sagnn_version",
     "spmm_plan_workspace_bytes", "spmm_plan_needed_rows", "spmm_plan_needed_rows_noalloc", "spmm_pack_rows",
-    "spmm_csr_workspace_bytes", "spmm_csr_workspace_bytes_opt", "spmm_csr_tile_info", "spmm_csr_prepare", "spmm_csr_prepare_opt", "spmm_csr_prepare_tuned", "spmm_csr_schedule_info",
+    "spmm_csr_workspace_bytes", "spmm_csr_workspace_bytes_opt", "spmm_csr_tile_info", "spmm_csr_prepare", "spmm_csr_prepare_opt", "spmm_csr_prepare_tuned", "spmm_csr_schedule_info", "spmm_csr_launch_info",
     "spmm_csr_release", "spmm_csr_tallskinny",
     "dense_gemm_act", "gcn_layer_fwd", "gcn_layer_fwd_fused", "gcn_layer_fwd_form", "gcn_bwd_workspace_bytes", "gcn_layer_bwd",
     "spmm_split_workspace_bytes", "spmm_split_colblocks", "spmm_stage_loop", "spmm_volume_stats",
@@ -128,6 +128,7 @@ def lib():
         L.spmm_csr_prepare_opt.argtypes = [vp, vp, vp, i64, i64, i64, i32, vp, sz, vp, vp]
         L.spmm_csr_prepare_tuned.argtypes = [vp, vp, vp, i64, i64, i64, i32, vp, sz, vp, i64, vp, i64, vp, vp, vp]
         L.spmm_csr_schedule_info.argtypes = [vp, vp]
+        L.spmm_csr_launch_info.argtypes = [vp, vp]
         L.spmm_csr_release.argtypes = [vp]
         L.spmm_csr_tallskinny.argtypes = [vp, vp, vp, i64, i64, i64, vp, i64, i32, vp, i64, i32, vp,
                                           sz, vp]
@@ -333,6 +334,12 @@ class SpmmWorkspace:
                 "split_rows", "has_empty_rows", "intervals", "sync_slabs", "gave_up_offset", "groups",
                 "pace_ps_per_step", "barriers", "slots", "longest_stream_steps")
         return dict(zip(keys, (int(x) for x in a)))
+
+    def launch_info(self) -> dict:
+        """How the product and the layer are launched (see spmm_csr_launch_info)."""
+        a = np.zeros(4, dtype=np.int64)
+        _check(lib().spmm_csr_launch_info(_ptr(self.buf), _host(a)), "spmm_csr_launch_info")
+        return dict(zip(("columns", "waves", "layer_waves", "slabs"), (int(x) for x in a)))
 
     def tile_info(self) -> dict:
         """What a preparation with dense tiles decided (see spmm_csr_tile_info)."""

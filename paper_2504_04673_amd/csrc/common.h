@@ -253,6 +253,7 @@ struct SpmmHostDesc {
   int32_t slots;
   int32_t barriers, pace_ps_per_step;
   int32_t max_slab;         // widest column slab of B per launch (256, or 128 for the lane-group kernels at wider f)
+  int32_t n_slabs;          // slabs of B that a stream passes over
   int32_t col_slab;         // columns per launch where the width is a multiple of it (0: as max_slab says)
   int32_t launch_waves;     // wavefronts per launch (0: all in one)
   int32_t fused_waves;      // the same with the layer's dense transform behind the sweep

@@ -720,6 +720,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   desc.sync_timeout_ticks = h.sync_timeout_ticks; desc.sync_test_extra = h.sync_test_extra;
   desc.slots = h.slots;
   desc.max_slab = h.max_slab > 0 ? h.max_slab : 256;
+  desc.n_slabs = h.n_slabs;
   desc.col_slab = h.col_slab; desc.launch_waves = h.launch_waves; desc.fused_waves = h.fused_waves;
   desc.apart = plan.use_sweep && !sweep_size(k, nnz, f) && opt.schedule != 2;
   desc.barriers = h.barriers; desc.pace_ps_per_step = h.pace_ps_per_step > 0 ? h.pace_ps_per_step : 0;
@@ -899,6 +900,19 @@ SAGNN_EXPORT int spmm_csr_schedule_info(const void* d_ws, int64_t* h_info) {
   h_info[13] = d.mode == 1 ? d.barriers : 0;
   h_info[14] = d.mode == 1 ? d.slots : 0;
   h_info[15] = d.mode == 1 ? (int64_t)d.max_steps : 0;
+  return SAGNN_OK;
+}
+
+SAGNN_EXPORT int spmm_csr_launch_info(const void* d_ws, int64_t* h_info) {
+  using namespace sagnn;
+  if (!d_ws || !h_info) return SAGNN_EINVAL;
+  SpmmHostDesc d{};
+  if (!spmm_desc_get(d_ws, &d)) return SAGNN_EINVAL;
+  const bool swept = d.mode == 1;
+  h_info[0] = swept ? d.col_slab : 0;
+  h_info[1] = swept ? d.launch_waves : 0;
+  h_info[2] = swept ? d.fused_waves : 0;
+  h_info[3] = swept ? d.n_slabs : 0;
   return SAGNN_OK;
 }
 

@@ -563,6 +563,42 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
         assert torch.equal(h, torch.relu(z))
 
 
+@pytest.mark.parametrize("f,f_out,prec", [(128, 40, sagnn.GEMM_FP32), (128, 128, sagnn.GEMM_BF16), (128, 64, sagnn.GEMM_FP32_BF16X3),
+                                          (128, 128, sagnn.GEMM_FP32), (64, 64, sagnn.GEMM_FP32), (256, 256, sagnn.GEMM_BF16)])
+def test_layer_on_a_schedule_in_groups_of_64_columns(f, f_out, prec):
+    """The layer whose A H is not wanted, on communities that are multiplied 64 columns at a time: at 128 columns with a
+    short dense part its wavefronts come in several launches.  Bounds as for the product, then f products and sums."""
+    gen = torch.Generator(device="cuda").manual_seed(f + f_out)
+    n, part = 300_000, 75_000
+    count = torch.randint(20, 34, (n,), device="cuda", generator=gen)
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(count, 0)
+    nnz = int(rp[-1])
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), count)
+    col = row // part * part + torch.randint(part, (nnz,), device="cuda", generator=gen)
+    col = torch.where(torch.rand(nnz, device="cuda", generator=gen) < 0.05, torch.randint(n, (nnz,), device="cuda", generator=gen), col)
+    ci = (torch.sort(row * n + col)[0] - row * n).to(torch.int32)
+    v, H = torch.randn(nnz, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    W = torch.randn(f, f_out, device="cuda", generator=gen) / f ** 0.5
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    launch = ws.launch_info()
+    assert launch["columns"] == 64 and launch["layer_waves"] * 2 == launch["waves"] and ws.info()["sweep_waves"] > 2 * launch["layer_waves"]
+    assert sagnn.gcn_layer_fwd_form(ws, f, f_out, prec) == 2
+    _, Z, Hout = sagnn.gcn_layer_fwd(rp, ci, v, H, W, prec=prec, ws=ws, want_t=False)
+    A, Aabs = (torch.sparse_csr_tensor(rp.long(), ci.long(), x.double(), (n, n)) for x in (v, v.abs()))
+    T, Tabs = A @ H.double(), Aabs @ H.double().abs()
+    unit = 2.0 ** -24 * (count.double() + 2)[:, None] * Tabs       # of a row of A H, any order of its sums
+    Wd = W.double()
+    if prec == sagnn.GEMM_BF16:
+        # both operands are rounded to 8 bits: 2^-9 of each, an element of A H after its own error
+        bound = (unit * (1 + 2.0 ** -8) + 2.0 ** -9 * T.abs()) @ Wd.abs() + (T.abs() * (1 + 2.0 ** -8)) @ (Wd.abs() * 2.0 ** -9)
+    else:
+        bound = unit @ Wd.abs()
+    bound += (f + 4) * 2.0 ** -24 * ((T.abs() * (1 + 2.0 ** -7)) @ Wd.abs())
+    assert bool(((Z.double() - T @ Wd).abs() <= bound).all())
+    assert torch.equal(Hout, torch.relu(Z))
+
+
 @pytest.mark.parametrize("f", [4, 16, 20, 32, 36, 64, 72, 100, 128, 192, 256])
 @pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "around 64", "hub", "few"])
 def test_spmm_small_matrices_without_hubs(kind, f):
