@@ -806,7 +806,8 @@ typedef __bf16 sweep_bf16x8 __attribute__((ext_vector_type(8)));
 // Dense transform of a sweep workgroup's 64 finished rows of T (LDS, [4 waves][16 slots][KROW]):
 // wavefront (rt, half) multiplies row tile rt by the 32-column tiles half, half + 2, .. of W and
 // stores the rows of Z / sigma(Z) at the rows the pieces belong to (slots that hold a piece of a
-// split row, or nothing, are skipped).  Called by all four wavefronts after a workgroup barrier.
+// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup, in the LDS behind the rows.  Called
+// by all four wavefronts after a workgroup barrier.
 // MODE: the matrix-core operands, numbered like SAGNN_GEMM_*: 0 fp32, 1 rounded to bfloat16, 2 fp32
 // as the exact sum of three bfloat16 terms with the six products down to 2^-16 of the leading one.
 // |t2| <= 2^-8 |x| and |t3| <= 2^-16 |x|; both subtractions are exact.
@@ -819,8 +820,8 @@ __device__ __forceinline__ void sweep_split3(float x, __bf16& t1, __bf16& t2, __
 
 template <int KROW, int MODE, int QT>
 __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ lds_acc,
-                                                     const int32_t* __restrict__ piece_target,
-                                                     const SweepFusedArgs& fa, int64_t block, int wave, int lane) {
+                                                     const int32_t* __restrict__ targets,
+                                                     const SweepFusedArgs& fa, int wave, int lane) {
   constexpr int kRow = KROW;
   const int r = lane & 31, h = lane >> 5;
   const int rt = wave & 1;
@@ -948,24 +949,29 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
           for (int i = 0; i < 4; ++i) cur[q][i] = nxt[q][i];
       }
     }
-    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4.  (Looked up here and
-    // not before the loop over k, whose registers decide how many workgroups walk at the same time; hence the opaque index.)
-    uint32_t t0 = (uint32_t)block * (4 * kSweepSlots) + rt * 32 + h * 4;
+    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4, from the LDS.  Looked up
+    // in memory, here, they were one more trip in every pass over k; looked up before the loop over k they took sixteen
+    // registers, which decide how many workgroups walk at the same time at 64 columns.  us here, before the loop and so:
+    // communities, 700 k vertices of 40, 256 to 256 fp32 3760, 3665, 3640, bfloat16 3290, 3200, 3110; random columns, 250 k of
+    // 60 2080, 2030, 2000; a rank's 306 k rows of 11, 64 to 64 180, 220, 174.  (The index is opaque because look-ups moved out
+    // of the loop hold their registers all the same.)
+    uint32_t t0 = rt * 32 + h * 4;
     asm volatile("" : "+v"(t0));
-    int32_t tg[16];   // (all at once: a load between the stores waits for them; four at a time 332 us for 315, R-MAT, 300 k
-                      // vertices of 60, 64 to 64 columns, and 3330 for 3237, random columns, 1 M of 18, 256 to 256 in bfloat16)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) tg[v] = piece_target[t0 + (v >> 2) * 8 + (v & 3)];
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
       const int col = (ct0 + 2 * q) * 32 + r;
       if (q >= nmy || col >= fa.f_out) continue;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (tg[v] < 0) continue;               // unused slot, or a piece of a split row
-        const float zz = z[q][v];
-        if (fa.Z) fa.Z[(int64_t)tg[v] * fa.f_out + col] = zz;
-        if (fa.Hout) fa.Hout[(int64_t)tg[v] * fa.f_out + col] = fa.act == SAGNN_ACT_RELU ? (zz > 0.f ? zz : 0.f) : zz;
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int4 t4 = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
+        const int32_t tg[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (tg[v] < 0) continue;               // unused slot, or a piece of a split row
+          const float zz = z[q][v4 * 4 + v];
+          if (fa.Z) fa.Z[(int64_t)tg[v] * fa.f_out + col] = zz;
+          if (fa.Hout) fa.Hout[(int64_t)tg[v] * fa.f_out + col] = fa.act == SAGNN_ACT_RELU ? (zz > 0.f ? zz : 0.f) : zz;
+        }
       }
     }
   }
@@ -978,7 +984,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
     const SpmmWsHeader* __restrict__ hdr, const float* __restrict__ B, float* __restrict__ partial,
     const SweepDims d, const SweepFusedArgs fa) {
   using vec = typename Vec<FPL>::T;
-  extern __shared__ __attribute__((aligned(16))) float lds_acc[];  // [4 waves][16][64*FPL]
+  extern __shared__ __attribute__((aligned(16))) float lds_acc[];  // [4 waves][16][64*FPL], then [4 waves][16] targets
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t loff = lane * (FPL * 4);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -988,6 +994,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
       hdr->groups != 1)
     return;
   constexpr int kRow = 64 * FPL;  // floats per accumulator row = f_in
+  const int32_t target = piece_target[w * kSweepSlots + (lane & (kSweepSlots - 1))];
   float* __restrict__ my = lds_acc + (size_t)wave * kSweepSlots * kRow + lane * FPL;
   for (int s = 0; s < kSweepSlots; ++s) *reinterpret_cast<vec*>(my + s * kRow) = vec(0.f);
 
@@ -1000,6 +1007,8 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
   // (turns: at 256 columns only two wavefronts share a SIMD)
   walk_stream<FPL, U, BUF, false, FPL < 4>(cw, vw, len, rs, B, d, loff, my, kRow);
 
+  int32_t* __restrict__ targets = reinterpret_cast<int32_t*>(lds_acc + 4 * kSweepSlots * kRow);
+  if (lane < kSweepSlots) targets[wave * kSweepSlots + lane] = target;
   // pieces of split rows to `partial`; T rows to memory if wanted
 #pragma unroll 1
   for (int s = 0; s < kSweepSlots; ++s) {
@@ -1017,7 +1026,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
 
   // tiles per pass: 4 at f = 256 (the LDS already limits a CU to two workgroups; 2 with three operand
   // terms per tile in registers), 1 below
-  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(lds_acc, piece_target, fa, (int64_t)d.block0 + blockIdx.x, wave, (int)lane);
+  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(lds_acc, targets, fa, wave, (int)lane);
 }
 
 // W (f_in x f_out, row-major fp32) -> [f_in / 8][NB] vectors of 8 bfloat16 (k fastest), NB = f_out
@@ -1074,6 +1083,8 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   float* __restrict__ my = lds_acc + (size_t)wave * d.slots * kRow + el;
   for (int ls = 0; ls < SL; ++ls) *reinterpret_cast<vec*>(my + (gid * SL + ls) * kRow) = vec(0.f);
 
+  [[maybe_unused]] int32_t target = 0;
+  if constexpr (FUSE != 0) target = piece_target[w * kSweepSlots + (lane & (kSweepSlots - 1))];
   const int32_t base = wave_base[w];
   const int32_t steps = (wave_base[w + 1] - base) / R;   // a multiple of U (padded when built)
   const uint32_t* __restrict__ cw = code + base;
@@ -1212,8 +1223,10 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   if constexpr (FUSE != 0) {
     // (whole workgroups: the launcher only takes this form when n_waves is a multiple of 4 and
     // every wavefront owns 16 slots)
+    int32_t* __restrict__ targets = reinterpret_cast<int32_t*>(lds_acc + 4 * kSweepSlots * kRow);
+    if (lane < kSweepSlots) targets[wave * kSweepSlots + lane] = target;
     __syncthreads();
-    sweep_dense_epilogue<LG * V, FUSE - 1, 1>(lds_acc, piece_target, fa, blockIdx.x, wave, (int)lane);
+    sweep_dense_epilogue<LG * V, FUSE - 1, 1>(lds_acc, targets, fa, wave, (int)lane);
   }
 }
 
@@ -1801,7 +1814,10 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
   sd.fw = fw;
   sd.turn = turn_steps(kmax, fw);
-  const size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
+  size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
+  // (the layer: the targets behind the rows, and no more than five workgroups a CU, which 64 columns would allow: a sixth
+  // only drives the others' rows out of the L2, 233 k vertices of 489, 64 to 64 columns 1480 us, with five 1410)
+  if (fuse != 0) lds = std::max(lds + 4 * kSweepSlots * sizeof(int32_t), (size_t)28 << 10);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1943,7 +1959,7 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   const bool buf = buffer_addressable(kmax, ldb, f_in, &sd.b_bytes);
   sd.row_bytes = (uint32_t)(ldb * 4);
   const unsigned blocks = (unsigned)(d.n_waves / 4);
-  const size_t lds = (size_t)4 * kSweepSlots * f_in * sizeof(float);
+  const size_t lds = (size_t)4 * kSweepSlots * (f_in + 1) * sizeof(float);   // (rows and their targets)
   SweepFusedArgs fb = fa;
   fb.Wp = nullptr;
   if (mode != 0) {
