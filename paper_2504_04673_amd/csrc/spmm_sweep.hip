@@ -1782,7 +1782,8 @@ namespace {
 // Strides of 32, 64 and 128 steps on three matrices in turn: 233 k vertices f = 128 (119 MB) 1992, 2057, 2101 us; 1 M f = 64
 // (256 MB) 710, 716, 711, f = 128 1320, 1329, 1299; 1.2 M f = 128 1740, 1751, 1765; 2.45 M f = 64 (627 MB) 2230, 2249, 2156,
 // f = 128 4155, 4240, 4127.
-int32_t turn_steps(uint32_t kmax, int32_t fw) { return ((int64_t)kmax + 1) * fw * 4 > (256ll << 20) ? 128 : 32; }
+int64_t operand_bytes(uint32_t kmax, int32_t fw) { return ((int64_t)kmax + 1) * fw * 4; }
+int32_t turn_steps(uint32_t kmax, int32_t fw) { return operand_bytes(kmax, fw) > (256ll << 20) ? 128 : 32; }
 }  // namespace
 
 namespace {
@@ -1916,14 +1917,17 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     return buf ? go_group(&spmm_sweep_group_kernel<4, 4, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 4, 8, false, 0, true>);
   }
   if (fw > 256) return SAGNN_EINVAL;
-  // Under 128 columns a matrix whose rows of B are hardly used twice gains nothing by an order among the wavefronts, and
-  // looking for one's turn before every batch costs it up to 3 % (676 k vertices of 11, f = 64, 96 229, 362 us, without 224,
-  // 354; a rank's 440 k rows of 20 f = 96 513, 499).  At 128 it gains (a rank's step, 867 k rows of 15, 2207 us without, 2168).
-  const bool turns = d.col_slab > 0 || d.f > 128;   // (otherwise one row per load is for such matrices, see sweep_prepare)
+  // At up to 128 columns, where one row per load is for matrices whose rows of B are hardly used twice (but for column
+  // groups), turns pay by the size of the operand, whatever its width.  us without and with, over 1 GB: a rank's rows
+  // f = 64 478, 466 (0.99 GB), 638, 618 (1.25), f = 96 753, 747 (1.48), f = 112 909, 888 (1.72), 1315, 1265 (2.2), f = 128
+  // 548, 545 (1.3), 588, 584 (1.4), 792, 758 (1.6), 927, 902 (2.0), 1351, 1288 (2.5), 1553, 1502 (3.4); under 1 GB: f = 96
+  // 446, 453 (0.95), f = 128 370, 371 (0.7), random columns of 9 to 19, f = 128 1037, 1065 (0.5), 1316, 1337 (0.6), f = 64
+  // and 96 the same.
+  const bool turns = d.col_slab > 0 || d.f > 128 || operand_bytes(kmax, fw) > (1ll << 30);
 #define SAGNN_ONE(FPL_, ODD_, TURN_) \
   (buf ? go(spmm_sweep_kernel<FPL_, 8, true, ODD_, TURN_>) : go(spmm_sweep_kernel<FPL_, 8, false, ODD_, TURN_>))
   if (fw == 256) return SAGNN_ONE(4, false, true);
-  if (fw == 128) return SAGNN_ONE(2, false, true);
+  if (fw == 128) return turns ? SAGNN_ONE(2, false, true) : SAGNN_ONE(2, false, false);
   if (fw == 64) return turns ? SAGNN_ONE(1, false, true) : SAGNN_ONE(1, false, false);
   if (fw > 128) return SAGNN_ONE(4, true, true);
   if (fw > 64) return turns ? SAGNN_ONE(2, true, true) : SAGNN_ONE(2, true, false);

@@ -563,6 +563,25 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
         assert torch.equal(h, torch.relu(z))
 
 
+@pytest.mark.parametrize("f,k", [(64, 4_150_000), (64, 4_250_000), (96, 2_700_000), (96, 2_900_000), (128, 2_050_000), (128, 2_150_000)])
+def test_spmm_one_row_per_load_on_both_sides_of_1_gb(f, k):
+    """Rows of B that are hardly used twice, one row per load, with B just under and just over 1 GB: whether the wavefronts
+    take turns changes nothing in the result, which is compared with 64-bit sums of the same rows."""
+    gen = torch.Generator(device="cuda").manual_seed(f)
+    m, deg = 170_000, 20
+    rp = torch.arange(0, m * deg + 1, deg, dtype=torch.int32, device="cuda")
+    ci = torch.sort(torch.randint(k, (m, deg), device="cuda", generator=gen), dim=1)[0].to(torch.int32).reshape(-1)
+    ci[-1] = k - 1
+    v, B = torch.randn(m * deg, device="cuda", generator=gen), torch.randn(k, f, device="cuda", generator=gen)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, k, f)
+    info = ws.info()
+    assert info["mode"] == 1 and info["groups"] == 1 and ws.launch_info()["columns"] == 0
+    C = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+    rows = torch.cat([torch.arange(0, m, 37, device="cuda"), torch.tensor([m - 1], device="cuda")])
+    t = v.reshape(m, deg)[rows].double()[:, :, None] * B[ci.reshape(m, deg)[rows].long()].double()
+    assert bool(((C[rows].double() - t.sum(1)).abs() <= (deg + 2) * 2.0 ** -24 * t.abs().sum(1)).all())
+
+
 @pytest.mark.parametrize("f,f_out,prec", [(128, 40, sagnn.GEMM_FP32), (128, 128, sagnn.GEMM_BF16), (128, 64, sagnn.GEMM_FP32_BF16X3),
                                           (128, 128, sagnn.GEMM_FP32), (64, 64, sagnn.GEMM_FP32), (256, 256, sagnn.GEMM_BF16)])
 def test_layer_on_a_schedule_in_groups_of_64_columns(f, f_out, prec):
