@@ -1115,11 +1115,11 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   // Words of H steps in scalar registers, requested while the rows of the steps before are on their way: they come from
   // HBM, and waiting for them at the head of a batch left the address units idle.  With four groups half a batch, a whole
   // one does not fit the scalar registers (1547 and 1947 us for 1723 before: 233 k vertices, 114 M entries, f = 64).
-  // f = 128 2313 -> 2102; 2.45 M, 125 M entries 4200 -> 4022.  (Before the wavefronts took turns this cost more misses
+  // f = 128 2313 -> 2102.  (Before the wavefronts took turns this cost more misses
   // than it gave.  One vector load per batch with DPP broadcasts instead, half the vector instructions: 2671, 4196;
   // vector loads return in order, so every row waits for the words before it.)
-  // AHEAD false: at 128 columns of more than 1 GB, where HBM gives all it has and running ahead only costs misses (the
-  // step of the 2.45 M-vertex graph 5593 us without, 5702 and 5741 with; 1.2 M vertices, 614 MB 1856 without, 1739 with).
+  // AHEAD false: operands over a size, where this costs more misses than it gives (sweep_launch; with four groups it pays
+  // at all sizes but some: 3.5 M vertices of 40, f = 64 2802, 2863 without, 4 M 3773, 3348, 6 M of 30 4632, 4845).
   constexpr int kParts = R == 4 ? 2 : 1, H = U / kParts;
   uint32_t c[H][R];
   float v[H][R];
@@ -1788,12 +1788,12 @@ int32_t turn_steps(uint32_t kmax, int32_t fw) { return operand_bytes(kmax, fw) >
 
 namespace {
 // lane-group kernels: fuse = 0 product, 1 / 2 / 3 layer form with fp32 / bfloat16 / three-term operands
-template <int V, int R, bool BUF>
+template <int V, int R, bool BUF, bool AHEAD>
 auto group_kernel_of(int fuse) {
-  if (fuse == 1) return &spmm_sweep_group_kernel<V, R, 8, BUF, 1>;
-  if (fuse == 2) return &spmm_sweep_group_kernel<V, R, 8, BUF, 2>;
-  if (fuse == 3) return &spmm_sweep_group_kernel<V, R, 8, BUF, 3>;
-  return &spmm_sweep_group_kernel<V, R, 8, BUF, 0>;
+  if (fuse == 1) return &spmm_sweep_group_kernel<V, R, 8, BUF, 1, false, AHEAD>;
+  if (fuse == 2) return &spmm_sweep_group_kernel<V, R, 8, BUF, 2, false, AHEAD>;
+  if (fuse == 3) return &spmm_sweep_group_kernel<V, R, 8, BUF, 3, false, AHEAD>;
+  return &spmm_sweep_group_kernel<V, R, 8, BUF, 0, false, AHEAD>;
 }
 }  // namespace
 
@@ -1900,30 +1900,45 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     return buf ? go_perm(spmm_sweep_perm_kernel<8, true, true>) : go_perm(spmm_sweep_perm_kernel<8, false, true>);
   }
   if (d.groups == 2) {   // half a wavefront per row
-    if (fw == 128 && !fuse && buf && ((int64_t)kmax + 1) * fw * 4 > (1ll << 30)) return go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, false, false>);
-    if (fw == 128) return buf ? go_group(group_kernel_of<4, 2, true>(fuse)) : go_group(group_kernel_of<4, 2, false>(fuse));
-    if (fw == 64) return buf ? go_group(group_kernel_of<2, 2, true>(fuse)) : go_group(group_kernel_of<2, 2, false>(fuse));
+    // Words ahead (see the kernel) up to a size of the operand, whatever its addressing, in the product and in the layer:
+    // beyond it wavefronts that run ahead only cost misses.  us with and without, products of power-law matrices at 128
+    // columns: 300 k vertices of 30 278, 320, 600 k of 51 849, 892, 1.1 M of 51 (563 MB) 1639, 1704, 1.2 M of 51 (614 MB) 1785,
+    // 1873, 1.3 M of 30, 51, 80 (666 MB) 1392, 2148, 3279 and 1386, 2101, 2979, 1.6 M of 51 2880, 2729, 2.1 M 4109, 3521, 2.45 M
+    // 4179, 4135, of 30 3303, 3050, 3.3 M of 45 6927, 5538, 5 M of 40 10328, 8921, 9 M of 30 (4.6 GB) 16867, 15440; its layer
+    // in fp32 1.2 M of 51 2173, 2293, 1.6 M 3315, 3201, 2.45 M 4833, 4740.  Between the kernels' own widths, whose rows begin
+    // inside lines, from the memory-side cache's size on: 233 k of 489, f = 100 1975, 2286, 600 k of 60 (240 MB) 970, 1005, 1 M
+    // of 51, f = 72 (288 MB) 1345, 1205, 2 M of 51, f = 72, 100, 112 3604, 3942, 3934 and 2637, 3739, 3739, 2.45 M of 40, f = 96
+    // 3261, 2686.
+    const int64_t b = operand_bytes(kmax, fw);
+    if (fw == 128) {
+      if (b <= (600ll << 20)) return buf ? go_group(group_kernel_of<4, 2, true, true>(fuse)) : go_group(group_kernel_of<4, 2, false, true>(fuse));
+      return buf ? go_group(group_kernel_of<4, 2, true, false>(fuse)) : go_group(group_kernel_of<4, 2, false, false>(fuse));
+    }
+    if (fw == 64) return buf ? go_group(group_kernel_of<2, 2, true, true>(fuse)) : go_group(group_kernel_of<2, 2, false, true>(fuse));
     if (fw > 128 || fuse) return SAGNN_EINVAL;
     // (two sums where nonzero splitting would be the alternative, with its tree: communities, 30 k vertices of 60, f = 100
     // 7.7e-8 from 64 bits by the tree, 13.8e-8 by one sum; elsewhere they cost up to 2 %)
     if (d.apart)
       return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true, true, true>)
                  : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true, true, true>);
-    return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true>);
+    if (b <= (256ll << 20))
+      return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true>);
+    return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true, false>)
+               : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true, false>);
   }
   if (d.groups == 4) {   // a quarter wavefront per row
-    if (fw == 64) return buf ? go_group(group_kernel_of<4, 4, true>(fuse)) : go_group(group_kernel_of<4, 4, false>(fuse));
+    if (fw == 64) return buf ? go_group(group_kernel_of<4, 4, true, true>(fuse)) : go_group(group_kernel_of<4, 4, false, true>(fuse));
     if (fw > 64 || fuse) return SAGNN_EINVAL;
     return buf ? go_group(&spmm_sweep_group_kernel<4, 4, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 4, 8, false, 0, true>);
   }
   if (fw > 256) return SAGNN_EINVAL;
   // At up to 128 columns, where one row per load is for matrices whose rows of B are hardly used twice (but for column
-  // groups), turns pay by the size of the operand, whatever its width.  us without and with, over 1 GB: a rank's rows
-  // f = 64 478, 466 (0.99 GB), 638, 618 (1.25), f = 96 753, 747 (1.48), f = 112 909, 888 (1.72), 1315, 1265 (2.2), f = 128
-  // 548, 545 (1.3), 588, 584 (1.4), 792, 758 (1.6), 927, 902 (2.0), 1351, 1288 (2.5), 1553, 1502 (3.4); under 1 GB: f = 96
-  // 446, 453 (0.95), f = 128 370, 371 (0.7), random columns of 9 to 19, f = 128 1037, 1065 (0.5), 1316, 1337 (0.6), f = 64
-  // and 96 the same.
-  const bool turns = d.col_slab > 0 || d.f > 128 || operand_bytes(kmax, fw) > (1ll << 30);
+  // groups), turns pay by the size of the operand, whatever its width.  us without and with, over the line: a rank's rows
+  // f = 64 638, 618 (1.25 GB), f = 96 753, 747 (1.5), f = 112 909, 888 (1.7), 1315, 1265 (2.2), f = 128 548, 545 (1.3),
+  // 588, 584 (1.4), 792, 758 (1.6), 927, 902 (2.0), 1351, 1288 (2.5), 1553, 1502 (3.4); under it: f = 128 485, 493 (1.03),
+  // f = 96 446, 453 (0.95), f = 128 370, 371 (0.7), random columns of 9 to 19, f = 128 1037, 1065 (0.5), 1316, 1337 (0.6),
+  // f = 64 and 96 the same.
+  const bool turns = d.col_slab > 0 || d.f > 128 || operand_bytes(kmax, fw) > (1100ll << 20);
 #define SAGNN_ONE(FPL_, ODD_, TURN_) \
   (buf ? go(spmm_sweep_kernel<FPL_, 8, true, ODD_, TURN_>) : go(spmm_sweep_kernel<FPL_, 8, false, ODD_, TURN_>))
   if (fw == 256) return SAGNN_ONE(4, false, true);

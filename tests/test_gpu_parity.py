@@ -563,10 +563,10 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
         assert torch.equal(h, torch.relu(z))
 
 
-@pytest.mark.parametrize("f,k", [(64, 4_150_000), (64, 4_250_000), (96, 2_700_000), (96, 2_900_000), (128, 2_050_000), (128, 2_150_000)])
-def test_spmm_one_row_per_load_on_both_sides_of_1_gb(f, k):
-    """Rows of B that are hardly used twice, one row per load, with B just under and just over 1 GB: whether the wavefronts
-    take turns changes nothing in the result, which is compared with 64-bit sums of the same rows."""
+@pytest.mark.parametrize("f,k", [(64, 4_505_600), (64, 4_505_601), (96, 3_003_733), (96, 3_003_734), (128, 2_252_800), (128, 2_252_801)])
+def test_spmm_one_row_per_load_on_both_sides_of_turns(f, k):
+    """Rows of B that are hardly used twice, one row per load, with B just under and just over 1100 MB: whether the
+    wavefronts take turns changes nothing in the result, which is compared with 64-bit sums of the same rows."""
     gen = torch.Generator(device="cuda").manual_seed(f)
     m, deg = 170_000, 20
     rp = torch.arange(0, m * deg + 1, deg, dtype=torch.int32, device="cuda")
@@ -580,6 +580,37 @@ def test_spmm_one_row_per_load_on_both_sides_of_1_gb(f, k):
     rows = torch.cat([torch.arange(0, m, 37, device="cuda"), torch.tensor([m - 1], device="cuda")])
     t = v.reshape(m, deg)[rows].double()[:, :, None] * B[ci.reshape(m, deg)[rows].long()].double()
     assert bool(((C[rows].double() - t.sum(1)).abs() <= (deg + 2) * 2.0 ** -24 * t.abs().sum(1)).all())
+
+
+@pytest.mark.parametrize("f,k,ld", [(128, 1_228_800, 128), (128, 1_228_801, 128), (128, 1_228_801, 1024), (100, 671_088, 100), (100, 671_089, 100),
+                                    (100, 671_089, 1700)])
+def test_spmm_two_rows_per_load_on_both_sides_of_words_ahead(f, k, ld):
+    """Two lane groups with B on either side of the sizes up to which the stream's words are requested ahead, also with rows
+    of B so far apart that buffer loads do not reach them; at 128 columns the layer in its three precisions too."""
+    gen = torch.Generator(device="cuda").manual_seed(f)
+    m, deg = 106_000, 30
+    rp = torch.arange(0, m * deg + 1, deg, dtype=torch.int32, device="cuda")
+    ci = torch.sort(torch.randint(k, (m, deg), device="cuda", generator=gen), dim=1)[0].to(torch.int32).reshape(-1)
+    ci[-1] = k - 1
+    v, B = torch.randn(m * deg, device="cuda", generator=gen), torch.randn(k, ld, device="cuda", generator=gen)[:, :f]
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, k, f, options=sagnn.SpmmOptions(groups=2))
+    assert ws.info()["mode"] == 1 and ws.info()["groups"] == 2
+    C = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+    rows = torch.cat([torch.arange(0, m, 23, device="cuda"), torch.tensor([m - 1], device="cuda")])
+    t = v.reshape(m, deg)[rows].double()[:, :, None] * B[ci.reshape(m, deg)[rows].long()].double()
+    T, unit = t.sum(1), (deg + 2) * 2.0 ** -24 * t.abs().sum(1)
+    assert bool(((C[rows].double() - T).abs() <= unit).all())
+    if f != 128:
+        return
+    W = torch.randn(f, 64, device="cuda", generator=gen) / f ** 0.5
+    Wd = W.double()
+    for prec in (sagnn.GEMM_FP32, sagnn.GEMM_BF16, sagnn.GEMM_FP32_BF16X3):
+        assert sagnn.gcn_layer_fwd_form(ws, f, 64, prec) == 2
+        _, Z, _ = sagnn.gcn_layer_fwd(rp, ci, v, B, W, prec=prec, ws=ws, want_t=False)
+        bound = unit @ Wd.abs() + (f + 4) * 2.0 ** -24 * (T.abs() @ Wd.abs())
+        if prec == sagnn.GEMM_BF16:   # both operands rounded to 8 bits, the sums on top
+            bound = (unit * 1.01 + 2.0 ** -8 * T.abs()) @ Wd.abs() * 1.01 + bound
+        assert bool(((Z[rows].double() - T @ Wd).abs() <= bound).all())
 
 
 @pytest.mark.parametrize("f,f_out,prec", [(128, 40, sagnn.GEMM_FP32), (128, 128, sagnn.GEMM_BF16), (128, 64, sagnn.GEMM_FP32_BF16X3),
