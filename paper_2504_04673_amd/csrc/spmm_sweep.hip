@@ -806,7 +806,7 @@ typedef __bf16 sweep_bf16x8 __attribute__((ext_vector_type(8)));
 // Dense transform of a sweep workgroup's 64 finished rows of T (LDS, [4 waves][16 slots][KROW]):
 // wavefront (rt, half) multiplies row tile rt by the 32-column tiles half, half + 2, .. of W and
 // stores the rows of Z / sigma(Z) at the rows the pieces belong to (slots that hold a piece of a
-// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup, in the LDS behind the rows.  Called
+// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup (see sweep_targets_far).  Called
 // by all four wavefronts after a workgroup barrier.
 // MODE: the matrix-core operands, numbered like SAGNN_GEMM_*: 0 fp32, 1 rounded to bfloat16, 2 fp32
 // as the exact sum of three bfloat16 terms with the six products down to 2^-16 of the leading one.
@@ -817,6 +817,16 @@ __device__ __forceinline__ void sweep_split3(float x, __bf16& t1, __bf16& t2, __
   t2 = (__bf16)r;
   t3 = (__bf16)(r - (float)t2);
 }
+
+// Where the epilogue finds its rows: the LDS, written beside the walk, but memory in fp32 at 256 columns.  In memory, behind
+// the matrix instructions, they are one more trip in every pass over k; looked up before the loop over k they take sixteen
+// registers, which decide how many workgroups walk at the same time at 64 columns.  us behind, before and from the LDS:
+// communities, 700 k vertices of 40, 256 to 256 bfloat16 3290, 3200, 3110; a rank's 306 k rows of 11, 64 to 64 180, 220, 174.
+// In fp32 at 256 the trip does not show beside 14 us of matrix instructions, and what comes sooner from the LDS is worse for
+// random columns: 800 k vertices of 15 2738 from memory, 3182 from the LDS, 1 M of 16, 18, 22 3663, 3995, 4559 and 4275,
+// 4495, 4958, 1.5 M of 20 6569, 7208, 2 M of 18 8175, 9361 (in communities, 700 k of 40, 4069 and 4086; bfloat16 2 M of 18
+// 7262 and 7058).
+constexpr bool sweep_targets_far(int krow, int mode) { return mode == 0 && krow == 256; }
 
 template <int KROW, int MODE, int QT>
 __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ lds_acc,
@@ -949,21 +959,25 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
           for (int i = 0; i < 4; ++i) cur[q][i] = nxt[q][i];
       }
     }
-    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4, from the LDS.  Looked up
-    // in memory, here, they were one more trip in every pass over k; looked up before the loop over k they took sixteen
-    // registers, which decide how many workgroups walk at the same time at 64 columns.  us here, before the loop and so:
-    // communities, 700 k vertices of 40, 256 to 256 fp32 3760, 3665, 3640, bfloat16 3290, 3200, 3110; random columns, 250 k of
-    // 60 2080, 2030, 2000; a rank's 306 k rows of 11, 64 to 64 180, 220, 174.  (The index is opaque because look-ups moved out
-    // of the loop hold their registers all the same.)
+    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4, from `targets`.  (The
+    // index is opaque because look-ups moved out of the loop hold their registers all the same; those from memory are made
+    // all at once, a load between the stores would wait for them.)
     uint32_t t0 = rt * 32 + h * 4;
     asm volatile("" : "+v"(t0));
+    int4 far[4];
+    if constexpr (sweep_targets_far(KROW, MODE)) {
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) far[v4] = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
+    }
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
       const int col = (ct0 + 2 * q) * 32 + r;
       if (q >= nmy || col >= fa.f_out) continue;
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        const int4 t4 = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
+        int4 t4;
+        if constexpr (sweep_targets_far(KROW, MODE)) t4 = far[v4];
+        else t4 = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
         const int32_t tg[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -1026,7 +1040,8 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
 
   // tiles per pass: 4 at f = 256 (the LDS already limits a CU to two workgroups; 2 with three operand
   // terms per tile in registers), 1 below
-  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(lds_acc, targets, fa, wave, (int)lane);
+  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(
+      lds_acc, sweep_targets_far(kRow, MODE) ? piece_target + ((int64_t)d.block0 + blockIdx.x) * 4 * kSweepSlots : targets, fa, wave, (int)lane);
 }
 
 // W (f_in x f_out, row-major fp32) -> [f_in / 8][NB] vectors of 8 bfloat16 (k fastest), NB = f_out
