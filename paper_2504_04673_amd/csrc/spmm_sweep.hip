@@ -991,7 +991,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
   }
 }
 
-template <int FPL, int U, bool BUF, int MODE>
+template <int FPL, int U, bool BUF, int MODE, bool TURN>
 __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1018,8 +1018,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
   const float* __restrict__ vw = vals + base;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
 
-  // (turns: at 256 columns only two wavefronts share a SIMD)
-  walk_stream<FPL, U, BUF, false, FPL < 4>(cw, vw, len, rs, B, d, loff, my, kRow);
+  walk_stream<FPL, U, BUF, false, TURN>(cw, vw, len, rs, B, d, loff, my, kRow);
 
   int32_t* __restrict__ targets = reinterpret_cast<int32_t*>(lds_acc + 4 * kSweepSlots * kRow);
   if (lane < kSweepSlots) targets[wave * kSweepSlots + lane] = target;
@@ -1501,9 +1500,11 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // not with hubs, whose rows hit in any case (233 k vertices of 489: 5627, 7060).
   const bool local = tot.locality >= kLocalPermille;
   const double span = (double)k * tot.span / 1000.0;
+  // how often the 16384 rows of A that an XCD holds at 64 columns a launch want a row of the columns they choose from
+  const double reuse = 16384.0 * (double)nnz / (std::max(span, 1.0) * (double)m);
   const bool col_groups = f >= 64 && (f & 63) == 0 && opt.groups == 0 && opt.slab_width == 0 && opt.sync_slabs <= 0 &&
                           opt.barriers != 1 && opt.pace_ps_per_step <= 0 && span >= 40000.0 &&
-                          16384.0 * (double)nnz >= 0.6 * span * (double)m && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz &&
+                          reuse >= 0.6 && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz &&
                           (!local || (nnz >= 18 * m && span >= 60000.0));
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
@@ -1766,6 +1767,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.col_slab = col_groups ? 64 : 0;
   h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
   h.fused_waves = local ? h.launch_waves / 2 : 0;
+  out->reuse = (float)reuse;
   out->mean_steps = rec.scan.mean_steps;
   out->max_steps = rec.scan.max_steps;
   out->use_sweep = true;
@@ -2004,6 +2006,13 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
     SAGNN_LAUNCH_CHECK();
     fb.Wp = wp;
   }
+  // At 128 columns turns pay in the layer where rows of B are used often by rows that are resident together, and those are
+  // not short.  us without and with, random columns, 200 k vertices of 30 (2.5 uses) to 40 columns 404, 400, 200 k of 60 (4.9)
+  // 709, 663, 100 k of 40 (6.6) 205, 188, 350 k of 60 (2.8) to 128 1369, 1342; 300 k of 20 (1.1) to 128 526, 545, 275 k of 40
+  // (2.4) 791, 804, 150 k of 24 (2.6) 311, 318; 1 M of 15 1341, 1381; communities, 1.6 M of 31 in bfloat16 3069, 2906, 700 k of
+  // 21 to 40 1024, 995, but to 128 1061, 1110.  Over 1100 MB as in the product.
+  const bool brief = mode != 0 || fa.f_out <= 64;
+  const bool turns = (d.reuse >= 2.4f && (d.nnz >= 28 * d.m || (brief && d.fused_waves > 0))) || operand_bytes(kmax, f_in) > (1100ll << 20);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -2012,7 +2021,6 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
     // carries locality and the dense part is not long: 1.6 M vertices of 40 in communities to 40 columns in fp32 3950 -> 3718
     // us, to 128 in bfloat16 4042 -> 3795, in fp32 4086 -> 4132; random columns, 500 k of 24, 976 -> 1096.  At 64 and 256 the
     // dense parts of workgroups that end together are left without gathers beside them: 803 -> 822, 3862 -> 4120.)
-    const bool brief = mode != 0 || fb.f_out <= 64;
     const unsigned per = f_in == 128 && brief && d.fused_waves >= 4 ? (unsigned)(d.fused_waves / 4) : blocks;
     for (unsigned b0 = 0; b0 < blocks; b0 += per) {
       sd.block0 = (int32_t)b0;
@@ -2027,13 +2035,13 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
     }
     return SAGNN_OK;
   };
-#define SAGNN_SWF(FPL_)                                                                                      \
-  (mode == 2 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 2>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 2>))   \
-   : mode == 1 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 1>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 1>)) \
-               : (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 0>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 0>)))
-  if (f_in == 256) return SAGNN_SWF(4);
-  if (f_in == 128) return SAGNN_SWF(2);
-  return SAGNN_SWF(1);
+#define SAGNN_SWF(FPL_, TURN_)                                                                               \
+  (mode == 2 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 2, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 2, TURN_>))   \
+   : mode == 1 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 1, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 1, TURN_>)) \
+               : (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 0, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 0, TURN_>)))
+  if (f_in == 256) return SAGNN_SWF(4, false);   // (only two wavefronts share a SIMD)
+  if (f_in == 128) return turns ? SAGNN_SWF(2, true) : SAGNN_SWF(2, false);
+  return SAGNN_SWF(1, true);
 #undef SAGNN_SWF
 }
 
