@@ -1578,12 +1578,18 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
     const int64_t up = round_up((size_t)n_target_waves, (size_t)resident_waves);
     if (up + 64 <= L.max_waves - 8) n_target_waves = up;
   }
-  // (column groups without locality: not under 8192 rows a slab, which wide operands would get; 250 k vertices of 60, f = 256
-  // 1286 -> 1254 us, a row block of a partitioned graph 445 -> 424.  Finer slabs than 4 MB of the whole width for narrow
-  // operands would be up to 5 % faster, but a row's sum has a term per slab it has entries in, and more terms are further
-  // from exact: f = 64 8.7e-8 with 4 MB, 1.04e-7 with 2.)
-  const int64_t slab_bytes = opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : (col_groups && !local && f > 128 ? 32 * f : 4096)) << 10;
-  int64_t S = slab_bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * slab_bytes) : kSweepMaxSlabs;
+  // (column groups without locality: not under 8192 rows a slab, which wide operands would get, 250 k vertices of 60, f = 256
+  // 1286 -> 1254 us, a row block of a partitioned graph 445 -> 424; but while a row has at most 16 entries a slab, since the
+  // sum of longer segments is further from exact: f = 256, 8192 rows and 4 MB a slab 60 k of 120 9.3e-8, 9.4e-8, of 200
+  // 10.9e-8, 10.2e-8, of 489 15.3e-8, 12.8e-8, 120 k of 200 10.3e-8, 11.7e-8, of 489 12.8e-8, 12.9e-8.  Finer slabs than 4 MB
+  // of the whole width for narrow operands would be up to 5 % faster, but a row's sum has a term per slab it has entries in,
+  // and more terms are further from exact too: f = 64 8.7e-8 with 4 MB, 1.04e-7 with 2.)
+  auto slabs_of = [&](int64_t bytes) { return bytes >= (1 << 16) ? 8 * ceil_div(b_bytes, 8 * bytes) : (int64_t)kSweepMaxSlabs; };
+  int64_t S = slabs_of(opt.slab_kb < 0 ? 0 : (int64_t)(opt.slab_kb > 0 ? opt.slab_kb : 4096) << 10);
+  if (opt.slab_kb == 0 && col_groups && !local && f > 128) {
+    const int64_t coarse = std::max<int64_t>(8, slabs_of((int64_t)32 * f << 10));
+    if (nnz <= 16 * coarse * m) S = coarse;
+  }
   if (S < 8) S = 8;
   // Where the order of the rows carries locality at least four slabs (eight with 64 entries a row) in the columns that
   // neighbouring rows choose from: slabs of 4 MB may hold all of them, and then nothing keeps the wavefronts of a window in

@@ -582,6 +582,31 @@ def test_spmm_one_row_per_load_on_both_sides_of_turns(f, k):
     assert bool(((C[rows].double() - t.sum(1)).abs() <= (deg + 2) * 2.0 ** -24 * t.abs().sum(1)).all())
 
 
+@pytest.mark.parametrize("n,deg,slabs", [(60_000, 120, 8), (60_000, 200, 16), (60_000, 489, 16), (45_000, 60, 8)])
+def test_spmm_column_groups_keep_segments_short(n, deg, slabs):
+    """Random columns, 256 of B, 64 a launch: slabs of 8192 rows of B while a row has at most 16 entries in one, else slabs of
+    4 MB.  The error against 64 bits is no larger than in slabs of 4 MB (1 % for what a sample of rows leaves open)."""
+    gen = torch.Generator(device="cuda").manual_seed(deg)
+    f = 256
+    rp = torch.arange(0, n * deg + 1, deg, dtype=torch.int32, device="cuda")
+    ci = torch.sort(torch.randint(n, (n, deg), device="cuda", generator=gen), dim=1)[0].to(torch.int32).reshape(-1)
+    v, B = torch.randn(n * deg, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    rows = torch.arange(0, n, 7, device="cuda")
+    At = torch.sparse_csr_tensor(torch.arange(0, rows.numel() * deg + 1, deg, device="cuda"), ci.reshape(n, deg)[rows].reshape(-1).long(),
+                                 v.reshape(n, deg)[rows].reshape(-1).double(), (rows.numel(), n))
+    ref = At @ B.double()
+
+    def error(options):
+        ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f, options=options)
+        assert ws.launch_info()["columns"] == 64
+        C = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+        return ws.launch_info()["slabs"], float((C[rows].double() - ref).norm() / ref.norm())
+
+    got, err = error(None)
+    assert got == slabs
+    assert err <= 1.01 * error(sagnn.SpmmOptions(slab_kb=4096))[1]
+
+
 @pytest.mark.parametrize("f,k,ld", [(128, 1_228_800, 128), (128, 1_228_801, 128), (128, 1_228_801, 1024), (100, 671_088, 100), (100, 671_089, 100),
                                     (100, 671_089, 1700)])
 def test_spmm_two_rows_per_load_on_both_sides_of_words_ahead(f, k, ld):
