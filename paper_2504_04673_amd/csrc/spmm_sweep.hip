@@ -1342,10 +1342,10 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
         sum.add(u, mv[u], h[u]);
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
           vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
-          *p += sum.take();
+          *p += tot + sum.take();
+          tot = 0.f;
         }
       }
-      sum.batch_ends();
     } else {
       if (e + 8 <= all_own) {
 #pragma unroll
@@ -1355,10 +1355,11 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
         for (int u = 0; u < 8; ++u)
           if (e + u < own) sum.add(u, mv[u], h[u]);
       }
-      sum.batch_ends();
-      // no slots to flush into: fold the running sum every 32 entries instead
-      if ((e & 31) == 24) tot += sum.take();
     }
+    sum.batch_ends();
+    // The running sum is folded every 32 entries: with 16 groups there are no slots to flush into, with 8 a long segment is
+    // nearer to exact (rows of 60 in one segment 7.5e-8 without, 6.9e-8 so, of 110 8.8e-8, 7.5e-8; as a tree 7.4e-8, 8.2e-8).
+    if ((e & 31) == 24) tot += sum.take();
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       cb[q] = ncb[q];
@@ -1600,15 +1601,18 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   if (local && opt.slab_kb == 0 && (f > 64 || (f > 32 && b_bytes >= (48ll << 20))))
     S = std::max(S, (int64_t)((nnz >= 64 * m ? 8.0 : 4.0) * (double)k / std::max(span, 1.0) + 0.5));
   // Small matrices: the columns that neighbouring rows choose from in four slabs where the order of the rows carries
-  // locality, in eight where all choose from the same, but four where nonzero splitting would add as a tree, and one per 64
-  // entries of a row at 17 to 32 columns, where a stream has two rows.  Error against 64 bits by nonzero splitting and so:
-  // random columns, 30 k vertices of 60, f = 16, 32, 64, 100, 256 7.3e-8, 7.4e-8, 12.2e-8, 7.7e-8, 13.1e-8 and 7.0e-8,
-  // 7.5e-8, 7.8e-8, 7.0e-8, 7.8e-8; communities 7.3e-8, 7.4e-8, 12.3e-8, 7.7e-8, 13.1e-8 and 7.0e-8, 7.5e-8, 8.7e-8,
-  // 7.7e-8, 8.7e-8 (in eight slabs for all 13.8e-8 from f = 64, and 131 us for 110 at f = 256).
+  // locality, in eight where all choose from the same; where nonzero splitting would add as a tree three and four; and at 17
+  // to 32 columns, where a stream has two rows and longer segments are folded, one per 64 entries of a row in all columns
+  // (an entry outside the community is a segment of its own in slabs of its size).  Error against 64 bits by nonzero splitting
+  // and so, e-8: random columns, 30 k vertices of 60, f = 16, 32, 64, 100, 256 7.2, 7.4, 12.2, 7.7, 13.1 and 6.9, 6.9, 7.8, 7.0,
+  // 7.8; sixteen communities 7.2, 7.4, 12.3, 7.7, 13.1 and 6.9, 6.9, 8.8, 7.64, 8.8, f = 48 7.59 and 7.64; of 110, f = 20, 48
+  // 8.2, 8.5 and 7.9, 8.6 (f = 20 in slabs that follow the communities 8.7); 80 k of 31, f = 48, 100 6.82, 6.82 and 6.83,
+  // 6.84 (in four slabs 6.90 at both).  In eight slabs for all 13.8e-8 from f = 64, and 131 us for 110 at f = 256.
   if (no_hubs && opt.slab_kb == 0) {
-    const double per_span = f > 16 && f <= 32 ? (double)ceil_div(nnz, 64 * m) : (local || tree ? 4.0 : 8.0);
-    S = per_span <= 1.0 ? 1 : (int64_t)(per_span * (double)k / std::max(span, 1.0) + 0.5);
+    if (f > 16 && f <= 32) S = ceil_div(nnz, 64 * m);
+    else S = (int64_t)((tree ? (local ? 3.0 : 4.0) : (local ? 4.0 : 8.0)) * (double)k / std::max(span, 1.0) + 0.5);
   }
+  if (S < 1) S = 1;
   if (S > kSweepMaxSlabs) S = kSweepMaxSlabs;
   const int64_t width = ceil_div(k, S);
   std::vector<int64_t> win_entries(1, long_entries);

@@ -674,6 +674,32 @@ def test_layer_on_a_schedule_in_groups_of_64_columns(f, f_out, prec):
     assert torch.equal(Hout, torch.relu(Z))
 
 
+@pytest.mark.parametrize("n,lo,hi,parts", [(30_000, 55, 65, 1), (30_000, 64, 64, 1), (30_000, 55, 65, 16), (30_000, 100, 120, 16), (80_000, 28, 34, 16)])
+@pytest.mark.parametrize("f", [20, 32, 48, 100])
+def test_spmm_small_matrices_swept_are_no_further_from_exact(f, n, lo, hi, parts):
+    """Small matrices whose sweep takes the place of nonzero splitting, which adds as a tree at these widths: the error
+    against 64 bits is no larger (1 %: rows in communities at 48 columns measure 0.7 % at most, the others less than by the
+    tree).  One entry in twenty lies outside its row's community."""
+    gen = torch.Generator(device="cuda").manual_seed(n + lo)
+    deg = torch.randint(lo, hi + 1, (n,), device="cuda", generator=gen)
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(deg, 0)
+    nnz, part = int(rp[-1]), n // parts
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), deg)
+    col = row // part * part + torch.randint(part, (nnz,), device="cuda", generator=gen)
+    col = torch.where(torch.rand(nnz, device="cuda", generator=gen) < 0.05, torch.randint(n, (nnz,), device="cuda", generator=gen), col)
+    ci = (torch.sort(row * n + col)[0] - row * n).to(torch.int32)
+    v, B = torch.randn(nnz, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    ref = torch.sparse_csr_tensor(rp.long(), ci.long(), v.double(), (n, n)) @ B.double()
+
+    def error(mode, options):
+        ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f, options=options)
+        assert ws.info()["mode"] == mode
+        return float((sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws).double() - ref).norm())
+
+    assert error(1, None) <= 1.01 * error(0, sagnn.SpmmOptions(schedule=1))
+
+
 @pytest.mark.parametrize("f", [4, 16, 20, 32, 36, 64, 72, 100, 128, 192, 256])
 @pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "around 64", "hub", "few"])
 def test_spmm_small_matrices_without_hubs(kind, f):
