@@ -1442,7 +1442,8 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const int64_t b_bytes = k * (int64_t)f * 4;
   // worth it only if B is much larger than an L2 (the long-row share is checked below) and there are enough entries
   // for balanced streams on every CU (2.4 M entries: 129 against 139 us at f = 128, 49 against 67 at f = 16; 4 M: 154
-  // against 146 the other way), or if no row is so long that it would have to be cut: then 1 M entries are enough, whatever
+  // against 146 the other way), or if there are no hubs (rows of more than 32 chunks of nonzero splitting; a tenth of the
+  // entries at most in rows that are cut into pieces, see below): then 1 M entries are enough, whatever
   // the size of B.  us by nonzero splitting and swept, random columns: 30 k vertices of 48, f = 16, 64, 256 34, 45, 190 and
   // 15, 33, 123; 100 k of 24 47, 91, 352 and 33, 64, 250; 100 k of 64, f = 16 109 and 50; 10 k of 120 28, 29, 115 and 17,
   // 30, 72; in communities: 30 k of 64 42, 44, 162 and 22, 38, 136; a row block of 85 k rows of 30, f = 64, 256 97, 375 and

@@ -539,7 +539,7 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
     wide = torch.randn(n, f + 12, device="cuda", generator=gen)
     B = wide[:, :f]
     ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
-    assert ws.info()["mode"] == 1 and ws.info()["groups"] == 1
+    assert ws.info()["mode"] == 1 and ws.info()["groups"] == 1 and ws.launch_info()["columns"] == 64
     A, Aabs = (torch.sparse_csr_tensor(rp.long(), ci.long(), x.double(), (n, n)) for x in (v, v.abs()))
     C0 = torch.randn(n, f, device="cuda", generator=gen)
     for w in {f, 64, 52}:
@@ -674,7 +674,7 @@ def test_layer_on_a_schedule_in_groups_of_64_columns(f, f_out, prec):
     assert torch.equal(Hout, torch.relu(Z))
 
 
-@pytest.mark.parametrize("n,lo,hi,parts", [(30_000, 55, 65, 1), (30_000, 64, 64, 1), (30_000, 55, 65, 16), (30_000, 100, 120, 16), (80_000, 28, 34, 16)])
+@pytest.mark.parametrize("n,lo,hi,parts", [(30_000, 55, 65, 1), (30_000, 64, 64, 1), (30_000, 55, 65, 16), (25_600, 70, 80, 4), (80_000, 28, 34, 16)])
 @pytest.mark.parametrize("f", [20, 32, 48, 100])
 def test_spmm_small_matrices_swept_are_no_further_from_exact(f, n, lo, hi, parts):
     """Small matrices whose sweep takes the place of nonzero splitting, which adds as a tree at these widths: the error
@@ -701,10 +701,11 @@ def test_spmm_small_matrices_swept_are_no_further_from_exact(f, n, lo, hi, parts
 
 
 @pytest.mark.parametrize("f", [4, 16, 20, 32, 36, 64, 72, 100, 128, 192, 256])
-@pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "around 64", "hub", "few"])
+@pytest.mark.parametrize("kind", ["even", "local", "empty rows", "long", "cut", "around 64", "hub", "few"])
 def test_spmm_small_matrices_without_hubs(kind, f):
     """From 1 M entries on a matrix whose rows are all of a size is swept; one row of many entries, or fewer entries, and it
-    is not.  Rows of 20 to 52 entries, some empty, some of exactly a piece's 256, or of 60 to 92; products, sums and the layer."""
+    is not.  Rows of 20 to 52 entries, some empty, some of exactly a piece's 256, some cut into two pieces, or of 60 to 92;
+    products, sums and the layer."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(f)
     m, k = (28_000 if kind == "few" else 31_003), 30_011
@@ -714,6 +715,8 @@ def test_spmm_small_matrices_without_hubs(kind, f):
         deg[1::7] += 24
     if kind == "long":
         deg[::500] = 256
+    if kind == "cut":
+        deg[::200] = torch.randint(257, 501, (deg[::200].numel(),), device="cuda", generator=gen)
     if kind == "around 64":
         deg += 40
     if kind == "hub":
@@ -732,6 +735,7 @@ def test_spmm_small_matrices_without_hubs(kind, f):
     ci32 = ci.to(torch.int32)
     ws = sagnn.spmm_csr_prepare(rp, ci32, v, k, f)
     assert ws.info()["mode"] == (0 if kind in ("hub", "few") else 1)
+    assert kind != "cut" or ws.info()["split_rows"] > 0
     ref = torch.zeros(m, f, dtype=torch.float64, device="cuda")
     size = torch.zeros_like(ref)
     for at in range(0, nnz, 1 << 18):
