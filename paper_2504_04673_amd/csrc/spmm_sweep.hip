@@ -1359,6 +1359,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     sum.batch_ends();
     // The running sum is folded every 32 entries: with 16 groups there are no slots to flush into, with 8 a long segment is
     // nearer to exact (rows of 60 in one segment 7.5e-8 without, 6.9e-8 so, of 110 8.8e-8, 7.5e-8; as a tree 7.4e-8, 8.2e-8).
+    // (Four groups and two would be 1 to 3 % slower for 0.2 to 2 %: what is left there are the entries outside a community.)
     if ((e & 31) == 24) tot += sum.take();
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
@@ -1516,11 +1517,22 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // 8 M columns, f = 64, 256 85, 298 and 124, 321).  Nonzero splitting adds as a tree at the widths under 128 but 64, and a
   // row's sum here has a term per slab: not swept at these where the slabs that locality needs are more than a row's
   // entries fill (a row block of 85 k rows of 30 in communities, f = 100 6.7e-8 from 64 bits, 7.5e-8 in the slabs of the
-  // other widths, 6.8e-8 in so few that nothing is gained).
+  // other widths, 6.8e-8 in so few that nothing is gained), nor long rows in many small communities, whose entries elsewhere
+  // are each a term (16 communities, 16 k of 75 f = 48 7.7e-8, 7.9e-8, of 140 f = 48, 100 8.5e-8, 9.0e-8, 9.0e-8, 9.0e-8).
+  // And few long rows make few streams, long ones: by nonzero splitting and swept 5 k of 220 f = 48, 64 23, 23 and 32, 33 us, 10 k
+  // of 228 f = 32, 48, 64 29, 38, 36 and 36, 41, 43, in communities, where the streams of a window are fewer, f = 48, 64, 128
+  // 36, 35, 54 and 57, 59, 59, 15 k of 180 f = 48, 64 44, 41 and 54, 53, 10 k of 228 f = 4 25, 27; but random columns, 10 k of 160, f = 16, 32, 256 30, 27,
+  // 148 and 18, 25, 76.
   const bool tree = f > 16 && f < 128 && f != 64;
-  if (no_hubs && (10 * tot.multi_pieces * (int64_t)piece_max > nnz || (f <= 32 && long_entries * 10 < nnz * 9) ||
-                  (double)nnz < 8.0 * span || (tree && !local && 2.0 * span < (double)k)))
-    return SAGNN_OK;
+  if (no_hubs) {
+    const double deg = (double)nnz / (double)m;
+    const bool few = (double)m < 64.0 * deg;
+    if (10 * tot.multi_pieces * (int64_t)piece_max > nnz || (f <= 32 && long_entries * 10 < nnz * 9) || (double)nnz < 8.0 * span ||
+        (tree && !local && 2.0 * span < (double)k) || (tree && f > 32 && local && 8.0 * span < (double)k && deg >= (f < 64 ? 64.0 : 128.0)) ||
+        (f > 32 && f <= 64 && (few || (local && (double)m < 128.0 * deg))) || (f <= 32 && few && deg >= 200.0) ||
+        (f > 64 && local && few && deg >= 150.0))
+      return SAGNN_OK;
+  }
   if (opt.groups != 2 && long_entries < 8 * k) {
     if (f <= 32) return SAGNN_OK;  // one row per instruction would leave most lanes idle: plain schedule
     R = 1;

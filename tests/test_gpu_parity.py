@@ -674,7 +674,7 @@ def test_layer_on_a_schedule_in_groups_of_64_columns(f, f_out, prec):
     assert torch.equal(Hout, torch.relu(Z))
 
 
-@pytest.mark.parametrize("n,lo,hi,parts", [(30_000, 55, 65, 1), (30_000, 64, 64, 1), (30_000, 55, 65, 16), (25_600, 70, 80, 4), (80_000, 28, 34, 16)])
+@pytest.mark.parametrize("n,lo,hi,parts", [(30_000, 55, 65, 1), (30_000, 64, 64, 1), (30_000, 55, 65, 16), (25_600, 100, 120, 16), (80_000, 28, 34, 16)])
 @pytest.mark.parametrize("f", [20, 32, 48, 100])
 def test_spmm_small_matrices_swept_are_no_further_from_exact(f, n, lo, hi, parts):
     """Small matrices whose sweep takes the place of nonzero splitting, which adds as a tree at these widths: the error
@@ -697,7 +697,25 @@ def test_spmm_small_matrices_swept_are_no_further_from_exact(f, n, lo, hi, parts
         assert ws.info()["mode"] == mode
         return float((sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws).double() - ref).norm())
 
-    assert error(1, None) <= 1.01 * error(0, sagnn.SpmmOptions(schedule=1))
+    assert error(0 if lo == 100 and f == 48 else 1, None) <= 1.01 * error(0, sagnn.SpmmOptions(schedule=1))
+
+
+@pytest.mark.parametrize("n,deg,parts,f,mode", [(10_000, 160, 1, 16, 1), (10_000, 228, 1, 16, 0), (10_000, 228, 1, 32, 0), (10_000, 228, 1, 48, 0), (10_000, 228, 1, 64, 0),
+                                                (10_000, 228, 1, 256, 1), (5_000, 220, 4, 128, 0), (14_400, 180, 16, 64, 0), (14_400, 180, 16, 256, 1)])
+def test_spmm_few_long_rows_without_hubs(n, deg, parts, f, mode):
+    """Few long rows make few, long streams: such small matrices are swept only where that is faster."""
+    gen = torch.Generator(device="cuda").manual_seed(f)
+    part = n // parts
+    home = (torch.arange(n, device="cuda") // part * part)[:, None]
+    ci = torch.sort(home + torch.randint(part, (n, deg), device="cuda", generator=gen), dim=1)[0].to(torch.int32)
+    rp = torch.arange(0, n * deg + 1, deg, dtype=torch.int32, device="cuda")
+    v, B = torch.randn(n * deg, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    ws = sagnn.spmm_csr_prepare(rp, ci.reshape(-1), v, n, f)
+    assert ws.info()["mode"] == mode
+    C = sagnn.spmm_csr_tallskinny(rp, ci.reshape(-1), v, B, ws=ws)
+    rows = torch.arange(0, n, 13, device="cuda")
+    t = v.reshape(n, deg)[rows].double()[:, :, None] * B[ci[rows].long()].double()
+    assert bool(((C[rows].double() - t.sum(1)).abs() <= (deg + 2) * 2.0 ** -24 * t.abs().sum(1)).all())
 
 
 @pytest.mark.parametrize("f", [4, 16, 20, 32, 36, 64, 72, 100, 128, 192, 256])
