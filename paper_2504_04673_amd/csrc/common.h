@@ -332,12 +332,14 @@ struct SweepRowTotals {
   bool has_empty, bad;
 };
 bool sweep_plan_fits(const SpmmWsLayout& L);
-// classify rows, build the short-row CSR, the list of split rows and the piece records; one
+// what the rows look like: the threshold of long rows, locality, span (d_colidx may be null: no locality then).  With `out`
+// the host waits for it: bad, min_long, locality, span, and short_entries where the threshold is the lowest (0 otherwise)
+int sweep_plan_sample(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz, int32_t opt_min_long,
+                      char* ws, const SpmmWsLayout& L, hipStream_t s, SweepRowTotals* out);
+// behind sweep_plan_sample: classify rows, build the short-row CSR, the list of split rows and the piece records; one
 // stream synchronisation (a 128-byte copy)
 // (short_pieces: the short rows also get piece records, one whole row each, behind those of the long rows)
-// (d_colidx may be null: no locality then)
-int sweep_plan_rows(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz,
-                    int32_t opt_min_long, int32_t piece_max, char* ws, const SpmmWsLayout& L, hipStream_t s,
+int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int32_t piece_max, char* ws, const SpmmWsLayout& L, hipStream_t s,
                     SweepRowTotals* out, bool short_pieces = false);
 // entries of the pieces of every window (only needed with several windows; synchronises)
 int sweep_plan_window_entries(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, int32_t nwin,

@@ -1455,16 +1455,46 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   int piece_max = opt.piece > 0 ? opt.piece : (force == 1 ? 4096 : sweep_piece_default(nnz, f));
   if (piece_max < sweep_piece_floor(nnz, f)) piece_max = sweep_piece_floor(nnz, f);
   if (piece_max > 32768) piece_max = 32768;
-  // Row classification, the short-row CSR, the list of split rows and one record per piece are
-  // made on the device (the long-row threshold is chosen there from the degree distribution);
-  // the host gets the totals.
+  constexpr int kLocalPermille = 400;   // (between what the two kinds of order measure, see the windows below)
+  const bool tree = f > 16 && f < 128 && f != 64;
   SweepRowTotals tot{};
+  // Without hubs, small: short rows are swept beside the others above 32 columns only (100 k rows of 16, 55 % of the entries
+  // in rows of 16 or more, f = 16 29 us by nonzero splitting, 31 swept); hardly any re-use (a rank's 125 k rows of 15 by
+  // 8 M columns, f = 64, 256 85, 298 and 124, 321).  Nonzero splitting adds as a tree at the widths under 128 but 64, and a
+  // row's sum here has a term per slab: not swept at these where the slabs that locality needs are more than a row's
+  // entries fill (a row block of 85 k rows of 30 in communities, f = 100 6.7e-8 from 64 bits, 7.5e-8 in the slabs of the
+  // other widths, 6.8e-8 in so few that nothing is gained), nor long rows in many small communities, whose entries elsewhere
+  // are each a term (16 communities, 16 k of 75 f = 48 7.7e-8, 7.9e-8, of 140 f = 48, 100 8.5e-8, 9.0e-8, 9.0e-8, 9.0e-8).
+  // And few long rows make few streams, long ones: by nonzero splitting and swept 5 k of 220 f = 48, 64 23, 23 and 32, 33 us, 10 k
+  // of 228 f = 32, 48, 64 29, 38, 36 and 36, 41, 43, in communities, where the streams of a window are fewer, f = 48, 64, 128
+  // 36, 35, 54 and 57, 59, 59, 15 k of 180 f = 48, 64 44, 41 and 54, 53, 10 k of 228 f = 4 25, 27; but random columns, 10 k of 160, f = 16, 32, 256 30, 27,
+  // 148 and 18, 25, 76.
+  auto small_refused = [&]() {
+    const int64_t long_entries = nnz - tot.short_entries;
+    const bool local = tot.locality >= kLocalPermille;
+    const double span = (double)k * tot.span / 1000.0, deg = (double)nnz / (double)m;
+    const bool few = (double)m < 64.0 * deg;
+    return (f <= 32 && long_entries * 10 < nnz * 9) || (double)nnz < 8.0 * span || (tree && !local && 2.0 * span < (double)k) ||
+           (tree && f > 32 && local && 8.0 * span < (double)k && deg >= (f < 64 ? 64.0 : 128.0)) ||
+           (f > 32 && f <= 64 && (few || (local && (double)m < 128.0 * deg))) || (f <= 32 && few && deg >= 200.0) ||
+           (f > 64 && local && few && deg >= 150.0) || long_entries * 10 < nnz * 3 ||
+           (opt.groups != 2 && f <= 32 && long_entries < 8 * k);
+  };
+  // (without hubs every row that may be is long: sixteen short rows of up to 63 entries are several times the stream of a
+  // small matrix' other wavefronts.  15 k rows of 80, f = 64, 256 32, 139 us by nonzero splitting, 46, 126 with rows from
+  // 64 entries on long, 27, 78 from 16 on)
+  const int32_t min_long = no_hubs && opt.min_long <= 0 ? kSweepMinLong : opt.min_long;   // (negative: "where 64 is picked")
+  if (no_hubs && opt.groups != 2 && f <= 32 && nnz < 8 * k) return SAGNN_OK;              // (see small_refused)
   {
-    // (without hubs every row that may be is long: sixteen short rows of up to 63 entries are several times the stream of a
-    // small matrix' other wavefronts.  15 k rows of 80, f = 64, 256 32, 139 us by nonzero splitting, 46, 126 with rows from
-    // 64 entries on long, 27, 78 from 16 on)
-    const int32_t min_long = no_hubs && opt.min_long <= 0 ? kSweepMinLong : opt.min_long;   // (negative: "where 64 is picked")
-    const int rc = sweep_plan_rows(d_rowptr, d_colidx, m, k, nnz, min_long, piece_max, ws, L, s, &tot, opt.short_rows >= 0);
+    // (small matrices that are refused are so by what the sample tells: looking costs them 50 us, with the pass over their
+    // rows 90; 100 k rows of 16, f = 16 49 us without, 99)
+    int rc = sweep_plan_sample(d_rowptr, d_colidx, m, k, nnz, min_long, ws, L, s, no_hubs ? &tot : nullptr);
+    if (rc != SAGNN_OK) return rc;
+    if (no_hubs && (tot.bad || small_refused())) return SAGNN_OK;
+    // Row classification, the short-row CSR, the list of split rows and one record per piece are
+    // made on the device (the long-row threshold is chosen there from the degree distribution);
+    // the host gets the totals.
+    rc = sweep_plan_rows(d_rowptr, m, piece_max, ws, L, s, &tot, opt.short_rows >= 0);
     if (rc != SAGNN_OK) return rc;
   }
   if (tot.bad) return SAGNN_OK;   // not a CSR row pointer for this nnz: keep the plain schedule
@@ -1484,7 +1514,6 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // splitting, 1905 swept; f = 48 3599 and 2560, f = 100 8135 and 5407, f = 200 13857 and 8598).
   // Wider operands (multiples of 64 above 128) can be taken as 128-wide slabs by the two-group
   // kernels (a last slab of 64 is served by the same streams): an option, see sagnn_spmm_options.
-  constexpr int kLocalPermille = 400;   // (between what the two kinds of order measure, see the windows below)
   const bool narrow_slabs = opt.slab_width == 128 && f > 128 && (f & 63) == 0 && opt.groups != 1;
   // Columns 64 at a time, one row per load and one stream per wavefront, where the product costs what its L2 misses cost
   // and the rows that are resident together want the same rows of B: an XCD holds 16384 rows of A then (256 workgroups of
@@ -1512,27 +1541,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
-  // Without hubs, small: short rows are swept beside the others above 32 columns only (100 k rows of 16, 55 % of the entries
-  // in rows of 16 or more, f = 16 29 us by nonzero splitting, 31 swept); hardly any re-use (a rank's 125 k rows of 15 by
-  // 8 M columns, f = 64, 256 85, 298 and 124, 321).  Nonzero splitting adds as a tree at the widths under 128 but 64, and a
-  // row's sum here has a term per slab: not swept at these where the slabs that locality needs are more than a row's
-  // entries fill (a row block of 85 k rows of 30 in communities, f = 100 6.7e-8 from 64 bits, 7.5e-8 in the slabs of the
-  // other widths, 6.8e-8 in so few that nothing is gained), nor long rows in many small communities, whose entries elsewhere
-  // are each a term (16 communities, 16 k of 75 f = 48 7.7e-8, 7.9e-8, of 140 f = 48, 100 8.5e-8, 9.0e-8, 9.0e-8, 9.0e-8).
-  // And few long rows make few streams, long ones: by nonzero splitting and swept 5 k of 220 f = 48, 64 23, 23 and 32, 33 us, 10 k
-  // of 228 f = 32, 48, 64 29, 38, 36 and 36, 41, 43, in communities, where the streams of a window are fewer, f = 48, 64, 128
-  // 36, 35, 54 and 57, 59, 59, 15 k of 180 f = 48, 64 44, 41 and 54, 53, 10 k of 228 f = 4 25, 27; but random columns, 10 k of 160, f = 16, 32, 256 30, 27,
-  // 148 and 18, 25, 76.
-  const bool tree = f > 16 && f < 128 && f != 64;
-  if (no_hubs) {
-    const double deg = (double)nnz / (double)m;
-    const bool few = (double)m < 64.0 * deg;
-    if (10 * tot.multi_pieces * (int64_t)piece_max > nnz || (f <= 32 && long_entries * 10 < nnz * 9) || (double)nnz < 8.0 * span ||
-        (tree && !local && 2.0 * span < (double)k) || (tree && f > 32 && local && 8.0 * span < (double)k && deg >= (f < 64 ? 64.0 : 128.0)) ||
-        (f > 32 && f <= 64 && (few || (local && (double)m < 128.0 * deg))) || (f <= 32 && few && deg >= 200.0) ||
-        (f > 64 && local && few && deg >= 150.0))
-      return SAGNN_OK;
-  }
+  if (no_hubs && (10 * tot.multi_pieces * (int64_t)piece_max > nnz || small_refused())) return SAGNN_OK;
   if (opt.groups != 2 && long_entries < 8 * k) {
     if (f <= 32) return SAGNN_OK;  // one row per instruction would leave most lanes idle: plain schedule
     R = 1;

@@ -33,6 +33,7 @@ enum Stat : int {
   ST_MID = 0,       // entries in rows of kSweepMinLong..63 entries
   ST_EMPTY,         // rows without entries
   ST_BAD,           // != 0: not a CSR row pointer for this nnz, or a row needs too many pieces
+  ST_FROM_MIN,      // entries in rows of kSweepMinLong and more
   ST_MINLONG,       // the degree from which a row is swept
   ST_PIECES,        // five totals of the row scan, in the order of RowQ
   ST_SHORT_ROWS,
@@ -51,30 +52,35 @@ __global__ __launch_bounds__(kT) void plan_zero_kernel(unsigned long long* __res
 
 __global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restrict__ rowptr, int64_t m,
                                                           int64_t nnz, unsigned long long* __restrict__ stat) {
-  long long mid = 0, empty = 0, bad = 0;
+  long long mid = 0, empty = 0, bad = 0, from_min = 0;
   const int64_t stride = (int64_t)gridDim.x * kT;
   for (int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x; r < m; r += stride) {
     const int64_t d = (int64_t)rowptr[r + 1] - rowptr[r];
     if (d < 0) bad = 1;
     else if (d == 0) ++empty;
-    else if (d >= kSweepMinLong && d < 64) mid += d;
+    else if (d >= kSweepMinLong) {
+      from_min += d;
+      if (d < 64) mid += d;
+    }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && (rowptr[0] != 0 || (int64_t)rowptr[m] != nnz)) bad = 1;
-  __shared__ long long part[kT / 64][3];
+  __shared__ long long part[kT / 64][4];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     mid += __shfl_down(mid, o, 64);
     empty += __shfl_down(empty, o, 64);
     bad += __shfl_down(bad, o, 64);
+    from_min += __shfl_down(from_min, o, 64);
   }
   if ((threadIdx.x & 63) == 0) {
     part[threadIdx.x >> 6][0] = mid;
     part[threadIdx.x >> 6][1] = empty;
     part[threadIdx.x >> 6][2] = bad;
+    part[threadIdx.x >> 6][3] = from_min;
   }
   __syncthreads();
-  if (threadIdx.x < 3) {
-    static_assert(ST_MID == 0 && ST_EMPTY == 1 && ST_BAD == 2, "order of part[]");
+  if (threadIdx.x < 4) {
+    static_assert(ST_MID == 0 && ST_EMPTY == 1 && ST_BAD == 2 && ST_FROM_MIN == 3, "order of part[]");
     long long t = 0;
     for (int w = 0; w < kT / 64; ++w) t += part[w][threadIdx.x];
     if (t) atomicAdd(&stat[threadIdx.x], (unsigned long long)t);
@@ -594,13 +600,10 @@ bool sweep_plan_fits(const SpmmWsLayout& L) {
   return carve_plan(nullptr, L.max_pieces, L.max_waves * kSweepSlots).bytes <= have;
 }
 
-int sweep_plan_rows(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz,
-                    int32_t opt_min_long, int32_t piece_max, char* ws, const SpmmWsLayout& L, hipStream_t s,
-                    SweepRowTotals* out, bool short_pieces) {
+int sweep_plan_sample(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz, int32_t opt_min_long,
+                      char* ws, const SpmmWsLayout& L, hipStream_t s, SweepRowTotals* out) {
   const PlanSmall sm = carve_small(ws, L);
-  const PlanScratch sc = carve_plan(ws + L.code, L.max_pieces, L.max_waves * kSweepSlots);
   int32_t* d_flag = reinterpret_cast<int32_t*>(ws + L.carry);
-  const int64_t ntiles = ceil_div(m, kRowTile);
   hipLaunchKernelGGL(plan_zero_kernel, dim3(1), dim3(kT), 0, s, sm.stat, d_flag);
   SAGNN_LAUNCH_CHECK();
   // (few workgroups: all of them add to one cache line)
@@ -613,6 +616,24 @@ int sweep_plan_rows(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m,
   }
   hipLaunchKernelGGL(plan_rule_kernel, dim3(1), dim3(64), 0, s, sm.stat, nnz, opt_min_long);
   SAGNN_LAUNCH_CHECK();
+  if (out) {
+    unsigned long long h[ST_COUNT];
+    SAGNN_HIP(hipMemcpyAsync(h, sm.stat, sizeof(h), hipMemcpyDeviceToHost, s));
+    SAGNN_HIP(hipStreamSynchronize(s));
+    out->bad = h[ST_BAD] != 0;
+    out->min_long = (int32_t)h[ST_MINLONG];
+    out->locality = (int32_t)h[ST_LOCALITY];
+    out->span = (int32_t)h[ST_SPAN];
+    out->short_entries = out->min_long == kSweepMinLong ? nnz - (int64_t)h[ST_FROM_MIN] : 0;
+  }
+  return SAGNN_OK;
+}
+
+int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int32_t piece_max, char* ws, const SpmmWsLayout& L, hipStream_t s,
+                    SweepRowTotals* out, bool short_pieces) {
+  const PlanSmall sm = carve_small(ws, L);
+  const PlanScratch sc = carve_plan(ws + L.code, L.max_pieces, L.max_waves * kSweepSlots);
+  const int64_t ntiles = ceil_div(m, kRowTile);
   int32_t* rowptr_s = reinterpret_cast<int32_t*>(ws + L.rowptr_s);
   int32_t* rowmap_s = reinterpret_cast<int32_t*>(ws + L.rowmap_s);
   int32_t* multi_row = reinterpret_cast<int32_t*>(ws + L.multi_row);
