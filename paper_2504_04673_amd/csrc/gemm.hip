@@ -488,7 +488,11 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
     };
     const int va = columns(fi), vb = columns(fo);
     const int nbx = (fi + 16 * va - 1) / (16 * va), nbs = (fo + 16 * vb - 1) / (16 * vb), nb = nbx * nbs;
-    const int waves = td_waves(prec), nwg = (nb + waves - 1) / waves, per = (nb + nwg - 1) / nwg;
+    // Blocks of Y in a workgroup: one for each wavefront, but eight where sixteen would leave half of the CUs without a
+    // workgroup (256 x 256 behind a product of one entry a row, 1000, 4000, 10000 rows 58, 62, 65 us with sixteen, 33, 39, 41
+    // with eight; 20000 x 256 x 160 55, 59).
+    const int waves = td_waves(prec), most = parts <= 128 ? std::min(waves, 8) : waves;
+    const int nwg = (nb + most - 1) / most, per = (nb + nwg - 1) / nwg;
     // Shares of a slice's rows: one for each wavefront, but of eight where a slice has 128 rows, the fewest (30 k x 128 x
     // 128: 21 us with sixteen, 18 with eight).  Still fewer would take up to 2 us off such calls, but sums of 64 rows in a
     // chain are up to 1.4 times as far from exact as sums of 16.

@@ -1563,6 +1563,20 @@ def test_weight_gradient_with_three_columns_a_lane(m, fin, fout):
         assert bool(((Y.cpu().double() - ref).abs() <= (m + 2) * 2.0**-24 * size)[first:].all())
 
 
+@pytest.mark.parametrize("fin,fout", [(256, 256), (200, 160), (144, 256)])
+@pytest.mark.parametrize("m", [1, 129, 1000, 16_384, 16_385, 40_003])
+def test_weight_gradient_of_more_than_eight_blocks(m, fin, fout):
+    """Nine to sixteen blocks of Y: eight a workgroup up to 128 slices of 128 rows, sixteen beyond."""
+    gen = torch.Generator().manual_seed(m + fin)
+    rp = torch.arange(m + 1, dtype=torch.int32, device="cuda")
+    ci, v = torch.arange(m, dtype=torch.int32, device="cuda"), torch.ones(m, device="cuda")
+    H, G, W = torch.randn(m, fin, generator=gen), torch.randn(m, fout, generator=gen), torch.zeros(fin, fout, device="cuda")
+    ref, size = H.double().T @ G.double(), H.abs().double().T @ G.abs().double()
+    _, _, Y = sagnn.gcn_layer_bwd(rp, ci, v, G.cuda(), W, None, H.cuda(), prec=sagnn.GEMM_FP32, want_gprev=False)
+    # any order of m additions: at most m 2^-24 of the sum of the terms' sizes
+    assert bool(((Y.cpu().double() - ref).abs() <= (m + 2) * 2.0**-24 * size).all())
+
+
 @pytest.mark.parametrize("prec,fin,fout", [(0, 128, 128), (1, 256, 256), (0, 64, 32), (0, 16, 16), (1, 48, 20),
                                            (2, 128, 128), (2, 256, 256), (2, 48, 20)])
 def test_gcn_layer_fwd_bwd_small(prec, fin, fout):
