@@ -1253,7 +1253,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
 // lands behind the last flush; here it would land in the result, so the steps behind the end of the wavefront's shortest
 // stream are masked per lane (no check in the steps before: 1 M vertices, 50 M entries, training at f = 16
 // 2281 us without and 2283 with the masks).
-template <int R, bool BUF, bool ODD>
+template <int R, bool BUF, bool ODD, bool TURN>
 __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1308,9 +1308,9 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     cb[q] = steps > 0 ? cw[q * 64 + lane] : 0u;
     vb[q] = steps > 0 ? vw[q * 64 + lane] : 0.f;
   }
-  TurnTaking turn(steps, d.turn);
+  [[maybe_unused]] TurnTaking turn(steps, d.turn);
   for (int32_t e = 0; e < steps; e += 8) {
-    if constexpr (SL > 1) turn.at(e);
+    if constexpr (TURN) turn.at(e);
     // the next iteration's stream words are requested before this one's gathers are waited for
     const bool more = e + 8 < steps;
     uint32_t ncb[NB];
@@ -1534,14 +1534,15 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const double span = (double)k * tot.span / 1000.0;
   // how often the 16384 rows of A that an XCD holds at 64 columns a launch want a row of the columns they choose from
   const double reuse = 16384.0 * (double)nnz / (std::max(span, 1.0) * (double)m);
+  const bool hubs = 10 * tot.multi_pieces * (int64_t)piece_max > nnz;   // a tenth of the entries in rows that are cut
   const bool col_groups = f >= 64 && (f & 63) == 0 && opt.groups == 0 && opt.slab_width == 0 && opt.sync_slabs <= 0 &&
                           opt.barriers != 1 && opt.pace_ps_per_step <= 0 && span >= 40000.0 &&
-                          reuse >= 0.6 && 10 * tot.multi_pieces * (int64_t)piece_max <= nnz &&
+                          reuse >= 0.6 && !hubs &&
                           (!local || (nnz >= 18 * m && span >= 60000.0));
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries
-  if (no_hubs && (10 * tot.multi_pieces * (int64_t)piece_max > nnz || small_refused())) return SAGNN_OK;
+  if (no_hubs && (hubs || small_refused())) return SAGNN_OK;
   if (opt.groups != 2 && long_entries < 8 * k) {
     if (f <= 32) return SAGNN_OK;  // one row per instruction would leave most lanes idle: plain schedule
     R = 1;
@@ -1800,6 +1801,12 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
   h.fused_waves = local ? h.launch_waves / 2 : 0;
   out->reuse = (float)reuse;
+  // Turns with eight groups, f = 20, 32, us without and with: with hubs where resident rows use a row of B often, 300 k vertices
+  // of 200 566, 535 and 539, 510, 233 k of 489 961, 930 and 934, 904; but 300 k of 30 (1.6 uses) 140, 122 and 143, 125, 1.5 M of
+  // 51 930, 824 and 976, 874, 2 M of 51 1266, 1100 and 1301, 1139 (1 M and 2.45 M of 51 596 and 1568, 1356 with, 1 % more
+  // without); else but where rows of a community are short, 500 k of 45, random, 441, 408 and 425, 390, 100 k of 24 40, 37 and
+  // 35, 35, 2 M of 35 in communities 1136, 1029 and 1121, 992, but 1 M of 18 318, 275 and 330, 281, of 26 390, 339 and 396, 345.
+  out->narrow_turns = hubs ? reuse >= 4.0 : !local || nnz >= 30 * m;
   out->mean_steps = rec.scan.mean_steps;
   out->max_steps = rec.scan.max_steps;
   out->use_sweep = true;
@@ -1940,13 +1947,16 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   if (fw <= 0 || (fw & 3)) return SAGNN_EINVAL;
   if (d.groups == 16) {  // four lanes per row
     if (fw > 16) return SAGNN_EINVAL;
-    if (fw == 16) return buf ? go_perm(spmm_sweep_perm_kernel<16, true, false>) : go_perm(spmm_sweep_perm_kernel<16, false, false>);
-    return buf ? go_perm(spmm_sweep_perm_kernel<16, true, true>) : go_perm(spmm_sweep_perm_kernel<16, false, true>);
+    if (fw == 16) return buf ? go_perm(spmm_sweep_perm_kernel<16, true, false, false>) : go_perm(spmm_sweep_perm_kernel<16, false, false, false>);
+    return buf ? go_perm(spmm_sweep_perm_kernel<16, true, true, false>) : go_perm(spmm_sweep_perm_kernel<16, false, true, false>);
   }
   if (d.groups == 8) {   // eight lanes per row
     if (fw > 32) return SAGNN_EINVAL;
-    if (fw == 32) return buf ? go_perm(spmm_sweep_perm_kernel<8, true, false>) : go_perm(spmm_sweep_perm_kernel<8, false, false>);
-    return buf ? go_perm(spmm_sweep_perm_kernel<8, true, true>) : go_perm(spmm_sweep_perm_kernel<8, false, true>);
+#define SAGNN_EIGHT(ODD_, TURN_) \
+  (buf ? go_perm(spmm_sweep_perm_kernel<8, true, ODD_, TURN_>) : go_perm(spmm_sweep_perm_kernel<8, false, ODD_, TURN_>))
+    if (fw == 32) return d.narrow_turns ? SAGNN_EIGHT(false, true) : SAGNN_EIGHT(false, false);
+    return d.narrow_turns ? SAGNN_EIGHT(true, true) : SAGNN_EIGHT(true, false);
+#undef SAGNN_EIGHT
   }
   if (d.groups == 2) {   // half a wavefront per row
     // Words ahead (see the kernel) up to a size of the operand, whatever its addressing, in the product and in the layer:
