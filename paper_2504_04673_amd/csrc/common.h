@@ -262,6 +262,7 @@ struct SpmmHostDesc {
                             // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
   float reuse;              // uses of a row of B among the rows of A that an XCD holds (see sweep_prepare)
   bool narrow_turns;        // wavefronts of eight lane groups take turns (see there)
+  int32_t narrow_sums;      // sums of eight lane groups: 0 plain, 1 two, 2 two and folded (see there)
   float mean_steps;         // average stream steps per wavefront (the end of the pacing schedule)
   float max_steps;          // steps of the longest stream
   // dense-tile schedule (tiles.hip): when tiles != 0 everything above describes the rest CSR
@@ -314,6 +315,7 @@ struct SweepPlanResult {
   bool use_sweep;
   float reuse;       // see SpmmHostDesc
   bool narrow_turns; // see there
+  int32_t narrow_sums;
   float mean_steps;  // average stream steps per wavefront
   float max_steps;   // steps of the longest stream
   SpmmWsHeader hdr;  // filled in for mode 1 (sweep part + short CSR sizes)

@@ -629,8 +629,9 @@ __device__ __forceinline__ uint32_t row_element(uint32_t at, int v, int32_t fw) 
 }
 
 // Sum of a segment.  TWO: the entries of a batch of eight in two sums, then the batches, where a plain sum goes on through
-// the segment.  For the widths between the kernels' own (ODD) below 64, and below 128 with one row per load, for 16 and 32
-// (1 M vertices, 50 M entries, training at f = 16 2267 us with a plain sum, 2249 so), and below 128 in small matrices:
+// the segment.  For the widths between the kernels' own (ODD) below 64, and below 128 with one row per load, for 16, for 32
+// by the length of the segments (1 M vertices, 50 M entries, training at f = 16 2267 us with a plain sum, 2249 so), and below
+// 128 in small matrices:
 // nonzero splitting, which had these widths before, added their entries as a tree.  Error against 64 bits (2-norm) by the tree,
 // by a plain sum, by two: 300 k vertices of 42 in 16 communities f = 8 6.9e-8, 1.18e-7, 6.9e-8, f = 48 7.8e-8, 1.17e-7,
 // 7.4e-8; a rank's rows f = 48 3.0e-8, 3.6e-8, 3.2e-8.  (What is left is the order of the slabs: random columns, 40 a row,
@@ -1253,7 +1254,9 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
 // lands behind the last flush; here it would land in the result, so the steps behind the end of the wavefront's shortest
 // stream are masked per lane (no check in the steps before: 1 M vertices, 50 M entries, training at f = 16
 // 2281 us without and 2283 with the masks).
-template <int R, bool BUF, bool ODD, bool TURN>
+// TWO: two sums (SegmentSum), FOLD: the running sum is folded every 32 entries; with 16 groups always both, with 8 by the
+// length of the segments (narrow_sums).
+template <int R, bool BUF, bool ODD, bool TURN, bool TWO, bool FOLD>
 __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1299,8 +1302,8 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     all_own = __builtin_amdgcn_readfirstlane(all_own);
   }
 
-  SegmentSum<vec, true> sum;
-  vec tot = 0.f;
+  SegmentSum<vec, TWO> sum;
+  [[maybe_unused]] vec tot = 0.f;
   uint32_t cb[NB];
   float vb[NB];
 #pragma unroll
@@ -1342,8 +1345,12 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
         sum.add(u, mv[u], h[u]);
         if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
           vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
-          *p += tot + sum.take();
-          tot = 0.f;
+          if constexpr (FOLD) {
+            *p += tot + sum.take();
+            tot = 0.f;
+          } else {
+            *p += sum.take();
+          }
         }
       }
     } else {
@@ -1357,10 +1364,10 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
       }
     }
     sum.batch_ends();
-    // The running sum is folded every 32 entries: with 16 groups there are no slots to flush into, with 8 a long segment is
-    // nearer to exact (rows of 60 in one segment 7.5e-8 without, 6.9e-8 so, of 110 8.8e-8, 7.5e-8; as a tree 7.4e-8, 8.2e-8).
-    // (Four groups and two would be 1 to 3 % slower for 0.2 to 2 %: what is left there are the entries outside a community.)
-    if ((e & 31) == 24) tot += sum.take();
+    // (folded every 32 entries: with 16 groups there are no slots to flush into; four groups and two would be 1 to 3 % slower
+    // for 0.2 to 2 %, what is left there are the entries outside a community)
+    if constexpr (FOLD)
+      if ((e & 31) == 24) tot += sum.take();
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       cb[q] = ncb[q];
@@ -1801,6 +1808,15 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
   h.fused_waves = local ? h.launch_waves / 2 : 0;
   out->reuse = (float)reuse;
+  // Sums of eight groups by the entries a segment has on average, as many of a row's as lie in one of the slabs that it
+  // chooses from.  At 32 columns plain of short ones, two from 6 on, between the kernel's widths, which nonzero splitting added
+  // as a tree, two at least; folded from 36 on, without locality with the two.  Error against 64 bits plain, with two sums, folded, e-8: random columns,
+  // 300 k of 20 (1.3 a segment) 7.17, 7.34, 7.34, of 60 (3.8) 8.69, 8.81, 8.81, 200 k of 60 (7.5) 7.84, 7.57, 7.57;
+  // communities, 500 k of 16 7.02, 6.02, 6.02, of 32 10.2, 6.92, 6.91, of 42 11.7, 7.42, 7.16, 150 k of 110 18.5, 9.47, 8.42;
+  // rows within 3000 of the diagonal, of 30 9.72, 6.43, 6.52.  Folding takes random columns, 200 k of 120, 150 k of 200
+  // from 248, 291 to 241, 285 us, power-law matrices, as near every way, 500 k of 30, take 199 plain, 207, 212.
+  const double segment = (double)nnz / (double)m / std::max(1.0, (double)S * span / (double)k);
+  out->narrow_sums = segment >= 36.0 || (segment >= 6.0 && !local) ? 2 : (segment >= 6.0 ? 1 : 0);
   // Turns with eight groups, f = 20, 32, us without and with: with hubs where resident rows use a row of B often, 300 k vertices
   // of 200 566, 535 and 539, 510, 233 k of 489 961, 930 and 934, 904; but 300 k of 30 (1.6 uses) 140, 122 and 143, 125, 1.5 M of
   // 51 930, 824 and 976, 874, 2 M of 51 1266, 1100 and 1301, 1139 (1 M and 2.45 M of 51 596 and 1568, 1356 with, 1 % more
@@ -1947,15 +1963,21 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   if (fw <= 0 || (fw & 3)) return SAGNN_EINVAL;
   if (d.groups == 16) {  // four lanes per row
     if (fw > 16) return SAGNN_EINVAL;
-    if (fw == 16) return buf ? go_perm(spmm_sweep_perm_kernel<16, true, false, false>) : go_perm(spmm_sweep_perm_kernel<16, false, false, false>);
-    return buf ? go_perm(spmm_sweep_perm_kernel<16, true, true, false>) : go_perm(spmm_sweep_perm_kernel<16, false, true, false>);
+#define SAGNN_SIXTEEN(ODD_) \
+  (buf ? go_perm(spmm_sweep_perm_kernel<16, true, ODD_, false, true, true>) : go_perm(spmm_sweep_perm_kernel<16, false, ODD_, false, true, true>))
+    return fw == 16 ? SAGNN_SIXTEEN(false) : SAGNN_SIXTEEN(true);
+#undef SAGNN_SIXTEEN
   }
   if (d.groups == 8) {   // eight lanes per row
     if (fw > 32) return SAGNN_EINVAL;
-#define SAGNN_EIGHT(ODD_, TURN_) \
-  (buf ? go_perm(spmm_sweep_perm_kernel<8, true, ODD_, TURN_>) : go_perm(spmm_sweep_perm_kernel<8, false, ODD_, TURN_>))
-    if (fw == 32) return d.narrow_turns ? SAGNN_EIGHT(false, true) : SAGNN_EIGHT(false, false);
-    return d.narrow_turns ? SAGNN_EIGHT(true, true) : SAGNN_EIGHT(true, false);
+#define SAGNN_EIGHT(ODD_, TURN_, TWO_, FOLD_)                                      \
+  (buf ? go_perm(spmm_sweep_perm_kernel<8, true, ODD_, TURN_, TWO_, FOLD_>) \
+       : go_perm(spmm_sweep_perm_kernel<8, false, ODD_, TURN_, TWO_, FOLD_>))
+    if (d.narrow_sums == 2 && fw == 32) return d.narrow_turns ? SAGNN_EIGHT(false, true, true, true) : SAGNN_EIGHT(false, false, true, true);
+    if (d.narrow_sums == 2) return d.narrow_turns ? SAGNN_EIGHT(true, true, true, true) : SAGNN_EIGHT(true, false, true, true);
+    if (fw != 32) return d.narrow_turns ? SAGNN_EIGHT(true, true, true, false) : SAGNN_EIGHT(true, false, true, false);
+    if (d.narrow_sums == 1) return d.narrow_turns ? SAGNN_EIGHT(false, true, true, false) : SAGNN_EIGHT(false, false, true, false);
+    return d.narrow_turns ? SAGNN_EIGHT(false, true, false, false) : SAGNN_EIGHT(false, false, false, false);
 #undef SAGNN_EIGHT
   }
   if (d.groups == 2) {   // half a wavefront per row
