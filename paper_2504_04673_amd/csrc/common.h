@@ -261,7 +261,7 @@ struct SpmmHostDesc {
                             // may hold fewer than 16 rows, which the epilogue multiplies all the same: 60 k vertices of 20 in
                             // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
   float reuse;              // uses of a row of B among the rows of A that an XCD holds (see sweep_prepare)
-  bool narrow_turns;        // wavefronts of eight lane groups take turns (see there)
+  bool turns, layer_turns;  // wavefronts take turns in the product, in the layer with lane groups (see there)
   int32_t narrow_sums;      // sums of eight lane groups: 0 plain, 1 two, 2 two and folded (see there)
   float mean_steps;         // average stream steps per wavefront (the end of the pacing schedule)
   float max_steps;          // steps of the longest stream
@@ -314,7 +314,7 @@ int flat_fixup(const FlatArgs& a, const int2* list, int64_t list_cap, int64_t n_
 struct SweepPlanResult {
   bool use_sweep;
   float reuse;       // see SpmmHostDesc
-  bool narrow_turns; // see there
+  bool turns, layer_turns;
   int32_t narrow_sums;
   float mean_steps;  // average stream steps per wavefront
   float max_steps;   // steps of the longest stream

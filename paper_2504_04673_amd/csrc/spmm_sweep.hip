@@ -671,7 +671,8 @@ struct SegmentSum {
 struct TurnTaking {
   int32_t next, stride;
   uint32_t level;
-  __device__ __forceinline__ TurnTaking(int32_t steps, int32_t longest) : next(0), level(0) {
+  // (longest 0: no turns)
+  __device__ __forceinline__ TurnTaking(int32_t steps, int32_t longest) : next(longest > 0 ? 0 : -1), level(0) {
     stride = (steps >> 4) & ~7;
     stride = stride > longest ? longest : (stride < 8 ? 8 : stride);
   }
@@ -1810,19 +1811,43 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   out->reuse = (float)reuse;
   // Sums of eight groups by the entries a segment has on average, as many of a row's as lie in one of the slabs that it
   // chooses from.  At 32 columns plain of short ones, two from 6 on, between the kernel's widths, which nonzero splitting added
-  // as a tree, two at least; folded from 36 on, without locality with the two.  Error against 64 bits plain, with two sums, folded, e-8: random columns,
-  // 300 k of 20 (1.3 a segment) 7.17, 7.34, 7.34, of 60 (3.8) 8.69, 8.81, 8.81, 200 k of 60 (7.5) 7.84, 7.57, 7.57;
-  // communities, 500 k of 16 7.02, 6.02, 6.02, of 32 10.2, 6.92, 6.91, of 42 11.7, 7.42, 7.16, 150 k of 110 18.5, 9.47, 8.42;
-  // rows within 3000 of the diagonal, of 30 9.72, 6.43, 6.52.  Folding takes random columns, 200 k of 120, 150 k of 200
+  // as a tree, two at least; folded from 36 on, without locality with the two.  Error against 64 bits plain, with two
+  // sums, folded, e-8: random columns, 300 k of 20 (1.3 a segment) 7.17, 7.34, 7.34, of 60 (3.8) 8.69, 8.81, 8.81, 200 k of 60
+  // (7.5) 7.84, 7.57, 7.57; communities, 500 k of 16 7.02, 6.02, 6.02, of 32 10.2, 6.92, 6.91, of 42 11.7, 7.42, 7.16, 150 k of
+  // 110 18.5, 9.47, 8.42; rows within 3000 of the diagonal, of 30 9.72, 6.43, 6.52.  Folding takes random columns, 200 k of 120, 150 k of 200
   // from 248, 291 to 241, 285 us, power-law matrices, as near every way, 500 k of 30, take 199 plain, 207, 212.
   const double segment = (double)nnz / (double)m / std::max(1.0, (double)S * span / (double)k);
   out->narrow_sums = segment >= 36.0 || (segment >= 6.0 && !local) ? 2 : (segment >= 6.0 ? 1 : 0);
-  // Turns with eight groups, f = 20, 32, us without and with: with hubs where resident rows use a row of B often, 300 k vertices
-  // of 200 566, 535 and 539, 510, 233 k of 489 961, 930 and 934, 904; but 300 k of 30 (1.6 uses) 140, 122 and 143, 125, 1.5 M of
-  // 51 930, 824 and 976, 874, 2 M of 51 1266, 1100 and 1301, 1139 (1 M and 2.45 M of 51 596 and 1568, 1356 with, 1 % more
-  // without); else but where rows of a community are short, 500 k of 45, random, 441, 408 and 425, 390, 100 k of 24 40, 37 and
-  // 35, 35, 2 M of 35 in communities 1136, 1029 and 1121, 992, but 1 M of 18 318, 275 and 330, 281, of 26 390, 339 and 396, 345.
-  out->narrow_turns = hubs ? reuse >= 4.0 : !local || nnz >= 30 * m;
+  // Turns (TurnTaking; column groups have them always, one row per load up to 128 columns by the size of B, sweep_launch).  us
+  // without and with:
+  // Where the order of the rows carries locality not if the columns that neighbouring rows choose from are few megabytes of
+  // B, which the L2s hold for all that are near each other in their streams: 16 communities, two groups, 200 k of 50 (6 MB at
+  // 128 columns) f = 72, 96, 128 336, 370, 501 and 354, 388, 513, 300 k of 24 264, 314, 401 and 275, 326, 425, 500 k of 42 f =
+  // 72, 100 784, 1010 and 807, 992, 700 k of 60 f = 100, 128 (25 MB) 2244, 2428 and 2031, 2377; four, 500 k of 42 f = 36, 48, 64
+  // (9 MB) 400, 462, 548 and 438, 491, 561, 1 M of 40 f = 48 (13 MB) 1003, 991; eight, f = 32, 500 k of 42 249, 268, 700 k of 60
+  // 503, 513, but 2 M of 35 (18 MB) 1066, 1040 and 150 k of 110 136, 123; four floats a lane only short rows, f = 160, 200,
+  // 300 k of 24 516, 714 and 531, 738, 500 k of 16 (22 MB) 713, 960 and 748, 997, of 42 1515, 2036 and 1453, 1874, 1 M of 24
+  // (45 MB) 1890, 2661 and 1797, 2506, 700 k of 20 (31, 39 MB) 1112, 1557 and 1071, 1436.  Rows within 3000 of the diagonal, 300 k of 60, f = 32, 48, 96 184, 281, 577 and 205, 305,
+  // 621, 500 k of 30, f = 200 1343 and 1257; within 20000, 500 k of 24, f = 128, 200 582, 1008 and 645, 1172.
+  // In the layer with two groups not with locality at any size: 128 to 128 in fp32 200 k of 50 507, 558, 500 k of 42 1126,
+  // 1185, 700 k of 20 940, 1010, of 60 (25 MB) 2392, 2386.
+  // With hubs and eight groups where resident rows use a row of B often, f = 20, 32: 300 k of 200 566, 535 and 539, 510, 233 k
+  // of 489 961, 930 and 934, 904, but 300 k of 30 (1.6 uses) 140, 122 and 143, 125, 1.5 M of 51 930, 824 and 976, 874; with four
+  // floats a lane not at 160 and 192 columns, whose rows are whole lines, if they do and rows are not long: 60 k of 200 366, 588
+  // and 396, 609, 100 k of 100 316, 494 and 338, 509, 233 k of 100 790, 1100 and 796, 1132, but of 489 f = 192 5032, 4801, 1 M of
+  // 50 (0.8 uses) 2195, 2674 and 2116, 2664; f = 200 in all of them 2 to 20 % faster with.
+  const double near = span * (double)f * 4.0;
+  bool turns = true;
+  if (local && !col_groups) {
+    if (R > 1) turns = near >= 12e6 || (R == 8 && nnz >= 80 * m);
+    else if (f > 128) turns = near >= 28e6 || nnz >= 28 * m;
+  } else if (hubs && R == 8) {
+    turns = reuse >= 4.0;
+  } else if (hubs && R == 1 && f > 128 && f <= 192 && (f & 31) == 0) {
+    turns = reuse < 2.0 || nnz >= 300 * m;
+  }
+  out->turns = turns;
+  out->layer_turns = R == 2 ? !local : turns;
   out->mean_steps = rec.scan.mean_steps;
   out->max_steps = rec.scan.max_steps;
   out->use_sweep = true;
@@ -1886,7 +1911,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   const unsigned blocks = (unsigned)ceil_div(d.n_waves, 4);
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
   sd.fw = fw;
-  sd.turn = turn_steps(kmax, fw);
+  sd.turn = (fuse != 0 ? d.layer_turns : d.turns) ? turn_steps(kmax, fw) : 0;
   size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
   // (the layer: the targets behind the rows, and no more than five workgroups a CU, which 64 columns would allow: a sixth
   // only drives the others' rows out of the L2, 233 k vertices of 489, 64 to 64 columns 1480 us, with five 1410)
@@ -1973,11 +1998,11 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
 #define SAGNN_EIGHT(ODD_, TURN_, TWO_, FOLD_)                                      \
   (buf ? go_perm(spmm_sweep_perm_kernel<8, true, ODD_, TURN_, TWO_, FOLD_>) \
        : go_perm(spmm_sweep_perm_kernel<8, false, ODD_, TURN_, TWO_, FOLD_>))
-    if (d.narrow_sums == 2 && fw == 32) return d.narrow_turns ? SAGNN_EIGHT(false, true, true, true) : SAGNN_EIGHT(false, false, true, true);
-    if (d.narrow_sums == 2) return d.narrow_turns ? SAGNN_EIGHT(true, true, true, true) : SAGNN_EIGHT(true, false, true, true);
-    if (fw != 32) return d.narrow_turns ? SAGNN_EIGHT(true, true, true, false) : SAGNN_EIGHT(true, false, true, false);
-    if (d.narrow_sums == 1) return d.narrow_turns ? SAGNN_EIGHT(false, true, true, false) : SAGNN_EIGHT(false, false, true, false);
-    return d.narrow_turns ? SAGNN_EIGHT(false, true, false, false) : SAGNN_EIGHT(false, false, false, false);
+    if (d.narrow_sums == 2 && fw == 32) return d.turns ? SAGNN_EIGHT(false, true, true, true) : SAGNN_EIGHT(false, false, true, true);
+    if (d.narrow_sums == 2) return d.turns ? SAGNN_EIGHT(true, true, true, true) : SAGNN_EIGHT(true, false, true, true);
+    if (fw != 32) return d.turns ? SAGNN_EIGHT(true, true, true, false) : SAGNN_EIGHT(true, false, true, false);
+    if (d.narrow_sums == 1) return d.turns ? SAGNN_EIGHT(false, true, true, false) : SAGNN_EIGHT(false, false, true, false);
+    return d.turns ? SAGNN_EIGHT(false, true, false, false) : SAGNN_EIGHT(false, false, false, false);
 #undef SAGNN_EIGHT
   }
   if (d.groups == 2) {   // half a wavefront per row

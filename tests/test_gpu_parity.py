@@ -735,6 +735,33 @@ def test_spmm_eight_groups_sum_by_the_length_of_segments(n, deg, parts, f):
         assert float((C[rows].double() - ref).norm()) <= 1.005 * float((total.double() - ref).norm())
 
 
+@pytest.mark.parametrize("f", [20, 32, 36, 48, 64, 72, 96, 128, 160, 192, 200])
+@pytest.mark.parametrize("n,deg,parts", [(120_000, 40, 16), (640_000, 21, 16), (40_000, 90, 1)])
+def test_spmm_with_and_without_turns(n, deg, parts, f):
+    """Communities of few and of many columns, and random ones: whether the wavefronts take turns changes nothing in the
+    product, nor in the layer where it ends the sweep."""
+    gen = torch.Generator(device="cuda").manual_seed(n + f)
+    part = n // parts
+    home = (torch.arange(n, device="cuda") // part * part)[:, None]
+    cols = torch.sort(home + torch.randint(part, (n, deg), device="cuda", generator=gen), dim=1)[0]
+    rp = torch.arange(0, n * deg + 1, deg, dtype=torch.int32, device="cuda")
+    ci = cols.to(torch.int32).reshape(-1)
+    v, B = torch.randn(n * deg, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 1
+    C = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+    rows = torch.arange(0, n, 29, device="cuda")
+    t = v.reshape(n, deg)[rows].double()[:, :, None] * B[cols[rows]].double()
+    T, unit = t.sum(1), (deg + 2) * 2.0 ** -24 * t.abs().sum(1)
+    assert bool(((C[rows].double() - T).abs() <= unit).all())
+    if f in (64, 128) and sagnn.gcn_layer_fwd_form(ws, f, 64) == 2:
+        W = torch.randn(f, 64, device="cuda", generator=gen) / f ** 0.5
+        Wd = W.double()
+        _, Z, _ = sagnn.gcn_layer_fwd(rp, ci, v, B, W, ws=ws, want_t=False)
+        bound = unit @ Wd.abs() + (f + 4) * 2.0 ** -24 * (T.abs() @ Wd.abs())
+        assert bool(((Z[rows].double() - T @ Wd).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("n,deg,parts,f,mode", [(10_000, 160, 1, 16, 1), (10_000, 228, 1, 16, 0), (10_000, 228, 1, 32, 0), (10_000, 228, 1, 48, 0), (10_000, 228, 1, 64, 0),
                                                 (10_000, 228, 1, 256, 1), (5_000, 220, 4, 128, 0), (14_400, 180, 16, 64, 0), (14_400, 180, 16, 256, 1)])
 def test_spmm_few_long_rows_without_hubs(n, deg, parts, f, mode):
