@@ -1827,8 +1827,9 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // (9 MB) 400, 462, 548 and 438, 491, 561, 1 M of 40 f = 48 (13 MB) 1003, 991; eight, f = 32, 500 k of 42 249, 268, 700 k of 60
   // 503, 513, but 2 M of 35 (18 MB) 1066, 1040 and 150 k of 110 136, 123; four floats a lane only short rows, f = 160, 200,
   // 300 k of 24 516, 714 and 531, 738, 500 k of 16 (22 MB) 713, 960 and 748, 997, of 42 1515, 2036 and 1453, 1874, 1 M of 24
-  // (45 MB) 1890, 2661 and 1797, 2506, 700 k of 20 (31, 39 MB) 1112, 1557 and 1071, 1436.  Rows within 3000 of the diagonal, 300 k of 60, f = 32, 48, 96 184, 281, 577 and 205, 305,
-  // 621, 500 k of 30, f = 200 1343 and 1257; within 20000, 500 k of 24, f = 128, 200 582, 1008 and 645, 1172.
+  // (45 MB) 1890, 2661 and 1797, 2506, 700 k of 20 (31, 39 MB) 1112, 1557 and 1071, 1436.  Rows within 3000 of the diagonal,
+  // 300 k of 60, f = 32, 48, 96 184, 281, 577 and 205, 305, 621, 500 k of 30, f = 200 1343 and 1257; within 20000, 500 k of 24,
+  // f = 128, 160 582, 805 and 645, 908.
   // In the layer with two groups not with locality at any size: 128 to 128 in fp32 200 k of 50 507, 558, 500 k of 42 1126,
   // 1185, 700 k of 20 940, 1010, of 60 (25 MB) 2392, 2386.
   // With hubs and eight groups where resident rows use a row of B often, f = 20, 32: 300 k of 200 566, 535 and 539, 510, 233 k
@@ -2014,7 +2015,9 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     // in fp32 1.2 M of 51 2173, 2293, 1.6 M 3315, 3201, 2.45 M 4833, 4740.  Between the kernels' own widths, whose rows begin
     // inside lines, from the memory-side cache's size on: 233 k of 489, f = 100 1975, 2286, 600 k of 60 (240 MB) 970, 1005, 1 M
     // of 51, f = 72 (288 MB) 1345, 1205, 2 M of 51, f = 72, 100, 112 3604, 3942, 3934 and 2637, 3739, 3739, 2.45 M of 40, f = 96
-    // 3261, 2686.
+    // 3261, 2686; and where rows are whole lines (96), in smaller and shorter ones, with and without: 100 k of 60 152, 172, 200 k
+    // of 30, 120 164, 436 and 171, 452, 300 k of 70 408, 425, 400 k of 30 (154 MB) 301, 322, but of 70, 120 664, 1084 and 576,
+    // 884, 233 k of 200 868, 766, 500 k of 30, 60 (192 MB) 442, 778 and 397, 647.
     const int64_t b = operand_bytes(kmax, fw);
     if (fw == 128) {
       if (b <= (600ll << 20)) return buf ? go_group(group_kernel_of<4, 2, true, true>(fuse)) : go_group(group_kernel_of<4, 2, false, true>(fuse));
@@ -2027,7 +2030,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     if (d.apart)
       return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true, true, true>)
                  : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true, true, true>);
-    if (b <= (256ll << 20))
+    if ((fw & 31) == 0 ? b <= (160ll << 20) && d.nnz <= 25000000 : b <= (256ll << 20))
       return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true>) : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true>);
     return buf ? go_group(&spmm_sweep_group_kernel<4, 2, 8, true, 0, true, false>)
                : go_group(&spmm_sweep_group_kernel<4, 2, 8, false, 0, true, false>);

@@ -607,7 +607,7 @@ def test_spmm_column_groups_keep_segments_short(n, deg, slabs):
     assert err <= 1.01 * error(sagnn.SpmmOptions(slab_kb=4096))[1]
 
 
-@pytest.mark.parametrize("f,k,ld", [(128, 1_228_800, 128), (128, 1_228_801, 128), (128, 1_228_801, 1024), (100, 671_088, 100), (100, 671_089, 100),
+@pytest.mark.parametrize("f,k,ld", [(96, 436_906, 96), (96, 436_907, 96), (128, 1_228_800, 128), (128, 1_228_801, 128), (128, 1_228_801, 1024), (100, 671_088, 100), (100, 671_089, 100),
                                     (100, 671_089, 1700)])
 def test_spmm_two_rows_per_load_on_both_sides_of_words_ahead(f, k, ld):
     """Two lane groups with B on either side of the sizes up to which the stream's words are requested ahead, also with rows
