@@ -1915,8 +1915,10 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   sd.turn = (fuse != 0 ? d.layer_turns : d.turns) ? turn_steps(kmax, fw) : 0;
   size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
   // (the layer: the targets behind the rows, and no more than five workgroups a CU, which 64 columns would allow: a sixth
-  // only drives the others' rows out of the L2, 233 k vertices of 489, 64 to 64 columns 1480 us, with five 1410)
-  if (fuse != 0) lds = std::max(lds + 4 * kSweepSlots * sizeof(int32_t), (size_t)28 << 10);
+  // only drives the others' rows out of the L2, 233 k vertices of 489, 64 to 64 columns 1480 us, with five 1410, 300 k of 60 in
+  // communities 460, 447; but in fp32, whose dense part is longest, not where rows are short, 500 k of 18 in communities 319,
+  // 334, power-law of 30 314, 337)
+  if (fuse != 0) lds = std::max(lds + 4 * kSweepSlots * sizeof(int32_t), (size_t)(fuse == 1 && d.nnz < 40 * d.m ? 0 : 28) << 10);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
