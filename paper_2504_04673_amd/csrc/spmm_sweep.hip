@@ -808,7 +808,7 @@ typedef __bf16 sweep_bf16x8 __attribute__((ext_vector_type(8)));
 // Dense transform of a sweep workgroup's 64 finished rows of T (LDS, [4 waves][16 slots][KROW]):
 // wavefront (rt, half) multiplies row tile rt by the 32-column tiles half, half + 2, .. of W and
 // stores the rows of Z / sigma(Z) at the rows the pieces belong to (slots that hold a piece of a
-// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup (see sweep_targets_far).  Called
+// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup (see Targets).  Called
 // by all four wavefronts after a workgroup barrier.
 // MODE: the matrix-core operands, numbered like SAGNN_GEMM_*: 0 fp32, 1 rounded to bfloat16, 2 fp32
 // as the exact sum of three bfloat16 terms with the six products down to 2^-16 of the leading one.
@@ -824,13 +824,15 @@ __device__ __forceinline__ void sweep_split3(float x, __bf16& t1, __bf16& t2, __
 // the matrix instructions, they are one more trip in every pass over k; looked up before the loop over k they take sixteen
 // registers, which decide how many workgroups walk at the same time at 64 columns.  us behind, before and from the LDS:
 // communities, 700 k vertices of 40, 256 to 256 bfloat16 3290, 3200, 3110; a rank's 306 k rows of 11, 64 to 64 180, 220, 174.
-// In fp32 at 256 the trip does not show beside 14 us of matrix instructions, and what comes sooner from the LDS is worse for
-// random columns: 800 k vertices of 15 2738 from memory, 3182 from the LDS, 1 M of 16, 18, 22 3663, 3995, 4559 and 4275,
-// 4495, 4958, 1.5 M of 20 6569, 7208, 2 M of 18 8175, 9361 (in communities, 700 k of 40, 4069 and 4086; bfloat16 2 M of 18
-// 7262 and 7058).
-constexpr bool sweep_targets_far(int krow, int mode) { return mode == 0 && krow == 256; }
+// In fp32 at 256 the trip does not show beside 14 us of matrix instructions, and what comes sooner is worse for random columns
+// whose rows of B are hardly used twice: from memory behind, before (TARGETS_BEFORE) and from the LDS 800 k vertices of 15
+// 2738, 3166, 3182, 1 M of 16, 18, 22 from the LDS 3663, 3995, 4559 -> 4275, 4495, 4958, 300 k of 20 (1.1 uses) 1237, 1263,
+// 1272; but 200 k of 40 (3.3) 1291, 1264, 1280, 1 M rows of 20 by 20 k columns 2914, 2713, 2750, in communities 500 k of 42
+// 2644, 2547, 2536, 700 k of 40 3759, 3714, 3677, though 500 k of 18 1708, 1781, 1.5 M of 42 8500, 8848 (bfloat16 2 M of 18
+// random 7262 behind, 7058 from the LDS).
+enum Targets { TARGETS_LDS, TARGETS_BEHIND, TARGETS_BEFORE };
 
-template <int KROW, int MODE, int QT>
+template <int KROW, int MODE, int QT, Targets FROM = TARGETS_LDS>
 __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ lds_acc,
                                                      const int32_t* __restrict__ targets,
                                                      const SweepFusedArgs& fa, int wave, int lane) {
@@ -838,6 +840,11 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
   const int r = lane & 31, h = lane >> 5;
   const int rt = wave & 1;
   const int nct = (fa.f_out + 31) >> 5;
+  [[maybe_unused]] int4 far[4];
+  if constexpr (FROM == TARGETS_BEFORE) {
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) far[v4] = *reinterpret_cast<const int4*>(targets + rt * 32 + h * 4 + v4 * 8);
+  }
   const float* __restrict__ trow = lds_acc + (size_t)(rt * 32 + r) * kRow;
   // this wavefront's column tiles: ct_first, ct_first + 2, ..  (at most 4 of the at most 8).  k runs
   // in the outer loop so that a row piece of T is read from LDS once for the tiles of a pass, and the
@@ -966,8 +973,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
     // all at once, a load between the stores would wait for them.)
     uint32_t t0 = rt * 32 + h * 4;
     asm volatile("" : "+v"(t0));
-    int4 far[4];
-    if constexpr (sweep_targets_far(KROW, MODE)) {
+    if constexpr (FROM == TARGETS_BEHIND) {
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) far[v4] = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
     }
@@ -978,7 +984,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
         int4 t4;
-        if constexpr (sweep_targets_far(KROW, MODE)) t4 = far[v4];
+        if constexpr (FROM != TARGETS_LDS) t4 = far[v4];
         else t4 = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
         const int32_t tg[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
@@ -993,7 +999,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
   }
 }
 
-template <int FPL, int U, bool BUF, int MODE, bool TURN>
+template <int FPL, int U, bool BUF, int MODE, bool TURN, Targets FROM = TARGETS_LDS>
 __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1041,8 +1047,8 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
 
   // tiles per pass: 4 at f = 256 (the LDS already limits a CU to two workgroups; 2 with three operand
   // terms per tile in registers), 1 below
-  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1)>(
-      lds_acc, sweep_targets_far(kRow, MODE) ? piece_target + ((int64_t)d.block0 + blockIdx.x) * 4 * kSweepSlots : targets, fa, wave, (int)lane);
+  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1), FROM>(
+      lds_acc, FROM != TARGETS_LDS ? piece_target + ((int64_t)d.block0 + blockIdx.x) * 4 * kSweepSlots : targets, fa, wave, (int)lane);
 }
 
 // W (f_in x f_out, row-major fp32) -> [f_in / 8][NB] vectors of 8 bfloat16 (k fastest), NB = f_out
@@ -2133,6 +2139,12 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   (mode == 2 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 2, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 2, TURN_>))   \
    : mode == 1 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 1, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 1, TURN_>)) \
                : (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 0, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 0, TURN_>)))
+  if (f_in == 256 && mode == 0) {   // (see Targets)
+    const int64_t b = operand_bytes(kmax, f_in);
+    if (d.reuse >= 2.f && (b <= (256ll << 20) || (b <= (768ll << 20) && d.nnz >= 36 * d.m)))
+      return buf ? go(spmm_sweep_fused_kernel<4, 8, true, 0, false, TARGETS_BEFORE>) : go(spmm_sweep_fused_kernel<4, 8, false, 0, false, TARGETS_BEFORE>);
+    return buf ? go(spmm_sweep_fused_kernel<4, 8, true, 0, false, TARGETS_BEHIND>) : go(spmm_sweep_fused_kernel<4, 8, false, 0, false, TARGETS_BEHIND>);
+  }
   if (f_in == 256) return SAGNN_SWF(4, false);   // (only two wavefronts share a SIMD)
   if (f_in == 128) return turns ? SAGNN_SWF(2, true) : SAGNN_SWF(2, false);
   return SAGNN_SWF(1, true);
