@@ -350,9 +350,9 @@ int sweep_plan_window_entries(char* ws, const SpmmWsLayout& L, int64_t P, int64_
                               hipStream_t s, std::vector<int64_t>* entries);
 // sort the pieces and deal them to the streams: fills piece_info / piece_target; synchronises
 // (it looks at a flag every few batches to see whether pieces are left); flags[2] of the carry
-// area stays 1 if pieces were left over
+// area stays 1 if pieces were left over (whole: all of a window's streams get a piece in a batch, else half of them)
 int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, const int32_t* h_win_unit0,
-                    int32_t nwin, int64_t n_waves4, int32_t R, int32_t SL, int32_t piece_max, bool snake, hipStream_t s);
+                    int32_t nwin, int64_t n_waves4, int32_t R, int32_t SL, int32_t piece_max, bool snake, bool whole, hipStream_t s);
 // the short rows' pieces (records P_long .. P_long + n_short), longest first, 16 consecutive ones
 // per wavefront from wavefront first_wave on (n_waves4 of sweep_plan_deal must cover them); no
 // synchronisation

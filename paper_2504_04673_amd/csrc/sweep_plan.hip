@@ -398,6 +398,7 @@ __global__ __launch_bounds__(kT) void plan_zero_units_kernel(int32_t* __restrict
 struct DealDims {
   int64_t P, window, U;    // pieces, pieces per window, streams (units) in all
   int32_t nwin, R, SL;     // windows, lane groups per wavefront, slots per unit
+  int32_t share;           // a batch deals to one in `share` of a window's streams
   int32_t load_bits, win_bits;   // of a stream's sort key: an open stream's length, its window; one more bit: not open
 };
 
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(kT) void deal_first_kernel(DealDims d, const uint32
 }
 
 // position i of the sorted streams: the rank-th shortest open stream of its window takes the
-// rank-th largest piece the window has left, for rank < B = half the window's streams.  The last of them in a window
+// rank-th largest piece the window has left, for rank < B = half or all of the window's streams.  The last of them in a window
 // says how many have been dealt (one atomic per stream instead was a queue of U additions to one word:
 // 148 us a batch of 33 k streams, now 4).
 __global__ __launch_bounds__(kT) void deal_assign_kernel(DealDims d, const int32_t* __restrict__ win_unit0,
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(kT) void deal_assign_kernel(DealDims d, const int32
   if (w >= d.nwin) return;      // (not open)
   const int64_t rank = i - (d.nwin > 1 ? (int64_t)first[w] : 0);
   const int64_t units_w = (int64_t)win_unit0[w + 1] - win_unit0[w];
-  const int64_t B = units_w / 2 > 0 ? units_w / 2 : 1;
+  const int64_t B = units_w / d.share > 0 ? units_w / d.share : 1;
   const int64_t left = window_pieces(d, w) - done[w];
   const int64_t most = B < left ? B : left;
   if (rank >= most) return;
@@ -703,7 +704,7 @@ int sweep_plan_deal_short(char* ws, const SpmmWsLayout& L, int64_t P_long, int64
 }
 
 int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, const int32_t* h_win_unit0,
-                    int32_t nwin, int64_t n_waves4, int32_t R, int32_t SL, int32_t piece_max, bool snake, hipStream_t s) {
+                    int32_t nwin, int64_t n_waves4, int32_t R, int32_t SL, int32_t piece_max, bool snake, bool whole, hipStream_t s) {
   const PlanSmall sm = carve_small(ws, L);
   const PlanScratch sc = carve_plan(ws + L.code, L.max_pieces, L.max_waves * kSweepSlots);
   int32_t* d_flag = reinterpret_cast<int32_t*>(ws + L.carry);
@@ -733,7 +734,8 @@ int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, 
   // (an open stream holds at most SL - 1 pieces; a window of the key that is not open sorts behind all of them)
   int load_bits = 0;
   while (((int64_t)(SL - 1) * piece_max) >> load_bits) ++load_bits;
-  DealDims d{P, window, U, nwin, R, SL, load_bits, wbits};
+  const int32_t share = whole ? 1 : 2;
+  DealDims d{P, window, U, nwin, R, SL, share, load_bits, wbits};
   if (snake) {
     hipLaunchKernelGGL(deal_snake_kernel, grid_for(P), dim3(kT), 0, s, d, sm.win_unit0, piece_order, sc.pa, info,
                        target, d_flag + 2);
@@ -751,7 +753,7 @@ int sweep_plan_deal(char* ws, const SpmmWsLayout& L, int64_t P, int64_t window, 
   for (int32_t w = 0; w < nwin; ++w) {
     const int64_t a = (int64_t)w * window, n_w = std::min(P, a + window) - a;
     const int64_t units_w = (int64_t)h_win_unit0[w + 1] - h_win_unit0[w];
-    per_unit = std::max(per_unit, ceil_div(n_w, std::max<int64_t>(units_w / 2, 1)));
+    per_unit = std::max(per_unit, ceil_div(n_w, std::max<int64_t>(units_w / share, 1)));
   }
   int next_check = (int)std::min<int64_t>(per_unit + 1, max_batches);
   int32_t *done = sm.done, *done_next = sm.done_next;
