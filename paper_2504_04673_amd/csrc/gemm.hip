@@ -569,16 +569,28 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
   // on a few CUs there: staging W, then the matrix instructions of all its columns, and the slabs one after the other.
   // us before and so, fp32 4096 x 256 x 256 86, 13; 128 x 128 18, 10; 30 k 256 x 256 94, 53; 128 x 128 23, 21; 45 k
   // 256 x 256 98, 77; 200 x 100 48, 44; rounded 10 k 256 x 256 26, 17; three terms 10 k 256 x 256 65, 25.  The lines lie
-  // where the wide form is as fast: fp32 70 k x 100 x 64 (2188 row tiles) 30 and 34, 100 k x 200 x 100 (3125) 97 and 104;
-  // rounded operands, whose matrix instructions cost little and whose workgroups have eight wavefronts, 20 k x 128 x 128
-  // 15, with 1024 wavefronts 13, with 2048 17; three terms 45 k x 256 x 40 20 and 24, but where the wide form is several
-  // launches 30 k x 256 x 256 73 and 53.  An output that overlaps X is written tile by tile behind the reads as before.
+  // where the wide form is as fast: rounded operands, whose matrix instructions cost little and whose workgroups have eight
+  // wavefronts, 20 k x 128 x 128 15, with 1024 wavefronts 13, with 2048 17; three terms 45 k x 256 x 40 20 and 24, but where
+  // the wide form is several launches 30 k x 256 x 256 73 and 53.  And from 1536 row tiles to 2048 the wide form is one round
+  // of wavefronts that is nearly full, which narrow slabs cut in two: wide and narrow fp32 47 k rows (1469 row tiles) 100 x 64,
+  // 256 x 40, 96 x 96, 200 x 100 16, 24, 22, 41 and 15, 20, 17, 37, 52 k (1625) 17, 25, 22, 42 and 21, 26, 25, 50; three terms
+  // 48 x 200, 128 x 256 47 k 25, 38 and 20, 32, 52 k 24, 39 and 27, 41, and beyond k = 128 192 x 132 37 k
+  // (1157) 34, 31, 42 k (1313) 35, 38.  In more than a round 128 columns of fp32 gain while its end is short: 67 k (2094)
+  // 200 x 100 75, 61, 97 k 76, 71; 128 x 128, whose chains are short, 67 k 37, 34, 75 k (2344) 36, 36, 85 k 37, 39 and 52 k
+  // 28, 26.  An output that overlaps X is written tile by tile behind the reads as before.
   const int64_t row_tiles = (m + 31) / 32;
   const int64_t enough = prec == SAGNN_GEMM_BF16 ? 1024 : (prec == SAGNN_GEMM_FP32 ? (tiles >= 4 ? 3072 : 2048) : (tiles > widest ? 4096 : 1024));
+  int64_t most = INT64_MAX;   // row tiles up to which the slabs are narrow
+  if (prec == SAGNN_GEMM_FP32) {
+    if (tiles < 4 || (kdim > 128 && row_tiles <= 2048)) most = 1536;
+    else if (kdim <= 128) most = 2560;
+  } else if (prec == SAGNN_GEMM_FP32_BF16X3) {
+    most = kdim > 128 ? 1200 : 1536;
+  }
   auto apart = [&](const float* out, int64_t ld) {
     return !out || out + (m - 1) * ld + nout <= X || X + (m - 1) * ldx + kdim <= out;
   };
-  if (row_tiles * ((tiles + nt - 1) / nt) < enough && apart(Z, ldz) && apart(A, lda)) {
+  if (row_tiles <= most && row_tiles * ((tiles + nt - 1) / nt) < enough && apart(Z, ldz) && apart(A, lda)) {
     while (nt > 1 && row_tiles * ((tiles + nt - 1) / nt) < enough) nt /= 2;
     g.slabs = (tiles + nt - 1) / nt;
     return run(nt);

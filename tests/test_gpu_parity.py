@@ -1501,7 +1501,8 @@ def test_dense_gemm_at_the_edges_of_its_groups_and_slabs(m, k, n, prec):
 
 
 @pytest.mark.parametrize("prec", [sagnn.GEMM_FP32, sagnn.GEMM_BF16, sagnn.GEMM_FP32_BF16X3])
-@pytest.mark.parametrize("m,k,n", [(65_537, 36, 64), (98_305, 64, 132), (98_306, 100, 256), (49_130, 128, 256), (131_073, 132, 96),
+@pytest.mark.parametrize("m,k,n", [(49_152, 100, 64), (49_153, 132, 40), (38_400, 132, 132), (38_401, 132, 132), (65_537, 132, 128), (81_921, 128, 128),
+                                   (65_537, 36, 64), (98_305, 64, 132), (98_306, 100, 256), (49_130, 128, 256), (131_073, 132, 96),
                                    (131_041, 256, 256), (16_380, 160, 200), (32_770, 40, 40), (200_001, 28, 20),
                                    (40_000, 64, 64)])
 def test_dense_gemm_with_wide_and_narrow_slabs(m, k, n, prec):
