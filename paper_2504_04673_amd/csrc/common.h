@@ -333,11 +333,12 @@ struct SweepRowTotals {
   int32_t min_long;
   int32_t locality;   // permille: how far the columns of neighbouring rows differ from those of all rows
   int32_t span;       // permille of the columns that neighbouring rows choose from
+  int32_t slide;      // permille: how often they change a little from one run of rows to the next
   bool has_empty, bad;
 };
 bool sweep_plan_fits(const SpmmWsLayout& L);
 // what the rows look like: the threshold of long rows, locality, span (d_colidx may be null: no locality then).  With `out`
-// the host waits for it: bad, min_long, locality, span, and short_entries where the threshold is the lowest (0 otherwise)
+// the host waits for it: bad, min_long, locality, span, slide, and short_entries where the threshold is the lowest (0 otherwise)
 int sweep_plan_sample(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int64_t k, int64_t nnz, int32_t opt_min_long,
                       char* ws, const SpmmWsLayout& L, hipStream_t s, SweepRowTotals* out);
 // behind sweep_plan_sample: classify rows, build the short-row CSR, the list of split rows and the piece records; one

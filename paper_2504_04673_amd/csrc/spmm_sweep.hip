@@ -1543,7 +1543,9 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // inference, whose dense part needs the whole width in one launch, at f = 128 1628 and 1831) or rows are short (of 125 k,
   // 16 a row, f = 64, 256 1129, 4835 and 1180, 4696; 24 a row 1557, 6355 and 1338, 5005), where there are too many for a
   // second use (a rank's rows; random columns, 500 k of 18, f = 128 661 and 653, 1 M of 30 in inference 2278 and 2392), and
-  // not with hubs, whose rows hit in any case (233 k vertices of 489: 5627, 7060).
+  // not with hubs, whose rows hit in any case (233 k vertices of 489: 5627, 7060).  Nor where the columns go along with the
+  // rows: resident rows then begin in different slabs, and the more of them there are the more slabs (1 M rows of 40 within
+  // 50 k of the diagonal, f = 64, 128, 192, 256 973, 2417, 3276, 5094 and 1304, 2634, 4014, 5084).
   const bool local = tot.locality >= kLocalPermille;
   const double span = (double)k * tot.span / 1000.0;
   // how often the 16384 rows of A that an XCD holds at 64 columns a launch want a row of the columns they choose from
@@ -1552,7 +1554,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const bool col_groups = f >= 64 && (f & 63) == 0 && opt.groups == 0 && opt.slab_width == 0 && opt.sync_slabs <= 0 &&
                           opt.barriers != 1 && opt.pace_ps_per_step <= 0 && span >= 40000.0 &&
                           reuse >= 0.6 && !hubs &&
-                          (!local || (nnz >= 18 * m && span >= 60000.0));
+                          (!local || (nnz >= 18 * m && span >= 60000.0 && tot.slide < 600));
   int64_t R = narrow_slabs ? 2 : (f > 128 ? 1 : (f > 64 ? 2 : (f > 32 ? 4 : (f > 16 ? 8 : 16))));
   if ((opt.groups == 1 && f > 32) || col_groups) R = 1;
   if (force != 1 && long_entries * 10 < nnz * 3) return SAGNN_OK;   // < 30 % of the entries

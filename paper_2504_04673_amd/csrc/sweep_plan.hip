@@ -42,6 +42,7 @@ enum Stat : int {
   ST_MULTI_PIECES,
   ST_LOCALITY,      // permille, see plan_locality_kernel
   ST_SPAN,          // permille of the columns, see there
+  ST_SLIDE,         // permille of the runs, see there
   ST_COUNT = 16
 };
 
@@ -107,13 +108,16 @@ __global__ void plan_rule_kernel(unsigned long long* __restrict__ stat, int64_t 
 // power law or not), 0.89 for sixteen communities in order with one partner in twenty elsewhere.
 // And how many columns do neighbouring rows choose from?  1 / sum of share^2 ranges, the mean over the runs: 64 of 64
 // where they choose from all, 4.5 with sixteen communities.
+// And do the columns go along with the rows?  The share of the runs that have 0.2 to 0.9 of their shares in common with the
+// next: none with communities, where it is nearly all or nearly nothing, all where entries lie within a distance of the
+// diagonal.
 // One workgroup, all samples of a row in flight: two chains of three dependent loads.
 constexpr int kLocRuns = 32, kLocBins = 64, kLocSamples = 32;
 __global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                                              int64_t m, int64_t nnz, int64_t k,
                                                              unsigned long long* __restrict__ stat) {
   __shared__ int hist[kLocRuns][kLocBins];
-  __shared__ float diff[kLocRuns], span[kLocRuns];
+  __shared__ float diff[kLocRuns], span[kLocRuns], slide[kLocRuns];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = threadIdx.x; i < kLocRuns * kLocBins; i += 1024) hist[i / kLocBins][i % kLocBins] = 0;
   __syncthreads();
@@ -148,20 +152,25 @@ __global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __re
     const int mine = hist[j][lane], n = sum(mine);
     const float t = sum(n > 0 ? fabsf((float)mine / (float)n - share) : 0.f);
     const float q = sum((float)mine * (float)mine);
+    const int next = j + 1 < kLocRuns ? hist[j + 1][lane] : 0, nn = sum(next);
+    const float common = sum(n > 0 && nn > 0 ? fminf((float)mine / (float)n, (float)next / (float)nn) : 0.f);
     if (lane == 0) {
+      slide[j] = common >= 0.2f && common <= 0.9f ? 1.f : 0.f;
       diff[j] = 0.5f * t;
       span[j] = n > 0 ? (float)n * (float)n / (q * kLocBins) : 0.f;
     }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    float t = 0.f, w = 0.f;
+    float t = 0.f, w = 0.f, v = 0.f;
     for (int j = 0; j < kLocRuns; ++j) {
       t += diff[j];
       w += span[j];
+      v += slide[j];
     }
     stat[ST_LOCALITY] = (unsigned long long)(t * (1000.f / kLocRuns));
     stat[ST_SPAN] = (unsigned long long)(w * (1000.f / kLocRuns));
+    stat[ST_SLIDE] = (unsigned long long)(v * (1000.f / (kLocRuns - 1)));
   }
 }
 
@@ -625,6 +634,7 @@ int sweep_plan_sample(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t 
     out->min_long = (int32_t)h[ST_MINLONG];
     out->locality = (int32_t)h[ST_LOCALITY];
     out->span = (int32_t)h[ST_SPAN];
+    out->slide = (int32_t)h[ST_SLIDE];
     out->short_entries = out->min_long == kSweepMinLong ? nnz - (int64_t)h[ST_FROM_MIN] : 0;
   }
   return SAGNN_OK;
@@ -658,6 +668,7 @@ int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int32_t piece_max, char*
   out->min_long = (int32_t)h[ST_MINLONG];
   out->locality = (int32_t)h[ST_LOCALITY];
   out->span = (int32_t)h[ST_SPAN];
+  out->slide = (int32_t)h[ST_SLIDE];
   out->pieces = (int64_t)h[ST_PIECES];
   out->short_rows = (int64_t)h[ST_SHORT_ROWS];
   out->short_entries = (int64_t)h[ST_SHORT_ENTRIES];

@@ -563,6 +563,25 @@ def test_spmm_sweep_in_groups_of_64_columns(f, n, deg, parts):
         assert torch.equal(h, torch.relu(z))
 
 
+@pytest.mark.parametrize("f", [64, 128, 192])
+@pytest.mark.parametrize("n,deg,half", [(700_000, 20, 35_000), (500_000, 24, 60_000)])
+def test_spmm_no_column_groups_along_the_diagonal(n, deg, half, f):
+    """Entries within a distance of the diagonal: resident rows do not choose from the same columns, as they do in
+    communities, and the product keeps the whole width in a launch where it can."""
+    gen = torch.Generator(device="cuda").manual_seed(n + f)
+    cols = torch.arange(n, device="cuda")[:, None] + torch.randint(-half, half + 1, (n, deg), device="cuda", generator=gen)
+    cols = torch.sort(cols.clamp_(0, n - 1), dim=1)[0]
+    rp = torch.arange(0, n * deg + 1, deg, dtype=torch.int32, device="cuda")
+    ci = cols.to(torch.int32).reshape(-1)
+    v, B = torch.randn(n * deg, device="cuda", generator=gen), torch.randn(n, f, device="cuda", generator=gen)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 1 and ws.launch_info()["columns"] == 0
+    C = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+    rows = torch.cat([torch.arange(0, n, 101, device="cuda"), torch.tensor([n - 1], device="cuda")])
+    t = v.reshape(n, deg)[rows].double()[:, :, None] * B[cols[rows]].double()
+    assert bool(((C[rows].double() - t.sum(1)).abs() <= (deg + 2) * 2.0 ** -24 * t.abs().sum(1)).all())
+
+
 @pytest.mark.parametrize("f,k", [(64, 4_505_600), (64, 4_505_601), (96, 3_003_733), (96, 3_003_734), (128, 2_252_800), (128, 2_252_801)])
 def test_spmm_one_row_per_load_on_both_sides_of_turns(f, k):
     """Rows of B that are hardly used twice, one row per load, with B just under and just over 1100 MB: whether the
