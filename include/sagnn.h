@@ -413,7 +413,8 @@ int dense_gemm_act(const float* d_X, int64_t ldx, const float* d_W, int64_t ldw,
  * short_rows of sagnn_spmm_options, the default where possible -- a few thousand), the sweep kernel
  * itself ends with the dense transform: a workgroup's 64 finished rows of A H are multiplied by
  * W on the matrix cores straight out of LDS, the few other rows go through a small kernel.
- * gcn_layer_fwd_form() tells which form a call would take.
+ * gcn_layer_fwd_form() tells which form a call would take.  It is the form for a caller without room for A H; where the
+ * product runs in groups of 64 columns (spmm_csr_launch_info) and f_in is 256, d_T and two kernels are faster.
  * gcn_layer_fwd_fused may also be called directly, with d_T non-NULL to get T as a by-product.
  */
 int gcn_layer_fwd(const int32_t* d_rowptr, const int32_t* d_colidx, const float* d_val,

@@ -1533,7 +1533,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // and the rows that are resident together want the same rows of B: an XCD holds 16384 rows of A then (256 workgroups of
   // 16 KB), four times as many as at 256 columns, so a row of B is wanted that many times more often while they pass over
   // it; sixteen rows in one stream stand at the same column to within 2 % of the stream where four streams of four rows
-  // are 4 % apart; and a load of one float per lane costs the address units 5 clocks (two floats 16, four 16).
+  // are 4 % apart; and a load of one float per lane keeps the address units busy for 8.5 clocks (two rows of four 17).
   // us as before (256 columns at once; two streams of 128; four of 64) and so, f = 256, 128, 64: 16 communities of 125 k
   // vertices, 84 M entries 10999, 5557, 2866 -> 7131, 3524, 1837; of 62 k, 30 M 3719, 1834, 893 -> 2818, 1479, 852; one of
   // the former as a row block 590, 279, 134 -> 424, 200, 105; random columns, 250 k vertices of 60 1864, 973, 501 -> 1265,
