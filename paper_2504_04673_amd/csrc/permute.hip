@@ -189,8 +189,8 @@ __device__ __forceinline__ void sort_lanes(uint32_t& x, int lane) {
 // the latency of its dependent loads (old row, row pointer, columns, new ids), so a wavefront has four rows in flight
 // while they fit 64 lanes each.  There the key carries the lane in its low bits (n <= 2^26), which makes equal columns
 // different and finds the value.  21 M entries in 500 k rows: 300 us by ranks and in the order of A, 265 so, 236 with eight
-// wavefronts per SIMD (25 of the registers that rows of 257 to 512 entries would like are spilled there: 20 k rows of 300,
-// two thirds of them so long, 348 -> 336 in all, 60 k of 200 414 -> 386); in the
+// wavefronts per SIMD (25 of the registers that rows of 257 to 512 entries would like are spilled there: 20 k rows of 300
+// 348 -> 336, 60 k of 200 414 -> 386); in the
 // order of A 245.  27 M requests to the L2s, most of them the new ids of random columns, at 85 % of the rate gathers reach.
 // Relabelling and sorting the entries twice through memory took 1.4 ms.
 // Nothing is done where check_perm_kernel found a reason against it (the host looks afterwards).
