@@ -2024,7 +2024,8 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
     // beyond it wavefronts that run ahead only cost misses.  us with and without, products of power-law matrices at 128
     // columns: 300 k vertices of 30 278, 320, 600 k of 51 849, 892, 1.1 M of 51 (563 MB) 1639, 1704, 1.2 M of 51 (614 MB) 1785,
     // 1873, 1.3 M of 30, 51, 80 (666 MB) 1392, 2148, 3279 and 1386, 2101, 2979, 1.6 M of 51 2880, 2729, 2.1 M 4109, 3521, 2.45 M
-    // 4179, 4135, of 30 3303, 3050, 3.3 M of 45 6927, 5538, 5 M of 40 10328, 8921, 9 M of 30 (4.6 GB) 16867, 15440; its layer
+    // 4179, 4135, of 30 3303, 3050, 3.3 M of 45 6927, 5538, 5 M of 40 10328, 8921, 9 M of 30 (4.6 GB) 16867, 15440 (at the line
+    // itself either may win: 1.24 M of 20, 42 1087, 1580 and 1042, 1652, 1.29 M of 42 1673, 1767, 1.32 M 1997, 1862); its layer
     // in fp32 1.2 M of 51 2173, 2293, 1.6 M 3315, 3201, 2.45 M 4833, 4740.  Between the kernels' own widths, whose rows begin
     // inside lines, from the memory-side cache's size on: 233 k of 489, f = 100 1975, 2286, 600 k of 60 (240 MB) 970, 1005, 1 M
     // of 51, f = 72 (288 MB) 1345, 1205, 2 M of 51, f = 72, 100, 112 3604, 3942, 3934 and 2637, 3739, 3739, 2.45 M of 40, f = 96
