@@ -262,6 +262,8 @@ struct SpmmHostDesc {
                             // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
   float reuse;              // uses of a row of B among the rows of A that an XCD holds (see sweep_prepare)
   bool turns, layer_turns;  // wavefronts take turns in the product, in the layer with lane groups (see there)
+  int32_t run_blocks;       // workgroups that are resident at once where the order of the rows carries locality, else 0
+  float run_rows;           // rows of a generation from which the XCDs take runs of workgroups (see sweep_prepare)
   int32_t narrow_sums;      // sums of eight lane groups: 0 plain, 1 two, 2 two and folded (see there)
   float mean_steps;         // average stream steps per wavefront (the end of the pacing schedule)
   float max_steps;          // steps of the longest stream
@@ -315,7 +317,8 @@ struct SweepPlanResult {
   bool use_sweep;
   float reuse;       // see SpmmHostDesc
   bool turns, layer_turns;
-  int32_t narrow_sums;
+  int32_t narrow_sums, run_blocks;
+  float run_rows;
   float mean_steps;  // average stream steps per wavefront
   float max_steps;   // steps of the longest stream
   SpmmWsHeader hdr;  // filled in for mode 1 (sweep part + short CSR sizes)

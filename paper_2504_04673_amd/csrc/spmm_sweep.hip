@@ -555,7 +555,19 @@ struct SweepDims {
   float pace_ticks;     // pacing: 100 MHz ticks per stream step (0: none)
   int32_t block0;       // first workgroup of this launch (one row per load)
   int32_t turn;         // steps between two priorities, at most (TurnTaking)
+  int32_t run;          // workgroups whose rows are shared out among the XCDs in runs (run_block; a multiple of 8, 0: none)
 };
+
+// The workgroup whose streams this one walks.  Workgroups go to the eight XCDs in turn, so that neighbouring rows, which want
+// the same rows of B where their order carries locality, were walked on all of them and every L2 fetched every neighbourhood.
+// Of each `run` workgroups of the schedule an XCD now takes an eighth that lies together (sweep_run has the rule).
+__device__ __forceinline__ int64_t run_block(const SweepDims& d) {
+  const uint32_t b = blockIdx.x;
+  if (d.run == 0) return (int64_t)d.block0 + b;
+  const uint32_t first = b / (uint32_t)d.run * (uint32_t)d.run;
+  const uint32_t n = min((uint32_t)d.run, gridDim.x - first), i = b - first, x = i & 7u;
+  return (int64_t)d.block0 + first + x * (n >> 3) + min(x, n & 7u) + (i >> 3);
+}
 
 // Barrier between two intervals of the sweep for the workgroups that run at the same time on
 // one XCD ("cohort" c = workgroup index / wg_per_cohort, XCD = workgroup index mod 8: workgroups
@@ -761,7 +773,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_kernel(
   const uint32_t el = row_element<ODD>(lane * FPL, FPL, d.fw);
   const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = ((int64_t)d.block0 + blockIdx.x) * 4 + wave;
+  const int64_t block = run_block(d), w = block * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != 1)
@@ -1010,7 +1022,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t loff = lane * (FPL * 4);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = ((int64_t)d.block0 + blockIdx.x) * 4 + wave;
+  const int64_t block = run_block(d), w = block * 4 + wave;
   // (the launch has whole workgroups: n_waves is a multiple of 4, checked by the launcher)
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != 1)
@@ -1048,7 +1060,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
   // tiles per pass: 4 at f = 256 (the LDS already limits a CU to two workgroups; 2 with three operand
   // terms per tile in registers), 1 below
   sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1), FROM>(
-      lds_acc, FROM != TARGETS_LDS ? piece_target + ((int64_t)d.block0 + blockIdx.x) * 4 * kSweepSlots : targets, fa, wave, (int)lane);
+      lds_acc, FROM != TARGETS_LDS ? piece_target + block * 4 * kSweepSlots : targets, fa, wave, (int)lane);
 }
 
 // W (f_in x f_out, row-major fp32) -> [f_in / 8][NB] vectors of 8 bfloat16 (k fastest), NB = f_out
@@ -1097,7 +1109,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_group_kernel(
   const uint32_t el = row_element<ODD>(lig * V, V, d.fw);
   const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t w = run_block(d) * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != R)
@@ -1281,7 +1293,7 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
   const uint32_t el = row_element<ODD>(lig * 4, 4, d.fw);
   const uint32_t loff = el * 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t w = run_block(d) * 4 + wave;
   if (w >= d.n_waves) return;
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != R)
@@ -1820,6 +1832,15 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
   h.fused_waves = local ? h.launch_waves / 2 : 0;
   out->reuse = (float)reuse;
+  out->run_blocks = local && NI == 1 ? (int32_t)std::min<int64_t>(resident_waves / 4, 1 << 20) : 0;
+  // Rows of a generation from which runs pay (sweep_run): 1.3 times the rows of a neighbourhood, three times where the columns
+  // go along with the rows, since the runs then begin in different slabs.  us without and with runs: 16 communities, 1 M of 42
+  // (62 k rows) f = 64, 128, 256 (131 k rows a generation) 1074, 1803, 3498 and 802, 1572, 3274; 300 k of 20 f = 64, 128, 256
+  // 183, 351, 702 and 157, 310, 589; 100 k of 42 f = 32, 100, 256 44, 179, 420 and 37, 111, 238; a layer 64 to 64 1084 and 893,
+  // 200 k of 50, 128 to 128 489 and 402; of 125 k rows 1772, 3414, 7041 and 1773, 3416, 7036, the layer 64 to 64 2125 and 2174.
+  // Columns within 3000 of the diagonal, 500 k of 30, f = 32, 64, 128 154, 292, 649 and 107, 205, 486; within 20000, 1 M of 24,
+  // f = 32 (131 k rows for 40 k) 249 and 237, but f = 64, 128 551, 1180 and 609, 1285; within 50000, 1 M of 40, f = 64 932 and 1125.
+  out->run_rows = (float)((tot.slide >= 600 ? 3.0 : 1.3) * span * (double)m / (double)k);
   // Sums of eight groups by the entries a segment has on average, as many of a row's as lie in one of the slabs that it
   // chooses from.  At 32 columns plain of short ones, two from 6 on, between the kernel's widths, which nonzero splitting added
   // as a tree, two at least; folded from 36 on, without locality with the two.  Error against 64 bits plain, with two
@@ -1893,6 +1914,18 @@ namespace {
 // f = 128 4155, 4240, 4127.
 int64_t operand_bytes(uint32_t kmax, int32_t fw) { return ((int64_t)kmax + 1) * fw * 4; }
 int32_t turn_steps(uint32_t kmax, int32_t fw) { return operand_bytes(kmax, fw) > (256ll << 20) ? 128 : 32; }
+
+// Workgroups that are shared out among the XCDs in runs (run_block): those of two generations, where the order of the rows
+// carries locality and one generation has the rows of more than one neighbourhood (run_rows); otherwise all XCDs want the same
+// rows of B in any case, and what one has fetched the others read from the memory-side cache.  (With one and four generations
+// 1 M of 42 in communities, f = 64 519 and 531 for 533 us, 500 k, f = 256 2052 and 1939 for 1971.)  Above 128 columns from one
+// neighbourhood on, 500 k of 42 (31 k rows), f = 256 product 2146, 1975, bfloat16 layer 2190, 1846; of 125 k the fp32 layer
+// 11456, 11775.  The layer holds the whole width in the LDS where the product goes in column groups.
+int32_t sweep_run(const SpmmHostDesc& d, int32_t fw, bool layer) {
+  if (d.run_blocks < 8) return 0;
+  const float rows = (float)d.run_blocks * 4 * kSweepSlots * (layer && d.col_slab > 0 ? (float)d.col_slab / (float)fw : 1.f);
+  return rows >= d.run_rows / (fw > 128 ? 1.3f : 1.f) ? 2 * d.run_blocks / 8 * 8 : 0;
+}
 }  // namespace
 
 namespace {
@@ -1923,6 +1956,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   const unsigned blocks = (unsigned)ceil_div(d.n_waves, 4);
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
   sd.fw = fw;
+  sd.run = sweep_run(d, fw, false);
   sd.turn = (fuse != 0 ? d.layer_turns : d.turns) ? turn_steps(kmax, fw) : 0;
   size_t lds = (size_t)4 * sd.slots * sweep_lds_width(fw) * sizeof(float);
   // (the layer: the targets behind the rows, and no more than five workgroups a CU, which 64 columns would allow: a sixth
@@ -2097,6 +2131,7 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   sd.n_waves = d.n_waves; sd.ldb = ldb; sd.ldc = f_in; sd.f_total = f_in;
   sd.generation = d.generation; sd.col0 = 0; sd.accumulate = 0; sd.slots = kSweepSlots;
   sd.turn = turn_steps(kmax, f_in);
+  sd.run = sweep_run(d, f_in, true);
   sd.b_bytes = 0;
   const bool buf = buffer_addressable(kmax, ldb, f_in, &sd.b_bytes);
   sd.row_bytes = (uint32_t)(ldb * 4);

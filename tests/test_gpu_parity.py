@@ -925,6 +925,40 @@ def test_spmm_sweep_with_and_without_locality_of_the_rows(f, labels):
     assert_close(got, ref.cpu().numpy(), zabs.cpu().numpy(), RTOL_SPMM, f"f={f} {labels}")
 
 
+@pytest.mark.parametrize("f,n,deg,parts", [(16, 300_011, 18, 50), (24, 300_011, 18, 50), (64, 300_011, 18, 50), (100, 150_001, 24, 40),
+                                           (128, 150_001, 24, 40), (256, 100_003, 24, 64), (256, 70_001, 40, 1000)])
+def test_spmm_runs_of_workgroups_for_each_xcd(f, n, deg, parts):
+    """Small communities in row order: the workgroups of two generations are shared out among the XCDs in runs.  More rows
+    than two generations hold and counts of workgroups that are no multiple of eight; product, accumulation, layer."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(f + n)
+    count = torch.randint(deg - 2, deg + 9, (n,), device="cuda", generator=gen)
+    count[::977] = 0
+    count[5::1234] = 3
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(count, 0)
+    nnz, part = int(rp[-1]), n // parts
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), count)
+    col = (row // part * part + torch.randint(part, (nnz,), device="cuda", generator=gen)).clamp(max=n - 1)
+    ci = (torch.sort(row * n + col)[0] - row * n).to(torch.int32)
+    v = torch.randn(nnz, device="cuda", generator=gen)
+    B = torch.randn(n, f, device="cuda", generator=gen)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 1
+    A, Aabs = (torch.sparse_csr_tensor(rp.long(), ci.long(), x.double(), (n, n)) for x in (v, v.abs()))
+    ref, zabs = A @ B.double(), Aabs @ B.double().abs()
+    C0 = torch.randn(n, f, device="cuda", generator=gen)
+    for C in (None, C0.clone()):
+        want, scale = (ref, zabs) if C is None else (ref + C.double(), zabs + C.double().abs())
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, B, C=C, accumulate=C is not None, ws=ws)
+        assert float(((got.double() - want).abs() - RTOL_SPMM * scale).max()) <= 1e-30, f"f={f} accumulate={C is not None}"
+    W = torch.randn(f, 40, device="cuda", generator=gen) / f ** 0.5
+    _, Z, _ = sagnn.gcn_layer_fwd(rp, ci, v, B, W, ws=ws, want_t=sagnn.gcn_layer_fwd_form(ws, f, 40) != 2)
+    # (the rows of A H, then f products and sums in 32 bits)
+    bound = (RTOL_SPMM + f * 2.0 ** -24) * (zabs @ W.double().abs())
+    assert float(((Z.double() - ref @ W.double()).abs() - bound).max()) <= 1e-30
+
+
 @pytest.mark.parametrize("f", [4, 8, 12, 20, 28, 36, 60])
 def test_spmm_sweep_of_narrow_widths_between_the_kernels_is_closer_than_one_sum(f, monkeypatch):
     """Rows whose 120 entries lie in one slab of B and are one segment: at the widths below 64 that no kernel has exactly,
