@@ -1634,6 +1634,50 @@ def test_bf16x3_gemm_has_the_accuracy_of_the_fp32_gemm(k, n):
     assert bool((Zs[4] == 0).all())
 
 
+@pytest.mark.parametrize("m,k,n,transW", [(51_203, 64, 64, False), (51_203, 100, 68, True), (53_001, 256, 132, False), (70_001, 160, 40, False),
+                                          (90_001, 128, 128, True), (170_003, 128, 40, False), (70_001, 40, 256, False), (307_203, 8, 36, True)])
+def test_fp32_gemm_in_three_terms_and_the_tiles_they_do_not_hold(m, k, n, transW):
+    """Row counts at which fp32 products run as three bfloat16 terms: no further from 64 bits than fp32 instructions, which
+    the same rows in a call of few rows take; a tile with an infinity, a tiny or a huge value, or all tiles of its columns if
+    it is in W, gives bit for bit what they give; a row with a NaN is NaN, and no other."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + k)
+    X = torch.randn(m, k, device="cuda", generator=gen)
+    W = torch.randn(k, n, device="cuda", generator=gen) / k ** 0.5
+    M = torch.randn(m, n, device="cuda", generator=gen)
+    few = 640                                       # rows of a call in fp32 instructions, whole tiles
+    odd = {3: float("inf"), 40: 1e-31, 100: 3e38, 140: -1e-42, m - 1: 2.0 ** 61}
+    run = lambda x, w, mask: sagnn.dense_gemm_act(x, w.t().contiguous() if transW else w, transW=transW, mask=mask, want_z=True)[0]
+    for mask in (None, M):
+        Z, Z0 = run(X, W, mask), run(X[:few], W, None if mask is None else M[:few])
+        ref = X.double() @ W.double()
+        if mask is not None:
+            ref = torch.where(M > 0, ref, 0.0)
+        bound = k * 2.0 ** -24 * (X.double().abs() @ W.double().abs())
+        assert float(((Z.double() - ref).abs() - bound).max()) <= 0
+        assert float((Z.double() - ref)[:few].norm()) <= 1.02 * float((Z0.double() - ref[:few]).norm())
+        Y = X.clone()
+        for r, x in odd.items():
+            Y[r, r % k] = x
+        Y[75, 75 % k] = float("nan")
+        last = (m - 1) // 32 * 32
+        Z = run(Y, W, mask)
+        tail = run(Y[last:], W, None if mask is None else M[last:])
+        Z0 = run(Y[:few], W, None if mask is None else M[:few])
+        for t in {r // 32 for r in odd if r < few}:
+            a, b = Z[32 * t:32 * t + 32], Z0[32 * t:32 * t + 32]
+            assert bool(((a == b) | (torch.isnan(a) & torch.isnan(b))).all()), t
+        assert torch.equal(Z[last:], tail)
+        want = torch.zeros(32, n, dtype=torch.bool, device="cuda")
+        want[75 - 64] = True if mask is None else mask[75] > 0
+        assert torch.equal(torch.isnan(Z[64:96]), want)
+    for x in (float("inf"), 1e-38):
+        V = W.clone()
+        V[k - 1, n - 1] = x
+        a, b = (z[:, (n - 1) // 32 * 32:] for z in (run(X, V, None)[:few], run(X[:few], V, None)))
+        assert bool(((a == b) | (torch.isnan(a) & torch.isnan(b))).all()), x
+
+
 def test_bf16_gemm_is_tight_against_bf16_rounded_oracle():
     """With operands rounded the same way the only difference left is fp32 vs fp64 accumulation,
     so the result must sit far inside the 1e-2 budget; a wrong rounding mode would not."""
