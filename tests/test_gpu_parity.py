@@ -1860,6 +1860,33 @@ def test_gcn_layer_fwd_fused(prec, fin, fout, graph, cfg1):
     assert_close(Z, zt, ztabs, rtol, "fused Z vs oracle GEMM of the kernel's own T")
 
 
+@pytest.mark.parametrize("groups,fin,fout", [("1", 64, 36), ("1", 128, 128), ("1", 256, 132), ("2", 64, 256), ("2", 128, 100)])
+def test_fp32_layer_with_values_that_three_terms_do_not_hold(groups, fin, fout, monkeypatch):
+    """fp32 operands of the sweep's epilogue go as three bfloat16 terms, tiles of rows of A H with an infinity, a NaN, a tiny or
+    a huge value, and all of them with such a value in W, in fp32 instructions: what the product and the dense transform of
+    a few rows, which is in fp32 instructions, give of the same rows of A H."""
+    monkeypatch.setenv("SAGNN_SWEEP", "1")
+    monkeypatch.setenv("SAGNN_SWEEP_GROUPS", groups)
+    g = synth.sbm_graph(6000, 16, 40, 2, 5)
+    rp, ci, v = dev(g.rowptr), dev(g.colidx), dev(g.val)
+    H = synth.normal((g.n, fin), 3, synth.STREAM_H)
+    H[7, 3], H[1500, 5], H[3000, 1], H[4500] = np.inf, np.nan, 3e38, 1e-36
+    W = synth.normal((fin, fout), 3, synth.STREAM_W, scale=1 / np.sqrt(fin))
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, g.n, fin)
+    assert ws.info()["mode"] == 1 and sagnn.gcn_layer_fwd_form(ws, fin, fout) == 2
+    for x in (None, np.inf, 1e-38):
+        if x is not None:
+            W[fin - 1, fout - 1] = x
+        T = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(H), ws=ws)
+        Z0 = sagnn.dense_gemm_act(T, dev(W), want_z=True)[0]
+        _, Z, _ = sagnn.gcn_layer_fwd(rp, ci, v, dev(H), dev(W), ws=ws, want_t=False, want_h=False)
+        assert torch.equal(torch.isnan(Z), torch.isnan(Z0)) and torch.equal(torch.isposinf(Z), torch.isposinf(Z0))
+        assert torch.equal(torch.isneginf(Z), torch.isneginf(Z0))
+        bound = 2 * fin * 2.0 ** -24 * (T.double().abs() @ dev(W).double().abs())   # the error of either
+        ok = torch.isfinite(Z0)
+        assert bool(((Z.double() - Z0.double()).abs() <= bound + 1e-44)[ok].all())
+
+
 @pytest.mark.parametrize("prec,fin,fout", [(0, 128, 128), (1, 256, 256), (0, 64, 36), (1, 128, 100), (1, 256, 64),
                                            (2, 128, 128), (2, 256, 256), (2, 64, 36), (2, 128, 100)])
 @pytest.mark.parametrize("graph", ["regular_all_rows_swept", "with_split_short_and_empty_rows"])
