@@ -458,6 +458,14 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
 #define SAGNN_FLAT(LPE_, NC_, FOLD_) \
   (buf ? go(spmm_flat_kernel<LPE_, NC_, FOLD_, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, FOLD_, false>, LPE_))
   const bool brief = a.nnz < 64 * a.nchunks;
+  // Up to 32 columns four groups of sixteen lanes a wavefront, most of them idle, where groups as narrow as a row would leave
+  // SIMDs without a wavefront: with sixteen groups some row ends at nearly every step, and its wavefront stores what the
+  // others wait for.  us, calls one after the other (7.6 is the launch), f = 16, 32: 4 k rows of 8 9.3, 8.0 -> 7.5, 7.6; 20 k of 12
+  // 9.3, 8.4 -> 8.1, 8.1; 5 k power-law rows of 19 15.3, 14.1 -> 12.0, 12.4; beyond the line 20 k of 20 12.0, 12.5 and 13.4, 13.2,
+  // 30 k of 12 9.9, 10.5 and 10.4, 10.6.
+  const bool few = a.nchunks <= 16384;
+  if (fw <= 16 && few) return SAGNN_FLAT(16, 2, 2);
+  if (fw <= 32 && few) return SAGNN_FLAT(16, 2, 1);
   if (fw <= 16) return brief ? SAGNN_FLAT(4, 4, 2) : SAGNN_FLAT(4, 8, 2);
   if (fw <= 32) return brief ? SAGNN_FLAT(8, 4, 1) : SAGNN_FLAT(8, 8, 1);
   if (fw < 64) return SAGNN_FLAT(16, 2, 1);
