@@ -608,41 +608,43 @@ __global__ __launch_bounds__(kLdsThreads) void mark_bucket_kernel(const int32_t*
     atomicAdd(&blocksum[w0 / kWordsPerBlock + threadIdx.x], tally[threadIdx.x]);
 }
 
-// Membership words from the private bitmaps.  A workgroup owns 16 consecutive 64-bit words;
-// thread (wi, sl) ORs the bitmaps of groups sl, sl+16, ... for word wi, LDS combines the 16
-// slices.
-__global__ __launch_bounds__(kThreads) void merge_kernel(const uint32_t* __restrict__ part,
-                                                         int32_t groups_per_pass, int64_t W, int64_t n,
-                                                         uint64_t* __restrict__ bm, int32_t* __restrict__ blocksum) {
-  __shared__ uint64_t red[16][17];
-  const int wi = threadIdx.x & 15, sl = threadIdx.x >> 4;
-  const int64_t w = (int64_t)blockIdx.x * 16 + wi;
+// Membership words from the private bitmaps.  A workgroup owns 64 consecutive 64-bit words, a lane a word; wavefront sl ORs
+// the bitmaps of groups sl, sl + 16, .., LDS combines the 16 slices.  Whole lines of a bitmap, and one sum to a tile's counter
+// per 64 words: the counters are few, additions to one of them follow each other across the XCDs, and with 16 words a
+// workgroup (128 of them to a counter) that was the kernel: 2 M columns, 128 bitmaps 27 -> 11 us.
+constexpr int kMergeWords = 64, kMergeSlices = 16;
+__global__ __launch_bounds__(kMergeWords * kMergeSlices) void merge_kernel(const uint32_t* __restrict__ part,
+                                                                           int32_t groups_per_pass, int64_t W, int64_t n,
+                                                                           uint64_t* __restrict__ bm, int32_t* __restrict__ blocksum) {
+  __shared__ uint64_t red[kMergeSlices][kMergeWords];
+  const int wi = threadIdx.x % kMergeWords, sl = threadIdx.x / kMergeWords;
+  const int64_t w = (int64_t)blockIdx.x * kMergeWords + wi;
   uint64_t word = 0;
   if (w < W) {
     const int64_t col = w * 64;
     const int pass = (int)(col / kLdsCols);          // kLdsCols is a multiple of 64
     const int64_t idx = (col - (int64_t)pass * kLdsCols) >> 5;
     const uint32_t* __restrict__ p = part + ((size_t)pass * groups_per_pass) * kLdsWords + idx;
-#pragma unroll 4
-    for (int g = sl; g < groups_per_pass; g += 16) {
+#pragma unroll 8
+    for (int g = sl; g < groups_per_pass; g += kMergeSlices) {
       const uint2 t = *reinterpret_cast<const uint2*>(p + (size_t)g * kLdsWords);
       word |= (uint64_t)t.x | ((uint64_t)t.y << 32);
     }
   }
   red[sl][wi] = word;
   __syncthreads();
-  if (sl == 0) {   // sixteen lanes; their words lie in one tile
+  if (sl == 0) {   // (their words lie in one tile)
     int cnt = 0;
     if (w < W) {
 #pragma unroll
-      for (int j = 1; j < 16; ++j) word |= red[j][wi];
+      for (int j = 1; j < kMergeSlices; ++j) word |= red[j][wi];
       const int64_t col = w * 64;
       if (n - col < 64) word &= (1ull << (n - col)) - 1ull;
       bm[w] = word;
       cnt = __popcll(word);
     }
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 16);
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
     if (wi == 0 && cnt) atomicAdd(&blocksum[w / kWordsPerBlock], cnt);
   }
 }
@@ -1206,7 +1208,7 @@ int plan_launch(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t m, int
                        lds, s, d_colidx, nnz, n, (int32_t)groups_per_pass, w.part, err, al ? 1 : 0,
                        speculated ? d_colidx_compact : (int32_t*)nullptr, w.blocksum, w.nblk);
     SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(merge_kernel, dim3((unsigned)ceil_div(w.W, 16)), dim3(kThreads), 0, s, w.part,
+    hipLaunchKernelGGL(merge_kernel, dim3((unsigned)ceil_div(w.W, kMergeWords)), dim3(kMergeWords * kMergeSlices), 0, s, w.part,
                        (int32_t)groups_per_pass, w.W, n, w.bitmap, w.blocksum);
     SAGNN_LAUNCH_CHECK();
   } else {
