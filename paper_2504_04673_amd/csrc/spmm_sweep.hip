@@ -354,6 +354,12 @@ __global__ __launch_bounds__(1024) void sweep_scan_kernel(const int32_t* __restr
 // g owns slots g*SL .. g*SL+SL-1), stored zipped: step t of group g at position R*t + g.  Steps that no
 // entry lands on (padding of the shorter group streams and at interval boundaries) multiply
 // row 0 of B by 0.
+// BY_PLACE: a thread takes a place of the stream and looks up its entry, else an entry and looks up its place.  Where four and
+// more streams are zipped an entry's two stores go to lines of their own, and requests to lines were the kernel's time (1 M
+// vertices, 40 M entries, four streams 422 us by entry, 260 by place; the whole preparation 1230, 1089, with sixteen 1908, 1354,
+// with eight 300 k of 60 932, 860); one or two take runs either way, and so do rows whose columns lie in few slabs, and looking
+// up costs more (2.45 M, 125 M entries, two 4365, 4778; communities, 500 k of 42, four 1238, 1277).
+template <bool BY_PLACE>
 __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const float* __restrict__ val, const int32_t* __restrict__ piece_info,
@@ -366,12 +372,12 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
   const int tid = threadIdx.x;
   const int S = n_slabs, R = groups, SL = slots_per_group;
   const BuildTables T = carve_tables(build_lds, S);
-  int32_t* slab_base_ = T.slab_tot + S * kSweepSlots;          // [S][16]: first step of slab s, group g
+  int32_t* slab_base_ = T.slab_tot + S * kSweepSlots;          // [16][S]: first step of slab s of group g at g S + s
   build_tables<false>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, SL, pc, T, nullptr);
   const int per = sync_slabs > 0 ? sync_slabs : S;
   const int32_t* __restrict__ so = sync_off + w * (kSweepMaxIntervals + 1);
   const int64_t base = wave_base[w];
-  // first step of every slab, a wavefront per (interval, group); the steps no entry lands on are zeroed on the way
+  // first step of every slab, a wavefront per (interval, group)
   const int lane = tid & 63;
   for (int idx = tid >> 6; idx < n_intervals * R; idx += kBuildThreads / 64) {
     const int i = idx / R, gi = idx - i * R;
@@ -386,50 +392,108 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
         const int32_t t = __shfl_up(inc, o, 64);
         if (lane >= o) inc += t;
       }
-      if (s < s1) slab_base_[s * kSweepSlots + gi] = run + inc - v;
+      if (s < s1) slab_base_[gi * S + s] = run + inc - v;
       run += __shfl(inc, 63, 64);
     }
-    for (int32_t t = run + lane; t < so[i + 1]; t += 64) {
-      code[base + (int64_t)t * R + gi] = 0u;
-      vals[base + (int64_t)t * R + gi] = 0.f;
-    }
+    if constexpr (!BY_PLACE)
+      for (int32_t t = run + lane; t < so[i + 1]; t += 64) {   // the steps no entry lands on
+        code[base + (int64_t)t * R + gi] = 0u;
+        vals[base + (int64_t)t * R + gi] = 0.f;
+      }
   }
-  if (tid < kSweepSlots) lay_slots(pc, tid, pc.row[tid] >= 0 ? count_upto(pc.deg[tid], pc.j[tid], pc.p[tid]) : 0);
+  if constexpr (!BY_PLACE) {
+    if (tid < kSweepSlots) lay_slots(pc, tid, pc.row[tid] >= 0 ? count_upto(pc.deg[tid], pc.j[tid], pc.p[tid]) : 0);
+    __syncthreads();
+    const float inv = 1.0f / (float)slab_width;
+    const int32_t total = pc.pre[kSweepSlots];
+    for (int32_t e0 = tid; e0 < total; e0 += 4 * kBuildThreads) {
+      int slot[4];
+      int32_t i[4], at[4];
+      uint32_t c[4];
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int32_t e = e0 + q * kBuildThreads < total ? e0 + q * kBuildThreads : total - 1;
+        slot[q] = slot_at(pc, e);
+        at[q] = e - pc.pre[slot[q]];
+        i[q] = pc.j[slot[q]] + at[q] * pc.p[slot[q]];
+        c[q] = (uint32_t)colidx[pc.beg[slot[q]] + i[q]];
+        v[q] = val[pc.beg[slot[q]] + i[q]];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (e0 + q * kBuildThreads >= total) break;
+        const int sl = slot[q];
+        const int32_t j = pc.j[sl], p = pc.p[sl];
+        const uint32_t cc = c[q] > kmax ? kmax : c[q];
+        int s = slab_of(cc, (uint32_t)slab_width, inv, S);
+        // the row is ascending, but clamped / equal columns may sit on a slab boundary: trust lo[]
+        while (s > 0 && i[q] < T.LO(sl, s)) --s;
+        while (s < S - 1 && i[q] >= T.LO(sl, s + 1)) ++s;
+        const int32_t rank = at[q] - count_upto(T.LO(sl, s), j, p);
+        // a segment also ends every kSweepRunMax entries, which bounds the length of any serial
+        // fp32 accumulation (and with it the rounding bias on rows of equal terms)
+        const bool last = i[q] + p >= T.LO(sl, s + 1) || (rank & (kSweepRunMax - 1)) == kSweepRunMax - 1;
+        const int gi = sl / SL;
+        const int64_t pos = base + (int64_t)(slab_base_[gi * S + s] + T.OFF(s, sl) + rank) * R + gi;
+        code[pos] = cc | ((uint32_t)sl << kSweepColBits) | (last ? 0x80000000u : 0u);
+        vals[pos] = v[q];
+      }
+    }
+    return;
+  }
   __syncthreads();
-  const float inv = 1.0f / (float)slab_width;
-  const int32_t total = pc.pre[kSweepSlots];
-  for (int32_t e0 = tid; e0 < total; e0 += 4 * kBuildThreads) {
-    int slot[4];
-    int32_t i[4], at[4];
-    uint32_t c[4];
+  // In the order of the stream: a thread looks up which entry its place takes, so that the stores are whole lines and the loads
+  // runs of a segment's entries.
+  const int group_bits = 31 - __clz(R);
+  const int32_t words = so[n_intervals] * R;
+  for (int32_t q0 = tid; q0 < words; q0 += 4 * kBuildThreads) {
+    int32_t from[4];
+    uint32_t tag[4], c[4];
     float v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int32_t e = e0 + q * kBuildThreads < total ? e0 + q * kBuildThreads : total - 1;
-      slot[q] = slot_at(pc, e);
-      at[q] = e - pc.pre[slot[q]];
-      i[q] = pc.j[slot[q]] + at[q] * pc.p[slot[q]];
-      c[q] = (uint32_t)colidx[pc.beg[slot[q]] + i[q]];
-      v[q] = val[pc.beg[slot[q]] + i[q]];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (e0 + q * kBuildThreads >= total) break;
-      const int sl = slot[q];
-      const int32_t j = pc.j[sl], p = pc.p[sl];
-      const uint32_t cc = c[q] > kmax ? kmax : c[q];
-      int s = slab_of(cc, (uint32_t)slab_width, inv, S);
-      // the row is ascending, but clamped / equal columns may sit on a slab boundary: trust lo[]
-      while (s > 0 && i[q] < T.LO(sl, s)) --s;
-      while (s < S - 1 && i[q] >= T.LO(sl, s + 1)) ++s;
-      const int32_t rank = at[q] - count_upto(T.LO(sl, s), j, p);
+    for (int u = 0; u < 4; ++u) {
+      const int32_t q = q0 + u * kBuildThreads;
+      const int gi = q & (R - 1);
+      const int32_t t = q >> group_bits;
+      // the last slab, then the last slot of the group, that begins at or before step t: the one that has it, if any
+      int s = 0;
+      const int32_t* __restrict__ first = slab_base_ + gi * S;
+      for (int n = S; n > 1;) {
+        const int half = n >> 1;
+        s = first[s + half] <= t ? s + half : s;
+        n -= half;
+      }
+      const int32_t in_slab = t - first[s], total = T.TOT(s, gi);
+      int sl = gi * SL;
+      for (int n = SL; n > 1;) {
+        const int half = n >> 1;
+        sl = T.OFF(s, sl + half) <= in_slab ? sl + half : sl;
+        n -= half;
+      }
+      const int32_t rank = in_slab - T.OFF(s, sl);
+      const int32_t len = (sl + 1 < (gi + 1) * SL ? T.OFF(s, sl + 1) : total) - T.OFF(s, sl);
+      const bool in = q < words && rank >= 0 && rank < len;
+      // entry `rank` of those of the row's slab that are this piece's: every p-th from the j-th of the row on
+      const int32_t p = pc.p[sl], lo = T.LO(sl, s);
+      const int32_t skip = p == 1 ? 0 : ((pc.j[sl] - lo) % p + p) % p;
+      from[u] = in ? pc.beg[sl] + lo + skip + rank * p : -1;
       // a segment also ends every kSweepRunMax entries, which bounds the length of any serial
       // fp32 accumulation (and with it the rounding bias on rows of equal terms)
-      const bool last = i[q] + p >= T.LO(sl, s + 1) || (rank & (kSweepRunMax - 1)) == kSweepRunMax - 1;
-      const int gi = sl / SL;
-      const int64_t pos = base + (int64_t)(slab_base_[s * kSweepSlots + gi] + T.OFF(s, sl) + rank) * R + gi;
-      code[pos] = cc | ((uint32_t)sl << kSweepColBits) | (last ? 0x80000000u : 0u);
-      vals[pos] = v[q];
+      const bool last = rank + 1 == len || (rank & (kSweepRunMax - 1)) == kSweepRunMax - 1;
+      tag[u] = ((uint32_t)sl << kSweepColBits) | (last ? 0x80000000u : 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      c[u] = from[u] >= 0 ? (uint32_t)colidx[from[u]] : 0u;
+      v[u] = from[u] >= 0 ? val[from[u]] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int32_t q = q0 + u * kBuildThreads;
+      if (q >= words) break;
+      code[base + q] = from[u] >= 0 ? (c[u] > kmax ? kmax : c[u]) | tag[u] : 0u;
+      vals[base + q] = v[u];
     }
   }
 }
@@ -1738,7 +1802,8 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const size_t count_lds = sweep_count_lds_bytes(S), build_lds = sweep_build_lds_bytes(S);
   SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_count_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)count_lds));
-  SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_build_kernel),
+  const auto build = R >= 4 && !local ? sweep_build_kernel<true> : sweep_build_kernel<false>;
+  SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(build),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)build_lds));
   int64_t stream_len = 0, short_base = 0;
   for (int attempt = 0; attempt < 2; ++attempt) {
@@ -1771,7 +1836,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
                        reinterpret_cast<float*>(ws + L.sched));
     SAGNN_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(sweep_build_kernel, dim3((unsigned)NW4), dim3(kBuildThreads), build_lds, s, d_rowptr,
+  hipLaunchKernelGGL(build, dim3((unsigned)NW4), dim3(kBuildThreads), build_lds, s, d_rowptr,
                      d_colidx, d_val, d_info, d_wave_base, d_sync_off, (int32_t)S, (int32_t)width, kmax,
                      (int32_t)R, (int32_t)SL, (int32_t)NI, (int32_t)sync_slabs, reinterpret_cast<uint32_t*>(ws + L.code),
                      reinterpret_cast<float*>(ws + L.vals));
