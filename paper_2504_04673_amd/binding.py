@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import types
 from dataclasses import dataclass
 
 import numpy as np
@@ -158,6 +159,26 @@ def lib():
     return _lib
 
 
+_bound = None
+# the calls of a step: integers and pointers only
+STEP_CALLS = ("spmm_plan_needed_rows", "spmm_pack_rows", "spmm_csr_tallskinny", "dense_gemm_act", "gcn_layer_fwd", "gcn_layer_bwd")
+
+
+def _calls():
+    """The calls of a step by address (csrc/marshal.c), with the parameters that lib() declares."""
+    global _bound
+    if _bound is None:
+        L = lib()
+        if not os.path.exists(_build.MARSHAL):
+            _build.build_marshal()
+        from . import _marshal
+        _bound = types.SimpleNamespace(**{
+            name: _marshal.bind(ctypes.cast(getattr(L, name), ctypes.c_void_p).value,
+                                "".join("p" if t is ctypes.c_void_p else "i" for t in getattr(L, name).argtypes))
+            for name in STEP_CALLS})
+    return _bound
+
+
 def _check(rc: int, where: str):
     if rc != 0:
         raise SagnnError(rc, where)
@@ -239,16 +260,14 @@ def spmm_plan_needed_rows(rowptr, colidx, n: int, colblk, want_compact=True, val
     m, nnz = rowptr.numel() - 1, colidx.numel()
     colblk = np.ascontiguousarray(colblk, dtype=np.int64)
     nb = colblk.size - 1
-    L = lib()
     cap = int((n if oblivious else min(n, nnz)) if needed_cap is None else needed_cap)
     if bufs is None:
         bufs = plan_buffers(m, n, nnz, nb, rowptr.device, cap, want_compact)
     ws, needed, compact = bufs
     blk_off = np.zeros(nb + 1, dtype=np.int64)
-    rc = L.spmm_plan_needed_rows(_ptr(rowptr), _ptr(colidx), m, n, nnz,
-                                 _host(colblk), nb, _ptr(needed), cap,
-                                 _host(blk_off), _ptr(compact), _ptr(ws),
-                                 ws.numel(), _plan_flags(validate, oblivious, multipass), _stream())
+    rc = _calls().spmm_plan_needed_rows(_ptr(rowptr), _ptr(colidx), m, n, nnz, colblk, nb, _ptr(needed), cap,
+                                        blk_off, _ptr(compact), _ptr(ws), ws.numel(),
+                                        _plan_flags(validate, oblivious, multipass), _stream())
     _check(rc, "spmm_plan_needed_rows")
     N = int(blk_off[-1])
     if compact is not None and compact.numel() != nnz:
@@ -299,7 +318,7 @@ def spmm_pack_rows(H, rows, out=None):
     if out is None:
         out = torch.empty((N, f), dtype=torch.float32, device=H.device)
     _mat(out, "out")
-    _check(lib().spmm_pack_rows(_ptr(H), n, _ld(H), f, _ptr(rows), N, _ptr(out), _ld(out),
+    _check(_calls().spmm_pack_rows(_ptr(H), n, _ld(H), f, _ptr(rows), N, _ptr(out), _ld(out),
                                 _stream()), "spmm_pack_rows")
     return out
 
@@ -414,7 +433,7 @@ def spmm_csr_tallskinny(rowptr, colidx, val, B, C=None, accumulate=False, ws: Sp
     _mat(C, "C")
     if ws is not None and (ws.m != m or ws.nnz != nnz or ws.f < f or k < ws.k):
         raise ValueError("workspace was prepared for another matrix or a taller operand")
-    rc = lib().spmm_csr_tallskinny(_ptr(rowptr), _ptr(colidx), _ptr(val), m, k, nnz, _ptr(B),
+    rc = _calls().spmm_csr_tallskinny(_ptr(rowptr), _ptr(colidx), _ptr(val), m, k, nnz, _ptr(B),
                                    _ld(B), f, _ptr(C), _ld(C), int(accumulate),
                                    _ptr(ws.buf) if ws else None, ws.buf.numel() if ws else 0,
                                    _stream())
@@ -433,7 +452,7 @@ def dense_gemm_act(X, W, transW=False, prec=GEMM_FP32, act=ACT_IDENTITY, mask=No
     else:
         Z = torch.empty((m, nout), dtype=torch.float32, device=X.device) if want_z else None
         A = torch.empty((m, nout), dtype=torch.float32, device=X.device) if want_act else None
-    rc = lib().dense_gemm_act(_ptr(X), _ld(X), _ptr(W), _ld(W), int(transW), m, kdim, nout,
+    rc = _calls().dense_gemm_act(_ptr(X), _ld(X), _ptr(W), _ld(W), int(transW), m, kdim, nout,
                               prec, act, _ptr(mask), _ld(mask) if mask is not None else 0,
                               _ptr(Z), nout, _ptr(A), nout, _stream())
     _check(rc, "dense_gemm_act")
@@ -464,7 +483,7 @@ def gcn_layer_fwd(rowptr, colidx, val, H, W, act=ACT_RELU, prec=GEMM_FP32, ws: S
                                        f_in, _ptr(W), f_out, act, prec, _ptr(T), _ptr(Z), _ptr(Ho), _stream())
         _check(rc, "gcn_layer_fwd_fused")
         return T, Z, Ho
-    rc = lib().gcn_layer_fwd(_ptr(rowptr), _ptr(colidx), _ptr(val), m, k, nnz, _ptr(H), _ld(H),
+    rc = _calls().gcn_layer_fwd(_ptr(rowptr), _ptr(colidx), _ptr(val), m, k, nnz, _ptr(H), _ld(H),
                              f_in, _ptr(W), f_out, act, prec, _ptr(T), _ptr(Z), _ptr(Ho),
                              _ptr(ws.buf) if ws else None, ws.buf.numel() if ws else 0, _stream())
     _check(rc, "gcn_layer_fwd")
@@ -499,7 +518,7 @@ def gcn_layer_bwd(rowptr, colidx, val, G, W, Zprev, Hprev, prec=GEMM_FP32, ws: S
         b = ctypes.c_size_t(0)
         _check(lib().gcn_bwd_workspace_bytes(m, f_in, f_out, ctypes.byref(b)), "gcn_bwd_workspace_bytes")
         yws = _ws(b.value, dev)
-    rc = lib().gcn_layer_bwd(_ptr(rowptr), _ptr(colidx), _ptr(val), m, nnz, _ptr(G), f_out, _ptr(W),
+    rc = _calls().gcn_layer_bwd(_ptr(rowptr), _ptr(colidx), _ptr(val), m, nnz, _ptr(G), f_out, _ptr(W),
                              f_in, _ptr(Zprev), _ptr(Hprev), prec, _ptr(S), _ptr(Gp), _ptr(Y),
                              _ptr(ws.buf) if ws else None, ws.buf.numel() if ws else 0,
                              _ptr(yws), yws.numel() if yws is not None else 0, _stream())

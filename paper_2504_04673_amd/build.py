@@ -3,12 +3,14 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(_HERE), "include")
 LIB = os.path.join(_HERE, "libsagnn.so")
+MARSHAL = os.path.join(_HERE, "_marshal.so")     # csrc/marshal.c, the calls of binding.py
 OBJDIR = os.path.join(_HERE, "_build")
 SOURCES = ["api.hip", "pack.hip", "plan.hip", "spmm.hip", "spmm_flat.hip", "spmm_sweep.hip", "gemm_nn_bf16.hip", "gemm_nn_fp32.hip", "gemm_nn_bf16x3.hip", "gemm_nn_guarded.hip", "gemm.hip", "stages.hip", "radix.hip",
            "fused.hip", "permute.hip", "sweep_plan.hip", "tiles.hip"]
@@ -31,7 +33,7 @@ def stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(d) > t for d in sources() + HEADERS)
+    return not os.path.exists(MARSHAL) or any(os.path.getmtime(d) > t for d in sources() + HEADERS)
 
 
 def _run(cmd, verbose):
@@ -40,7 +42,7 @@ def _run(cmd, verbose):
         print(res.stdout)
         print(res.stderr)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd[-3:]))
+        raise RuntimeError("compilation failed: " + " ".join(cmd[-3:]))
 
 
 def build_hip(verbose: bool = False, incremental: bool = False, jobs: int = 8) -> str:
@@ -60,4 +62,11 @@ def build_hip(verbose: bool = False, incremental: bool = False, jobs: int = 8) -
     with ThreadPoolExecutor(max_workers=max(1, jobs)) as ex:
         list(ex.map(lambda c: _run(c, verbose), todo))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
+    build_marshal(verbose)
     return LIB
+
+
+def build_marshal(verbose: bool = False) -> str:
+    _run([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", MARSHAL,
+          os.path.join(CSRC, "marshal.c")], verbose)
+    return MARSHAL

@@ -5,6 +5,7 @@ import os
 import random
 import re
 
+import numpy as np
 import pytest
 
 import paper_2504_04673_amd as sagnn
@@ -224,3 +225,28 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode == 2
     assert "ONE GPU" in r.stderr or "one GPU" in r.stderr.lower()
     assert r.stdout.strip() == ""
+
+
+def test_step_calls_by_address_take_what_the_declared_ones_take():
+    """The calls of a step go by address instead of through ctypes: the same results for the same arguments, and what has no
+    integer (or, for a pointer, None or a host array) in a parameter's place, or another number of arguments, is refused."""
+    L, calls = sagnn.lib(), binding._calls()
+    for name in binding.STEP_CALLS:
+        declared, bound = getattr(L, name), getattr(calls, name)
+        none = [None if t is ctypes.c_void_p else 0 for t in declared.argtypes]
+        for x in (0, 1, 4, -1, 1 << 40):          # all of them invalid calls: no pointer is given
+            args = [a if a is None else x for a in none]
+            assert bound(*args) == declared(*args), (name, x)
+        for args in (none[:-1], none + [0], [], [1.0 if a is None else a for a in none], ["" for a in none],
+                     [0 if t is ctypes.c_void_p else None for t in declared.argtypes]):
+            with pytest.raises(TypeError):
+                bound(*args)
+    # host arrays: block boundaries that begin at 0, ascend and end at n (what is refused then is the missing row pointer) or not
+    for blocks in ([0, 3, 8], [1, 3, 8], [0, 3, 9], [0, 9, 8]):
+        a, out = np.array(blocks, dtype=np.int64), np.zeros(3, dtype=np.int64)
+        args = [1 << 12, 1 << 12, 1, 8, 0, a, 2, 1 << 12, 8, out, None, None, 0, 0, None]      # (no workspace)
+        rc = calls.spmm_plan_needed_rows(*args)
+        assert rc == L.spmm_plan_needed_rows(*[x.ctypes.data if isinstance(x, np.ndarray) else x for x in args])
+        assert (rc == -3) == (blocks != [0, 3, 8]) and rc < 0
+    with pytest.raises((TypeError, BufferError, ValueError)):
+        calls.spmm_plan_needed_rows(*[np.zeros((4, 4), dtype=np.int64)[:, 1] if i == 5 else x for i, x in enumerate(args)])
