@@ -266,8 +266,8 @@ typedef struct sagnn_spmm_options {
                               through the nonzero-splitting kernel on a compacted CSR.  Every row then
                               ends in a wavefront of the sweep, so gcn_layer_fwd with d_T = NULL can
                               take its sweep-epilogue form on graphs with many short rows.  Possible
-                              with widths of 64 and up, 16 accumulator rows, no slab intervals and
-                              short rows of at most 255 entries.
+                              with 16 accumulator rows, no slab intervals and short rows of at most
+                              255 entries.
                               0 or 1 = where possible, -1 = never                                     */
   int32_t dense_tiles;     /* 1: the tiles of A that are dense enough to re-use staged rows of the dense
                               operand are taken out of the matrix and multiplied by a kernel that keeps

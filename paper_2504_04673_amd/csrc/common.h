@@ -262,6 +262,7 @@ struct SpmmHostDesc {
                             // communities, f = 128 to 128 173 us, 256 to 256 455; product and transform apart 109, 253
   float reuse;              // uses of a row of B among the rows of A that an XCD holds (see sweep_prepare)
   bool turns, layer_turns;  // wavefronts take turns in the product, in the layer with lane groups (see there)
+  int32_t long_waves;       // wavefronts of a sweep before those of whole short rows
   int32_t run_blocks;       // workgroups that are resident at once where the order of the rows carries locality, else 0
   float run_rows;           // rows of a generation from which the XCDs take runs of workgroups (see sweep_prepare)
   int32_t narrow_sums;      // sums of eight lane groups: 0 plain, 1 two, 2 two and folded (see there)
@@ -317,7 +318,7 @@ struct SweepPlanResult {
   bool use_sweep;
   float reuse;       // see SpmmHostDesc
   bool turns, layer_turns;
-  int32_t narrow_sums, run_blocks;
+  int32_t narrow_sums, run_blocks, long_waves;
   float run_rows;
   float mean_steps;  // average stream steps per wavefront
   float max_steps;   // steps of the longest stream

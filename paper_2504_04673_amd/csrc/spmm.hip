@@ -726,7 +726,7 @@ SAGNN_EXPORT int spmm_csr_prepare_opt(const int32_t* d_rowptr, const int32_t* d_
   desc.apart = plan.use_sweep && !sweep_size(k, nnz, f) && opt.schedule != 2;
   desc.barriers = h.barriers; desc.pace_ps_per_step = h.pace_ps_per_step > 0 ? h.pace_ps_per_step : 0;
   desc.reuse = plan.reuse; desc.turns = plan.turns; desc.layer_turns = plan.layer_turns; desc.narrow_sums = plan.narrow_sums;
-  desc.run_blocks = plan.run_blocks; desc.run_rows = plan.run_rows;
+  desc.run_blocks = plan.run_blocks; desc.long_waves = plan.long_waves; desc.run_rows = plan.run_rows;
   desc.mean_steps = plan.mean_steps;
   desc.max_steps = plan.max_steps;
   spmm_desc_put(d_ws, desc);

@@ -32,6 +32,7 @@
 #include <algorithm>
 #include <atomic>
 #include <functional>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -508,16 +509,19 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_short_count_kernel(
   const int64_t w = w0 + ((int64_t)blockIdx.x * kBuildThreads + threadIdx.x) / kSweepSlots;   // sixteen lanes a wavefront
   const int slot = threadIdx.x & (kSweepSlots - 1);
   const int32_t row = w < w1 ? piece_info[2 * (w * kSweepSlots + slot)] : -1;
-  int32_t t = row >= 0 ? rowptr[row + 1] - rowptr[row] : 0;
+  const int32_t deg = row >= 0 ? rowptr[row + 1] - rowptr[row] : 0;
+  int32_t t = deg;
   for (int o = 1; o < kSweepSlots; o <<= 1) {                  // sum over a group, largest of the groups
     const int32_t u = __shfl_xor(t, o, kSweepSlots);
     t = o < slots_per_group ? t + u : (u > t ? u : t);
   }
+  int32_t* __restrict__ so = sync_off + w * (kSweepMaxIntervals + 1);
+  if (w < w1 && slots_per_group == 1) so[kSweepOwnSteps + slot] = deg;
   t = (t + 7) & ~7;
   if (w < w1 && slot == 0) {
     wave_steps[w] = t;
-    sync_off[w * (kSweepMaxIntervals + 1)] = 0;
-    sync_off[w * (kSweepMaxIntervals + 1) + 1] = t;
+    so[0] = 0;
+    so[1] = t;
   }
 }
 
@@ -620,6 +624,7 @@ struct SweepDims {
   float pace_ticks;     // pacing: 100 MHz ticks per stream step (0: none)
   int32_t block0;       // first workgroup of this launch (one row per load)
   int32_t turn;         // steps between two priorities, at most (TurnTaking)
+  int32_t long_waves;   // wavefronts before those of whole short rows
   int32_t run;          // workgroups whose rows are shared out among the XCDs in runs (run_block; a multiple of 8, 0: none)
 };
 
@@ -732,6 +737,27 @@ struct SegmentSum {
     batch_ends();
     const vec t = acc;
     acc = 0.f;
+    return t;
+  }
+};
+
+// Sum of a whole short row with eight lane groups: four entries at a time, then these sums, which is as near to 64 bits as
+// nonzero splitting's batches of eight were (2-norm by that, as one sum and so, e-8, f = 32, power-law 2.45 M vertices of 51
+// 1.47, 1.58, 1.46, 1 M of 14 1.31, 1.41, 1.29, random columns, 300 k of 20 7.18, 7.31, 7.16).
+template <typename vec>
+struct ShortRowSum {
+  vec acc = 0.f, part = 0.f;
+  __device__ __forceinline__ void add(int u, float v, const vec& h) {
+    part += v * h;
+    if ((u & 3) == 3) {
+      acc += part;
+      part = 0.f;
+    }
+  }
+  __device__ __forceinline__ void batch_ends() {}
+  __device__ __forceinline__ vec take() {
+    const vec t = acc + part;
+    acc = part = 0.f;
     return t;
   }
 };
@@ -1371,79 +1397,87 @@ __global__ __launch_bounds__(256) void spmm_sweep_perm_kernel(
     all_own = __builtin_amdgcn_readfirstlane(all_own);
   }
 
-  SegmentSum<vec, TWO> sum;
   [[maybe_unused]] vec tot = 0.f;
-  uint32_t cb[NB];
-  float vb[NB];
-#pragma unroll
-  for (int q = 0; q < NB; ++q) {
-    cb[q] = steps > 0 ? cw[q * 64 + lane] : 0u;
-    vb[q] = steps > 0 ? vw[q * 64 + lane] : 0.f;
-  }
-  [[maybe_unused]] TurnTaking turn(steps, d.turn);
-  for (int32_t e = 0; e < steps; e += 8) {
-    if constexpr (TURN) turn.at(e);
-    // the next iteration's stream words are requested before this one's gathers are waited for
-    const bool more = e + 8 < steps;
-    uint32_t ncb[NB];
-    float nvb[NB];
+  auto walk = [&](auto sum, auto folded) {
+    constexpr bool kFold = decltype(folded)::value;
+    uint32_t cb[NB];
+    float vb[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
-      ncb[q] = more ? cw[(e + 8) * R + q * 64 + lane] : 0u;
-      nvb[q] = more ? vw[(e + 8) * R + q * 64 + lane] : 0.f;
+      cb[q] = steps > 0 ? cw[q * 64 + lane] : 0u;
+      vb[q] = steps > 0 ? vw[q * 64 + lane] : 0.f;
     }
-    uint32_t mc[8];
-    float mv[8];
-    vec h[8];
+    [[maybe_unused]] TurnTaking turn(steps, d.turn);
+    for (int32_t e = 0; e < steps; e += 8) {
+      if constexpr (TURN) turn.at(e);
+      // the next iteration's stream words are requested before this one's gathers are waited for
+      const bool more = e + 8 < steps;
+      uint32_t ncb[NB];
+      float nvb[NB];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      mc[u] = (uint32_t)__shfl((int)cb[u / UB], (u % UB) * R + (int)gid, 64);
-      mv[u] = __shfl(vb[u / UB], (u % UB) * R + (int)gid, 64);
-      const uint32_t col = mc[u] & kColMask;
-      if constexpr (BUF) {
-        h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(rs, col * d.row_bytes + loff, 0, 0));
-      } else {
-        h[u] = *reinterpret_cast<const vec*>(reinterpret_cast<const char*>(B + (int64_t)col * d.ldb) + loff);
+      for (int q = 0; q < NB; ++q) {
+        ncb[q] = more ? cw[(e + 8) * R + q * 64 + lane] : 0u;
+        nvb[q] = more ? vw[(e + 8) * R + q * 64 + lane] : 0.f;
       }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(h[u]));
-    if constexpr (SL > 1) {
+      uint32_t mc[8];
+      float mv[8];
+      vec h[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        sum.add(u, mv[u], h[u]);
-        if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
-          vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
-          if constexpr (FOLD) {
-            *p += tot + sum.take();
-            tot = 0.f;
-          } else {
-            *p += sum.take();
-          }
+        mc[u] = (uint32_t)__shfl((int)cb[u / UB], (u % UB) * R + (int)gid, 64);
+        mv[u] = __shfl(vb[u / UB], (u % UB) * R + (int)gid, 64);
+        const uint32_t col = mc[u] & kColMask;
+        if constexpr (BUF) {
+          h[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(rs, col * d.row_bytes + loff, 0, 0));
+        } else {
+          h[u] = *reinterpret_cast<const vec*>(reinterpret_cast<const char*>(B + (int64_t)col * d.ldb) + loff);
         }
       }
-    } else {
-      if (e + 8 <= all_own) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) sum.add(u, mv[u], h[u]);
+      for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(h[u]));
+      if constexpr (SL > 1) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          sum.add(u, mv[u], h[u]);
+          if (mc[u] >> 31) {   // last entry of a (piece, slab) segment of this lane's group
+            vec* p = reinterpret_cast<vec*>(my + __mul24((mc[u] >> kSweepColBits) & (kSweepSlots - 1), kRow));
+            if constexpr (kFold) {
+              *p += tot + sum.take();
+              tot = 0.f;
+            } else {
+              *p += sum.take();
+            }
+          }
+        }
       } else {
+        if (e + 8 <= all_own) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (e + u < own) sum.add(u, mv[u], h[u]);
+          for (int u = 0; u < 8; ++u) sum.add(u, mv[u], h[u]);
+        } else {
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (e + u < own) sum.add(u, mv[u], h[u]);
+        }
+      }
+      sum.batch_ends();
+      // (folded every 32 entries: with 16 groups there are no slots to flush into; four groups and two would be 1 to 3 % slower
+      // for 0.2 to 2 %, what is left there are the entries outside a community)
+      if constexpr (kFold)
+        if ((e & 31) == 24) tot += sum.take();
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        cb[q] = ncb[q];
+        vb[q] = nvb[q];
       }
     }
-    sum.batch_ends();
-    // (folded every 32 entries: with 16 groups there are no slots to flush into; four groups and two would be 1 to 3 % slower
-    // for 0.2 to 2 %, what is left there are the entries outside a community)
-    if constexpr (FOLD)
-      if ((e & 31) == 24) tot += sum.take();
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      cb[q] = ncb[q];
-      vb[q] = nvb[q];
-    }
+    if constexpr (SL == 1) tot += sum.take();
+  };
+  if constexpr (SL > 1) {
+    if (w >= d.long_waves) walk(ShortRowSum<vec>{}, std::false_type{});
+    else walk(SegmentSum<vec, TWO>{}, std::integral_constant<bool, FOLD>{});
+  } else {
+    walk(SegmentSum<vec, TWO>{}, std::integral_constant<bool, FOLD>{});
   }
-  if constexpr (SL == 1) tot += sum.take();
 
 #pragma unroll 1
   for (int ls = 0; ls < SL; ++ls) {
@@ -1749,9 +1783,15 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // what the layer form with the dense transform as the sweep's epilogue needs.
   // Measured never slower than the nonzero-splitting kernel on the power-law graphs (233 k vertices:
   // 2.54 -> 2.50 ms, 2.45 M vertices: 2.78 -> 2.62 ms at f = 64, 4.24 -> 4.19 ms at f = 128), also
-  // when the short rows are very short (2 M rows of which 92 % hold one entry each: 3.50 -> 3.38 ms).
+  // when the short rows are very short (2 M rows of which 92 % hold one entry each: 3.50 -> 3.38 ms).  With eight and sixteen
+  // groups us so for in kernels of their own, power-law 1 M vertices of 50 f = 16, 24, 32 472, 588, 522 -> 398, 510, 444, of 14
+  // f = 16, 32 199, 250 -> 161, 180, 2.45 M of 51 1232, 1370 -> 1094, 1184, 233 k of 489 815, 900 -> 760, 854; random columns, 100 k of
+  // 20 28, 36 -> 22, 30; communities, 500 k of 18 94, 133 -> 79, 117; and the preparation, which does without the tables of
+  // nonzero splitting, 1340, 1260 -> 1060, 1110 (1 M of 50).  A row of theirs is padded by up to seven steps: where the streams
+  // have room for twice that.
+  const bool roomy = 7 * (short_rows + kSweepSlots) + 4096 <= (L.stream_cap - nnz) / 2;
   bool whole_rows = opt.short_rows >= 0 &&
-                    short_rows > 0 && tot.min_long <= 255 && slots == kSweepSlots && R <= 4 &&
+                    short_rows > 0 && tot.min_long <= 255 && slots == kSweepSlots && (R <= 4 || roomy) &&
                     P + short_rows <= L.max_pieces && opt.sync_slabs <= 0 && opt.barriers != 1 &&
                     opt.pace_ps_per_step <= 0;
   int64_t NWT4 = NW4;
@@ -1826,6 +1866,11 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
     short_base = (int64_t)round_up((size_t)stream_len + 64, 256);
     const bool fits = !rec.scan.overflow && short_base + short_entries_csr + 256 <= L.stream_cap;
     if (fits) break;
+    if (whole_rows && R > 4) {             // (their streams' padding did not fit: with the short rows beside the sweep)
+      sagnn_spmm_options apart = opt;
+      apart.short_rows = -1;
+      return sweep_prepare(d_rowptr, d_colidx, d_val, m, k, nnz, f, ws, L, apart, no_hubs, s, out);
+    }
     if (attempt == 1 || NI == 1) return SAGNN_OK;
     NI = 1;                                // the interval padding did not fit: lay out without it
     sync_slabs = 0;
@@ -1883,6 +1928,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   h.launch_waves = col_groups ? (int32_t)(2 * resident_waves) : 0;
   h.fused_waves = local ? h.launch_waves / 2 : 0;
   out->reuse = (float)reuse;
+  out->long_waves = (int32_t)NW4;
   out->run_blocks = local && NI == 1 ? (int32_t)std::min<int64_t>(resident_waves / 4, 1 << 20) : 0;
   // Rows of a generation from which runs pay (sweep_run): 1.3 times the rows of a neighbourhood, three times where the columns
   // go along with the rows, since the runs then begin in different slabs.  us without and with runs: 16 communities, 1 M of 42
@@ -2008,6 +2054,7 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   sd.slots = d.slots > 0 && d.slots <= kSweepSlots ? d.slots : kSweepSlots;
   sd.fw = fw;
   sd.run = sweep_run(d, fw, false);
+  sd.long_waves = d.long_waves;
   sd.turn = (fuse != 0 ? d.layer_turns : d.turns) ? turn_steps(kmax, fw) : 0;
   size_t lds = (size_t)4 * sd.slots * (sweep_lds_width(fw) + (fuse != 0 ? kPadRow : 0)) * sizeof(float);
   // (the layer: the targets behind the rows, and no more than five workgroups a CU, which 64 columns would allow: a sixth

@@ -985,6 +985,46 @@ def test_spmm_sweep_of_narrow_widths_between_the_kernels_is_closer_than_one_sum(
     assert float((got.double() - exact).norm()) < 0.6 * float((serial.double() - exact).norm())
 
 
+@pytest.mark.parametrize("f", [4, 12, 16, 20, 28, 32])
+def test_spmm_narrow_sweep_short_rows_as_whole_rows(f, monkeypatch):
+    """Eight and sixteen lane groups sweep short rows as whole rows too: rows of 1 to 63 entries and around the steps of a
+    batch, unsorted and repeated columns in them, hubs, empty rows; plain, accumulating, and with infinite rows of B, which
+    reach the rows that use them and no other (streams of a wavefront end at different steps)."""
+    monkeypatch.setenv("SAGNN_SWEEP", "1")
+    monkeypatch.setenv("SAGNN_SWEEP_PIECE", "1024")
+    monkeypatch.setenv("SAGNN_SWEEP_SLAB_MB", "0")
+    monkeypatch.setenv("SAGNN_SWEEP_MINDEG", "64")
+    monkeypatch.setenv("SAGNN_SWEEP_GROUPS", "2")     # (whatever the uses of a row of B)
+    rng = np.random.default_rng(700 + f)
+    n = 30_000
+    deg = rng.choice([0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33, 62, 63, 64, 65, 200], size=7001)
+    deg[[3, 7, 2500]] = 9000, 3000, 1025
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    colidx = rng.integers(0, n, size=rowptr[-1]).astype(np.int32)
+    for r in np.flatnonzero(deg >= 64):
+        colidx[rowptr[r]:rowptr[r + 1]].sort()
+    val = rng.uniform(0.5, 1.5, size=colidx.size).astype(np.float32)
+    B = np.abs(synth.normal((n, f), f, synth.STREAM_H)) + np.float32(0.1)
+    rp, ci, v = dev(rowptr), dev(colidx), dev(val)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    info = ws.info()
+    assert info["mode"] == 1 and info["groups"] in (8, 16) and info["chunk_rows"] == 0 and info["split_rows"] >= 3, info
+    infinite = rng.random(n) < 0.02
+    infinite[0] = True                                # what padding multiplies by 0
+    hit = np.bincount(np.repeat(np.arange(deg.size), deg)[infinite[colidx]], minlength=deg.size) > 0
+    for C0 in (None, synth.normal((deg.size, f), f + 1, synth.STREAM_G)):
+        ref, zabs = oracle.spmm(rowptr, colidx, val, B, C=C0, want_abs=True)
+        C = None if C0 is None else dev(C0)
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(B), C=C, accumulate=C0 is not None, ws=ws)
+        assert_close(got, ref, zabs, RTOL_SPMM, f"f={f}")
+        Binf = B.copy()
+        Binf[infinite] = np.inf
+        C = None if C0 is None else dev(C0)
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(Binf), C=C, accumulate=C0 is not None, ws=ws).cpu().numpy()
+        assert np.isposinf(got[hit]).all()
+        assert_close(got[~hit], ref[~hit], zabs[~hit], RTOL_SPMM, f"f={f} beside infinite rows")
+
+
 @pytest.mark.parametrize("f", [64, 128, 192, 256])
 @pytest.mark.parametrize("groups", [1, 2])
 def test_spmm_sweep_short_rows_as_whole_rows(f, groups, monkeypatch):
