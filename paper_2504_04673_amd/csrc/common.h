@@ -305,6 +305,7 @@ struct FlatArgs {
   float* C; int64_t ldc; int32_t accumulate;
   const SpmmWsHeader* hdr; uint64_t generation;
   const int4* chunks; const uint32_t* flags; float* carry; int64_t carry_ld; const int32_t* rowmap;
+  bool hubs;                           // rows that many chunks share (the back fix-up list)
 };
 // d_stat (4 ints of device memory): [0] 1 if some row is empty, [1] / [2] rows on the front / back fix-up list
 int flat_build_tables(const int32_t* d_rowptr, int64_t rows, int64_t nnz, int64_t T, char* ws, const SpmmWsLayout& L,

@@ -363,6 +363,7 @@ int launch_spmm_body(const int32_t* rowptr, const int32_t* colidx, const float* 
   fl.rows = d.m; fl.nnz = d.nnz; fl.nchunks = d.nchunks; fl.colidx = p.colidx; fl.val = p.val; fl.B = B; fl.ldb = ldb;
   fl.kmax = d.kmax; fl.C = C; fl.ldc = ldc; fl.accumulate = accumulate; fl.hdr = p.hdr; fl.generation = d.generation;
   fl.chunks = p.chunks; fl.flags = p.flags; fl.carry = p.carry; fl.carry_ld = f; fl.rowmap = p.rowmap;
+  fl.hubs = desc.n_fix_big > 0;
   if (desc.mode == 1) {
     const int32_t max_slab = desc.max_slab == 128 ? 128 : 256;
     const bool narrow = desc.col_slab > 0 && f % desc.col_slab == 0;

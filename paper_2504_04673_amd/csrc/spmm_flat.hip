@@ -31,6 +31,7 @@ struct FlatDims {
   uint64_t generation;
   uint32_t b_bytes, row_bytes, kmax;
   int32_t f, accumulate;
+  int32_t parts, part_cols, blocks;   // column parts, a share of the XCDs each (1: none), columns and workgroups of a part
 };
 
 // (no short cuts: all fields are read at once instead of one after the other)
@@ -81,9 +82,17 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
   constexpr int U = 8;                       // rows of B in flight
   const int lane = threadIdx.x & 63;
   const int lig = lane % LPE, sub = lane % UNIT;
-  const bool active = lig * 4 < d.f;
+  int32_t block = blockIdx.x, col0 = 0, width = d.f;
+  if (d.parts > 1) {                         // (workgroups go to the eight XCDs in turn; see flat_launch)
+    const int32_t xcd = block & 7, each = 8 / d.parts;     // XCDs of a part
+    col0 = xcd / each * d.part_cols;
+    width = d.f - col0 < d.part_cols ? d.f - col0 : d.part_cols;
+    block = (block >> 3) * each + xcd % each;
+    if (block >= d.blocks) return;
+  }
+  const bool active = lig * 4 < width;
   const uint32_t loff = active ? lig * 16 : 0;     // (idle lanes read the row's first piece again)
-  const int64_t wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6));
+  const int64_t wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)block * kBlock + threadIdx.x) >> 6));
   if (wave * R >= d.nchunks) return;
   const int32_t k = (int32_t)(wave * R) + lane / LPE;
   // (the header is looked at beside the chunk, not before it: a trip to memory less in a chain of four)
@@ -109,8 +118,8 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
     return rowmap ? rowmap[ii] : ii;
   };
   int32_t rid = row_at(r);
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(B, d.b_bytes);
-  const float* __restrict__ Bl = B + (active ? lig * 4 : 0);
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(B + col0, d.b_bytes - (uint32_t)col0 * 4u);
+  const float* __restrict__ Bl = B + col0 + (active ? lig * 4 : 0);
 
   vec4 acc = 0.f, part[2] = {0.f, 0.f};   // the row's sum up to this batch, and in this batch
   auto fold = [&]() {
@@ -122,9 +131,9 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
     fold();
     if (active && r <= rmax) {
       if (head) {
-        *reinterpret_cast<vec4*>(carry + (k * d.carry_ld + lig * 4)) = acc;
+        *reinterpret_cast<vec4*>(carry + (k * d.carry_ld + col0 + lig * 4)) = acc;
       } else {
-        vec4* p = reinterpret_cast<vec4*>(C + (rid * d.ldc + lig * 4));
+        vec4* p = reinterpret_cast<vec4*>(C + (rid * d.ldc + col0 + lig * 4));
         if (d.accumulate) acc += *p;
         *p = acc;
       }
@@ -448,15 +457,34 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   d.generation = a.generation; d.kmax = a.kmax; d.f = fw; d.accumulate = a.accumulate;
   d.row_bytes = (uint32_t)(a.ldb * 4);
   const bool buf = buffer_addressable(a.kmax, a.ldb, fw, &d.b_bytes);
+  d.parts = 1;
   auto go = [&](auto kern, int lpe) -> int {
     const int64_t waves = ceil_div(a.nchunks, 64 / lpe);
-    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(waves, kWaves)), dim3(kBlock), 0, s, a.colidx, a.val, a.B + col0,
+    d.blocks = (int32_t)ceil_div(waves, kWaves);
+    const int64_t grid = d.parts > 1 ? 8 * ceil_div((int64_t)d.blocks * d.parts, 8) : d.blocks;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kBlock), 0, s, a.colidx, a.val, a.B + col0,
                        a.C + col0, a.hdr, a.chunks, a.flags, a.carry + col0, a.rowmap, d);
     SAGNN_LAUNCH_CHECK();
     return SAGNN_OK;
   };
 #define SAGNN_FLAT(LPE_, NC_, FOLD_) \
   (buf ? go(spmm_flat_kernel<LPE_, NC_, FOLD_, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, FOLD_, false>, LPE_))
+  // Column parts: each on a share of the XCDs, so that an L2 has to hold that share of the rows of B only, and is asked for
+  // a line of it that many times as often; the sums are the same.  Parts of whole lines; where rows of B are used ten times or
+  // more and B is larger than two L2s, with hubs, whose rows hit in any case, than several.  Four parts without hubs at 256.
+  // us whole, in two and in four parts: random columns, 30 k vertices of 12 f = 128, 256 (31 MB) 29, 57, 25, 53 and -, 45, 20 k of
+  // 45 52, 115, 39, 96, -, 68, 10 k of 90 f = 256 (10 MB) 86, 60, 50, 60 k of 12 (61 MB) 114, 112, 105; communities, 40 k of 24 57,
+  // 125, 48, 110, -, 95; power-law 170 k of 14 f = 128, 192, 256 (174 MB) 122, 193, 256, 111, 166, 231, -, -, 238, 60 k of 30 (61 MB)
+  // 146, 122, 125; not: 10 k of 12 f = 128 (5 MB) 8.7, 8.3, power-law 30 k of 20 f = 128 (15 MB) 29, 32, 10 k of 30 f = 256 25, 28,
+  // random 200 k of 4 f = 128 78, 81; in narrower parts 60 k of 12, f = 64 31, 30, 170 k 64, 76; in parts of 13 lines or less that
+  // begin inside one, 30 k of 12 f = 100 27, 31.
+  const bool lines = (a.ldb & 31) == 0 && (reinterpret_cast<uintptr_t>(a.B + col0) & 127) == 0;
+  const int64_t b_rows = (int64_t)a.kmax + 1, floor_mb = !a.hubs ? 8 : (fw == 128 ? 48 : 30);
+  if (fw >= 128 && (fw & 63) == 0 && lines && a.nnz >= 10 * b_rows && b_rows * fw * 4 >= floor_mb << 20) {
+    d.parts = fw == 256 && !a.hubs ? 4 : 2;
+    d.part_cols = fw / d.parts;
+    return d.part_cols <= 64 ? SAGNN_FLAT(16, 2, 0) : SAGNN_FLAT(32, 2, 0);
+  }
   const bool brief = a.nnz < 64 * a.nchunks;
   // Up to 32 columns four groups of sixteen lanes a wavefront, most of them idle, where groups as narrow as a row would leave
   // SIMDs without a wavefront: with sixteen groups some row ends at nearly every step, and its wavefront stores what the

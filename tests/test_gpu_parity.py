@@ -365,6 +365,38 @@ def test_spmm_chunks_at_their_edges(f, target, monkeypatch):
     assert_close(run_spmm(rowptr, colidx, val, B, True, C0=C0), ref2, zabs2, RTOL_SPMM, f"chunks accumulate f={f}")
 
 
+@pytest.mark.parametrize("f,n,deg,hubs", [(128, 16_411, 12, 0), (192, 16_411, 17, 0), (256, 9_001, 11, 0), (256, 33_001, 20, 3), (320, 9_001, 13, 0),
+                                          (128, 100_003, 11, 2)])
+def test_spmm_chunks_in_column_parts(f, n, deg, hubs, monkeypatch):
+    """Nonzero splitting of operands that are larger than two L2s takes columns in parts: bit for bit what the same workspace
+    gives of 64 columns at a time, which are not cut.  Counts of workgroups that the XCDs of a part do not share evenly,
+    rows shared by chunks, empty rows, hubs, accumulation, an operand with gaps and one that begins inside a line."""
+    monkeypatch.setenv("SAGNN_SWEEP", "0")
+    gen = torch.Generator(device="cuda").manual_seed(f + n)
+    count = torch.randint(0, 2 * deg + 2, (n,), device="cuda", generator=gen)
+    count[5::499] = 0
+    count[:hubs] = 4000
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(count, 0)
+    nnz = int(rp[-1])
+    assert nnz >= 10 * n
+    ci = torch.randint(n, (nnz,), device="cuda", generator=gen, dtype=torch.int32)
+    v = torch.randn(nnz, device="cuda", generator=gen)
+    wide = torch.randn(n, f + 64, device="cuda", generator=gen)
+    C0 = torch.randn(n, f, device="cuda", generator=gen)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+    assert ws.info()["mode"] == 0
+    A, Aabs = (torch.sparse_csr_tensor(rp.long(), ci.long(), x.double(), (n, n)) for x in (v, v.abs()))
+    for B in (wide[:, :f].contiguous(), wide[:, :f], wide[:, 4:f + 4]):
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, B, ws=ws)
+        for c in range(0, f, 64):
+            assert torch.equal(got[:, c:c + 64], sagnn.spmm_csr_tallskinny(rp, ci, v, B[:, c:c + 64], ws=ws)), c
+        assert float(((got.double() - A @ B.double()).abs() - RTOL_SPMM * (Aabs @ B.double().abs())).max()) <= 1e-30
+        acc = sagnn.spmm_csr_tallskinny(rp, ci, v, B, C=C0.clone(), accumulate=True, ws=ws)
+        bound = RTOL_SPMM * (Aabs @ B.double().abs() + C0.double().abs())
+        assert float(((acc.double() - A @ B.double() - C0.double()).abs() - bound).max()) <= 1e-30
+
+
 @pytest.mark.parametrize("f,target", [(4, 3_000), (16, 8_500_000), (32, 400_000), (64, 600_000), (100, 300_000), (128, 300_000),
                                       (256, 270_000), (320, 60_000)])
 def test_spmm_infinities_in_rows_that_chunks_cut(f, target, monkeypatch):
