@@ -281,6 +281,21 @@ def test_csr_transpose_at_the_edges_of_the_sort_tiles(nnz, m, n):
     check_transpose(rowptr, colidx, rng.standard_normal(nnz).astype(np.float32), n)
 
 
+@pytest.mark.parametrize("nnz", [1024 + 63, 262_145, 4_194_305 + 8191])
+def test_csr_transpose_rows_that_begin_at_the_edges_of_tiles(nnz):
+    """Rows that begin at, just before and just behind tiles, wavefronts' shares of them and runs of 64 entries, each
+    after up to two empty ones, runs of empty rows at both ends, and a row that covers a whole tile."""
+    rng = np.random.default_rng(nnz)
+    starts = np.arange(0, min(nnz, 200_000), 64)
+    starts = np.concatenate([starts, starts[1:] - 1, starts + 1, np.arange(0, nnz, 8192) + rng.integers(-2, 3)])
+    starts = starts[(starts > 0) & (starts < nnz) & ((starts < 20_000) | (starts > 40_000))]
+    starts = np.sort(np.repeat(starts, rng.integers(1, 4, size=starts.size)))
+    rowptr = np.concatenate([np.zeros(70, np.int64), starts, np.full(70, nnz)]).astype(np.int32)
+    n = 3000
+    colidx = rng.integers(0, n, size=nnz).astype(np.int32)
+    check_transpose(rowptr, colidx, rng.standard_normal(nnz).astype(np.float32), n)
+
+
 def test_directed_graph_layer_uses_both_orientations():
     """Directed graph: the forward product runs on A^T (Sec. 2.1 forward equation), the backward
     product on A.  A^T comes from the device transpose; both layer calls against the oracle."""
