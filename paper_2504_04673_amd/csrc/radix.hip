@@ -7,6 +7,7 @@
 //   scan     one workgroup per digit: exclusive scan along the tiles, digit total
 //   scatter  ranks inside the tile by ballots (stable), the tile is sorted by digit in LDS and then
 //            written out in that order, so that neighbouring lanes store to neighbouring places
+// Up to kFewTiles tiles there is no scan: counts[tile][digit], and a tile adds up the others' counts by itself.
 // What bounds it: HBM.  A pass reads and writes every key and payload word once and reads the keys once
 // more for the counts.  The earlier form (one wavefront per tile, a serial loop over the distinct digits
 // of 64 keys, stores in entry order) took 14.4 ms for seven passes over 21 M pairs, almost all of it in
@@ -29,6 +30,11 @@ constexpr int kMaxBins = 256;
 constexpr int64_t kTileSmallMax = 1 << 18;   // up to here: tiles of 1024 pairs
 constexpr int64_t kTileMidMax = 1 << 22;     // up to here: tiles of 2048 pairs
 
+// Sorts of few tiles are bound by their launches, and the scan is one of three.  (A tile reads all counts, ntiles lines of
+// 1 KB.  A pass over 33 k pairs: scan and scatter 3.4 + 5.8 us, now 6.0; over 100 k, 4.2 + 6.5 and 10.6, one launch fewer;
+// the reads grow with the tiles, the scan does not.)
+constexpr int64_t kFewTiles = 128;
+
 inline int radix_tile(int64_t n) { return n <= kTileSmallMax ? 1024 : (n <= kTileMidMax ? 2048 : 8192); }
 
 struct PassArgs {
@@ -38,7 +44,7 @@ struct PassArgs {
   uint32_t *keys_out, *p0_out, *p1_out;
   int64_t n, ntiles;
   int32_t shift, bits;
-  int32_t* counts;            // [bins][ntiles]
+  int32_t* counts;            // [bins][ntiles], few tiles: [ntiles][bins]
   int32_t* totals;            // [bins]
   const int32_t* rowptr;      // SRC_ROWS: the first payload word is the row of the entry
   int64_t m;
@@ -47,7 +53,7 @@ struct PassArgs {
 enum Src { SRC_ARRAYS = 0, SRC_INDEX = 1, SRC_ROWS = 2 };
 
 // limit > 0: err[0] = 1 if some key is >= limit
-template <int THREADS, int KPT>
+template <int THREADS, int KPT, bool FEW>
 __global__ __launch_bounds__(THREADS) void radix_count_kernel(const uint32_t* __restrict__ keys, int64_t n,
                                                               int64_t ntiles, int32_t shift, int32_t bits,
                                                               int32_t* __restrict__ counts, uint32_t limit,
@@ -69,7 +75,8 @@ __global__ __launch_bounds__(THREADS) void radix_count_kernel(const uint32_t* __
     }
   if (bad) err[0] = 1;
   __syncthreads();
-  for (int i = threadIdx.x; i < bins; i += THREADS) counts[(int64_t)i * ntiles + blockIdx.x] = hist[i];
+  for (int i = threadIdx.x; i < bins; i += THREADS)
+    counts[FEW ? (int64_t)blockIdx.x * bins + i : (int64_t)i * ntiles + blockIdx.x] = hist[i];
 }
 
 // exclusive scan of one value per thread over the workgroup; *total = sum
@@ -133,7 +140,7 @@ __device__ __forceinline__ int64_t wave_find_row(const int32_t* __restrict__ row
   return lo;
 }
 
-template <int THREADS, int KPT, int NP, int SRC>
+template <int THREADS, int KPT, int NP, int SRC, bool FEW>
 __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a) {
   constexpr int TILE = THREADS * KPT, WAVES = THREADS / 64;
   __shared__ uint32_t stage[TILE];
@@ -150,6 +157,22 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
   uint32_t key[KPT];
 #pragma unroll
   for (int j = 0; j < KPT; ++j) key[j] = seg + j * 64 < cnt ? a.keys_in[tile0 + seg + j * 64] : 0u;
+  int32_t digit_total = 0, digit_before = 0;       // pairs of digit `tid` in all tiles, in the tiles before this one
+  if constexpr (FEW) {
+    if (tid < bins) {
+#pragma unroll 16
+      for (int t = 0; t < (int)a.ntiles; ++t) {
+        const int32_t v = a.counts[t * bins + tid];
+        digit_total += v;
+        digit_before += t < (int)blockIdx.x ? v : 0;
+      }
+    }
+  } else {
+    if (tid < bins) {
+      digit_total = a.totals[tid];
+      digit_before = a.counts[(int64_t)tid * a.ntiles + blockIdx.x];
+    }
+  }
   __syncthreads();
 
   // rank of every pair among the wavefront's earlier pairs of its digit
@@ -183,9 +206,9 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
     }
     int32_t tot, dtot;
     const int32_t start = block_scan<THREADS>(mine, wsum, &tot);
-    const int32_t before = block_scan<THREADS>(d < bins ? a.totals[d] : 0, wsum, &dtot);
+    const int32_t before = block_scan<THREADS>(digit_total, wsum, &dtot);
     if (d < bins) {
-      gbase[d] = before + a.counts[(int64_t)d * a.ntiles + blockIdx.x] - start;
+      gbase[d] = before + digit_before - start;
       int32_t run = start;
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) {
@@ -279,18 +302,21 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
   }
 }
 
-template <int THREADS, int KPT>
+template <int THREADS, int KPT, bool FEW>
 int run_pass(const PassArgs& a, int np, int src, uint32_t limit, int32_t* err, hipStream_t s) {
   const dim3 grid((unsigned)a.ntiles);
-  hipLaunchKernelGGL((radix_count_kernel<THREADS, KPT>), grid, dim3(THREADS), 0, s, a.keys_in, a.n, a.ntiles, a.shift,
+  hipLaunchKernelGGL((radix_count_kernel<THREADS, KPT, FEW>), grid, dim3(THREADS), 0, s, a.keys_in, a.n, a.ntiles, a.shift,
                      a.bits, a.counts, limit, err);
   SAGNN_LAUNCH_CHECK();
-  hipLaunchKernelGGL(radix_scan_kernel, dim3(1u << a.bits), dim3(1024), 0, s, a.counts, a.ntiles, a.totals);
-  SAGNN_LAUNCH_CHECK();
-  if (src == SRC_ROWS) hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 2, SRC_ROWS>), grid, dim3(THREADS), 0, s, a);
-  else if (src == SRC_INDEX) hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 1, SRC_INDEX>), grid, dim3(THREADS), 0, s, a);
-  else if (np == 2) hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 2, SRC_ARRAYS>), grid, dim3(THREADS), 0, s, a);
-  else hipLaunchKernelGGL((radix_scatter_kernel<THREADS, KPT, 1, SRC_ARRAYS>), grid, dim3(THREADS), 0, s, a);
+  if (!FEW) {
+    hipLaunchKernelGGL(radix_scan_kernel, dim3(1u << a.bits), dim3(1024), 0, s, a.counts, a.ntiles, a.totals);
+    SAGNN_LAUNCH_CHECK();
+  }
+  const auto scatter = src == SRC_ROWS    ? radix_scatter_kernel<THREADS, KPT, 2, SRC_ROWS, FEW>
+                       : src == SRC_INDEX ? radix_scatter_kernel<THREADS, KPT, 1, SRC_INDEX, FEW>
+                       : np == 2          ? radix_scatter_kernel<THREADS, KPT, 2, SRC_ARRAYS, FEW>
+                                          : radix_scatter_kernel<THREADS, KPT, 1, SRC_ARRAYS, FEW>;
+  hipLaunchKernelGGL(scatter, grid, dim3(THREADS), 0, s, a);
   SAGNN_LAUNCH_CHECK();
   return SAGNN_OK;
 }
@@ -298,9 +324,12 @@ int run_pass(const PassArgs& a, int np, int src, uint32_t limit, int32_t* err, h
 int run_pass(PassArgs a, int np, int src, uint32_t limit, int32_t* err, hipStream_t s) {
   const int tile = radix_tile(a.n);
   a.ntiles = ceil_div(a.n, tile);
-  if (tile == 1024) return run_pass<256, 4>(a, np, src, limit, err, s);
-  if (tile == 2048) return run_pass<256, 8>(a, np, src, limit, err, s);
-  return run_pass<512, 16>(a, np, src, limit, err, s);
+  if (tile == 1024) {
+    return a.ntiles <= kFewTiles ? run_pass<256, 4, true>(a, np, src, limit, err, s)
+                                 : run_pass<256, 4, false>(a, np, src, limit, err, s);
+  }
+  if (tile == 2048) return run_pass<256, 8, false>(a, np, src, limit, err, s);
+  return run_pass<512, 16, false>(a, np, src, limit, err, s);
 }
 
 inline int passes_of(int bits) { return (bits + 7) / 8; }

@@ -281,10 +281,11 @@ def test_csr_transpose_at_the_edges_of_the_sort_tiles(nnz, m, n):
     check_transpose(rowptr, colidx, rng.standard_normal(nnz).astype(np.float32), n)
 
 
-@pytest.mark.parametrize("nnz", [1024 + 63, 262_145, 4_194_305 + 8191])
+@pytest.mark.parametrize("nnz", [1024 + 63, 131_072, 131_073, 262_145, 4_194_305 + 8191])
 def test_csr_transpose_rows_that_begin_at_the_edges_of_tiles(nnz):
     """Rows that begin at, just before and just behind tiles, wavefronts' shares of them and runs of 64 entries, each
-    after up to two empty ones, runs of empty rows at both ends, and a row that covers a whole tile."""
+    after up to two empty ones, runs of empty rows at both ends, and a row that covers a whole tile.  (Tiles with and
+    without a scan of their counts: 128 tiles, one more.)"""
     rng = np.random.default_rng(nnz)
     starts = np.arange(0, min(nnz, 200_000), 64)
     starts = np.concatenate([starts, starts[1:] - 1, starts + 1, np.arange(0, nnz, 8192) + rng.integers(-2, 3)])
