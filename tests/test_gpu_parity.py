@@ -1208,6 +1208,24 @@ def test_spmm_sweep_planner_balances_streams(f, monkeypatch):
     assert_close(got[torch.from_numpy(rows).cuda()], ref, zabs, RTOL_SPMM, f"balanced planner f={f}")
 
 
+@pytest.mark.parametrize("groups", [1, 2])
+@pytest.mark.parametrize("min_waves", [1, 16])
+def test_spmm_sweep_planner_deals_few_pieces(groups, min_waves, force_sweep, monkeypatch):
+    """The batches that meet empty streams are dealt without a sort: two and three wavefronts' streams with about as many
+    pieces as they have slots, one or four streams a wavefront."""
+    monkeypatch.setenv("SAGNN_SWEEP_GROUPS", str(groups))
+    monkeypatch.setenv("SAGNN_SWEEP_MIN_WAVES", str(min_waves))
+    monkeypatch.setenv("SAGNN_SWEEP_SHORT_ROWS", "-1")
+    f, n = 64, 5000
+    B = synth.normal((n, f), 3, synth.STREAM_H)
+    for rows in (31, 32, 33, 47, 48, 49, 64, 65, 513):
+        rng = np.random.default_rng(rows)
+        rowptr, colidx, val = random_csr(rows, n, 0, rng, hubs=[(r, 64 + int(rng.integers(0, 200))) for r in range(rows)])
+        ref, zabs = oracle.spmm(rowptr, colidx, val, B, want_abs=True)
+        got = run_spmm(rowptr, colidx, val, B, True, expect_mode=1)
+        assert_close(got, ref, zabs, RTOL_SPMM, f"{rows} long rows, {groups}")
+
+
 @pytest.mark.parametrize("f", [192, 256, 320])
 def test_spmm_sweep_wide_operand_as_128_wide_slabs(f, force_sweep, monkeypatch):
     """Operands wider than 128 taken as 128-wide column slabs (plus a 64-wide rest) by the kernels
