@@ -196,25 +196,33 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const int32_t* __restric
 // columns, a workgroup instead ORs the bits of its share of the entries into a private LDS
 // bitmap of one column range (pass), reading colidx once per pass as a stream, and writes
 // the bitmap out; merge_kernel ORs the private bitmaps into the membership words.
-__device__ __forceinline__ void lds_mark_one(int32_t c, int64_t n, int64_t c0, uint32_t* bits,
-                                             int32_t* __restrict__ err) {
-  if (c < 0 || c >= n) {
-    err[1] = 1;
-    return;
+// c0, cols: the range; a column outside [0, n) lies in no range.  Test first: lanes that read one
+// address are served by a broadcast, lanes that update one address are serialised, and hub columns
+// come up thousands of times.  The words of all N entries are read before the first is tested
+// (entry by entry the reads wait for each other).
+template <int N>
+__device__ __forceinline__ void lds_mark(const int32_t (&c)[N], uint32_t c0, uint32_t cols, uint32_t* bits) {
+  uint32_t rel[N], word[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    rel[i] = (uint32_t)c[i] - c0;
+    word[i] = __hip_atomic_load(&bits[rel[i] < cols ? rel[i] >> 5 : 0u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  const int64_t rel = (int64_t)c - c0;
-  if (rel >= 0 && rel < kLdsCols) {
-    // test first: lanes that read one address are served by a broadcast, lanes that update one
-    // address are serialised, and hub columns come up thousands of times
-    const uint32_t bit = 1u << (rel & 31);
-    if ((__hip_atomic_load(&bits[rel >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) == 0)
-      __hip_atomic_fetch_or(&bits[rel >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (rel[i] < cols && ((word[i] >> (rel[i] & 31)) & 1u) == 0u)
+      __hip_atomic_fetch_or(&bits[rel[i] >> 5], 1u << (rel[i] & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// `spec` (may be NULL): the workgroups of the first column range also write the range-checked
-// copy of colidx that the remap is if every column turns out to be needed (a whole graph planned
-// as one block): the entries are in registers anyway, and the separate copy pass is then skipped.
+// `spec` (may be NULL): also write the range-checked copy of colidx that the remap is if every
+// column turns out to be needed (a whole graph planned as one block): the entries are in registers
+// anyway, and the separate copy pass is then skipped.  The workgroups of the column ranges take
+// turns at that and at the check of the range, so that those of one share, which lie on one XCD
+// for two and four ranges, go through the entries together and the second read finds them in its
+// L2.  The next sixteen entries of a thread are requested before the present ones are marked.
+// Bound by HBM: 125 M entries, 2.45 M columns, one read and one write of 500 MB; 267 us with all
+// copies made by the workgroups of the first range and nothing requested ahead, now 242 (the copy
+// past the caches 268); 5 M entries over 123 k columns 20, now 16.
 __device__ __forceinline__ int32_t identity_or_bad(int32_t c, int64_t n) { return (c < 0 || c >= n) ? -1 : c; }
 
 __global__ __launch_bounds__(kLdsThreads) void mark_lds_kernel(const int32_t* __restrict__ colidx,
@@ -227,65 +235,76 @@ __global__ __launch_bounds__(kLdsThreads) void mark_lds_kernel(const int32_t* __
   extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
   if (blockIdx.x == 0)   // (merge_kernel adds to them)
     for (int64_t i = threadIdx.x; i < nblk; i += kLdsThreads) blocksum[i] = 0;
-  const int pass = blockIdx.x / groups_per_pass, share = blockIdx.x % groups_per_pass;
-  if (pass != 0) spec = nullptr;
+  const int pass = blockIdx.x / groups_per_pass, share = blockIdx.x % groups_per_pass, passes = gridDim.x / groups_per_pass;
   const int64_t c0 = (int64_t)pass * kLdsCols;
+  const uint32_t c0w = (uint32_t)c0, cols = (uint32_t)(n - c0 < kLdsCols ? n - c0 : kLdsCols);
   uint4* b4 = reinterpret_cast<uint4*>(bits);
   for (int i = threadIdx.x; i < kLdsWords / 4; i += kLdsThreads) b4[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
+  bool bad = false;
+  auto copy4 = [&](const int4& c, int64_t q) {
+    const int4 d = make_int4(identity_or_bad(c.x, n), identity_or_bad(c.y, n), identity_or_bad(c.z, n), identity_or_bad(c.w, n));
+    bad |= (d.x | d.y | d.z | d.w) < 0;
+    if (spec) reinterpret_cast<int4*>(spec)[q] = d;
+  };
   if (aligned) {
     const int64_t quads = nnz >> 2;
     const int64_t per = ceil_div_dev(quads, groups_per_pass);
     const int64_t q0 = (int64_t)share * per;
     const int64_t q1 = q0 + per < quads ? q0 + per : quads;
     const int4* __restrict__ c4 = reinterpret_cast<const int4*>(colidx);
-    // four independent 16-byte loads per thread in flight (the scan is a pure stream)
-    int64_t q = q0 + threadIdx.x;
-    for (; q + 3 * kLdsThreads < q1; q += 4 * kLdsThreads) {
-      int4 c[4];
+    int turn = pass;                       // 0: this workgroup copies
+    int64_t q = q0;
+    int4 c[4];
+    if (q + 4 * kLdsThreads <= q1) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) c[j] = c4[q + j * kLdsThreads];
-      if (spec) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          reinterpret_cast<int4*>(spec)[q + j * kLdsThreads] =
-              make_int4(identity_or_bad(c[j].x, n), identity_or_bad(c[j].y, n), identity_or_bad(c[j].z, n),
-                        identity_or_bad(c[j].w, n));
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        lds_mark_one(c[j].x, n, c0, bits, err);
-        lds_mark_one(c[j].y, n, c0, bits, err);
-        lds_mark_one(c[j].z, n, c0, bits, err);
-        lds_mark_one(c[j].w, n, c0, bits, err);
-      }
+      for (int j = 0; j < 4; ++j) c[j] = c4[q + j * kLdsThreads + threadIdx.x];
     }
-    for (; q < q1; q += kLdsThreads) {
-      const int4 c = c4[q];
-      if (spec)
-        reinterpret_cast<int4*>(spec)[q] = make_int4(identity_or_bad(c.x, n), identity_or_bad(c.y, n),
-                                                     identity_or_bad(c.z, n), identity_or_bad(c.w, n));
-      lds_mark_one(c.x, n, c0, bits, err);
-      lds_mark_one(c.y, n, c0, bits, err);
-      lds_mark_one(c.z, n, c0, bits, err);
-      lds_mark_one(c.w, n, c0, bits, err);
+    for (; q + 4 * kLdsThreads <= q1; q += 4 * kLdsThreads) {
+      int4 next[4] = {};
+      const int64_t qn = q + 4 * kLdsThreads;
+      if (qn + 4 * kLdsThreads <= q1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) next[j] = c4[qn + j * kLdsThreads + threadIdx.x];
+      }
+      if (turn == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) copy4(c[j], q + j * kLdsThreads + threadIdx.x);
+      }
+      turn = turn == 0 ? passes - 1 : turn - 1;
+      const int32_t all[16] = {c[0].x, c[0].y, c[0].z, c[0].w, c[1].x, c[1].y, c[1].z, c[1].w,
+                               c[2].x, c[2].y, c[2].z, c[2].w, c[3].x, c[3].y, c[3].z, c[3].w};
+      lds_mark(all, c0w, cols, bits);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = next[j];
+    }
+    for (q += threadIdx.x; q < q1; q += kLdsThreads) {
+      const int4 t = c4[q];
+      if (turn == 0) copy4(t, q);
+      const int32_t all[4] = {t.x, t.y, t.z, t.w};
+      lds_mark(all, c0w, cols, bits);
     }
     if (share == 0)
       for (int64_t e = (quads << 2) + threadIdx.x; e < nnz; e += kLdsThreads) {
-        const int32_t c = colidx[e];
-        if (spec) spec[e] = identity_or_bad(c, n);
-        lds_mark_one(c, n, c0, bits, err);
+        const int32_t t = colidx[e];
+        bad |= identity_or_bad(t, n) < 0;
+        if (spec && pass == 0) spec[e] = identity_or_bad(t, n);
+        const int32_t one[1] = {t};
+        lds_mark(one, c0w, cols, bits);
       }
   } else {
     const int64_t per = ceil_div_dev(nnz, groups_per_pass);
     const int64_t e0 = (int64_t)share * per;
     const int64_t e1 = e0 + per < nnz ? e0 + per : nnz;
     for (int64_t e = e0 + threadIdx.x; e < e1; e += kLdsThreads) {
-      const int32_t c = colidx[e];
-      if (spec) spec[e] = identity_or_bad(c, n);
-      lds_mark_one(c, n, c0, bits, err);
+      const int32_t t = colidx[e];
+      bad |= identity_or_bad(t, n) < 0;
+      if (spec && pass == 0) spec[e] = identity_or_bad(t, n);
+      const int32_t one[1] = {t};
+      lds_mark(one, c0w, cols, bits);
     }
   }
+  if (bad) err[1] = 1;
   __syncthreads();
   // only the words that cover columns below n are ever read back
   const int64_t cols_here = n - c0 < kLdsCols ? n - c0 : kLdsCols;

@@ -264,6 +264,28 @@ def test_plan_large_entry_counts_lds_marking(n, nnz, misalign):
     assert ei.value.code == -3
 
 
+@pytest.mark.parametrize("n,nnz", [(1_245_185, 10_000_003), (2_500_000, 20_000_000)])
+def test_plan_identity_written_by_several_column_ranges(n, nnz):
+    """Every column of two and of three ranges is needed: their workgroups take turns at the copy of the columns and at the
+    check of their range, in runs of 16384 entries and what is left of a share."""
+    rng = np.random.default_rng(n)
+    cols = np.concatenate([np.arange(n), rng.integers(0, n, size=nnz - n)]).astype(np.int32)
+    rng.shuffle(cols)
+    rowptr = np.linspace(0, nnz, 4001).astype(np.int32)
+    ci, rp = dev(cols), dev(rowptr)
+    plan = sagnn.spmm_plan_needed_rows(rp, ci, n, np.array([0, n], dtype=np.int64), validate=True)
+    assert plan.N == n and torch.equal(plan.colidx_compact[:nnz], ci)
+    per = -(-(nnz // 4) // (256 // -(-n // 1_245_184))) * 4      # entries of a share
+    for at in (0, 16_384, 2 * 16_384 + 1, per - 1, per, per + 40_000, nnz // 4 * 4 - 1, nnz - 1):
+        for bad in (n, -1):
+            keep = int(ci[at])
+            ci[at] = bad
+            with pytest.raises(sagnn.SagnnError) as ei:
+                sagnn.spmm_plan_needed_rows(rp, ci, n, np.array([0, n], dtype=np.int64), validate=True)
+            assert ei.value.code == -3, (at, bad)
+            ci[at] = keep
+
+
 def test_plan_empty_matrix_and_capacity_and_validate():
     rp = np.zeros(6, np.int32)
     plan = sagnn.spmm_plan_needed_rows(dev(rp), torch.empty(0, dtype=torch.int32, device="cuda"), 100,
