@@ -31,7 +31,7 @@ struct FlatDims {
   uint64_t generation;
   uint32_t b_bytes, row_bytes, kmax;
   int32_t f, accumulate;
-  int32_t parts, part_cols, blocks;   // column parts, a share of the XCDs each (1: none), columns and workgroups of a part
+  int32_t parts, part_cols, blocks;   // PARTS: column parts, a share of the XCDs each, columns and workgroups of a part
 };
 
 // (no short cuts: all fields are read at once instead of one after the other)
@@ -73,7 +73,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // per SIMD instead of seven).  30 k rows x 12, training 140.0 -> 140.3 us; 1 M x 50, f = 16, training 2278 -> 2286;
 // 4 k rows x 8, f = 16, this kernel 10.5 -> 11.2.  One sum per batch at f <= 16: 10.8 us, but 7.6e-8 on the rows of 60; four
 // sums through the whole row: 11.4 us and 7.5e-8.
-template <int LPE, int NC, int FOLD, bool BUF>
+// PARTS: column parts (see flat_launch; in kernels of their own, the others' were 2 to 4 % slower with them, 30 k x 12, f = 64
+// 14.9 and 15.3 us).
+template <int LPE, int NC, int FOLD, bool PARTS, bool BUF>
 __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, const FlatDims d) {
   constexpr bool QUAD = LPE < 16;
   constexpr int R = 64 / LPE;                // groups (chunks) per wavefront
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
   const int lane = threadIdx.x & 63;
   const int lig = lane % LPE, sub = lane % UNIT;
   int32_t block = blockIdx.x, col0 = 0, width = d.f;
-  if (d.parts > 1) {                         // (workgroups go to the eight XCDs in turn; see flat_launch)
+  if constexpr (PARTS) {                     // (workgroups go to the eight XCDs in turn; see flat_launch)
     const int32_t xcd = block & 7, each = 8 / d.parts;     // XCDs of a part
     col0 = xcd / each * d.part_cols;
     width = d.f - col0 < d.part_cols ? d.f - col0 : d.part_cols;
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
     return rowmap ? rowmap[ii] : ii;
   };
   int32_t rid = row_at(r);
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(B + col0, d.b_bytes - (uint32_t)col0 * 4u);
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(B + col0, d.b_bytes - (PARTS ? (uint32_t)col0 * 4u : 0u));
   const float* __restrict__ Bl = B + col0 + (active ? lig * 4 : 0);
 
   vec4 acc = 0.f, part[2] = {0.f, 0.f};   // the row's sum up to this batch, and in this batch
@@ -468,7 +470,9 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
     return SAGNN_OK;
   };
 #define SAGNN_FLAT(LPE_, NC_, FOLD_) \
-  (buf ? go(spmm_flat_kernel<LPE_, NC_, FOLD_, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, FOLD_, false>, LPE_))
+  (buf ? go(spmm_flat_kernel<LPE_, NC_, FOLD_, false, true>, LPE_) : go(spmm_flat_kernel<LPE_, NC_, FOLD_, false, false>, LPE_))
+#define SAGNN_FLAT_PARTS(LPE_) \
+  (buf ? go(spmm_flat_kernel<LPE_, 2, 0, true, true>, LPE_) : go(spmm_flat_kernel<LPE_, 2, 0, true, false>, LPE_))
   // Column parts: each on a share of the XCDs, so that an L2 has to hold that share of the rows of B only, and is asked for
   // a line of it that many times as often; the sums are the same.  Parts of whole lines; where rows of B are used ten times or
   // more and B is larger than two L2s, with hubs, whose rows hit in any case, than several.  Four parts without hubs at 256.
@@ -483,7 +487,7 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   if (fw >= 128 && (fw & 63) == 0 && lines && a.nnz >= 10 * b_rows && b_rows * fw * 4 >= floor_mb << 20) {
     d.parts = fw == 256 && !a.hubs ? 4 : 2;
     d.part_cols = fw / d.parts;
-    return d.part_cols <= 64 ? SAGNN_FLAT(16, 2, 0) : SAGNN_FLAT(32, 2, 0);
+    return d.part_cols <= 64 ? SAGNN_FLAT_PARTS(16) : SAGNN_FLAT_PARTS(32);
   }
   const bool brief = a.nnz < 64 * a.nchunks;
   // Up to 32 columns four groups of sixteen lanes a wavefront, most of them idle, where groups as narrow as a row would leave
@@ -502,6 +506,7 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   if (fw == 128) return SAGNN_FLAT(32, 2, 0);
   return SAGNN_FLAT(64, 2, 0);
 #undef SAGNN_FLAT
+#undef SAGNN_FLAT_PARTS
 }
 
 int flat_fixup(const FlatArgs& a, const int2* list, int64_t list_cap, int64_t n_small, int64_t n_big, int32_t f_total,
