@@ -114,12 +114,14 @@ constexpr int kSearchPieces = 4;   // rows cut into more pieces are searched: re
 // order, then a kernel of its own, 194 + 614 us, now 216; the building pass 1010 us, now 535; by place, with an entry's
 // predecessor taken from the neighbouring lane instead of memory, 260, now 240.  CHECK: *unsorted = 1 if a row's columns do not
 // ascend or leave [0, kmax].
+// kept (may be NULL): lo as the counting pass leaves it for the building pass, which then reads no columns for it (the layout
+// of 40 M entries over four streams 240 -> 187 us).
 template <bool CHECK>
 __device__ __forceinline__ void build_tables(const int32_t* __restrict__ rowptr,
                                              const int32_t* __restrict__ colidx,
                                              const int32_t* __restrict__ piece_info, int64_t w, int S,
                                              int32_t slab_width, uint32_t kmax, int R, int SL,
-                                             BuildPieces& pc, const BuildTables& T, int32_t* __restrict__ unsorted) {
+                                             BuildPieces& pc, const BuildTables& T, int32_t* __restrict__ unsorted, int4* __restrict__ kept) {
   const int tid = threadIdx.x;
   if (tid < kSweepSlots) {
     const int32_t row = piece_info[2 * (w * kSweepSlots + tid)];
@@ -136,15 +138,19 @@ __device__ __forceinline__ void build_tables(const int32_t* __restrict__ rowptr,
     if (searched) pc.hub[__popc(hubs & ((1u << tid) - 1u))] = tid;
     if (tid == 0) pc.n_hub = __popc(hubs);
   }
+  const bool scan = CHECK || kept == nullptr;
+  if (!scan)
+    for (int idx = tid; idx < kSweepSlots / 4 * (S + 1); idx += kBuildThreads) reinterpret_cast<int4*>(T.lo)[idx] = kept[idx];
   __syncthreads();
-  for (int idx = tid; idx < kSweepSlots * (S + 1); idx += kBuildThreads) {
-    const int slot = idx / (S + 1), s = idx - slot * (S + 1);
-    T.LO(slot, s) = s == 0 ? 0 : pc.deg[slot];
-  }
+  if (scan)
+    for (int idx = tid; idx < kSweepSlots * (S + 1); idx += kBuildThreads) {
+      const int slot = idx / (S + 1), s = idx - slot * (S + 1);
+      T.LO(slot, s) = s == 0 ? 0 : pc.deg[slot];
+    }
   __syncthreads();
   const float inv = 1.0f / (float)slab_width;
   bool bad = false;
-  const int32_t total = pc.pre[kSweepSlots];
+  const int32_t total = scan ? pc.pre[kSweepSlots] : 0;
   for (int32_t e0 = tid; e0 < total; e0 += 4 * kBuildThreads) {
     int slot[4];
     int32_t i[4];
@@ -175,7 +181,7 @@ __device__ __forceinline__ void build_tables(const int32_t* __restrict__ rowptr,
   // rows cut into many pieces: all (row, slab) pairs side by side, four searches in flight per thread (row by row, with
   // the slabs side by side, the sixteen chains followed each other; 40 M entries: counting 152 -> 136 us, layout
   // 440 -> 423)
-  const int n_hub = S > 1 ? pc.n_hub : 0;
+  const int n_hub = scan && S > 1 ? pc.n_hub : 0;
   if (CHECK) {   // every piece looks at its own entries
     for (int h = 0; h < n_hub; ++h) {
       const int slot = pc.hub[h];
@@ -217,6 +223,8 @@ __device__ __forceinline__ void build_tables(const int32_t* __restrict__ rowptr,
   }
   if (CHECK && bad) *unsorted = 1;
   __syncthreads();
+  if (CHECK && kept)
+    for (int idx = tid; idx < kSweepSlots / 4 * (S + 1); idx += kBuildThreads) kept[idx] = reinterpret_cast<const int4*>(T.lo)[idx];
   // entries of segment (s, slot); then per slab the prefix over the slots of each group
   for (int idx = tid; idx < S * kSweepSlots; idx += kBuildThreads) {
     const int s = idx / kSweepSlots, slot = idx - s * kSweepSlots;
@@ -238,6 +246,17 @@ __device__ __forceinline__ void build_tables(const int32_t* __restrict__ rowptr,
   __syncthreads();
 }
 
+// Where the counting pass keeps the first entries of wavefront w's segments: at the ends of the two stream arrays, which are laid
+// out afterwards, even wavefronts at the one's and odd ones at the other's.  from: the first of these words, a multiple of 64
+// (negative: nothing is kept).
+struct KeptTables {
+  int32_t *code, *vals;
+  int64_t from;
+  __device__ int4* of(int64_t w, int S) const {
+    return from < 0 ? nullptr : reinterpret_cast<int4*>((w & 1 ? vals : code) + from + (w >> 1) * (kSweepSlots * (S + 1)));
+  }
+};
+
 __device__ __forceinline__ BuildTables carve_tables(int32_t* lds, int S) {
   BuildTables T;
   T.SS = S;
@@ -256,14 +275,14 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_count_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const int32_t* __restrict__ piece_info, int32_t n_slabs, int32_t slab_width, uint32_t kmax,
     int32_t groups, int32_t slots_per_group, int32_t n_intervals, int32_t sync_slabs,
-    int32_t* __restrict__ sync_off, int32_t* __restrict__ wave_steps, int32_t* __restrict__ unsorted) {
+    int32_t* __restrict__ sync_off, int32_t* __restrict__ wave_steps, int32_t* __restrict__ unsorted, const KeptTables kept) {
   extern __shared__ __attribute__((aligned(16))) int32_t build_lds[];
   __shared__ BuildPieces pc;
   __shared__ int32_t ivl_len[kSweepMaxIntervals];
   const int64_t w = blockIdx.x;
   const int S = n_slabs, R = groups;
   const BuildTables T = carve_tables(build_lds, S);
-  build_tables<true>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, slots_per_group, pc, T, unsorted);
+  build_tables<true>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, slots_per_group, pc, T, unsorted, kept.of(w, S));
   const int per = sync_slabs > 0 ? sync_slabs : S;
   const int lane = threadIdx.x & 63;
   int32_t* so = sync_off + w * (kSweepMaxIntervals + 1);
@@ -381,7 +400,7 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
     const float* __restrict__ val, const int32_t* __restrict__ piece_info,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ sync_off, int32_t n_slabs,
     int32_t slab_width, uint32_t kmax, int32_t groups, int32_t slots_per_group, int32_t n_intervals,
-    int32_t sync_slabs, uint32_t* __restrict__ code, float* __restrict__ vals) {
+    int32_t sync_slabs, uint32_t* __restrict__ code, float* __restrict__ vals, const KeptTables kept) {
   extern __shared__ __attribute__((aligned(16))) int32_t build_lds[];
   __shared__ BuildPieces pc;
   const int64_t w = blockIdx.x;
@@ -389,7 +408,7 @@ __global__ __launch_bounds__(kBuildThreads) void sweep_build_kernel(
   const int S = n_slabs, R = groups, SL = slots_per_group;
   const BuildTables T = carve_tables(build_lds, S);
   int32_t* slab_base_ = T.slab_tot + S * kSweepSlots;          // [16][S]: first step of slab s of group g at g S + s
-  build_tables<false>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, SL, pc, T, nullptr);
+  build_tables<false>(rowptr, colidx, piece_info, w, S, slab_width, kmax, R, SL, pc, T, nullptr, kept.of(w, S));
   const int per = sync_slabs > 0 ? sync_slabs : S;
   const int32_t* __restrict__ so = sync_off + w * (kSweepMaxIntervals + 1);
   const int64_t base = wave_base[w];
@@ -1860,11 +1879,14 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   const auto build = R >= 4 && !local ? sweep_build_kernel<true> : sweep_build_kernel<false>;
   SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(build),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)build_lds));
+  KeptTables kept{reinterpret_cast<int32_t*>(ws + L.code), reinterpret_cast<int32_t*>(ws + L.vals),
+                  (L.stream_cap - ceil_div(NW4, 2) * kSweepSlots * (S + 1)) / 64 * 64};
+  if (L.stream_cap < ceil_div(NW4, 2) * kSweepSlots * (S + 1)) kept.from = -1;
   int64_t stream_len = 0, short_base = 0;
   for (int attempt = 0; attempt < 2; ++attempt) {
     hipLaunchKernelGGL(sweep_count_kernel, dim3((unsigned)NW4), dim3(kBuildThreads), count_lds, s, d_rowptr,
                        d_colidx, d_info, (int32_t)S, (int32_t)width, kmax, (int32_t)R, (int32_t)SL, (int32_t)NI,
-                       (int32_t)sync_slabs, d_sync_off, d_wave_steps, d_flag);
+                       (int32_t)sync_slabs, d_sync_off, d_wave_steps, d_flag, kept);
     SAGNN_LAUNCH_CHECK();
     if (NWT4 > NW4) {
       hipLaunchKernelGGL(sweep_short_count_kernel, dim3((unsigned)ceil_div(NWT4 - NW4, kBuildThreads / kSweepSlots)),
@@ -1896,10 +1918,11 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
                        reinterpret_cast<float*>(ws + L.sched));
     SAGNN_LAUNCH_CHECK();
   }
+  if (stream_len > kept.from) kept.from = -1;   // (the streams take the place of the tables)
   hipLaunchKernelGGL(build, dim3((unsigned)NW4), dim3(kBuildThreads), build_lds, s, d_rowptr,
                      d_colidx, d_val, d_info, d_wave_base, d_sync_off, (int32_t)S, (int32_t)width, kmax,
                      (int32_t)R, (int32_t)SL, (int32_t)NI, (int32_t)sync_slabs, reinterpret_cast<uint32_t*>(ws + L.code),
-                     reinterpret_cast<float*>(ws + L.vals));
+                     reinterpret_cast<float*>(ws + L.vals), kept);
   SAGNN_LAUNCH_CHECK();
   if (NWT4 > NW4) {
     hipLaunchKernelGGL(sweep_short_build_kernel, dim3((unsigned)ceil_div(NWT4 - NW4, kBuildThreads / 64)), dim3(kBuildThreads), 0,
