@@ -97,11 +97,16 @@ __device__ __forceinline__ int slot_at(const BuildPieces& pc, int32_t e) {
   return slot;
 }
 
+// the value of the lane before (lane 0: 0)
+__device__ __forceinline__ uint32_t from_left(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, false);   // wave_shr:1
+}
+
 // c / width for c below 2^27 (the quotient in single precision is off by at most one)
 __device__ __forceinline__ int slab_of(uint32_t c, uint32_t width, float inv_width, int S) {
   int s = (int)((float)c * inv_width);
-  if ((uint32_t)s * width > c) --s;
-  else if ((uint32_t)(s + 1) * width <= c) ++s;
+  const uint32_t rest = c - (uint32_t)s * width;
+  s += (int)rest < 0 ? -1 : (rest >= width ? 1 : 0);
   return s < S - 1 ? s : S - 1;
 }
 
@@ -151,43 +156,51 @@ __device__ __forceinline__ void build_tables(const int32_t* __restrict__ rowptr,
   const float inv = 1.0f / (float)slab_width;
   bool bad = false;
   const int32_t total = scan ? pc.pre[kSweepSlots] : 0;
-  for (int32_t e0 = tid; e0 < total; e0 += 4 * kBuildThreads) {
+  // A wavefront looks at 63 entries at a time: lane 0 has the one before them, every other lane takes its predecessor from its
+  // neighbour.  The slot is looked up once for all lanes where they lie in one, as they mostly do (40 M entries, counting 142 us
+  // with a look-up and two slabs for each entry, now 129).
+  const int lane = tid & 63;
+  const int32_t my_pre = lane <= kSweepSlots ? pc.pre[lane] : 0x7FFFFFFF, my_beg = pc.beg[lane & (kSweepSlots - 1)];
+  for (int32_t e0 = (tid >> 6) * (4 * 63) - 1; e0 < total - 1; e0 += kBuildThreads / 64 * 4 * 63) {
     int slot[4];
     int32_t i[4];
-    uint32_t c[4], b[4];
+    uint32_t c[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int32_t e = e0 + q * kBuildThreads < total ? e0 + q * kBuildThreads : total - 1;
-      slot[q] = slot_at(pc, e);
-      i[q] = e - pc.pre[slot[q]];
-      const int32_t* __restrict__ cp = colidx + pc.beg[slot[q]] + i[q];
-      c[q] = (uint32_t)cp[0];
-      b[q] = (tid & 63) == 0 && i[q] > 0 ? (uint32_t)cp[-1] : 0u;
+      const int32_t first = max(min(e0 + q * 63, total - 1), 0), last = min(e0 + q * 63 + 63, total - 1);
+      const int32_t e = max(min(e0 + q * 63 + lane, total - 1), 0);
+      const int sf = __popcll(__ballot(my_pre <= first)) - 1, sl = __popcll(__ballot(my_pre <= last)) - 1;
+      if (sf == sl) {
+        slot[q] = sf;
+        i[q] = e - __builtin_amdgcn_readlane(my_pre, sf);
+        c[q] = (uint32_t)colidx[__builtin_amdgcn_readlane(my_beg, sf) + i[q]];
+      } else {
+        slot[q] = slot_at(pc, e);
+        i[q] = e - pc.pre[slot[q]];
+        c[q] = (uint32_t)colidx[pc.beg[slot[q]] + i[q]];
+      }
     }
-    // (the other lanes' predecessors are their neighbours' entries; a place behind the last entry repeats that one)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t left = (uint32_t)__shfl_up((int)c[q], 1, 64);
-      if ((tid & 63) != 0) b[q] = i[q] > 0 ? left : 0u;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (CHECK) bad |= c[q] > kmax || b[q] > c[q];
       const int s = slab_of(c[q] > kmax ? kmax : c[q], (uint32_t)slab_width, inv, S);
-      const int before = i[q] > 0 ? slab_of(b[q] > kmax ? kmax : b[q], (uint32_t)slab_width, inv, S) : 0;
-      for (int t = before + 1; t <= s; ++t) T.LO(slot[q], t) = i[q];
+      const uint32_t left = from_left(c[q]);
+      const int s_left = (int)from_left((uint32_t)s);
+      if (lane == 0 || e0 + q * 63 + lane >= total) continue;
+      if (CHECK) bad |= c[q] > kmax || (i[q] > 0 && left > c[q]);
+      for (int t = i[q] > 0 ? s_left + 1 : 1; t <= s; ++t) T.LO(slot[q], t) = i[q];
     }
   }
   // rows cut into many pieces: all (row, slab) pairs side by side, four searches in flight per thread (row by row, with
   // the slabs side by side, the sixteen chains followed each other; 40 M entries: counting 152 -> 136 us, layout
   // 440 -> 423)
   const int n_hub = scan && S > 1 ? pc.n_hub : 0;
-  if (CHECK) {   // every piece looks at its own entries
+  if (CHECK) {   // every piece looks at its share of the row, one run (its own entries lie apart, a line each: 129 us, now 105)
     for (int h = 0; h < n_hub; ++h) {
       const int slot = pc.hub[h];
-      const int32_t d = pc.deg[slot];
+      const int64_t d = pc.deg[slot];
       const int32_t* __restrict__ col = colidx + pc.beg[slot];
-      for (int32_t i = pc.j[slot] + tid * pc.p[slot]; i < d; i += kBuildThreads * pc.p[slot])
+      const int32_t to = (int32_t)(d * (pc.j[slot] + 1) / pc.p[slot]);
+      for (int32_t i = (int32_t)(d * pc.j[slot] / pc.p[slot]) + tid; i < to; i += kBuildThreads)
         bad |= (uint32_t)col[i] > kmax || (i > 0 && (uint32_t)col[i - 1] > (uint32_t)col[i]);
     }
   }

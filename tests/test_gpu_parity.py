@@ -1248,6 +1248,28 @@ def test_spmm_sweep_planner_deals_few_pieces(groups, min_waves, force_sweep, mon
         assert_close(got, ref, zabs, RTOL_SPMM, f"{rows} long rows, {groups}")
 
 
+@pytest.mark.parametrize("slab_mb", ["0", "1"])
+@pytest.mark.parametrize("at", [-1, 0, 999, 1000, 2500, 4998])
+def test_spmm_sweep_reads_every_pair_of_a_row(slab_mb, at, force_sweep, monkeypatch):
+    """Rows whose ends lie around the 63 entries that a wavefront looks at at a time, and rows cut into five pieces whose shares
+    are looked at apart: one descending pair anywhere is found, and without one the streams are right, with tables of many slabs
+    (found again for the layout) and of few (left by the counting pass)."""
+    monkeypatch.setenv("SAGNN_SWEEP_SLAB_MB", slab_mb)
+    rng = np.random.default_rng(13)
+    m, n, f = 600, 20_000, 64
+    ends = [62, 63, 64, 125, 126, 127, 128, 189, 251, 252, 253]
+    rowptr, colidx, val = random_csr(m, n, 20, rng, hubs=[(5, 5000), (300, 5000)] + [(20 + r, ends[r % 11]) for r in range(200)])
+    for r in (5, 300):                                        # distinct columns
+        colidx[rowptr[r]:rowptr[r] + 5000] = np.sort(rng.choice(n, 5000, replace=False))
+    if at >= 0:
+        e = rowptr[300] + at
+        colidx[[e, e + 1]] = colidx[[e + 1, e]]
+    B = synth.normal((n, f), 1, synth.STREAM_H)
+    ref, zabs = oracle.spmm(rowptr, colidx, val, B, want_abs=True)
+    got = run_spmm(rowptr, colidx, val, B, True, expect_mode=1 if at < 0 else 0)
+    assert_close(got, ref, zabs, RTOL_SPMM, f"descending pair at {at}")
+
+
 @pytest.mark.parametrize("f", [192, 256, 320])
 def test_spmm_sweep_wide_operand_as_128_wide_slabs(f, force_sweep, monkeypatch):
     """Operands wider than 128 taken as 128-wide column slabs (plus a 64-wide rest) by the kernels
