@@ -31,7 +31,8 @@ struct FlatDims {
   uint64_t generation;
   uint32_t b_bytes, row_bytes, kmax;
   int32_t f, accumulate;
-  int32_t parts, part_cols, blocks;   // PARTS: column parts, a share of the XCDs each, columns and workgroups of a part
+  int32_t blocks, window;             // workgroups (of a part), those that are shared out among the XCDs at a time
+  int32_t parts, part_cols;           // PARTS: column parts, a share of the XCDs each, and their columns
 };
 
 // (no short cuts: all fields are read at once instead of one after the other)
@@ -84,13 +85,21 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
   constexpr int U = 8;                       // rows of B in flight
   const int lane = threadIdx.x & 63;
   const int lig = lane % LPE, sub = lane % UNIT;
-  int32_t block = blockIdx.x, col0 = 0, width = d.f;
-  if constexpr (PARTS) {                     // (workgroups go to the eight XCDs in turn; see flat_launch)
-    const int32_t xcd = block & 7, each = 8 / d.parts;     // XCDs of a part
+  // (workgroups go to the eight XCDs in turn; of each window of them an XCD takes a run of the chunks, see flat_launch)
+  int32_t col0 = 0, width = d.f, first = 0, block;
+  if constexpr (PARTS) {
+    const int32_t xcd = blockIdx.x & 7, i = blockIdx.x >> 3, each = 8 / d.parts, rounds = d.window / each;   // each: XCDs of a part
     col0 = xcd / each * d.part_cols;
     width = d.f - col0 < d.part_cols ? d.f - col0 : d.part_cols;
-    block = (block >> 3) * each + xcd % each;
+    const int32_t all = (d.blocks + each - 1) / each;
+    if (rounds < all) first = i / rounds * rounds;
+    const int32_t n = all - first < rounds ? all - first : rounds;
+    block = first * each + xcd % each * n + (i - first);
     if (block >= d.blocks) return;
+  } else {
+    if (d.window < d.blocks) first = (int32_t)blockIdx.x / d.window * d.window;
+    const int32_t n = d.blocks - first < d.window ? d.blocks - first : d.window, i = blockIdx.x - first, xcd = i & 7;
+    block = first + xcd * (n >> 3) + (xcd < (n & 7) ? xcd : n & 7) + (i >> 3);
   }
   const bool active = lig * 4 < width;
   const uint32_t loff = active ? lig * 16 : 0;     // (idle lanes read the row's first piece again)
@@ -463,7 +472,18 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   auto go = [&](auto kern, int lpe) -> int {
     const int64_t waves = ceil_div(a.nchunks, 64 / lpe);
     d.blocks = (int32_t)ceil_div(waves, kWaves);
-    const int64_t grid = d.parts > 1 ? 8 * ceil_div((int64_t)d.blocks * d.parts, 8) : d.blocks;
+    const int64_t grid = d.parts > 1 ? 8 * ceil_div(d.blocks, 8 / d.parts) : d.blocks;
+    // An XCD takes a run of neighbouring chunks, so that where neighbouring rows want the same rows of B its L2 is asked for
+    // an eighth of them; where they do not nothing changes.  At most as many at a time as the memory-side cache holds the rows
+    // of, and in turn from 1200 MB on, where that is less than two neighbourhoods (one run, such runs: 1 M vertices of 6, f = 256
+    // in turn 959, 1000, 957; 2 M, f = 128, 192, 256 989, 1451, 1945 and 976, 1462, 1976).  us in turn and so, 16 communities:
+    // 20 k vertices of 12, f = 64, 128 9.6, 14.6 and 8.0, 13.5; 40 k of 24 f = 100, 192, 256 50, 91, 94 and 33, 50, 72; 100 k of
+    // 12 f = 16, 64, 100, 256 20, 50, 85, 165 and 16, 28, 45, 138; 300 k of 8 f = 64, 128, 256 111, 200, 378 and 83, 163, 347;
+    // random and power-law columns within 2 %.
+    const double bytes = (double)a.rows * fw * 4.0;
+    d.window = d.blocks + 64;
+    if (bytes > 256.0 * (1 << 20)) d.window = (int32_t)std::max(64.0, 256.0 * (1 << 20) / bytes * d.blocks) / 64 * 64;
+    if (bytes > 1200.0 * (1 << 20)) d.window = 8 / d.parts;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kBlock), 0, s, a.colidx, a.val, a.B + col0,
                        a.C + col0, a.hdr, a.chunks, a.flags, a.carry + col0, a.rowmap, d);
     SAGNN_LAUNCH_CHECK();

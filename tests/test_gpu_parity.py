@@ -363,6 +363,19 @@ def force_sweep(request, monkeypatch):
     monkeypatch.setenv("SAGNN_SWEEP_GROUPS", "2")      # lane-group kernels at f = 128 / 64 even with little reuse
 
 
+@pytest.mark.parametrize("m,n,f", [(1, 50, 64), (700, 300, 16), (30_001, 30_001, 64), (300_000, 1000, 256), (300_000, 9000, 256)])
+def test_spmm_chunks_in_runs_for_each_xcd(m, n, f, monkeypatch):
+    """Nonzero splitting with the chunks dealt to the XCDs in runs: fewer workgroups than XCDs, all in one run each, and
+    several windows of runs (more rows than the memory-side cache holds), also with the columns in parts; rows that neighbouring
+    chunks share."""
+    monkeypatch.setenv("SAGNN_SWEEP", "0")
+    rng = np.random.default_rng(m)
+    rowptr, colidx, val = random_csr(m, n, 2, rng, empty_frac=0.1, hubs=[(m // 2, 200), (m - 1, 40)])
+    B = synth.normal((n, f), 3, synth.STREAM_H)
+    ref, zabs = oracle.spmm(rowptr, colidx, val, B, want_abs=True)
+    assert_close(run_spmm(rowptr, colidx, val, B, True, expect_mode=0), ref, zabs, RTOL_SPMM, f"{m} rows, f={f}")
+
+
 @pytest.mark.parametrize("f,target", [(4, 3_000), (16, 8_500_000), (20, 400_000), (32, 4_300_000), (36, 40_000), (64, 600_000),
                                       (100, 300_000), (132, 140_000), (256, 270_000), (260, 1_100_000)])
 def test_spmm_chunks_at_their_edges(f, target, monkeypatch):
