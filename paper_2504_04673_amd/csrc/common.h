@@ -418,11 +418,15 @@ int tile_launch(const TilePlan& p, uint64_t generation, char* base, const TileWs
 struct RadixWs {
   uint32_t *keys[2], *pay[2];
   int32_t* counts;     // [digits][tiles]
-  int32_t* totals;     // [digits]
+  int32_t* totals;     // [digits], then a word for radix_order's flag
   int64_t cap;         // pairs the workspace was carved for
   size_t bytes;
 };
 RadixWs carve_radix(void* base, int64_t n);   // base == NULL: sizes only
+// Stable order of keys of up to 8 bits: order[place] = index, inverse[index] = place.  w.totals = pairs of every key, behind 256 of
+// them the flag of a key >= limit (cleared by the caller).
+int radix_order(const uint32_t* keys, int64_t n, int bits, const RadixWs& w, int32_t* order, int32_t* inverse, hipStream_t s,
+                int64_t limit);
 int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* pay_in, int64_t n, int bits, const RadixWs& w,
                      hipStream_t s, int* result, int64_t limit = 0, int32_t* err = nullptr);
 // rowptr[c] = number of the cnt sorted keys below c, c in [0, n]

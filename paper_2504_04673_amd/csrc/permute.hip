@@ -133,11 +133,24 @@ __global__ __launch_bounds__(kThreads) void scan_sums_kernel(int32_t* __restrict
   }
 }
 
+// SUMMED: tilesum has been scanned.  Up to kFewSums tiles every workgroup adds up the tiles before its own by itself instead:
+// they are in cache, and the scan is one of three launches.
+constexpr int64_t kFewSums = 1024;
+template <bool SUMMED>
 __global__ __launch_bounds__(kThreads) void scan_add_kernel(const int32_t* __restrict__ tilesum, int64_t n, int64_t nnz,
                                                             int32_t* __restrict__ rowptr) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) rowptr[i] += tilesum[i / kScanTile];
-  else if (i == n) rowptr[n] = (int32_t)nnz;
+  int32_t before = 0;
+  if constexpr (SUMMED) {
+    before = tilesum[blockIdx.x];
+  } else {
+    int32_t part = 0;
+    for (int64_t t = threadIdx.x; t < blockIdx.x; t += kThreads) part += tilesum[t];
+    scan_block(part, &before);
+  }
+  for (int64_t i = (int64_t)blockIdx.x * kScanTile + threadIdx.x; i < ((int64_t)blockIdx.x + 1) * kScanTile && i <= n; i += kThreads) {
+    if (i < n) rowptr[i] += before;
+    else rowptr[n] = (int32_t)nnz;
+  }
 }
 
 // Ascending bitonic sort over the 64 lanes.  Partners at 1, 2, 4 and 8 lanes come by DPP (two steps for 4), at 16 and 32
@@ -362,12 +375,25 @@ SAGNN_EXPORT int spmm_perm_from_labels(const int32_t* d_labels, int64_t n, int32
   if (n == 0) return SAGNN_OK;
   // stable sort of the vertices by label; the part offsets come from the sorted labels.  The error flag lies
   // behind the offsets so that one copy brings both to the host.
-  int32_t* d_off = w.rp_b;
-  int32_t* d_err = w.rp_b + n_parts + 1;
-  SAGNN_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
   const RadixWs rw = carve_radix(w.tws, n);
   int bits = 1;
   while ((1 << bits) < n_parts) ++bits;
+  int32_t h[1026];
+  if (bits <= 8) {
+    // one pass, which writes both orders; the offsets are sums of its totals (500 k labels of 16: sorted pairs, offsets and
+    // orders by kernels of their own 26 us, now 18)
+    SAGNN_HIP(hipMemsetAsync(rw.totals + 256, 0, sizeof(int32_t), s));
+    rc = radix_order(reinterpret_cast<const uint32_t*>(d_labels), n, bits, rw, d_perm, d_inv, s, n_parts);
+    if (rc != SAGNN_OK) return rc;
+    SAGNN_HIP(hipMemcpyAsync(h, rw.totals, sizeof(int32_t) * 257, hipMemcpyDeviceToHost, s));
+    SAGNN_HIP(hipStreamSynchronize(s));
+    if (h[256]) return SAGNN_EFORMAT;   // a label outside [0, n_parts)
+    for (int32_t q = 0; q < n_parts; ++q) h_part_off[q + 1] = h_part_off[q] + h[q];
+    return SAGNN_OK;
+  }
+  int32_t* d_off = w.rp_b;
+  int32_t* d_err = w.rp_b + n_parts + 1;
+  SAGNN_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
   int res = 0;
   rc = radix_sort_pairs(reinterpret_cast<const uint32_t*>(d_labels), nullptr, n, bits, rw, s, &res, n_parts, d_err);
   if (rc != SAGNN_OK) return rc;
@@ -375,7 +401,6 @@ SAGNN_EXPORT int spmm_perm_from_labels(const int32_t* d_labels, int64_t n, int32
   if (rc != SAGNN_OK) return rc;
   hipLaunchKernelGGL(order_kernel, grid_for(n), dim3(kThreads), 0, s, rw.pay[res], n, d_perm, d_inv);
   SAGNN_LAUNCH_CHECK();
-  int32_t h[1026];
   SAGNN_HIP(hipMemcpyAsync(h, d_off, sizeof(int32_t) * (size_t)(n_parts + 2), hipMemcpyDeviceToHost, s));
   SAGNN_HIP(hipStreamSynchronize(s));
   if (h[n_parts + 1]) return SAGNN_EFORMAT;   // a label outside [0, n_parts)
@@ -410,10 +435,12 @@ SAGNN_EXPORT int spmm_csr_permute_symmetric(const int32_t* d_rowptr, const int32
     const int64_t ntiles = ceil_div(n > 0 ? n : 1, kScanTile);
     hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, s, w.rp_b, n, d_rowptr_p, w.tilesum);
     SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kThreads), 0, s, w.tilesum, ntiles);
-    SAGNN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)ceil_div(n + 1, kThreads)), dim3(kThreads), 0, s, w.tilesum, n, nnz,
-                       d_rowptr_p);
+    if (ntiles > kFewSums) {
+      hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kThreads), 0, s, w.tilesum, ntiles);
+      SAGNN_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(ntiles > kFewSums ? scan_add_kernel<true> : scan_add_kernel<false>, dim3((unsigned)ceil_div(n + 1, kScanTile)),
+                       dim3(kThreads), 0, s, w.tilesum, n, nnz, d_rowptr_p);
     SAGNN_LAUNCH_CHECK();
     if (nnz > 0 && n > 0) {
       hipLaunchKernelGGL(permute_rows_kernel, dim3((unsigned)ceil_div(n, 4 * (kThreads / 64))), dim3(kThreads), 0, s,

@@ -48,9 +48,10 @@ struct PassArgs {
   int32_t* totals;            // [bins]
   const int32_t* rowptr;      // SRC_ROWS: the first payload word is the row of the entry
   int64_t m;
+  int32_t* inverse;           // SRC_ORDER: the place of every pair
 };
 
-enum Src { SRC_ARRAYS = 0, SRC_INDEX = 1, SRC_ROWS = 2 };
+enum Src { SRC_ARRAYS = 0, SRC_INDEX = 1, SRC_ROWS = 2, SRC_ORDER = 3 };   // (SRC_ORDER: as SRC_INDEX, without sorted keys)
 
 // limit > 0: err[0] = 1 if some key is >= limit
 // Eight counters per digit, side by side, taken by the lanes in turn: lanes that add to one counter wait for each other, and the
@@ -187,6 +188,7 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
         digit_total += v;
         digit_before += t < (int)tile ? v : 0;
       }
+      if (SRC == SRC_ORDER && tile == 0) a.totals[tid] = digit_total;
     }
   } else {
     if (tid < bins) {
@@ -297,7 +299,7 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
     if (i < cnt) {
       const uint32_t k = stage[i];
       dst[j] = gbase[(k >> a.shift) & (uint32_t)(bins - 1)] + i;
-      a.keys_out[dst[j]] = k;
+      if constexpr (SRC != SRC_ORDER) a.keys_out[dst[j]] = k;
     }
   }
 #pragma unroll
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       const int i = seg + j * 64;
-      if (q == 0 && SRC == SRC_INDEX) v[j] = (uint32_t)(tile0 + i);
+      if (q == 0 && (SRC == SRC_INDEX || SRC == SRC_ORDER)) v[j] = (uint32_t)(tile0 + i);
       else if (q == 0 && SRC == SRC_ROWS) v[j] = row[SRC == SRC_ROWS ? j : 0];
       else v[j] = i < cnt ? in[tile0 + i] : 0u;
     }
@@ -319,7 +321,10 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < KPT; ++j)
-      if (dst[j] >= 0) out[dst[j]] = stage[j * THREADS + tid];
+      if (dst[j] >= 0) {
+        out[dst[j]] = stage[j * THREADS + tid];
+        if constexpr (SRC == SRC_ORDER) a.inverse[stage[j * THREADS + tid]] = dst[j];
+      }
   }
 }
 
@@ -335,6 +340,7 @@ int run_pass(const PassArgs& a, int np, int src, uint32_t limit, int32_t* err, h
   }
   const auto scatter = src == SRC_ROWS    ? radix_scatter_kernel<THREADS, KPT, 2, SRC_ROWS, FEW>
                        : src == SRC_INDEX ? radix_scatter_kernel<THREADS, KPT, 1, SRC_INDEX, FEW>
+                       : src == SRC_ORDER ? radix_scatter_kernel<THREADS, KPT, 1, SRC_ORDER, FEW>
                        : np == 2          ? radix_scatter_kernel<THREADS, KPT, 2, SRC_ARRAYS, FEW>
                                           : radix_scatter_kernel<THREADS, KPT, 1, SRC_ARRAYS, FEW>;
   hipLaunchKernelGGL(scatter, grid, dim3(THREADS), 0, s, a);
@@ -375,7 +381,7 @@ RadixWs carve_radix(void* base, int64_t n) {
     w.pay[i] = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)cap));
   }
   w.counts = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * kMaxBins * (size_t)max_tiles));
-  w.totals = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * kMaxBins));
+  w.totals = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (kMaxBins + 1)));
   w.cap = cap;
   w.bytes = off;
   return w;
@@ -403,6 +409,20 @@ int radix_sort_pairs(const uint32_t* keys_in, const uint32_t* pay_in, int64_t n,
     if (rc != SAGNN_OK) return rc;
   }
   return SAGNN_OK;
+}
+
+int radix_order(const uint32_t* keys, int64_t n, int bits, const RadixWs& w, int32_t* order, int32_t* inverse, hipStream_t s,
+                int64_t limit) {
+  if (n < 1 || n > w.cap || bits < 1 || bits > 8 || !w.keys[0]) return SAGNN_EINVAL;
+  PassArgs a{};
+  a.keys_in = keys;
+  a.p0_out = reinterpret_cast<uint32_t*>(order);
+  a.inverse = inverse;
+  a.n = n;
+  a.bits = bits;
+  a.counts = w.counts;
+  a.totals = w.totals;
+  return run_pass(a, 1, SRC_ORDER, (uint32_t)limit, w.totals + kMaxBins, s);
 }
 
 namespace {

@@ -390,6 +390,26 @@ def test_reorder_by_labels_and_permute_symmetric(case, cfg1):
     assert_close(Z, ref, zabs, RTOL_SPMM, f"reordered product {case}")
 
 
+@pytest.mark.parametrize("n,parts", [(1, 1), (3, 3), (255, 255), (1024, 256), (1025, 257), (2049, 1024), (131_072, 256), (131_073, 2),
+                                     (262_145, 16), (2_100_000, 200)])
+def test_order_from_labels_at_the_edges_of_its_tiles(n, parts):
+    """One pass for up to 256 parts, sorted pairs beyond; few tiles that add up the counts by themselves, and many; the row
+    pointer of the permuted matrix with its tile sums added up by every workgroup (up to 1024 tiles of 2048 rows) or scanned."""
+    rng = np.random.default_rng(n)
+    labels = np.minimum(rng.integers(0, parts, size=n), rng.integers(0, parts, size=n)).astype(np.int32)
+    perm, inv, off = sagnn.spmm_perm_from_labels(dev(labels), parts)
+    operm, oinv, ooff = oracle.perm_from_labels(labels, parts)
+    assert np.array_equal(perm.cpu().numpy(), operm) and np.array_equal(inv.cpu().numpy(), oinv) and np.array_equal(off, ooff)
+    deg = rng.integers(0, 3, size=n)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    colidx = rng.integers(0, n, size=int(rowptr[-1])).astype(np.int32)
+    rpp, _, _ = sagnn.spmm_csr_permute_symmetric(dev(rowptr), dev(colidx), dev(np.ones(colidx.size, np.float32)), inv)
+    assert np.array_equal(rpp.cpu().numpy(), np.concatenate([[0], np.cumsum(deg[operm])]).astype(np.int32))
+    labels[n // 2] = parts
+    with pytest.raises(sagnn.SagnnError):
+        sagnn.spmm_perm_from_labels(dev(labels), parts)
+
+
 def test_reorder_rejects_bad_labels_and_maps():
     labels = dev(np.array([0, 1, 2, 5, 1], np.int32))
     with pytest.raises(sagnn.SagnnError) as ei:
