@@ -1728,7 +1728,7 @@ int sweep_prepare(const int32_t* d_rowptr, const int32_t* d_colidx, const float*
   // the pieces are sorted by size and dealt longest-first, so its wavefronts have nearly equal
   // stream lengths (they pass the slabs in step).  A matrix of up to ~4 generations is one
   // window (measured best on randomly labelled graphs: 4.95 ms against 5.4 ms with one window
-  // per generation on the 2.45 M-vertex R-MAT graph).  Where the row order carries locality (plan_locality_kernel) a
+  // per generation on the 2.45 M-vertex R-MAT graph).  Where the row order carries locality (row_locality) a
   // window of a quarter of a generation keeps its wavefronts in the part of B that its rows' neighbourhoods share.
   // One generation in four against four generations, 50 entries a row in 16 communities: 1 M vertices f = 16 783 ->
   // 418 us, f = 64 1733 -> 1420, f = 256 6383 -> 5960; 300 k vertices f = 16 208 -> 94, f = 256 1834 -> 1468; 2 M of

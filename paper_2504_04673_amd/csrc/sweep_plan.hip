@@ -34,13 +34,14 @@ enum Stat : int {
   ST_EMPTY,         // rows without entries
   ST_BAD,           // != 0: not a CSR row pointer for this nnz, or a row needs too many pieces
   ST_FROM_MIN,      // entries in rows of kSweepMinLong and more
-  ST_MINLONG,       // the degree from which a row is swept
+  ST_MINLONG,       // the caller's degree from which a row is swept, or its rule (min_long_of)
+  ST_NNZ,
   ST_PIECES,        // five totals of the row scan, in the order of RowQ
   ST_SHORT_ROWS,
   ST_SHORT_ENTRIES,
   ST_MULTI_ROWS,
   ST_MULTI_PIECES,
-  ST_LOCALITY,      // permille, see plan_locality_kernel
+  ST_LOCALITY,      // permille, see row_locality
   ST_SPAN,          // permille of the columns, see there
   ST_SLIDE,         // permille of the runs, see there
   ST_COUNT = 16
@@ -51,11 +52,13 @@ __global__ __launch_bounds__(kT) void plan_zero_kernel(unsigned long long* __res
   if (threadIdx.x < 4) flags[threadIdx.x] = 0;
 }
 
-__global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restrict__ rowptr, int64_t m,
-                                                          int64_t nnz, unsigned long long* __restrict__ stat) {
+constexpr int kSampleThreads = 1024;
+// workgroup `block` of `blocks`
+__device__ __forceinline__ void row_statistics(const int32_t* __restrict__ rowptr, int64_t m, int64_t nnz, int block, int blocks,
+                                               unsigned long long* __restrict__ stat) {
   long long mid = 0, empty = 0, bad = 0, from_min = 0;
-  const int64_t stride = (int64_t)gridDim.x * kT;
-  for (int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x; r < m; r += stride) {
+  const int64_t stride = (int64_t)blocks * kSampleThreads;
+  for (int64_t r = (int64_t)block * kSampleThreads + threadIdx.x; r < m; r += stride) {
     const int64_t d = (int64_t)rowptr[r + 1] - rowptr[r];
     if (d < 0) bad = 1;
     else if (d == 0) ++empty;
@@ -64,8 +67,8 @@ __global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restr
       if (d < 64) mid += d;
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && (rowptr[0] != 0 || (int64_t)rowptr[m] != nnz)) bad = 1;
-  __shared__ long long part[kT / 64][4];
+  if (block == 0 && threadIdx.x == 0 && (rowptr[0] != 0 || (int64_t)rowptr[m] != nnz)) bad = 1;
+  __shared__ long long part[kSampleThreads / 64][4];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     mid += __shfl_down(mid, o, 64);
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restr
   if (threadIdx.x < 4) {
     static_assert(ST_MID == 0 && ST_EMPTY == 1 && ST_BAD == 2 && ST_FROM_MIN == 3, "order of part[]");
     long long t = 0;
-    for (int w = 0; w < kT / 64; ++w) t += part[w][threadIdx.x];
+    for (int w = 0; w < kSampleThreads / 64; ++w) t += part[w][threadIdx.x];
     if (t) atomicAdd(&stat[threadIdx.x], (unsigned long long)t);
   }
 }
@@ -93,13 +96,10 @@ __global__ __launch_bounds__(kT) void plan_rowstat_kernel(const int32_t* __restr
 // entries hold a large share of the matrix (near-regular graphs, e.g. a partitioned graph's row
 // block) the threshold drops so that they are swept too.  opt > 0: forced; opt < 0: -opt is used
 // where the rule would pick 64.
-__global__ void plan_rule_kernel(unsigned long long* __restrict__ stat, int64_t nnz, int32_t opt_min_long) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int32_t min_long = opt_min_long;
-  if (min_long <= 0)
-    min_long = ((long long)stat[ST_MID] * 4 >= nnz) ? kSweepMinLong : (min_long < 0 ? -min_long : 64);
-  if (min_long < kSweepMinLong) min_long = kSweepMinLong;
-  stat[ST_MINLONG] = (unsigned long long)min_long;
+__host__ __device__ inline int32_t min_long_of(const unsigned long long* stat) {
+  int32_t min_long = (int32_t)(long long)stat[ST_MINLONG];
+  if (min_long <= 0) min_long = (long long)stat[ST_MID] * 4 >= (long long)stat[ST_NNZ] ? kSweepMinLong : (min_long < 0 ? -min_long : 64);
+  return min_long < kSweepMinLong ? kSweepMinLong : min_long;
 }
 
 // Does the row order carry locality?  32 runs of 64 neighbouring rows, evenly spread, up to 32 evenly spaced entries
@@ -113,10 +113,10 @@ __global__ void plan_rule_kernel(unsigned long long* __restrict__ stat, int64_t 
 // diagonal.
 // One workgroup, all samples of a row in flight: two chains of three dependent loads.  The places and ranges come without
 // divisions of 64 bits, whose instructions were most of the time (41 us, now 22).
+static_assert(kSampleThreads == 1024, "sixteen wavefronts take the runs");
 constexpr int kLocRuns = 32, kLocBins = 64, kLocSamples = 32;
-__global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-                                                             int64_t m, int64_t nnz, int64_t k,
-                                                             unsigned long long* __restrict__ stat) {
+__device__ __forceinline__ void row_locality(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx, int64_t m,
+                                             int64_t nnz, int64_t k, unsigned long long* __restrict__ stat) {
   __shared__ int hist[kLocRuns][kLocBins];
   __shared__ float diff[kLocRuns], span[kLocRuns], slide[kLocRuns];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -182,6 +182,22 @@ __global__ __launch_bounds__(1024) void plan_locality_kernel(const int32_t* __re
   }
 }
 
+// The first workgroup looks at the locality while the others go through the row pointer (one after the other 22 + 12.5 us and a
+// launch for the rule, which is worked out where it is used).
+__global__ __launch_bounds__(kSampleThreads) void plan_sample_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+                                                                     int64_t m, int64_t nnz, int64_t k, int32_t opt_min_long,
+                                                                     unsigned long long* __restrict__ stat) {
+  if (blockIdx.x > 0) {
+    row_statistics(rowptr, m, nnz, (int)blockIdx.x - 1, (int)gridDim.x - 1, stat);
+    return;
+  }
+  if (threadIdx.x == 0) {
+    stat[ST_MINLONG] = (unsigned long long)(long long)opt_min_long;
+    stat[ST_NNZ] = (unsigned long long)nnz;
+  }
+  if (colidx && k > 0) row_locality(rowptr, colidx, m, nnz, k, stat);
+}
+
 struct RowQ {
   int v[5];   // pieces, short row (0/1), entries if short, cut into several pieces (0/1), pieces if so
 };
@@ -244,7 +260,7 @@ __global__ __launch_bounds__(kT) void plan_rows_kernel(
     unsigned long long* __restrict__ stat, int32_t* __restrict__ tilesum, int32_t* __restrict__ rowptr_s,
     int32_t* __restrict__ rowmap_s, int32_t* __restrict__ multi_row, int32_t* __restrict__ multi_first,
     PieceArrays pa, int64_t max_pieces, int64_t max_multi_rows, int32_t short_pieces) {
-  const int32_t min_long = (int32_t)stat[ST_MINLONG];
+  const int32_t min_long = min_long_of(stat);
   const int64_t r0 = (int64_t)blockIdx.x * kRowTile + (int64_t)threadIdx.x * 8;
   RowQ q[8];
   int64_t deg[8];
@@ -645,21 +661,15 @@ int sweep_plan_sample(const int32_t* d_rowptr, const int32_t* d_colidx, int64_t 
   hipLaunchKernelGGL(plan_zero_kernel, dim3(1), dim3(kT), 0, s, sm.stat, d_flag);
   SAGNN_LAUNCH_CHECK();
   // (few workgroups: all of them add to one cache line)
-  hipLaunchKernelGGL(plan_rowstat_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(m, kT), 512)), dim3(kT), 0, s, d_rowptr, m,
-                     nnz, sm.stat);
-  SAGNN_LAUNCH_CHECK();
-  if (d_colidx && k > 0) {
-    hipLaunchKernelGGL(plan_locality_kernel, dim3(1), dim3(1024), 0, s, d_rowptr, d_colidx, m, nnz, k, sm.stat);
-    SAGNN_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(plan_rule_kernel, dim3(1), dim3(64), 0, s, sm.stat, nnz, opt_min_long);
+  hipLaunchKernelGGL(plan_sample_kernel, dim3((unsigned)(1 + std::max<int64_t>(1, std::min<int64_t>(ceil_div(m, kSampleThreads), 255)))),
+                     dim3(kSampleThreads), 0, s, d_rowptr, d_colidx, m, nnz, k, opt_min_long, sm.stat);
   SAGNN_LAUNCH_CHECK();
   if (out) {
     unsigned long long h[ST_COUNT];
     SAGNN_HIP(hipMemcpyAsync(h, sm.stat, sizeof(h), hipMemcpyDeviceToHost, s));
     SAGNN_HIP(hipStreamSynchronize(s));
     out->bad = h[ST_BAD] != 0;
-    out->min_long = (int32_t)h[ST_MINLONG];
+    out->min_long = min_long_of(h);
     out->locality = (int32_t)h[ST_LOCALITY];
     out->span = (int32_t)h[ST_SPAN];
     out->slide = (int32_t)h[ST_SLIDE];
@@ -693,7 +703,7 @@ int sweep_plan_rows(const int32_t* d_rowptr, int64_t m, int32_t piece_max, char*
   SAGNN_HIP(hipStreamSynchronize(s));
   out->bad = h[ST_BAD] != 0;
   out->has_empty = h[ST_EMPTY] != 0;
-  out->min_long = (int32_t)h[ST_MINLONG];
+  out->min_long = min_long_of(h);
   out->locality = (int32_t)h[ST_LOCALITY];
   out->span = (int32_t)h[ST_SPAN];
   out->slide = (int32_t)h[ST_SLIDE];
