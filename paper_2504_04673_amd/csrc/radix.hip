@@ -250,8 +250,8 @@ __global__ __launch_bounds__(THREADS) void radix_scatter_kernel(const PassArgs a
   if constexpr (SRC == SRC_ROWS) {
     // Rows of the tile's entries: every row that begins inside the tile leaves its number where it begins (of several, all
     // but the last empty, the last), and an entry's row is the nearest mark at or before it, found in a ballot of 64 entries.
-    // (A binary search per entry, nine dependent LDS reads, bound the pass: 40 M entries, 1 M rows 370 us, now 261; the
-    // passes whose payloads are both read from memory take 229..293.)
+    // (A binary search per entry, nine dependent LDS reads, bound the pass: 40 M entries, 1 M rows 370 us, so 250, in runs
+    // for each XCD 234; the passes whose payloads are both read from memory take 209 and 233.)
     __shared__ int64_t ends[2];
     __shared__ int32_t last_mark[WAVES];
     if (wave < 2) {
