@@ -31,7 +31,7 @@ struct FlatDims {
   uint64_t generation;
   uint32_t b_bytes, row_bytes, kmax;
   int32_t f, accumulate;
-  int32_t blocks, window;             // workgroups (of a part), those that are shared out among the XCDs at a time
+  int32_t blocks, window;             // workgroups (of a part), those that are shared out among the XCDs at a time (0: in turn)
   int32_t parts, part_cols;           // PARTS: column parts, a share of the XCDs each, and their columns
 };
 
@@ -97,9 +97,12 @@ __global__ __launch_bounds__(kBlock) void spmm_flat_kernel(FLAT_PTR_PARAMS, cons
     block = first * each + xcd % each * n + (i - first);
     if (block >= d.blocks) return;
   } else {
-    if (d.window < d.blocks) first = (int32_t)blockIdx.x / d.window * d.window;
-    const int32_t n = d.blocks - first < d.window ? d.blocks - first : d.window, i = blockIdx.x - first, xcd = i & 7;
-    block = first + xcd * (n >> 3) + (xcd < (n & 7) ? xcd : n & 7) + (i >> 3);
+    block = blockIdx.x;
+    if (d.window > 0) {
+      if (d.window < d.blocks) first = block / d.window * d.window;
+      const int32_t n = d.blocks - first < d.window ? d.blocks - first : d.window, i = block - first, xcd = i & 7;
+      block = first + xcd * (n >> 3) + (xcd < (n & 7) ? xcd : n & 7) + (i >> 3);
+    }
   }
   const bool active = lig * 4 < width;
   const uint32_t loff = active ? lig * 16 : 0;     // (idle lanes read the row's first piece again)
@@ -469,6 +472,7 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   d.row_bytes = (uint32_t)(a.ldb * 4);
   const bool buf = buffer_addressable(a.kmax, a.ldb, fw, &d.b_bytes);
   d.parts = 1;
+  const int64_t b_rows = (int64_t)a.kmax + 1;
   auto go = [&](auto kern, int lpe) -> int {
     const int64_t waves = ceil_div(a.nchunks, 64 / lpe);
     d.blocks = (int32_t)ceil_div(waves, kWaves);
@@ -479,11 +483,12 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
     // in turn 959, 1000, 957; 2 M, f = 128, 192, 256 989, 1451, 1945 and 976, 1462, 1976).  us in turn and so, 16 communities:
     // 20 k vertices of 12, f = 64, 128 9.6, 14.6 and 8.0, 13.5; 40 k of 24 f = 100, 192, 256 50, 91, 94 and 33, 50, 72; 100 k of
     // 12 f = 16, 64, 100, 256 20, 50, 85, 165 and 16, 28, 45, 138; 300 k of 8 f = 64, 128, 256 111, 200, 378 and 83, 163, 347;
-    // random and power-law columns within 2 %.
+    // random and power-law columns within 2 %.  And in turn where a row of B is hardly used twice (a rank's stage loop of
+    // 190 k rows, eight blocks of 2 entries a row, f = 100, 128 515, 525 us in runs, 509, 526 in turn).
     const double bytes = (double)a.rows * fw * 4.0;
     d.window = d.blocks + 64;
     if (bytes > 256.0 * (1 << 20)) d.window = (int32_t)std::max(64.0, 256.0 * (1 << 20) / bytes * d.blocks) / 64 * 64;
-    if (bytes > 1200.0 * (1 << 20)) d.window = 8 / d.parts;
+    if (bytes > 1200.0 * (1 << 20) || a.nnz < 3 * b_rows) d.window = d.parts > 1 ? 8 / d.parts : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kBlock), 0, s, a.colidx, a.val, a.B + col0,
                        a.C + col0, a.hdr, a.chunks, a.flags, a.carry + col0, a.rowmap, d);
     SAGNN_LAUNCH_CHECK();
@@ -503,7 +508,7 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   // random 200 k of 4 f = 128 78, 81; in narrower parts 60 k of 12, f = 64 31, 30, 170 k 64, 76; in parts of 13 lines or less that
   // begin inside one, 30 k of 12 f = 100 27, 31.
   const bool lines = (a.ldb & 31) == 0 && (reinterpret_cast<uintptr_t>(a.B + col0) & 127) == 0;
-  const int64_t b_rows = (int64_t)a.kmax + 1, floor_mb = !a.hubs ? 8 : (fw == 128 ? 48 : 30);
+  const int64_t floor_mb = !a.hubs ? 8 : (fw == 128 ? 48 : 30);
   if (fw >= 128 && (fw & 63) == 0 && lines && a.nnz >= 10 * b_rows && b_rows * fw * 4 >= floor_mb << 20) {
     d.parts = fw == 256 && !a.hubs ? 4 : 2;
     d.part_cols = fw / d.parts;
