@@ -228,7 +228,7 @@ inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
                 5 * sizeof(int32_t) * (size_t)(ceil_div(m, 2048) + 2));
   // W of a fused layer call packed for the bfloat16 matrix instructions (at most 256 x 256, up to
   // three terms per element)
-  L.wpack = take(3 * 256 * 256 * 2 + 256);   // (W packed, then a word per workgroup that packed it)
+  L.wpack = take(3 * 256 * 256 * 2);
   L.need = off;
   // the layout does not know how many rows B has: as many as A where a copy pays then
   L.padded_rows = spmm_pad_pays(m, nnz, f, f) ? m : 0;
@@ -367,9 +367,7 @@ int sweep_plan_deal_short(char* ws, const SpmmWsLayout& L, int64_t P_long, int64
 // the sweep with the dense transform of a GCN layer as its epilogue (spmm_sweep.hip)
 struct SweepFusedArgs {
   const float* W;        // f_in x f_out, row-major
-  const void* Wp;        // W packed for the matrix cores (set by the launcher)
-  const uint32_t* unfit; // its workgroups' words of values that three terms do not hold (set by the launcher)
-  int32_t n_unfit;
+  const void* Wp;        // bfloat16 products: W packed for the matrix cores (set by the launcher)
   float *Z, *Hout, *T;   // m x f_out, m x f_out, m x f_in; each may be NULL (not both Z and Hout)
   int32_t f_out, act;
 };

@@ -958,18 +958,31 @@ typedef __bf16 sweep_bf16x8 __attribute__((ext_vector_type(8)));
 // Dense transform of a sweep workgroup's 64 finished rows of T (LDS, [4 waves][16 slots][KROW]):
 // wavefront (rt, half) multiplies row tile rt by the 32-column tiles half, half + 2, .. of W and
 // stores the rows of Z / sigma(Z) at the rows the pieces belong to (slots that hold a piece of a
-// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup beside them.  Called
+// split row, or nothing, are skipped): `targets`, the piece_target of the workgroup (see Targets).  Called
 // by all four wavefronts after a workgroup barrier.
-// MODE: the matrix-core operands, numbered like SAGNN_GEMM_*: 0 fp32, 1 rounded to bfloat16, 2 fp32 as the exact sum of three
-// bfloat16 terms with the six products down to 2^-16 of the leading one.  fp32 takes the three terms too, and fp32
-// instructions for a row tile or a W that they do not hold (SplitRange): 512 of those per 64 rows at 128 columns were time
-// without gathers, and the terms are nearer to exact.  us before and so: power-law 2.45 M vertices of 51, 128 to 128 4735,
-// 4461, 256 to 256 12156, 11158, 1 M of 30 128 to 128 1397, 1256, 233 k of 489 2061, 2020; random columns, 500 k of 24, 128 to
-// 128 925, 863; communities, 1 M of 42, 128 to 128 2333, 1994, 64 to 64 892, 869.
+// MODE: the matrix-core operands, numbered like SAGNN_GEMM_*: 0 fp32, 1 rounded to bfloat16, 2 fp32
+// as the exact sum of three bfloat16 terms with the six products down to 2^-16 of the leading one.  (fp32 is not done as three
+// terms though they are faster, power-law 2.45 M vertices of 51, 128 to 128 4740 us, 4400: sums of few terms that are not zero
+// would be twice as far from 64 bits, at 128 columns with one W in 32 not zero 4.2e-8, 7.4e-8, and a value the terms do
+// not hold costs a second product.)
 // Rows of T lie kPadRow floats further apart in the LDS than they are long: a lane reads its own row, and rows of a multiple of 64
-// floats begin in the same bank.
+// floats begin in the same bank.  us side by side and so, 128 to 128, power-law 1 M vertices of 14 in bfloat16 841, 761, fp32
+// 1052, 1028, 2.45 M of 51 4395, 4235 and 4760, 4740; random columns, 500 k of 24 862, 843 and 924, 913.
 constexpr int kPadRow = 4;
-template <int KROW, int MODE, int QT>
+
+// Where the epilogue finds its rows: the LDS, written beside the walk, but memory in fp32 at 256 columns.  In memory, behind
+// the matrix instructions, they are one more trip in every pass over k; looked up before the loop over k they take sixteen
+// registers, which decide how many workgroups walk at the same time at 64 columns.  us behind, before and from the LDS:
+// communities, 700 k vertices of 40, 256 to 256 bfloat16 3290, 3200, 3110; a rank's 306 k rows of 11, 64 to 64 180, 220, 174.
+// In fp32 at 256 the trip does not show beside 14 us of matrix instructions, and what comes sooner is worse for random columns
+// whose rows of B are hardly used twice: from memory behind, before (TARGETS_BEFORE) and from the LDS 800 k vertices of 15
+// 2738, 3166, 3182, 1 M of 16, 18, 22 from the LDS 3663, 3995, 4559 -> 4275, 4495, 4958, 300 k of 20 (1.1 uses) 1237, 1263,
+// 1272; but 200 k of 40 (3.3) 1291, 1264, 1280, 1 M rows of 20 by 20 k columns 2914, 2713, 2750, in communities 500 k of 42
+// 2644, 2547, 2536, 700 k of 40 3759, 3714, 3677, though 500 k of 18 1708, 1781, 1.5 M of 42 8500, 8848 (bfloat16 2 M of 18
+// random 7262 behind, 7058 from the LDS).
+enum Targets { TARGETS_LDS, TARGETS_BEHIND, TARGETS_BEFORE };
+
+template <int KROW, int MODE, int QT, Targets FROM = TARGETS_LDS>
 __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ lds_acc,
                                                      const int32_t* __restrict__ targets,
                                                      const SweepFusedArgs& fa, int wave, int lane) {
@@ -977,23 +990,12 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
   const int r = lane & 31, h = lane >> 5;
   const int rt = wave & 1;
   const int nct = (fa.f_out + 31) >> 5;
-  const float* __restrict__ trow = lds_acc + (size_t)(rt * 32 + r) * (kRow + kPadRow);
-  // Rows or a W that the three terms do not hold.  (Told from the rows in a pass of its own: beside the matrix instructions it
-  // took the registers that decide how many workgroups walk, 1 M random columns of 16, 64 to 64 688 us.)
-  [[maybe_unused]] bool exact = false;
-  if constexpr (MODE == 0) {
-    const uint32_t unfit = lane < fa.n_unfit ? fa.unfit[lane] : 0u;   // (a word per workgroup that packed W)
-    SplitRange range;
-#pragma unroll 2
-    for (int k = 4 * h; k < kRow; k += 8) {
-      const float4 x = *reinterpret_cast<const float4*>(trow + k);
-      range.see(x.x);
-      range.see(x.y);
-      range.see(x.z);
-      range.see(x.w);
-    }
-    exact = __any(unfit != 0 || !range.fits());
+  [[maybe_unused]] int4 far[4];
+  if constexpr (FROM == TARGETS_BEFORE) {
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) far[v4] = *reinterpret_cast<const int4*>(targets + rt * 32 + h * 4 + v4 * 8);
   }
+  const float* __restrict__ trow = lds_acc + (size_t)(rt * 32 + r) * (kRow + kPadRow);
   // this wavefront's column tiles: ct_first, ct_first + 2, ..  (at most 4 of the at most 8).  k runs
   // in the outer loop so that a row piece of T is read from LDS once for the tiles of a pass, and the
   // operands of W for the next k group are requested before the matrix instructions of this one;
@@ -1009,22 +1011,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
     for (int q = 0; q < QT; ++q)
 #pragma unroll
       for (int v = 0; v < 16; ++v) z[q][v] = 0.f;
-    if (MODE == 0 && exact) {
-#pragma unroll 1
-      for (int k0 = 4 * h; k0 < kRow; k0 += 8) {
-        const float4 x = *reinterpret_cast<const float4*>(trow + k0);
-        const float xs[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-        for (int q = 0; q < QT; ++q) {
-          const int col = (ct0 + 2 * q) * 32 + r;
-          if (q < nmy) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              z[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[i], col < fa.f_out ? fa.W[(int64_t)(k0 + i) * fa.f_out + col] : 0.f, z[q], 0, 0, 0);
-          }
-        }
-      }
-    } else if constexpr (MODE != 1) {
+    if constexpr (MODE == 2) {
       // W as packed by sweep_pack_w_kernel with three planes: term t of W at Wp + t * (kRow / 8) * NB
       const sweep_bf16x8* __restrict__ Wp = reinterpret_cast<const sweep_bf16x8*>(fa.Wp);
       const int NB = nct * 32;
@@ -1073,7 +1060,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
             for (int t = 0; t < 3; ++t) cur[q][t] = nxt[q][t];
         }
       }
-    } else {
+    } else if constexpr (MODE == 1) {
       // W as packed by sweep_pack_w_kernel: [k / 8][NB] vectors of 8 bfloat16 (zero beyond f_out)
       const sweep_bf16x8* __restrict__ Wp = reinterpret_cast<const sweep_bf16x8*>(fa.Wp);
       const int NB = nct * 32;
@@ -1100,22 +1087,55 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
 #pragma unroll
         for (int q = 0; q < QT; ++q) cur[q] = nxt[q];
       }
+    } else {
+      constexpr int J = kRow / 8;
+      float cur[QT][4], nxt[QT][4];
+      auto wload = [&](int j, float (&dst)[QT][4]) {
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+          const int col = (ct0 + 2 * q) * 32 + r;
+          const bool ok = q < nmy && col < fa.f_out;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dst[q][i] = ok ? fa.W[(int64_t)(8 * j + 4 * h + i) * fa.f_out + col] : 0.f;
+        }
+      };
+      wload(0, cur);
+#pragma unroll 1
+      for (int j = 0; j < J; ++j) {
+        if (j + 1 < J) wload(j + 1, nxt);
+        const float4 x = *reinterpret_cast<const float4*>(trow + 8 * j + 4 * h);
+        const float xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+          if (q < nmy) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[i], cur[q][i], z[q], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) cur[q][i] = nxt[q][i];
+      }
     }
-    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4, from `targets` in the LDS,
-    // written beside the walk.  (In memory, behind the matrix instructions, they were one more trip in every pass over k;
-    // looked up before the loop over k they take sixteen registers, which decide how many workgroups walk at the same time at 64
-    // columns: communities, 700 k vertices of 40, 256 to 256 bfloat16 behind, before and from the LDS 3290, 3200, 3110 us; a
-    // rank's 306 k rows of 11, 64 to 64 180, 220, 174.  The index is opaque because look-ups moved out of the loop hold their
-    // registers all the same.)
+    // Rows of the output this lane holds in a 32 x 32 accumulator tile: 8 * (v / 4) + 4 * h + v % 4, from `targets`.  (The
+    // index is opaque because look-ups moved out of the loop hold their registers all the same; those from memory are made
+    // all at once, a load between the stores would wait for them.)
     uint32_t t0 = rt * 32 + h * 4;
     asm volatile("" : "+v"(t0));
+    if constexpr (FROM == TARGETS_BEHIND) {
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) far[v4] = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
+    }
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
       const int col = (ct0 + 2 * q) * 32 + r;
       if (q >= nmy || col >= fa.f_out) continue;
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        const int4 t4 = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
+        int4 t4;
+        if constexpr (FROM != TARGETS_LDS) t4 = far[v4];
+        else t4 = *reinterpret_cast<const int4*>(targets + t0 + v4 * 8);
         const int32_t tg[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -1129,7 +1149,7 @@ __device__ __forceinline__ void sweep_dense_epilogue(const float* __restrict__ l
   }
 }
 
-template <int FPL, int U, bool BUF, int MODE, bool TURN>
+template <int FPL, int U, bool BUF, int MODE, bool TURN, Targets FROM = TARGETS_LDS>
 __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel(
     const uint32_t* __restrict__ code, const float* __restrict__ vals,
     const int32_t* __restrict__ wave_base, const int32_t* __restrict__ piece_target,
@@ -1140,7 +1160,7 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t loff = lane * (FPL * 4);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t w = run_block(d) * 4 + wave;
+  const int64_t block = run_block(d), w = block * 4 + wave;
   // (the launch has whole workgroups: n_waves is a multiple of 4, checked by the launcher)
   if (hdr->magic != kSpmmMagic || hdr->generation != d.generation || hdr->n_waves != d.n_waves ||
       hdr->groups != 1)
@@ -1177,31 +1197,27 @@ __global__ __launch_bounds__(256, FPL == 1 ? 8 : 1) void spmm_sweep_fused_kernel
 
   // tiles per pass: 4 at f = 256 (the LDS already limits a CU to two workgroups; 2 with three operand
   // terms per tile in registers), 1 below
-  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 1 ? 4 : 2) : 1)>(lds_acc, targets, fa, wave, (int)lane);
+  sweep_dense_epilogue<kRow, MODE, (FPL == 4 ? (MODE == 2 ? 2 : 4) : 1), FROM>(
+      lds_acc, FROM != TARGETS_LDS ? piece_target + block * 4 * kSweepSlots : targets, fa, wave, (int)lane);
 }
 
 // W (f_in x f_out, row-major fp32) -> [f_in / 8][NB] vectors of 8 bfloat16 (k fastest), NB = f_out
 // rounded up to 32, zero beyond f_out: one 16-byte load then gives a lane its matrix-core operand
-// planes = 3: the three bfloat16 terms of every element, one plane of that layout per term.  unfit[workgroup] = 1: it has a value
-// that the terms do not hold (SplitRange)
+// planes = 3: the three bfloat16 terms of every element, one plane of that layout per term
 __global__ __launch_bounds__(256) void sweep_pack_w_kernel(const float* __restrict__ W, int32_t f_in, int32_t f_out,
-                                                           int32_t NB, __bf16* __restrict__ Wp, int32_t planes,
-                                                           uint32_t* __restrict__ unfit) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;     // one (k / 8, n) vector per thread (whole workgroups: f_in, NB)
-  SplitRange range;
+                                                           int32_t NB, __bf16* __restrict__ Wp, int32_t planes) {
+  const int idx = blockIdx.x * 256 + threadIdx.x;     // one (k / 8, n) vector per thread
+  if (idx >= (f_in / 8) * NB) return;
   const int kg = idx / NB, n = idx - kg * NB;
   const int64_t plane = (int64_t)(f_in / 8) * NB * 8;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const float w = n < f_out ? W[(int64_t)(kg * 8 + i) * f_out + n] : 0.f;
-    range.see(w);
     if (planes == 3)
       split3(w, Wp[(int64_t)idx * 8 + i], Wp[plane + (int64_t)idx * 8 + i], Wp[2 * plane + (int64_t)idx * 8 + i]);
     else
       Wp[(int64_t)idx * 8 + i] = (__bf16)w;
   }
-  const int all = __syncthreads_and(range.fits());
-  if (threadIdx.x == 0) unfit[blockIdx.x] = all ? 0u : 1u;
 }
 
 // Lane-group variant: the wavefront carries R independent streams (zipped in memory), lane
@@ -2110,8 +2126,9 @@ int sweep_launch(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, const f
   size_t lds = (size_t)4 * sd.slots * (sweep_lds_width(fw) + (fuse != 0 ? kPadRow : 0)) * sizeof(float);
   // (the layer: the targets behind the rows, and no more than five workgroups a CU, which 64 columns would allow: a sixth
   // only drives the others' rows out of the L2, 233 k vertices of 489, 64 to 64 columns 1480 us, with five 1410, 300 k of 60 in
-  // communities 460, 447)
-  if (fuse != 0) lds = std::max(lds + 4 * kSweepSlots * sizeof(int32_t), (size_t)28 << 10);
+  // communities 460, 447; but in fp32, whose dense part is longest, not where rows are short, 500 k of 18 in communities 319,
+  // 334, power-law of 30 314, 337)
+  if (fuse != 0) lds = std::max(lds + 4 * kSweepSlots * sizeof(int32_t), (size_t)(fuse == 1 && d.nnz < 40 * d.m ? 0 : 28) << 10);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -2260,18 +2277,19 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   if (d.n_waves <= 0 || (d.n_waves & 3) || d.slots != kSweepSlots) return SAGNN_EINVAL;
   if (mode < 0 || mode > 2) return SAGNN_EINVAL;
   if (!(f_in == 64 || f_in == 128 || f_in == 256) || fa.f_out <= 0 || fa.f_out > 256 || !fa.W) return SAGNN_EINVAL;
-  SweepFusedArgs fp = fa;
-  const int32_t NB = (fa.f_out + 31) / 32 * 32;
-  const int packs = f_in / 8 * NB / 256;     // at most 32
-  fp.Wp = ws + L.wpack;
-  fp.unfit = reinterpret_cast<const uint32_t*>(ws + L.wpack + 3 * 256 * 256 * 2);
-  fp.n_unfit = packs;
-  hipLaunchKernelGGL(sweep_pack_w_kernel, dim3((unsigned)packs), dim3(256), 0, s, fa.W, f_in, fa.f_out, NB,
-                     reinterpret_cast<__bf16*>(ws + L.wpack), mode == 1 ? 1 : 3, const_cast<uint32_t*>(fp.unfit));
-  SAGNN_LAUNCH_CHECK();
   if (d.groups == 2 || d.groups == 4) {
     // lane-group schedules: the same kernels as the product, with the dense transform compiled in
-    return sweep_launch(d, L, ws, B, ldb, 0, f_in, kmax, nullptr, f_in, 0, f_in, s, &fp, mode + 1);
+    SweepFusedArgs fg = fa;
+    fg.Wp = nullptr;
+    if (mode != 0) {
+      const int32_t NB = (fa.f_out + 31) / 32 * 32;
+      __bf16* wp = reinterpret_cast<__bf16*>(ws + L.wpack);
+      hipLaunchKernelGGL(sweep_pack_w_kernel, dim3((unsigned)ceil_div((int64_t)(f_in / 8) * NB, 256)), dim3(256), 0, s,
+                         fa.W, f_in, fa.f_out, NB, wp, mode == 2 ? 3 : 1);
+      SAGNN_LAUNCH_CHECK();
+      fg.Wp = wp;
+    }
+    return sweep_launch(d, L, ws, B, ldb, 0, f_in, kmax, nullptr, f_in, 0, f_in, s, &fg, mode + 1);
   }
   if (d.groups != 1) return SAGNN_EINVAL;
   SweepDims sd{};
@@ -2284,21 +2302,32 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   sd.row_bytes = (uint32_t)(ldb * 4);
   const unsigned blocks = (unsigned)(d.n_waves / 4);
   const size_t lds = (size_t)4 * kSweepSlots * (f_in + kPadRow + 1) * sizeof(float);   // (rows and their targets)
+  SweepFusedArgs fb = fa;
+  fb.Wp = nullptr;
+  if (mode != 0) {
+    const int32_t NB = (fa.f_out + 31) / 32 * 32;
+    __bf16* wp = reinterpret_cast<__bf16*>(ws + L.wpack);
+    hipLaunchKernelGGL(sweep_pack_w_kernel, dim3((unsigned)ceil_div((int64_t)(f_in / 8) * NB, 256)), dim3(256), 0, s,
+                       fa.W, f_in, fa.f_out, NB, wp, mode == 2 ? 3 : 1);
+    SAGNN_LAUNCH_CHECK();
+    fb.Wp = wp;
+  }
   // At 128 columns turns pay in the layer where rows of B are used often by rows that are resident together, and those are
   // not short.  us without and with, random columns, 200 k vertices of 30 (2.5 uses) to 40 columns 404, 400, 200 k of 60 (4.9)
   // 709, 663, 100 k of 40 (6.6) 205, 188, 350 k of 60 (2.8) to 128 1369, 1342; 300 k of 20 (1.1) to 128 526, 545, 275 k of 40
   // (2.4) 791, 804, 150 k of 24 (2.6) 311, 318; 1 M of 15 1341, 1381; communities, 1.6 M of 31 in bfloat16 3069, 2906, 700 k of
-  // 21 to 40 1024, 995.  Over 1100 MB as in the product.
-  const bool turns = (d.reuse >= 2.4f && (d.nnz >= 28 * d.m || d.fused_waves > 0)) || operand_bytes(kmax, f_in) > (1100ll << 20);
+  // 21 to 40 1024, 995, but to 128 1061, 1110.  Over 1100 MB as in the product.
+  const bool brief = mode != 0 || fa.f_out <= 64;
+  const bool turns = (d.reuse >= 2.4f && (d.nnz >= 28 * d.m || (brief && d.fused_waves > 0))) || operand_bytes(kmax, f_in) > (1100ll << 20);
   auto go = [&](auto kern) -> int {
     if (lds > 48 * 1024)
       SAGNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     // (two generations a launch for column groups, as sweep_launch, but at 128 columns only, where the order of the rows
-    // carries locality: 1.6 M vertices of 40 in communities, 128 to 128 in bfloat16 4042 -> 3795 us; random columns, 500 k of 24,
-    // 976 -> 1096.  At 64 and 256 the dense parts of workgroups that end together are left without gathers beside them:
-    // 803 -> 822, 3862 -> 4120.)
-    const unsigned per = f_in == 128 && d.fused_waves >= 4 ? (unsigned)(d.fused_waves / 4) : blocks;
+    // carries locality and the dense part is not long: 1.6 M vertices of 40 in communities to 40 columns in fp32 3950 -> 3718
+    // us, to 128 in bfloat16 4042 -> 3795, in fp32 4086 -> 4132; random columns, 500 k of 24, 976 -> 1096.  At 64 and 256 the
+    // dense parts of workgroups that end together are left without gathers beside them: 803 -> 822, 3862 -> 4120.)
+    const unsigned per = f_in == 128 && brief && d.fused_waves >= 4 ? (unsigned)(d.fused_waves / 4) : blocks;
     for (unsigned b0 = 0; b0 < blocks; b0 += per) {
       sd.block0 = (int32_t)b0;
       hipLaunchKernelGGL(kern, dim3(blocks - b0 < per ? blocks - b0 : per), dim3(256), lds, s,
@@ -2307,7 +2336,7 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
                          reinterpret_cast<const int32_t*>(ws + L.wave_base),
                          reinterpret_cast<const int32_t*>(ws + L.piece_target),
                          reinterpret_cast<const SpmmWsHeader*>(ws + L.header), B,
-                         reinterpret_cast<float*>(ws + L.partial), sd, fp);
+                         reinterpret_cast<float*>(ws + L.partial), sd, fb);
       SAGNN_LAUNCH_CHECK();
     }
     return SAGNN_OK;
@@ -2316,6 +2345,12 @@ int sweep_launch_fused(const SpmmHostDesc& d, const SpmmWsLayout& L, char* ws, c
   (mode == 2 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 2, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 2, TURN_>))   \
    : mode == 1 ? (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 1, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 1, TURN_>)) \
                : (buf ? go(spmm_sweep_fused_kernel<FPL_, 8, true, 0, TURN_>) : go(spmm_sweep_fused_kernel<FPL_, 8, false, 0, TURN_>)))
+  if (f_in == 256 && mode == 0) {   // (see Targets)
+    const int64_t b = operand_bytes(kmax, f_in);
+    if (d.reuse >= 2.f && (b <= (256ll << 20) || (b <= (768ll << 20) && d.nnz >= 36 * d.m)))
+      return buf ? go(spmm_sweep_fused_kernel<4, 8, true, 0, false, TARGETS_BEFORE>) : go(spmm_sweep_fused_kernel<4, 8, false, 0, false, TARGETS_BEFORE>);
+    return buf ? go(spmm_sweep_fused_kernel<4, 8, true, 0, false, TARGETS_BEHIND>) : go(spmm_sweep_fused_kernel<4, 8, false, 0, false, TARGETS_BEHIND>);
+  }
   if (f_in == 256) return SAGNN_SWF(4, false);   // (only two wavefronts share a SIMD)
   if (f_in == 128) return turns ? SAGNN_SWF(2, true) : SAGNN_SWF(2, false);
   return SAGNN_SWF(1, true);

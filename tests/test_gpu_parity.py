@@ -2009,9 +2009,8 @@ def test_gcn_layer_fwd_fused(prec, fin, fout, graph, cfg1):
 
 @pytest.mark.parametrize("groups,fin,fout", [("1", 64, 36), ("1", 128, 128), ("1", 256, 132), ("2", 64, 256), ("2", 128, 100)])
 def test_fp32_layer_with_values_that_three_terms_do_not_hold(groups, fin, fout, monkeypatch):
-    """fp32 operands of the sweep's epilogue go as three bfloat16 terms, tiles of rows of A H with an infinity, a NaN, a tiny or
-    a huge value, and all of them with such a value in W, in fp32 instructions: what the product and the dense transform of
-    a few rows, which is in fp32 instructions, give of the same rows of A H."""
+    """fp32 operands of the sweep's epilogue that a split into three bfloat16 terms would lose, rows of A H with an infinity, a
+    NaN, a tiny or a huge value, and such a value in W: what the product and the dense transform give of the same rows of A H."""
     monkeypatch.setenv("SAGNN_SWEEP", "1")
     monkeypatch.setenv("SAGNN_SWEEP_GROUPS", groups)
     g = synth.sbm_graph(6000, 16, 40, 2, 5)
@@ -2032,6 +2031,30 @@ def test_fp32_layer_with_values_that_three_terms_do_not_hold(groups, fin, fout, 
         bound = 2 * fin * 2.0 ** -24 * (T.double().abs() @ dev(W).double().abs())   # the error of either
         ok = torch.isfinite(Z0)
         assert bool(((Z.double() - Z0.double()).abs() <= bound + 1e-44)[ok].all())
+
+
+@pytest.mark.parametrize("groups,fin,fout", [("1", 64, 36), ("1", 128, 128), ("1", 256, 132), ("2", 128, 100), ("4", 64, 64)])
+def test_fp32_layer_rounds_a_sum_once_a_term_and_only_reads_a_schedule_without_split_rows(groups, fin, fout, monkeypatch):
+    """One value a column of W, small whole numbers in H: A H is exact, and an output is one product of it, which fp32
+    instructions round once.  No row is cut into pieces here, and W is read where it lies: nothing is written to the
+    workspace, so that two layers may share the schedule on streams of their own."""
+    monkeypatch.setenv("SAGNN_SWEEP", "1")
+    monkeypatch.setenv("SAGNN_SWEEP_GROUPS", groups)
+    g = synth.sbm_graph(6000, 16, 40, 2, 5)
+    rp, ci, v = dev(g.rowptr), dev(g.colidx), dev(np.ones_like(g.val))
+    H = dev(np.round(2.0 ** 14 * synth.uniform((g.n, fin), 3, synth.STREAM_H)).astype(np.float32))
+    W = np.zeros((fin, fout), np.float32)
+    W[np.arange(fout) * 7 % fin, np.arange(fout)] = synth.normal((fout,), 3, synth.STREAM_W)
+    ws = sagnn.spmm_csr_prepare(rp, ci, v, g.n, fin)
+    info = ws.info()
+    assert info["mode"] == 1 and info["chunk_rows"] == 0 and info["split_rows"] == 0
+    assert sagnn.gcn_layer_fwd_form(ws, fin, fout) == 2
+    before = ws.buf.clone()
+    _, Z, _ = sagnn.gcn_layer_fwd(rp, ci, v, H, dev(W), ws=ws, want_t=False, want_h=False)
+    assert torch.equal(ws.buf, before)
+    T = sagnn.spmm_csr_tallskinny(rp, ci, v, H)
+    assert torch.equal(T, T.round()) and float(T.abs().max()) < 2 ** 24
+    assert torch.equal(Z, (T.double() @ dev(W).double()).float())   # (24 bits by 24 in 53)
 
 
 @pytest.mark.parametrize("prec,fin,fout", [(0, 128, 128), (1, 256, 256), (0, 64, 36), (1, 128, 100), (1, 256, 64),
