@@ -61,9 +61,7 @@ enum {
 #define SAGNN_ACT_IDENTITY 0
 #define SAGNN_ACT_RELU 1
 
-#define SAGNN_GEMM_FP32 0 /* fp32 operands and sums: fp32 MFMA, or where it is faster the exact three-term
-                             split below with fp32 MFMA for the rows it does not hold (infinities,
-                             magnitudes under 2^-100 or over 2^60), no further from 64 bits */
+#define SAGNN_GEMM_FP32 0 /* fp32 operands, fp32 MFMA                          */
 #define SAGNN_GEMM_BF16 1 /* operands rounded to bfloat16 (RNE), fp32 accumulate */
 #define SAGNN_GEMM_FP32_BF16X3 2 /* fp32 operands (finite, below 2^127), each split exactly into three
                                    bfloat16 terms (round to nearest, remainder, remainder); the six

@@ -12,7 +12,7 @@ INCLUDE = os.path.join(os.path.dirname(_HERE), "include")
 LIB = os.path.join(_HERE, "libsagnn.so")
 MARSHAL = os.path.join(_HERE, "_marshal.so")     # csrc/marshal.c, the calls of binding.py
 OBJDIR = os.path.join(_HERE, "_build")
-SOURCES = ["api.hip", "pack.hip", "plan.hip", "spmm.hip", "spmm_flat.hip", "spmm_sweep.hip", "gemm_nn_bf16.hip", "gemm_nn_fp32.hip", "gemm_nn_bf16x3.hip", "gemm_nn_guarded.hip", "gemm.hip", "stages.hip", "radix.hip",
+SOURCES = ["api.hip", "pack.hip", "plan.hip", "spmm.hip", "spmm_flat.hip", "spmm_sweep.hip", "gemm_nn_bf16.hip", "gemm_nn_fp32.hip", "gemm_nn_bf16x3.hip", "gemm.hip", "stages.hip", "radix.hip",
            "fused.hip", "permute.hip", "sweep_plan.hip", "tiles.hip"]
 HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "rowload.h"), os.path.join(CSRC, "gemm.h"),
            os.path.join(CSRC, "gemm_nn.h"), os.path.join(INCLUDE, "sagnn.h")]

@@ -19,23 +19,6 @@ __device__ __forceinline__ void split3(float x, __bf16& t1, __bf16& t2, __bf16& 
   t3 = (__bf16)(r - (float)t2);
 }
 
-// What SAGNN_GEMM_FP32 runs where the bfloat16 instructions are faster: the three terms, and the fp32 instructions for a tile
-// of 32 rows with a value that the terms do not hold (or all tiles, if it is one of W).
-constexpr int kGemmGuarded = 3;
-
-// Values that the three terms and their products hold as well as fp32 does: zero, and magnitudes of 2^-100 to 2^60.  The last
-// term of a smaller one would end below bfloat16's smallest; sums of 256 products of larger ones may overflow in an order of
-// their own, and an infinity has no terms.  (A NaN counts as held: its row of the result is NaN either way.)
-struct SplitRange {
-  float high = 0.f;
-  uint32_t low = 0xFFFFFFFFu;   // least of the magnitudes' bits, twice and minus one: zero is the greatest
-  __device__ __forceinline__ void see(float x) {
-    high = fmaxf(high, fabsf(x));
-    low = min(low, (__builtin_bit_cast(uint32_t, x) << 1) - 1u);
-  }
-  __device__ __forceinline__ bool fits() const { return high < 0x1p60f && low >= ((127u - 100u) << 24) - 1u; }
-};
-
 struct GemmArgs {
   const float* X; int64_t ldx;
   const float* W; int64_t ldw; int32_t transW;
@@ -57,7 +40,6 @@ inline size_t nn_slab_bytes(int32_t kdim, int nt, int prec) {
 // nt: 32-column tiles of the slab (1, 2, 4; bf16 also 8)
 int gemm_nn_fp32(int nt, const GemmArgs& g, hipStream_t s);
 int gemm_nn_bf16(int nt, const GemmArgs& g, hipStream_t s);
-int gemm_nn_guarded(int nt, const GemmArgs& g, hipStream_t s);
 int gemm_nn_bf16x3(int nt, const GemmArgs& g, hipStream_t s);
 
 }  // namespace sagnn

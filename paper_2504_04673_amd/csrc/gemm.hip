@@ -535,27 +535,6 @@ int launch_gemm_tn(const float* X, int64_t ldx, const float* S, int64_t lds_, in
   return SAGNN_OK;
 }
 
-// Where SAGNN_GEMM_FP32 runs as three bfloat16 terms (kGemmGuarded): fp32 instructions bound it, at 1/16 of the bfloat16 rate
-// and six for one, and the terms' sums are nearer to exact at every shape, since an instruction adds sixteen products instead of
-// two (error against 64 bits, e-7, k = 16, 64, 128, 256 0.7, 1.4, 2.0, 2.9 and 0.3, 1.1, 1.6, 2.4).  us by fp32 instructions
-// and so, one output: 170 k rows 128 x 128 68, 51, 128 x 256 133, 98, 256 x 40 63, 46, 100 x 64 42, 36; 2 M 128 x 128 615, 475,
-// 100 x 64 553, 355, 64 x 48 251, 190; 52 k 96 x 96 22, 16, 256 x 256 89, 76.  Not
-// - up to 32 columns, which are read and written (170 k 128 x 32 23, 27; 1 M 48 x 24 69, 80), nor with short sums and few
-//   columns under 300 k rows (75 k 32 x 48 11, 13, 12 x 64 11, 12, 36 x 36 14, 15; 1 M 32 x 48 93, 73, 36 x 36 135, 88);
-// - under 50 k rows, whose time is the chain load - split - multiply - store (30 k 128 x 256 27, 34; 16 k 256 x 40 10, 14);
-// - from 65 k rows on, where a round of workgroups of eight wavefronts is full, to 85 k up to 128 columns (75 k 64 x 100 masked
-//   27, 34, 256 x 128 58, 62) and to 160 k up to 64 (68 k 64 x 48 14, 16; 135 k 64 x 64 21, 23);
-// - over 260 k rows where three planes of 128 columns do not fit the LDS and X is read once per 64 (1 M 256 x 100 601, 669,
-//   both outputs 646, 921; 256 x 256 1190, 1100, both 1268, 1259; but 250 k 256 x 128 167, 138).
-bool split_pays(int64_t row_tiles, int32_t kdim, int tiles) {
-  if (tiles < 2 || row_tiles < 1600) return false;
-  if (nn_slab_bytes(kdim, 4, kGemmGuarded) > 160 * 1024 && tiles > 2 && row_tiles > 8192) return false;
-  if (kdim < (tiles > 4 ? 40 : 64)) return row_tiles >= 9600;
-  if (row_tiles <= 2048 || tiles > 4) return true;
-  if (tiles == 2 && kdim <= 128) return row_tiles >= 5000;
-  return tiles == 2 || row_tiles >= 2600;
-}
-
 int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_t transW,
                 int64_t m, int32_t kdim, int32_t nout, int32_t prec, int32_t act,
                 const float* mask, int64_t ldmask, float* Z, int64_t ldz, float* A, int64_t lda,
@@ -577,14 +556,11 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
   g.nout = nout; g.act = act; g.mask = mask; g.ldmask = ldmask; g.Z = Z; g.ldz = ldz; g.A = A;
   g.lda = lda;
   const int tiles = (nout + 31) / 32;
-  // (an output that overlaps X: written tile by tile behind the reads of one launch, where the terms may take two)
-  auto apart = [&](const float* out, int64_t ld) {
-    return !out || out + (m - 1) * ld + nout <= X || X + (m - 1) * ldx + kdim <= out;
-  };
-  if (prec == SAGNN_GEMM_FP32 && split_pays((m + 31) / 32, kdim, tiles) && apart(Z, ldz) && apart(A, lda)) prec = kGemmGuarded;
+  // (fp32 is not run as three terms though these are faster from 50 k rows on, 170 k 128 x 256 135 us, 100: on an X with one
+  // value in 32 not zero they are twice as far from 64 bits, 4.4e-8, 7.7e-8; one value of W that they do not hold makes it 330;
+  // and a row's result would depend on how many rows there are and on those beside it)
   auto run = [&](int nt) {
     if (prec == SAGNN_GEMM_FP32) return gemm_nn_fp32(nt, g, s);
-    if (prec == kGemmGuarded) return gemm_nn_guarded(nt, g, s);
     return prec == SAGNN_GEMM_BF16 ? gemm_nn_bf16(nt, g, s) : gemm_nn_bf16x3(nt, g, s);
   };
   // 32-column tiles of the widest slab: all of W in one launch with rounded operands; 128 columns in fp32 and in three
@@ -611,9 +587,12 @@ int launch_gemm(const float* X, int64_t ldx, const float* W, int64_t ldw, int32_
   if (prec == SAGNN_GEMM_FP32) {
     if (tiles < 4 || (kdim > 128 && row_tiles <= 2048)) most = 1536;
     else if (kdim <= 128) most = 2560;
-  } else if (prec != SAGNN_GEMM_BF16) {
+  } else if (prec == SAGNN_GEMM_FP32_BF16X3) {
     most = kdim > 128 ? 1200 : 1536;
   }
+  auto apart = [&](const float* out, int64_t ld) {
+    return !out || out + (m - 1) * ld + nout <= X || X + (m - 1) * ldx + kdim <= out;
+  };
   if (row_tiles <= most && row_tiles * ((tiles + nt - 1) / nt) < enough && apart(Z, ldz) && apart(A, lda)) {
     while (nt > 1 && row_tiles * ((tiles + nt - 1) / nt) < enough) nt /= 2;
     g.slabs = (tiles + nt - 1) / nt;

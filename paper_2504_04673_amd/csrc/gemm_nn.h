@@ -16,11 +16,9 @@ namespace {
 // lane per column touched 64 lines per load).  Loads outside W are clamped into it, so no branch stands between them.
 // One element per thread and round trip before: 4096 x 256 x 256 bf16 40 -> 22 us as it lies, 44 -> 19 transposed;
 // 125 k rows 131 -> 93 and 119 -> 89.
-// Returns with kGemmGuarded: all values of this thread may be split.
 template <int NB, int PREC, int THREADS>
-__device__ __forceinline__ bool stage_w(const GemmArgs& g, int n0, char* smem, int kdim, int tid) {
-  constexpr bool SPLIT = PREC == SAGNN_GEMM_FP32_BF16X3 || PREC == kGemmGuarded;
-  SplitRange range;
+__device__ __forceinline__ void stage_w(const GemmArgs& g, int n0, char* smem, int kdim, int tid) {
+  constexpr bool SPLIT = PREC == SAGNN_GEMM_FP32_BF16X3;
   const int kreal = g.kdim;
   float* __restrict__ Wf = reinterpret_cast<float*>(smem);
   __bf16* __restrict__ Wp = reinterpret_cast<__bf16*>(smem);
@@ -45,10 +43,7 @@ __device__ __forceinline__ bool stage_w(const GemmArgs& g, int n0, char* smem, i
         const int n = u % NB, k0 = (u / NB) * 8;
         const bool in = n0 + n < g.nout;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          w[b][i] = in && k0 + i < kreal ? w[b][i] : 0.f;
-          if constexpr (PREC == kGemmGuarded) range.see(w[b][i]);
-        }
+        for (int i = 0; i < 8; ++i) w[b][i] = in && k0 + i < kreal ? w[b][i] : 0.f;
         if constexpr (PREC == SAGNN_GEMM_FP32) {
 #pragma unroll
           for (int i = 0; i < 8; ++i) Wf[(k0 + i) * NB + n] = w[b][i];
@@ -93,8 +88,6 @@ __device__ __forceinline__ bool stage_w(const GemmArgs& g, int n0, char* smem, i
         const int n = (u >> 3) % NB, k0 = ((u / (8 * NB)) * 8 + (u & 7)) * 4;
         const bool in = n0 + n < g.nout && k0 < kreal;
         const float x[4] = {in ? w[b].x : 0.f, in ? w[b].y : 0.f, in ? w[b].z : 0.f, in ? w[b].w : 0.f};
-        if constexpr (PREC == kGemmGuarded)
-          for (int i = 0; i < 4; ++i) range.see(x[i]);
         if constexpr (PREC == SAGNN_GEMM_FP32) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) Wf[(k0 + i) * NB + n] = x[i];
@@ -117,29 +110,6 @@ __device__ __forceinline__ bool stage_w(const GemmArgs& g, int n0, char* smem, i
     }
   }
   (void)Wf; (void)Wp;
-  return range.fits();
-}
-
-// A tile of kGemmGuarded once more, in fp32 instructions with W from memory: the sums of SAGNN_GEMM_FP32, in its order.
-template <int NT, typename Load>
-__device__ __forceinline__ void multiply_fp32(const GemmArgs& g, int n0, int kdim, int r, int h, Load ldx4, floatx16 (&acc)[NT]) {
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[nt][v] = 0.f;
-#pragma unroll 1
-  for (int k0 = 4 * h; k0 < kdim; k0 += 8) {
-    const float4 x = ldx4(k0);
-    const float xs[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int k = k0 + i, col = n0 + nt * 32 + r;
-        const float w = k < g.kdim && col < g.nout ? (g.transW ? g.W[(int64_t)col * g.ldw + k] : g.W[(int64_t)k * g.ldw + col]) : 0.f;
-        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[i], w, acc[nt], 0, 0, 0);
-      }
-  }
 }
 
 // KPAD: kdim need not be a multiple of 32, loads of X are clamped to the real k extent.
@@ -152,17 +122,14 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int NB = NT * 32;
   constexpr bool BF16 = PREC == SAGNN_GEMM_BF16;
-  constexpr bool GUARDED = PREC == kGemmGuarded;
-  constexpr bool SPLIT = PREC == SAGNN_GEMM_FP32_BF16X3 || GUARDED;
+  constexpr bool SPLIT = PREC == SAGNN_GEMM_FP32_BF16X3;
   const int tid = threadIdx.x;
   const int kreal = g.kdim;                  // any multiple of 4
   const int kdim = (kreal + 31) & ~31;       // the k loop runs over the zero-padded extent
 
   const int n0 = g.n0 + (int)blockIdx.y * NB;   // first column of this workgroup's slab
-  const bool w_fits = stage_w<NB, PREC, WAVES * 64>(g, n0, smem, kdim, tid);
-  bool all_fits = true;                      // (all of the slab)
-  if constexpr (GUARDED) all_fits = __syncthreads_and(w_fits);
-  else __syncthreads();
+  stage_w<NB, PREC, WAVES * 64>(g, n0, smem, kdim, tid);
+  __syncthreads();
 
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, h = lane >> 5;
@@ -199,7 +166,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
       const int plane = (kdim >> 3) * NB;      // bf16x8 elements per term plane
       constexpr int JB = 2;
       const int ngroups = NG > 0 ? NG : kdim / (16 * JB);
-      SplitRange range;
       float4 cur[JB][2], nxt[JB][2];
 #pragma unroll
       for (int q = 0; q < JB; ++q) {
@@ -225,7 +191,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             __bf16 t1, t2, t3;
-            if constexpr (GUARDED) range.see(xs[i]);
             split3(xs[i], t1, t2, t3);
             a1[i] = t1; a2[i] = t2; a3[i] = t3;
           }
@@ -248,8 +213,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_nn_kernel(const GemmArgs g) {
           cur[q][1] = nxt[q][1];
         }
       }
-      if constexpr (GUARDED)
-        if (!all_fits || __any(!range.fits())) multiply_fp32<NT>(g, n0, kdim, r, h, ldx4, acc);
     } else if (BF16) {
       const bf16x8* __restrict__ Ws = reinterpret_cast<const bf16x8*>(smem);
       constexpr int JB = 2;

@@ -1783,16 +1783,16 @@ def test_bf16x3_gemm_has_the_accuracy_of_the_fp32_gemm(k, n):
 
 @pytest.mark.parametrize("m,k,n,transW", [(51_203, 64, 64, False), (51_203, 100, 68, True), (53_001, 256, 132, False), (70_001, 160, 40, False),
                                           (90_001, 128, 128, True), (170_003, 128, 40, False), (70_001, 40, 256, False), (307_203, 8, 36, True)])
-def test_fp32_gemm_in_three_terms_and_the_tiles_they_do_not_hold(m, k, n, transW):
-    """Row counts at which fp32 products run as three bfloat16 terms: no further from 64 bits than fp32 instructions, which
-    the same rows in a call of few rows take; a tile with an infinity, a tiny or a huge value, or all tiles of its columns if
-    it is in W, gives bit for bit what they give; a row with a NaN is NaN, and no other."""
+def test_fp32_gemm_of_many_rows_with_values_that_three_terms_do_not_hold(m, k, n, transW):
+    """Products of many rows are no further from 64 bits than those of few; a tile with an infinity, a tiny or a huge value, or
+    all tiles of its columns if it is in W, gives bit for bit what a call of few rows gives; a row with a NaN is NaN, and no
+    other."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(m + k)
     X = torch.randn(m, k, device="cuda", generator=gen)
     W = torch.randn(k, n, device="cuda", generator=gen) / k ** 0.5
     M = torch.randn(m, n, device="cuda", generator=gen)
-    few = 640                                       # rows of a call in fp32 instructions, whole tiles
+    few = 640                                       # whole tiles
     odd = {3: float("inf"), 40: 1e-31, 100: 3e38, 140: -1e-42, m - 1: 2.0 ** 61}
     run = lambda x, w, mask: sagnn.dense_gemm_act(x, w.t().contiguous() if transW else w, transW=transW, mask=mask, want_z=True)[0]
     for mask in (None, M):
@@ -1823,6 +1823,33 @@ def test_fp32_gemm_in_three_terms_and_the_tiles_they_do_not_hold(m, k, n, transW
         V[k - 1, n - 1] = x
         a, b = (z[:, (n - 1) // 32 * 32:] for z in (run(X, V, None)[:few], run(X[:few], V, None)))
         assert bool(((a == b) | (torch.isnan(a) & torch.isnan(b))).all()), x
+
+
+@pytest.mark.parametrize("m,k,n,transW", [(51_203, 64, 64, False), (53_001, 256, 132, False), (70_001, 160, 40, False),
+                                          (90_001, 128, 128, True), (70_001, 40, 256, False), (307_203, 8, 36, True)])
+def test_fp32_gemm_rounds_once_a_term_and_row_by_row(m, k, n, transW):
+    """One value a row of X: an output is one product, which fp32 instructions round once.  And a row's result is its own:
+    bit for bit the same in a call of other rows, of few or many, and beside a row with an infinity, an underflowed and a
+    huge value."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + n)
+    X = torch.randn(m, k, device="cuda", generator=gen)
+    W = torch.randn(k, n, device="cuda", generator=gen) / k ** 0.5
+    run = lambda x: sagnn.dense_gemm_act(x, W.t().contiguous() if transW else W, transW=transW, want_z=True)[0]
+    one = torch.zeros_like(X)
+    at = torch.randint(k, (m, 1), device="cuda", generator=gen)
+    one.scatter_(1, at, X.gather(1, at))
+    assert torch.equal(run(one), (X.gather(1, at).double() * W.double()[at[:, 0]]).float())   # (24 bits by 24 in 53)
+    Z = run(X)
+    for a, b in ((0, 1), (17, 700), (700, 51_100), (51_100, m)):
+        assert torch.equal(run(X[a:b]), Z[a:b]), (a, b)
+    Y = X.clone()
+    odd = [5, 640, m - 2]
+    for r, x in zip(odd, (float("inf"), 1e-41, 3e38)):
+        Y[r, r % k] = x
+    rest = torch.ones(m, dtype=torch.bool, device="cuda")
+    rest[odd] = False
+    assert torch.equal(run(Y)[rest], Z[rest])
 
 
 def test_bf16_gemm_is_tight_against_bf16_rounded_oracle():
