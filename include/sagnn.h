@@ -508,7 +508,8 @@ int spmm_csr_transpose(const int32_t* d_rowptr, const int32_t* d_colidx, const f
  *               part by old id: a stable sort, so the result is unique)
  *   d_inv[v]  = new id of old vertex v
  *   h_part_off[0..n_parts] (host): part q owns new ids [h_part_off[q], h_part_off[q+1])
- * n_parts <= 1024.  SAGNN_EFORMAT if a label is out of range.
+ * n_parts <= 1024.  SAGNN_EFORMAT if a label is out of range.  Either order may take the labels' place
+ * (d_perm or d_inv over d_labels).
  *
  * spmm_csr_permute_symmetric: B = P A P^T for the square CSR matrix A (n x n):
  *   B[d_inv[r], d_inv[c]] = A[r, c].  Rows of B come out with ascending column ids (entries

@@ -379,9 +379,11 @@ SAGNN_EXPORT int spmm_perm_from_labels(const int32_t* d_labels, int64_t n, int32
   int bits = 1;
   while ((1 << bits) < n_parts) ++bits;
   int32_t h[1026];
-  if (bits <= 8) {
+  auto apart = [&](const int32_t* out) { return out + n <= d_labels || d_labels + n <= out; };
+  if (bits <= 8 && apart(d_perm) && apart(d_inv)) {
     // one pass, which writes both orders; the offsets are sums of its totals (500 k labels of 16: sorted pairs, offsets and
-    // orders by kernels of their own 26 us, now 18)
+    // orders by kernels of their own 26 us, now 18).  Its tiles are written while others still read their labels: an order
+    // that takes the labels' place is written behind the sort.
     SAGNN_HIP(hipMemsetAsync(rw.totals + 256, 0, sizeof(int32_t), s));
     rc = radix_order(reinterpret_cast<const uint32_t*>(d_labels), n, bits, rw, d_perm, d_inv, s, n_parts);
     if (rc != SAGNN_OK) return rc;

@@ -1,5 +1,7 @@
 """GPU parity of the entry points around the 1.5D stage loop: sparsity-oblivious plan,
 column-block split, stage loop (one and two streams) and volume statistics, against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -408,6 +410,27 @@ def test_order_from_labels_at_the_edges_of_its_tiles(n, parts):
     labels[n // 2] = parts
     with pytest.raises(sagnn.SagnnError):
         sagnn.spmm_perm_from_labels(dev(labels), parts)
+
+
+@pytest.mark.parametrize("over", ["perm", "inv", "both_ends"])
+@pytest.mark.parametrize("n,parts", [(5000, 16), (300_001, 3), (4_300_001, 256), (70_000, 300)])
+def test_order_from_labels_in_the_labels_own_buffer(n, parts, over):
+    """An order written over the labels that it is made from, whole or in part, by the C entry point: one pass writes its tiles
+    while others still read theirs."""
+    labels = np.random.default_rng(n).integers(0, parts, size=n).astype(np.int32)
+    operm, oinv, ooff = oracle.perm_from_labels(labels, parts)
+    nbytes = ctypes.c_size_t(0)
+    assert sagnn.lib().spmm_permute_workspace_bytes(n, n, ctypes.byref(nbytes)) == 0
+    ws = torch.empty(nbytes.value, dtype=torch.uint8, device="cuda")
+    room = torch.zeros(3 * n, dtype=torch.int32, device="cuda")       # the labels lie in the middle
+    room[n:2 * n] = dev(labels)
+    place = {"perm": (n, 2 * n), "inv": (0, n), "both_ends": (1, 2 * n - 1)}[over]
+    perm, inv = (room[p:p + n] for p in place)
+    off = np.zeros(parts + 1, np.int64)
+    rc = sagnn.lib().spmm_perm_from_labels(room[n:].data_ptr(), n, parts, perm.data_ptr(), inv.data_ptr(), off.ctypes.data,
+                                           ws.data_ptr(), nbytes.value, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and np.array_equal(off, ooff)
+    assert np.array_equal(perm.cpu().numpy(), operm) and np.array_equal(inv.cpu().numpy(), oinv)
 
 
 def test_reorder_rejects_bad_labels_and_maps():
