@@ -1,5 +1,5 @@
-/* Calls into libsagnn.so from Python: a bound function takes integers, and for a pointer also None or an object with a buffer
- * (a host array), and returns the C function's int.  Every exported call of the step has only integers and pointers, which go in the same registers and stack
+/* Calls into libsagnn.so from Python: a bound function takes integers (for a pointer Python's own, None, or an object with a
+ * buffer, a host array), and returns the C function's int.  Every exported call of the step has only integers and pointers, which go in the same registers and stack
  * slots whatever their width (System V x86-64), so that one call by address serves all of them.  ctypes converts an argument
  * at a time through its type objects: a call of 17 arguments 1.7 us, this way 0.3, of 7.5 for a whole launch. */
 #define PY_SSIZE_T_CLEAN
@@ -32,6 +32,11 @@ static PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t n) {
   for (Py_ssize_t i = 0; i < n; ++i) {
     if (PyLong_Check(args[i])) {
       v[i] = (I)PyLong_AsUnsignedLongLongMask(args[i]);
+    } else if (b->kind[i] == 'i' && PyIndex_Check(args[i])) {
+      PyObject* number = PyNumber_Index(args[i]);   /* (an integer of numpy or torch; an array of several has none) */
+      if (!number) goto end;
+      v[i] = (I)PyLong_AsUnsignedLongLongMask(number);
+      Py_DECREF(number);
     } else if (b->kind[i] == 'p' && args[i] == Py_None) {
       continue;
     } else if (b->kind[i] == 'p' && n_views < MOST_VIEWS && PyObject_CheckBuffer(args[i])) {

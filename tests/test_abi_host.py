@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2504_04673_amd as sagnn
 from paper_2504_04673_amd import binding
@@ -237,7 +238,11 @@ def test_step_calls_by_address_take_what_the_declared_ones_take():
         for x in (0, 1, 4, -1, 1 << 40):          # all of them invalid calls: no pointer is given
             args = [a if a is None else x for a in none]
             assert bound(*args) == declared(*args), (name, x)
+        for x in (np.int64(3), np.int32(-1), np.uint8(4), np.array(2), torch.tensor(1), True):
+            args = [a if a is None else x for a in none]
+            assert bound(*args) == declared(*args), (name, x)
         for args in (none[:-1], none + [0], [], [1.0 if a is None else a for a in none], ["" for a in none],
+                     [a if a is None else np.array([1, 2]) for a in none], [a if a is None else 2.0 for a in none],
                      [0 if t is ctypes.c_void_p else None for t in declared.argtypes]):
             with pytest.raises(TypeError):
                 bound(*args)

@@ -286,6 +286,20 @@ def test_plan_identity_written_by_several_column_ranges(n, nnz):
             ci[at] = keep
 
 
+def test_step_calls_take_numbers_of_numpy():
+    """Sizes and options as they come out of a host array, the block boundaries that the plan itself takes among them."""
+    g = synth.er_graph(4096, 8, 0)
+    blk = synth.block_offsets(g.n, 4)
+    rp, ci, v = dev(g.rowptr), dev(g.colidx), dev(g.val)
+    plan, same = (sagnn.spmm_plan_needed_rows(rp, ci, n, blk) for n in (blk[-1], g.n))
+    assert isinstance(blk[-1], np.int64) and plan.N == same.N and torch.equal(plan.needed, same.needed)
+    X, W = dev(synth.normal((g.n, 32), 0, synth.STREAM_H)), dev(synth.normal((32, 16), 0, synth.STREAM_W))
+    options = np.array([0, sagnn.GEMM_BF16, sagnn.ACT_RELU], dtype=np.int32)
+    for a, b in zip(sagnn.dense_gemm_act(X, W, transW=options[0], prec=options[1], act=options[2]),
+                    sagnn.dense_gemm_act(X, W, prec=sagnn.GEMM_BF16, act=sagnn.ACT_RELU)):
+        assert a is b or torch.equal(a, b)
+
+
 def test_plan_empty_matrix_and_capacity_and_validate():
     rp = np.zeros(6, np.int32)
     plan = sagnn.spmm_plan_needed_rows(dev(rp), torch.empty(0, dtype=torch.int32, device="cuda"), 100,
