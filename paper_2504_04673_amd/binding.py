@@ -159,6 +159,10 @@ def lib():
     return _lib
 
 
+class ArgumentError(ctypes.ArgumentError, TypeError):
+    """An argument of a call that is none, as ctypes refuses it."""
+
+
 _bound = None
 # the calls of a step: integers and pointers only
 STEP_CALLS = ("spmm_plan_needed_rows", "spmm_pack_rows", "spmm_csr_tallskinny", "dense_gemm_act", "gcn_layer_fwd", "gcn_layer_bwd")
@@ -174,7 +178,8 @@ def _calls():
         from . import _marshal
         _bound = types.SimpleNamespace(**{
             name: _marshal.bind(ctypes.cast(getattr(L, name), ctypes.c_void_p).value,
-                                "".join("p" if t is ctypes.c_void_p else "i" for t in getattr(L, name).argtypes))
+                                "".join("p" if t is ctypes.c_void_p else "i" for t in getattr(L, name).argtypes),
+                                ArgumentError)
             for name in STEP_CALLS})
     return _bound
 

@@ -17,6 +17,7 @@ typedef int64_t I;
 typedef int (*Fn)(I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I, I);
 typedef struct {
   Fn fn;
+  PyObject* error;   /* raised for an argument that is none */
   Py_ssize_t n;
   char kind[MOST];   /* 'p' a pointer, 'i' an integer */
 } Bound;
@@ -34,18 +35,23 @@ static PyObject* call(PyObject* self, PyObject* const* args, Py_ssize_t n) {
       v[i] = (I)PyLong_AsUnsignedLongLongMask(args[i]);
     } else if (b->kind[i] == 'i' && PyIndex_Check(args[i])) {
       PyObject* number = PyNumber_Index(args[i]);   /* (an integer of numpy or torch; an array of several has none) */
-      if (!number) goto end;
+      if (!number) goto refuse;
       v[i] = (I)PyLong_AsUnsignedLongLongMask(number);
       Py_DECREF(number);
     } else if (b->kind[i] == 'p' && args[i] == Py_None) {
       continue;
     } else if (b->kind[i] == 'p' && n_views < MOST_VIEWS && PyObject_CheckBuffer(args[i])) {
-      if (PyObject_GetBuffer(args[i], &views[n_views], PyBUF_SIMPLE)) goto end;
-      v[i] = (I)(uintptr_t)views[n_views++].buf;
+      if (PyObject_GetBuffer(args[i], &views[n_views], PyBUF_ND)) goto refuse;
+      if (views[n_views++].ndim == 0) goto refuse;   /* (a number of numpy is no array) */
+      v[i] = (I)(uintptr_t)views[n_views - 1].buf;
     } else {
-      PyErr_Format(PyExc_TypeError, "argument %zd: an integer expected, or None or a buffer for a pointer", i + 1);
-      goto end;
+      goto refuse;
     }
+    continue;
+  refuse:
+    PyErr_Clear();
+    PyErr_Format(b->error, "argument %zd: an integer expected, or None or an array for a pointer", i + 1);
+    goto end;
   }
   Py_BEGIN_ALLOW_THREADS
   rc = b->fn(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10], v[11], v[12], v[13], v[14], v[15], v[16], v[17],
@@ -59,22 +65,30 @@ end:
 
 static PyMethodDef call_def = {"call", (PyCFunction)(void (*)(void))call, METH_FASTCALL, "the bound C function"};
 
-static void drop(PyObject* capsule) { free(PyCapsule_GetPointer(capsule, NULL)); }
+static void drop(PyObject* capsule) {
+  Bound* b = (Bound*)PyCapsule_GetPointer(capsule, NULL);
+  Py_DECREF(b->error);
+  free(b);
+}
 
 static PyObject* bind(PyObject* self, PyObject* args) {
   unsigned long long address;
   const char* kinds;
+  PyObject* error;
   Py_ssize_t n;
   (void)self;
-  if (!PyArg_ParseTuple(args, "Ks#", &address, &kinds, &n)) return NULL;
+  if (!PyArg_ParseTuple(args, "Ks#O", &address, &kinds, &n, &error)) return NULL;
   if (!address || n > MOST) return PyErr_Format(PyExc_ValueError, "no address, or more than %d parameters", MOST);
   Bound* b = (Bound*)malloc(sizeof(Bound));
   if (!b) return PyErr_NoMemory();
   b->fn = (Fn)(uintptr_t)address;
+  b->error = error;
+  Py_INCREF(error);
   b->n = n;
   for (Py_ssize_t i = 0; i < n; ++i) b->kind[i] = kinds[i];
   PyObject* capsule = PyCapsule_New(b, NULL, drop);
   if (!capsule) {
+    Py_DECREF(error);
     free(b);
     return NULL;
   }
@@ -84,6 +98,6 @@ static PyObject* bind(PyObject* self, PyObject* args) {
 }
 
 static PyMethodDef methods[] = {
-    {"bind", bind, METH_VARARGS, "bind(address, kinds) -> callable; kinds: a letter per parameter, p pointer, i integer"}, {NULL, NULL, 0, NULL}};
+    {"bind", bind, METH_VARARGS, "bind(address, kinds, error) -> callable; kinds: a letter per parameter, p pointer, i integer; error: raised for another argument"}, {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", NULL, -1, methods, NULL, NULL, NULL, NULL};
 PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }

@@ -246,6 +246,16 @@ def test_step_calls_by_address_take_what_the_declared_ones_take():
                      [0 if t is ctypes.c_void_p else None for t in declared.argtypes]):
             with pytest.raises(TypeError):
                 bound(*args)
+        for bad in (1.0, None, np.int64(0), np.array(0), torch.tensor(0)):              # each in each place, refused alike
+            for i, t in enumerate(declared.argtypes):
+                args = none[:i] + [bad] + none[i + 1:]
+                try:
+                    expected = declared(*args)
+                except ctypes.ArgumentError:
+                    with pytest.raises(ctypes.ArgumentError):
+                        bound(*args)
+                else:
+                    assert bound(*args) == expected, (name, i, bad)
     # host arrays: block boundaries that begin at 0, ascend and end at n (what is refused then is the missing row pointer) or not
     for blocks in ([0, 3, 8], [1, 3, 8], [0, 3, 9], [0, 9, 8]):
         a, out = np.array(blocks, dtype=np.int64), np.zeros(3, dtype=np.int64)
