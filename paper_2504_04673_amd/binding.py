@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 import types
 from dataclasses import dataclass
@@ -168,19 +169,28 @@ _bound = None
 STEP_CALLS = ("spmm_plan_needed_rows", "spmm_pack_rows", "spmm_csr_tallskinny", "dense_gemm_act", "gcn_layer_fwd", "gcn_layer_bwd")
 
 
+def _extension():
+    """csrc/marshal.c as built for this interpreter; None where it is not."""
+    try:
+        return importlib.import_module(f"{__package__}._marshal") if os.path.exists(_build.MARSHAL) else None
+    except ImportError:
+        return None
+
+
+def _by_ctypes(function):
+    """A declared function that takes host arrays for pointers, as the bound ones do."""
+    return lambda *args: function(*[_host(a) if isinstance(a, np.ndarray) and a.ndim else a for a in args])
+
+
 def _calls():
-    """The calls of a step by address (csrc/marshal.c), with the parameters that lib() declares."""
+    """The calls of a step, with the parameters that lib() declares: by address (csrc/marshal.c), or through ctypes."""
     global _bound
     if _bound is None:
-        L = lib()
-        if not os.path.exists(_build.MARSHAL):
-            _build.build_marshal()
-        from . import _marshal
+        L, ext = lib(), _extension()
         _bound = types.SimpleNamespace(**{
-            name: _marshal.bind(ctypes.cast(getattr(L, name), ctypes.c_void_p).value,
-                                "".join("p" if t is ctypes.c_void_p else "i" for t in getattr(L, name).argtypes),
-                                ArgumentError)
-            for name in STEP_CALLS})
+            name: ext.bind(ctypes.cast(getattr(L, name), ctypes.c_void_p).value,
+                           "".join("p" if t is ctypes.c_void_p else "i" for t in getattr(L, name).argtypes), ArgumentError)
+            if ext else _by_ctypes(getattr(L, name)) for name in STEP_CALLS})
     return _bound
 
 

@@ -4,13 +4,16 @@ from __future__ import annotations
 import os
 import subprocess
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(_HERE), "include")
 LIB = os.path.join(_HERE, "libsagnn.so")
-MARSHAL = os.path.join(_HERE, "_marshal.so")     # csrc/marshal.c, the calls of binding.py
+# csrc/marshal.c, the calls of binding.py: for one interpreter's headers, which its name carries
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.c")
+MARSHAL = os.path.join(_HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJDIR = os.path.join(_HERE, "_build")
 SOURCES = ["api.hip", "pack.hip", "plan.hip", "spmm.hip", "spmm_flat.hip", "spmm_sweep.hip", "gemm_nn_bf16.hip", "gemm_nn_fp32.hip", "gemm_nn_bf16x3.hip", "gemm.hip", "stages.hip", "radix.hip",
            "fused.hip", "permute.hip", "sweep_plan.hip", "tiles.hip"]
@@ -33,7 +36,11 @@ def stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    return not os.path.exists(MARSHAL) or any(os.path.getmtime(d) > t for d in sources() + HEADERS)
+    return any(os.path.getmtime(d) > t for d in sources() + HEADERS) or marshal_stale()
+
+
+def marshal_stale() -> bool:
+    return not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL_SOURCE) > os.path.getmtime(MARSHAL)
 
 
 def _run(cmd, verbose):
@@ -62,11 +69,23 @@ def build_hip(verbose: bool = False, incremental: bool = False, jobs: int = 8) -
     with ThreadPoolExecutor(max_workers=max(1, jobs)) as ex:
         list(ex.map(lambda c: _run(c, verbose), todo))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
-    build_marshal(verbose)
+    try:
+        build_marshal(verbose)
+    except (OSError, RuntimeError) as e:      # no C compiler, headers or x86-64: binding.py has ctypes then
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)                # (of another source)
+        warnings.warn(f"calls go through ctypes: {e}")
     return LIB
 
 
 def build_marshal(verbose: bool = False) -> str:
-    _run([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", MARSHAL,
-          os.path.join(CSRC, "marshal.c")], verbose)
+    """Compiled beside its place and moved there whole: another process may be loading it."""
+    part = f"{MARSHAL}.{os.getpid()}"
+    try:
+        _run([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", part,
+              MARSHAL_SOURCE], verbose)
+        os.replace(part, MARSHAL)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
     return MARSHAL

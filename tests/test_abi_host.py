@@ -4,13 +4,14 @@ import ctypes
 import os
 import random
 import re
+import sysconfig
 
 import numpy as np
 import pytest
 import torch
 
 import paper_2504_04673_amd as sagnn
-from paper_2504_04673_amd import binding
+from paper_2504_04673_amd import binding, build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -265,3 +266,45 @@ def test_step_calls_by_address_take_what_the_declared_ones_take():
         assert (rc == -3) == (blocks != [0, 3, 8]) and rc < 0
     with pytest.raises((TypeError, BufferError, ValueError)):
         calls.spmm_plan_needed_rows(*[np.zeros((4, 4), dtype=np.int64)[:, 1] if i == 5 else x for i, x in enumerate(args)])
+
+
+def test_step_calls_without_their_extension_go_through_ctypes(monkeypatch):
+    """Not built for this interpreter: the same results, host arrays in a pointer's place among the arguments."""
+    by_address = binding._calls()
+    monkeypatch.setattr(binding, "_bound", None)
+    monkeypatch.setattr(build, "MARSHAL", build.MARSHAL + ".none")
+    calls = binding._calls()
+    assert calls is not by_address
+    for name in binding.STEP_CALLS:
+        for x in (0, 4, -1, np.int64(3)):             # all of them invalid calls: no pointer is given
+            args = [None if t is ctypes.c_void_p else x for t in getattr(sagnn.lib(), name).argtypes]
+            assert getattr(calls, name)(*args) == getattr(by_address, name)(*args), (name, x)
+        for bad in (1.0, np.int64(0)):
+            with pytest.raises(ctypes.ArgumentError):
+                getattr(calls, name)(*[bad if a is None else a for a in args])
+    for blocks in ([0, 3, 8], [1, 3, 8]):
+        a, out = np.array(blocks, dtype=np.int64), np.zeros(3, dtype=np.int64)
+        args = [1 << 12, 1 << 12, 1, 8, 0, a, 2, 1 << 12, 8, out, None, None, 0, 0, None]
+        assert calls.spmm_plan_needed_rows(*args) == by_address.spmm_plan_needed_rows(*args) < 0
+
+
+def test_extension_of_the_calls_is_built_for_this_interpreter_and_moved_into_place(monkeypatch, tmp_path):
+    """Its name carries the interpreter's; it is out of date with its source; where there is no compiler the library is built
+    without it, and none of another source is left behind."""
+    assert build.MARSHAL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    source, out = tmp_path / "marshal.c", str(tmp_path / os.path.basename(build.MARSHAL))
+    source.write_text(open(build.MARSHAL_SOURCE).read())
+    monkeypatch.setattr(build, "MARSHAL_SOURCE", str(source))
+    monkeypatch.setattr(build, "MARSHAL", out)
+    assert build.marshal_stale()
+    assert build.build_marshal() == out and not build.marshal_stale()
+    assert sorted(os.listdir(tmp_path)) == sorted(["marshal.c", os.path.basename(out)])
+    os.utime(source, (os.path.getmtime(out) + 1,) * 2)
+    assert build.marshal_stale() and build.stale()
+    monkeypatch.setattr(build, "SOURCES", [])                        # (nothing but this to build)
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "lib.so"))
+    monkeypatch.setenv("HIPCC", "true")
+    monkeypatch.setenv("CC", str(tmp_path / "no_compiler"))
+    with pytest.warns(UserWarning, match="ctypes"):
+        build.build_hip()
+    assert os.listdir(tmp_path) == ["marshal.c"]
