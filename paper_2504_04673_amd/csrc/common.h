@@ -197,10 +197,13 @@ inline SpmmWsLayout spmm_ws_layout(int64_t m, int64_t nnz, int32_t f) {
   L.max_multi_rows = cuts + 1;
   L.max_multi_pieces = partial_floats / f;   // (at least twice the cuts at width f, and 2)
   // sweep streams + gap + short CSR entries + padding.  A wavefront's stream is padded to the
-  // batch of 8 steps at every interval boundary; with lane groups (up to 4 zipped streams per
+  // batch of 8 steps at every interval boundary; with lane groups (2 to 16 zipped streams per
   // wavefront) also to the longest of its group streams inside every interval.  If a pattern
   // needs more than this, the planner lays the streams out as one interval.  A whole-row
-  // wavefront has one interval: at most 8 steps of padding for each of its up to 4 group streams.
+  // wavefront has one interval, and short rows of like length: with up to 4 group streams at most
+  // 8 steps of padding for each, 32 words; 8 and 16 streams (up to 128 words) sweep short rows whole
+  // only where the rest of the room takes that, and if the long rows' padding has filled it the
+  // planner starts over with the short rows beside the sweep.  What fits neither way is not swept.
   L.stream_cap = nnz + nnz / 4 + 256 * long_waves + 32 * short_waves + 1024;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };

@@ -1106,6 +1106,40 @@ def test_spmm_narrow_sweep_short_rows_as_whole_rows(f, monkeypatch):
         assert_close(got[~hit], ref[~hit], zabs[~hit], RTOL_SPMM, f"f={f} beside infinite rows")
 
 
+@pytest.mark.parametrize("f,longest", [(16, range(600, 1800, 40)), (24, range(1600, 3600, 60)), (32, range(1600, 3600, 60))])
+def test_spmm_narrow_sweep_where_padded_short_rows_do_not_fit(f, longest, monkeypatch):
+    """The streams of eight and sixteen lane groups are padded to the longest of a wavefront, here by one long row more and
+    more.  Short rows are swept whole, then, where their padding is what no longer fits, the preparation is made again with
+    them beside the sweep, then nothing is swept.  The second preparation is the one without whole short rows, bit for bit."""
+    monkeypatch.setenv("SAGNN_SWEEP", "1")
+    monkeypatch.setenv("SAGNN_SWEEP_MINDEG", "64")
+    monkeypatch.setenv("SAGNN_SWEEP_GROUPS", "2")
+    rng = np.random.default_rng(f)
+    n, short = 5000, 300
+    B = synth.normal((n, f), f, synth.STREAM_H)
+    met = []
+    for x in longest:
+        deg = rng.permutation(np.concatenate([[x], np.full(159, 64), np.ones(short)])).astype(np.int64)
+        rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+        colidx = np.concatenate([np.sort(rng.choice(n, size=d, replace=False)) for d in deg]).astype(np.int32)
+        val = rng.standard_normal(colidx.size).astype(np.float32)
+        rp, ci, v = dev(rowptr), dev(colidx), dev(val)
+        ws = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+        got = sagnn.spmm_csr_tallskinny(rp, ci, v, dev(B), ws=ws)
+        ref, zabs = oracle.spmm(rowptr, colidx, val, B, want_abs=True)
+        assert_close(got, ref, zabs, RTOL_SPMM, f"f={f}, longest row {x}")
+        info = ws.info()
+        met.append("plain" if info["mode"] == 0 else ("beside" if info["chunk_rows"] else "whole"))
+        if met[-1] == "beside":
+            assert info["chunk_rows"] == short and info["groups"] == (16 if f == 16 else 8)
+            with monkeypatch.context() as apart:
+                apart.setenv("SAGNN_SWEEP_SHORT_ROWS", "-1")
+                ws2 = sagnn.spmm_csr_prepare(rp, ci, v, n, f)
+            assert ws2.info() == info
+            assert torch.equal(sagnn.spmm_csr_tallskinny(rp, ci, v, dev(B), ws=ws2), got)
+    assert met == sorted(met, key=["whole", "beside", "plain"].index) and set(met) == {"whole", "beside", "plain"}, met
+
+
 @pytest.mark.parametrize("f", [64, 128, 192, 256])
 @pytest.mark.parametrize("groups", [1, 2])
 def test_spmm_sweep_short_rows_as_whole_rows(f, groups, monkeypatch):
