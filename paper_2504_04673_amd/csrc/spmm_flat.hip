@@ -499,18 +499,31 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
 #define SAGNN_FLAT_PARTS(LPE_) \
   (buf ? go(spmm_flat_kernel<LPE_, 2, 0, true, true>, LPE_) : go(spmm_flat_kernel<LPE_, 2, 0, true, false>, LPE_))
   // Column parts: each on a share of the XCDs, so that an L2 has to hold that share of the rows of B only, and is asked for
-  // a line of it that many times as often; the sums are the same.  Parts of whole lines; where rows of B are used ten times or
-  // more and B is larger than two L2s, with hubs, whose rows hit in any case, than several.  Four parts without hubs at 256.
-  // us whole, in two and in four parts: random columns, 30 k vertices of 12 f = 128, 256 (31 MB) 29, 57, 25, 53 and -, 45, 20 k of
-  // 45 52, 115, 39, 96, -, 68, 10 k of 90 f = 256 (10 MB) 86, 60, 50, 60 k of 12 (61 MB) 114, 112, 105; communities, 40 k of 24 57,
-  // 125, 48, 110, -, 95; power-law 170 k of 14 f = 128, 192, 256 (174 MB) 122, 193, 256, 111, 166, 231, -, -, 238, 60 k of 30 (61 MB)
-  // 146, 122, 125; not: 10 k of 12 f = 128 (5 MB) 8.7, 8.3, power-law 30 k of 20 f = 128 (15 MB) 29, 32, 10 k of 30 f = 256 25, 28,
-  // random 200 k of 4 f = 128 78, 81; in narrower parts 60 k of 12, f = 64 31, 30, 170 k 64, 76; in parts of 13 lines or less that
-  // begin inside one, 30 k of 12 f = 100 27, 31.
+  // a line of it that many times as often; the sums are the same.  Parts of whole lines, where rows of B are used ten times or
+  // more and B is larger than two L2s, with hubs, whose rows hit in any case, than more than eight.  Four parts without hubs at
+  // 256 columns from 12 MB on.  us in runs whole, in two and in four parts:
+  // - random columns, f = 128 16 k vertices of 11 (8 MB) 12.8, 12.1, 20 k of 40 48, 38, 60 k of 11 (29 MB) 53, 51; f = 256 10 k
+  //   of 16, 40 (10 MB) 22, 45, 18, 33, 17, 31, 12 k of 24 (12 MB) 37, 28, 24, 20 k of 40 103, 85, 62, 50 k of 16 (49 MB) 121, -,
+  //   104.
+  // - communities, which in runs are better off whole (the launch does not know them); chunks in turn, whole, took longer than
+  //   two parts from 8 MB, four from 12 MB on: f = 256 in turn, in two and in four parts 8.2 k of 16 13.6, 13.3, 14.6, 10 k of 40
+  //   30, 29.5, 32.6, 12 k of 40 40, 34, 37, 20 k of 16 40, 26, 28; f = 128 16 k of 24 22.9, 21.3.
+  // - 192 columns in parts of three lines, 10 to 28 MB: random columns, 14 k of 18 (10 MB) 25, 22, 30 k of 18 (22 MB) 58, 53; not
+  //   42 k of 18 (31 MB) 82, 88, 70 k of 14 (51 MB) 115, 118; communities in turn and in two parts 11 k of 24 (8 MB) 21.2, 22.2,
+  //   14 k of 24 25.7, 22.7.
+  // - hubs, power-law, from 34 MB where rows of B are used 24 times or more, from 48 MB where less, at 192 columns from 64 MB under
+  //   16 uses: f = 256 34 k of 24 (33 MB) 62, 63, 39 k of 24, 32 (38 MB) 72, 87, 70, 83, of 11, 14 42, 48, 44, 50, 52 k of 11 (51 MB)
+  //   58, 54; f = 192 48 k of 24, 32 (35 MB) 69, 84, 65, 78, 62 k of 14 (45 MB) 61, 63, 75 k of 11, 14, 17 (55 MB) 64, 72, 86, 65, 72,
+  //   79, 90 k of 11, 14 (66 MB) 76, 89, 75, 84; f = 128 30 k of 14 (15 MB) 25, 27, 62 k of 30 (30 MB) 71, 72, 78 k of 30 (38 MB) 90,
+  //   86, 98 k of 11, 14 (48 MB) 59, 66, 56, 63; 170 k of 14 f = 128, 192, 256 (to 174 MB) 122, 193, 256, 111, 166, 231.
+  // - not: 10 k random columns of 12 f = 128 (5 MB) 8.7, 8.3, 200 k of 4 f = 128 78, 81; in narrower parts 60 k of 12, f = 64 31, 30,
+  //   170 k 64, 76; in parts of 13 lines or less that begin inside one, 30 k of 12 f = 100 27, 31.
   const bool lines = (a.ldb & 31) == 0 && (reinterpret_cast<uintptr_t>(a.B + col0) & 127) == 0;
-  const int64_t floor_mb = !a.hubs ? 8 : (fw == 128 ? 48 : 30);
-  if (fw >= 128 && (fw & 63) == 0 && lines && a.nnz >= 10 * b_rows && b_rows * fw * 4 >= floor_mb << 20) {
-    d.parts = fw == 256 && !a.hubs ? 4 : 2;
+  const int64_t mb = b_rows * fw * 4 >> 20;
+  const int64_t from = !a.hubs ? (fw == 192 ? 10 : 8) : (a.nnz >= 24 * b_rows ? 34 : (fw == 192 && a.nnz < 16 * b_rows ? 64 : 48));
+  const bool large = fw == 192 && !a.hubs && mb >= 28;
+  if (fw >= 128 && (fw & 63) == 0 && lines && a.nnz >= 10 * b_rows && mb >= from && !large) {
+    d.parts = fw == 256 && !a.hubs && mb >= 12 ? 4 : 2;
     d.part_cols = fw / d.parts;
     return d.part_cols <= 64 ? SAGNN_FLAT_PARTS(16) : SAGNN_FLAT_PARTS(32);
   }

@@ -415,10 +415,11 @@ def test_spmm_chunks_at_their_edges(f, target, monkeypatch):
 
 
 @pytest.mark.parametrize("f,n,deg,hubs", [(128, 16_411, 12, 0), (192, 16_411, 17, 0), (256, 9_001, 11, 0), (256, 33_001, 20, 3), (320, 9_001, 13, 0),
-                                          (128, 100_003, 11, 2)])
+                                          (128, 100_003, 11, 2), (256, 13_001, 11, 0), (256, 50_003, 12, 2), (192, 38_503, 30, 2),
+                                          (192, 48_001, 12, 0), (192, 48_001, 12, 2)])
 def test_spmm_chunks_in_column_parts(f, n, deg, hubs, monkeypatch):
-    """Nonzero splitting of operands that are larger than two L2s takes columns in parts: bit for bit what the same workspace
-    gives of 64 columns at a time, which are not cut.  Counts of workgroups that the XCDs of a part do not share evenly,
+    """Nonzero splitting of operands that are larger than two L2s takes columns in two and four parts: bit for bit
+    what the same workspace gives of 64 columns at a time, which are not cut.  Counts of workgroups that the XCDs of a part do not share evenly,
     rows shared by chunks, empty rows, hubs, accumulation, an operand with gaps and one that begins inside a line."""
     monkeypatch.setenv("SAGNN_SWEEP", "0")
     gen = torch.Generator(device="cuda").manual_seed(f + n)
