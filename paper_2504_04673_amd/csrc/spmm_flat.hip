@@ -530,9 +530,10 @@ int flat_launch(const FlatArgs& a, int32_t col0, int32_t fw, hipStream_t s) {
   const bool brief = a.nnz < 64 * a.nchunks;
   // Up to 32 columns four groups of sixteen lanes a wavefront, most of them idle, where groups as narrow as a row would leave
   // SIMDs without a wavefront: with sixteen groups some row ends at nearly every step, and its wavefront stores what the
-  // others wait for.  us, calls one after the other (7.6 is the launch), f = 16, 32: 4 k rows of 8 9.3, 8.0 -> 7.5, 7.6; 20 k of 12
-  // 9.3, 8.4 -> 8.1, 8.1; 5 k power-law rows of 19 15.3, 14.1 -> 12.0, 12.4; beyond the line 20 k of 20 12.0, 12.5 and 13.4, 13.2,
-  // 30 k of 12 9.9, 10.5 and 10.4, 10.6.
+  // others wait for.  us of the kernel alone, f = 16, 32: 1 k rows of 8 8.7, 7.2 -> 5.9, 5.8; 4 k of 8 9.4, 7.5 -> 6.3, 6.1; 15 k of
+  // 16 9.1, 8.5 -> 8.8, 8.8, 20 k of 12 9.8, 8.9 -> 8.8, 8.8 (both 15000 chunks); 5 k power-law rows of 19 11.6, 9.4 -> 8.3, 8.1;
+  // beyond the line 20 k of 20 10.5, 11.4 and 12.9, 12.8, 30 k of 12 (22500 chunks) 10.5, 10.6 and 11.0, 11.4, power-law 20 k of 19
+  // 12.8, 13.1 and 13.8, 13.8.
   const bool few = a.nchunks <= 16384;
   if (fw <= 16 && few) return SAGNN_FLAT(16, 2, 2);
   if (fw <= 32 && few) return SAGNN_FLAT(16, 2, 1);
