@@ -2112,8 +2112,8 @@ def test_fp32_layer_with_values_that_three_terms_do_not_hold(groups, fin, fout, 
 @pytest.mark.parametrize("groups,fin,fout", [("1", 64, 36), ("1", 128, 128), ("1", 256, 132), ("2", 128, 100), ("4", 64, 64)])
 def test_fp32_layer_rounds_a_sum_once_a_term_and_only_reads_a_schedule_without_split_rows(groups, fin, fout, monkeypatch):
     """One value a column of W, small whole numbers in H: A H is exact, and an output is one product of it, which fp32
-    instructions round once.  No row is cut into pieces here, and W is read where it lies: nothing is written to the
-    workspace, so that two layers may share the schedule on streams of their own."""
+    instructions round once.  No row is cut into pieces here, and W is read where it lies: the call writes nothing to the
+    workspace."""
     monkeypatch.setenv("SAGNN_SWEEP", "1")
     monkeypatch.setenv("SAGNN_SWEEP_GROUPS", groups)
     g = synth.sbm_graph(6000, 16, 40, 2, 5)
